@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void k_atom_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ abase, const int32_t *__restrict__ wait,
     const uint8_t *__restrict__ sla_class, unsigned long long *__restrict__ key_hi,
-    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm, int2 *__restrict__ atom_ja)
+    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm)
 {
     const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
     if (j >= n_jobs) return;
@@ -113,20 +113,27 @@ __global__ __launch_bounds__(256) void k_atom_keys(
         key_hi[a0 + a] = ~((tier << 62) | (F * mult));
         key_lo[a0 + a] = ~(mixed ? F : 0ull);
         perm[a0 + a] = uint32_t(a0 + a);
-        atom_ja[a0 + a] = make_int2(j, a);
     }
 }
 
-// rank of every atom, and the (job, atom) that holds each rank
+// The job of every reachable atom (one wave per job): needed only where list keys have no room for it.
+__global__ __launch_bounds__(256) void k_atom_jobs(int n_jobs, const int32_t *__restrict__ abase, uint32_t *__restrict__ atom_job)
+{
+    const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
+    if (j >= n_jobs) return;
+    for (int a = abase[j] + int(threadIdx.x & (kWave - 1)); a < abase[j + 1]; a += kWave) atom_job[a] = uint32_t(j);
+}
+
+// rank of every atom, and (with atom_job) the job that holds each rank
 __global__ void k_rank_from_perm(const int32_t *n_ptr, const uint32_t *__restrict__ perm,
-                                 const int2 *__restrict__ atom_ja, uint32_t *__restrict__ rank,
-                                 int2 *__restrict__ ranked)
+                                 const uint32_t *__restrict__ atom_job, uint32_t *__restrict__ rank,
+                                 uint32_t *__restrict__ ranked_job)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < *n_ptr) {
         const uint32_t a = perm[i];
         rank[a] = uint32_t(i);
-        ranked[i] = atom_ja[a];
+        if (atom_job) ranked_job[i] = atom_job[a];
     }
 }
 
@@ -301,12 +308,13 @@ __device__ __forceinline__ unsigned long long claim_of(int round, int g)
     return (static_cast<unsigned long long>(round) << 32) | (0xffffffffu - uint32_t(g));
 }
 
-// Sorted entries as 16-byte records (job, rank, lo | hi << 8, 0): one load per entry.
+// Sorted entries as records: one load per entry.
+template <typename REC>
 __global__ void k_list_pack(const int32_t *n_ptr, const unsigned long long *__restrict__ ekey, KeyRecords out)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= *n_ptr) return;
-    out.rec[i] = key_record(out, ekey[i]);
+    static_cast<REC *>(out.rec)[i] = key_record<REC>(out, ekey[i]);
 }
 
 // One round for one list block (one wave, one lane per gap position).  First
@@ -314,7 +322,7 @@ __global__ void k_list_pack(const int32_t *n_ptr, const unsigned long long *__re
 // claim word has won (the grant is final), otherwise it lost.  Then, if
 // `propose`, every lane that still needs a job walks on from its own pointer to
 // the first entry that covers it and whose job is not held, and claims it.
-// st = (pointer, candidate job, rank of the candidate atom, flag) with flag 0 = active,
+// st = (pointer, candidate job, unused, flag) with flag 0 = active,
 // 1 = granted, 2 = no candidate left (in memory the flag shares its word with
 // the gap index).
 //
@@ -350,9 +358,9 @@ __device__ __forceinline__ bool held_bit(const uint32_t *s_held, uint32_t job)
 // held from round k+1 on, whoever wins it: the gaps naming it set its bit in the
 // bitmap round k+1 reads, and its winner, when it learns in round k+1 that it
 // won, sets it in the other one, after which both carry it.
-template <bool HELD>
+template <bool HELD, typename REC>
 __device__ __forceinline__ void grant_step(int round, bool propose, int lane, int g, int list_begin, int list_end,
-                                           const uint4 *__restrict__ rec, unsigned long long *claim, int4 &st,
+                                           const REC *__restrict__ rec, unsigned long long *claim, int4 &st,
                                            bool &lost, bool &cand, int *s_n, int *s_job,
                                            unsigned long long *s_word, const uint32_t *s_held,
                                            uint32_t *held_next)
@@ -365,7 +373,7 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
     int e0 = wave_min_dpp(open_now ? st.x : 0x7fffffff);
     bool ahead = e0 != 0x7fffffff;                 // rr holds the chunks from c0 on
     int c0 = ahead ? list_begin + ((e0 - list_begin) & ~(kWave - 1)) : 0;
-    uint4 rr[SW];
+    REC rr[SW];
     if (ahead) {
 #pragma unroll
         for (int k = 0; k < SW; ++k) rr[k] = rec[min(c0 + k * kWave + lane, list_end - 1)];
@@ -381,14 +389,14 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
     int cand_job = -1;
     unsigned long long cand_word = 0;      // the candidate job's claim word as the walk saw it
     const bool walking = st.w == 0 && propose;
-    int e = st.x, found = -1, found_j = -1, found_a = -1;
+    int e = st.x, found = -1, found_j = -1;
     bool by_bitmap = false;                // found with HELD: the claim word is still to fetch
     bool looking = walking && e < list_end;
     // HELD: the chunks behind the ones being looked at are asked for before the look starts (a wave
     // whose lanes' pointers lie thousands of records apart takes window after window, and a lane
     // that finds nothing goes on exactly there), so their trip overlaps the look.  Always issued,
     // at clamped addresses: a load that may be skipped makes every later wait a wait for all.
-    uint4 rn[HELD ? SW : 1];
+    REC rn[HELD ? SW : 1];
     int c_next = -1;
     for (;;) {
         const unsigned long long need = __ballot(looking);
@@ -416,20 +424,20 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
         bool open_job[HELD ? SW : 1];
         if (HELD) {
 #pragma unroll
-            for (int k = 0; k < SW; ++k) open_job[k] = !held_bit(s_held, rr[k].x);
+            for (int k = 0; k < SW; ++k) open_job[k] = !held_bit(s_held, rr[k].job());
         } else {
             // every lane loads (the others word 0, one request per wave) so that the loads of all
             // chunks are issued back to back: a load that may be skipped makes the next one wait for it
             bool worth[SW];
 #pragma unroll
-            for (int k = 0; k < SW; ++k) worth[k] = int(rr[k].z & 255u) <= all_hi && int(rr[k].z >> 8) > all_lo;
+            for (int k = 0; k < SW; ++k) worth[k] = rr[k].lo() <= all_hi && rr[k].hi() > all_lo;
 #pragma unroll
-            for (int k = 0; k < SW; ++k) cw[k] = claim[worth[k] ? rr[k].x : 0u];
+            for (int k = 0; k < SW; ++k) cw[k] = claim[worth[k] ? rr[k].job() : 0u];
 #pragma unroll
             for (int k = 0; k < SW; ++k) cw[k] = worth[k] ? cw[k] : ~0ull;
         }
         const bool here = looking && e < c0 + SW * kWave;
-        int hit = -1, hj = 0, ha = 0;
+        int hit = -1, hj = 0;
         unsigned int hw_lo = 0, hw_hi = 0;
 #pragma unroll
         for (int k = 0; k < SW; ++k) {
@@ -445,29 +453,28 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
             const uint32_t stamp = HELD ? 0u : uint32_t(cw[HELD ? 0 : k] >> 32);
             const bool not_held = HELD ? open_job[HELD ? k : 0] : (stamp == 0 || (stamp >= uint32_t(round) && stamp != 0xffffffffu));
             const bool free_rec = c0 + k * kWave + lane < list_end && not_held &&
-                                  int(rr[k].z & 255u) <= need_hi && int(rr[k].z >> 8) > need_lo;
+                                  rr[k].lo() <= need_hi && rr[k].hi() > need_lo;
             unsigned long long fm = __ballot(free_rec);
             int hk = -1;
             while (fm) {
                 const int t = __ffsll((long long)fm) - 1;
                 fm &= fm - 1;
-                const unsigned int z = __builtin_amdgcn_readlane(rr[k].z, t);
-                const bool h = elig && hk < 0 && c0 + k * kWave + t >= e && lane >= int(z & 255u) &&
-                               lane < int(z >> 8);
+                const REC rt = rr[k].of_lane(t);
+                const bool h = elig && hk < 0 && c0 + k * kWave + t >= e && lane >= rt.lo() && lane < rt.hi();
                 if (__any(h)) {
-                    // record t's job, atom and claim word straight from lane t's registers
-                    const int tj = __builtin_amdgcn_readlane(int(rr[k].x), t), ta = __builtin_amdgcn_readlane(int(rr[k].y), t);
+                    // record t's job and claim word straight from lane t's registers
+                    const int tj = int(rt.job());
                     // (with HELD the claim word of the record a lane settles on is fetched afterwards)
                     const unsigned int t_lo = HELD ? 0u : __builtin_amdgcn_readlane(int(uint32_t(cw[HELD ? 0 : k])), t);
                     const unsigned int t_hi = HELD ? 0u : __builtin_amdgcn_readlane(int(uint32_t(cw[HELD ? 0 : k] >> 32)), t);
-                    if (h) { hk = t; hit = k * kWave + t; hj = tj; ha = ta; hw_lo = t_lo; hw_hi = t_hi; }
+                    if (h) { hk = t; hit = k * kWave + t; hj = tj; hw_lo = t_lo; hw_hi = t_hi; }
                 }
                 if (!__any(elig && hk < 0)) break;
             }
         }
         if (here) {
             if (hit >= 0) {
-                found = c0 + hit; found_j = hj; found_a = ha;
+                found = c0 + hit; found_j = hj;
                 cand_word = (static_cast<unsigned long long>(hw_hi) << 32) | hw_lo;
                 by_bitmap = HELD;
                 looking = false;
@@ -480,7 +487,7 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
     if (HELD && by_bitmap) cand_word = claim[found_j];      // what this round's earlier claims left there
     if (walking) {
         if (found >= 0) {
-            st = make_int4(found + 1, found_j, found_a, 0);
+            st = make_int4(found + 1, found_j, 0, 0);
             cand = true;
             cand_job = found_j;
         } else {
@@ -540,9 +547,9 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
 // The arguments a wave needs first come first: the library is built so that
 // the leading 16 dwords of a kernel's arguments are in scalar registers when
 // the wave starts, and the state load does not wait for an argument load.
-template <bool HELD>
+template <bool HELD, typename REC>
 __global__ __launch_bounds__(kRoundBlock) void k_grant_round(
-    int4 *state, const int32_t *__restrict__ list_off, const uint4 *__restrict__ rec, unsigned long long *claim,
+    int4 *state, const int32_t *__restrict__ list_off, const REC *__restrict__ rec, unsigned long long *claim,
     int round, int propose, int n_lb, int held_words, uint32_t *held, const int32_t *__restrict__ lb_begin,
     const int32_t *__restrict__ lb_end, const int32_t *__restrict__ gap_order, int32_t *cnt_lost, int32_t *cnt_cand)
 {
@@ -583,7 +590,7 @@ __global__ __launch_bounds__(kRoundBlock) void k_grant_round(
         int4 st = make_int4(raw.x, raw.y, raw.z, raw.w & 3);
         const int4 before = st;
         bool lost, cand;
-        grant_step<HELD>(round, propose != 0, lane, g, list_begin, list_end, rec, claim, st, lost, cand, &s_n, s_job,
+        grant_step<HELD, REC>(round, propose != 0, lane, g, list_begin, list_end, rec, claim, st, lost, cand, &s_n, s_job,
                          s_word, s_held, held_next);
         if (st.x != before.x || st.w != before.w || round == 1) state[slot] = make_int4(st.x, st.y, st.z, st.w | (g << 2));
         if (__ballot(lost) && lane == 0) cnt_lost[round - 1] = 1;
@@ -657,11 +664,12 @@ __global__ __launch_bounds__(1024) void k_count_open(int lb_cap, const int32_t *
 }
 
 // After the last round: the grants themselves.  A granted position still holds
-// its winning job and the rank of the winning atom in its state; `ranked` turns
-// the rank into the atom.
+// its winning job in its state; which of the job's atoms it got is what the fit
+// says for that pair, min(#{D <= W}, #{P <= C}) - 1.
 __global__ void k_grant_finish(int lb_cap, PolicyDev pol, const int32_t *__restrict__ plan,
-                               const int4 *__restrict__ state, const int2 *__restrict__ ranked,
-                               const int64_t *__restrict__ seg_off,
+                               const int4 *__restrict__ state, const int32_t *__restrict__ lb_begin,
+                               const int32_t *__restrict__ gap_w, const int32_t *__restrict__ gap_c,
+                               const int64_t *__restrict__ seg_off, const int32_t *__restrict__ n_atoms,
                                const int2 *__restrict__ atom_dp, const int2 *__restrict__ atom_db,
                                const long long *__restrict__ atom_area,
                                const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
@@ -673,8 +681,16 @@ __global__ void k_grant_finish(int lb_cap, PolicyDev pol, const int32_t *__restr
     const int4 st = state[slot];
     if ((st.w & 3) != 1) return;
     const int g = st.w >> 2, j = st.y;
-    const int atom = ranked[st.z].y;
+    const int pos = lb_begin[slot / kWave] + (slot & (kWave - 1));
+    const int w = gap_w[pos], c = gap_c[pos];
     const int64_t base = seg_off[j];
+    int atom = 0, hi = n_atoms[j];              // atoms that fit (a prefix: durations and peaks ascend)
+    while (atom < hi) {
+        const int mid = (atom + hi) >> 1;
+        const int2 v = atom_dp[base + mid];
+        if (v.x <= w && v.y <= c) atom = mid + 1; else hi = mid;
+    }
+    --atom;                                     // the job was a candidate of this gap: at least one fits
     const int2 v = atom_dp[base + atom];
     unsigned long long mult, tier;
     job_policy(pol, wait, sla_class, j, mult, tier);

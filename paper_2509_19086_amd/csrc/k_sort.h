@@ -3,6 +3,8 @@
 // kernels each; sizes here are tens of millions of items at most.
 #pragma once
 
+#include <type_traits>
+
 #include "sja_internal.h"
 
 namespace sja {
@@ -145,27 +147,53 @@ __global__ __launch_bounds__(256) void k_keys_hist(const unsigned long long *__r
     hist[int64_t(tid) * n_tiles + blockIdx.x] = s_h[tid];
 }
 
-// What the last pass over list entries writes instead of the keys themselves: 16-byte records
-// (job, rank, lo | hi << 8, 0); rank is the key's rank field, lo (6 bits) and hi (7 bits) its
-// lowest lane_bits bits, and the job either rides in the key above job_shift (no pass sorts by
-// those bits) or, with job_shift < 0, is looked up through the rank (one gather per key).
+// A list record: a job and the lane range [lo, hi) of its list block that one of the job's atoms
+// serves.  Four bytes while job ids fit 19 bits (the rounds are bound by the records they sweep:
+// 16-byte records with the atom's rank in them cost the early rounds four times the bytes), eight
+// beyond.  Which atom it is need not be kept: job and gap determine it.
+constexpr int kRec32JobBits = 19;
+struct Rec32 {
+    uint32_t v;
+    __device__ static Rec32 make(uint32_t job, uint32_t lo, uint32_t hi) { return {job | (lo << kRec32JobBits) | (hi << (kRec32JobBits + 6))}; }
+    __device__ uint32_t job() const { return v & ((1u << kRec32JobBits) - 1u); }
+    __device__ int lo() const { return int((v >> kRec32JobBits) & 63u); }
+    __device__ int hi() const { return int(v >> (kRec32JobBits + 6)); }
+    __device__ Rec32 of_lane(int t) const { return {uint32_t(__builtin_amdgcn_readlane(int(v), t))}; }
+};
+struct Rec64 {
+    uint32_t j, z;
+    __device__ static Rec64 make(uint32_t job, uint32_t lo, uint32_t hi) { return {job, lo | (hi << 8)}; }
+    __device__ uint32_t job() const { return j; }
+    __device__ int lo() const { return int(z & 255u); }
+    __device__ int hi() const { return int(z >> 8); }
+    __device__ Rec64 of_lane(int t) const
+    {
+        return {uint32_t(__builtin_amdgcn_readlane(int(j), t)), uint32_t(__builtin_amdgcn_readlane(int(z), t))};
+    }
+};
+struct NoRec {};
+
+// What the last pass over list entries writes instead of the keys themselves: their records.  lo (6
+// bits) and hi (7 bits) are the key's lowest lane_bits bits, and the job either rides in the key above
+// job_shift (no pass sorts by those bits) or, with job_shift < 0, is looked up through the key's rank
+// field (one gather per key).
 struct KeyRecords {
-    const int2 *ranked;
-    uint4 *rec;
+    const uint32_t *ranked_job;
+    void *rec;
     int lane_bits, rank_bits, job_shift;
 };
 
-__device__ __forceinline__ uint4 key_record(const KeyRecords &out, unsigned long long v)
+template <typename REC>
+__device__ __forceinline__ REC key_record(const KeyRecords &out, unsigned long long v)
 {
     const uint32_t rank = uint32_t((v >> out.lane_bits) & ((1ull << out.rank_bits) - 1ull));
-    const uint32_t job = out.job_shift >= 0 ? uint32_t(v >> out.job_shift) : uint32_t(out.ranked[rank].x);
-    const unsigned int lo = unsigned(v) & 63u, hi = unsigned(v >> 6) & 127u;
-    return make_uint4(job, rank, lo | (hi << 8), 0u);
+    const uint32_t job = out.job_shift >= 0 ? uint32_t(v >> out.job_shift) : out.ranked_job[rank];
+    return REC::make(job, unsigned(v) & 63u, unsigned(v >> 6) & 127u);
 }
 
-// PAY: every key carries a 32-bit payload that moves with it.  REC: the sorted keys are not
-// written at all, their records are (the pass that finishes the order of the list entries).
-template <bool PAY, bool REC = false>
+// PAY: every key carries a 32-bit payload that moves with it.  REC other than NoRec: the sorted keys
+// are not written at all, their records are (the pass that finishes the order of the list entries).
+template <bool PAY, typename REC = NoRec>
 __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *__restrict__ src,
                                                       unsigned long long *__restrict__ dst,
                                                       const uint32_t *__restrict__ pay_src,
@@ -244,8 +272,8 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
         const unsigned long long v = s_key[k];
         const unsigned d = unsigned(v >> shift) & digit_mask;
         const int64_t o = int64_t(s_goff[d]) + (k - s_start[d]);
-        if (REC) {
-            out.rec[o] = key_record(out, v);
+        if constexpr (!std::is_same<REC, NoRec>::value) {
+            static_cast<REC *>(out.rec)[o] = key_record<REC>(out, v);
         } else {
             dst[o] = v;
         }

@@ -164,7 +164,7 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
 int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host,
                     unsigned byte_mask, int bit_offset, bool &flip, unsigned long long *const buf[2],
                     uint32_t *const pay[2], const KeyRecords *records = nullptr, bool *records_written = nullptr,
-                    int sorted_bits = 64)
+                    int sorted_bits = 64, bool wide_records = false)
 {
     // sorted_bits: bits above bit_offset + sorted_bits are not part of the order (a rider) and are masked
     // out of the last digit
@@ -189,15 +189,16 @@ int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t
         SJA_HIP(hipGetLastError(), "k_keys_hist launch");
         SJA_HIP(enqueue_scan(st, hist, int64_t(256) * n_tiles, tmp, nullptr), "radix scan launch");
         if (pay)
-            hipLaunchKernelGGL((k_keys_scatter<true, false>), dim3(n_tiles), dim3(256), 0, st, src, dst, pay[flip ? 1 : 0],
+            hipLaunchKernelGGL((k_keys_scatter<true, NoRec>), dim3(n_tiles), dim3(256), 0, st, src, dst, pay[flip ? 1 : 0],
                                pay[flip ? 0 : 1], n_dev, shift, digit_mask, hist, n_tiles, KeyRecords{});
         else if (records && b == last_byte) {
-            hipLaunchKernelGGL((k_keys_scatter<false, true>), dim3(n_tiles), dim3(256), 0, st, src, dst,
+            auto kern = wide_records ? k_keys_scatter<false, Rec64> : k_keys_scatter<false, Rec32>;
+            hipLaunchKernelGGL(kern, dim3(n_tiles), dim3(256), 0, st, src, dst,
                                static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr), n_dev, shift,
                                digit_mask, hist, n_tiles, *records);
             if (records_written) *records_written = true;
         } else
-            hipLaunchKernelGGL((k_keys_scatter<false, false>), dim3(n_tiles), dim3(256), 0, st, src, dst,
+            hipLaunchKernelGGL((k_keys_scatter<false, NoRec>), dim3(n_tiles), dim3(256), 0, st, src, dst,
                                static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr), n_dev, shift,
                                digit_mask, hist, n_tiles, KeyRecords{});
         SJA_HIP(hipGetLastError(), "k_keys_scatter launch");
@@ -244,7 +245,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     uint32_t *perm[2] = {ws_ptr<uint32_t>(ctx, L.g_perm0), ws_ptr<uint32_t>(ctx, L.g_perm1)};
     uint32_t *rank = ws_ptr<uint32_t>(ctx, L.g_rank);
     unsigned long long *ekey[2] = {ws_ptr<unsigned long long>(ctx, L.g_ekey0), ws_ptr<unsigned long long>(ctx, L.g_ekey1)};
-    int2 *atom_ja = ws_ptr<int2>(ctx, L.g_atom_ja), *ranked = ws_ptr<int2>(ctx, L.g_ranked);
+    uint32_t *atom_job = ws_ptr<uint32_t>(ctx, L.g_atom_job), *ranked_job = ws_ptr<uint32_t>(ctx, L.g_ranked_job);
 
     // 1. list blocks; reachable atoms per job -> compact atom ids
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, st, counters, int64_t(16), 0);
@@ -268,7 +269,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     // policy keys of the atoms and the bytes in which they differ (both only need the device-side counts)
     hipLaunchKernelGGL(k_atom_keys, dim3((J + 3) / 4), dim3(256), 0, st, J, pol, ctx->seg_off, atom_dp,
                        atom_area_of(ctx, L), abase, wait,
-                       sla_class, key_hi, key_lo, perm[0], atom_ja);
+                       sla_class, key_hi, key_lo, perm[0]);
     SJA_HIP(hipGetLastError(), "k_atom_keys launch");
     hipLaunchKernelGGL(k_key_bits, dim3(256), dim3(256), 0, st, counters + 2, key_hi, key_lo,
                        reinterpret_cast<unsigned long long *>(counters + 4));
@@ -280,6 +281,14 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     const int64_t n_atoms = host_counters[2];
     const int n_subs = host_plan[kPlanListBlocks];          // list blocks from here on
     if (!host_plan[kPlanTabled] || n_subs > lb_bound || n_atoms > L.atom_cap) return SJA_OK;
+
+    const int rank_bits = bits_for(n_atoms > 1 ? n_atoms : 2);
+    const int sub_bits = bits_for(n_subs > 1 ? n_subs : 2);
+    // the job of an entry rides in its key above the sorted bits when the key has room for it:
+    // then the pass that writes the records need not look it up through the rank
+    const int job_bits = bits_for(J > 1 ? J : 2);
+    const bool ride = ctx->resolve_mode != SJA_RESOLVE_LISTS_LOOKUP && kEntryLaneBits + rank_bits + sub_bits + job_bits <= 64;
+    const int job_shift = ride ? kEntryLaneBits + rank_bits + sub_bits : -1;
 
     // 2. rank the atoms by policy key (descending key, ascending job id): stable passes over
     //    (inverted key, atom id) pairs, the secondary key first; the entry buffers serve as the
@@ -308,19 +317,16 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         SJA_HIP(hipGetLastError(), "k_gather_keys launch");
         rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), 0, flip, kh, perm);
         if (rc != SJA_OK) return rc;
+        if (!ride) {
+            hipLaunchKernelGGL(k_atom_jobs, dim3((J + 3) / 4), dim3(256), 0, st, J, abase, atom_job);
+            SJA_HIP(hipGetLastError(), "k_atom_jobs launch");
+        }
         hipLaunchKernelGGL(k_rank_from_perm, dim3(unsigned((n_atoms + 255) / 256)), dim3(256), 0, st, counters + 2,
-                           perm[flip ? 1 : 0], atom_ja, rank, ranked);
+                           perm[flip ? 1 : 0], ride ? static_cast<const uint32_t *>(nullptr) : atom_job, rank, ranked_job);
         SJA_HIP(hipGetLastError(), "k_rank_from_perm launch");
     }
 
     // 3. list entries (one pass, counted as they are written), then sorted by (block, rank)
-    const int rank_bits = bits_for(n_atoms > 1 ? n_atoms : 2);
-    const int sub_bits = bits_for(n_subs > 1 ? n_subs : 2);
-    // the job of an entry rides in its key above the sorted bits when the key has room for it:
-    // then the pass that writes the records need not look it up through the rank
-    const int job_bits = bits_for(J > 1 ? J : 2);
-    const bool ride = ctx->resolve_mode != SJA_RESOLVE_LISTS_LOOKUP && kEntryLaneBits + rank_bits + sub_bits + job_bits <= 64;
-    const int job_shift = ride ? kEntryLaneBits + rank_bits + sub_bits : -1;
     const dim3 emit_grid((J + 256 * kEmitTiles - 1) / (256 * kEmitTiles), lb_bound);
     hipLaunchKernelGGL(k_list_emit, emit_grid, dim3(256), 0, st, J, rank_bits, job_shift, lb_bound, (long long)L.entry_cap, plan,
                        lb_begin, lb_end, lb_sub, sub_class, gap_w, ctx->seg_off, atom_dp, sub_tab, ncap_tab, abase, rank,
@@ -332,18 +338,20 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     if (n_entries > L.entry_cap || n_entries >= (1ll << 31)) return SJA_OK;
     SJA_HIP(enqueue_scan(st, list_off, int64_t(lb_bound) + 2, tmp, nullptr), "list offset scan launch");
     bool eflip = false, packed = false;
-    uint4 *rec = ws_ptr<uint4>(ctx, L.g_rec);
-    const KeyRecords records{ranked, rec, kEntryLaneBits, rank_bits, job_shift};
+    void *rec = ws_ptr<void>(ctx, L.g_rec);
+    const KeyRecords records{ranked_job, rec, kEntryLaneBits, rank_bits, job_shift};
+    const bool wide_records = int64_t(J) > (int64_t(1) << kRec32JobBits);
     if (n_entries > 0) {
-        // the pass that finishes the order writes the 16-byte records straight away
+        // the pass that finishes the order writes the records straight away
         const int key_bytes = (rank_bits + sub_bits + 7) / 8;
         int rc = radix_sort_keys(ctx, st, L, counters, n_entries, (1u << key_bytes) - 1u, kEntryLaneBits, eflip, ekey,
-                                 nullptr, &records, &packed, rank_bits + sub_bits);
+                                 nullptr, &records, &packed, rank_bits + sub_bits, wide_records);
         if (rc != SJA_OK) return rc;
     }
     const int fb = eflip ? 1 : 0;
     if (n_entries > 0 && !packed) {
-        hipLaunchKernelGGL(k_list_pack, dim3(unsigned((n_entries + 255) / 256)), dim3(256), 0, st, counters, ekey[fb],
+        auto kern = wide_records ? k_list_pack<Rec64> : k_list_pack<Rec32>;
+        hipLaunchKernelGGL(kern, dim3(unsigned((n_entries + 255) / 256)), dim3(256), 0, st, counters, ekey[fb],
                            records);
         SJA_HIP(hipGetLastError(), "k_list_pack launch");
     }
@@ -370,12 +378,16 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         SJA_HIP(hipGetLastError(), "k_fill_i32 launch");
     }
     auto launch_round = [&](int64_t k, int propose) {
-        if (use_held && k <= kHeldRounds)
-            hipLaunchKernelGGL(k_grant_round<true>, dim3(round_grid), dim3(kRoundBlock), 0, st, state, list_off, rec, claim, int(k), propose, n_subs,
-                               held_words, held, lb_begin, lb_end, gap_order, cnt_lost, cnt_cand);
+        const bool with_bitmap = use_held && k <= kHeldRounds;
+        auto go = [&](auto kern, auto *records) {
+            hipLaunchKernelGGL(kern, dim3(round_grid), dim3(kRoundBlock), 0, st, state, list_off, records, claim, int(k), propose, n_subs,
+                               with_bitmap ? held_words : 0, with_bitmap ? held : static_cast<uint32_t *>(nullptr), lb_begin,
+                               lb_end, gap_order, cnt_lost, cnt_cand);
+        };
+        if (wide_records)
+            go(with_bitmap ? k_grant_round<true, Rec64> : k_grant_round<false, Rec64>, static_cast<const Rec64 *>(rec));
         else
-            hipLaunchKernelGGL(k_grant_round<false>, dim3(round_grid), dim3(kRoundBlock), 0, st, state, list_off, rec, claim, int(k), propose, n_subs,
-                               0, static_cast<uint32_t *>(nullptr), lb_begin, lb_end, gap_order, cnt_lost, cnt_cand);
+            go(with_bitmap ? k_grant_round<true, Rec32> : k_grant_round<false, Rec32>, static_cast<const Rec32 *>(rec));
         return hipGetLastError();
     };
     std::vector<int32_t> h_lost, h_cand;
@@ -410,9 +422,8 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         }
     }
     hipLaunchKernelGGL(k_grant_finish, dim3(unsigned((int64_t(n_subs) * kWave + 255) / 256)), dim3(256), 0, st, lb_bound, pol,
-                       plan, state, ranked, ctx->seg_off, atom_dp, atom_db, atom_area_of(ctx, L), wait, sla_class, grant_job,
-                       grant_cut, grant_score,
-                       job_gap);
+                       plan, state, lb_begin, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), ctx->seg_off, ws_ptr<int32_t>(ctx, L.n_atoms),
+                       atom_dp, atom_db, atom_area_of(ctx, L), wait, sla_class, grant_job, grant_cut, grant_score, job_gap);
     SJA_HIP(hipGetLastError(), "k_grant_finish launch");
     *done = true;
     return SJA_OK;

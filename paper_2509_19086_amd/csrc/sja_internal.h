@@ -70,8 +70,8 @@ struct Layout {
     size_t g_perm0, g_perm1, g_rank;       // [atom_cap] uint32
     size_t g_hist;                         // [256 * tiles] int32, tiles of the larger of the two sorts
     size_t g_ekey0, g_ekey1;               // [entry_cap] uint64: list entries (block : rank : lane range)
-    size_t g_rec;                          // [entry_cap] uint4: the sorted lists as records
-    size_t g_atom_ja, g_ranked;            // [atom_cap] int2: (job, atom) by atom id and by rank
+    size_t g_rec;                          // [entry_cap] Rec32 or Rec64: the sorted lists as records
+    size_t g_atom_job, g_ranked_job;       // [atom_cap] uint32: job by atom id and by rank (keys without room for it)
     size_t lb_begin, lb_end, lb_sub;       // [list_bound] int32: grant-list blocks (pieces of sub-blocks)
     size_t lb_off;                         // [sub_bound+2] int32: first list block of a sub-block
     size_t g_list_off;                     // [list_bound+2] int32
@@ -180,9 +180,9 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     L.g_hist = take(hist_ints * 4);
     L.g_ekey0 = take(ec * 8);
     L.g_ekey1 = take(ec * 8);
-    L.g_rec = take(ec * 16);
-    L.g_atom_ja = take(ac * 8);
-    L.g_ranked = take(ac * 8);
+    L.g_rec = take(ec * 8);
+    L.g_atom_job = take(ac * 4);
+    L.g_ranked_job = take(ac * 4);
     L.lb_begin = take(lb * 4);
     L.lb_end = take(lb * 4);
     L.lb_sub = take(lb * 4);

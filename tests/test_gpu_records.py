@@ -1,0 +1,46 @@
+"""Grant-list records: four bytes while job ids fit 19 bits, eight beyond.  Both forms, on both
+sides of the line, with the job in the list key and looked up through the rank, against the oracle."""
+import numpy as np
+import pytest
+
+from gen import make_workload
+from test_gpu_parity import full_tick_check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def engine():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2509_19086_amd as P
+    return P.Engine(0)
+
+
+def _short_jobs(n_jobs, n_gaps, seed):
+    """Jobs of one to three segments, so that half a million of them are quick; the best jobs sit at
+    both ends of the id range, where a truncated id would show."""
+    wl = make_workload("small", seed, n_gaps=n_gaps, n_jobs=8)
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(1, 4, size=n_jobs)
+    wl.n_jobs = n_jobs
+    wl.seg_off = np.zeros(n_jobs + 1, dtype=np.int64)
+    np.cumsum(lens, out=wl.seg_off[1:])
+    S = int(wl.seg_off[-1])
+    wl.dur = rng.integers(1, 700, size=S).astype(np.int32)
+    wl.mem = rng.integers(256, 41000, size=S).astype(np.int32)
+    wl.safe = (rng.random(S) < 0.5).astype(np.uint8)
+    wl.progress = (rng.random(n_jobs) * lens).astype(np.int32)
+    wl.wait = rng.integers(0, 1000, size=n_jobs).astype(np.int32)
+    wl.wait[:40] += 900000
+    wl.wait[-40:] += 900000
+    wl.sla_class = rng.integers(0, 3, size=n_jobs).astype(np.uint8)
+    return wl
+
+
+@pytest.mark.parametrize("n_jobs", [(1 << 19) - 1, 1 << 19, (1 << 19) + 65])
+def test_both_record_sizes(engine, oracle, n_jobs):
+    wl = _short_jobs(n_jobs, 90, n_jobs & 7)
+    t = full_tick_check(engine, oracle, wl, policies=[1], resolve_modes=(0, 2))
+    jobs = t.grant_job.cpu().numpy()
+    assert (jobs > n_jobs - 50).any() and (jobs < 50).any()
