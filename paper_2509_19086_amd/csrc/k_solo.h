@@ -1,0 +1,437 @@
+// K4, the long tail of the conflict rounds in one thread block.
+//
+// After the first rounds nearly all open gaps want the same job: at Stress
+// (32768 gaps x 65536 jobs) all but the first 300 of 9400 rounds name one to
+// three jobs, each by thousands of gaps.  Such a round has next to no work in
+// it, and a launch per round paid 4.4 us for the memory trips of its chain
+// (state, records, claim words) and 1.3 us more until the next launch.
+// Here ONE block runs round after round: a thread per list block, which keeps
+// its open lanes, its place in the list and its lowest open gap in registers;
+// the held jobs (a bitmap) and the round's claims (a small hash table) live in
+// LDS, and a round has a single barrier.
+//
+// What a thread relies on: along the positions of a list block a job's key
+// never falls (F grows with the cut; the host sees to it where the hysteresis
+// rule could undo that), so the job of the highest open lane is the job of every open
+// lane its record covers, and of no other records need be looked at for them.
+// Lanes below that record form further pieces with jobs of their own; those
+// (and a thread that has many records to pass) are served by the whole wave,
+// 64 records a trip.
+//
+// When the pieces get many (the first rounds of a large batch, or when a
+// service class runs out and the next one's jobs begin) the block stops and
+// leaves the gaps' state as the round kernel expects it.
+#pragma once
+
+#include "k_grant.h"
+
+namespace sja {
+
+constexpr int kSoloMaxWaves = 16;
+constexpr int kSoloMinWaves = 4;        // one per SIMD: list blocks in pieces are served by several waves side by side
+constexpr int kSoloMaxBlocks = kSoloMaxWaves * kWave;
+constexpr int kSoloFirstRounds = 4;     // launched rounds before the block first takes over
+constexpr int kSoloTable = 2048;        // claim words: one per job named in a round (power of two)
+constexpr int kSoloFewLooking = 4;      // lanes still looking that the wave serves together
+constexpr int kSoloEasyPieces = 8;      // pieces per wave and round that cost no more than a launched round
+constexpr int kSoloPatience = 96;       // pieces beyond that, summed up, after which the block stops
+enum { kSoloDone = 0, kSoloRounds = 1, kSoloStable = 2 };
+
+// A claim: round (24 bits) : job (20) : inverted gap (20).  A word of an earlier round is told from a
+// current one by its stamp, so nothing is ever cleared.
+__device__ __forceinline__ unsigned long long solo_word(int round, int job, int g)
+{
+    return (static_cast<unsigned long long>(uint32_t(round)) << 40) | (static_cast<unsigned long long>(uint32_t(job)) << 20) |
+           (0xfffffu - uint32_t(g));
+}
+
+// Enters a claim in the table.  The larger of two words keeps a slot and the other one moves on, so all
+// claims for a job end in one slot, the first from the job's own whose word is not larger, with the lowest gap.
+__device__ __forceinline__ bool solo_enter(unsigned long long *tab, unsigned long long v)
+{
+    int h = int(v >> 20) & (kSoloTable - 1);
+#pragma unroll 1
+    for (int tries = 0; tries < kSoloTable; ++tries) {
+        const unsigned long long old = atomicMax(&tab[h], v);
+        if (__builtin_expect((old >> 40) != (v >> 40) || ((old ^ v) >> 20) == 0, 1)) return true;
+        v = min(old, v);
+        h = (h + 1) & (kSoloTable - 1);
+    }
+    return false;           // no slot left: the round is given up
+}
+
+// Whether the claim `v` is the one that stands for its job, once all claims of the round are in.
+__device__ __forceinline__ bool solo_wins(const unsigned long long *tab, unsigned long long v)
+{
+    int h = int(v >> 20) & (kSoloTable - 1);
+    unsigned long long x = tab[h];
+#pragma unroll 1
+    for (int tries = 1; __builtin_expect(((x ^ v) >> 20) != 0, 0) && tries < kSoloTable; ++tries) {
+        h = (h + 1) & (kSoloTable - 1);
+        x = tab[h];
+    }
+    return x == v;
+}
+
+__device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long v, int l)
+{
+    return (static_cast<unsigned long long>(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v >> 32)), l))) << 32) |
+           uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), l));
+}
+
+// Rounds after + 1 .. at most cap, by blockDim.x / kWave waves (n_lb <= blockDim.x).  `after` rounds have
+// been launched; cnt_lost / cnt_cand tell of those from first_check on whether one of them was already the
+// last.  out: whether the process has ended (1) or is to be taken up again by launched rounds (0), the
+// rounds done, whether they are stable.
+//
+// A wave has its SIMD to itself (or shares it with one or two others), so a round takes as long as its
+// instructions: what a thread tests every round (eight records' held bits) is prepared when the records
+// arrive or its highest open lane changes.  The held jobs are two bitmaps: a round reads one and marks the
+// jobs it names in the other, and in the first one round later.
+__global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
+    int4 *state, const int32_t *__restrict__ list_off, const Rec32 *__restrict__ rec, unsigned long long *claim, int after,
+    int first_check, int cap, int n_lb, int held_words, uint32_t *held, const int32_t *__restrict__ cnt_lost,
+    const int32_t *__restrict__ cnt_cand, int32_t *out)
+{
+    __shared__ uint32_t s_held[2][kHeldMaxWords + 4];           // the word behind the last job's is all ones: nobody's job
+    __shared__ unsigned long long s_tab[kSoloTable];
+    __shared__ unsigned long long s_piece[kSoloMaxWaves][kWave];        // a wave's claims for pieces of list blocks
+    __shared__ int s_at[kSoloMaxWaves][kWave];                  // whose they are: thread << 6 | lane
+    __shared__ unsigned long long s_log[kSoloMaxWaves][kWave];  // grants not yet written to the state: slot << 32 | job
+    // by round stamp: somebody claims, a wave gives up, (round << 8 | most pieces of a wave), open lanes found nothing more
+    __shared__ int4 s_ctl[2];
+    __shared__ int s_flag;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int threads = blockDim.x, waves = threads / kWave;
+    // neighbouring list blocks split in the same rounds: they go to different waves
+    const int u = lane * waves + wave;
+    const uint32_t nobody = uint32_t(held_words) * 32u;
+
+    for (int i = tid; i < held_words; i += threads) s_held[0][i] = s_held[1][i] = held[size_t((after + 1) & 1) * held_words + i];
+    for (int i = tid; i < kSoloTable; i += threads) s_tab[i] = 0;
+    if (tid < 2) { s_ctl[tid] = make_int4(0, 0, 0, 0); s_held[tid][held_words] = ~0u; }
+    if (tid == 0) s_flag = 0;
+    __syncthreads();
+
+    // the outcome of round `after`, the open lanes, and the lanes of every list block by gap index
+    unsigned long long open = 0;        // open lanes of this thread's list block
+    int e = 0, list_end = 0;            // its place in the list: what covers its highest open lane before it is held
+    {
+        bool any_lost = false;
+        for (int i = 0; i * waves + wave < n_lb; ++i) {
+            const int slot0 = (i * waves + wave) * kWave;
+            int4 raw = state[slot0 + lane];
+            const int g = raw.w >> 2;
+            if ((raw.w & 3) == 0 && raw.y >= 0) {
+                if (claim[raw.y] == claim_of(after, g)) {
+                    state[slot0 + lane].w = raw.w |= 1;
+                } else {
+                    state[slot0 + lane].y = -1;
+                    any_lost = true;
+                }
+            }
+            const unsigned long long on = __ballot((raw.w & 3) == 0);
+            int place = 0;
+            for (unsigned long long m = on; m; m &= m - 1)
+                place += __builtin_amdgcn_readlane(g, __ffsll((long long)m) - 1) < g;
+            if ((on >> lane) & 1ull) state[slot0 + place].z = (g << 6) | lane;
+            const int e_top = __builtin_amdgcn_readlane(raw.x, on ? 63 - __clzll((long long)on) : 0);
+            if (lane == i) { open = on; e = e_top; }
+        }
+        if (any_lost) s_flag = 1;
+        if (u < n_lb) list_end = list_off[u + 1];
+        if (e >= list_end) open = 0;
+        __threadfence_block();
+    }
+    int top = 0, bottom = 0;            // its highest and lowest open lane
+    int order = 0, next_low = 0, low_gap = -1, low_lane = 0;    // its lowest open gap, and the entry after it
+    uint32_t w[8];                      // its records from w0 on (0 where there is none)
+    uint32_t job_of[8];                 // and their jobs, `nobody` where the highest open lane is not covered
+    int w0 = 0;
+    uint4 behind = make_uint4(0, 0, 0, 0);      // the four records after them, asked for ahead
+    const uint4 *rec4 = reinterpret_cast<const uint4 *>(rec);
+    auto cover = [&](int q) {
+        const Rec32 r{w[q]};
+        job_of[q] = uint32_t(top - r.lo()) < uint32_t(r.hi() - r.lo()) ? r.job() : nobody;
+    };
+    auto ends = [&]() {
+        top = 63 - __clzll((long long)open);
+        bottom = __ffsll((long long)open) - 1;
+    };
+    // the half window from record i on; records before `from` and behind the list are none
+    auto take = [&](int half, const uint4 &r, int i, int from) {
+        w[4 * half] = r.x; w[4 * half + 1] = r.y; w[4 * half + 2] = r.z; w[4 * half + 3] = r.w;
+        if (__builtin_expect(i < from || i + 4 > list_end, 0)) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (i + q < from || i + q >= list_end) w[4 * half + q] = 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cover(4 * half + q);
+    };
+    auto ask = [&](int i) { return rec4[min(i, (list_end - 1) & ~3) >> 2]; };
+    auto window = [&]() {
+        w0 = e & ~3;
+        const uint4 r = ask(w0), r2 = ask(w0 + 4);
+        behind = ask(w0 + 8);
+        take(0, r, w0, e);
+        take(1, r2, w0 + 4, e);
+    };
+    auto closed = [&]() {       // lanes were closed: the ends, what covers the highest, the lowest gap
+        const int was = top;
+        if (!open) { low_gap = -1; return; }
+        ends();
+        if (top != was) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) cover(q);
+        }
+        while (!((open >> low_lane) & 1ull) && order <= kWave) {
+            low_gap = next_low >> 6; low_lane = next_low & 63;
+            ++order;
+            next_low = state[u * kWave + min(order, kWave - 1)].z;
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { w[q] = 0; job_of[q] = nobody; }
+    if (open) {
+        const int first = state[u * kWave].z;
+        low_gap = first >> 6; low_lane = first & 63;
+        order = 1;
+        next_low = state[u * kWave + 1].z;
+        ends();
+        window();
+    }
+    __syncthreads();
+    const bool lost_before = s_flag != 0;
+    __syncthreads();
+    if (tid == 0) {
+        // the process may have ended within the launched rounds
+        s_flag = 0;
+        for (int r = first_check; r <= after; ++r)
+            if (cnt_cand[r] == 0 || (r < after ? cnt_lost[r] != 0 : lost_before) == false) {
+                out[kSoloDone] = 1; out[kSoloRounds] = r; out[kSoloStable] = 1;
+                s_flag = 1;
+                break;
+            }
+    }
+    __syncthreads();
+    if (s_flag) return;
+
+    int n_log = 0;
+    auto flush = [&]() {
+        if (lane < n_log) {
+            const unsigned long long x = s_log[wave][lane];
+            const int slot = int(x >> 32);
+            state[slot].y = int(uint32_t(x));
+            state[slot].w |= 1;
+        }
+        n_log = 0;
+    };
+    int strain = 0;             // pieces beyond what is easy, summed up
+    int done = after;           // rounds finished
+    int ended = 0, stable = 0;
+    uint32_t marked = nobody, marked_piece = nobody;    // the jobs this lane marked a round ago
+    for (int round = after + 1;; ++round) {
+        const int half = round & 1;
+        const uint32_t *const is_held = s_held[half];
+        uint32_t *const mark = s_held[half ^ 1];
+        auto set_mark = [&](uint32_t j) { atomicOr(&mark[j >> 5], 1u << (j & 31u)); };
+        bool looking = open != 0, found = false, have = false;
+        const bool any_open = __ballot(looking) != 0;
+        uint32_t job = 0;
+        int lo = 0;
+        // the job of the highest open lane: eight records a step
+        for (int step = 0;; ++step) {
+            uint32_t b[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) b[q] = is_held[job_of[q] >> 5];
+            uint32_t taken = 0;
+#pragma unroll
+            for (int q = 7; q >= 0; --q) taken = (taken << 1) | ((b[q] >> (job_of[q] & 31u)) & 1u);
+            const int first = __ffs(int(~taken)) - 1;       // 8: none of them
+            const bool in0 = first < 4;
+            const uint32_t r01 = (first & 1) ? w[1] : w[0], r23 = (first & 1) ? w[3] : w[2];
+            const uint32_t r45 = (first & 1) ? w[5] : w[4], r67 = (first & 1) ? w[7] : w[6];
+            const uint32_t r03 = (first & 2) ? r23 : r01, r47 = (first & 2) ? r67 : r45;
+            const uint32_t r = in0 ? r03 : r47;
+            found = looking & (first < 8);
+            if (found) {
+                job = Rec32{r}.job();
+                lo = Rec32{r}.lo();
+                e = w0 + first;
+            }
+            if (looking & !in0) {       // the first half is used up
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { w[q] = w[q + 4]; job_of[q] = job_of[q + 4]; }
+                w0 += 4;
+                take(1, behind, w0 + 4, 0);
+                behind = ask(w0 + 8);
+                if (!found) e = w0;
+                if (w0 >= list_end) {   // no job is left for the highest lane, and so for none below it
+                    open = 0;
+                    low_gap = -1;
+                    looking = false;
+                }
+            }
+            have = have | found;
+            looking = looking & !found;
+            const unsigned long long look = __ballot(looking);
+            if (!look || (step >= 1 && __popcll(look) <= kSoloFewLooking)) break;
+        }
+        found = have;
+        const bool split = found & (lo > bottom);
+        unsigned long long together = __ballot(looking | split);
+        int n_pieces = 0;
+        bool over = false;
+        if (together) {
+            // list blocks the whole wave looks at: those still looking, and those in pieces
+            const unsigned long long have_first = __ballot(found);
+            while (together) {
+                const int t = __ffsll((long long)together) - 1;
+                together &= together - 1;
+                const int slot0 = (t * waves + wave) * kWave;
+                const int end = __builtin_amdgcn_readlane(list_end, t);
+                int g = state[slot0 + lane].w >> 2;
+                int from = state[slot0 + lane].x;               // where this lane's own search may start
+                asm volatile("" : "+v"(g), "+v"(from));         // both have arrived: no load is left open over the rest of the round
+                unsigned long long rest = solo_readlane64(open, t);
+                int at = __builtin_amdgcn_readlane(e, t);
+                int pj = __builtin_amdgcn_readlane(int(job), t), plo = __builtin_amdgcn_readlane(lo, t);
+                bool have = (have_first >> t) & 1ull, first = true;
+                const int e_was = at;
+                int e_first = at;
+                while (rest) {
+                    const int p = 63 - __clzll((long long)rest);
+                    if (!have) {
+                        // a lower lane's record lies behind the higher lane's, but for records of that same
+                        // job with an equal key (at most 63 of them, next to it)
+                        int c = first ? at : max(at - 63, __builtin_amdgcn_readlane(from, p));
+                        unsigned long long ok = 0;
+                        Rec32 r{0};
+                        for (; c < end; c += kWave) {
+                            const int i = c + lane;
+                            r = rec[min(i, end - 1)];
+                            const uint32_t word = is_held[r.job() >> 5];
+                            ok = __ballot((i < end) & (r.lo() <= p) & (p < r.hi()) & !((word >> (r.job() & 31u)) & 1u));
+                            if (ok) break;
+                        }
+                        if (!ok) break;             // none for lane p, nor for any below it
+                        const int hit = __ffsll((long long)ok) - 1;
+                        const Rec32 x = r.of_lane(hit);
+                        at = c + hit; pj = int(x.job()); plo = x.lo();
+                    }
+                    if (n_pieces == kWave) { over = true; rest = 0; break; }
+                    if (first) e_first = at;
+                    else if (lane == p) state[slot0 + lane].x = at;
+                    const unsigned long long piece = rest & ~((1ull << plo) - 1ull);
+                    const bool in = (piece >> lane) & 1ull;
+                    const int low = wave_min_dpp(in ? g : 0x7fffffff);
+                    if (in && g == low) {
+                        s_piece[wave][n_pieces] = solo_word(round, pj, low);
+                        s_at[wave][n_pieces] = (t << 6) | lane;
+                    }
+                    ++n_pieces;
+                    rest &= ~piece;
+                    have = false;
+                    first = false;
+                }
+                if (lane == t) {
+                    found = false;
+                    if (rest) { open &= ~rest; closed(); }
+                    if (e_first != e_was) { e = e_first; window(); }
+                }
+            }
+        }
+        // claims: the list blocks that name the first one's job agree on their lowest gap, the rest go by themselves
+        const bool whole = found & !split;
+        const unsigned long long todo = __ballot(whole);
+        if (marked != nobody) set_mark(marked);
+        marked = nobody;
+        if (todo) {
+            const int leader = __ffsll((long long)todo) - 1;
+            const bool same = whole & (job == uint32_t(__builtin_amdgcn_readlane(int(job), leader)));
+            const int low = wave_min_dpp(same ? low_gap : 0x7fffffff);
+            if (whole & (!same | (lane == leader))) {
+                if (!solo_enter(s_tab, solo_word(round, int(job), same ? low : low_gap))) s_ctl[half].y = round;
+                set_mark(job);
+                marked = job;
+            }
+        }
+        if (marked_piece != nobody) set_mark(marked_piece);
+        marked_piece = nobody;
+        if (n_pieces) {
+            if (lane < n_pieces) {
+                const unsigned long long v = s_piece[wave][lane];
+                if (!solo_enter(s_tab, v)) s_ctl[half].y = round;
+                marked_piece = uint32_t(v >> 20) & 0xfffffu;
+                set_mark(marked_piece);
+            }
+            if (lane == 0 && over) s_ctl[half].y = round;
+            if (lane == 0 && n_pieces > kSoloEasyPieces) atomicMax(&s_ctl[half].z, (round << 8) | n_pieces);
+        }
+        if (lane == 0) {
+            if (todo != 0 || n_pieces) s_ctl[half].x = round;
+            else if (any_open) s_ctl[half].w = round;
+        }
+        __syncthreads();        // the round's only barrier: all claims are in
+        const int4 ctl = s_ctl[half];
+        bool won = false;
+        if (whole) won = solo_wins(s_tab, solo_word(round, int(job), low_gap));
+        if (ctl.y == round) break;      // the launched rounds take this one over
+        if (ctl.x != round) {           // nobody claims anything: the end
+            ended = 1; stable = 1;
+            done = ctl.w == round ? round : round - 1;
+            break;
+        }
+        auto grant = [&](bool mine, int l, uint32_t j) {       // lane l of this thread's list block gets job j
+            const unsigned long long b = __ballot(mine);
+            const int k = __popcll(b);
+            if (n_log + k > kWave) flush();
+            if (mine) {
+                s_log[wave][n_log + __popcll(b & ((1ull << lane) - 1ull))] =
+                    (static_cast<unsigned long long>(uint32_t(u * kWave + l)) << 32) | j;
+                open &= ~(1ull << l);
+                closed();
+            }
+            n_log += k;
+        };
+        if (__ballot(won)) grant(won, low_lane, job);
+        if (n_pieces) {
+            unsigned long long hits = __ballot(lane < n_pieces && solo_wins(s_tab, s_piece[wave][lane]));
+            while (hits) {
+                const int k = __ffsll((long long)hits) - 1;
+                hits &= hits - 1;
+                const int at = s_at[wave][k];
+                grant(lane == at >> 6, at & 63, uint32_t(s_piece[wave][k] >> 20) & 0xfffffu);
+            }
+        }
+        done = round;
+        if (round == cap) {
+            if (open) s_flag = 1;
+            __syncthreads();
+            ended = 1; stable = s_flag ? 0 : 1;
+            break;
+        }
+        strain = max(strain + max((ctl.z >> 8) == round ? (ctl.z & 255) - kSoloEasyPieces : 0, 0) - 1, 0);
+        if (strain > kSoloPatience) break;
+    }
+    flush();
+    if (tid == 0) { out[kSoloDone] = ended; out[kSoloRounds] = done; out[kSoloStable] = stable; }
+    if (ended) return;
+    // too many pieces: the state as a launched round leaves it, but for the outcome already known
+    __syncthreads();
+    // (the bitmap the next round would read: the jobs of the last one are marked in that one only)
+    for (int i = tid; i < held_words; i += threads) held[i] = held[held_words + i] = s_held[(done + 1) & 1][i];
+    for (int i = 0; i * waves + wave < n_lb; ++i) {
+        const int slot = (i * waves + wave) * kWave + lane;
+        const unsigned long long on = solo_readlane64(open, i);
+        const int e_top = __builtin_amdgcn_readlane(e, i);
+        const int flag = state[slot].w & 3;
+        const bool highest = on != 0 && lane == 63 - __clzll((long long)on);
+        if ((on >> lane) & 1ull) state[slot].x = max(state[slot].x, highest ? e_top : e_top - 63);
+        else if (flag == 0) state[slot].w |= 2;
+        else if (flag == 1) claim[state[slot].y] = claim_of(1, state[slot].w >> 2);     // any stamp of a past round says held
+    }
+}
+
+}  // namespace sja

@@ -1,6 +1,7 @@
 // C ABI of the gap-job fit / slot-grant engine: argument validation, workspace
 // bookkeeping and kernel launches.  See include/sja.h for the contract.
 #include "sja_kernels.h"
+#include "k_solo.h"
 
 #include <mutex>
 #include <new>
@@ -377,8 +378,16 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
                            reinterpret_cast<int32_t *>(held), int64_t(2) * held_words, 0);
         SJA_HIP(hipGetLastError(), "k_fill_i32 launch");
     }
+    // the block that runs rounds by itself: it needs the held bitmap, a thread per list block, and keys
+    // that never fall along a job's atoms (a minimum gain above the distance of two capacities of the
+    // hysteresis set can let a longer fit end in a shorter cut)
+    bool rising = true;
+    for (int i = 1; i < ctx->hyst_used_n_caps; ++i)
+        rising = rising && int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] >= ctx->hyst_used_min_gain;
+    const bool solo = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks;
+    const int solo_waves = (n_subs + kWave - 1) / kWave > kSoloMinWaves ? (n_subs + kWave - 1) / kWave : kSoloMinWaves;
     auto launch_round = [&](int64_t k, int propose) {
-        const bool with_bitmap = use_held && k <= kHeldRounds;
+        const bool with_bitmap = use_held && (solo || k <= kHeldRounds);
         auto go = [&](auto kern, auto *records) {
             hipLaunchKernelGGL(kern, dim3(round_grid), dim3(kRoundBlock), 0, st, state, list_off, records, claim, int(k), propose, n_subs,
                                with_bitmap ? held_words : 0, with_bitmap ? held : static_cast<uint32_t *>(nullptr), lb_begin,
@@ -394,11 +403,28 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     int64_t launched = 0;        // kernels 1..launched have been enqueued
     int64_t next_check = 1;      // first round whose end is not yet decided
     bool finished = false;
-    int64_t batch = 64;          // rounds enqueued between looks at the flags; grows, a finished batch costs little
+    int64_t batch = solo ? kSoloFirstRounds : 64;   // rounds enqueued between looks at the flags; grows, a finished batch costs little
     while (!finished) {
         const int64_t upto = (launched + batch < cap) ? launched + batch : cap;
-        if (batch < 1024) batch *= 2;
+        if (batch < 1024) batch *= solo ? 4 : 2;
         for (int64_t k = launched + 1; k <= upto; ++k) SJA_HIP(launch_round(k, 1), "k_grant_round launch");
+        if (solo && upto < cap) {
+            hipLaunchKernelGGL(k_grant_solo, dim3(1), dim3(solo_waves * kWave), 0, st, state, list_off, static_cast<const Rec32 *>(rec),
+                               claim, int(upto), int(next_check), int(cap), n_subs, held_words, held, cnt_lost, cnt_cand,
+                               counters + 8);
+            SJA_HIP(hipGetLastError(), "k_grant_solo launch");
+            int32_t h_out[3] = {0, 0, 0};
+            SJA_HIP(hipMemcpyAsync(h_out, counters + 8, sizeof(h_out), hipMemcpyDeviceToHost, st), "rounds readback");
+            SJA_HIP(hipStreamSynchronize(st), "round synchronise");
+            launched = h_out[kSoloRounds];
+            next_check = launched + 1;
+            if (h_out[kSoloDone]) {
+                result[0] = h_out[kSoloRounds];
+                result[1] = h_out[kSoloStable];
+                finished = true;
+            }
+            continue;
+        }
         if (upto == cap) SJA_HIP(launch_round(cap + 1, 0), "k_grant_round launch");
         launched = upto;
         hipLaunchKernelGGL(k_count_open, dim3(1), dim3(1024), 0, st, lb_bound, plan, state, counters + 12);

@@ -1,0 +1,65 @@
+"""Conflict rounds run by one thread block: what its rule takes and what it leaves to the launched
+rounds, round caps on both sides of the hand-over, equal keys, lists that run dry, and keys that fall
+along a job's atoms, against the oracle."""
+import numpy as np
+import pytest
+
+from gen import make_workload
+from test_gpu_parity import full_tick_check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def engine():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2509_19086_amd as P
+    return P.Engine(0)
+
+
+@pytest.mark.parametrize("max_rounds", [1, 4, 5, 6, 33, 0])
+def test_caps_around_the_hand_over(engine, oracle, max_rounds):
+    wl = make_workload("medium", 3, n_gaps=513, n_jobs=900)
+    wl.max_rounds = max_rounds
+    full_tick_check(engine, oracle, wl, policies=[0, 3], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("name,gaps,jobs", [("stress", 900, 700), ("stress", 700, 1500), ("large", 1025, 513), ("small", 65, 4000),
+                                            ("medium", 1400, 40), ("tiny", 3, 700)])
+def test_many_pieces_and_lists_that_run_dry(engine, oracle, name, gaps, jobs):
+    wl = make_workload(name, gaps + jobs, n_gaps=gaps, n_jobs=jobs)
+    full_tick_check(engine, oracle, wl, policies=[0, 1, 2, 3], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("weights", [(0, 0, 0), (1, 0, 0)])
+def test_equal_keys(engine, oracle, weights):
+    # with weight 0 every cut of every job has the same key: the job id decides, and a lower
+    # window's record of the same job comes before a higher one's
+    wl = make_workload("stress", 11, n_gaps=600, n_jobs=800)
+    wl.sla_weight = weights
+    wl.class0_override = 0
+    full_tick_check(engine, oracle, wl, policies=[2], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("caps,gain", [((36864, 73728, 110592), 36864), ((36864, 73728, 110592), 50000), ((36864, 40000, 147456), 4000)])
+def test_hysteresis_keys_that_fall(engine, oracle, caps, gain):
+    # with a gain above the distance of two capacities a longer fit can end in a shorter cut
+    import paper_2509_19086_amd as P
+    wl = make_workload("stress", 5, n_gaps=500, n_jobs=700)
+    engine.sja_set_hysteresis(list(caps), gain)
+    try:
+        t = P.DeviceTick(engine, wl)
+        t.prepare()
+        t.fit()
+        want = None
+        for mode in (1, 0):                 # the matrix-scanning rounds are checked against the oracle elsewhere
+            engine.sja_set_resolve_mode(mode)
+            t.resolve(P.Params.make(3))
+            got = [x.cpu().numpy().copy() for x in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds)]
+            want = want or got
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a, b)
+    finally:
+        engine.sja_set_resolve_mode(0)
+        engine.sja_set_hysteresis([], 1)
