@@ -440,13 +440,9 @@ int sja_store_reference(sja_ctx *ctx, void *stream, int32_t *cut);
  *                       ungranted: the rows of the cut matrix after sja_fit,
  *                       the pairs themselves (evaluated again, nothing stored)
  *                       after sja_fit_select.
- *   SJA_RESOLVE_LISTS_LOOKUP  as SJA_RESOLVE_LISTS, but the job of every list
- *                       record is looked up through the record's rank even
- *                       where the list keys have room to carry it: the form
- *                       the lists take by themselves for batches whose block,
- *                       rank and job numbers do not fit one 64-bit key
- *                       together; selectable so that it can be tested at any
- *                       size.
+ *   SJA_RESOLVE_LISTS_LOOKUP  the same as SJA_RESOLVE_LISTS (once a form that
+ *                       looked the job of a list record up; every list entry
+ *                       now carries its job).
  * SJA_ERR_SIZE for any other value.
  */
 typedef enum {

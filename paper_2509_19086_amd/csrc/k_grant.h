@@ -9,7 +9,7 @@
 // one contiguous range of positions.  So:
 //   1. all reachable atoms are ranked once by policy key (stable radix passes:
 //      key descending, job id ascending);
-//   2. for every list block (<= 64 sorted gap positions of one capacity class
+//   2. along the ranked atoms, for every list block (<= 64 sorted gap positions of one capacity class
 //      whose windows are of similar length) the atoms some position of it would
 //      get are listed in rank order, each with the range of lanes (positions)
 //      it applies to;
@@ -28,7 +28,9 @@
 
 namespace sja {
 
-constexpr int kEntryLaneBits = 13;      // low bits of a list entry: lane range lo (6), hi (7)
+// A list entry as it is sorted: list block (27 bits) : job (24) : lane range hi (7) : lo (6).
+constexpr int kEntryJobShift = 13, kEntryBlockShift = 37;
+static_assert(SJA_MAX_JOBS <= 1 << (kEntryBlockShift - kEntryJobShift), "job ids fit an entry");
 
 struct PolicyDev {
     int policy;
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(256) void k_atom_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ abase, const int32_t *__restrict__ wait,
     const uint8_t *__restrict__ sla_class, unsigned long long *__restrict__ key_hi,
-    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm)
+    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm, int4 *__restrict__ info)
 {
     const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
     if (j >= n_jobs) return;
@@ -113,39 +115,8 @@ __global__ __launch_bounds__(256) void k_atom_keys(
         key_hi[a0 + a] = ~((tier << 62) | (F * mult));
         key_lo[a0 + a] = ~(mixed ? F : 0ull);
         perm[a0 + a] = uint32_t(a0 + a);
+        info[a0 + a] = make_int4(j, v.x, v.y, 0);
     }
-}
-
-// The job of every reachable atom (one wave per job): needed only where list keys have no room for it.
-__global__ __launch_bounds__(256) void k_atom_jobs(int n_jobs, const int32_t *__restrict__ abase, uint32_t *__restrict__ atom_job)
-{
-    const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-    if (j >= n_jobs) return;
-    for (int a = abase[j] + int(threadIdx.x & (kWave - 1)); a < abase[j + 1]; a += kWave) atom_job[a] = uint32_t(j);
-}
-
-// rank of every atom, and (with atom_job) the job that holds each rank
-__global__ void k_rank_from_perm(const int32_t *n_ptr, const uint32_t *__restrict__ perm,
-                                 const uint32_t *__restrict__ atom_job, uint32_t *__restrict__ rank,
-                                 uint32_t *__restrict__ ranked_job)
-{
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < *n_ptr) {
-        const uint32_t a = perm[i];
-        rank[a] = uint32_t(i);
-        if (atom_job) ranked_job[i] = atom_job[a];
-    }
-}
-
-// Number of entries of sorted w[0..len) that are < d, known to be at least `from`.
-__device__ __forceinline__ int count_less(const int *w, int len, int d, int from = 0)
-{
-    int lo = from, hi = len;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (w[mid] < d) lo = mid + 1; else hi = mid;
-    }
-    return lo;
 }
 
 // Grant-list blocks.  A list serves its gaps well when most of its records
@@ -176,145 +147,245 @@ __global__ void k_list_blocks_count(int n_slots, const int32_t *__restrict__ pla
     lb_off[u] = cnt;
 }
 
-__global__ void k_list_blocks_write(int lb_cap, const int32_t *__restrict__ plan,
+// Writes the pieces, the list block of every position, and per class a table of positions by duration:
+// entry k of a class's kPosTable / n_classes entries is the first position whose window reaches k << shift
+// (the class's end from the last window on), so that a search for a duration only has a few positions left.
+constexpr int kPosTable = 2048;
+
+__device__ __forceinline__ int pos_shift(int longest, int entries)
+{
+    int s = 0;
+    while (s < 31 && (max(longest, 0) >> s) > entries - 2) ++s;
+    return s;
+}
+
+__global__ void k_list_blocks_write(int lb_cap, int n_gaps, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
                                     const int32_t *__restrict__ sub_begin, const int32_t *__restrict__ sub_end,
                                     const int32_t *__restrict__ gap_w, const int32_t *__restrict__ lb_off,
-                                    int32_t *lb_begin, int32_t *lb_end, int32_t *lb_sub)
+                                    int32_t *lb_begin, int32_t *lb_end, int32_t *pos_block, int32_t *pos_tab)
 {
     const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    if (!plan[kPlanTabled] || u >= plan[kPlanSubBlocks]) return;
-    int v = lb_off[u];
-    const int e = sub_end[u];
-    for (int b = sub_begin[u]; b < e && v < lb_cap; ++v) {
-        const int p = list_piece_end(gap_w, b, e);
-        lb_begin[v] = b;
-        lb_end[v] = p;
-        lb_sub[v] = u;
-        b = p;
+    if (!plan[kPlanTabled]) return;
+    if (u < plan[kPlanSubBlocks]) {
+        int v = lb_off[u];
+        const int e = sub_end[u];
+        for (int b = sub_begin[u]; b < e && v < lb_cap; ++v) {
+            const int p = list_piece_end(gap_w, b, e);
+            lb_begin[v] = b;
+            lb_end[v] = p;
+            for (int i = b; i < p; ++i) pos_block[i] = v;
+            b = p;
+        }
+    }
+    const int n_classes = plan[kPlanClasses], entries = kPosTable / n_classes;
+    const int c = u / entries;
+    if (c < n_classes) {
+        const int k = u - c * entries;
+        const int begin = class_begin[c], end = c + 1 < n_classes ? class_begin[c + 1] : n_gaps;
+        const int shift = pos_shift(gap_w[end - 1], entries);
+        const int64_t d = int64_t(k) << shift;
+        int lo = begin, hi = end;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (gap_w[mid] < d) lo = mid + 1; else hi = mid;
+        }
+        pos_tab[u] = k == entries - 1 ? end : lo;
     }
 }
 
-// Entries of the lists.  Thread (list block v, job j) visits the atoms of j
-// that some position of v gets: atom a applies to lanes [lo, hi) where lo is
-// the first position whose window reaches D_a and hi the first one that
-// already reaches atom a+1.  Every entry is one 64-bit word, v : rank : hi (7
-// bits) : lo (6 bits); where it is stored does not matter (the sort orders
-// them); entries beyond entry_cap are counted but not stored.
-// A block takes kEmitTiles tiles of 256 jobs for one list block.  Each tile is
-// visited once: the entries go to a buffer in LDS as they are found (the lanes
-// of a wave that find one in the same step of the visit take their places with
-// one addition); once the buffer is half full, and after the last tile, the
-// block reserves room in the output with one addition to the running total
-// (additions to one word are served one after the other: one per wave made
-// this kernel three times slower) and copies the buffer out with coalesced
-// stores.  Entries that find the buffer full go straight to the output, a
-// wave's step at a time.
-constexpr int kEmitTiles = 8;
-constexpr int kEmitBuffer = 3072;     // entries staged in LDS (24 KB: six blocks per compute unit)
+// Entries of the lists, in rank order.  An atom is the answer of its job for the positions from the first
+// window that reaches its duration up to the first that reaches the next atom's: in every capacity class one
+// range of positions, an entry for each list block it touches.  Lanes walk along the atoms as they are ranked,
+// so that the entries leave in rank order and only their list block is left to sort by.  Two passes: counts per
+// 64 atoms and per list block (EMIT false; chunk_at receives the counts), then the entries (chunk_at holds
+// their exclusive sums).  The chunks go to the waves in turn: ranks far down, where many an atom answers for
+// a whole class, hold most of the entries.
+// Ranked atoms lie anywhere, so every load of a step is 64 lines for a wave: with the windows in global
+// memory the count took 1.25 ms at Stress (8.5 million atoms, 8 classes), all of it those lines.  WIN > 0:
+// the windows of all positions are kept in LDS (up to WIN of them, and up to kEntryBlocks list blocks).
+constexpr int kEntryThreads = 1024;
+constexpr int kEntryBlocks = 1024;        // list blocks whose first positions a thread block keeps in LDS
+constexpr int kEntryGrid = 512;           // most thread blocks: two per compute unit
+constexpr int kEntryFewWide = 2;          // ranges of three or more list blocks among a wave's that are served one by one
+constexpr int kEntryWinBig = 32768, kEntryWinSmall = 8192;
 
-template <typename Sink>
-__device__ __forceinline__ void list_visit(const int2 *__restrict__ dp, const int *s_w, int len, int a_first, int n_cap,
-                                           Sink &&sink)
-{
-    const int a_begin = max(a_first - 1, 0);
-    if (a_begin >= n_cap) return;
-    // an atom's range ends where the next one's begins: one search per atom
-    int lo = a_begin < a_first ? 0 : count_less(s_w, len, dp[a_begin].x);
-    for (int a = a_begin; a < n_cap && lo < len; ++a) {
-        const int hi = a + 1 < n_cap ? count_less(s_w, len, dp[a + 1].x, lo) : len;    // durations ascend
-        if (hi > lo) sink(a, lo, hi);
-        lo = hi;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_list_emit(
-    int n_jobs, int rank_bits, int job_shift, int lb_cap, long long entry_cap, const int32_t *__restrict__ plan, const int32_t *__restrict__ lb_begin,
-    const int32_t *__restrict__ lb_end, const int32_t *__restrict__ lb_sub, const int32_t *__restrict__ sub_class,
-    const int32_t *__restrict__ gap_w, const int64_t *__restrict__ seg_off,
-    const int2 *__restrict__ atom_dp, const int32_t *__restrict__ start_tab,
-    const int32_t *__restrict__ ncap_tab, const int32_t *__restrict__ abase,
-    const uint32_t *__restrict__ rank, int32_t *sub_count, unsigned long long *total,
+template <bool EMIT, int WIN>
+__global__ __launch_bounds__(kEntryThreads) void k_list_entries(
+    int n_atoms, int n_lb, int n_gaps, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
+    const int32_t *__restrict__ lb_begin, const int32_t *__restrict__ pos_block, const int32_t *__restrict__ pos_tab,
+    const int32_t *__restrict__ gap_w, const int32_t *__restrict__ gap_c, const uint32_t *__restrict__ perm,
+    const int4 *__restrict__ info, int32_t *chunk_at, int32_t *list_count, unsigned long long *total,
     unsigned long long *__restrict__ ekey)
 {
-    __shared__ int s_w[64];
-    __shared__ unsigned long long s_buf[kEmitBuffer];
-    __shared__ int s_cursor, s_all;
-    __shared__ unsigned long long s_base;
-    const int u = blockIdx.y;                  // list block
-    if (!plan[kPlanTabled] || u >= min(plan[kPlanListBlocks], lb_cap)) return;
-    const int b0 = lb_begin[u], len = lb_end[u] - b0;
-    if (threadIdx.x < 64) s_w[threadIdx.x] = threadIdx.x < len ? gap_w[b0 + threadIdx.x] : INT32_MAX;
-    if (threadIdx.x == 0) { s_cursor = 0; s_all = 0; }
-    __syncthreads();
-    const int lane = threadIdx.x & (kWave - 1);
-    const int sub = lb_sub[u];
-    const int cls = sub_class[sub];
-    const int j0 = blockIdx.x * (kEmitTiles * 256) + threadIdx.x;
-    const unsigned long long head = (unsigned long long)u << rank_bits;
-    for (int it = 0; it < kEmitTiles; ++it) {
-        const int j = j0 + it * 256;
-        if (j < n_jobs) {
-            int af = start_tab[int64_t(sub) * n_jobs + j];
-            const int nc = ncap_tab[int64_t(cls) * n_jobs + j];
-            const int2 *dp = atom_dp + seg_off[j];
-            // the table holds the count at the sub-block's first position; a later piece starts further on
-            while (af < nc && dp[af].x <= s_w[0]) ++af;
-            const int a0 = abase[j];
-            // the job rides above the sorted bits when there is room for it (job_shift >= 0)
-            const unsigned long long rider = job_shift >= 0 ? (unsigned long long)uint32_t(j) << job_shift : 0ull;
-            list_visit(dp, s_w, len, af, nc, [&](int a, int lo, int hi) {
-                const unsigned long long key = rider | ((head | rank[a0 + a]) << kEntryLaneBits) | (unsigned long long)((hi << 6) | lo);
-                // the lanes of this wave that are at this point together
-                const unsigned long long peers = __ballot(true);
-                const int n_peers = __popcll(peers);
-                const int mine = __builtin_amdgcn_mbcnt_hi(uint32_t(peers >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(peers), 0u));
-                int at = 0;
-                if (mine == 0) at = atomicAdd(&s_cursor, n_peers);
-                at = __builtin_amdgcn_readlane(at, __ffsll((long long)peers) - 1) + mine;
-                if (at < kEmitBuffer) {
-                    s_buf[at] = key;
-                } else {
-                    // the buffer is full: this step's surplus goes straight out
-                    const unsigned long long over = __ballot(true);
-                    unsigned long long to = 0;
-                    if (lane == __ffsll((long long)over) - 1) to = atomicAdd(total, (unsigned long long)__popcll(over));
-                    to = __shfl(to, __ffsll((long long)over) - 1, kWave) + __popcll(over & lanes_below(lane));
-                    if ((long long)to < entry_cap) ekey[to] = key;
-                }
-            });
-        }
-        __syncthreads();
-        const int found = s_cursor;                           // entries since the last copy, surplus included
-        __syncthreads();                                      // everybody has read it before anybody adds to it again
-        if (found < kEmitBuffer / 2 && it + 1 < kEmitTiles) continue;       // uniform over the block
-        const int staged = min(found, kEmitBuffer);
-        if (threadIdx.x == 0) {
-            s_all += found;
-            s_base = staged ? atomicAdd(total, (unsigned long long)staged) : 0ull;
-        }
-        __syncthreads();
-        const unsigned long long out0 = s_base;
-        for (int i = threadIdx.x; i < staged; i += 256)
-            if ((long long)(out0 + i) < entry_cap) ekey[out0 + i] = s_buf[i];
-        __syncthreads();
-        if (threadIdx.x == 0) s_cursor = 0;
-        __syncthreads();
+    constexpr bool kLds = WIN > 0;
+    __shared__ int s_w[kLds ? WIN : 1];
+    __shared__ int s_pos[kPosTable];
+    __shared__ int s_begin[kLds ? kEntryBlocks + 1 : 1];       // first positions of the list blocks
+    __shared__ int s_hint[kLds ? WIN / kWave : 1];             // list block of every 64th position
+    __shared__ int s_diff[!EMIT && kLds ? kEntryBlocks + 1 : 1];
+    __shared__ int s_cap[kMaxClasses], s_end[kMaxClasses], s_shift[kMaxClasses], s_lb[kMaxClasses + 1];
+    __shared__ long long s_all[kEntryThreads / kWave];
+    __shared__ int s_src[EMIT ? kEntryThreads / kWave : 1][kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int n_classes = min(plan[kPlanClasses], kMaxClasses), entries = kPosTable / n_classes;
+    for (int i = tid; i < entries * n_classes; i += kEntryThreads) s_pos[i] = pos_tab[i];
+    for (int c = tid; c < n_classes; c += kEntryThreads) {
+        const int end = c + 1 < n_classes ? class_begin[c + 1] : n_gaps;
+        s_cap[c] = gap_c[end - 1];
+        s_end[c] = end;
+        s_shift[c] = pos_shift(gap_w[end - 1], entries);
+        s_lb[c + 1] = end < n_gaps ? pos_block[end] : n_lb;       // list blocks of class c: [s_lb[c], s_lb[c + 1])
     }
-    if (threadIdx.x == 0 && s_all) atomicAdd(&sub_count[u], s_all);
+    if (tid == 0) s_lb[0] = 0;
+    if (kLds) {
+        for (int i = tid; i < n_gaps; i += kEntryThreads) {
+            s_w[kLds ? i : 0] = gap_w[i];
+            if ((i & (kWave - 1)) == 0) s_hint[kLds ? i / kWave : 0] = pos_block[i];
+        }
+        for (int k = tid; k <= n_lb; k += kEntryThreads) {
+            s_begin[kLds ? k : 0] = k < n_lb ? lb_begin[k] : n_gaps;
+            if (!EMIT) s_diff[kLds && !EMIT ? k : 0] = 0;
+        }
+    }
+    __syncthreads();
+    auto window = [&](int p) { return kLds ? s_w[kLds ? p : 0] : gap_w[p]; };
+    auto begin_of = [&](int k) { return kLds ? s_begin[kLds ? k : 0] : (k < n_lb ? lb_begin[k] : n_gaps); };
+    auto block_of = [&](int p) {
+        if (!kLds) return pos_block[p];
+        int k = s_hint[kLds ? p / kWave : 0];
+        while (begin_of(k + 1) <= p) ++k;
+        return k;
+    };
+
+    const int n_chunks = int((int64_t(n_atoms) + kWave - 1) / kWave), n_waves = int(gridDim.x) * (kEntryThreads / kWave);
+    long long count_all = 0;
+    for (int chunk = blockIdx.x * (kEntryThreads / kWave) + wave; chunk < n_chunks; chunk += n_waves) {
+        const int64_t i = int64_t(chunk) * kWave + lane;
+        const bool valid = i < n_atoms;
+        int64_t at = EMIT ? chunk_at[chunk] : 0;
+        int count = 0;
+        const int a = valid ? int(perm[i]) : 0;
+        const int4 x = info[a], y = info[min(a + 1, n_atoms - 1)];
+        const bool more = a + 1 < n_atoms && y.x == x.x;           // the job's next atom
+        for (int c = 0; c < n_classes; ++c) {
+            int n = 0, k_lo = 0, p1 = 0, p2 = 0;
+            if (valid && x.z <= s_cap[c]) {
+                const int *tab = s_pos + c * entries;
+                const int shift = s_shift[c];
+                const int t1 = min(x.y >> shift, entries - 1);
+                p1 = tab[t1];
+                int q1 = tab[min(t1 + 1, entries - 1)];
+                p2 = s_end[c];
+                int q2 = p2;
+                if (more && y.z <= s_cap[c]) {
+                    const int t2 = min(y.y >> shift, entries - 1);
+                    p2 = tab[t2];
+                    q2 = tab[min(t2 + 1, entries - 1)];
+                }
+                if (p1 < q2) {          // else no position is left between the two
+                    while (p1 < q1) {
+                        const int m = (p1 + q1) >> 1;
+                        if (window(m) < x.y) p1 = m + 1; else q1 = m;
+                    }
+                    while (p2 < q2) {
+                        const int m = (p2 + q2) >> 1;
+                        if (window(m) < y.y) p2 = m + 1; else q2 = m;
+                    }
+                    if (p1 < p2) {
+                        k_lo = block_of(p1);
+                        n = block_of(p2 - 1) - k_lo + 1;
+                    }
+                }
+            }
+            if (EMIT) {
+                if (!__ballot(n > 0)) continue;
+                const int upto = wave_scan_add(n);
+                const int64_t out = at + (upto - n);
+                auto put = [&](int64_t to, int k, int job, int lo, int hi) {
+                    ekey[to] = (static_cast<unsigned long long>(uint32_t(k)) << kEntryBlockShift) |
+                               (static_cast<unsigned long long>(uint32_t(job)) << kEntryJobShift) | uint32_t((hi << 6) | lo);
+                };
+                unsigned long long wide = __ballot(n > 2);
+                if (__popcll(wide) > kEntryFewWide) {
+                    // many ranges over several list blocks: a lane per entry (its range is the last one that starts
+                    // at or before it)
+                    const int total_n = __builtin_amdgcn_readlane(upto, kWave - 1), start = upto - n;
+                    volatile int *src = s_src[EMIT ? wave : 0];
+                    int carry = -1;
+                    for (int e0 = 0; e0 < total_n; e0 += kWave) {
+                        src[lane] = -1;
+                        __builtin_amdgcn_wave_barrier();
+                        if (n > 0 && start >= e0 && start < e0 + kWave) src[start - e0] = lane;
+                        __builtin_amdgcn_wave_barrier();
+                        const int mark = src[lane];
+                        const int from_lane = wave_scan_max_dpp(lane == 0 ? max(mark, carry) : mark);
+                        carry = __builtin_amdgcn_readlane(from_lane, kWave - 1);
+                        const int fl = max(from_lane, 0);
+                        const int k = e0 + lane - __shfl(start, fl, kWave), fn = __shfl(n, fl, kWave), fk = __shfl(k_lo, fl, kWave) + k;
+                        const int f1 = __shfl(p1, fl, kWave), f2 = __shfl(p2, fl, kWave), fj = __shfl(x.x, fl, kWave);
+                        if (e0 + lane < total_n) {
+                            const int b = begin_of(fk);
+                            put(at + e0 + lane, fk, fj, k == 0 ? f1 - b : 0, (k == fn - 1 ? f2 : begin_of(fk + 1)) - b);
+                        }
+                    }
+                } else {
+                    // most ranges lie in one list block or reach over one border: the first and the last part by the
+                    // atom's lane, the whole list blocks between them, if any, by the wave together
+                    if (n > 0) {
+                        const int b = begin_of(k_lo);
+                        put(out, k_lo, x.x, p1 - b, (n == 1 ? p2 : begin_of(k_lo + 1)) - b);
+                    }
+                    if (n > 1) put(out + n - 1, k_lo + n - 1, x.x, 0, p2 - begin_of(k_lo + n - 1));
+                    for (; wide; wide &= wide - 1) {
+                        const int t = __ffsll((long long)wide) - 1;
+                        const int tn = lane_value(n, t), tk = lane_value(k_lo, t), tj = lane_value(x.x, t);
+                        const int64_t to = at + lane_value(upto, t) - tn;
+                        for (int k = lane + 1; k < tn - 1; k += kWave) put(to + k, tk + k, tj, 0, begin_of(tk + k + 1) - begin_of(tk + k));
+                    }
+                }
+                at += __builtin_amdgcn_readlane(upto, kWave - 1);
+            } else if (n > 0) {
+                count += n;
+                if (kLds) {
+                    atomicAdd(&s_diff[kLds && !EMIT ? k_lo : 0], 1);
+                    // (nothing to take back behind the class: the sums start anew there)
+                    if (k_lo + n < s_lb[c + 1]) atomicAdd(&s_diff[kLds && !EMIT ? k_lo + n : 0], -1);
+                } else {
+                    for (int k = k_lo; k < k_lo + n; ++k) atomicAdd(&list_count[k], 1);
+                }
+            }
+        }
+        if (!EMIT) {
+            const int all = __builtin_amdgcn_readlane(wave_scan_add(count), kWave - 1);
+            if (lane == 0) chunk_at[chunk] = all;
+            count_all += all;
+        }
+    }
+    if (EMIT) return;
+    if (lane == 0) s_all[wave] = count_all;
+    __syncthreads();
+    if (tid == 0) {         // (an addition per wave, thousands to one word, took 80 us)
+        unsigned long long t = 0;
+        for (int v = 0; v < kEntryThreads / kWave; ++v) t += (unsigned long long)s_all[v];
+        if (t) atomicAdd(total, t);
+    }
+    if (!kLds) return;
+    // the list blocks' counts are the running sums of a class's differences
+    for (int c = wave; c < n_classes; c += kEntryThreads / kWave) {
+        const int lb0 = s_lb[c], lb1 = s_lb[c + 1];
+        int run = 0;
+        for (int k0 = lb0; k0 < lb1; k0 += kWave) {
+            const int k = k0 + lane;
+            const int upto = run + wave_scan_add(k < lb1 ? s_diff[kLds && !EMIT ? k : 0] : 0);
+            if (k < lb1 && upto) atomicAdd(&list_count[k], upto);
+            run = __builtin_amdgcn_readlane(upto, kWave - 1);
+        }
+    }
 }
 
 __device__ __forceinline__ unsigned long long claim_of(int round, int g)
 {
     return (static_cast<unsigned long long>(round) << 32) | (0xffffffffu - uint32_t(g));
-}
-
-// Sorted entries as records: one load per entry.
-template <typename REC>
-__global__ void k_list_pack(const int32_t *n_ptr, const unsigned long long *__restrict__ ekey, KeyRecords out)
-{
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= *n_ptr) return;
-    static_cast<REC *>(out.rec)[i] = key_record<REC>(out, ekey[i]);
 }
 
 // One round for one list block (one wave, one lane per gap position).  First

@@ -31,6 +31,7 @@ constexpr int kSoloMaxWaves = 16;
 constexpr int kSoloMinWaves = 4;        // one per SIMD: list blocks in pieces are served by several waves side by side
 constexpr int kSoloMaxBlocks = kSoloMaxWaves * kWave;
 constexpr int kSoloFirstRounds = 4;     // launched rounds before the block first takes over
+constexpr int kSoloFewRounds = 16;      // rounds it takes over at least, if the caller bounds them
 constexpr int kSoloTable = 2048;        // claim words: one per job named in a round (power of two)
 constexpr int kSoloFewLooking = 4;      // lanes still looking that the wave serves together
 constexpr int kSoloEasyPieces = 8;      // pieces per wave and round that cost no more than a launched round
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
                             const int i = c + lane;
                             r = rec[min(i, end - 1)];
                             const uint32_t word = is_held[r.job() >> 5];
-                            ok = __ballot((i < end) & (r.lo() <= p) & (p < r.hi()) & !((word >> (r.job() & 31u)) & 1u));
+                            ok = __ballot((i < end) & (r.lo() <= p) & (p < r.hi()) & (((word >> (r.job() & 31u)) & 1u) == 0));
                             if (ok) break;
                         }
                         if (!ok) break;             // none for lane p, nor for any below it

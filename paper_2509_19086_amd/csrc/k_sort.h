@@ -173,22 +173,12 @@ struct Rec64 {
 };
 struct NoRec {};
 
-// What the last pass over list entries writes instead of the keys themselves: their records.  lo (6
-// bits) and hi (7 bits) are the key's lowest lane_bits bits, and the job either rides in the key above
-// job_shift (no pass sorts by those bits) or, with job_shift < 0, is looked up through the key's rank
-// field (one gather per key).
-struct KeyRecords {
-    const uint32_t *ranked_job;
-    void *rec;
-    int lane_bits, rank_bits, job_shift;
-};
-
+// What the last pass over list entries writes instead of the keys themselves: the record of an entry
+// job : hi (7 bits) : lo (6 bits), whatever bits (the list block) lie above the job's 24.
 template <typename REC>
-__device__ __forceinline__ REC key_record(const KeyRecords &out, unsigned long long v)
+__device__ __forceinline__ REC key_record(unsigned long long v)
 {
-    const uint32_t rank = uint32_t((v >> out.lane_bits) & ((1ull << out.rank_bits) - 1ull));
-    const uint32_t job = out.job_shift >= 0 ? uint32_t(v >> out.job_shift) : out.ranked_job[rank];
-    return REC::make(job, unsigned(v) & 63u, unsigned(v >> 6) & 127u);
+    return REC::make(uint32_t(v >> 13) & 0xffffffu, unsigned(v) & 63u, unsigned(v >> 6) & 127u);
 }
 
 // PAY: every key carries a 32-bit payload that moves with it.  REC other than NoRec: the sorted keys
@@ -199,7 +189,7 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
                                                       const uint32_t *__restrict__ pay_src,
                                                       uint32_t *__restrict__ pay_dst, const int32_t *n_ptr,
                                                       int shift, unsigned digit_mask, const int32_t *__restrict__ hist,
-                                                      int n_tiles, KeyRecords out = KeyRecords{})
+                                                      int n_tiles, void *rec)
 {
     __shared__ unsigned long long s_key[kKeyTile];
     __shared__ uint32_t s_pay[PAY ? kKeyTile : 1];
@@ -273,7 +263,7 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
         const unsigned d = unsigned(v >> shift) & digit_mask;
         const int64_t o = int64_t(s_goff[d]) + (k - s_start[d]);
         if constexpr (!std::is_same<REC, NoRec>::value) {
-            static_cast<REC *>(out.rec)[o] = key_record<REC>(out, v);
+            static_cast<REC *>(rec)[o] = key_record<REC>(v);
         } else {
             dst[o] = v;
         }

@@ -158,52 +158,63 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
 }
 
 
-// Stable radix passes over bare 64-bit keys (key-only tiles) between two
-// buffers, optionally with a 32-bit payload per key.  Only the bytes named in
-// byte_mask are sorted on, lowest first (a byte that is the same in every key
-// needs no pass).
-int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host,
-                    unsigned byte_mask, int bit_offset, bool &flip, unsigned long long *const buf[2],
-                    uint32_t *const pay[2], const KeyRecords *records = nullptr, bool *records_written = nullptr,
-                    int sorted_bits = 64, bool wide_records = false)
+// One stable pass over the `width` bits of the keys at `shift` (at most 8), from buf[flip] to the other
+// buffer; `launch` enqueues the scatter kernel of the kind the caller wants.
+template <typename Launch>
+int radix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host, int shift, int width,
+               bool &flip, unsigned long long *const buf[2], Launch &&launch)
 {
-    // sorted_bits: bits above bit_offset + sorted_bits are not part of the order (a rider) and are masked
-    // out of the last digit
-    if (records_written) *records_written = false;
-    if (n_host <= 0) return SJA_OK;
-    int last_byte = -1;         // the pass that finishes the order: with `records` it writes those instead of keys
-    for (int b = 0; b < 8; ++b)
-        if (((byte_mask >> b) & 1u) && bit_offset + 8 * b < 64) last_byte = b;
     const int n_tiles = int((n_host + kKeyTile - 1) / kKeyTile);
     int32_t *hist = ws_ptr<int32_t>(ctx, L.g_hist);
-    int32_t *tmp = ws_ptr<int32_t>(ctx, L.g_scan_tmp);
-    for (int b = 0; b < 8; ++b) {
+    const unsigned long long *src = buf[flip ? 1 : 0];
+    const unsigned digit_mask = (1u << width) - 1u;
+    hipLaunchKernelGGL(k_keys_hist, dim3(n_tiles), dim3(256), 0, st, src, n_dev, shift, digit_mask, hist, n_tiles);
+    SJA_HIP(hipGetLastError(), "k_keys_hist launch");
+    SJA_HIP(enqueue_scan(st, hist, (int64_t(1) << width) * n_tiles, ws_ptr<int32_t>(ctx, L.g_scan_tmp), nullptr),
+            "radix scan launch");
+    launch(dim3(n_tiles), src, buf[flip ? 0 : 1], shift, digit_mask, hist, n_tiles);
+    SJA_HIP(hipGetLastError(), "k_keys_scatter launch");
+    flip = !flip;
+    return SJA_OK;
+}
+
+// Stable radix passes over 64-bit keys with a 32-bit payload each, lowest byte first; only the bytes named
+// in byte_mask are sorted on (a byte that is the same in every key needs no pass).
+int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host,
+                    unsigned byte_mask, bool &flip, unsigned long long *const buf[2], uint32_t *const pay[2])
+{
+    for (int b = 0; b < 8 && n_host > 0; ++b) {
         if (!((byte_mask >> b) & 1u)) continue;
-        const int shift = bit_offset + 8 * b;
-        if (shift >= 64) break;
-        const unsigned long long *src = buf[flip ? 1 : 0];
-        unsigned long long *dst = buf[flip ? 0 : 1];
-        const int live = sorted_bits - 8 * b;                   // bits of this digit that belong to the order
-        if (live <= 0) break;
-        const unsigned digit_mask = live >= 8 ? 255u : (1u << live) - 1u;
-        hipLaunchKernelGGL(k_keys_hist, dim3(n_tiles), dim3(256), 0, st, src, n_dev, shift, digit_mask, hist, n_tiles);
-        SJA_HIP(hipGetLastError(), "k_keys_hist launch");
-        SJA_HIP(enqueue_scan(st, hist, int64_t(256) * n_tiles, tmp, nullptr), "radix scan launch");
-        if (pay)
-            hipLaunchKernelGGL((k_keys_scatter<true, NoRec>), dim3(n_tiles), dim3(256), 0, st, src, dst, pay[flip ? 1 : 0],
-                               pay[flip ? 0 : 1], n_dev, shift, digit_mask, hist, n_tiles, KeyRecords{});
-        else if (records && b == last_byte) {
-            auto kern = wide_records ? k_keys_scatter<false, Rec64> : k_keys_scatter<false, Rec32>;
-            hipLaunchKernelGGL(kern, dim3(n_tiles), dim3(256), 0, st, src, dst,
-                               static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr), n_dev, shift,
-                               digit_mask, hist, n_tiles, *records);
-            if (records_written) *records_written = true;
-        } else
-            hipLaunchKernelGGL((k_keys_scatter<false, NoRec>), dim3(n_tiles), dim3(256), 0, st, src, dst,
-                               static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr), n_dev, shift,
-                               digit_mask, hist, n_tiles, KeyRecords{});
-        SJA_HIP(hipGetLastError(), "k_keys_scatter launch");
-        flip = !flip;
+        const bool from = flip;
+        const int rc = radix_pass(ctx, st, L, n_dev, n_host, 8 * b, 8, flip, buf,
+                                  [&](dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
+                                      const int32_t *hist, int n_tiles) {
+                                      hipLaunchKernelGGL((k_keys_scatter<true, NoRec>), grid, dim3(256), 0, st, src, dst,
+                                                         pay[from ? 1 : 0], pay[from ? 0 : 1], n_dev, shift, mask, hist, n_tiles,
+                                                         static_cast<void *>(nullptr));
+                                  });
+        if (rc != SJA_OK) return rc;
+    }
+    return SJA_OK;
+}
+
+// The list entries by list block (they come in rank order), the last pass writes their records.
+template <typename REC>
+int radix_sort_entries(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host, int block_bits,
+                       unsigned long long *const buf[2], void *rec)
+{
+    bool flip = false;
+    const int passes = (block_bits + 7) / 8, width = (block_bits + passes - 1) / passes;
+    for (int p = 0; p < passes; ++p) {
+        const int rc = radix_pass(ctx, st, L, n_dev, n_host, kEntryBlockShift + p * width, width, flip, buf,
+                                  [&](dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
+                                      const int32_t *hist, int n_tiles) {
+                                      auto kern = p == passes - 1 ? k_keys_scatter<false, REC> : k_keys_scatter<false, NoRec>;
+                                      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, dst,
+                                                         static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr),
+                                                         n_dev, shift, mask, hist, n_tiles, rec);
+                                  });
+        if (rc != SJA_OK) return rc;
     }
     return SJA_OK;
 }
@@ -236,17 +247,16 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     const int2 *atom_dp = ws_ptr<int2>(ctx, L.atom_dp);
     const int2 *atom_db = ws_ptr<int2>(ctx, L.atom_db);
     const int32_t *sub_begin = ws_ptr<int32_t>(ctx, L.sub_begin), *sub_end = ws_ptr<int32_t>(ctx, L.sub_end);
-    const int32_t *sub_class = ws_ptr<int32_t>(ctx, L.sub_class);
     int32_t *lb_begin = ws_ptr<int32_t>(ctx, L.lb_begin), *lb_end = ws_ptr<int32_t>(ctx, L.lb_end);
-    int32_t *lb_sub = ws_ptr<int32_t>(ctx, L.lb_sub), *lb_off = ws_ptr<int32_t>(ctx, L.lb_off);
+    int32_t *lb_off = ws_ptr<int32_t>(ctx, L.lb_off);
     const int32_t *ncap_tab = ws_ptr<int32_t>(ctx, L.ncap_tab);
     const int32_t *gap_w = ws_ptr<int32_t>(ctx, L.gap_w);
     unsigned long long *key_hi = ws_ptr<unsigned long long>(ctx, L.g_key_hi);
     unsigned long long *key_lo = ws_ptr<unsigned long long>(ctx, L.g_key_lo);
     uint32_t *perm[2] = {ws_ptr<uint32_t>(ctx, L.g_perm0), ws_ptr<uint32_t>(ctx, L.g_perm1)};
-    uint32_t *rank = ws_ptr<uint32_t>(ctx, L.g_rank);
+    int4 *info = ws_ptr<int4>(ctx, L.g_info);
+    int32_t *chunk_at = ws_ptr<int32_t>(ctx, L.g_chunk_at);
     unsigned long long *ekey[2] = {ws_ptr<unsigned long long>(ctx, L.g_ekey0), ws_ptr<unsigned long long>(ctx, L.g_ekey1)};
-    uint32_t *atom_job = ws_ptr<uint32_t>(ctx, L.g_atom_job), *ranked_job = ws_ptr<uint32_t>(ctx, L.g_ranked_job);
 
     // 1. list blocks; reachable atoms per job -> compact atom ids
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, st, counters, int64_t(16), 0);
@@ -254,23 +264,19 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     hipLaunchKernelGGL(k_list_blocks_count, dim3((sub_bound + 1 + 255) / 256), dim3(256), 0, st, sub_bound + 1, plan, sub_begin,
                        sub_end, gap_w, lb_off);
     SJA_HIP(enqueue_scan(st, lb_off, int64_t(sub_bound) + 1, tmp, plan + kPlanListBlocks), "list block scan launch");
-    hipLaunchKernelGGL(k_list_blocks_write, dim3((sub_bound + 255) / 256), dim3(256), 0, st, lb_bound, plan, sub_begin,
-                       sub_end, gap_w, lb_off, lb_begin, lb_end, lb_sub);
+    int32_t *pos_block = ws_ptr<int32_t>(ctx, L.g_pos_block), *pos_tab = ws_ptr<int32_t>(ctx, L.g_pos_tab);
+    const int32_t *class_begin = ws_ptr<int32_t>(ctx, L.class_begin);
+    const int write_threads = sub_bound > kPosTable ? sub_bound : kPosTable;
+    hipLaunchKernelGGL(k_list_blocks_write, dim3((write_threads + 255) / 256), dim3(256), 0, st, lb_bound, G, plan, class_begin,
+                       sub_begin, sub_end, gap_w, lb_off, lb_begin, lb_end, pos_block, pos_tab);
     SJA_HIP(hipGetLastError(), "list block launch");
-    // where every sub-block starts in every job's atom list (the fit only keeps this per chunk)
-    int32_t *sub_tab = ws_ptr<int32_t>(ctx, L.sub_tab);
-    const int starts_jobs = kStartsJobs;
-    hipLaunchKernelGGL(k_fit_starts, dim3((J + starts_jobs - 1) / starts_jobs), dim3(256), 0, st, J, int(kPlanSubBlocks), plan,
-                       ws_ptr<int32_t>(ctx, L.class_begin), sub_begin, sub_class, gap_w, ws_ptr<int32_t>(ctx, L.gap_c),
-                       ctx->seg_off, atom_dp, ws_ptr<int32_t>(ctx, L.n_atoms), sub_tab, static_cast<int32_t *>(nullptr));
-    SJA_HIP(hipGetLastError(), "k_fit_starts launch");
     hipLaunchKernelGGL(k_reach, dim3((J + 1 + 255) / 256), dim3(256), 0, st, J, plan, ncap_tab, abase);
     SJA_HIP(hipGetLastError(), "k_reach launch");
     SJA_HIP(enqueue_scan(st, abase, int64_t(J) + 1, tmp, counters + 2), "atom scan launch");
     // policy keys of the atoms and the bytes in which they differ (both only need the device-side counts)
     hipLaunchKernelGGL(k_atom_keys, dim3((J + 3) / 4), dim3(256), 0, st, J, pol, ctx->seg_off, atom_dp,
                        atom_area_of(ctx, L), abase, wait,
-                       sla_class, key_hi, key_lo, perm[0]);
+                       sla_class, key_hi, key_lo, perm[0], info);
     SJA_HIP(hipGetLastError(), "k_atom_keys launch");
     hipLaunchKernelGGL(k_key_bits, dim3(256), dim3(256), 0, st, counters + 2, key_hi, key_lo,
                        reinterpret_cast<unsigned long long *>(counters + 4));
@@ -283,17 +289,10 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     const int n_subs = host_plan[kPlanListBlocks];          // list blocks from here on
     if (!host_plan[kPlanTabled] || n_subs > lb_bound || n_atoms > L.atom_cap) return SJA_OK;
 
-    const int rank_bits = bits_for(n_atoms > 1 ? n_atoms : 2);
-    const int sub_bits = bits_for(n_subs > 1 ? n_subs : 2);
-    // the job of an entry rides in its key above the sorted bits when the key has room for it:
-    // then the pass that writes the records need not look it up through the rank
-    const int job_bits = bits_for(J > 1 ? J : 2);
-    const bool ride = ctx->resolve_mode != SJA_RESOLVE_LISTS_LOOKUP && kEntryLaneBits + rank_bits + sub_bits + job_bits <= 64;
-    const int job_shift = ride ? kEntryLaneBits + rank_bits + sub_bits : -1;
-
     // 2. rank the atoms by policy key (descending key, ascending job id): stable passes over
     //    (inverted key, atom id) pairs, the secondary key first; the entry buffers serve as the
     //    second key buffer, they are not in use yet
+    bool flip = false;      // where the atom ids are: perm[flip]
     if (n_atoms > 0) {
         unsigned long long bits_hi = 0, bits_lo = 0;
         memcpy(&bits_hi, host_counters + 4, 8);
@@ -303,11 +302,10 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             for (int b = 0; b < 8; ++b) if ((v >> (8 * b)) & 0xffull) m |= 1u << b;
             return m;
         };
-        bool flip = false;      // where the atom ids are: perm[flip]
         int rc = SJA_OK;
         if (params->policy == SJA_POLICY_MIXED) {
             unsigned long long *kb[2] = {key_lo, ekey[0]};
-            rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_lo), 0, flip, kb, perm);
+            rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_lo), flip, kb, perm);
             if (rc != SJA_OK) return rc;
         }
         // the primary keys in the order reached so far
@@ -316,45 +314,43 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         hipLaunchKernelGGL(k_gather_keys, dim3(unsigned((n_atoms + 255) / 256)), dim3(256), 0, st, counters + 2, key_hi,
                            perm[flip ? 1 : 0], kh[flip ? 1 : 0]);
         SJA_HIP(hipGetLastError(), "k_gather_keys launch");
-        rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), 0, flip, kh, perm);
+        rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), flip, kh, perm);
         if (rc != SJA_OK) return rc;
-        if (!ride) {
-            hipLaunchKernelGGL(k_atom_jobs, dim3((J + 3) / 4), dim3(256), 0, st, J, abase, atom_job);
-            SJA_HIP(hipGetLastError(), "k_atom_jobs launch");
-        }
-        hipLaunchKernelGGL(k_rank_from_perm, dim3(unsigned((n_atoms + 255) / 256)), dim3(256), 0, st, counters + 2,
-                           perm[flip ? 1 : 0], ride ? static_cast<const uint32_t *>(nullptr) : atom_job, rank, ranked_job);
-        SJA_HIP(hipGetLastError(), "k_rank_from_perm launch");
     }
 
-    // 3. list entries (one pass, counted as they are written), then sorted by (block, rank)
-    const dim3 emit_grid((J + 256 * kEmitTiles - 1) / (256 * kEmitTiles), lb_bound);
-    hipLaunchKernelGGL(k_list_emit, emit_grid, dim3(256), 0, st, J, rank_bits, job_shift, lb_bound, (long long)L.entry_cap, plan,
-                       lb_begin, lb_end, lb_sub, sub_class, gap_w, ctx->seg_off, atom_dp, sub_tab, ncap_tab, abase, rank,
-                       list_off, reinterpret_cast<unsigned long long *>(counters), ekey[0]);
-    SJA_HIP(hipGetLastError(), "k_list_emit launch");
+    // 3. list entries in rank order: counted, then written, then sorted by list block
+    const uint32_t *ranked = perm[flip ? 1 : 0];
+    constexpr int waves_per_block = kEntryThreads / kWave;
+    // windows in LDS: a block with 32768 of them has a compute unit to itself
+    const bool in_lds = n_subs <= kEntryBlocks && G <= kEntryWinBig, small = in_lds && G <= kEntryWinSmall;
+    const int64_t n_chunks = (n_atoms + kWave - 1) / kWave, want = (n_chunks + waves_per_block - 1) / waves_per_block;
+    const int most = in_lds && !small ? kEntryGrid / 2 : kEntryGrid;
+    const unsigned entry_grid = unsigned(want < most ? want : most);
+    auto launch_entries = [&](auto emit) {
+        auto kern = small ? k_list_entries<decltype(emit)::value, kEntryWinSmall>
+                          : in_lds ? k_list_entries<decltype(emit)::value, kEntryWinBig> : k_list_entries<decltype(emit)::value, 0>;
+        hipLaunchKernelGGL(kern, dim3(entry_grid), dim3(kEntryThreads), 0, st, int(n_atoms), n_subs, G, plan,
+                           class_begin, lb_begin, pos_block, pos_tab, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), ranked, info, chunk_at,
+                           list_off, reinterpret_cast<unsigned long long *>(counters), ekey[0]);
+        return hipGetLastError();
+    };
+    if (n_atoms > 0) {
+        SJA_HIP(launch_entries(std::false_type{}), "k_list_entries launch");
+        SJA_HIP(enqueue_scan(st, chunk_at, n_chunks, tmp, nullptr), "entry scan launch");
+    }
     long long n_entries = 0;
     SJA_HIP(hipMemcpyAsync(&n_entries, counters, sizeof(n_entries), hipMemcpyDeviceToHost, st), "entry count readback");
     SJA_HIP(hipStreamSynchronize(st), "entry count synchronise");
     if (n_entries > L.entry_cap || n_entries >= (1ll << 31)) return SJA_OK;
     SJA_HIP(enqueue_scan(st, list_off, int64_t(lb_bound) + 2, tmp, nullptr), "list offset scan launch");
-    bool eflip = false, packed = false;
     void *rec = ws_ptr<void>(ctx, L.g_rec);
-    const KeyRecords records{ranked_job, rec, kEntryLaneBits, rank_bits, job_shift};
     const bool wide_records = int64_t(J) > (int64_t(1) << kRec32JobBits);
     if (n_entries > 0) {
-        // the pass that finishes the order writes the records straight away
-        const int key_bytes = (rank_bits + sub_bits + 7) / 8;
-        int rc = radix_sort_keys(ctx, st, L, counters, n_entries, (1u << key_bytes) - 1u, kEntryLaneBits, eflip, ekey,
-                                 nullptr, &records, &packed, rank_bits + sub_bits, wide_records);
+        SJA_HIP(launch_entries(std::true_type{}), "k_list_entries launch");
+        const int block_bits = bits_for(n_subs > 1 ? n_subs : 2);
+        const int rc = wide_records ? radix_sort_entries<Rec64>(ctx, st, L, counters, n_entries, block_bits, ekey, rec)
+                                    : radix_sort_entries<Rec32>(ctx, st, L, counters, n_entries, block_bits, ekey, rec);
         if (rc != SJA_OK) return rc;
-    }
-    const int fb = eflip ? 1 : 0;
-    if (n_entries > 0 && !packed) {
-        auto kern = wide_records ? k_list_pack<Rec64> : k_list_pack<Rec32>;
-        hipLaunchKernelGGL(kern, dim3(unsigned((n_entries + 255) / 256)), dim3(256), 0, st, counters, ekey[fb],
-                           records);
-        SJA_HIP(hipGetLastError(), "k_list_pack launch");
     }
 
     // 4. rounds
@@ -380,11 +376,12 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     }
     // the block that runs rounds by itself: it needs the held bitmap, a thread per list block, and keys
     // that never fall along a job's atoms (a minimum gain above the distance of two capacities of the
-    // hysteresis set can let a longer fit end in a shorter cut)
+    // hysteresis set can let a longer fit end in a shorter cut); and more than a few rounds, which cost no
+    // more launched than the block needs to start and report (240 us of a Large tick of eight rounds)
     bool rising = true;
     for (int i = 1; i < ctx->hyst_used_n_caps; ++i)
         rising = rising && int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] >= ctx->hyst_used_min_gain;
-    const bool solo = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks;
+    const bool solo = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks && cap >= kSoloFirstRounds + kSoloFewRounds;
     const int solo_waves = (n_subs + kWave - 1) / kWave > kSoloMinWaves ? (n_subs + kWave - 1) / kWave : kSoloMinWaves;
     auto launch_round = [&](int64_t k, int propose) {
         const bool with_bitmap = use_held && (solo || k <= kHeldRounds);

@@ -55,7 +55,6 @@ struct Layout {
     size_t chunk_begin, chunk_end, chunk_class, chunk_sub;  // [chunk_bound] int32
     size_t sub_begin, sub_end, sub_class;  // [sub_bound] int32
     size_t start_tab;                      // [chunk_bound * J] int32: per chunk of the stepping kernels
-    size_t sub_tab;                        // [sub_bound * J] int32: per sub-block, built by sja_resolve for its lists
     size_t ncap_tab;                       // [kMaxClasses * J] int32
     size_t sel_part;                       // [ceil(J/kSelBlock) * G] SelPartial
     size_t res_cand_job, res_cand_cut;     // [G] int32
@@ -67,12 +66,14 @@ struct Layout {
     size_t g_abase;                        // [J+2] int32
     size_t g_scan_tmp;                     // tile sums of the scans
     size_t g_key_hi, g_key_lo;             // [atom_cap] uint64
-    size_t g_perm0, g_perm1, g_rank;       // [atom_cap] uint32
+    size_t g_perm0, g_perm1;               // [atom_cap] uint32
+    size_t g_info;                         // [atom_cap] int4: job, duration, peak of an atom
+    size_t g_pos_block, g_pos_tab;         // [G] int32: list block of a position; [2048] int32: positions by duration
+    size_t g_chunk_at;                     // [atom_cap / 64 + 1] int32: entries per 64 ranked atoms, then where they start
     size_t g_hist;                         // [256 * tiles] int32, tiles of the larger of the two sorts
-    size_t g_ekey0, g_ekey1;               // [entry_cap] uint64: list entries (block : rank : lane range)
+    size_t g_ekey0, g_ekey1;               // [entry_cap] uint64: list entries (block : job : lane range), second buffers of the sorts
     size_t g_rec;                          // [entry_cap] Rec32 or Rec64: the sorted lists as records
-    size_t g_atom_job, g_ranked_job;       // [atom_cap] uint32: job by atom id and by rank (keys without room for it)
-    size_t lb_begin, lb_end, lb_sub;       // [list_bound] int32: grant-list blocks (pieces of sub-blocks)
+    size_t lb_begin, lb_end;               // [list_bound] int32: grant-list blocks (pieces of sub-blocks)
     size_t lb_off;                         // [sub_bound+2] int32: first list block of a sub-block
     size_t g_list_off;                     // [list_bound+2] int32
     size_t g_held;                         // 2 x held_bitmap_words(J) uint32: jobs held before a round, two alternating copies
@@ -155,7 +156,6 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     L.sub_end = take(ub * 4);
     L.sub_class = take(ub * 4);
     L.start_tab = take(cb * size_t(J) * 4);
-    L.sub_tab = take(ub * size_t(J) * 4);
     L.ncap_tab = take(size_t(kMaxClasses) * size_t(J) * 4);
     size_t job_tiles = size_t((J + kSelBlock - 1) / kSelBlock);
     L.sel_part = take(job_tiles * size_t(G) * sizeof(SelPartial));
@@ -171,21 +171,21 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     const size_t ac = size_t(L.atom_cap), ec = size_t(L.entry_cap);
     const size_t hist_ints = 256 * ((ec + 4095) / 4096);      // ec >= ac: the atom sort fits too
     L.g_abase = take(size_t(J + 2) * 4);
-    L.g_scan_tmp = take(((hist_ints + 2047) / 2048 + size_t(J) / 2048 + lb / 2048 + 16) * 4);
+    L.g_scan_tmp = take(((hist_ints + 2047) / 2048 + size_t(J) / 2048 + lb / 2048 + 80) * 4);
     L.g_key_hi = take(ac * 8);
     L.g_key_lo = take(ac * 8);
     L.g_perm0 = take(ac * 4);
     L.g_perm1 = take(ac * 4);
-    L.g_rank = take(ac * 4);
+    L.g_info = take(ac * 16);
+    L.g_chunk_at = take((ac / kWave + 1) * 4);
+    L.g_pos_block = take(size_t(G) * 4);
+    L.g_pos_tab = take(G > 0 ? 2048 * 4 : 0);
     L.g_hist = take(hist_ints * 4);
     L.g_ekey0 = take(ec * 8);
     L.g_ekey1 = take(ec * 8);
     L.g_rec = take(ec * 8);
-    L.g_atom_job = take(ac * 4);
-    L.g_ranked_job = take(ac * 4);
     L.lb_begin = take(lb * 4);
     L.lb_end = take(lb * 4);
-    L.lb_sub = take(lb * 4);
     L.lb_off = take((ub + 2) * 4);
     L.g_list_off = take((lb + 2) * 4);
     L.g_state = take(lb * size_t(kWave) * 16);

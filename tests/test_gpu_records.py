@@ -44,3 +44,16 @@ def test_both_record_sizes(engine, oracle, n_jobs):
     t = full_tick_check(engine, oracle, wl, policies=[1], resolve_modes=(0, 2))
     jobs = t.grant_job.cpu().numpy()
     assert (jobs > n_jobs - 50).any() and (jobs < 50).any()
+
+
+@pytest.mark.parametrize("classes,all_safe", [(64, True), (40, True), (1, False)])
+def test_entries_by_groups_of_classes(engine, oracle, classes, all_safe):
+    # every boundary safe and many capacities: an atom's places in all classes do not fit the buffer at once
+    wl = make_workload("stress", 21, n_gaps=700, n_jobs=30)
+    rng = np.random.default_rng(classes)
+    if all_safe:
+        wl.safe[:] = 1
+        wl.progress[:] = 0
+    caps = np.sort(rng.choice(np.arange(2000, 150000), size=classes, replace=False)).astype(np.int32)
+    wl.C = caps[rng.integers(0, classes, size=700)]
+    full_tick_check(engine, oracle, wl, policies=[0, 3], resolve_modes=(0,))

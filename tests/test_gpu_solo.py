@@ -18,7 +18,7 @@ def engine():
     return P.Engine(0)
 
 
-@pytest.mark.parametrize("max_rounds", [1, 4, 5, 6, 33, 0])
+@pytest.mark.parametrize("max_rounds", [1, 4, 5, 19, 20, 21, 33, 0])
 def test_caps_around_the_hand_over(engine, oracle, max_rounds):
     wl = make_workload("medium", 3, n_gaps=513, n_jobs=900)
     wl.max_rounds = max_rounds
