@@ -97,25 +97,45 @@ __global__ __launch_bounds__(256) void k_atom_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ abase, const int32_t *__restrict__ wait,
     const uint8_t *__restrict__ sla_class, unsigned long long *__restrict__ key_hi,
-    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm, int4 *__restrict__ info)
+    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm, int4 *__restrict__ info, unsigned long long *bits)
 {
-    const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-    if (j >= n_jobs) return;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int a0 = abase[j], n = abase[j + 1] - a0;
-    const int64_t base = seg_off[j];
-    const int2 *dp = atom_dp + base;
-    unsigned long long mult, tier;
-    job_policy(pol, wait, sla_class, j, mult, tier);
+    __shared__ unsigned long long s_bits[2][256 / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const bool mixed = pol.policy == SJA_POLICY_MIXED;
-    for (int a = lane; a < n; a += kWave) {
-        const int2 v = dp[a];
-        const unsigned long long F = atom_area ? (unsigned long long)atom_area[base + a]
-                                               : (unsigned long long)v.x * (unsigned long long)v.y;
-        key_hi[a0 + a] = ~((tier << 62) | (F * mult));
-        key_lo[a0 + a] = ~(mixed ? F : 0ull);
-        perm[a0 + a] = uint32_t(a0 + a);
-        info[a0 + a] = make_int4(j, v.x, v.y, 0);
+    unsigned long long any_hi = 0, any_lo = 0;
+    for (int j = blockIdx.x * (256 / kWave) + wave; j < n_jobs; j += gridDim.x * (256 / kWave)) {
+        const int a0 = abase[j], n = abase[j + 1] - a0;
+        const int64_t base = seg_off[j];
+        const int2 *dp = atom_dp + base;
+        unsigned long long mult, tier;
+        job_policy(pol, wait, sla_class, j, mult, tier);
+        for (int a = lane; a < n; a += kWave) {
+            const int2 v = dp[a];
+            const unsigned long long F = atom_area ? (unsigned long long)atom_area[base + a]
+                                                   : (unsigned long long)v.x * (unsigned long long)v.y;
+            const unsigned long long k = (tier << 62) | (F * mult);
+            key_hi[a0 + a] = ~k;
+            any_hi |= k;
+            if (mixed) {
+                key_lo[a0 + a] = ~F;
+                any_lo |= F;
+            }
+            perm[a0 + a] = uint32_t(a0 + a);
+            info[a0 + a] = make_int4(j, v.x, v.y, 0);
+        }
+    }
+    // bits that are set in some key: a byte without any is the same in all (inverted) keys
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        any_hi |= (unsigned long long)__shfl_xor((long long)any_hi, d, kWave);
+        any_lo |= (unsigned long long)__shfl_xor((long long)any_lo, d, kWave);
+    }
+    if (lane == 0) { s_bits[0][wave] = any_hi; s_bits[1][wave] = any_lo; }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const unsigned long long v = s_bits[threadIdx.x][0] | s_bits[threadIdx.x][1] | s_bits[threadIdx.x][2] | s_bits[threadIdx.x][3];
+        // after the first few blocks there is nothing left to add
+        if (v & ~__hip_atomic_load(&bits[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(&bits[threadIdx.x], v);
     }
 }
 
@@ -159,6 +179,24 @@ __device__ __forceinline__ int pos_shift(int longest, int entries)
     return s;
 }
 
+__device__ __forceinline__ void pos_table_entry(int i, int n_gaps, const int32_t *__restrict__ plan,
+                                                const int32_t *__restrict__ class_begin,
+                                                const int32_t *__restrict__ gap_w, int32_t *pos_tab)
+{
+    const int n_classes = plan[kPlanClasses], entries = kPosTable / n_classes;
+    const int c = i / entries;
+    if (c >= n_classes) return;
+    const int k = i - c * entries;
+    const int begin = class_begin[c], end = c + 1 < n_classes ? class_begin[c + 1] : n_gaps;
+    const int64_t d = int64_t(k) << pos_shift(gap_w[end - 1], entries);
+    int lo = begin, hi = end;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (gap_w[mid] < d) lo = mid + 1; else hi = mid;
+    }
+    pos_tab[i] = k == entries - 1 ? end : lo;
+}
+
 __global__ void k_list_blocks_write(int lb_cap, int n_gaps, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
                                     const int32_t *__restrict__ sub_begin, const int32_t *__restrict__ sub_end,
                                     const int32_t *__restrict__ gap_w, const int32_t *__restrict__ lb_off,
@@ -177,19 +215,78 @@ __global__ void k_list_blocks_write(int lb_cap, int n_gaps, const int32_t *__res
             b = p;
         }
     }
-    const int n_classes = plan[kPlanClasses], entries = kPosTable / n_classes;
-    const int c = u / entries;
-    if (c < n_classes) {
-        const int k = u - c * entries;
-        const int begin = class_begin[c], end = c + 1 < n_classes ? class_begin[c + 1] : n_gaps;
-        const int shift = pos_shift(gap_w[end - 1], entries);
-        const int64_t d = int64_t(k) << shift;
-        int lo = begin, hi = end;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (gap_w[mid] < d) lo = mid + 1; else hi = mid;
+    if (u < kPosTable) pos_table_entry(u, n_gaps, plan, class_begin, gap_w, pos_tab);
+}
+
+// All of it in one launch while the sub-blocks are few: block 0 cuts them into pieces (a wave per sub-block,
+// a lane per position: a piece ends at the first lane beyond its limit), the other blocks make the table.
+// The serial walk of one thread per sub-block above takes 60 us at Stress, with its scan.
+constexpr int kListBlocksOne = 2048;
+
+__global__ __launch_bounds__(1024) void k_list_blocks(int lb_cap, int n_gaps, int32_t *plan, const int32_t *__restrict__ class_begin,
+                                                      const int32_t *__restrict__ sub_begin, const int32_t *__restrict__ sub_end,
+                                                      const int32_t *__restrict__ gap_w, int32_t *lb_begin, int32_t *lb_end,
+                                                      int32_t *pos_block, int32_t *pos_tab)
+{
+    __shared__ unsigned long long s_start[kListBlocksOne];     // lanes that start a piece
+    __shared__ int s_off[kListBlocksOne];
+    __shared__ int s_sum[1024 / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const bool tabled = plan[kPlanTabled] != 0;
+    if (blockIdx.x > 0) {
+        const int i = (int(blockIdx.x) - 1) * 1024 + tid;
+        if (tabled && i < kPosTable) pos_table_entry(i, n_gaps, plan, class_begin, gap_w, pos_tab);
+        return;
+    }
+    const int n_subs = tabled ? min(plan[kPlanSubBlocks], kListBlocksOne) : 0;
+    for (int u = wave; u < n_subs; u += 1024 / kWave) {
+        const int b = sub_begin[u], len = sub_end[u] - b;
+        const int w = gap_w[b + min(lane, len - 1)];
+        unsigned long long starts = 0;
+        for (int s = 0; s < len;) {
+            starts |= 1ull << s;
+            const int64_t w0 = max(__builtin_amdgcn_readlane(w, s), 0);
+            const unsigned long long beyond = __ballot(lane > s && lane < len && int64_t(w) > w0 + (w0 >> 1) + 64);
+            s = beyond ? __ffsll((long long)beyond) - 1 : len;
         }
-        pos_tab[u] = k == entries - 1 ? end : lo;
+        if (lane == 0) s_start[u] = starts;
+    }
+    __syncthreads();
+    int mine[kListBlocksOne / 1024], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kListBlocksOne / 1024; ++k) {
+        const int u = tid * (kListBlocksOne / 1024) + k;
+        mine[k] = u < n_subs ? __popcll(s_start[u]) : 0;
+        sum += mine[k];
+    }
+    const int upto = wave_scan_add(sum);
+    if (lane == kWave - 1) s_sum[wave] = upto;
+    __syncthreads();
+    int off = upto - sum, all = 0;
+    for (int v = 0; v < 1024 / kWave; ++v) {
+        if (v < wave) off += s_sum[v];
+        all += s_sum[v];
+    }
+#pragma unroll
+    for (int k = 0; k < kListBlocksOne / 1024; ++k) {
+        const int u = tid * (kListBlocksOne / 1024) + k;
+        if (u < n_subs) s_off[u] = off;
+        off += mine[k];
+    }
+    if (tid == 0) plan[kPlanListBlocks] = all;
+    __syncthreads();
+    for (int u = wave; u < n_subs; u += 1024 / kWave) {
+        const int b = sub_begin[u], len = sub_end[u] - b;
+        const unsigned long long starts = s_start[u], upto_me = starts & (~0ull >> (kWave - 1 - lane));
+        const int v = s_off[u] + __popcll(upto_me) - 1;
+        if (lane < len && v < lb_cap) {
+            pos_block[b + lane] = v;
+            if ((starts >> lane) & 1ull) {
+                const unsigned long long later = starts & ~upto_me;
+                lb_begin[v] = b + lane;
+                lb_end[v] = later ? b + __ffsll((long long)later) - 1 : b + len;
+            }
+        }
     }
 }
 
@@ -745,9 +842,10 @@ __global__ void k_grant_finish(int lb_cap, PolicyDev pol, const int32_t *__restr
                                const long long *__restrict__ atom_area,
                                const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
                                int32_t *grant_job, int32_t *grant_cut, int64_t *grant_score,
-                               int32_t *job_gap)
+                               int32_t *job_gap, int rounds, int stable, int32_t *rounds_and_stable)
 {
     const int slot = blockIdx.x * blockDim.x + threadIdx.x;
+    if (slot == 0) { rounds_and_stable[0] = rounds; rounds_and_stable[1] = stable; }
     if (slot >= min(plan[kPlanListBlocks], lb_cap) * kWave) return;
     const int4 st = state[slot];
     if ((st.w & 3) != 1) return;

@@ -313,7 +313,8 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
                             const int i = c + lane;
                             r = rec[min(i, end - 1)];
                             const uint32_t word = is_held[r.job() >> 5];
-                            ok = __ballot((i < end) & (r.lo() <= p) & (p < r.hi()) & (((word >> (r.job() & 31u)) & 1u) == 0));
+                            const bool free_job = ((word >> (r.job() & 31u)) & 1u) == 0;
+                            ok = __ballot((i < end) & (r.lo() <= p) & (p < r.hi()) & free_job);
                             if (ok) break;
                         }
                         if (!ok) break;             // none for lane p, nor for any below it

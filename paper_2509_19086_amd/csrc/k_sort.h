@@ -78,11 +78,53 @@ __global__ __launch_bounds__(256) void k_scan_add(int32_t *data, int64_t n, cons
         if (base + i < n) data[base + i] += add;
 }
 
+// The same by one thread block, for scans whose three launches cost more than the work: a thread takes
+// 32 consecutive items a turn.
+constexpr int kScanOneItems = 32, kScanOneMost = 2 * 1024 * kScanOneItems;
+
+__global__ __launch_bounds__(1024) void k_scan_one(int32_t *data, int n, int32_t *total)
+{
+    __shared__ int s_sum[1024 / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    int carry = 0;
+    for (int b0 = 0; b0 < n; b0 += 1024 * kScanOneItems) {
+        const int left = (n - b0 + 1023) / 1024;                       // items per thread of this turn
+        const int each = min(kScanOneItems, (left + 3) / 4 * 4);
+        const int base = b0 + int(threadIdx.x) * each;
+        int v[kScanOneItems];
+        int sum = 0;
+#pragma unroll
+        for (int i = 0; i < kScanOneItems; ++i) {
+            v[i] = i < each && base + i < n ? data[base + i] : 0;
+            sum += v[i];
+        }
+        const int upto = wave_scan_add(sum);
+        if (lane == kWave - 1) s_sum[wave] = upto;
+        __syncthreads();
+        int run = carry + upto - sum;
+        for (int w = 0; w < 1024 / kWave; ++w) {
+            if (w < wave) run += s_sum[w];
+            carry += s_sum[w];
+        }
+#pragma unroll
+        for (int i = 0; i < kScanOneItems; ++i) {
+            if (i < each && base + i < n) data[base + i] = run;
+            run += v[i];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && total) *total = carry;
+}
+
 // Enqueues an in-place exclusive scan; tile_sums needs ceil(n/2048) ints.
 // total (device, may be null) receives the sum of all items.
 inline hipError_t enqueue_scan(hipStream_t st, int32_t *data, int64_t n, int32_t *tile_sums, int32_t *total)
 {
     if (n <= 0) return hipSuccess;
+    if (n <= kScanOneMost) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, st, data, int(n), total);
+        return hipGetLastError();
+    }
     const int n_tiles = int((n + kScanTile - 1) / kScanTile);
     hipLaunchKernelGGL(k_scan_tiles, dim3(n_tiles), dim3(256), 0, st, data, n, tile_sums);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, tile_sums, n_tiles, total);
@@ -96,8 +138,10 @@ inline hipError_t enqueue_scan(hipStream_t st, int32_t *data, int64_t n, int32_t
 // quarter, walked in order so the pass stays stable), put in digit order in
 // LDS and written out from there, so that items of one digit leave as one
 // contiguous run.  hist is digit-major ([256][n_tiles]) so that one exclusive
-// scan over it yields every (digit, tile) output offset.  n lives in device
-// memory (it is produced by earlier kernels).
+// scan over it yields every (digit, tile) output offset; with few tiles
+// (FEW) it is tile-major and every tile of the scatter adds its column up
+// itself, which saves the scan's launches.  n lives in device memory (it is
+// produced by earlier kernels).
 // --------------------------------------------------------------------------
 constexpr int kKeyTile = 4096;
 constexpr int kKeyPerWave = kKeyTile / 4;
@@ -115,6 +159,9 @@ __device__ __forceinline__ unsigned long long digit_peers(unsigned d, bool valid
     return peers;
 }
 
+constexpr int kKeyFewTiles = 256;        // (at 256 tiles the sums take 2 us more in the scatter, the scan takes 10)
+
+template <bool FEW>
 __global__ __launch_bounds__(256) void k_keys_hist(const unsigned long long *__restrict__ keys,
                                                    const int32_t *n_ptr, int shift, unsigned digit_mask, int32_t *hist,
                                                    int n_tiles)
@@ -144,7 +191,7 @@ __global__ __launch_bounds__(256) void k_keys_hist(const unsigned long long *__r
         }
     }
     __syncthreads();
-    hist[int64_t(tid) * n_tiles + blockIdx.x] = s_h[tid];
+    hist[FEW ? int64_t(blockIdx.x) * 256 + tid : int64_t(tid) * n_tiles + blockIdx.x] = s_h[tid];
 }
 
 // A list record: a job and the lane range [lo, hi) of its list block that one of the job's atoms
@@ -183,7 +230,7 @@ __device__ __forceinline__ REC key_record(unsigned long long v)
 
 // PAY: every key carries a 32-bit payload that moves with it.  REC other than NoRec: the sorted keys
 // are not written at all, their records are (the pass that finishes the order of the list entries).
-template <bool PAY, typename REC = NoRec>
+template <bool FEW, bool PAY, typename REC = NoRec>
 __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *__restrict__ src,
                                                       unsigned long long *__restrict__ dst,
                                                       const uint32_t *__restrict__ pay_src,
@@ -203,7 +250,24 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
 #pragma unroll
     for (int w = 0; w < 4; ++w) s_cnt[w][tid] = 0;
-    s_goff[tid] = hist[int64_t(tid) * n_tiles + blockIdx.x];
+    if (FEW) {
+        // digit tid: its items in all tiles and in those before this one
+        int all = 0, before = 0;
+#pragma unroll 16
+        for (int t = 0; t < n_tiles; ++t) {
+            const int h = hist[int64_t(t) * 256 + tid];
+            all += h;
+            before += t < int(blockIdx.x) ? h : 0;
+        }
+        const int upto = wave_scan_add(all);
+        if (lane == kWave - 1) s_wsum[wave] = upto;
+        __syncthreads();
+        int off = upto - all + before;
+        for (int w = 0; w < wave; ++w) off += s_wsum[w];
+        s_goff[tid] = off;
+    } else {
+        s_goff[tid] = hist[int64_t(tid) * n_tiles + blockIdx.x];
+    }
     __syncthreads();
 
     unsigned long long key[kKeyChunks];
@@ -271,38 +335,95 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
     }
 }
 
+// The whole sort of up to kKeyTile keys with their payloads by one thread block: by the bytes of `mask_lo`
+// of the secondary keys (if any), then by those of `mask_hi` of the primary ones, lowest byte first.  A few
+// thousand keys are a few microseconds a pass here, and a launch or three a pass as a chain of kernels.
+constexpr int kSortOneThreads = 1024;
+
+__global__ __launch_bounds__(kSortOneThreads) void k_sort_one(int n, const unsigned long long *__restrict__ key_lo, unsigned mask_lo,
+                                                              const unsigned long long *__restrict__ key_hi, unsigned mask_hi,
+                                                              uint32_t *__restrict__ perm)
+{
+    constexpr int WAVES = kSortOneThreads / kWave, PER = kKeyTile / kSortOneThreads;
+    __shared__ unsigned long long s_key[kKeyTile];
+    __shared__ uint32_t s_pay[kKeyTile];
+    __shared__ int s_cnt[WAVES][256];
+    __shared__ int s_start[256], s_wsum[4];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int first = wave * PER * kWave + lane;
+    unsigned long long key[PER];
+    uint32_t pay[PER];
+#pragma unroll
+    for (int c = 0; c < PER; ++c) pay[c] = uint32_t(first + c * kWave);
+    for (int half = 0; half < 2; ++half) {
+        const unsigned mask = half ? mask_hi : mask_lo;
+        const unsigned long long *src = half ? key_hi : key_lo;
+        if (!mask) continue;
+#pragma unroll
+        for (int c = 0; c < PER; ++c) key[c] = first + c * kWave < n ? src[pay[c]] : ~0ull;
+        for (int b = 0; b < 8; ++b) {
+            if (!((mask >> b) & 1u)) continue;
+            for (int i = tid; i < WAVES * 256; i += kSortOneThreads) s_cnt[0][i] = 0;
+            __syncthreads();
+            volatile int *cnt = &s_cnt[wave][0];
+            int pos[PER];
+#pragma unroll
+            for (int c = 0; c < PER; ++c) {
+                const bool valid = first + c * kWave < n;
+                const unsigned d = unsigned(key[c] >> (8 * b)) & 255u;
+                const unsigned long long peers = digit_peers(d, valid);
+                const int before = __popcll(peers & ((1ull << lane) - 1ull));
+                const int prev = cnt[d];
+                pos[c] = prev + before;
+                __builtin_amdgcn_wave_barrier();
+                if (valid && before == 0) cnt[d] = prev + __popcll(peers);
+                __builtin_amdgcn_wave_barrier();
+            }
+            __syncthreads();
+            int total = 0, upto = 0;
+            if (tid < 256) {            // digit tid: the waves' offsets inside the digit, then the digits' starts
+                for (int w = 0; w < WAVES; ++w) {
+                    const int h = s_cnt[w][tid];
+                    s_cnt[w][tid] = total;
+                    total += h;
+                }
+                upto = wave_scan_add(total);
+                if (lane == kWave - 1) s_wsum[wave] = upto;
+            }
+            __syncthreads();
+            if (tid < 256) {
+                int off = upto - total;
+                for (int w = 0; w < wave; ++w) off += s_wsum[w];
+                s_start[tid] = off;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < PER; ++c) {
+                if (first + c * kWave < n) {
+                    const unsigned d = unsigned(key[c] >> (8 * b)) & 255u;
+                    const int slot = s_start[d] + s_cnt[wave][d] + pos[c];
+                    s_key[slot] = key[c];
+                    s_pay[slot] = pay[c];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < PER; ++c) {
+                if (first + c * kWave < n) { key[c] = s_key[first + c * kWave]; pay[c] = s_pay[first + c * kWave]; }
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < PER; ++c)
+        if (first + c * kWave < n) perm[first + c * kWave] = pay[c];
+}
+
 // out[i] = keys[idx[i]]: the keys of a permutation, laid out in its order.
 __global__ void k_gather_keys(const int32_t *n_ptr, const unsigned long long *__restrict__ keys,
                               const uint32_t *__restrict__ idx, unsigned long long *__restrict__ out)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < *n_ptr) out[i] = keys[idx[i]];
-}
-
-// bits[0] |= ~a[i], bits[1] |= ~b[i] over all items: the bytes in which inverted keys differ from "all ones".
-__global__ __launch_bounds__(256) void k_key_bits(const int32_t *n_ptr, const unsigned long long *__restrict__ a,
-                                                  const unsigned long long *__restrict__ b,
-                                                  unsigned long long *bits)
-{
-    __shared__ unsigned long long s_a[4], s_b[4];
-    const int64_t n = *n_ptr;
-    unsigned long long oa = 0, ob = 0;
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x) {
-        oa |= ~a[i];
-        ob |= ~b[i];
-    }
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        oa |= (unsigned long long)__shfl_xor((long long)oa, d, kWave);
-        ob |= (unsigned long long)__shfl_xor((long long)ob, d, kWave);
-    }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    if (lane == 0) { s_a[wave] = oa; s_b[wave] = ob; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        atomicOr(&bits[0], s_a[0] | s_a[1] | s_a[2] | s_a[3]);
-        atomicOr(&bits[1], s_b[0] | s_b[1] | s_b[2] | s_b[3]);
-    }
 }
 
 }  // namespace sja

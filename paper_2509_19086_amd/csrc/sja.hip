@@ -168,11 +168,14 @@ int radix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_d
     int32_t *hist = ws_ptr<int32_t>(ctx, L.g_hist);
     const unsigned long long *src = buf[flip ? 1 : 0];
     const unsigned digit_mask = (1u << width) - 1u;
-    hipLaunchKernelGGL(k_keys_hist, dim3(n_tiles), dim3(256), 0, st, src, n_dev, shift, digit_mask, hist, n_tiles);
+    const bool few = n_tiles <= kKeyFewTiles;
+    hipLaunchKernelGGL(few ? k_keys_hist<true> : k_keys_hist<false>, dim3(n_tiles), dim3(256), 0, st, src, n_dev, shift, digit_mask,
+                       hist, n_tiles);
     SJA_HIP(hipGetLastError(), "k_keys_hist launch");
-    SJA_HIP(enqueue_scan(st, hist, (int64_t(1) << width) * n_tiles, ws_ptr<int32_t>(ctx, L.g_scan_tmp), nullptr),
-            "radix scan launch");
-    launch(dim3(n_tiles), src, buf[flip ? 0 : 1], shift, digit_mask, hist, n_tiles);
+    if (!few)
+        SJA_HIP(enqueue_scan(st, hist, (int64_t(1) << width) * n_tiles, ws_ptr<int32_t>(ctx, L.g_scan_tmp), nullptr),
+                "radix scan launch");
+    launch(few, dim3(n_tiles), src, buf[flip ? 0 : 1], shift, digit_mask, hist, n_tiles);
     SJA_HIP(hipGetLastError(), "k_keys_scatter launch");
     flip = !flip;
     return SJA_OK;
@@ -187,9 +190,10 @@ int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t
         if (!((byte_mask >> b) & 1u)) continue;
         const bool from = flip;
         const int rc = radix_pass(ctx, st, L, n_dev, n_host, 8 * b, 8, flip, buf,
-                                  [&](dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
+                                  [&](bool few, dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
                                       const int32_t *hist, int n_tiles) {
-                                      hipLaunchKernelGGL((k_keys_scatter<true, NoRec>), grid, dim3(256), 0, st, src, dst,
+                                      auto kern = few ? k_keys_scatter<true, true, NoRec> : k_keys_scatter<false, true, NoRec>;
+                                      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, dst,
                                                          pay[from ? 1 : 0], pay[from ? 0 : 1], n_dev, shift, mask, hist, n_tiles,
                                                          static_cast<void *>(nullptr));
                                   });
@@ -207,9 +211,10 @@ int radix_sort_entries(sja_ctx *ctx, hipStream_t st, const Layout &L, const int3
     const int passes = (block_bits + 7) / 8, width = (block_bits + passes - 1) / passes;
     for (int p = 0; p < passes; ++p) {
         const int rc = radix_pass(ctx, st, L, n_dev, n_host, kEntryBlockShift + p * width, width, flip, buf,
-                                  [&](dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
+                                  [&](bool few, dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
                                       const int32_t *hist, int n_tiles) {
-                                      auto kern = p == passes - 1 ? k_keys_scatter<false, REC> : k_keys_scatter<false, NoRec>;
+                                      auto kern = p == passes - 1 ? (few ? k_keys_scatter<true, false, REC> : k_keys_scatter<false, false, REC>)
+                                                                  : (few ? k_keys_scatter<true, false, NoRec> : k_keys_scatter<false, false, NoRec>);
                                       hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, dst,
                                                          static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr),
                                                          n_dev, shift, mask, hist, n_tiles, rec);
@@ -232,9 +237,10 @@ int bits_for(int64_t n)
 // workspace holds) and the caller must take the matrix-scanning rounds.
 int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params,
                        const int32_t *wait, const uint8_t *sla_class, int32_t *grant_job, int32_t *grant_cut,
-                       int64_t *grant_score, int32_t *job_gap, int64_t cap, int32_t result[2], bool *done)
+                       int64_t *grant_score, int32_t *job_gap, int64_t cap, int32_t *rounds_and_stable, bool *done)
 {
     *done = false;
+    int32_t result[2] = {0, 0};
     const int G = ctx->n_gaps, J = ctx->n_jobs;
     const int sub_bound = int(fit_sub_bound(G, J));
     const int lb_bound = int(list_block_bound(G, J));
@@ -259,32 +265,35 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     unsigned long long *ekey[2] = {ws_ptr<unsigned long long>(ctx, L.g_ekey0), ws_ptr<unsigned long long>(ctx, L.g_ekey1)};
 
     // 1. list blocks; reachable atoms per job -> compact atom ids
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, st, counters, int64_t(16), 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3((lb_bound + 2 + 255) / 256), dim3(256), 0, st, list_off, int64_t(lb_bound + 2), 0);
-    hipLaunchKernelGGL(k_list_blocks_count, dim3((sub_bound + 1 + 255) / 256), dim3(256), 0, st, sub_bound + 1, plan, sub_begin,
-                       sub_end, gap_w, lb_off);
-    SJA_HIP(enqueue_scan(st, lb_off, int64_t(sub_bound) + 1, tmp, plan + kPlanListBlocks), "list block scan launch");
     int32_t *pos_block = ws_ptr<int32_t>(ctx, L.g_pos_block), *pos_tab = ws_ptr<int32_t>(ctx, L.g_pos_tab);
     const int32_t *class_begin = ws_ptr<int32_t>(ctx, L.class_begin);
-    const int write_threads = sub_bound > kPosTable ? sub_bound : kPosTable;
-    hipLaunchKernelGGL(k_list_blocks_write, dim3((write_threads + 255) / 256), dim3(256), 0, st, lb_bound, G, plan, class_begin,
-                       sub_begin, sub_end, gap_w, lb_off, lb_begin, lb_end, pos_block, pos_tab);
+    if (sub_bound <= kListBlocksOne) {
+        hipLaunchKernelGGL(k_list_blocks, dim3(1 + kPosTable / 1024), dim3(1024), 0, st, lb_bound, G, plan, class_begin, sub_begin,
+                           sub_end, gap_w, lb_begin, lb_end, pos_block, pos_tab);
+    } else {
+        hipLaunchKernelGGL(k_list_blocks_count, dim3((sub_bound + 1 + 255) / 256), dim3(256), 0, st, sub_bound + 1, plan, sub_begin,
+                           sub_end, gap_w, lb_off);
+        SJA_HIP(enqueue_scan(st, lb_off, int64_t(sub_bound) + 1, tmp, plan + kPlanListBlocks), "list block scan launch");
+        hipLaunchKernelGGL(k_list_blocks_write, dim3((sub_bound + 255) / 256), dim3(256), 0, st, lb_bound, G, plan, class_begin,
+                           sub_begin, sub_end, gap_w, lb_off, lb_begin, lb_end, pos_block, pos_tab);
+    }
     SJA_HIP(hipGetLastError(), "list block launch");
     hipLaunchKernelGGL(k_reach, dim3((J + 1 + 255) / 256), dim3(256), 0, st, J, plan, ncap_tab, abase);
     SJA_HIP(hipGetLastError(), "k_reach launch");
     SJA_HIP(enqueue_scan(st, abase, int64_t(J) + 1, tmp, counters + 2), "atom scan launch");
-    // policy keys of the atoms and the bytes in which they differ (both only need the device-side counts)
-    hipLaunchKernelGGL(k_atom_keys, dim3((J + 3) / 4), dim3(256), 0, st, J, pol, ctx->seg_off, atom_dp,
-                       atom_area_of(ctx, L), abase, wait,
-                       sla_class, key_hi, key_lo, perm[0], info);
-    SJA_HIP(hipGetLastError(), "k_atom_keys launch");
-    hipLaunchKernelGGL(k_key_bits, dim3(256), dim3(256), 0, st, counters + 2, key_hi, key_lo,
+    // policy keys of the atoms and the bytes in which they differ
+    hipLaunchKernelGGL(k_atom_keys, dim3(J < 4 * 4096 ? (J + 3) / 4 : 4096), dim3(256), 0, st, J, pol, ctx->seg_off, atom_dp,
+                       atom_area_of(ctx, L), abase, wait, sla_class, key_hi, key_lo, perm[0], info,
                        reinterpret_cast<unsigned long long *>(counters + 4));
-    SJA_HIP(hipGetLastError(), "k_key_bits launch");
-    int32_t host_plan[kPlanWords] = {0}, host_counters[8] = {0};
-    SJA_HIP(hipMemcpyAsync(host_plan, plan, sizeof(host_plan), hipMemcpyDeviceToHost, st), "plan readback");
-    SJA_HIP(hipMemcpyAsync(host_counters, counters, sizeof(host_counters), hipMemcpyDeviceToHost, st), "count readback");
+    SJA_HIP(hipGetLastError(), "k_atom_keys launch");
+    char host_both[512] = {0};      // the plan, and the counters behind it
+    const size_t apart = L.res_counters - L.plan;
+    static_assert(sizeof(host_both) >= 256 + 64, "plan and counters");
+    SJA_HIP(hipMemcpyAsync(host_both, plan, apart + 64, hipMemcpyDeviceToHost, st), "plan and count readback");
     SJA_HIP(hipStreamSynchronize(st), "count synchronise");
+    int32_t host_plan[kPlanWords], host_counters[8];
+    memcpy(host_plan, host_both, sizeof(host_plan));
+    memcpy(host_counters, host_both + apart, sizeof(host_counters));
     const int64_t n_atoms = host_counters[2];
     const int n_subs = host_plan[kPlanListBlocks];          // list blocks from here on
     if (!host_plan[kPlanTabled] || n_subs > lb_bound || n_atoms > L.atom_cap) return SJA_OK;
@@ -303,7 +312,13 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             return m;
         };
         int rc = SJA_OK;
-        if (params->policy == SJA_POLICY_MIXED) {
+        const bool mixed = params->policy == SJA_POLICY_MIXED;
+        if (n_atoms <= kKeyTile) {
+            hipLaunchKernelGGL(k_sort_one, dim3(1), dim3(kSortOneThreads), 0, st, int(n_atoms), key_lo, mixed ? bytes_of(bits_lo) : 0u,
+                               key_hi, bytes_of(bits_hi), perm[0]);
+            SJA_HIP(hipGetLastError(), "k_sort_one launch");
+        } else {
+        if (mixed) {
             unsigned long long *kb[2] = {key_lo, ekey[0]};
             rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_lo), flip, kb, perm);
             if (rc != SJA_OK) return rc;
@@ -316,6 +331,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         SJA_HIP(hipGetLastError(), "k_gather_keys launch");
         rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), flip, kh, perm);
         if (rc != SJA_OK) return rc;
+        }
     }
 
     // 3. list entries in rank order: counted, then written, then sorted by list block
@@ -355,10 +371,6 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
 
     // 4. rounds
     int32_t *cnt_lost = ws_ptr<int32_t>(ctx, L.g_cnt_lost), *cnt_cand = ws_ptr<int32_t>(ctx, L.g_cnt_cand);
-    const int64_t rounds_cap = int64_t(G < J ? G : J) + 4;
-    hipLaunchKernelGGL(k_fill_i32, dim3(unsigned((rounds_cap + 255) / 256)), dim3(256), 0, st, cnt_lost, rounds_cap, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(unsigned((rounds_cap + 255) / 256)), dim3(256), 0, st, cnt_cand, rounds_cap, 0);
-    SJA_HIP(hipGetLastError(), "counter fill launch");
     const int32_t *gap_order = ws_ptr<int32_t>(ctx, L.gap_order);
     unsigned long long *claim = ws_ptr<unsigned long long>(ctx, L.res_claim);
     int4 *state = ws_ptr<int4>(ctx, L.g_state);
@@ -369,11 +381,6 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     const int held_words = held_bitmap_words(J);
     const bool use_held = held_words <= kHeldMaxWords;
     uint32_t *held = ws_ptr<uint32_t>(ctx, L.g_held);
-    if (use_held) {
-        hipLaunchKernelGGL(k_fill_i32, dim3((2 * held_words + 255) / 256), dim3(256), 0, st,
-                           reinterpret_cast<int32_t *>(held), int64_t(2) * held_words, 0);
-        SJA_HIP(hipGetLastError(), "k_fill_i32 launch");
-    }
     // the block that runs rounds by itself: it needs the held bitmap, a thread per list block, and keys
     // that never fall along a job's atoms (a minimum gain above the distance of two capacities of the
     // hysteresis set can let a longer fit end in a shorter cut); and more than a few rounds, which cost no
@@ -446,7 +453,8 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     }
     hipLaunchKernelGGL(k_grant_finish, dim3(unsigned((int64_t(n_subs) * kWave + 255) / 256)), dim3(256), 0, st, lb_bound, pol,
                        plan, state, lb_begin, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), ctx->seg_off, ws_ptr<int32_t>(ctx, L.n_atoms),
-                       atom_dp, atom_db, atom_area_of(ctx, L), wait, sla_class, grant_job, grant_cut, grant_score, job_gap);
+                       atom_dp, atom_db, atom_area_of(ctx, L), wait, sla_class, grant_job, grant_cut, grant_score, job_gap, result[0],
+                       result[1], rounds_and_stable);
     SJA_HIP(hipGetLastError(), "k_grant_finish launch");
     *done = true;
     return SJA_OK;
@@ -1011,10 +1019,23 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
     unsigned long long *claim = ws_ptr<unsigned long long>(ctx, L.res_claim);
     int32_t *counters = ws_ptr<int32_t>(ctx, L.res_counters);
 
-    const int n_init = G > J ? G : J;
+    ClearList clear{};
+    int n_init = G > J ? G : J;
+    if (G > 0 && J > 0) {
+        auto also = [&, k = 0](size_t off, int64_t n) mutable {
+            clear.p[k] = ws_ptr<int32_t>(ctx, off);
+            clear.n[k++] = int(n);
+            if (n > n_init) n_init = int(n);
+        };
+        also(L.res_counters, 16);
+        also(L.g_list_off, list_block_bound(G, J) + 2);
+        also(L.g_cnt_lost, (G < J ? G : J) + 4);
+        also(L.g_cnt_cand, (G < J ? G : J) + 4);
+        if (held_bitmap_words(J) <= kHeldMaxWords) also(L.g_held, 2 * held_bitmap_words(J));
+    }
     if (n_init > 0) {
         hipLaunchKernelGGL(k_resolve_init, dim3((n_init + 255) / 256), dim3(256), 0, st, G, J, grant_job,
-                           grant_cut, grant_score, job_gap, active, claim);
+                           grant_cut, grant_score, job_gap, active, claim, clear);
         SJA_HIP(hipGetLastError(), "k_resolve_init launch");
     }
     // every round that does not end the process grants at least one job, so it
@@ -1025,10 +1046,14 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
     bool done = false;
     if (G > 0 && J > 0 && ctx->resolve_mode != SJA_RESOLVE_MATRIX) {
         rc = resolve_with_lists(ctx, st, L, params, wait, sla_class, grant_job, grant_cut, grant_score, job_gap, cap,
-                                result, &done);
+                                rounds_used_and_stable, &done);
         if (rc != SJA_OK) return rc;
     }
-    for (int64_t r = 1; !done && r <= cap; ++r) {
+    if (done) {
+        SJA_HIP(hipStreamSynchronize(st), "final synchronise");
+        return SJA_OK;
+    }
+    for (int64_t r = 1; r <= cap; ++r) {
         ++result[0];
         int32_t host_counters[2] = {0, 0};
         if (G > 0) {

@@ -141,6 +141,7 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     L.bits_table = take(size_t(kMaxClasses) * size_t((J + 31) / 32) * 4);
     L.gap_row = take(size_t(G + 16) * 8);
     L.plan = take(kPlanWords * 4);
+    L.res_counters = take(64);             // right behind the plan: read back together
     L.class_begin = take((kMaxClasses + 1) * 4);
     L.class_chunk0 = take((kMaxClasses + 1) * 4);
     L.class_sub0 = take((kMaxClasses + 1) * 4);
@@ -164,7 +165,6 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     L.res_cand_score = take(size_t(G) * 8);
     L.res_active = take(size_t(G));
     L.res_claim = take(size_t(J) * 8);
-    L.res_counters = take(64);
     L.atom_cap = S + 8;
     const size_t lb = size_t(list_block_bound(G, J));
     L.entry_cap = int64_t(ub + 128) * J + 2 * S + 8;

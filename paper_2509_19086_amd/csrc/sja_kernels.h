@@ -915,13 +915,23 @@ __global__ void k_select_reduce(int n_gaps, int n_job_tiles, const SelPartial *_
 // the lowest-index gap that named it, stamped with the round so that no reset
 // is needed), k_commit (winners become grants, losers stay active).
 // --------------------------------------------------------------------------
+// Arrays that start at zero, cleared along with the outputs (a launch each was a sixth of a small resolve).
+struct ClearList {
+    static constexpr int kMost = 5;
+    int32_t *p[kMost];
+    int n[kMost];
+};
+
 __global__ void k_resolve_init(int n_gaps, int n_jobs, int32_t *grant_job, int32_t *grant_cut,
                                int64_t *grant_score, int32_t *job_gap, uint8_t *active,
-                               unsigned long long *claim)
+                               unsigned long long *claim, ClearList clear)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n_gaps) { grant_job[i] = -1; grant_cut[i] = -1; grant_score[i] = 0; active[i] = 1; }
     if (i < n_jobs) { job_gap[i] = -1; claim[i] = 0ull; }
+#pragma unroll
+    for (int k = 0; k < ClearList::kMost; ++k)
+        if (i < clear.n[k]) clear.p[k][i] = 0;
 }
 
 __device__ __forceinline__ unsigned long long claim_word(int round, int g)

@@ -57,3 +57,24 @@ def test_entries_by_groups_of_classes(engine, oracle, classes, all_safe):
     caps = np.sort(rng.choice(np.arange(2000, 150000), size=classes, replace=False)).astype(np.int32)
     wl.C = caps[rng.integers(0, classes, size=700)]
     full_tick_check(engine, oracle, wl, policies=[0, 3], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("n_jobs", [1, 63, 64, 65])
+def test_atoms_around_the_sort_of_one_block(engine, oracle, n_jobs):
+    # every cut of every job can be reached: 64 atoms a job, and one thread block sorts up to 4096
+    wl = make_workload("tiny", n_jobs, n_gaps=70, n_jobs=n_jobs)
+    wl.safe[:] = 1
+    wl.progress[:] = 0
+    wl.C[:] = 40960
+    wl.C[:3] = 20480
+    full_tick_check(engine, oracle, wl, policies=[0, 1, 2, 3], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("n_gaps", [1, 2, 1023, 1025, 4095, 4096, 4097])
+def test_gap_order_at_the_edges_of_a_tile(engine, oracle, n_gaps):
+    # few distinct pairs, so that most are equal and the index decides; the largest pair equals the padding
+    wl = make_workload("tiny", n_gaps, n_gaps=n_gaps, n_jobs=5)
+    rng = np.random.default_rng(n_gaps)
+    wl.W = rng.choice(np.array([50, 51, 700, 2**31 - 1], dtype=np.int32), size=n_gaps)
+    wl.C = rng.choice(np.array([5120, 40960, 2**31 - 1], dtype=np.int32), size=n_gaps)
+    full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
