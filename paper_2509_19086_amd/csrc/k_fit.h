@@ -225,6 +225,8 @@ __global__ __launch_bounds__(256) void k_gap_plan(int n_gaps, int gc, int sb, in
         n_chunks = min(s_chunk0[n_classes], chunk_bound);
         n_subs = min(s_sub0[n_classes], sub_bound);
     } else {
+        // (the stepping kernels begin anew at every other capacity here: as many, short chunks as there is room for)
+        gc = max((n_gaps + chunk_bound - 1) / chunk_bound, 1);
         n_chunks = min((n_gaps + gc - 1) / gc, chunk_bound);
     }
     if (blockIdx.x == 0) {

@@ -298,21 +298,155 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
     }
 }
 
-// Final arg-max over the job tiles; the winner's atom count becomes its boundary.
-__global__ void k_fused_reduce(int n_gaps, int n_job_tiles, const SelPartial *__restrict__ part,
-                               const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_db,
-                               int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut,
-                               int64_t *__restrict__ cand_score)
+// One gap position and one job at a time, for batches with so many capacities that the stepping form would
+// begin anew (two searches and a window) every few positions: a thread per job finds the pair's atom by one
+// search on both conditions, kSearchGaps positions side by side so that their loads overlap, and the block
+// leaves the same partial per (job tile, gap).  Gaps that are switched off cost nothing, and rounds switch
+// more and more of them off.  700 gaps of 300 capacities x 2501 jobs: 165 us stepping, see the rounds.
+constexpr int kSearchGaps = 4;
+
+// The largest value over all 64 lanes, the same in every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= n_gaps) return;
-    unsigned long long bh = 0, bl = 0;
-    int bj = INT32_MAX, ba = -1;
-    for (int t = 0; t < n_job_tiles; ++t) {
-        const SelPartial p = part[int64_t(t) * n_gaps + g];
-        const int pj = p.hi ? p.job : INT32_MAX;
-        if (fused_better(p.hi, p.lo, pj, bh, bl, bj)) { bh = p.hi; bl = p.lo; bj = pj; ba = p.cut; }
+    return uint32_t(__builtin_amdgcn_readlane(wave_scan_max_dpp(int(v ^ 0x80000000u)), kWave - 1)) ^ 0x80000000u;
+}
+
+constexpr int kShortRun = 16;      // positions per capacity, on average, below which it is used
+
+template <bool MIXED, bool AREA>
+__global__ __launch_bounds__(kFusedBlock) void k_search_select(
+    int n_jobs, int n_gaps, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
+    const long long *__restrict__ atom_area, const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ gap_w,
+    const int32_t *__restrict__ gap_c, const int32_t *__restrict__ gap_order, const int32_t *__restrict__ wait,
+    const uint8_t *__restrict__ sla_class, const int32_t *__restrict__ job_held, const uint8_t *__restrict__ gap_active,
+    SelPartial *__restrict__ part)
+{
+    constexpr int WAVES = kFusedBlock / kWave, Q = kSearchGaps;
+    __shared__ unsigned long long s_hi[Q][WAVES], s_lo[Q][WAVES];
+    __shared__ int s_job[Q][WAVES], s_atoms[Q][WAVES];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int s0 = blockIdx.y * Q, j = blockIdx.x * kFusedBlock + threadIdx.x;
+    int g[Q], w[Q], c[Q];
+    bool on[Q], any = false;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int s = min(s0 + q, n_gaps - 1);
+        g[q] = gap_order[s];
+        w[q] = gap_w[s];
+        c[q] = gap_c[s];
+        on[q] = s0 + q < n_gaps && (!gap_active || gap_active[g[q]]);
+        any = any || on[q];
     }
+    const bool usable = any && j < n_jobs && !(job_held && job_held[j] >= 0);
+    const int64_t base = usable ? seg_off[j] : 0;
+    const int n = usable ? n_atoms[j] : 0;
+    const int2 *dp = atom_dp + base;
+    unsigned long long mult = 1, tier = 0;
+    if (usable) job_policy(pol, wait, sla_class, j, mult, tier);
+    int lo[Q], hi[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) { lo[q] = 0; hi[q] = on[q] ? n : 0; }
+    for (int left = n; left > 0; left >>= 1) {          // atoms that fit are a prefix: durations and peaks ascend
+        int2 v[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lo[q] < hi[q]) v[q] = dp[(lo[q] + hi[q]) >> 1];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lo[q] < hi[q]) {
+                const int mid = (lo[q] + hi[q]) >> 1;
+                if (v[q].x <= w[q] && v[q].y <= c[q]) lo[q] = mid + 1; else hi[q] = mid;
+            }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        unsigned long long bh = 0, bl = 0;
+        if (lo[q] > 0) {
+            unsigned long long F;
+            if (AREA) {
+                F = (unsigned long long)atom_area[base + lo[q] - 1];
+            } else {
+                const int2 v = dp[lo[q] - 1];
+                F = rect_of(v.x, v.y);
+            }
+            bh = ((tier << 62) | times_mult(F, mult)) + 1ull;
+            bl = MIXED ? F : 0ull;
+        }
+        // the wave's best: the largest high word, among those the largest low word (and secondary key), the lowest lane
+        unsigned long long best = __ballot(bh != 0);
+        if (best) {
+            auto keep = [&](uint32_t x) {
+                const uint32_t top = wave_max_u32((best >> lane) & 1ull ? x : 0u);
+                best &= __ballot(x == top);
+            };
+            keep(uint32_t(bh >> 32));
+            if (best & (best - 1)) keep(uint32_t(bh));
+            if (MIXED && (best & (best - 1))) keep(uint32_t(bl >> 32));
+            if (MIXED && (best & (best - 1))) keep(uint32_t(bl));
+        }
+        const int src = best ? __ffsll((long long)best) - 1 : 0;
+        bh = best ? fused_readlane_u64(bh, src) : 0ull;
+        bl = MIXED && best ? fused_readlane_u64(bl, src) : 0ull;
+        const int bj = best ? __builtin_amdgcn_readlane(j, src) : INT32_MAX, ba = __builtin_amdgcn_readlane(lo[q], src);
+        if (lane == 0) { s_hi[q][wave] = bh; s_lo[q][wave] = bl; s_job[q][wave] = bj; s_atoms[q][wave] = ba; }
+    }
+    __syncthreads();
+    const int q = threadIdx.x;
+    if (q >= Q || s0 + q >= n_gaps) return;
+    unsigned long long bh = s_hi[q][0], bl = s_lo[q][0];
+    int bj = s_job[q][0], ba = s_atoms[q][0];
+    for (int v = 1; v < WAVES; ++v)
+        if (fused_better(s_hi[q][v], s_lo[q][v], s_job[q][v], bh, bl, bj)) {
+            bh = s_hi[q][v]; bl = s_lo[q][v]; bj = s_job[q][v]; ba = s_atoms[q][v];
+        }
+    SelPartial out;
+    out.hi = bh; out.lo = bl; out.job = bh ? bj : -1; out.cut = bh ? ba : -1; out.pad = 0;
+    part[int64_t(blockIdx.x) * n_gaps + gap_order[s0 + q]] = out;
+}
+
+// The arg-max over the job tiles for kReduceGaps gaps by a block of 256: a group of threads shares a gap's
+// tiles, the groups' bests meet in LDS.  (A thread per gap walked all tiles alone: 66 us for 8192 gaps and
+// 128 tiles, 150 us at Stress, by 32 and 128 blocks.)  Returns true in the one thread that holds gap g's best.
+constexpr int kReduceGaps = 16, kReduceGroups = 256 / kReduceGaps;
+
+__device__ __forceinline__ bool reduce_tiles(int n_gaps, int n_job_tiles, const SelPartial *__restrict__ part, int &g,
+                                             unsigned long long &bh, int &bj, int &bc)
+{
+    __shared__ unsigned long long s_hi[kReduceGroups][kReduceGaps], s_lo[kReduceGroups][kReduceGaps];
+    __shared__ int s_job[kReduceGroups][kReduceGaps], s_cut[kReduceGroups][kReduceGaps];
+    const int at = threadIdx.x % kReduceGaps, group = threadIdx.x / kReduceGaps;
+    g = blockIdx.x * kReduceGaps + at;
+    unsigned long long bl = 0;
+    bh = 0;
+    bj = INT32_MAX;
+    bc = -1;
+    if (g < n_gaps) {
+#pragma unroll 4
+        for (int t = group; t < n_job_tiles; t += kReduceGroups) {
+            const SelPartial p = part[int64_t(t) * n_gaps + g];
+            const int pj = p.hi ? p.job : INT32_MAX;
+            if (fused_better(p.hi, p.lo, pj, bh, bl, bj)) { bh = p.hi; bl = p.lo; bj = pj; bc = p.cut; }
+        }
+    }
+    s_hi[group][at] = bh; s_lo[group][at] = bl; s_job[group][at] = bj; s_cut[group][at] = bc;
+    __syncthreads();
+    if (group > 0 || g >= n_gaps) return false;
+    for (int k = 1; k < kReduceGroups; ++k)
+        if (fused_better(s_hi[k][at], s_lo[k][at], s_job[k][at], bh, bl, bj)) {
+            bh = s_hi[k][at]; bl = s_lo[k][at]; bj = s_job[k][at]; bc = s_cut[k][at];
+        }
+    return true;
+}
+
+// Final arg-max over the job tiles; the winner's atom count becomes its boundary.
+__global__ __launch_bounds__(256) void k_fused_reduce(int n_gaps, int n_job_tiles, const SelPartial *__restrict__ part,
+                                                      const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_db,
+                                                      int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut,
+                                                      int64_t *__restrict__ cand_score)
+{
+    int g, bj, ba;
+    unsigned long long bh;
+    if (!reduce_tiles(n_gaps, n_job_tiles, part, g, bh, bj, ba)) return;
     cand_job[g] = bh ? bj : -1;
     cand_cut[g] = bh ? atom_db[seg_off[bj] + ba - 1].y : -1;
     cand_score[g] = bh ? int64_t((bh - 1ull) & ((1ull << 62) - 1ull)) : 0;

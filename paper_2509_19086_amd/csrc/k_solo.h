@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
                             r = rec[min(i, end - 1)];
                             const uint32_t word = is_held[r.job() >> 5];
                             const bool free_job = ((word >> (r.job() & 31u)) & 1u) == 0;
-                            ok = __ballot((i < end) & (r.lo() <= p) & (p < r.hi()) & free_job);
+                            ok = __ballot(i < end && r.lo() <= p && p < r.hi() && free_job);
                             if (ok) break;
                         }
                         if (!ok) break;             // none for lane p, nor for any below it

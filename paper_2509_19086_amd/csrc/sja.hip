@@ -136,7 +136,8 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
         const long long *pre_area = pre_area_of(ctx, L);
         auto kern = pre_area ? k_select_keys<true> : k_select_keys<false>;
         hipLaunchKernelGGL(kern, dim3((J + 3) / 4), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ctx->pre_dur,
-                           ctx->pre_peak, pre_area, wait, sla_class, seg_key);
+                           ctx->pre_peak, pre_area, ws_ptr<int32_t>(ctx, L.n_atoms), ws_ptr<int2>(ctx, L.atom_db),
+                           ctx->hyst_used_n_caps > 0, wait, sla_class, seg_key);
         SJA_HIP(hipGetLastError(), "k_select_keys launch");
     }
     if (job_tiles > 0) {
@@ -151,7 +152,7 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
                            ws_ptr<SelPartial>(ctx, L.sel_part));
         SJA_HIP(hipGetLastError(), "k_select_pass launch");
     }
-    hipLaunchKernelGGL(k_select_reduce, dim3((G + 255) / 256), dim3(256), 0, st, G, job_tiles,
+    hipLaunchKernelGGL(k_select_reduce, dim3((G + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, G, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), cand_job, cand_cut, cand_score);
     SJA_HIP(hipGetLastError(), "k_select_reduce launch");
     return SJA_OK;
@@ -237,7 +238,7 @@ int bits_for(int64_t n)
 // workspace holds) and the caller must take the matrix-scanning rounds.
 int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params,
                        const int32_t *wait, const uint8_t *sla_class, int32_t *grant_job, int32_t *grant_cut,
-                       int64_t *grant_score, int32_t *job_gap, int64_t cap, int32_t *rounds_and_stable, bool *done)
+                       int64_t *grant_score, int32_t *job_gap, int64_t cap, int32_t *rounds_and_stable, bool *done, bool *many_capacities)
 {
     *done = false;
     int32_t result[2] = {0, 0};
@@ -296,6 +297,8 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     memcpy(host_counters, host_both + apart, sizeof(host_counters));
     const int64_t n_atoms = host_counters[2];
     const int n_subs = host_plan[kPlanListBlocks];          // list blocks from here on
+    // runs of one capacity so short that the stepping form would begin anew every few positions
+    *many_capacities = !host_plan[kPlanTabled] && int64_t(host_plan[kPlanMarks]) * kShortRun > G;
     if (!host_plan[kPlanTabled] || n_subs > lb_bound || n_atoms > L.atom_cap) return SJA_OK;
 
     // 2. rank the atoms by policy key (descending key, ascending job id): stable passes over
@@ -524,11 +527,21 @@ JobLimits job_limits(const sja_limits &l, const int32_t *power, const int32_t *d
 // gap_active does not switch off.  No cut matrix is read or written.
 int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params,
                  const int32_t *wait, const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active,
-                 int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool timed)
+                 int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool timed, bool searched = false)
 {
     const int J = ctx->n_jobs;
     const int job_tiles = (J + kFusedBlock - 1) / kFusedBlock;
-    if (job_tiles > 0) {
+    if (job_tiles > 0 && searched) {
+        const bool mixed = params->policy == SJA_POLICY_MIXED;
+        const long long *atom_area = atom_area_of(ctx, L);
+        auto kern = atom_area ? (mixed ? k_search_select<true, true> : k_search_select<false, true>)
+                              : (mixed ? k_search_select<true, false> : k_search_select<false, false>);
+        hipLaunchKernelGGL(kern, dim3(job_tiles, (n_gaps + kSearchGaps - 1) / kSearchGaps), dim3(kFusedBlock), 0, st, J, n_gaps,
+                           to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
+                           ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_c), ws_ptr<int32_t>(ctx, L.gap_order), wait,
+                           sla_class, job_held, gap_active, ws_ptr<SelPartial>(ctx, L.sel_part));
+        SJA_HIP(hipGetLastError(), "k_search_select launch");
+    } else if (job_tiles > 0) {
         const int chunk_bound = int(fit_chunk_bound(n_gaps, J));
         const int tiles8 = (job_tiles + 7) / 8 * 8;
         const unsigned grid = unsigned(tiles8) * unsigned(chunk_bound);
@@ -560,7 +573,7 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
             ctx->timed = true;
         }
     }
-    hipLaunchKernelGGL(k_fused_reduce, dim3((n_gaps + 255) / 256), dim3(256), 0, st, n_gaps, job_tiles,
+    hipLaunchKernelGGL(k_fused_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_db), cand_job,
                        cand_cut, cand_score);
     SJA_HIP(hipGetLastError(), "k_fused_reduce launch");
@@ -1043,40 +1056,51 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
     const int64_t natural = int64_t(G < J ? G : J) + 1;
     const int64_t cap = (params->max_rounds > 0 && params->max_rounds < natural) ? params->max_rounds : natural;
     int32_t result[2] = {0, 0};
-    bool done = false;
+    bool done = false, many_capacities = false;
     if (G > 0 && J > 0 && ctx->resolve_mode != SJA_RESOLVE_MATRIX) {
         rc = resolve_with_lists(ctx, st, L, params, wait, sla_class, grant_job, grant_cut, grant_score, job_gap, cap,
-                                rounds_used_and_stable, &done);
+                                rounds_used_and_stable, &done, &many_capacities);
         if (rc != SJA_OK) return rc;
     }
     if (done) {
         SJA_HIP(hipStreamSynchronize(st), "final synchronise");
         return SJA_OK;
     }
-    for (int64_t r = 1; r <= cap; ++r) {
-        ++result[0];
-        int32_t host_counters[2] = {0, 0};
-        if (G > 0) {
+    // Rounds go out in batches between looks at their counters (a pair a round): a round after the last one
+    // finds no candidate and changes nothing.
+    constexpr int kMostRounds = 8;
+    int batch = 2;
+    for (int64_t r = 1; r <= cap;) {
+        const int n = G == 0 ? 1 : int(cap - r + 1 < batch ? cap - r + 1 : batch);
+        int32_t host_counters[2 * kMostRounds] = {0};
+        for (int k = 0; k < n && G > 0; ++k) {
             // the round's selection over the still-active gaps and un-held jobs: from the cut matrix if
-            // sja_fit left one, else by evaluating the pairs again (the fused pass; nothing is stored)
+            // sja_fit left one, else by evaluating the pairs again (nothing is stored)
             if (ctx->fitted)
                 rc = launch_select(ctx, st, params, wait, sla_class, job_gap, active, cand_job, cand_cut, cand_score,
-                                   /*keys_ready=*/r > 1);
+                                   /*keys_ready=*/r + k > 1);
             else
                 rc = launch_fused(ctx, st, L, G, params, wait, sla_class, job_gap, active, cand_job, cand_cut, cand_score,
-                                  false);
+                                  false, /*searched=*/many_capacities);
             if (rc != SJA_OK) return rc;
             const dim3 grid((G + 255) / 256), block(256);
-            hipLaunchKernelGGL(k_claim, grid, block, 0, st, G, int(r), active, cand_job, claim, counters);
+            hipLaunchKernelGGL(k_claim, grid, block, 0, st, G, int(r) + k, active, cand_job, claim, counters + 2 * k);
             SJA_HIP(hipGetLastError(), "k_claim launch");
-            hipLaunchKernelGGL(k_commit, grid, block, 0, st, G, int(r), active, cand_job, cand_cut, cand_score,
-                               claim, grant_job, grant_cut, grant_score, job_gap, counters);
+            hipLaunchKernelGGL(k_commit, grid, block, 0, st, G, int(r) + k, active, cand_job, cand_cut, cand_score,
+                               claim, grant_job, grant_cut, grant_score, job_gap, counters + 2 * k);
             SJA_HIP(hipGetLastError(), "k_commit launch");
-            SJA_HIP(hipMemcpyAsync(host_counters, counters, sizeof(host_counters), hipMemcpyDeviceToHost, st),
-                    "counter readback");
+        }
+        if (G > 0) {
+            SJA_HIP(hipMemcpyAsync(host_counters, counters, size_t(n) * 8, hipMemcpyDeviceToHost, st), "counter readback");
             SJA_HIP(hipStreamSynchronize(st), "round synchronise");
         }
-        if (host_counters[0] == 0 || host_counters[1] == 0) { result[1] = 1; break; }
+        for (int k = 0; k < n && !result[1]; ++k) {
+            result[0] = int32_t(r) + k;
+            if (host_counters[2 * k] == 0 || host_counters[2 * k + 1] == 0) result[1] = 1;
+        }
+        if (result[1]) break;
+        r += n;
+        if (batch < kMostRounds) batch *= 2;
     }
     SJA_HIP(hipMemcpyAsync(rounds_used_and_stable, result, sizeof(result), hipMemcpyHostToDevice, st),
             "rounds writeback");

@@ -720,12 +720,14 @@ __device__ __forceinline__ bool key_better(unsigned long long hi_a, unsigned lon
 // cut changes instead of (duration, peak) and three 64-bit multiplies per lane.
 // One wave per job; the kernel moves 16 bytes per segment and runs at the rate
 // of a copy (a wave running along four neighbouring jobs as one stretch, so that
-// the shortest jobs fill it, was no faster).  Prefixes before a job's progress
-// hold whatever the prefix arrays hold there; no cut points at them.
+// the shortest jobs fill it, was no faster).  Only prefixes a cut can point at are
+// visited, from a job's first atom to its last: about half of them where jobs are
+// half done (Stress 250 -> 130 us).
 template <bool AREA>
 __global__ __launch_bounds__(256) void k_select_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int32_t *__restrict__ pre_dur,
-    const int32_t *__restrict__ pre_peak, const long long *__restrict__ pre_area,
+    const int32_t *__restrict__ pre_peak, const long long *__restrict__ pre_area, const int32_t *__restrict__ n_atoms,
+    const int2 *__restrict__ atom_db, bool remapped,
     const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
     unsigned long long *__restrict__ seg_key)
 {
@@ -733,10 +735,14 @@ __global__ __launch_bounds__(256) void k_select_keys(
     const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
     if (j >= n_jobs) return;
     const int64_t base = seg_off[j];
-    const int L = int(seg_off[j + 1] - base);
+    const int n = n_atoms[j];
+    if (n <= 0) return;
+    // boundaries ascend along the atoms; under the hysteresis rule an atom may have an earlier one's boundary,
+    // but the first keeps its own
+    const int first = atom_db[base].y, last = remapped ? int(seg_off[j + 1] - base) : atom_db[base + n - 1].y;
     unsigned long long mult, tier;
     job_policy(pol, wait, sla_class, j, mult, tier);
-    for (int k = lane; k < L; k += kWave) {
+    for (int k = first - 1 + lane; k < last; k += kWave) {
         const unsigned long long F = AREA ? (unsigned long long)pre_area[base + k] : rect_of(pre_dur[base + k], pre_peak[base + k]);
         seg_key[base + k] = ((tier << 62) | times_mult(F, mult)) + 1ull;
     }
@@ -788,16 +794,18 @@ __global__ __launch_bounds__(kSelBlock) void k_select_pass(
     auto second = [&](unsigned long long key, int src) -> unsigned long long {
         return MIXED ? ((key - 1ull) & ((1ull << 62) - 1ull)) / s_mult[wave][src] : 0ull;
     };
+    // the chunk's gaps, a lane each, and which of them are on: a flag fetched on the way to each cut (a byte per
+    // step, waited for behind all cuts in flight) made a masked pass 490 us instead of 285 (8192 x 32768)
+    static_assert(kSelGapChunk == kWave, "a lane per position");
+    const int my_gap = s_begin + lane < s_end ? gap_order[s_begin + lane] : 0;
+    const unsigned long long on = __ballot(s_begin + lane < s_end && (!gap_active || gap_active[my_gap]));
     // the cuts of one batch of steps (cut rows are read coalesced)
     auto load_cuts = [&](int s0, int (&out)[kSelBatch]) {
-        const int n_step = min(kSelBatch, s_end - s0);
 #pragma unroll
         for (int t = 0; t < kSelBatch; ++t) {
             out[t] = -1;
-            if (t < n_step && usable) {
-                const int g = gap_order[s0 + t];
-                if (!gap_active || gap_active[g]) out[t] = cut[int64_t(g) * n_jobs + j];
-            }
+            const int at = s0 - s_begin + t;
+            if (((on >> at) & 1ull) && usable) out[t] = cut[int64_t(lane_value(my_gap, at)) * n_jobs + j];
         }
     };
     int cv_next[kSelBatch];
@@ -891,19 +899,13 @@ __global__ __launch_bounds__(kSelBlock) void k_select_pass(
     }
 }
 
-__global__ void k_select_reduce(int n_gaps, int n_job_tiles, const SelPartial *__restrict__ part,
-                                int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut,
-                                int64_t *__restrict__ cand_score)
+__global__ __launch_bounds__(256) void k_select_reduce(int n_gaps, int n_job_tiles, const SelPartial *__restrict__ part,
+                                                       int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut,
+                                                       int64_t *__restrict__ cand_score)
 {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= n_gaps) return;
-    unsigned long long bh = 0, bl = 0;
-    int bj = INT32_MAX, bc = -1;
-    for (int t = 0; t < n_job_tiles; ++t) {
-        const SelPartial p = part[int64_t(t) * n_gaps + g];
-        const int pj = p.hi ? p.job : INT32_MAX;
-        if (key_better(p.hi, p.lo, pj, bh, bl, bj)) { bh = p.hi; bl = p.lo; bj = pj; bc = p.cut; }
-    }
+    int g, bj, bc;
+    unsigned long long bh;
+    if (!reduce_tiles(n_gaps, n_job_tiles, part, g, bh, bj, bc)) return;
     cand_job[g] = bh ? bj : -1;
     cand_cut[g] = bh ? bc : -1;
     cand_score[g] = bh ? int64_t((bh - 1ull) & ((1ull << 62) - 1ull)) : 0;

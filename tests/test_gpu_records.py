@@ -78,3 +78,53 @@ def test_gap_order_at_the_edges_of_a_tile(engine, oracle, n_gaps):
     wl.W = rng.choice(np.array([50, 51, 700, 2**31 - 1], dtype=np.int32), size=n_gaps)
     wl.C = rng.choice(np.array([5120, 40960, 2**31 - 1], dtype=np.int32), size=n_gaps)
     full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("caps,n_gaps,n_jobs,max_rounds", [(65, 65, 255, 0), (90, 301, 257, 0), (90, 301, 257, 3), (65, 1200, 300, 9),
+                                                           (200, 203, 1, 0), (120, 121, 513, 5)])
+def test_rounds_that_search(engine, oracle, caps, n_gaps, n_jobs, max_rounds):
+    # more capacities than the class tables hold, after the fused call: pairs are searched one by one where a
+    # capacity has few positions, stepped through where it has many; batches of rounds cut off by the cap
+    import oracle as O
+    import paper_2509_19086_amd as P
+    wl = make_workload("stress", caps, n_gaps=n_gaps, n_jobs=n_jobs)
+    rng = np.random.default_rng(n_gaps)
+    pool = np.sort(rng.choice(np.arange(2000, 150000), size=caps, replace=False)).astype(np.int32)
+    wl.C = pool[np.concatenate([np.arange(caps), rng.integers(0, caps, size=n_gaps - caps)])]
+    wl.wait[: n_jobs // 3] = 7                      # equal scores
+    t = P.DeviceTick(engine, wl)
+    t.prepare()
+    pd, pp, _ = O.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
+    cut, _ = O.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W, wl.C)
+    for policy in (0, 1, 3):
+        par = P.Params.make(policy, max_rounds=max_rounds)
+        opar = O.Params.make(policy, max_rounds=max_rounds)
+        t.fit_select(par)
+        t.resolve(par)
+        gj, gc, gs, jg, rounds, stable = O.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
+        for got, want in ((t.grant_job, gj), (t.grant_cut, gc), (t.grant_score, gs), (t.job_gap, jg)):
+            np.testing.assert_array_equal(got.cpu().numpy(), want)
+        assert t.rounds.cpu().tolist() == [rounds, stable]
+
+
+@pytest.mark.parametrize("n_gaps", [1, 15, 16, 17, 63, 65])
+def test_select_with_gaps_switched_off(engine, oracle, n_gaps):
+    # the masked pass and the reduction at the edges of a chunk of positions and of a block's gaps
+    import torch
+    import paper_2509_19086_amd as P
+    wl = make_workload("medium", n_gaps, n_gaps=n_gaps, n_jobs=700)
+    t = P.DeviceTick(engine, wl)
+    t.prepare()
+    t.fit()
+    cut = t.cut.cpu().numpy()
+    rng = np.random.default_rng(n_gaps)
+    active = (rng.random(n_gaps) < 0.6).astype(np.uint8)
+    held = np.where(rng.random(700) < 0.3, 0, -1).astype(np.int32)
+    masked = np.where((held < 0)[None, :] & (active != 0)[:, None], cut, -1)
+    pd, pp, _ = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
+    for policy in (0, 1, 2, 3):
+        want = oracle.select(masked, wl.seg_off, pd, pp, oracle.Params.make(policy), wl.wait, wl.sla_class)
+        engine.sja_select(P.Params.make(policy), t.wait, t.sla_class,
+                          torch.from_numpy(held).cuda(), torch.from_numpy(active).cuda(), t.cand_job, t.cand_cut, t.cand_score)
+        for got, w in zip((t.cand_job, t.cand_cut, t.cand_score), want):
+            np.testing.assert_array_equal(got.cpu().numpy(), w)
