@@ -810,6 +810,73 @@ __global__ __launch_bounds__(kRoundBlock) void k_grant_round(
     }
 }
 
+// Round 1 where the lists are long.  No job is held yet, so a lane's candidate is the first record that covers
+// it, but the lowest lanes' lie tens of thousands of records down (a Large list block: 25 thousand records,
+// 200 us for one wave in k_grant_round).  A thread block per list block: its waves take stretches of
+// kFirstStretch records in turn and note the lowest record per lane; a wave stops once every lane has one
+// before its next stretch.  Leaves state and claims as k_grant_round does for round 1.
+constexpr int kFirstThreads = 1024, kFirstStretch = 4 * kWave;
+constexpr int kFirstLong = 1024;         // records per list, on average, from which it pays (4 us launched)
+
+template <typename REC>
+__global__ __launch_bounds__(kFirstThreads) void k_grant_first(
+    int4 *state, const int32_t *__restrict__ list_off, const REC *__restrict__ rec, unsigned long long *claim, uint32_t *held_next,
+    const int32_t *__restrict__ lb_begin, const int32_t *__restrict__ lb_end, const int32_t *__restrict__ gap_order,
+    int32_t *cnt_cand)
+{
+    __shared__ int s_first[kWave];
+    const int u = blockIdx.x, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int begin = list_off[u], end = list_off[u + 1], b0 = lb_begin[u], len = lb_end[u] - b0;
+    if (threadIdx.x < kWave) s_first[lane] = lane < len ? INT32_MAX : -1;
+    __syncthreads();
+    for (int64_t c64 = int64_t(begin) + wave * kFirstStretch; c64 < end; c64 += kFirstThreads / kWave * kFirstStretch) {
+        const int c = int(c64);
+        unsigned long long without = __ballot(s_first[lane] > c);       // lanes with no record before this stretch
+        if (!without) break;
+        REC r[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = rec[min(c64 + k * kWave + lane, int64_t(end) - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int width = r[k].hi() - r[k].lo();
+            const unsigned long long mine = width > 0 ? (~0ull >> (kWave - width)) << r[k].lo() : 0ull;
+            unsigned long long hits = __ballot(c64 + k * kWave + lane < end && (mine & without) != 0);
+            while (hits) {
+                const int t = __ffsll((long long)hits) - 1;
+                hits &= hits - 1;
+                const REC x = r[k].of_lane(t);
+                const bool takes = ((without >> lane) & 1ull) && lane >= x.lo() && lane < x.hi();
+                if (takes) atomicMin(&s_first[lane], c + k * kWave + t);
+                without &= ~__ballot(takes);
+            }
+        }
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    const int first = s_first[lane];
+    const bool valid = lane < len, cand = valid && first != INT32_MAX;
+    const int g = valid ? gap_order[b0 + lane] : 0;
+    const int job = cand ? int(rec[first].job()) : -1;
+    state[u * kWave + lane] = cand ? make_int4(first + 1, job, 0, g << 2) : make_int4(end, -1, 0, (g << 2) | 2);
+    if (__ballot(cand) && lane == 0) cnt_cand[1] = 1;
+    auto send = [&](int j, int low) {
+        atomicMax(&claim[j], claim_of(1, low));
+        if (held_next) atomicOr(&held_next[uint32_t(j) >> 5], 1u << (uint32_t(j) & 31u));
+    };
+    unsigned long long todo = __ballot(cand);
+    for (int turn = 0; todo; ++turn) {
+        if (turn == kClaimTurns) {
+            if ((todo >> lane) & 1ull) send(job, g);
+            break;
+        }
+        const int leader = __ffsll((long long)todo) - 1;
+        const bool same = cand && job == __builtin_amdgcn_readlane(job, leader);
+        const int low = wave_min_dpp(same ? g : 0x7fffffff);
+        if (lane == leader) send(job, low);
+        todo &= ~__ballot(same);
+    }
+}
+
 // Gap positions that are neither granted nor out of candidates.  Every round that
 // does not end the process grants at least one of them, so this bounds the rounds
 // that can still follow; the host sizes its next batch of launches with it.

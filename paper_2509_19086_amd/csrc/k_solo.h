@@ -28,13 +28,14 @@
 namespace sja {
 
 constexpr int kSoloMaxWaves = 16;
-constexpr int kSoloMinWaves = 4;        // one per SIMD: list blocks in pieces are served by several waves side by side
+constexpr int kSoloMinWaves = 8;        // list blocks in pieces are served by several waves side by side (4: 4 % slower, 16: 5 %)
+constexpr int kSoloSmallBlocks = 128;   // list blocks whose gap orders are kept in LDS
 constexpr int kSoloMaxBlocks = kSoloMaxWaves * kWave;
 constexpr int kSoloFirstRounds = 4;     // launched rounds before the block first takes over
 constexpr int kSoloFewRounds = 16;      // rounds it takes over at least, if the caller bounds them
 constexpr int kSoloTable = 2048;        // claim words: one per job named in a round (power of two)
-constexpr int kSoloFewLooking = 4;      // lanes still looking that the wave serves together
-constexpr int kSoloEasyPieces = 8;      // pieces per wave and round that cost no more than a launched round
+constexpr int kSoloSteps = 3;           // steps of eight records before a lane still looking alone is served by its wave
+constexpr int kSoloEasyPieces = 4;      // pieces per wave and round that cost no more than a launched round
 constexpr int kSoloPatience = 96;       // pieces beyond that, summed up, after which the block stops
 enum { kSoloDone = 0, kSoloRounds = 1, kSoloStable = 2 };
 
@@ -89,6 +90,9 @@ __device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long
 // instructions: what a thread tests every round (eight records' held bits) is prepared when the records
 // arrive or its highest open lane changes.  The held jobs are two bitmaps: a round reads one and marks the
 // jobs it names in the other, and in the first one round later.
+// SMALL: at most kSoloSmallBlocks list blocks, whose lanes' gap orders fit LDS (in global memory the next
+// entry's load is waited for together with the records that were asked for last).
+template <bool SMALL>
 __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     int4 *state, const int32_t *__restrict__ list_off, const Rec32 *__restrict__ rec, unsigned long long *claim, int after,
     int first_check, int cap, int n_lb, int held_words, uint32_t *held, const int32_t *__restrict__ cnt_lost,
@@ -102,6 +106,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     // by round stamp: somebody claims, a wave gives up, (round << 8 | most pieces of a wave), open lanes found nothing more
     __shared__ int4 s_ctl[2];
     __shared__ int s_flag;
+    __shared__ int s_order[SMALL ? kSoloSmallBlocks * kWave : 1];      // per list block its open lanes, lowest gap first: gap << 6 | lane
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int threads = blockDim.x, waves = threads / kWave;
     // neighbouring list blocks split in the same rounds: they go to different waves
@@ -135,7 +140,10 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
             int place = 0;
             for (unsigned long long m = on; m; m &= m - 1)
                 place += __builtin_amdgcn_readlane(g, __ffsll((long long)m) - 1) < g;
-            if ((on >> lane) & 1ull) state[slot0 + place].z = (g << 6) | lane;
+            if ((on >> lane) & 1ull) {
+                if (SMALL) s_order[SMALL ? slot0 + place : 0] = (g << 6) | lane;
+                else state[slot0 + place].z = (g << 6) | lane;
+            }
             const int e_top = __builtin_amdgcn_readlane(raw.x, on ? 63 - __clzll((long long)on) : 0);
             if (lane == i) { open = on; e = e_top; }
         }
@@ -178,6 +186,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         take(0, r, w0, e);
         take(1, r2, w0 + 4, e);
     };
+    auto order_at = [&](int k) { return SMALL ? s_order[SMALL ? u * kWave + min(k, kWave - 1) : 0] : state[u * kWave + min(k, kWave - 1)].z; };
     auto closed = [&]() {       // lanes were closed: the ends, what covers the highest, the lowest gap
         const int was = top;
         if (!open) { low_gap = -1; return; }
@@ -189,16 +198,16 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         while (!((open >> low_lane) & 1ull) && order <= kWave) {
             low_gap = next_low >> 6; low_lane = next_low & 63;
             ++order;
-            next_low = state[u * kWave + min(order, kWave - 1)].z;
+            next_low = order_at(order);
         }
     };
 #pragma unroll
     for (int q = 0; q < 8; ++q) { w[q] = 0; job_of[q] = nobody; }
     if (open) {
-        const int first = state[u * kWave].z;
+        const int first = order_at(0);
         low_gap = first >> 6; low_lane = first & 63;
         order = 1;
-        next_low = state[u * kWave + 1].z;
+        next_low = order_at(1);
         ends();
         window();
     }
@@ -277,7 +286,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
             have = have | found;
             looking = looking & !found;
             const unsigned long long look = __ballot(looking);
-            if (!look || (step >= 1 && __popcll(look) <= kSoloFewLooking)) break;
+            if (!look || (step >= kSoloSteps && (look & (look - 1)) == 0)) break;
         }
         found = have;
         const bool split = found & (lo > bottom);

@@ -393,8 +393,20 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         rising = rising && int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] >= ctx->hyst_used_min_gain;
     const bool solo = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks && cap >= kSoloFirstRounds + kSoloFewRounds;
     const int solo_waves = (n_subs + kWave - 1) / kWave > kSoloMinWaves ? (n_subs + kWave - 1) / kWave : kSoloMinWaves;
+    const bool long_lists = n_entries >= int64_t(kFirstLong) * n_subs;
     auto launch_round = [&](int64_t k, int propose) {
         const bool with_bitmap = use_held && (solo || k <= kHeldRounds);
+        if (k == 1 && long_lists && propose) {
+            auto first = [&](auto kern, auto *records) {        // (round 1 marks the bitmap that round 2 reads)
+                hipLaunchKernelGGL(kern, dim3(n_subs), dim3(kFirstThreads), 0, st, state, list_off, records, claim,
+                                   with_bitmap ? held : static_cast<uint32_t *>(nullptr), lb_begin, lb_end, gap_order, cnt_cand);
+            };
+            if (wide_records)
+                first(k_grant_first<Rec64>, static_cast<const Rec64 *>(rec));
+            else
+                first(k_grant_first<Rec32>, static_cast<const Rec32 *>(rec));
+            return hipGetLastError();
+        }
         auto go = [&](auto kern, auto *records) {
             hipLaunchKernelGGL(kern, dim3(round_grid), dim3(kRoundBlock), 0, st, state, list_off, records, claim, int(k), propose, n_subs,
                                with_bitmap ? held_words : 0, with_bitmap ? held : static_cast<uint32_t *>(nullptr), lb_begin,
@@ -416,7 +428,8 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         if (batch < 1024) batch *= solo ? 4 : 2;
         for (int64_t k = launched + 1; k <= upto; ++k) SJA_HIP(launch_round(k, 1), "k_grant_round launch");
         if (solo && upto < cap) {
-            hipLaunchKernelGGL(k_grant_solo, dim3(1), dim3(solo_waves * kWave), 0, st, state, list_off, static_cast<const Rec32 *>(rec),
+            auto solo_kern = n_subs <= kSoloSmallBlocks ? k_grant_solo<true> : k_grant_solo<false>;
+            hipLaunchKernelGGL(solo_kern, dim3(1), dim3(solo_waves * kWave), 0, st, state, list_off, static_cast<const Rec32 *>(rec),
                                claim, int(upto), int(next_check), int(cap), n_subs, held_words, held, cnt_lost, cnt_cand,
                                counters + 8);
             SJA_HIP(hipGetLastError(), "k_grant_solo launch");
