@@ -418,6 +418,40 @@ __global__ __launch_bounds__(kSortOneThreads) void k_sort_one(int n, const unsig
         if (first + c * kWave < n) perm[first + c * kWave] = pay[c];
 }
 
+// Two keys per item, sorted by the first only: puts the items whose first keys are equal in the order of their
+// second keys (stable).  Equal first keys are rare accidents (two jobs' products) where there is a second key at
+// all, so this replaces five or six passes over it; a run of more than kTieRun that is out of order sets *flag,
+// and the caller sorts by both keys after all.
+constexpr int kTieRun = 32;
+
+__global__ __launch_bounds__(256) void k_fix_ties(const int32_t *n_ptr, const unsigned long long *__restrict__ keys,
+                                                  const unsigned long long *__restrict__ second, uint32_t *perm, int32_t *flag)
+{
+    const int64_t n = *n_ptr, i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const unsigned long long key = keys[i];
+    const bool tied = i > 0 && keys[i - 1] == key;
+    if (tied) {
+        // beyond the part of a long run that its first item's thread looks at (such a run is never reordered here)
+        if (i > kTieRun && keys[i - kTieRun - 1] == key && second[perm[i - 1]] > second[perm[i]]) *flag = 1;
+        return;
+    }
+    if (i + 1 >= n || keys[i + 1] != key) return;
+    int64_t e = i + 1;
+    while (e < n && e - i <= kTieRun && keys[e] == key) ++e;
+    bool ordered = true;
+    for (int64_t k = i + 1; k < e; ++k) ordered = ordered && second[perm[k - 1]] <= second[perm[k]];
+    if (ordered) return;
+    if (e - i > kTieRun) { *flag = 1; return; }
+    for (int64_t k = i + 1; k < e; ++k) {
+        const uint32_t a = perm[k];
+        const unsigned long long v = second[a];
+        int64_t at = k;
+        for (; at > i && second[perm[at - 1]] > v; --at) perm[at] = perm[at - 1];
+        perm[at] = a;
+    }
+}
+
 // out[i] = keys[idx[i]]: the keys of a permutation, laid out in its order.
 __global__ void k_gather_keys(const int32_t *n_ptr, const unsigned long long *__restrict__ keys,
                               const uint32_t *__restrict__ idx, unsigned long long *__restrict__ out)

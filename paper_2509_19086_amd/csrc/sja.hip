@@ -250,6 +250,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     int32_t *abase = ws_ptr<int32_t>(ctx, L.g_abase);
     int32_t *tmp = ws_ptr<int32_t>(ctx, L.g_scan_tmp);
     int32_t *counters = ws_ptr<int32_t>(ctx, L.res_counters);      // [0..1] entries (64 bit), [2] atoms, [4..7] key bits
+    constexpr int kCountTies = 13;
     int32_t *list_off = ws_ptr<int32_t>(ctx, L.g_list_off);
     const int2 *atom_dp = ws_ptr<int2>(ctx, L.atom_dp);
     const int2 *atom_db = ws_ptr<int2>(ctx, L.atom_db);
@@ -283,10 +284,13 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     SJA_HIP(hipGetLastError(), "k_reach launch");
     SJA_HIP(enqueue_scan(st, abase, int64_t(J) + 1, tmp, counters + 2), "atom scan launch");
     // policy keys of the atoms and the bytes in which they differ
-    hipLaunchKernelGGL(k_atom_keys, dim3(J < 4 * 4096 ? (J + 3) / 4 : 4096), dim3(256), 0, st, J, pol, ctx->seg_off, atom_dp,
-                       atom_area_of(ctx, L), abase, wait, sla_class, key_hi, key_lo, perm[0], info,
-                       reinterpret_cast<unsigned long long *>(counters + 4));
-    SJA_HIP(hipGetLastError(), "k_atom_keys launch");
+    auto launch_keys = [&]() {
+        hipLaunchKernelGGL(k_atom_keys, dim3(J < 4 * 4096 ? (J + 3) / 4 : 4096), dim3(256), 0, st, J, pol, ctx->seg_off, atom_dp,
+                           atom_area_of(ctx, L), abase, wait, sla_class, key_hi, key_lo, perm[0], info,
+                           reinterpret_cast<unsigned long long *>(counters + 4));
+        return hipGetLastError();
+    };
+    SJA_HIP(launch_keys(), "k_atom_keys launch");
     char host_both[512] = {0};      // the plan, and the counters behind it
     const size_t apart = L.res_counters - L.plan;
     static_assert(sizeof(host_both) >= 256 + 64, "plan and counters");
@@ -302,10 +306,12 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     if (!host_plan[kPlanTabled] || n_subs > lb_bound || n_atoms > L.atom_cap) return SJA_OK;
 
     // 2. rank the atoms by policy key (descending key, ascending job id): stable passes over
-    //    (inverted key, atom id) pairs, the secondary key first; the entry buffers serve as the
-    //    second key buffer, they are not in use yet
+    //    (inverted key, atom id) pairs; the entry buffers serve as second key buffers, they are
+    //    not in use yet.  A secondary key only orders equal primary ones: the pairs are sorted by
+    //    the primary key and their ties put in order; `both`: by the secondary key first
+    const bool mixed = params->policy == SJA_POLICY_MIXED;
     bool flip = false;      // where the atom ids are: perm[flip]
-    if (n_atoms > 0) {
+    auto rank_atoms = [&](bool both) -> int {
         unsigned long long bits_hi = 0, bits_lo = 0;
         memcpy(&bits_hi, host_counters + 4, 8);
         memcpy(&bits_lo, host_counters + 6, 8);
@@ -314,31 +320,35 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             for (int b = 0; b < 8; ++b) if ((v >> (8 * b)) & 0xffull) m |= 1u << b;
             return m;
         };
-        int rc = SJA_OK;
-        const bool mixed = params->policy == SJA_POLICY_MIXED;
+        const dim3 grid(unsigned((n_atoms + 255) / 256)), block(256);
+        flip = false;
         if (n_atoms <= kKeyTile) {
             hipLaunchKernelGGL(k_sort_one, dim3(1), dim3(kSortOneThreads), 0, st, int(n_atoms), key_lo, mixed ? bytes_of(bits_lo) : 0u,
                                key_hi, bytes_of(bits_hi), perm[0]);
             SJA_HIP(hipGetLastError(), "k_sort_one launch");
-        } else {
-        if (mixed) {
-            unsigned long long *kb[2] = {key_lo, ekey[0]};
-            rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_lo), flip, kb, perm);
-            if (rc != SJA_OK) return rc;
+            return SJA_OK;
         }
+        if (!both) {
+            unsigned long long *kb[2] = {key_hi, ekey[0]};
+            const int rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), flip, kb, perm);
+            if (rc != SJA_OK || !mixed) return rc;
+            hipLaunchKernelGGL(k_fix_ties, grid, block, 0, st, counters + 2, kb[flip ? 1 : 0], key_lo, perm[flip ? 1 : 0],
+                               counters + kCountTies);
+            SJA_HIP(hipGetLastError(), "k_fix_ties launch");
+            return SJA_OK;
+        }
+        unsigned long long *kb[2] = {key_lo, ekey[0]};
+        const int rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_lo), flip, kb, perm);
+        if (rc != SJA_OK) return rc;
         // the primary keys in the order reached so far
         unsigned long long *kh[2] = {ekey[1], ekey[0]};
         if (flip) { kh[0] = ekey[0]; kh[1] = ekey[1]; }      // buffer index must follow the id buffers
-        hipLaunchKernelGGL(k_gather_keys, dim3(unsigned((n_atoms + 255) / 256)), dim3(256), 0, st, counters + 2, key_hi,
-                           perm[flip ? 1 : 0], kh[flip ? 1 : 0]);
+        hipLaunchKernelGGL(k_gather_keys, grid, block, 0, st, counters + 2, key_hi, perm[flip ? 1 : 0], kh[flip ? 1 : 0]);
         SJA_HIP(hipGetLastError(), "k_gather_keys launch");
-        rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), flip, kh, perm);
-        if (rc != SJA_OK) return rc;
-        }
-    }
+        return radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), flip, kh, perm);
+    };
 
     // 3. list entries in rank order: counted, then written, then sorted by list block
-    const uint32_t *ranked = perm[flip ? 1 : 0];
     constexpr int waves_per_block = kEntryThreads / kWave;
     // windows in LDS: a block with 32768 of them has a compute unit to itself
     const bool in_lds = n_subs <= kEntryBlocks && G <= kEntryWinBig, small = in_lds && G <= kEntryWinSmall;
@@ -349,17 +359,29 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         auto kern = small ? k_list_entries<decltype(emit)::value, kEntryWinSmall>
                           : in_lds ? k_list_entries<decltype(emit)::value, kEntryWinBig> : k_list_entries<decltype(emit)::value, 0>;
         hipLaunchKernelGGL(kern, dim3(entry_grid), dim3(kEntryThreads), 0, st, int(n_atoms), n_subs, G, plan,
-                           class_begin, lb_begin, pos_block, pos_tab, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), ranked, info, chunk_at,
+                           class_begin, lb_begin, pos_block, pos_tab, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), perm[flip ? 1 : 0], info, chunk_at,
                            list_off, reinterpret_cast<unsigned long long *>(counters), ekey[0]);
         return hipGetLastError();
     };
-    if (n_atoms > 0) {
-        SJA_HIP(launch_entries(std::false_type{}), "k_list_entries launch");
-        SJA_HIP(enqueue_scan(st, chunk_at, n_chunks, tmp, nullptr), "entry scan launch");
-    }
     long long n_entries = 0;
-    SJA_HIP(hipMemcpyAsync(&n_entries, counters, sizeof(n_entries), hipMemcpyDeviceToHost, st), "entry count readback");
-    SJA_HIP(hipStreamSynchronize(st), "entry count synchronise");
+    for (bool both = false;; both = true) {
+        if (n_atoms > 0) {
+            const int rc = rank_atoms(both);
+            if (rc != SJA_OK) return rc;
+            SJA_HIP(launch_entries(std::false_type{}), "k_list_entries launch");
+            SJA_HIP(enqueue_scan(st, chunk_at, n_chunks, tmp, nullptr), "entry scan launch");
+        }
+        int32_t h[kCountTies + 1] = {0};
+        SJA_HIP(hipMemcpyAsync(h, counters, sizeof(h), hipMemcpyDeviceToHost, st), "entry count readback");
+        SJA_HIP(hipStreamSynchronize(st), "entry count synchronise");
+        memcpy(&n_entries, h, sizeof(n_entries));
+        if (!h[kCountTies]) break;
+        // a long run of equal primary keys out of order: once more, by both keys
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, st, counters, int64_t(2), 0);
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, st, counters + kCountTies, int64_t(1), 0);
+        hipLaunchKernelGGL(k_fill_i32, dim3((lb_bound + 2 + 255) / 256), dim3(256), 0, st, list_off, int64_t(lb_bound + 2), 0);
+        SJA_HIP(launch_keys(), "k_atom_keys launch");
+    }
     if (n_entries > L.entry_cap || n_entries >= (1ll << 31)) return SJA_OK;
     SJA_HIP(enqueue_scan(st, list_off, int64_t(lb_bound) + 2, tmp, nullptr), "list offset scan launch");
     void *rec = ws_ptr<void>(ctx, L.g_rec);

@@ -128,3 +128,20 @@ def test_select_with_gaps_switched_off(engine, oracle, n_gaps):
                           torch.from_numpy(held).cuda(), torch.from_numpy(active).cuda(), t.cand_job, t.cand_cut, t.cand_score)
         for got, w in zip((t.cand_job, t.cand_cut, t.cand_score), want):
             np.testing.assert_array_equal(got.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("jobs_per_run", [2, 16, 33, 150])
+def test_equal_scores_ordered_by_the_second_key(engine, oracle, jobs_per_run):
+    # MIXED: jobs whose F x multiplier is equal while F is not, in runs shorter and longer than those put in
+    # order in place, the smaller F first; enough other atoms that the sort is not one block's
+    wl = make_workload("small", jobs_per_run, n_gaps=150, n_jobs=1200)
+    wl.safe[:] = 1
+    wl.sla_class[:] = 1
+    wl.progress[:] = 0
+    n = jobs_per_run
+    L = int(wl.seg_off[1])
+    for j in range(n):
+        a = int(wl.seg_off[j])
+        wl.dur[a:a + L], wl.mem[a:a + L] = 1, 512 if j % 2 == 0 else 1024        # key 512 * 2000 == 1024 * 1000 per tick
+        wl.wait[j] = 1000 if j % 2 == 0 else 0
+    full_tick_check(engine, oracle, wl, policies=[3], resolve_modes=(0,))

@@ -25,7 +25,7 @@ def test_caps_around_the_hand_over(engine, oracle, max_rounds):
     full_tick_check(engine, oracle, wl, policies=[0, 3], resolve_modes=(0,))
 
 
-@pytest.mark.parametrize("name,gaps,jobs", [("stress", 900, 700), ("stress", 700, 1500), ("large", 1025, 513), ("small", 65, 4000),
+@pytest.mark.parametrize("name,gaps,jobs", [("stress", 900, 700), ("stress", 700, 1500), ("stress", 130, 3000), ("large", 70, 5000), ("large", 1025, 513), ("small", 65, 4000),
                                             ("medium", 1400, 40), ("tiny", 3, 700)])
 def test_many_pieces_and_lists_that_run_dry(engine, oracle, name, gaps, jobs):
     wl = make_workload(name, gaps + jobs, n_gaps=gaps, n_jobs=jobs)
