@@ -302,7 +302,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
 // begin anew (two searches and a window) every few positions: a thread per job finds the pair's atom by one
 // search on both conditions, kSearchGaps positions side by side so that their loads overlap, and the block
 // leaves the same partial per (job tile, gap).  Gaps that are switched off cost nothing, and rounds switch
-// more and more of them off.  700 gaps of 300 capacities x 2501 jobs: 165 us stepping, see the rounds.
+// more and more of them off.  700 gaps of 300 capacities x 2501 jobs: 165 us a round stepping, 47 us so.
 constexpr int kSearchGaps = 4;
 
 // The largest value over all 64 lanes, the same in every lane.

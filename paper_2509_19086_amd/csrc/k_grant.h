@@ -19,9 +19,11 @@
 //      atomicMax of (round, ~gap index), the claims of a thread block merged
 //      first; the next round's kernel first checks who won.  Claims carry the
 //      round number, so nothing is ever reset and a claim made in the current
-//      round is not mistaken for a hold.  In the early rounds, where lanes
-//      pass hundreds of records of jobs that were just taken, the waves
-//      also keep the held jobs as a bitmap (see grant_step).
+//      round is not mistaken for a hold.  Where lanes pass hundreds of
+//      records of jobs that were just taken, the waves also keep the held
+//      jobs as a bitmap (see grant_step).  Round 1 of long lists has a kernel
+//      of its own (k_grant_first), and most rounds run in one thread block
+//      (k_grant_solo).
 #pragma once
 
 #include "k_sort.h"

@@ -8,7 +8,10 @@
 // Here ONE block runs round after round: a thread per list block, which keeps
 // its open lanes, its place in the list and its lowest open gap in registers;
 // the held jobs (a bitmap) and the round's claims (a small hash table) live in
-// LDS, and a round has a single barrier.
+// LDS, and a round has a single barrier.  A round takes 1.7 us at Medium (66
+// list blocks) and 2.7 at Stress (566), by its instructions, LDS trips and the
+// hand-overs between the scalar and the vector side: 440 instructions a wave.
+// Medium tick 4586 -> 2220 us, Stress 62.8 -> 56.3 ms when it came.
 //
 // What a thread relies on: along the positions of a list block a job's key
 // never falls (F grows with the cut; the host sees to it where the hysteresis

@@ -178,8 +178,8 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     L.g_perm1 = take(ac * 4);
     L.g_info = take(ac * 16);
     L.g_chunk_at = take((ac / kWave + 1) * 4);
-    L.g_pos_block = take(size_t(G) * 4);
-    L.g_pos_tab = take(G > 0 ? 2048 * 4 : 0);
+    L.g_pos_block = L.gap_tile_key;        // the sorted tiles are done with once the gaps are ranked
+    L.g_pos_tab = L.gap_tile_idx;
     L.g_hist = take(hist_ints * 4);
     L.g_ekey0 = take(ec * 8);
     L.g_ekey1 = take(ec * 8);
