@@ -52,9 +52,9 @@ def secondary_rates(wl, n_atoms_total, call_ms, rounds):
 # sources are hashed, and a different hash means the counters are stale.
 FIT_TRAFFIC = {
     "workload": ("stress", 0),
-    "sources_sha256": "c8e03b40c653190bbaddc66b9dce349b1f4f729e9d9c9efb8aebfc76fe43d981",
-    "fetch_kib": 51530.1, "fetch_scale": 2.0,
-    "write_kib": 8391936.0, "write_scale": 1.0,
+    "sources_sha256": "8f500af28be055d6e56be34c42cf16eb7ca44503498ad0cc0e6a3f8285d75b58",
+    "fetch_kib": 51419.6, "fetch_scale": 2.0,
+    "write_kib": 8391835.9, "write_scale": 1.0,
 }
 
 
