@@ -7,10 +7,11 @@
 // (state, records, claim words) and 1.3 us more until the next launch.
 // Here ONE block runs round after round: a thread per list block, which keeps
 // its open lanes, its place in the list and its lowest open gap in registers;
-// the held jobs (a bitmap) and the round's claims (a small hash table) live in
-// LDS, and a round has a single barrier.  A round takes 1.7 us at Medium (66
-// list blocks) and 2.7 at Stress (566), by its instructions, LDS trips and the
-// hand-overs between the scalar and the vector side: 440 instructions a wave.
+// the held jobs (a bitmap) and the claims (two small hash tables, by turns of
+// the rounds) live in LDS, and a round has a single barrier.  A round takes
+// 1.7 us at Medium (66 list blocks) and 2.7 at Stress (566), by its
+// instructions, LDS trips and the hand-overs between the scalar and the vector
+// side: 440 instructions a wave.
 // Medium tick 4586 -> 2220 us, Stress 62.8 -> 56.3 ms when it came.
 //
 // What a thread relies on: along the positions of a list block a job's key
@@ -26,6 +27,7 @@
 // leaves the gaps' state as the round kernel expects it.
 #pragma once
 
+#include "k_claims.h"
 #include "k_grant.h"
 
 namespace sja {
@@ -36,47 +38,10 @@ constexpr int kSoloSmallBlocks = 128;   // list blocks whose gap orders are kept
 constexpr int kSoloMaxBlocks = kSoloMaxWaves * kWave;
 constexpr int kSoloFirstRounds = 4;     // launched rounds before the block first takes over
 constexpr int kSoloFewRounds = 16;      // rounds it takes over at least, if the caller bounds them
-constexpr int kSoloTable = 2048;        // claim words: one per job named in a round (power of two)
 constexpr int kSoloSteps = 3;           // steps of eight records before a lane still looking alone is served by its wave
 constexpr int kSoloEasyPieces = 4;      // pieces per wave and round that cost no more than a launched round
 constexpr int kSoloPatience = 96;       // pieces beyond that, summed up, after which the block stops
 enum { kSoloDone = 0, kSoloRounds = 1, kSoloStable = 2 };
-
-// A claim: round (24 bits) : job (20) : inverted gap (20).  A word of an earlier round is told from a
-// current one by its stamp, so nothing is ever cleared.
-__device__ __forceinline__ unsigned long long solo_word(int round, int job, int g)
-{
-    return (static_cast<unsigned long long>(uint32_t(round)) << 40) | (static_cast<unsigned long long>(uint32_t(job)) << 20) |
-           (0xfffffu - uint32_t(g));
-}
-
-// Enters a claim in the table.  The larger of two words keeps a slot and the other one moves on, so all
-// claims for a job end in one slot, the first from the job's own whose word is not larger, with the lowest gap.
-__device__ __forceinline__ bool solo_enter(unsigned long long *tab, unsigned long long v)
-{
-    int h = int(v >> 20) & (kSoloTable - 1);
-#pragma unroll 1
-    for (int tries = 0; tries < kSoloTable; ++tries) {
-        const unsigned long long old = atomicMax(&tab[h], v);
-        if (__builtin_expect((old >> 40) != (v >> 40) || ((old ^ v) >> 20) == 0, 1)) return true;
-        v = min(old, v);
-        h = (h + 1) & (kSoloTable - 1);
-    }
-    return false;           // no slot left: the round is given up
-}
-
-// Whether the claim `v` is the one that stands for its job, once all claims of the round are in.
-__device__ __forceinline__ bool solo_wins(const unsigned long long *tab, unsigned long long v)
-{
-    int h = int(v >> 20) & (kSoloTable - 1);
-    unsigned long long x = tab[h];
-#pragma unroll 1
-    for (int tries = 1; __builtin_expect(((x ^ v) >> 20) != 0, 0) && tries < kSoloTable; ++tries) {
-        h = (h + 1) & (kSoloTable - 1);
-        x = tab[h];
-    }
-    return x == v;
-}
 
 __device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long v, int l)
 {
@@ -102,7 +67,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     const int32_t *__restrict__ cnt_cand, int32_t *out)
 {
     __shared__ uint32_t s_held[2][kHeldMaxWords + 4];           // the word behind the last job's is all ones: nobody's job
-    __shared__ unsigned long long s_tab[kSoloTable];
+    __shared__ SoloTables s_tabs;       // the claims of this round and of the one before or after it
     __shared__ unsigned long long s_piece[kSoloMaxWaves][kWave];        // a wave's claims for pieces of list blocks
     __shared__ int s_at[kSoloMaxWaves][kWave];                  // whose they are: thread << 6 | lane
     __shared__ unsigned long long s_log[kSoloMaxWaves][kWave];  // grants not yet written to the state: slot << 32 | job
@@ -117,7 +82,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     const uint32_t nobody = uint32_t(held_words) * 32u;
 
     for (int i = tid; i < held_words; i += threads) s_held[0][i] = s_held[1][i] = held[size_t((after + 1) & 1) * held_words + i];
-    for (int i = tid; i < kSoloTable; i += threads) s_tab[i] = 0;
+    for (int i = tid; i < kSoloTable; i += threads) s_tabs.word[0][i] = s_tabs.word[1][i] = 0;
     if (tid < 2) { s_ctl[tid] = make_int4(0, 0, 0, 0); s_held[tid][held_words] = ~0u; }
     if (tid == 0) s_flag = 0;
     __syncthreads();
@@ -248,6 +213,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         const int half = round & 1;
         const uint32_t *const is_held = s_held[half];
         uint32_t *const mark = s_held[half ^ 1];
+        unsigned long long *const tab = solo_table(s_tabs, round);
         auto set_mark = [&](uint32_t j) { atomicOr(&mark[j >> 5], 1u << (j & 31u)); };
         bool looking = open != 0, found = false, have = false;
         const bool any_open = __ballot(looking) != 0;
@@ -366,7 +332,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
             const bool same = whole & (job == uint32_t(__builtin_amdgcn_readlane(int(job), leader)));
             const int low = wave_min_dpp(same ? low_gap : 0x7fffffff);
             if (whole & (!same | (lane == leader))) {
-                if (!solo_enter(s_tab, solo_word(round, int(job), same ? low : low_gap))) s_ctl[half].y = round;
+                if (!solo_enter(tab, solo_word(round, int(job), same ? low : low_gap))) s_ctl[half].y = round;
                 set_mark(job);
                 marked = job;
             }
@@ -376,7 +342,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         if (n_pieces) {
             if (lane < n_pieces) {
                 const unsigned long long v = s_piece[wave][lane];
-                if (!solo_enter(s_tab, v)) s_ctl[half].y = round;
+                if (!solo_enter(tab, v)) s_ctl[half].y = round;
                 marked_piece = uint32_t(v >> 20) & 0xfffffu;
                 set_mark(marked_piece);
             }
@@ -387,10 +353,13 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
             if (todo != 0 || n_pieces) s_ctl[half].x = round;
             else if (any_open) s_ctl[half].w = round;
         }
-        __syncthreads();        // the round's only barrier: all claims are in
+        // the round's only barrier: all claims are in.  A wave that goes on to the next round writes the other
+        // halves of the claims and of s_ctl, while slower ones still read these; the bitmap it marks then,
+        // this round's, is not read behind the barrier
+        __syncthreads();
         const int4 ctl = s_ctl[half];
         bool won = false;
-        if (whole) won = solo_wins(s_tab, solo_word(round, int(job), low_gap));
+        if (whole) won = solo_wins(tab, solo_word(round, int(job), low_gap));
         if (ctl.y == round) break;      // the launched rounds take this one over
         if (ctl.x != round) {           // nobody claims anything: the end
             ended = 1; stable = 1;
@@ -411,7 +380,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         };
         if (__ballot(won)) grant(won, low_lane, job);
         if (n_pieces) {
-            unsigned long long hits = __ballot(lane < n_pieces && solo_wins(s_tab, s_piece[wave][lane]));
+            unsigned long long hits = __ballot(lane < n_pieces && solo_wins(tab, s_piece[wave][lane]));
             while (hits) {
                 const int k = __ffsll((long long)hits) - 1;
                 hits &= hits - 1;

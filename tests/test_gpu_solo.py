@@ -63,3 +63,21 @@ def test_hysteresis_keys_that_fall(engine, oracle, caps, gain):
     finally:
         engine.sja_set_resolve_mode(0)
         engine.sja_set_hysteresis([], 1)
+
+
+@pytest.mark.parametrize("gaps,jobs", [(600, 4500), (3001, 4500)])
+def test_jobs_that_meet_in_a_claim_slot(engine, oracle, gaps, jobs):
+    # ranked so that the jobs of consecutive rounds share a slot of the claim table (ids 2048 apart), with list
+    # blocks in every wave; few list blocks, and more than those whose gap orders are kept in LDS
+    wl = make_workload("stress", 3, n_gaps=gaps, n_jobs=jobs)
+    rng = np.random.default_rng(gaps)
+    wl.W = np.floor(10 * 10.0 ** (4 * rng.random(gaps))).astype(np.int32)
+    order = np.argsort(np.arange(jobs) % 2048, kind="stable")          # 0, 2048, 4096, 1, 2049, ...
+    wl.seg_off = np.arange(jobs + 1, dtype=np.int64)
+    wl.dur = np.full(jobs, 9, dtype=np.int32)
+    wl.mem = np.empty(jobs, dtype=np.int32)
+    wl.mem[order] = 30000 - np.arange(jobs)
+    wl.safe = np.ones(jobs, dtype=np.uint8)
+    wl.progress = np.zeros(jobs, dtype=np.int32)
+    wl.max_rounds = 90
+    full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
