@@ -389,14 +389,16 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
             }
         }
         done = round;
-        if (round == cap) {
+        strain = max(strain + max((ctl.z >> 8) == round ? (ctl.z & 255) - kSoloEasyPieces : 0, 0) - 1, 0);
+        if (round == cap || strain > kSoloPatience) {
+            // the block stops here.  A lane still open has lost this round; if there is none, the process has ended with it
             if (open) s_flag = 1;
             __syncthreads();
-            ended = 1; stable = s_flag ? 0 : 1;
+            const bool lost = s_flag != 0;
+            ended = !lost || round == cap;
+            stable = !lost;
             break;
         }
-        strain = max(strain + max((ctl.z >> 8) == round ? (ctl.z & 255) - kSoloEasyPieces : 0, 0) - 1, 0);
-        if (strain > kSoloPatience) break;
     }
     flush();
     if (tid == 0) { out[kSoloDone] = ended; out[kSoloRounds] = done; out[kSoloStable] = stable; }

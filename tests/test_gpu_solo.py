@@ -81,3 +81,33 @@ def test_jobs_that_meet_in_a_claim_slot(engine, oracle, gaps, jobs):
     wl.progress = np.zeros(jobs, dtype=np.int32)
     wl.max_rounds = 90
     full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
+
+
+def _by_windows(caps, windows, jobs_each, gaps_per_window=1, common=0, misfits=0):
+    """Every capacity holds every job; each capacity has gaps of the same windows, and a window's best job
+    is one as long as the window: a round serves one capacity, in as many pieces as there are windows.
+    `common` jobs fit every gap and come last, `misfits` fit none (they only lift the bound on the rounds)."""
+    wl = make_workload("tiny", 0, n_gaps=8, n_jobs=8)
+    wl.n_gaps, wl.n_jobs = caps * windows * gaps_per_window, windows * jobs_each + common + misfits
+    wl.W = np.tile(np.repeat(np.arange(1000, 1000 + windows, dtype=np.int32), gaps_per_window), caps)
+    wl.C = np.repeat(np.arange(10000, 10000 + caps, dtype=np.int32), windows * gaps_per_window)
+    wl.seg_off = np.arange(wl.n_jobs + 1, dtype=np.int64)
+    lengths = [np.repeat(np.arange(1000, 1000 + windows), jobs_each), np.full(common, 500), np.full(misfits, 1000)]
+    wl.dur = np.concatenate(lengths).astype(np.int32)
+    wl.mem = np.full(wl.n_jobs, 5000, dtype=np.int32)
+    wl.mem[wl.n_jobs - misfits:] = 90000
+    wl.safe = np.ones(wl.n_jobs, dtype=np.uint8)
+    wl.progress = np.zeros(wl.n_jobs, dtype=np.int32)
+    wl.wait = np.zeros(wl.n_jobs, dtype=np.int32)
+    wl.sla_class = np.ones(wl.n_jobs, dtype=np.uint8)
+    wl.max_rounds = 0
+    return wl
+
+
+@pytest.mark.parametrize("caps", [6, 7, 8, 9, 23, 28])
+def test_last_round_in_many_pieces(engine, oracle, caps):
+    # the pieces of rounds 5 to 8 add up to the block's patience: with 8 capacities it stops in the very round
+    # that serves the last gap, with fewer it has ended before, with more gaps are left
+    wl = _by_windows(caps, 64, caps)
+    t = full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
+    assert t.rounds.cpu().tolist() == [caps, 1]
