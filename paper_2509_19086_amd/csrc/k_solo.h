@@ -362,8 +362,10 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         if (whole) won = solo_wins(tab, solo_word(round, int(job), low_gap));
         if (ctl.y == round) break;      // the launched rounds take this one over
         if (ctl.x != round) {           // nobody claims anything: the end
+            // this round counts if a lane had lost the one before and found nothing more; in the first round one
+            // had, else the block had ended above (list blocks used up by then never had their lanes opened)
             ended = 1; stable = 1;
-            done = ctl.w == round ? round : round - 1;
+            done = ctl.w == round || round == after + 1 ? round : round - 1;
             break;
         }
         auto grant = [&](bool mine, int l, uint32_t j) {       // lane l of this thread's list block gets job j

@@ -111,3 +111,14 @@ def test_last_round_in_many_pieces(engine, oracle, caps):
     wl = _by_windows(caps, 64, caps)
     t = full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
     assert t.rounds.cpu().tolist() == [caps, 1]
+
+
+@pytest.mark.parametrize("caps,windows,jobs_each,gaps_per_window,common",
+                         [(1, 1, 3, 64, 0), (1, 1, 4, 64, 0), (1, 1, 5, 64, 0), (3, 1, 4, 30, 0),
+                          (28, 64, 10, 1, 9), (28, 64, 10, 1, 10), (28, 64, 10, 1, 11), (28, 64, 20, 1, 0)])
+def test_lists_that_end_where_the_block_takes_over(engine, oracle, caps, windows, jobs_each, gaps_per_window, common):
+    # the jobs are used up one round before, with and one round after the last launched round (4, or 20 where
+    # the block stops in round 5 because of its pieces); gaps are left, so one more round finds nothing
+    wl = _by_windows(caps, windows, jobs_each, gaps_per_window, common, misfits=64)
+    t = full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
+    assert t.rounds.cpu().tolist() == [jobs_each + common + 1, 1]
