@@ -304,6 +304,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
 // leaves the same partial per (job tile, gap).  Gaps that are switched off cost nothing, and rounds switch
 // more and more of them off.  700 gaps of 300 capacities x 2501 jobs: 165 us a round stepping, 47 us so.
 constexpr int kSearchGaps = 4;
+constexpr int kSearchRows = 32768;      // groups of positions per launch, a row of blocks each (a launch takes fewer than 65536 rows)
 
 // The largest value over all 64 lanes, the same in every lane.
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
@@ -315,7 +316,7 @@ constexpr int kShortRun = 16;      // positions per capacity, on average, below 
 
 template <bool MIXED, bool AREA>
 __global__ __launch_bounds__(kFusedBlock) void k_search_select(
-    int n_jobs, int n_gaps, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
+    int n_jobs, int n_gaps, int first_row, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ gap_w,
     const int32_t *__restrict__ gap_c, const int32_t *__restrict__ gap_order, const int32_t *__restrict__ wait,
     const uint8_t *__restrict__ sla_class, const int32_t *__restrict__ job_held, const uint8_t *__restrict__ gap_active,
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_search_select(
     __shared__ unsigned long long s_hi[Q][WAVES], s_lo[Q][WAVES];
     __shared__ int s_job[Q][WAVES], s_atoms[Q][WAVES];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int s0 = blockIdx.y * Q, j = blockIdx.x * kFusedBlock + threadIdx.x;
+    const int s0 = (first_row + int(blockIdx.y)) * Q, j = blockIdx.x * kFusedBlock + threadIdx.x;
     int g[Q], w[Q], c[Q];
     bool on[Q], any = false;
 #pragma unroll

@@ -571,11 +571,15 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
         const long long *atom_area = atom_area_of(ctx, L);
         auto kern = atom_area ? (mixed ? k_search_select<true, true> : k_search_select<false, true>)
                               : (mixed ? k_search_select<true, false> : k_search_select<false, false>);
-        hipLaunchKernelGGL(kern, dim3(job_tiles, (n_gaps + kSearchGaps - 1) / kSearchGaps), dim3(kFusedBlock), 0, st, J, n_gaps,
-                           to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
-                           ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_c), ws_ptr<int32_t>(ctx, L.gap_order), wait,
-                           sla_class, job_held, gap_active, ws_ptr<SelPartial>(ctx, L.sel_part));
-        SJA_HIP(hipGetLastError(), "k_search_select launch");
+        const int rows = (n_gaps + kSearchGaps - 1) / kSearchGaps;
+        for (int first = 0; first < rows; first += kSearchRows) {
+            const int n_rows = rows - first < kSearchRows ? rows - first : kSearchRows;
+            hipLaunchKernelGGL(kern, dim3(job_tiles, n_rows), dim3(kFusedBlock), 0, st, J, n_gaps, first, to_dev(params), ctx->seg_off,
+                               ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms), ws_ptr<int32_t>(ctx, L.gap_w),
+                               ws_ptr<int32_t>(ctx, L.gap_c), ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active,
+                               ws_ptr<SelPartial>(ctx, L.sel_part));
+            SJA_HIP(hipGetLastError(), "k_search_select launch");
+        }
     } else if (job_tiles > 0) {
         const int chunk_bound = int(fit_chunk_bound(n_gaps, J));
         const int tiles8 = (job_tiles + 7) / 8 * 8;

@@ -145,3 +145,27 @@ def test_equal_scores_ordered_by_the_second_key(engine, oracle, jobs_per_run):
         wl.dur[a:a + L], wl.mem[a:a + L] = 1, 512 if j % 2 == 0 else 1024        # key 512 * 2000 == 1024 * 1000 per tick
         wl.wait[j] = 1000 if j % 2 == 0 else 0
     full_tick_check(engine, oracle, wl, policies=[3], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("n_gaps", [4 * 32768, 4 * 32768 + 1, 270001])
+def test_rounds_that_search_over_more_gaps_than_a_launch_takes(engine, oracle, n_gaps):
+    # four positions per row of blocks: on both sides of a launch's rows, and beyond what any one launch takes
+    import paper_2509_19086_amd as P
+    wl = make_workload("tiny", 9, n_gaps=n_gaps, n_jobs=7)
+    rng = np.random.default_rng(n_gaps)
+    wl.W = rng.integers(10, 20, size=n_gaps).astype(np.int32)                  # too short for any job,
+    wl.W[-40:] = rng.integers(50, 4000, size=40)                               # but for a few at the end of the order
+    wl.C = (20000 + np.arange(n_gaps) // 8).astype(np.int32)                   # eight gaps per capacity
+    wl.dur = np.maximum(wl.dur, 25).astype(np.int32)
+    t = P.DeviceTick(engine, wl)
+    t.prepare()
+    pd, pp, _ = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
+    cut, _ = oracle.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W, wl.C)
+    for policy in (0, 3):
+        t.fit_select(P.Params.make(policy))
+        t.resolve(P.Params.make(policy))
+        gj, gc, gs, jg, rounds, stable = oracle.resolve(cut, wl.seg_off, pd, pp, oracle.Params.make(policy), wl.wait, wl.sla_class)
+        assert (gj[-40:] >= 0).any()
+        for got, want in ((t.grant_job, gj), (t.grant_cut, gc), (t.grant_score, gs), (t.job_gap, jg)):
+            np.testing.assert_array_equal(got.cpu().numpy(), want)
+        assert t.rounds.cpu().tolist() == [rounds, stable]
