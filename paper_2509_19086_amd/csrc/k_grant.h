@@ -170,9 +170,10 @@ __global__ void k_list_blocks_count(int n_slots, const int32_t *__restrict__ pla
 }
 
 // Writes the pieces, the list block of every position, and per class a table of positions by duration:
-// entry k of a class's kPosTable / n_classes entries is the first position whose window reaches k << shift
+// entry k of a class's pos_entries / n_classes entries is the first position whose window reaches k << shift
 // (the class's end from the last window on), so that a search for a duration only has a few positions left.
-constexpr int kPosTable = 2048;
+constexpr int kEntryWinBig = 32768, kEntryWinSmall = 8192;     // batches whose windows k_list_entries keeps in LDS
+constexpr int kPosTable = 2048, kPosTableMany = 16384;          // entries for such batches, and for larger ones
 
 __device__ __forceinline__ int pos_shift(int longest, int entries)
 {
@@ -181,11 +182,12 @@ __device__ __forceinline__ int pos_shift(int longest, int entries)
     return s;
 }
 
-__device__ __forceinline__ void pos_table_entry(int i, int n_gaps, const int32_t *__restrict__ plan,
+__device__ __forceinline__ void pos_table_entry(int i, int pos_entries, int n_gaps, const int32_t *__restrict__ plan,
                                                 const int32_t *__restrict__ class_begin,
                                                 const int32_t *__restrict__ gap_w, int32_t *pos_tab)
 {
-    const int n_classes = plan[kPlanClasses], entries = kPosTable / n_classes;
+    if (i >= pos_entries) return;
+    const int n_classes = plan[kPlanClasses], entries = pos_entries / n_classes;
     const int c = i / entries;
     if (c >= n_classes) return;
     const int k = i - c * entries;
@@ -199,7 +201,7 @@ __device__ __forceinline__ void pos_table_entry(int i, int n_gaps, const int32_t
     pos_tab[i] = k == entries - 1 ? end : lo;
 }
 
-__global__ void k_list_blocks_write(int lb_cap, int n_gaps, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
+__global__ void k_list_blocks_write(int lb_cap, int n_gaps, int pos_entries, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
                                     const int32_t *__restrict__ sub_begin, const int32_t *__restrict__ sub_end,
                                     const int32_t *__restrict__ gap_w, const int32_t *__restrict__ lb_off,
                                     int32_t *lb_begin, int32_t *lb_end, int32_t *pos_block, int32_t *pos_tab)
@@ -217,7 +219,7 @@ __global__ void k_list_blocks_write(int lb_cap, int n_gaps, const int32_t *__res
             b = p;
         }
     }
-    if (u < kPosTable) pos_table_entry(u, n_gaps, plan, class_begin, gap_w, pos_tab);
+    pos_table_entry(u, pos_entries, n_gaps, plan, class_begin, gap_w, pos_tab);
 }
 
 // All of it in one launch while the sub-blocks are few: block 0 cuts them into pieces (a wave per sub-block,
@@ -225,7 +227,7 @@ __global__ void k_list_blocks_write(int lb_cap, int n_gaps, const int32_t *__res
 // The serial walk of one thread per sub-block above takes 60 us at Stress, with its scan.
 constexpr int kListBlocksOne = 2048;
 
-__global__ __launch_bounds__(1024) void k_list_blocks(int lb_cap, int n_gaps, int32_t *plan, const int32_t *__restrict__ class_begin,
+__global__ __launch_bounds__(1024) void k_list_blocks(int lb_cap, int n_gaps, int pos_entries, int32_t *plan, const int32_t *__restrict__ class_begin,
                                                       const int32_t *__restrict__ sub_begin, const int32_t *__restrict__ sub_end,
                                                       const int32_t *__restrict__ gap_w, int32_t *lb_begin, int32_t *lb_end,
                                                       int32_t *pos_block, int32_t *pos_tab)
@@ -237,7 +239,7 @@ __global__ __launch_bounds__(1024) void k_list_blocks(int lb_cap, int n_gaps, in
     const bool tabled = plan[kPlanTabled] != 0;
     if (blockIdx.x > 0) {
         const int i = (int(blockIdx.x) - 1) * 1024 + tid;
-        if (tabled && i < kPosTable) pos_table_entry(i, n_gaps, plan, class_begin, gap_w, pos_tab);
+        if (tabled) pos_table_entry(i, pos_entries, n_gaps, plan, class_begin, gap_w, pos_tab);
         return;
     }
     const int n_subs = tabled ? min(plan[kPlanSubBlocks], kListBlocksOne) : 0;
@@ -296,21 +298,25 @@ __global__ __launch_bounds__(1024) void k_list_blocks(int lb_cap, int n_gaps, in
 // window that reaches its duration up to the first that reaches the next atom's: in every capacity class one
 // range of positions, an entry for each list block it touches.  Lanes walk along the atoms as they are ranked,
 // so that the entries leave in rank order and only their list block is left to sort by.  Two passes: counts per
-// 64 atoms and per list block (EMIT false; chunk_at receives the counts), then the entries (chunk_at holds
-// their exclusive sums).  The chunks go to the waves in turn: ranks far down, where many an atom answers for
-// a whole class, hold most of the entries.
+// chunk of per_chunk atoms and per list block (EMIT false; chunk_at receives the counts), then the entries
+// (chunk_at holds their exclusive sums).  The chunks go to the waves in turn: ranks far down, where many an
+// atom answers for a whole class, hold most of the entries.
 // Ranked atoms lie anywhere, so every load of a step is 64 lines for a wave: with the windows in global
 // memory the count took 1.25 ms at Stress (8.5 million atoms, 8 classes), all of it those lines.  WIN > 0:
 // the windows of all positions are kept in LDS (up to WIN of them, and up to kEntryBlocks list blocks).
+// WIN = 0: their space goes to a finer table of positions, which leaves one or two steps of a search, and to
+// the list blocks.  The counts per list block are added up in LDS in either form (an addition to global memory
+// per entry, to a few hundred words, took 4.2 ms for 40000 gaps x 8192 jobs).
 constexpr int kEntryThreads = 1024;
 constexpr int kEntryBlocks = 1024;        // list blocks whose first positions a thread block keeps in LDS
 constexpr int kEntryGrid = 512;           // most thread blocks: two per compute unit
+constexpr int kEntryLeastAtoms = 8;       // atoms per wave's turn, at least
 constexpr int kEntryFewWide = 2;          // ranges of three or more list blocks among a wave's that are served one by one
-constexpr int kEntryWinBig = 32768, kEntryWinSmall = 8192;
+constexpr int kEntryMostBlocks = 19456;   // list blocks that the largest batch can have
 
 template <bool EMIT, int WIN>
 __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
-    int n_atoms, int n_lb, int n_gaps, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
+    int n_atoms, int per_chunk, int n_lb, int n_gaps, int pos_entries, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
     const int32_t *__restrict__ lb_begin, const int32_t *__restrict__ pos_block, const int32_t *__restrict__ pos_tab,
     const int32_t *__restrict__ gap_w, const int32_t *__restrict__ gap_c, const uint32_t *__restrict__ perm,
     const int4 *__restrict__ info, int32_t *chunk_at, int32_t *list_count, unsigned long long *total,
@@ -318,15 +324,16 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
 {
     constexpr bool kLds = WIN > 0;
     __shared__ int s_w[kLds ? WIN : 1];
-    __shared__ int s_pos[kPosTable];
-    __shared__ int s_begin[kLds ? kEntryBlocks + 1 : 1];       // first positions of the list blocks
+    __shared__ int s_pos[kLds ? kPosTable : kPosTableMany];
+    constexpr bool kBegins = kLds || EMIT;
+    __shared__ int s_begin[kBegins ? (kLds ? kEntryBlocks : kEntryMostBlocks) + 1 : 1];      // first positions of the list blocks
     __shared__ int s_hint[kLds ? WIN / kWave : 1];             // list block of every 64th position
-    __shared__ int s_diff[!EMIT && kLds ? kEntryBlocks + 1 : 1];
+    __shared__ int s_diff[EMIT ? 1 : (kLds ? kEntryBlocks : kEntryMostBlocks) + 1];
     __shared__ int s_cap[kMaxClasses], s_end[kMaxClasses], s_shift[kMaxClasses], s_lb[kMaxClasses + 1];
     __shared__ long long s_all[kEntryThreads / kWave];
     __shared__ int s_src[EMIT ? kEntryThreads / kWave : 1][kWave];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-    const int n_classes = min(plan[kPlanClasses], kMaxClasses), entries = kPosTable / n_classes;
+    const int n_classes = min(plan[kPlanClasses], kMaxClasses), entries = pos_entries / n_classes;
     for (int i = tid; i < entries * n_classes; i += kEntryThreads) s_pos[i] = pos_tab[i];
     for (int c = tid; c < n_classes; c += kEntryThreads) {
         const int end = c + 1 < n_classes ? class_begin[c + 1] : n_gaps;
@@ -341,14 +348,14 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
             s_w[kLds ? i : 0] = gap_w[i];
             if ((i & (kWave - 1)) == 0) s_hint[kLds ? i / kWave : 0] = pos_block[i];
         }
-        for (int k = tid; k <= n_lb; k += kEntryThreads) {
-            s_begin[kLds ? k : 0] = k < n_lb ? lb_begin[k] : n_gaps;
-            if (!EMIT) s_diff[kLds && !EMIT ? k : 0] = 0;
-        }
     }
+    if (kBegins)
+        for (int k = tid; k <= n_lb; k += kEntryThreads) s_begin[kBegins ? k : 0] = k < n_lb ? lb_begin[k] : n_gaps;
+    if (!EMIT)
+        for (int k = tid; k <= n_lb; k += kEntryThreads) s_diff[EMIT ? 0 : k] = 0;
     __syncthreads();
     auto window = [&](int p) { return kLds ? s_w[kLds ? p : 0] : gap_w[p]; };
-    auto begin_of = [&](int k) { return kLds ? s_begin[kLds ? k : 0] : (k < n_lb ? lb_begin[k] : n_gaps); };
+    auto begin_of = [&](int k) { return s_begin[kBegins ? k : 0]; };
     auto block_of = [&](int p) {
         if (!kLds) return pos_block[p];
         int k = s_hint[kLds ? p / kWave : 0];
@@ -356,11 +363,11 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
         return k;
     };
 
-    const int n_chunks = int((int64_t(n_atoms) + kWave - 1) / kWave), n_waves = int(gridDim.x) * (kEntryThreads / kWave);
+    const int n_chunks = int((int64_t(n_atoms) + per_chunk - 1) / per_chunk), n_waves = int(gridDim.x) * (kEntryThreads / kWave);
     long long count_all = 0;
     for (int chunk = blockIdx.x * (kEntryThreads / kWave) + wave; chunk < n_chunks; chunk += n_waves) {
-        const int64_t i = int64_t(chunk) * kWave + lane;
-        const bool valid = i < n_atoms;
+        const int64_t i = int64_t(chunk) * per_chunk + lane;
+        const bool valid = lane < per_chunk && i < n_atoms;
         int64_t at = EMIT ? chunk_at[chunk] : 0;
         int count = 0;
         const int a = valid ? int(perm[i]) : 0;
@@ -445,13 +452,9 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
                 at += __builtin_amdgcn_readlane(upto, kWave - 1);
             } else if (n > 0) {
                 count += n;
-                if (kLds) {
-                    atomicAdd(&s_diff[kLds && !EMIT ? k_lo : 0], 1);
-                    // (nothing to take back behind the class: the sums start anew there)
-                    if (k_lo + n < s_lb[c + 1]) atomicAdd(&s_diff[kLds && !EMIT ? k_lo + n : 0], -1);
-                } else {
-                    for (int k = k_lo; k < k_lo + n; ++k) atomicAdd(&list_count[k], 1);
-                }
+                atomicAdd(&s_diff[EMIT ? 0 : k_lo], 1);
+                // (nothing to take back behind the class: the sums start anew there)
+                if (k_lo + n < s_lb[c + 1]) atomicAdd(&s_diff[EMIT ? 0 : k_lo + n], -1);
             }
         }
         if (!EMIT) {
@@ -468,14 +471,13 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
         for (int v = 0; v < kEntryThreads / kWave; ++v) t += (unsigned long long)s_all[v];
         if (t) atomicAdd(total, t);
     }
-    if (!kLds) return;
     // the list blocks' counts are the running sums of a class's differences
     for (int c = wave; c < n_classes; c += kEntryThreads / kWave) {
         const int lb0 = s_lb[c], lb1 = s_lb[c + 1];
         int run = 0;
         for (int k0 = lb0; k0 < lb1; k0 += kWave) {
             const int k = k0 + lane;
-            const int upto = run + wave_scan_add(k < lb1 ? s_diff[kLds && !EMIT ? k : 0] : 0);
+            const int upto = run + wave_scan_add(k < lb1 ? s_diff[EMIT ? 0 : k] : 0);
             if (k < lb1 && upto) atomicAdd(&list_count[k], upto);
             run = __builtin_amdgcn_readlane(upto, kWave - 1);
         }

@@ -269,14 +269,16 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     // 1. list blocks; reachable atoms per job -> compact atom ids
     int32_t *pos_block = ws_ptr<int32_t>(ctx, L.g_pos_block), *pos_tab = ws_ptr<int32_t>(ctx, L.g_pos_tab);
     const int32_t *class_begin = ws_ptr<int32_t>(ctx, L.class_begin);
+    const int pos_entries = G > kEntryWinBig ? kPosTableMany : kPosTable;       // (a batch has room for as many as it has gaps, at least 4096)
     if (sub_bound <= kListBlocksOne) {
-        hipLaunchKernelGGL(k_list_blocks, dim3(1 + kPosTable / 1024), dim3(1024), 0, st, lb_bound, G, plan, class_begin, sub_begin,
+        hipLaunchKernelGGL(k_list_blocks, dim3(1 + pos_entries / 1024), dim3(1024), 0, st, lb_bound, G, pos_entries, plan, class_begin, sub_begin,
                            sub_end, gap_w, lb_begin, lb_end, pos_block, pos_tab);
     } else {
         hipLaunchKernelGGL(k_list_blocks_count, dim3((sub_bound + 1 + 255) / 256), dim3(256), 0, st, sub_bound + 1, plan, sub_begin,
                            sub_end, gap_w, lb_off);
         SJA_HIP(enqueue_scan(st, lb_off, int64_t(sub_bound) + 1, tmp, plan + kPlanListBlocks), "list block scan launch");
-        hipLaunchKernelGGL(k_list_blocks_write, dim3((sub_bound + 255) / 256), dim3(256), 0, st, lb_bound, G, plan, class_begin,
+        const int items = sub_bound > pos_entries ? sub_bound : pos_entries;
+        hipLaunchKernelGGL(k_list_blocks_write, dim3((items + 255) / 256), dim3(256), 0, st, lb_bound, G, pos_entries, plan, class_begin,
                            sub_begin, sub_end, gap_w, lb_off, lb_begin, lb_end, pos_block, pos_tab);
     }
     SJA_HIP(hipGetLastError(), "list block launch");
@@ -350,16 +352,25 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
 
     // 3. list entries in rank order: counted, then written, then sorted by list block
     constexpr int waves_per_block = kEntryThreads / kWave;
-    // windows in LDS: a block with 32768 of them has a compute unit to itself
+    static_assert(SJA_MAX_GAPS / 64 + kMaxClasses + kMaxClasses * kListSplits <= kEntryMostBlocks, "a count per list block fits LDS");
+    // (sub-blocks are shorter than 64 positions only in batches of fewer than 2048 such chunks)
+    // windows in LDS: a block with 32768 of them has a compute unit to itself, and so has one with many list blocks
     const bool in_lds = n_subs <= kEntryBlocks && G <= kEntryWinBig, small = in_lds && G <= kEntryWinSmall;
-    const int64_t n_chunks = (n_atoms + kWave - 1) / kWave, want = (n_chunks + waves_per_block - 1) / waves_per_block;
-    const int most = in_lds && !small ? kEntryGrid / 2 : kEntryGrid;
+    const int most = small ? kEntryGrid : kEntryGrid / 2;
+    // 64 atoms a chunk; fewer where few atoms have many entries each, so that every wave has a chunk (131072 gaps x
+    // 1024 jobs: 274 -> 114 us)
+    int per_chunk = kWave;
+    auto chunks_of = [&](int per) { return (n_atoms + per - 1) / per; };
+    while (!in_lds && per_chunk > kEntryLeastAtoms && chunks_of(per_chunk / 2) <= int64_t(most) * waves_per_block &&
+           chunks_of(per_chunk / 2) <= L.atom_cap / kWave)
+        per_chunk /= 2;
+    const int64_t n_chunks = chunks_of(per_chunk), want = (n_chunks + waves_per_block - 1) / waves_per_block;
     const unsigned entry_grid = unsigned(want < most ? want : most);
     auto launch_entries = [&](auto emit) {
         auto kern = small ? k_list_entries<decltype(emit)::value, kEntryWinSmall>
                           : in_lds ? k_list_entries<decltype(emit)::value, kEntryWinBig> : k_list_entries<decltype(emit)::value, 0>;
-        hipLaunchKernelGGL(kern, dim3(entry_grid), dim3(kEntryThreads), 0, st, int(n_atoms), n_subs, G, plan,
-                           class_begin, lb_begin, pos_block, pos_tab, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), perm[flip ? 1 : 0], info, chunk_at,
+        hipLaunchKernelGGL(kern, dim3(entry_grid), dim3(kEntryThreads), 0, st, int(n_atoms), per_chunk, n_subs, G, pos_entries,
+                           plan, class_begin, lb_begin, pos_block, pos_tab, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), perm[flip ? 1 : 0], info, chunk_at,
                            list_off, reinterpret_cast<unsigned long long *>(counters), ekey[0]);
         return hipGetLastError();
     };

@@ -169,3 +169,19 @@ def test_rounds_that_search_over_more_gaps_than_a_launch_takes(engine, oracle, n
         for got, want in ((t.grant_job, gj), (t.grant_cut, gc), (t.grant_score, gs), (t.job_gap, jg)):
             np.testing.assert_array_equal(got.cpu().numpy(), want)
         assert t.rounds.cpu().tolist() == [rounds, stable]
+
+
+@pytest.mark.parametrize("name,n_gaps,n_jobs,classes,log_windows",
+                         [("medium", 32769, 131, 5, False), ("stress", 40001, 900, 8, False), ("stress", 12000, 70, 64, True),
+                          ("stress", 30001, 3, 64, True), ("tiny", 140003, 33, 3, True)])
+def test_entries_of_large_batches(engine, oracle, name, n_gaps, n_jobs, classes, log_windows):
+    # more gaps, or more list blocks, than those whose windows and first positions fit LDS; few and many atoms
+    # to a wave's turn
+    wl = make_workload(name, n_gaps, n_gaps=n_gaps, n_jobs=n_jobs)
+    rng = np.random.default_rng(n_gaps)
+    caps = np.sort(rng.choice(np.arange(2000, 150000), size=classes, replace=False)).astype(np.int32)
+    wl.C = caps[rng.integers(0, classes, size=n_gaps)]
+    if log_windows:
+        wl.W = np.floor(10 * 10.0 ** (4 * rng.random(n_gaps))).astype(np.int32)
+    wl.max_rounds = 6
+    full_tick_check(engine, oracle, wl, policies=[0, 3], resolve_modes=(0,))
