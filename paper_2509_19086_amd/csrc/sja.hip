@@ -1116,11 +1116,20 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
         SJA_HIP(hipStreamSynchronize(st), "final synchronise");
         return SJA_OK;
     }
-    // Rounds go out in batches between looks at their counters (a pair a round): a round after the last one
-    // finds no candidate and changes nothing.
+    // Rounds go out in batches between looks at their counters (a pair a round): a round after the last one finds
+    // no candidate and changes nothing.  It costs little where pairs are searched; the other forms pay a full
+    // pass over all pairs for it, so their batches are an eighth of the rounds done, and only while a pass takes
+    // no longer than a few looks (3 rounds of 6000 gaps x 12000 jobs: 311 us one by one, 465 in batches of 2
+    // and 4; 272 rounds of 700 x 2501: 12.0 ms one by one, 8.6 so).
     constexpr int kMostRounds = 8;
-    int batch = 2;
+    constexpr int64_t kShortPass = int64_t(1) << 24;        // pairs; 40 us
+    const bool searched = many_capacities && !ctx->fitted;
+    auto batch_from = [&](int64_t r) -> int64_t {
+        const int64_t n = searched ? r + 1 : int64_t(G) * J <= kShortPass ? r / 8 : 1;
+        return n < 1 ? 1 : n < kMostRounds ? n : kMostRounds;
+    };
     for (int64_t r = 1; r <= cap;) {
+        const int64_t batch = batch_from(r);
         const int n = G == 0 ? 1 : int(cap - r + 1 < batch ? cap - r + 1 : batch);
         int32_t host_counters[2 * kMostRounds] = {0};
         for (int k = 0; k < n && G > 0; ++k) {
@@ -1131,7 +1140,7 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
                                    /*keys_ready=*/r + k > 1);
             else
                 rc = launch_fused(ctx, st, L, G, params, wait, sla_class, job_gap, active, cand_job, cand_cut, cand_score,
-                                  false, /*searched=*/many_capacities);
+                                  false, searched);
             if (rc != SJA_OK) return rc;
             const dim3 grid((G + 255) / 256), block(256);
             hipLaunchKernelGGL(k_claim, grid, block, 0, st, G, int(r) + k, active, cand_job, claim, counters + 2 * k);
@@ -1150,7 +1159,6 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
         }
         if (result[1]) break;
         r += n;
-        if (batch < kMostRounds) batch *= 2;
     }
     SJA_HIP(hipMemcpyAsync(rounds_used_and_stable, result, sizeof(result), hipMemcpyHostToDevice, st),
             "rounds writeback");

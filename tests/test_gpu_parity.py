@@ -386,3 +386,27 @@ def test_store_reference_writes_the_whole_matrix(engine):
         assert bool((guard == -9).all())
         with pytest.raises(P.SjaError):                    # the matrix no longer holds the replies
             t.select(P.Params.make(0))
+
+
+@pytest.mark.parametrize("cap", [0, 15, 16, 17, 33, 70])
+def test_matrix_rounds_in_batches(engine, oracle, cap):
+    """Matrix-scanning rounds go out in batches that grow with the rounds done: ends and caps inside a
+    batch and at its edges, from the matrix and from the pairs."""
+    import paper_2509_19086_amd as P
+    wl = make_workload("small", 4, n_gaps=90, n_jobs=300)
+    wl.W[:] = 1500
+    wl.C[:] = 40960                                     # one gap a round: 90 rounds
+    wl.max_rounds = cap
+    t = full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(1,))
+    want = [x.cpu().numpy().copy() for x in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds)]
+    assert want[4][0] == (cap or 90)
+    par = _params(P, wl)
+    par.policy = 0
+    t.fit_select(par)
+    engine.sja_set_resolve_mode(1)
+    try:
+        t.resolve(par)
+    finally:
+        engine.sja_set_resolve_mode(0)
+    for a, b in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds), want):
+        np.testing.assert_array_equal(a.cpu().numpy(), b)
