@@ -514,6 +514,7 @@ constexpr int kBlockClaims = 256; // claims a block merges in LDS per round
 constexpr int kClaimTurns = 4;    // jobs whose claims a wave merges over its lanes before the rest are sent singly
 
 constexpr int kHeldMaxWords = 4096;   // words of the held-job bitmap a block keeps in LDS (jobs / 32)
+constexpr int kEffortWindow = 8;      // a window of kSweepHeld chunks in pieces (a block reads them chunk by chunk)
 constexpr int kHeldRounds = 512;      // rounds that keep and read the bitmap
 
 __device__ __forceinline__ bool held_bit(const uint32_t *s_held, uint32_t job)
@@ -530,13 +531,16 @@ __device__ __forceinline__ bool held_bit(const uint32_t *s_held, uint32_t job)
 // held from round k+1 on, whoever wins it: the gaps naming it set its bit in the
 // bitmap round k+1 reads, and its winner, when it learns in round k+1 that it
 // won, sets it in the other one, after which both carry it.
+// `pieces` and `windows`: how many jobs the lanes named, beyond one, and how many windows of records they took,
+// beyond one: what the round would cost a single thread block.
 template <bool HELD, typename REC>
 __device__ __forceinline__ void grant_step(int round, bool propose, int lane, int g, int list_begin, int list_end,
                                            const REC *__restrict__ rec, unsigned long long *claim, int4 &st,
                                            bool &lost, bool &cand, int *s_n, int *s_job,
                                            unsigned long long *s_word, const uint32_t *s_held,
-                                           uint32_t *held_next)
+                                           uint32_t *held_next, int &pieces, int &windows)
 {
+    pieces = windows = -1;
     constexpr int SW = HELD ? kSweepHeld : kSweep;
     lost = false;
     cand = false;
@@ -573,6 +577,7 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
     for (;;) {
         const unsigned long long need = __ballot(looking);
         if (!need) break;
+        ++windows;
         if (!ahead) {
             e0 = wave_min_dpp(looking ? e : 0x7fffffff);    // the wave's lowest pointer still looking
             c0 = list_begin + ((e0 - list_begin) & ~(kWave - 1));
@@ -674,7 +679,9 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
     // full is sent at once).
     unsigned long long todo = __ballot(cand);
     for (int turn = 0; todo; ++turn) {
+        ++pieces;
         if (turn == kClaimTurns) {
+            pieces += __popcll(todo) - 1;
             // a wave of the early rounds, whose lanes name dozens of different jobs: one turn of
             // this loop per job costs more than the claims it merges, so the rest go out as they are
             if ((todo >> lane) & 1ull) {
@@ -716,6 +723,8 @@ __device__ __forceinline__ void grant_step(int round, bool propose, int lane, in
 // n_lb, the number of list blocks, comes as an argument (the host has read it
 // back to size its launches): the state and the block's list bounds are all a
 // wave has to wait for before it can ask for its records and its claim word.
+// effort (may be null): two words by turns of the rounds, what the round would have cost one thread block beyond
+// the least; k_grant_solo looks at it.
 // The arguments a wave needs first come first: the library is built so that
 // the leading 16 dwords of a kernel's arguments are in scalar registers when
 // the wave starts, and the state load does not wait for an argument load.
@@ -723,9 +732,9 @@ template <bool HELD, typename REC>
 __global__ __launch_bounds__(kRoundBlock) void k_grant_round(
     int4 *state, const int32_t *__restrict__ list_off, const REC *__restrict__ rec, unsigned long long *claim,
     int round, int propose, int n_lb, int held_words, uint32_t *held, const int32_t *__restrict__ lb_begin,
-    const int32_t *__restrict__ lb_end, const int32_t *__restrict__ gap_order, int32_t *cnt_lost, int32_t *cnt_cand)
+    const int32_t *__restrict__ lb_end, const int32_t *__restrict__ gap_order, int32_t *cnt_lost, int32_t *cnt_cand, int32_t *effort)
 {
-    __shared__ int s_n;
+    __shared__ int s_n, s_effort;
     __shared__ int s_job[kBlockClaims];
     __shared__ unsigned long long s_word[kBlockClaims];
     __shared__ uint4 s_held4[HELD ? kHeldMaxWords / 4 : 1];
@@ -750,7 +759,7 @@ __global__ __launch_bounds__(kRoundBlock) void k_grant_round(
         for (int i = threadIdx.x; i < held_words / 4; i += kRoundBlock) s_held4[i] = src[i];
         held_next = held + size_t((round + 1) & 1) * held_words;
     }
-    if (threadIdx.x == 0) s_n = 0;
+    if (threadIdx.x == 0) s_n = s_effort = 0;
     __syncthreads();
     if (u < n_lb) {
         if (round == 1) {
@@ -762,13 +771,20 @@ __global__ __launch_bounds__(kRoundBlock) void k_grant_round(
         int4 st = make_int4(raw.x, raw.y, raw.z, raw.w & 3);
         const int4 before = st;
         bool lost, cand;
+        int pieces, windows;
         grant_step<HELD, REC>(round, propose != 0, lane, g, list_begin, list_end, rec, claim, st, lost, cand, &s_n, s_job,
-                         s_word, s_held, held_next);
+                         s_word, s_held, held_next, pieces, windows);
+        const int mine = max(pieces, 0) + kEffortWindow * max(windows, 0);
+        if (HELD && mine > 0 && lane == 0) atomicAdd(&s_effort, mine);
         if (st.x != before.x || st.w != before.w || round == 1) state[slot] = make_int4(st.x, st.y, st.z, st.w | (g << 2));
         if (__ballot(lost) && lane == 0) cnt_lost[round - 1] = 1;
         if (__ballot(cand) && lane == 0) cnt_cand[round] = 1;
     }
     __syncthreads();
+    if (HELD && effort && threadIdx.x == kRoundBlock - 1) {        // (not the wave that merges the claims)
+        if (s_effort > 0) atomicAdd(&effort[round & 1], s_effort);
+        if (blockIdx.x == 0) effort[(round + 1) & 1] = 0;
+    }
     const int n = min(s_n, kBlockClaims);
     if (n <= kWave) {
         // the usual case, a handful of claims: one lane of the first wave per claim, the others'

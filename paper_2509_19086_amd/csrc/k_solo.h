@@ -22,9 +22,11 @@
 // (and a thread that has many records to pass) are served by the whole wave,
 // 64 records a trip.
 //
-// When the pieces get many (the first rounds of a large batch, or when a
-// service class runs out and the next one's jobs begin) the block stops and
-// leaves the gaps' state as the round kernel expects it.
+// When a round is much work (the first rounds of a large batch, or when a
+// service class runs out and the next one's jobs begin) one block is the wrong
+// place for it: it starts only when the last launched round was little work,
+// and once the work adds up it stops and leaves the gaps' state as the round
+// kernel expects it.
 #pragma once
 
 #include "k_claims.h"
@@ -36,12 +38,21 @@ constexpr int kSoloMaxWaves = 16;
 constexpr int kSoloMinWaves = 8;        // list blocks in pieces are served by several waves side by side (4: 4 % slower, 16: 5 %)
 constexpr int kSoloSmallBlocks = 128;   // list blocks whose gap orders are kept in LDS
 constexpr int kSoloMaxBlocks = kSoloMaxWaves * kWave;
-constexpr int kSoloFirstRounds = 4;     // launched rounds before the block first takes over
-constexpr int kSoloFewRounds = 16;      // rounds it takes over at least, if the caller bounds them
+// launched rounds before the block may first take over: up to kSoloFewBlocks list blocks the fourth is little
+// work, with more of them the eighth (Medium, 66: 20 us saved over a look after four)
+constexpr int kSoloFirstFew = 4, kSoloFirstMany = 8, kSoloFewBlocks = 32;
+constexpr int kSoloFewRounds = 16;      // rounds it takes over at least, if the caller bounds them,
+constexpr int kSoloBlocksPerRound = 4;  // and one more for this many list blocks (it needs up to 3 us for each wave's next one to start)
 constexpr int kSoloSteps = 3;           // steps of eight records before a lane still looking alone is served by its wave
-constexpr int kSoloEasyPieces = 4;      // pieces per wave and round that cost no more than a launched round
-constexpr int kSoloPatience = 96;       // pieces beyond that, summed up, after which the block stops
+// A wave's effort in a round: pieces it serves and steps of records it takes (0.5 us each; a round without any
+// takes 1.7 us, a launched one 6).
+constexpr int kSoloEasy = 7;            // effort per wave and round that costs no more than a launched round
+constexpr int kSoloPatience = 96;       // effort beyond that, summed up, after which the block stops
+constexpr int kSoloMostSteps = 48;      // steps after which it stops in the middle of a round
+constexpr int kSoloStart = 3;           // effort per wave of the last launched round up to which it starts;
+constexpr int kSoloStartFew = 16;       // with few list blocks, whose start and whose rounds in pieces cost little
 enum { kSoloDone = 0, kSoloRounds = 1, kSoloStable = 2 };
+enum { kSoloHandedBack = 0, kSoloEnded = 1, kSoloPutOff = 2 };      // what out[kSoloDone] says
 
 __device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long v, int l)
 {
@@ -51,8 +62,8 @@ __device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long
 
 // Rounds after + 1 .. at most cap, by blockDim.x / kWave waves (n_lb <= blockDim.x).  `after` rounds have
 // been launched; cnt_lost / cnt_cand tell of those from first_check on whether one of them was already the
-// last.  out: whether the process has ended (1) or is to be taken up again by launched rounds (0), the
-// rounds done, whether they are stable.
+// last.  out: whether the process has ended, is to be taken up again by launched rounds, or has not been taken
+// over at all (the end of round `after` is then still open); the rounds done, whether they are stable.
 //
 // A wave has its SIMD to itself (or shares it with one or two others), so a round takes as long as its
 // instructions: what a thread tests every round (eight records' held bits) is prepared when the records
@@ -64,14 +75,14 @@ template <bool SMALL>
 __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     int4 *state, const int32_t *__restrict__ list_off, const Rec32 *__restrict__ rec, unsigned long long *claim, int after,
     int first_check, int cap, int n_lb, int held_words, uint32_t *held, const int32_t *__restrict__ cnt_lost,
-    const int32_t *__restrict__ cnt_cand, int32_t *out)
+    const int32_t *__restrict__ cnt_cand, int32_t *effort, int32_t *out)
 {
     __shared__ uint32_t s_held[2][kHeldMaxWords + 4];           // the word behind the last job's is all ones: nobody's job
     __shared__ SoloTables s_tabs;       // the claims of this round and of the one before or after it
     __shared__ unsigned long long s_piece[kSoloMaxWaves][kWave];        // a wave's claims for pieces of list blocks
     __shared__ int s_at[kSoloMaxWaves][kWave];                  // whose they are: thread << 6 | lane
     __shared__ unsigned long long s_log[kSoloMaxWaves][kWave];  // grants not yet written to the state: slot << 32 | job
-    // by round stamp: somebody claims, a wave gives up, (round << 8 | most pieces of a wave), open lanes found nothing more
+    // by round stamp: somebody claims, a wave gives up, (round << 8 | most effort of a wave), open lanes found nothing more
     __shared__ int4 s_ctl[2];
     __shared__ int s_flag;
     __shared__ int s_order[SMALL ? kSoloSmallBlocks * kWave : 1];      // per list block its open lanes, lowest gap first: gap << 6 | lane
@@ -81,6 +92,17 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     const int u = lane * waves + wave;
     const uint32_t nobody = uint32_t(held_words) * 32u;
 
+    if (effort[after & 1] > (n_lb <= kSoloFewBlocks ? kSoloStartFew : kSoloStart) * waves) {
+        if (tid == 0) {
+            out[kSoloDone] = kSoloPutOff; out[kSoloRounds] = after; out[kSoloStable] = 0;
+            for (int r = first_check; r <= after; ++r)
+                if (cnt_cand[r] == 0 || (r < after && cnt_lost[r] == 0)) {
+                    out[kSoloDone] = kSoloEnded; out[kSoloRounds] = r; out[kSoloStable] = 1;
+                    break;
+                }
+        }
+        return;
+    }
     for (int i = tid; i < held_words; i += threads) s_held[0][i] = s_held[1][i] = held[size_t((after + 1) & 1) * held_words + i];
     for (int i = tid; i < kSoloTable; i += threads) s_tabs.word[0][i] = s_tabs.word[1][i] = 0;
     if (tid < 2) { s_ctl[tid] = make_int4(0, 0, 0, 0); s_held[tid][held_words] = ~0u; }
@@ -92,28 +114,38 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     int e = 0, list_end = 0;            // its place in the list: what covers its highest open lane before it is held
     {
         bool any_lost = false;
-        for (int i = 0; i * waves + wave < n_lb; ++i) {
-            const int slot0 = (i * waves + wave) * kWave;
-            int4 raw = state[slot0 + lane];
-            const int g = raw.w >> 2;
-            if ((raw.w & 3) == 0 && raw.y >= 0) {
-                if (claim[raw.y] == claim_of(after, g)) {
-                    state[slot0 + lane].w = raw.w |= 1;
-                } else {
-                    state[slot0 + lane].y = -1;
-                    any_lost = true;
+        constexpr int Q = 4;            // list blocks whose state and claims are asked for together
+        for (int i0 = 0; i0 * waves + wave < n_lb; i0 += Q) {
+            int4 raw[Q];
+            unsigned long long word[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) raw[q] = state[min((i0 + q) * waves + wave, n_lb - 1) * kWave + lane];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) word[q] = claim[max(raw[q].y, 0)];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int i = i0 + q, slot0 = (i * waves + wave) * kWave;
+                if (i * waves + wave >= n_lb) break;
+                const int g = raw[q].w >> 2;
+                if ((raw[q].w & 3) == 0 && raw[q].y >= 0) {
+                    if (word[q] == claim_of(after, g)) {
+                        state[slot0 + lane].w = raw[q].w |= 1;
+                    } else {
+                        state[slot0 + lane].y = -1;
+                        any_lost = true;
+                    }
                 }
+                const unsigned long long on = __ballot((raw[q].w & 3) == 0);
+                int place = 0;
+                for (unsigned long long m = on; m; m &= m - 1)
+                    place += __builtin_amdgcn_readlane(g, __ffsll((long long)m) - 1) < g;
+                if ((on >> lane) & 1ull) {
+                    if (SMALL) s_order[SMALL ? slot0 + place : 0] = (g << 6) | lane;
+                    else state[slot0 + place].z = (g << 6) | lane;
+                }
+                const int e_top = __builtin_amdgcn_readlane(raw[q].x, on ? 63 - __clzll((long long)on) : 0);
+                if (lane == i) { open = on; e = e_top; }
             }
-            const unsigned long long on = __ballot((raw.w & 3) == 0);
-            int place = 0;
-            for (unsigned long long m = on; m; m &= m - 1)
-                place += __builtin_amdgcn_readlane(g, __ffsll((long long)m) - 1) < g;
-            if ((on >> lane) & 1ull) {
-                if (SMALL) s_order[SMALL ? slot0 + place : 0] = (g << 6) | lane;
-                else state[slot0 + place].z = (g << 6) | lane;
-            }
-            const int e_top = __builtin_amdgcn_readlane(raw.x, on ? 63 - __clzll((long long)on) : 0);
-            if (lane == i) { open = on; e = e_top; }
         }
         if (any_lost) s_flag = 1;
         if (u < n_lb) list_end = list_off[u + 1];
@@ -187,7 +219,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         s_flag = 0;
         for (int r = first_check; r <= after; ++r)
             if (cnt_cand[r] == 0 || (r < after ? cnt_lost[r] != 0 : lost_before) == false) {
-                out[kSoloDone] = 1; out[kSoloRounds] = r; out[kSoloStable] = 1;
+                out[kSoloDone] = kSoloEnded; out[kSoloRounds] = r; out[kSoloStable] = 1;
                 s_flag = 1;
                 break;
             }
@@ -205,7 +237,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         }
         n_log = 0;
     };
-    int strain = 0;             // pieces beyond what is easy, summed up
+    int strain = 0;             // effort beyond what is easy, summed up
     int done = after;           // rounds finished
     int ended = 0, stable = 0;
     uint32_t marked = nobody, marked_piece = nobody;    // the jobs this lane marked a round ago
@@ -220,7 +252,8 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         uint32_t job = 0;
         int lo = 0;
         // the job of the highest open lane: eight records a step
-        for (int step = 0;; ++step) {
+        int step = 0;
+        for (;; ++step) {
             uint32_t b[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) b[q] = is_held[job_of[q] >> 5];
@@ -255,14 +288,14 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
             have = have | found;
             looking = looking & !found;
             const unsigned long long look = __ballot(looking);
-            if (!look || (step >= kSoloSteps && (look & (look - 1)) == 0)) break;
+            if (!look || (step >= kSoloSteps && (look & (look - 1)) == 0) || step >= kSoloMostSteps) break;
         }
         found = have;
         const bool split = found & (lo > bottom);
         unsigned long long together = __ballot(looking | split);
         int n_pieces = 0;
-        bool over = false;
-        if (together) {
+        bool over = step >= kSoloMostSteps;     // a round for many thread blocks
+        if (together && !over) {
             // list blocks the whole wave looks at: those still looking, and those in pieces
             const unsigned long long have_first = __ballot(found);
             while (together) {
@@ -346,8 +379,10 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
                 marked_piece = uint32_t(v >> 20) & 0xfffffu;
                 set_mark(marked_piece);
             }
-            if (lane == 0 && over) s_ctl[half].y = round;
-            if (lane == 0 && n_pieces > kSoloEasyPieces) atomicMax(&s_ctl[half].z, (round << 8) | n_pieces);
+        }
+        if (n_pieces + step > kSoloEasy && lane == 0) {
+            if (over) s_ctl[half].y = round;
+            atomicMax(&s_ctl[half].z, (round << 8) | (n_pieces + step));
         }
         if (lane == 0) {
             if (todo != 0 || n_pieces) s_ctl[half].x = round;
@@ -391,7 +426,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
             }
         }
         done = round;
-        strain = max(strain + max((ctl.z >> 8) == round ? (ctl.z & 255) - kSoloEasyPieces : 0, 0) - 1, 0);
+        strain = max(strain + max((ctl.z >> 8) == round ? (ctl.z & 255) - kSoloEasy : 0, 0) - 1, 0);
         if (round == cap || strain > kSoloPatience) {
             // the block stops here.  A lane still open has lost this round; if there is none, the process has ended with it
             if (open) s_flag = 1;
@@ -403,9 +438,12 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         }
     }
     flush();
-    if (tid == 0) { out[kSoloDone] = ended; out[kSoloRounds] = done; out[kSoloStable] = stable; }
+    if (tid == 0) {
+        out[kSoloDone] = ended ? kSoloEnded : kSoloHandedBack; out[kSoloRounds] = done; out[kSoloStable] = stable;
+        effort[0] = effort[1] = 0;
+    }
     if (ended) return;
-    // too many pieces: the state as a launched round leaves it, but for the outcome already known
+    // too much work: the state as a launched round leaves it, but for the outcome already known
     __syncthreads();
     // (the bitmap the next round would read: the jobs of the last one are marked in that one only)
     for (int i = tid; i < held_words; i += threads) held[i] = held[held_words + i] = s_held[(done + 1) & 1][i];

@@ -419,12 +419,15 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     uint32_t *held = ws_ptr<uint32_t>(ctx, L.g_held);
     // the block that runs rounds by itself: it needs the held bitmap, a thread per list block, and keys
     // that never fall along a job's atoms (a minimum gain above the distance of two capacities of the
-    // hysteresis set can let a longer fit end in a shorter cut); and more than a few rounds, which cost no
-    // more launched than the block needs to start and report (240 us of a Large tick of eight rounds)
+    // hysteresis set can let a longer fit end in a shorter cut); and more than a few rounds to go, which cost no
+    // more launched than the block needs to start and report (20 us of a Medium batch, 200 at 630 list blocks)
     bool rising = true;
     for (int i = 1; i < ctx->hyst_used_n_caps; ++i)
         rising = rising && int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] >= ctx->hyst_used_min_gain;
-    const bool solo = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks && cap >= kSoloFirstRounds + kSoloFewRounds;
+    const bool solo_fits = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks;
+    const int solo_few = kSoloFewRounds + n_subs / kSoloBlocksPerRound;
+    const int solo_first = n_subs <= kSoloFewBlocks ? kSoloFirstFew : kSoloFirstMany;
+    const bool solo = solo_fits && cap >= solo_first + solo_few;
     const int solo_waves = (n_subs + kWave - 1) / kWave > kSoloMinWaves ? (n_subs + kWave - 1) / kWave : kSoloMinWaves;
     const bool long_lists = n_entries >= int64_t(kFirstLong) * n_subs;
     auto launch_round = [&](int64_t k, int propose) {
@@ -443,7 +446,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         auto go = [&](auto kern, auto *records) {
             hipLaunchKernelGGL(kern, dim3(round_grid), dim3(kRoundBlock), 0, st, state, list_off, records, claim, int(k), propose, n_subs,
                                with_bitmap ? held_words : 0, with_bitmap ? held : static_cast<uint32_t *>(nullptr), lb_begin,
-                               lb_end, gap_order, cnt_lost, cnt_cand);
+                               lb_end, gap_order, cnt_lost, cnt_cand, solo ? counters + 14 : static_cast<int32_t *>(nullptr));
         };
         if (wide_records)
             go(with_bitmap ? k_grant_round<true, Rec64> : k_grant_round<false, Rec64>, static_cast<const Rec64 *>(rec));
@@ -454,24 +457,30 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     std::vector<int32_t> h_lost, h_cand;
     int64_t launched = 0;        // kernels 1..launched have been enqueued
     int64_t next_check = 1;      // first round whose end is not yet decided
+    int64_t open_left = cap;     // rounds that can still follow, as far as is known
     bool finished = false;
-    int64_t batch = solo ? kSoloFirstRounds : 64;   // rounds enqueued between looks at the flags; grows, a finished batch costs little
+    constexpr int64_t kLaunchedRounds = 64;
+    int64_t batch = solo ? solo_first : kLaunchedRounds;   // rounds enqueued between looks at the flags; grows, a finished batch costs little
+    const int64_t most_rounds = solo ? 256 : 1024;  // (a look at whether the block can go on costs three or four rounds)
     while (!finished) {
-        const int64_t upto = (launched + batch < cap) ? launched + batch : cap;
-        if (batch < 1024) batch *= solo ? 4 : 2;
+        const bool take_over = solo && cap - launched - batch >= solo_few;
+        if (!take_over && batch < kLaunchedRounds) batch = kLaunchedRounds;
+        const int64_t rounds = batch < open_left ? batch : open_left;
+        const int64_t upto = (launched + rounds < cap) ? launched + rounds : cap;
+        if (batch < most_rounds) batch *= 2;
         for (int64_t k = launched + 1; k <= upto; ++k) SJA_HIP(launch_round(k, 1), "k_grant_round launch");
-        if (solo && upto < cap) {
+        if (take_over) {
             auto solo_kern = n_subs <= kSoloSmallBlocks ? k_grant_solo<true> : k_grant_solo<false>;
             hipLaunchKernelGGL(solo_kern, dim3(1), dim3(solo_waves * kWave), 0, st, state, list_off, static_cast<const Rec32 *>(rec),
                                claim, int(upto), int(next_check), int(cap), n_subs, held_words, held, cnt_lost, cnt_cand,
-                               counters + 8);
+                               counters + 14, counters + 8);
             SJA_HIP(hipGetLastError(), "k_grant_solo launch");
             int32_t h_out[3] = {0, 0, 0};
             SJA_HIP(hipMemcpyAsync(h_out, counters + 8, sizeof(h_out), hipMemcpyDeviceToHost, st), "rounds readback");
             SJA_HIP(hipStreamSynchronize(st), "round synchronise");
             launched = h_out[kSoloRounds];
-            next_check = launched + 1;
-            if (h_out[kSoloDone]) {
+            next_check = h_out[kSoloDone] == kSoloPutOff ? launched : launched + 1;
+            if (h_out[kSoloDone] == kSoloEnded) {
                 result[0] = h_out[kSoloRounds];
                 result[1] = h_out[kSoloStable];
                 finished = true;
@@ -491,7 +500,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         SJA_HIP(hipMemcpyAsync(&h_open, counters + 12, 4, hipMemcpyDeviceToHost, st), "open count");
         SJA_HIP(hipStreamSynchronize(st), "round synchronise");
         // every further round grants at least one open position: no point in enqueueing more than that
-        if (int64_t(h_open) + 1 < batch) batch = int64_t(h_open) + 1;
+        open_left = int64_t(h_open) + 1;
         for (int64_t r = next_check; r <= upto; ++r) {
             if (h_cand[size_t(r)] == 0) { result[0] = int32_t(r); result[1] = 1; finished = true; break; }
             if (r + 1 > known) { next_check = r; break; }              // losers of r not counted yet

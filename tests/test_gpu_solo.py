@@ -83,18 +83,20 @@ def test_jobs_that_meet_in_a_claim_slot(engine, oracle, gaps, jobs):
     full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
 
 
-def _by_windows(caps, windows, jobs_each, gaps_per_window=1, common=0, misfits=0):
+def _by_windows(caps, windows, jobs_each, gaps_per_window=1, common=0, misfits=0, first=0):
     """Every capacity holds every job; each capacity has gaps of the same windows, and a window's best job
     is one as long as the window: a round serves one capacity, in as many pieces as there are windows.
-    `common` jobs fit every gap and come last, `misfits` fit none (they only lift the bound on the rounds)."""
+    `first` jobs fit every gap and come before those, `common` ones after them; `misfits` fit none (they only
+    lift the bound on the rounds)."""
     wl = make_workload("tiny", 0, n_gaps=8, n_jobs=8)
-    wl.n_gaps, wl.n_jobs = caps * windows * gaps_per_window, windows * jobs_each + common + misfits
+    wl.n_gaps, wl.n_jobs = caps * windows * gaps_per_window, windows * jobs_each + common + first + misfits
     wl.W = np.tile(np.repeat(np.arange(1000, 1000 + windows, dtype=np.int32), gaps_per_window), caps)
     wl.C = np.repeat(np.arange(10000, 10000 + caps, dtype=np.int32), windows * gaps_per_window)
     wl.seg_off = np.arange(wl.n_jobs + 1, dtype=np.int64)
-    lengths = [np.repeat(np.arange(1000, 1000 + windows), jobs_each), np.full(common, 500), np.full(misfits, 1000)]
+    lengths = [np.repeat(np.arange(1000, 1000 + windows), jobs_each), np.full(common, 500), np.full(first + misfits, 1000)]
     wl.dur = np.concatenate(lengths).astype(np.int32)
     wl.mem = np.full(wl.n_jobs, 5000, dtype=np.int32)
+    wl.mem[wl.n_jobs - misfits - first:] = 6000
     wl.mem[wl.n_jobs - misfits:] = 90000
     wl.safe = np.ones(wl.n_jobs, dtype=np.uint8)
     wl.progress = np.zeros(wl.n_jobs, dtype=np.int32)
@@ -104,21 +106,24 @@ def _by_windows(caps, windows, jobs_each, gaps_per_window=1, common=0, misfits=0
     return wl
 
 
-@pytest.mark.parametrize("caps", [6, 7, 8, 9, 23, 28])
-def test_last_round_in_many_pieces(engine, oracle, caps):
-    # the pieces of rounds 5 to 8 add up to the block's patience: with 8 capacities it stops in the very round
-    # that serves the last gap, with fewer it has ended before, with more gaps are left
-    wl = _by_windows(caps, 64, caps)
+@pytest.mark.parametrize("windows,first,caps", [(w, 10, c) for w in (24, 28, 32) for c in (4, 5, 6, 7, 8)] +
+                         [(64, f, c) for f in (0, 10) for c in (3, 7, 8, 9, 28)])
+def test_last_round_in_many_pieces(engine, oracle, windows, first, caps):
+    # a round serves one capacity in as many pieces as it has windows, and the rounds add up to the block's
+    # patience: it stops there, and with some number of capacities that is the very round that serves the last
+    # gap (5 capacities of 28 or 32 windows, 7 of 24).  `first` jobs come before, one a round, so that the
+    # block has taken over by then
+    wl = _by_windows(caps, windows, caps, first=first)
     t = full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
-    assert t.rounds.cpu().tolist() == [caps, 1]
+    assert t.rounds.cpu().tolist() == [first + caps, 1]
 
 
 @pytest.mark.parametrize("caps,windows,jobs_each,gaps_per_window,common",
-                         [(1, 1, 3, 64, 0), (1, 1, 4, 64, 0), (1, 1, 5, 64, 0), (3, 1, 4, 30, 0),
-                          (28, 64, 10, 1, 9), (28, 64, 10, 1, 10), (28, 64, 10, 1, 11), (28, 64, 20, 1, 0)])
+                         [(1, 1, 3, 64, 0), (1, 1, 4, 64, 0), (1, 1, 5, 64, 0), (3, 1, 4, 30, 0)] +
+                         [(28, 64, 10, 1, c) for c in (9, 10, 11, 13, 14, 15)] + [(28, 64, 20, 1, 0)])
 def test_lists_that_end_where_the_block_takes_over(engine, oracle, caps, windows, jobs_each, gaps_per_window, common):
-    # the jobs are used up one round before, with and one round after the last launched round (4, or 20 where
-    # the block stops in round 5 because of its pieces); gaps are left, so one more round finds nothing
+    # the jobs are used up one round before, with and one round after the last launched round (4, or 24 where
+    # the rounds before are in too many pieces); gaps are left, so one more round finds nothing
     wl = _by_windows(caps, windows, jobs_each, gaps_per_window, common, misfits=64)
     t = full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
     assert t.rounds.cpu().tolist() == [jobs_each + common + 1, 1]
