@@ -26,8 +26,10 @@ def test_caps_around_the_hand_over(engine, oracle, max_rounds):
 
 
 @pytest.mark.parametrize("name,gaps,jobs", [("stress", 900, 700), ("stress", 700, 1500), ("stress", 130, 3000), ("large", 70, 5000), ("large", 1025, 513), ("small", 65, 4000),
-                                            ("medium", 1400, 40), ("tiny", 3, 700)])
+                                            ("medium", 1400, 40), ("tiny", 3, 700),
+                                            ("stress", 5001, 300), ("medium", 5003, 700)])
 def test_many_pieces_and_lists_that_run_dry(engine, oracle, name, gaps, jobs):
+    # (the last two have more list blocks than those whose gap orders are kept in LDS)
     wl = make_workload(name, gaps + jobs, n_gaps=gaps, n_jobs=jobs)
     full_tick_check(engine, oracle, wl, policies=[0, 1, 2, 3], resolve_modes=(0,))
 
@@ -127,3 +129,35 @@ def test_lists_that_end_where_the_block_takes_over(engine, oracle, caps, windows
     wl = _by_windows(caps, windows, jobs_each, gaps_per_window, common, misfits=64)
     t = full_tick_check(engine, oracle, wl, policies=[0], resolve_modes=(0,))
     assert t.rounds.cpu().tolist() == [jobs_each + common + 1, 1]
+
+
+def test_launched_rounds_in_several_batches(engine):
+    # more jobs than the one block's bitmaps hold: hundreds of launched rounds, in batches of 64, 128 and 256,
+    # caps inside a batch and at the edges of one, against the matrix rounds (checked against the oracle elsewhere)
+    import paper_2509_19086_amd as P
+    jobs, gaps = 140001, 470
+    wl = make_workload("tiny", 4, n_gaps=gaps, n_jobs=8)
+    rng = np.random.default_rng(4)
+    wl.n_jobs = jobs
+    wl.seg_off = np.arange(jobs + 1, dtype=np.int64)
+    wl.dur = rng.integers(1, 700, size=jobs).astype(np.int32)
+    wl.mem = rng.integers(256, 41000, size=jobs).astype(np.int32)
+    wl.safe, wl.progress = np.ones(jobs, dtype=np.uint8), np.zeros(jobs, dtype=np.int32)
+    wl.wait, wl.sla_class = np.zeros(jobs, dtype=np.int32), np.ones(jobs, dtype=np.uint8)
+    wl.W, wl.C = np.full(gaps, 1500, dtype=np.int32), np.full(gaps, 40960, dtype=np.int32)
+    t = P.DeviceTick(engine, wl, want_cut=False)
+    t.prepare()
+    try:
+        for cap in (0, 64, 65, 191, 192, 193, 447):
+            par = P.Params.make(0, max_rounds=cap)
+            t.fit_select(par)
+            got = []
+            for mode in (1, 0):
+                engine.sja_set_resolve_mode(mode)
+                t.resolve(par)
+                got.append([x.cpu().numpy().copy() for x in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds)])
+            for a, b in zip(*got):
+                np.testing.assert_array_equal(a, b)
+            assert got[1][4].tolist() == [cap or gaps, int(cap == 0)]
+    finally:
+        engine.sja_set_resolve_mode(0)
