@@ -187,8 +187,7 @@ __global__ __launch_bounds__(256) void k_gap_plan(int n_gaps, int gc, int sb, in
                                                   int32_t *chunk_begin, int32_t *chunk_end,
                                                   int32_t *chunk_class, int32_t *chunk_sub,
                                                   int32_t *sub_begin, int32_t *sub_end,
-                                                  int32_t *sub_class, int32_t *__restrict__ gap_cls,
-                                                  int32_t *__restrict__ run_end)
+                                                  int32_t *__restrict__ gap_cls, int32_t *__restrict__ run_end)
 {
     static_assert(kMaxClasses <= kWave, "one wave scans the classes");
     __shared__ int s_begin[kMaxClasses + 1], s_chunk0[kMaxClasses + 1], s_sub0[kMaxClasses + 1];
@@ -286,33 +285,30 @@ __global__ __launch_bounds__(256) void k_gap_plan(int n_gaps, int gc, int sb, in
         const int b = s_begin[c] + (u - s_sub0[c]) * sb;
         sub_begin[u] = b;
         sub_end[u] = min(s_begin[c + 1], b + sb);
-        sub_class[u] = c;
     }
 }
 
 // --------------------------------------------------------------------------
 // Start tables (table-driven path).  A row is a run of sorted positions of one
-// capacity class: the chunks of the stepping kernels (the table sja_fit and
-// sja_fit_select need) or the finer sub-blocks (the table the grant lists are
-// built from).
+// capacity class, a chunk of the stepping kernels.
 //   start[row][j] = #atoms of job j usable by the first gap of the row
 //   ncap[c][j]    = #atoms any gap of class c can reach (peak <= C_c and
-//                   duration <= the class's largest window); null: not wanted
+//                   duration <= the class's largest window)
 // A block takes kStartsJobs consecutive jobs: their atoms go to LDS once
 // (coalesced), then every lane keeps one of the jobs (lane % kStartsJobs) and
 // the lanes run along the classes and along the rows, each lane with a binary
 // search of its own: both counts are "how many atoms have a running duration
 // (peak) of at most x", and both sequences ascend.  A wave's store is then four
 // rows of sixteen consecutive jobs, 64 bytes each (a wave per job, lanes along
-// the rows, wrote every value into a cache line of its own: 0.6 ms for the 565
-// sub-block rows of the Stress workload against 0.14).
+// the rows, wrote every value into a cache line of its own: 0.6 ms for 565 rows
+// of the Stress workload against 0.14).
 // --------------------------------------------------------------------------
 constexpr int kStartsAtoms = 512;           // atoms of a job kept in LDS (more: the rest is read from memory)
 constexpr int kStartsJobs = 8;              // consecutive jobs of a block
 constexpr int kStartsRows = 1024;           // rows whose window and class are kept in LDS
 
 __global__ __launch_bounds__(256) void k_fit_starts(
-    int n_jobs, int rows_word, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
+    int n_jobs, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
     const int32_t *__restrict__ row_begin, const int32_t *__restrict__ row_class, const int32_t *__restrict__ gap_w,
     const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
     const int2 *__restrict__ atom_dp, const int32_t *__restrict__ n_atoms,
@@ -326,7 +322,7 @@ __global__ __launch_bounds__(256) void k_fit_starts(
     __shared__ int s_cap[kMaxClasses], s_wmax[kMaxClasses];
     __shared__ int s_ncap[kMaxClasses][kStartsJobs];
     if (!plan[kPlanTabled]) return;
-    const int n_classes = plan[kPlanClasses], n_rows = plan[rows_word];
+    const int n_classes = plan[kPlanClasses], n_rows = plan[kPlanChunks];
     const int tid = threadIdx.x;
     for (int q = tid; q < min(n_rows, kStartsRows); q += 256) {
         s_roww[q] = gap_w[row_begin[q]];
@@ -380,7 +376,7 @@ __global__ __launch_bounds__(256) void k_fit_starts(
         }
         const int reach = min(lo, count_dur(s_wmax[c]));
         s_ncap[c][jl] = reach;
-        if (ncap_tab && live) ncap_tab[int64_t(c) * n_jobs + j] = reach;
+        if (live) ncap_tab[int64_t(c) * n_jobs + j] = reach;
     }
     __syncthreads();
     for (int q = group; q < n_rows; q += GROUPS) {

@@ -1,6 +1,7 @@
 // Device-wide building blocks used by the grant path: an exclusive scan and a
-// stable least-significant-digit radix pass (8-bit digits).  Plain, three
-// kernels each; sizes here are tens of millions of items at most.
+// stable least-significant-digit radix pass (8-bit digits), each of three
+// kernels, or of one or two where the items are few; sizes here are tens of
+// millions of items at most.
 #pragma once
 
 #include <type_traits>

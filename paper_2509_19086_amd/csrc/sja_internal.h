@@ -53,7 +53,7 @@ struct Layout {
     size_t class_marks;                    // [kMaxClasses+1] int32: first positions of the capacity runs, unordered
     size_t class_dmax;                     // [kMaxClasses] int32: largest first-atom duration among the jobs that fit the class
     size_t chunk_begin, chunk_end, chunk_class, chunk_sub;  // [chunk_bound] int32
-    size_t sub_begin, sub_end, sub_class;  // [sub_bound] int32
+    size_t sub_begin, sub_end;             // [sub_bound] int32
     size_t start_tab;                      // [chunk_bound * J] int32: per chunk of the stepping kernels
     size_t ncap_tab;                       // [kMaxClasses * J] int32
     size_t sel_part;                       // [ceil(J/kSelBlock) * G] SelPartial
@@ -77,7 +77,7 @@ struct Layout {
     size_t lb_off;                         // [sub_bound+2] int32: first list block of a sub-block
     size_t g_list_off;                     // [list_bound+2] int32
     size_t g_held;                         // 2 x held_bitmap_words(J) uint32: jobs held before a round, two alternating copies
-    size_t g_state;                        // [list_bound * 64] int4: pointer, candidate job, candidate atom, flag | gap << 2
+    size_t g_state;                        // [list_bound * 64] int4: pointer, candidate job, scratch of k_grant_solo, flag | gap << 2
     size_t g_cnt_lost, g_cnt_cand;         // [min(G,J)+4] int32
     int64_t atom_cap, entry_cap;
     size_t total;
@@ -102,7 +102,7 @@ inline int64_t fit_chunk_bound(int64_t G, int64_t J)
 }
 
 // Sub-blocks: runs of at most 64 sorted positions inside one capacity class;
-// the start tables and the grant lists are kept per sub-block.
+// the grant lists are kept per sub-block or per piece of one.
 inline int fit_sub_len(int64_t G, int64_t J) { const int gc = fit_chunk_len(G, J); return gc < 64 ? gc : 64; }
 
 inline int64_t fit_sub_bound(int64_t G, int64_t J)
@@ -155,7 +155,6 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     L.chunk_sub = take(cb * 4);
     L.sub_begin = take(ub * 4);
     L.sub_end = take(ub * 4);
-    L.sub_class = take(ub * 4);
     L.start_tab = take(cb * size_t(J) * 4);
     L.ncap_tab = take(size_t(kMaxClasses) * size_t(J) * 4);
     size_t job_tiles = size_t((J + kSelBlock - 1) / kSelBlock);

@@ -707,14 +707,6 @@ __global__ __launch_bounds__(256) void k_validate(
 // partial per (job tile, gap); k_select_reduce finishes the arg-max.
 // Key order: hi desc, lo desc, job asc.
 // --------------------------------------------------------------------------
-__device__ __forceinline__ bool key_better(unsigned long long hi_a, unsigned long long lo_a, int j_a,
-                                           unsigned long long hi_b, unsigned long long lo_b, int j_b)
-{
-    if (hi_a != hi_b) return hi_a > hi_b;
-    if (lo_a != lo_b) return lo_a > lo_b;
-    return j_a < j_b;
-}
-
 // The key of every prefix of every job, ((tier << 62) | F * multiplier) + 1, once
 // per call: the stepping kernel below then fetches a finished key where a job's
 // cut changes instead of (duration, peak) and three 64-bit multiplies per lane.
