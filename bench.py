@@ -52,9 +52,9 @@ def secondary_rates(wl, n_atoms_total, call_ms, rounds):
 # sources are hashed, and a different hash means the counters are stale.
 FIT_TRAFFIC = {
     "workload": ("stress", 0),
-    "sources_sha256": "8f500af28be055d6e56be34c42cf16eb7ca44503498ad0cc0e6a3f8285d75b58",
-    "fetch_kib": 51419.6, "fetch_scale": 2.0,
-    "write_kib": 8391835.9, "write_scale": 1.0,
+    "sources_sha256": "7d94a74aaf7dbfd619afa1c38a3206c6b439246404927ed2df28b882d864af6b",
+    "fetch_kib": 51540.0, "fetch_scale": 2.0,
+    "write_kib": 8391880.8, "write_scale": 1.0,
 }
 
 
