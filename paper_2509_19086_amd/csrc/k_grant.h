@@ -31,7 +31,10 @@
 namespace sja {
 
 // A list entry as it is sorted: list block (27 bits) : job (24) : lane range hi (7) : lo (6).
-constexpr int kEntryJobShift = 13, kEntryBlockShift = 37;
+// With places: list block (18 bits) : place of the atom's first position (16) : job (17) : hi : lo; a place is
+// the list block and lane of a position (up to kPlacedBlocks list blocks and kPlacedJobs jobs).
+constexpr int kEntryJobShift = 13, kEntryBlockShift = 37, kEntryPlaceShift = 30, kEntryPlacedBlockShift = 46;
+constexpr int kPlacedBlocks = 1024, kPlacedJobs = 1 << (kEntryPlaceShift - kEntryJobShift);
 static_assert(SJA_MAX_JOBS <= 1 << (kEntryBlockShift - kEntryJobShift), "job ids fit an entry");
 
 struct PolicyDev {
@@ -320,7 +323,7 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
     const int32_t *__restrict__ lb_begin, const int32_t *__restrict__ pos_block, const int32_t *__restrict__ pos_tab,
     const int32_t *__restrict__ gap_w, const int32_t *__restrict__ gap_c, const uint32_t *__restrict__ perm,
     const int4 *__restrict__ info, int32_t *chunk_at, int32_t *list_count, unsigned long long *total,
-    unsigned long long *__restrict__ ekey)
+    unsigned long long *__restrict__ ekey, int placed)
 {
     constexpr bool kLds = WIN > 0;
     __shared__ int s_w[kLds ? WIN : 1];
@@ -407,10 +410,13 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
                 if (!__ballot(n > 0)) continue;
                 const int upto = wave_scan_add(n);
                 const int64_t out = at + (upto - n);
-                auto put = [&](int64_t to, int k, int job, int lo, int hi) {
-                    ekey[to] = (static_cast<unsigned long long>(uint32_t(k)) << kEntryBlockShift) |
+                const int block_shift = placed ? kEntryPlacedBlockShift : kEntryBlockShift;
+                auto put = [&](int64_t to, int k, int job, int lo, int hi, int place) {
+                    ekey[to] = (static_cast<unsigned long long>(uint32_t(k)) << block_shift) |
+                               (static_cast<unsigned long long>(uint32_t(place)) << kEntryPlaceShift) |
                                (static_cast<unsigned long long>(uint32_t(job)) << kEntryJobShift) | uint32_t((hi << 6) | lo);
                 };
+                const int place = placed && n > 0 ? (k_lo << 6) + p1 - begin_of(k_lo) : 0;
                 unsigned long long wide = __ballot(n > 2);
                 if (__popcll(wide) > kEntryFewWide) {
                     // many ranges over several list blocks: a lane per entry (its range is the last one that starts
@@ -428,10 +434,11 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
                         carry = __builtin_amdgcn_readlane(from_lane, kWave - 1);
                         const int fl = max(from_lane, 0);
                         const int k = e0 + lane - __shfl(start, fl, kWave), fn = __shfl(n, fl, kWave), fk = __shfl(k_lo, fl, kWave) + k;
-                        const int f1 = __shfl(p1, fl, kWave), f2 = __shfl(p2, fl, kWave), fj = __shfl(x.x, fl, kWave);
+                        const int f1 = __shfl(p1, fl, kWave), f2 = __shfl(p2, fl, kWave), fj = __shfl(x.x, fl, kWave),
+                                  fp = placed ? __shfl(place, fl, kWave) : 0;
                         if (e0 + lane < total_n) {
                             const int b = begin_of(fk);
-                            put(at + e0 + lane, fk, fj, k == 0 ? f1 - b : 0, (k == fn - 1 ? f2 : begin_of(fk + 1)) - b);
+                            put(at + e0 + lane, fk, fj, k == 0 ? f1 - b : 0, (k == fn - 1 ? f2 : begin_of(fk + 1)) - b, fp);
                         }
                     }
                 } else {
@@ -439,14 +446,14 @@ __global__ __launch_bounds__(kEntryThreads) void k_list_entries(
                     // atom's lane, the whole list blocks between them, if any, by the wave together
                     if (n > 0) {
                         const int b = begin_of(k_lo);
-                        put(out, k_lo, x.x, p1 - b, (n == 1 ? p2 : begin_of(k_lo + 1)) - b);
+                        put(out, k_lo, x.x, p1 - b, (n == 1 ? p2 : begin_of(k_lo + 1)) - b, place);
                     }
-                    if (n > 1) put(out + n - 1, k_lo + n - 1, x.x, 0, p2 - begin_of(k_lo + n - 1));
+                    if (n > 1) put(out + n - 1, k_lo + n - 1, x.x, 0, p2 - begin_of(k_lo + n - 1), place);
                     for (; wide; wide &= wide - 1) {
                         const int t = __ffsll((long long)wide) - 1;
-                        const int tn = lane_value(n, t), tk = lane_value(k_lo, t), tj = lane_value(x.x, t);
+                        const int tn = lane_value(n, t), tk = lane_value(k_lo, t), tj = lane_value(x.x, t), tp = lane_value(place, t);
                         const int64_t to = at + lane_value(upto, t) - tn;
-                        for (int k = lane + 1; k < tn - 1; k += kWave) put(to + k, tk + k, tj, 0, begin_of(tk + k + 1) - begin_of(tk + k));
+                        for (int k = lane + 1; k < tn - 1; k += kWave) put(to + k, tk + k, tj, 0, begin_of(tk + k + 1) - begin_of(tk + k), tp);
                     }
                 }
                 at += __builtin_amdgcn_readlane(upto, kWave - 1);

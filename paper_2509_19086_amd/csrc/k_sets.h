@@ -1,0 +1,788 @@
+// K4, the calm part of the conflict rounds: many rounds between two looks at the lists.
+//
+// After the first hundreds of rounds nearly all open gaps want the same few
+// jobs: at Stress (32768 gaps x 65536 jobs) most of 9400 rounds name one to
+// three jobs, each by thousands of gaps.  k_grant_solo pays 1.7 to 3 us for such
+// a round, most of it for looking at every list block's list and for its
+// barrier.  Here the rounds are played in batches:
+//   * a wave per list block searches its list for the next free jobs of its
+//     highest open lane; the lanes below that share at least the first of them
+//     are a piece, the rest form further ones (sets_form);
+//   * neighbouring pieces of a capacity class whose gaps want the same jobs for
+//     some rounds to come are joined to a set, a range of the class's sorted
+//     positions (sets_join);
+//   * one wave plays round after round on what lies in LDS, a lane for one to
+//     four sets: the first of the set's jobs that no round has named yet, a claim
+//     for the set's lowest open gap, the outcome (sets_play).  A round is two
+//     trips to LDS and needs no barrier: 0.35 us.
+// A batch ends when some set has used up its jobs or the lowest gaps it has at
+// hand: some 30 to 60 rounds.  Up to kSetsOneBlocks list blocks one launch does
+// all of it (k_sets_one); beyond that the lists are searched by many thread
+// blocks and the rounds played by one, in turn (k_sets_form, k_sets_play).
+//
+// What the sets rely on: along the positions of a class a job's key never falls
+// (F grows with the cut; the host sees to it where the hysteresis rule could
+// undo that).  Take the next free jobs of an open gap, and a gap of the class
+// with a shorter window that gets the same atoms of these jobs: it meets them in
+// the same order and no other free job between them, whatever other gaps are
+// granted meanwhile.  (Another job would come earlier for the longer window,
+// too, but for equal keys; then it is one of these jobs by another atom.)  Every
+// record says from which position on its atom is the job's answer.
+//
+// It takes over from k_grant_solo once the rounds are calm (few list blocks whose
+// lanes want different jobs), and hands back when batches get short.
+#pragma once
+
+#include "k_solo.h"
+
+namespace sja {
+
+constexpr int kSetsWaves = 16, kSetsThreads = kSetsWaves * kWave;
+constexpr int kSetsMaxBlocks = 768;     // list blocks
+constexpr int kSetsOneBlocks = 128;     // and up to which one thread block does it all
+constexpr int kSetsPieces = 6;          // pieces of a list block, at most
+constexpr int kSetsMost = 256;          // sets, at most
+constexpr int kSetsK = 63;              // jobs at hand per set, at most (a lane each)
+constexpr int kSetsRoom = 70;           // 16-bit words for them: twice an odd number (banks); the last four used ones are nobody's job
+constexpr int kSetsHeads = 6144;        // lowest gaps at hand of all sets: as many each as there is room for,
+constexpr int kSetsMostHeads = 63;      // up to so many
+constexpr int kSetsGapsAhead = 8;       // chunks of 64 gaps a wave looks at together,
+constexpr int kSetsFewGaps = 8, kSetsGapsFar = 512;     // and how far for more than a few gaps
+constexpr int kSetsChunk = 4 * kWave;   // records a wave reads at a time, four a lane
+constexpr int kSetsMostSteps = 64;      // chunks a wave reads for one piece before it gives up
+constexpr int kSetsLeastFirst = 16, kSetsLeast = 32;      // jobs that the gaps of a set have in common, at least: at first, and at most
+constexpr int kSetsShort = 8, kSetsPatience = 3;       // batches of so few rounds are short ones; more of those than others by so many end it
+constexpr int kSetsState = 3;           // out[]: k_grant_solo's words, and this one between launches: least << 8 | strain
+enum { kSetsRunning = 4, kSetsLeft = 5 };       // out[kSoloDone]: between launches; on with k_grant_solo
+enum { kSetsPause = 0, kSetsNoClaim = 1, kSetsAtCap = 2 };          // why the rounds of a batch stopped
+
+// The jobs at hand: slots of a hash table, so that a set needs two bytes for a job and a claim has a word of its
+// own, which also says whether the job is held.  A job is named in one round only: its word is the smallest of
+// that round's claims, round of the batch (12 bits) : gap (20 bits), all ones before.  The slot behind the last
+// one is nobody's job: never free.
+constexpr int kSetsSlots = 4096;
+constexpr uint32_t kSetsNoJob = ~0u;
+constexpr int kSetsTries = 16;
+struct SetsJobs {
+    uint32_t job[kSetsSlots];
+    uint32_t claim[kSetsSlots + 1];
+};
+__device__ __forceinline__ void sets_clear(SetsJobs &t, int i)
+{
+    if (i < kSetsSlots) t.job[i] = kSetsNoJob;
+    t.claim[i] = i < kSetsSlots ? ~0u : 0u;
+}
+// The job's slot, -1 if there is none within reach: the set has fewer jobs at hand then.
+__device__ __forceinline__ int sets_slot(SetsJobs &t, uint32_t job)
+{
+    uint32_t h = (job * 2654435761u) >> 20;
+#pragma unroll 1
+    for (int k = 0; k < kSetsTries; ++k) {
+        uint32_t was = t.job[h];
+        if (was == kSetsNoJob) was = atomicCAS(&t.job[h], kSetsNoJob, job);
+        if (was == job || was == kSetsNoJob) return int(h);
+        h = (h + 1) & (kSetsSlots - 1);
+    }
+    return -1;
+}
+static_assert(kSetsSlots == 1 << 12, "slots by the upper 12 bits of the product");
+
+__device__ __forceinline__ unsigned long long sets_readlane64(unsigned long long v, int l)
+{
+    return (static_cast<unsigned long long>(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v >> 32)), l))) << 32) |
+           uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), l));
+}
+
+// A gap's place is its list block and lane: block << 6 | lane, ascending along the positions of a class.
+// The gaps of every class by index, for the lowest ones of a set: by_class[class_begin[c] ...] = (place, gap).
+// 16 waves take a stretch of the gaps each: they count per class, then write behind the waves before them.
+__device__ __forceinline__ void sets_by_class(int n_gaps, int n_classes, const int32_t *__restrict__ class_begin, const int *s_first,
+                                              const int32_t *place_of, int2 *by_class, int (*s_count)[kMaxClasses])
+{
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int each = ((n_gaps + kSetsWaves - 1) / kSetsWaves + kWave - 1) / kWave * kWave;
+    const int begin = wave * each, end = min(begin + each, n_gaps);
+    s_count[wave][lane] = 0;
+    auto class_of = [&](int place) {
+        const int u = place >> 6;
+        int lo = 0, hi = n_classes - 1;         // the last class that begins at or before the list block
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_first[mid] <= u) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    for (int g0 = begin; g0 < end; g0 += kWave)
+        if (g0 + lane < end) atomicAdd(&s_count[wave][class_of(place_of[g0 + lane])], 1);
+    __syncthreads();
+    int at = lane < n_classes ? class_begin[lane] : 0;
+    for (int w = 0; w < wave; ++w) at += s_count[w][lane];
+    __syncthreads();
+    s_count[wave][lane] = at;
+    for (int g0 = begin; g0 < end; g0 += kWave) {
+        const bool valid = g0 + lane < end;
+        const int place = valid ? place_of[g0 + lane] : 0, c = class_of(place);
+        const unsigned long long peers = digit_peers(unsigned(c), valid);
+        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+        const int to = s_count[wave][c];
+        asm volatile("" ::: "memory");          // (the wave's lanes read before one of them writes)
+        if (valid) by_class[to + rank] = make_int2(place, g0 + lane);
+        if (valid && rank == 0) s_count[wave][c] = to + __popcll(peers);
+        asm volatile("" ::: "memory");
+    }
+}
+
+// Per list block what the last search found: its open lanes, where the search for the highest one's jobs goes on,
+// and the pieces.
+struct SetsPiece {
+    uint16_t top, bottom;           // places of its highest and lowest lane
+    uint16_t from_most;             // the highest place from which on one of the first jobs' atoms is the answer
+    uint8_t jobs, last;             // jobs; no more behind them.  No jobs at all: none is left for these lanes
+};
+struct SetsBlock {
+    unsigned long long open;
+    int at, pieces;                 // pieces: -1 if the block has more of them, -2 if the next job lies further on
+    SetsPiece piece[kSetsPieces];
+};
+struct SetsList {                   // the jobs of a piece
+    uint32_t job[kWave];
+    uint16_t from[kWave];
+};
+static_assert(sizeof(SetsBlock) == 64 && sizeof(SetsList) == 384, "layout");
+constexpr int kSetsBlockBytes = int(sizeof(SetsBlock)) + kSetsPieces * int(sizeof(SetsList));      // what a list block needs in all
+
+struct SetsArgs {
+    int4 *state;
+    const int32_t *list_off;
+    const Rec32 *rec;
+    const uint16_t *rec_from;       // per record the place from which on its atom is the job's answer
+    unsigned long long *claim;
+    uint32_t *held;
+    const int32_t *plan, *class_begin, *gap_cls, *lb_begin, *lb_end, *gap_order;
+    int32_t *place_of;              // [gaps]
+    int2 *by_class;                 // [gaps]
+    SetsBlock *block;               // [list blocks]
+    SetsList *list;                 // [list blocks][kSetsPieces]
+    int32_t *low;                   // per class where its lowest open gap lies among its gaps (between launches)
+    int32_t *out;
+    int cap, n_gaps, n_lb, held_words;
+    int build;                      // place_of and by_class are to be made
+};
+
+// The open lanes of list block u, and where the search for the highest one's jobs starts.
+__device__ __forceinline__ void sets_open(const SetsArgs &A, int u, int lane)
+{
+    const int b0 = A.lb_begin[u], len = A.lb_end[u] - b0, slot = u * kWave + lane;
+    if (A.build && lane < len) A.place_of[A.gap_order[b0 + lane]] = slot;
+    const int4 st = A.state[slot];
+    const unsigned long long on = __ballot((st.w & 3) == 0);
+    const int at = __builtin_amdgcn_readlane(st.x, on ? 63 - __clzll((long long)on) : 0);
+    if (lane == 0) {
+        A.block[u].open = on;
+        A.block[u].at = at;
+    }
+}
+
+// The pieces of list block u.  A lane's records lie behind a higher lane's, but for 63 of equal keys.
+__device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, int least, const uint32_t *s_held, uint32_t *s_job, uint32_t *s_from)
+{
+    SetsBlock &B = A.block[u];
+    unsigned long long rest = B.open;
+    if (!rest) return;
+    int at = B.at, n_pieces = 0;
+    const int end = A.list_off[u + 1], last4 = (end - 1) >> 2;
+    auto ask = [&](int i, uint4 &r, ushort4 &f) {
+        const int k = min((i >> 2) + lane, last4);
+        r = reinterpret_cast<const uint4 *>(A.rec)[k];
+        f = reinterpret_cast<const ushort4 *>(A.rec_from)[k];
+    };
+    int first_at = at;
+    for (bool first = true; rest; first = false) {
+    again:
+        const int top = 63 - __clzll((long long)rest);
+        int bottom = __ffsll((long long)rest) - 1;
+        int i0 = at;
+        if (!first) i0 = max(at - 63, __builtin_amdgcn_readfirstlane(A.state[u * kWave + top].x));
+        int n = 0, hit = -1, base = i0 & ~3, steps = 0;
+        if (i0 < end) {
+            uint4 r0, r1;
+            ushort4 f0, f1;
+            ask(base, r0, f0);
+            ask(base + kSetsChunk, r1, f1);
+            for (;;) {
+                const uint32_t r[4] = {r0.x, r0.y, r0.z, r0.w};
+                const uint16_t f[4] = {f0.x, f0.y, f0.z, f0.w};
+                unsigned ok = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const Rec32 x{r[k]};
+                    const int i = base + 4 * lane + k;
+                    const bool covers = (i >= i0) & (i < end) & (uint32_t(top - x.lo()) < uint32_t(x.hi() - x.lo()));
+                    ok |= unsigned(covers && !held_bit(s_held, x.job())) << k;
+                }
+                const unsigned long long some = __ballot(ok != 0);
+                if (some) {
+                    const int mine = __popc(ok), upto = wave_scan_add(mine);
+                    int rank = n + upto - mine;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (!(ok >> k & 1u)) continue;
+                        if (rank < kSetsK) { s_job[rank] = Rec32{r[k]}.job(); s_from[rank] = f[k]; }
+                        ++rank;
+                    }
+                    if (n == 0) {
+                        const int t = __ffsll((long long)some) - 1;
+                        hit = base + 4 * t + __ffs(__builtin_amdgcn_readlane(int(ok), t)) - 1;
+                    }
+                    n += __builtin_amdgcn_readlane(upto, kWave - 1);
+                }
+                base += kSetsChunk;
+                if (n >= kSetsK || base >= end || ++steps > kSetsMostSteps) break;
+                r0 = r1; f0 = f1;
+                ask(base + kSetsChunk, r1, f1);
+            }
+        }
+        const bool last = (i0 >= end || base >= end) && n <= kSetsK;        // nothing behind these
+        if (n == 0 && !last) {              // from there on the next time
+            if (lane == 0) { if (first) B.at = base; else A.state[u * kWave + top].x = base; }
+            n_pieces = -2;
+            break;
+        }
+        if (n_pieces == kSetsPieces) {
+            if (least == 1) { n_pieces = -1; break; }
+            // too many: once more, with fewer jobs in common
+            least /= 2;
+            rest = B.open;
+            at = first_at;
+            n_pieces = 0;
+            first = true;
+            goto again;
+        }
+        SetsList &L = A.list[u * kSetsPieces + n_pieces];
+        SetsPiece &P = B.piece[n_pieces++];
+        if (n == 0) {               // no job is left for the highest lane, and so for none below it
+            if (lane == 0) { P.top = uint16_t(u * kWave + top); P.bottom = uint16_t(u * kWave + bottom); P.from_most = 0; P.jobs = P.last = 0; }
+            break;
+        }
+        n = min(n, kSetsK);
+        asm volatile("" ::: "memory");
+        const uint32_t job = s_job[lane];
+        const int from = lane < n ? int(s_from[lane]) : 0;
+        // the lanes that share the jobs, or at least the first of them
+        unsigned long long set = rest;
+        unsigned long long beyond = __ballot(from > u * kWave + bottom);
+        const int most = -wave_min_dpp(lane < least ? -from : 0);
+        if (beyond && __ffsll((long long)beyond) - 1 < least) {
+            set = rest & (~0ull << (most & 63));
+            bottom = __ffsll((long long)set) - 1;
+            beyond = __ballot(from > u * kWave + bottom);
+        }
+        const int jobs = beyond ? __ffsll((long long)beyond) - 1 : n;
+        L.job[lane] = job;
+        L.from[lane] = uint16_t(from);
+        if (lane == 0) {
+            P.top = uint16_t(u * kWave + top);
+            P.bottom = uint16_t(u * kWave + bottom);
+            P.from_most = uint16_t(most);
+            P.jobs = uint8_t(jobs);
+            P.last = uint8_t(last && jobs == n);
+            if (first) B.at = hit; else A.state[u * kWave + top].x = hit;
+        }
+        if (first) first_at = hit;
+        at = hit;
+        rest &= ~set;
+    }
+    if (lane == 0) B.pieces = n_pieces;
+}
+
+template <int BLOCKS>
+struct SetsShared {
+    SetsJobs jobs;                                      // the jobs at hand and their claims
+    uint16_t seq[kSetsMost * kSetsRoom];                // per set its jobs' slots in there; then those it was granted
+    uint32_t head[kSetsHeads];                          // its lowest open gaps, [H][sets]
+    uint16_t place[kSetsHeads];                         // and their places
+    unsigned long long open[BLOCKS];            // open lanes of the list blocks
+    uint16_t piece[BLOCKS * kSetsPieces], ends[BLOCKS * kSetsPieces], from_most[BLOCKS * kSetsPieces];  // the pieces: number, highest lane << 8 | lowest lane
+    uint8_t piece_jobs[BLOCKS * kSetsPieces];
+    int8_t pieces[BLOCKS];
+    uint16_t lo[kSetsMost], hi[kSetsMost], source[kSetsMost], cls[kSetsMost];    // first and last place of a set, the piece whose jobs it has, its class
+    uint32_t set[kSetsMost];                            // jobs at hand : gaps at hand : no more jobs : no more gaps
+    int won[kSetsMost];
+    int first[kMaxClasses + 1], gaps_at[kMaxClasses + 1];       // first list block of a class, its first position,
+    int low[kMaxClasses];                               // and where its lowest open gap lies among its gaps
+    uint32_t found[kSetsWaves][kWave], found_from[kSetsWaves][kWave];
+    int n, over, closed, lost, end, why;
+};
+
+template <int BLOCKS>
+__device__ __forceinline__ unsigned long long sets_lanes(const SetsShared<BLOCKS> &S, int u, int from, int to)      // open lanes of list block u between two places
+{
+    unsigned long long m = u >= from >> 6 && u <= to >> 6 ? S.open[u] : 0ull;
+    if (u == from >> 6) m &= ~0ull << (from & 63);
+    if (u == to >> 6) m &= ~0ull >> (63 - (to & 63));
+    return m;
+}
+
+// The sets of class c: from the highest piece down, each takes the gaps that get the same atoms of its first jobs.
+template <int BLOCKS>
+__device__ __forceinline__ void sets_join(const SetsArgs &A, SetsShared<BLOCKS> &S, int c, int lane)
+{
+    // its pieces, the highest first
+    const int u_first = S.first[c], u_last = S.first[c + 1] - 1, base = u_first * kSetsPieces;
+    int n = 0;
+    for (int k0 = 0; k0 < (u_last - u_first + 1) * kSetsPieces; k0 += kWave) {
+        const int u = max(u_last - (k0 + lane) / kSetsPieces, u_first), i = (k0 + lane) % kSetsPieces;
+        const bool there = k0 + lane < (u_last - u_first + 1) * kSetsPieces && i < S.pieces[u];
+        const unsigned long long b = __ballot(there);
+        if (there) {
+            const int to = base + n + __popcll(b & ((1ull << lane) - 1ull));
+            const SetsPiece P = A.block[u].piece[i];
+            S.ends[to] = uint16_t((P.top & 63) << 8 | (P.bottom & 63));
+            S.from_most[to] = P.from_most;
+            S.piece[to] = uint16_t(u * kSetsPieces + i);
+        }
+        n += __popcll(b);
+    }
+    asm volatile("" ::: "memory");
+    auto top_of = [&](int k) { return S.piece[base + k] / kSetsPieces * kWave + (S.ends[base + k] >> 8); };
+    auto bottom_of = [&](int k) { return S.piece[base + k] / kSetsPieces * kWave + (S.ends[base + k] & 63); };
+    int top = n ? top_of(0) : 0;        // the highest gap not yet in a set
+    for (int k = 0; k < n;) {
+        const int piece = __builtin_amdgcn_readfirstlane(int(S.piece[base + k])), most = S.from_most[base + k];
+        top = __builtin_amdgcn_readfirstlane(top);
+        // the first one behind it that reaches below the place from which on the first jobs' atoms are the answer
+        int k1 = k + 1, next_top = 0, next_bottom = 0, its_piece = 0;
+        for (; k1 < n; k1 += kWave) {
+            const int at = min(k1 + lane, n - 1), t = top_of(at), bt = bottom_of(at), its = S.piece[base + at];
+            const unsigned long long b = __ballot(k1 + lane < n && bt < most);
+            if (!b) continue;
+            const int l = __ffsll((long long)b) - 1;
+            k1 += l;
+            next_top = __builtin_amdgcn_readlane(t, l);
+            next_bottom = __builtin_amdgcn_readlane(bt, l);
+            its_piece = __builtin_amdgcn_readlane(its, l);
+            break;
+        }
+        int lo = u_first * kWave;
+        if (S.piece_jobs[piece] == 0) {         // no job is left for these lanes
+            k1 = k + 1;
+            next_top = k1 < n ? top_of(k1) : 0;
+            if (lane == 0) {
+                S.open[piece / kSetsPieces] &= ~sets_lanes(S, piece / kSetsPieces, bottom_of(k), top);
+                S.closed = 1;
+            }
+            asm volatile("" ::: "memory");
+        } else {
+            if (k1 < n) {
+                lo = most;
+                if (next_top < most) {
+                    lo = next_top + 1;
+                } else {            // the part of it below goes on
+                    const int v = its_piece / kSetsPieces;
+                    next_top = v * kWave + 63 - __clzll((long long)sets_lanes(S, v, next_bottom, most - 1));
+                }
+            }
+            if (lane == 0) {
+                const int id = atomicAdd(&S.n, 1);
+                if (id < kSetsMost) {
+                    S.lo[id] = uint16_t(lo);
+                    S.hi[id] = uint16_t(top);
+                    S.source[id] = uint16_t(piece);
+                    S.cls[id] = uint16_t(c);
+                }
+            }
+        }
+        k = k1;
+        top = next_top;
+    }
+}
+
+// The jobs and the lowest gaps of a set.
+template <int BLOCKS>
+__device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> &S, int id, int lane, int wave, int width, int H)
+{
+    const int lo = __builtin_amdgcn_readfirstlane(int(S.lo[id])), hi = __builtin_amdgcn_readfirstlane(int(S.hi[id]));
+    const int piece = __builtin_amdgcn_readfirstlane(int(S.source[id])), c = __builtin_amdgcn_readfirstlane(int(S.cls[id]));
+    const uint32_t job = A.list[piece].job[lane];
+    const int from = A.list[piece].from[lane];
+    const int n = S.piece_jobs[piece] & 127;
+    const bool last = S.piece_jobs[piece] >> 7;
+    const int begin = S.gaps_at[c], count = S.gaps_at[c + 1] - begin;
+    const int low = S.low[c];
+    int2 ahead[kSetsGapsAhead];
+#pragma unroll
+    for (int k = 0; k < kSetsGapsAhead; ++k) ahead[k] = A.by_class[begin + min(low + k * kWave + lane, count - 1)];
+    // its lowest place, and how many are open (a few, or more than a wave)
+    int bottom = hi, n_open = 0;
+    for (int v0 = hi >> 6; v0 >= lo >> 6; v0 -= kWave) {
+        const unsigned long long m = sets_lanes(S, v0 - lane, lo, hi), some = __ballot(m != 0);
+        if (some) {
+            const int t = 63 - __clzll((long long)some);
+            bottom = (v0 - t) * kWave + __ffsll((long long)sets_readlane64(m, t)) - 1;
+            n_open += __builtin_amdgcn_readlane(wave_scan_add(__popcll(m)), kWave - 1);
+        }
+    }
+    const unsigned long long beyond = __ballot(lane < n && from > bottom);
+    int jobs = beyond ? __ffsll((long long)beyond) - 1 : n;
+    const int slot = lane < jobs ? sets_slot(S.jobs, job) : -1;
+    const unsigned long long none = __ballot(lane < jobs && slot < 0);
+    if (none) jobs = __ffsll((long long)none) - 1;
+    if (jobs == 0 && lane == 0) S.over = 1;
+    if (lane < jobs + 4) S.seq[id * kSetsRoom + lane] = uint16_t(4 * (lane < jobs ? slot : kSetsSlots));
+    if (lane < jobs + 4 - kWave) S.seq[id * kSetsRoom + kWave + lane] = uint16_t(4 * kSetsSlots);
+    // its lowest gaps: few open ones are put in order, of many the class's are looked through
+    int gaps = 0;
+    bool all_gaps;
+    if (n_open <= kWave) {
+        uint32_t *list = S.found[wave];
+        for (int v0 = lo >> 6; v0 <= hi >> 6; v0 += kWave) {
+            const unsigned long long m = sets_lanes(S, v0 + lane, lo, hi);
+            for (unsigned long long some = __ballot(m != 0); some; some &= some - 1) {
+                const int t = __ffsll((long long)some) - 1;
+                const unsigned long long mt = sets_readlane64(m, t);
+                if ((mt >> lane) & 1ull) list[gaps + __popcll(mt & ((1ull << lane) - 1ull))] = uint32_t((v0 + t) << 6 | lane);
+                gaps += __popcll(mt);
+            }
+        }
+        asm volatile("" ::: "memory");
+        const int place = int(list[min(lane, gaps - 1)]);
+        const int g = A.state[place].w >> 2;
+        int rank = 0;
+        for (int l = 0; l < gaps; ++l) rank += __builtin_amdgcn_readlane(g, l) < g;
+        if (lane < gaps && rank < H) { S.head[rank * width + id] = uint32_t(g); S.place[rank * width + id] = uint16_t(place); }
+        all_gaps = gaps <= H;
+    } else {
+        int g0 = low;
+        for (;;) {
+#pragma unroll
+            for (int k = 0; k < kSetsGapsAhead; ++k) {
+                if (g0 >= count || gaps >= H) continue;
+                const int2 x = ahead[k];
+                const bool on = g0 + lane < count && ((S.open[x.x >> 6] >> (x.x & 63)) & 1ull);
+                const bool in = on && x.x >= lo && x.x <= hi;
+                const unsigned long long b = __ballot(in);
+                const int rank = gaps + __popcll(b & ((1ull << lane) - 1ull));
+                if (in && rank < H) { S.head[rank * width + id] = uint32_t(x.y); S.place[rank * width + id] = uint16_t(x.x); }
+                gaps += __popcll(b);
+                if (g0 == low) {                        // the class's lowest open gap only moves up
+                    const unsigned long long o = __ballot(on);
+                    if (lane == 0) atomicMax(&S.low[c], o ? g0 + __ffsll((long long)o) - 1 : min(g0 + kWave, count - 1));
+                }
+                g0 += kWave;
+            }
+            if (g0 >= count || gaps >= H || (gaps >= kSetsFewGaps && g0 - low >= kSetsGapsFar)) break;
+#pragma unroll
+            for (int k = 0; k < kSetsGapsAhead; ++k) ahead[k] = A.by_class[begin + min(g0 + k * kWave + lane, count - 1)];
+        }
+        all_gaps = g0 >= count && gaps <= H;
+    }
+    if (lane == 0) S.set[id] = uint32_t(jobs) | uint32_t(min(gaps, H)) << 8 | uint32_t(last && jobs == n) << 16 | uint32_t(all_gaps) << 17;
+}
+
+// The rounds of a batch by one wave, N sets per lane.  Leaves why they stopped, at which round of the batch, and
+// what the sets were granted.
+template <int N, int BLOCKS>
+__device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n_sets, int width, int H, int before, int cap)
+{
+    constexpr uint32_t nobody = 4 * kSetsSlots;
+    auto claim_at = [&](uint32_t off) -> uint32_t & { return *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(S.jobs.claim) + off); };
+    uint2 c[N];                     // the slots of the next four jobs (byte offsets of their claims)
+    uint32_t head[N], next[N];      // the lowest open gap, and the next one
+    int p[N], len[N], heads[N], won[N];         // jobs passed, jobs and gaps at hand, gaps granted
+    int active[N], no_jobs[N], no_gaps[N];      // it has gaps and jobs; nothing behind those at hand
+    uint32_t cand[N], word[N];      // the claim of the round before
+    auto window = [&](int i) { __builtin_memcpy(&c[i], &S.seq[(lane + i * kWave) * kSetsRoom + p[i]], 8); };
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int id = lane + i * kWave;
+        const uint32_t info = id < n_sets ? S.set[id] : 0u;
+        len[i] = int(info & 255u);
+        heads[i] = int(info >> 8 & 255u);
+        no_jobs[i] = int(info >> 16 & 1u);
+        no_gaps[i] = int(info >> 17 & 1u);
+        p[i] = 0;
+        won[i] = 0;
+        active[i] = int(id < n_sets);
+        head[i] = S.head[id];
+        next[i] = S.head[width + id];
+        cand[i] = nobody;
+        word[i] = ~0u;
+        window(i);
+    }
+    int why = kSetsPause, q = 1;
+    for (;; ++q) {
+        const uint32_t now = uint32_t(q) << 20;
+        uint32_t w[N][4], outcome[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            w[i][0] = claim_at(c[i].x & 0xffffu); w[i][1] = claim_at(c[i].x >> 16);
+            w[i][2] = claim_at(c[i].y & 0xffffu); w[i][3] = claim_at(c[i].y >> 16);
+            outcome[i] = claim_at(cand[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i)     // all of them are on their way before the first is waited for
+            asm volatile("" : "+v"(w[i][0]), "+v"(w[i][1]), "+v"(w[i][2]), "+v"(w[i][3]), "+v"(outcome[i]));
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (outcome[i] == word[i]) {      // (the job it was granted goes where the set's first ones have been read)
+                S.seq[(lane + i * kWave) * kSetsRoom + won[i]] = uint16_t(cand[i]);
+                ++won[i];
+                head[i] = next[i];
+                next[i] = S.head[min(won[i] + 1, H - 1) * width + lane + i * kWave];
+                if (no_gaps[i] & int(won[i] == heads[i])) active[i] = 0;
+            }
+        }
+        if (before + q > cap) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (active[i]) S.lost = 1;
+            why = kSetsAtCap;
+            break;
+        }
+        int passed[N], cannot = 0, dry = 0, some = 0;
+        uint32_t job[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            for (;;) {          // none of the four is free, and there are more: seldom
+                const bool more = active[i] != 0 && max(max(w[i][0], w[i][1]), max(w[i][2], w[i][3])) < now && p[i] + 4 < len[i];
+                if (__builtin_expect(__ballot(more) == 0, 1)) break;
+                if (more) { p[i] += 4; window(i); }
+                w[i][0] = claim_at(c[i].x & 0xffffu); w[i][1] = claim_at(c[i].x >> 16);
+                w[i][2] = claim_at(c[i].y & 0xffffu); w[i][3] = claim_at(c[i].y >> 16);
+            }
+            // the first free one
+            job[i] = w[i][2] >= now ? c[i].y & 0xffffu : c[i].y >> 16;
+            int f = w[i][2] >= now ? 3 : w[i][3] >= now ? 4 : 0;
+            job[i] = w[i][1] >= now ? c[i].x >> 16 : job[i];
+            f = w[i][1] >= now ? 2 : f;
+            job[i] = w[i][0] >= now ? c[i].x & 0xffffu : job[i];
+            f = w[i][0] >= now ? 1 : f;
+            f = active[i] ? f : 0;
+            dry |= active[i] & int(f == 0) & no_jobs[i];
+            cannot |= active[i] & ((int(f == 0) & ~no_jobs[i]) | (int(f != 0) & int(won[i] >= heads[i])));
+            some |= f;
+            passed[i] = f;
+        }
+        if (__builtin_expect(__ballot(cannot) != 0, 0)) break;         // round q cannot be played
+        if (__builtin_expect(__ballot(dry) != 0, 0)) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (passed[i] == 0) active[i] = 0;
+            S.closed = q;
+        }
+        if (__builtin_expect(__ballot(some) == 0, 0)) { why = kSetsNoClaim; break; }       // nobody claims anything in round q
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            cand[i] = passed[i] ? job[i] : nobody;
+            word[i] = passed[i] ? now | head[i] : ~0u;
+            p[i] += passed[i];
+            // (without a claim: the word behind the last slot, which stays what it is)
+            atomicMin(&claim_at(cand[i]), word[i]);
+            window(i);
+        }
+        asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (lane + i * kWave < n_sets) S.won[lane + i * kWave] = won[i];
+    if (lane == 0) { S.end = q; S.why = why; }
+}
+
+// The classes, once per launch.
+template <int BLOCKS>
+__device__ __forceinline__ void sets_classes(const SetsArgs &A, SetsShared<BLOCKS> &S)
+{
+    const int tid = threadIdx.x, n_classes = A.plan[kPlanClasses];
+    if (tid <= kMaxClasses) {
+        S.first[tid] = A.n_lb;
+        S.gaps_at[tid] = tid < n_classes ? A.class_begin[tid] : A.n_gaps;
+    }
+    __syncthreads();
+    if (tid < A.n_lb) {
+        const int c = A.gap_cls[A.lb_begin[tid]];
+        if (tid == 0 || A.gap_cls[A.lb_begin[tid - 1]] != c) S.first[c] = tid;
+    }
+    for (int i = tid; i <= kSetsSlots; i += kSetsThreads) sets_clear(S.jobs, i);
+    if (tid < 4 * kSetsMost) S.seq[(tid >> 2) * kSetsRoom + (tid & 3)] = uint16_t(4 * kSetsSlots);      // (sets that there are not)
+    if (tid < kMaxClasses) S.low[tid] = 0;
+    __syncthreads();
+}
+
+// A batch: the pieces are joined, its rounds played, and the grants written down.  held: the bitmap that sets_form
+// reads.  Returns whether the process has ended (out says how), and how many rounds were played; -1: too much
+// work, none was.
+template <int BLOCKS>
+__device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS> &S, int done, uint32_t *held, int &played)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_classes = A.plan[kPlanClasses];
+    if (tid == 0) S.n = S.over = S.closed = S.lost = 0;
+    __syncthreads();
+    for (int u = tid; u < A.n_lb; u += kSetsThreads) {
+        const unsigned long long open = A.block[u].open;
+        const int n = open ? A.block[u].pieces : 0;
+        S.open[u] = open;
+        S.pieces[u] = int8_t(max(n, 0));
+        if (n < 0) atomicOr(&S.over, -n);
+    }
+    for (int k = tid; k < A.n_lb * kSetsPieces; k += kSetsThreads) S.piece_jobs[k] = uint8_t(A.block[k / kSetsPieces].piece[k % kSetsPieces].jobs | A.block[k / kSetsPieces].piece[k % kSetsPieces].last << 7);
+    __syncthreads();
+    played = S.over & 1 ? -1 : 0;
+    if (S.over) return false;
+    played = -1;
+    for (int c = wave; c < n_classes; c += kSetsWaves) sets_join(A, S, c, lane);
+    __syncthreads();
+    const int n_sets = S.n;
+    if (n_sets > kSetsMost) return false;
+    const int width = n_sets <= kWave ? kWave : n_sets <= 2 * kWave ? 2 * kWave : kSetsMost, H = min(kSetsMostHeads, kSetsHeads / width);
+    for (int id = wave; id < n_sets; id += kSetsWaves) sets_fill(A, S, id, lane, wave, width, H);
+    __syncthreads();
+    const bool over = S.over != 0;
+    if (!over && wave == 0) {
+        if (width == kWave) sets_play<1>(S, lane, n_sets, width, H, done, A.cap);
+        else if (width == 2 * kWave) sets_play<2>(S, lane, n_sets, width, H, done, A.cap);
+        else sets_play<4>(S, lane, n_sets, width, H, done, A.cap);
+    }
+    __syncthreads();
+    // the rounds played: not one that could not be; one without any claim if it found out that a set has no job left
+    const int why = S.why;
+    played = over ? -1 : why == kSetsNoClaim && S.closed == S.end ? S.end : S.end - 1;
+    if (!over) {
+        for (int id = wave; id < n_sets; id += kSetsWaves) {        // the grants of a set, a lane each
+            if (lane >= S.won[id]) continue;
+            const int place = S.place[lane * width + id];
+            A.state[place].y = int(S.jobs.job[S.seq[id * kSetsRoom + lane] >> 2]);
+            A.state[place].w = int(S.head[lane * width + id]) << 2 | 1;
+            atomicAnd(&S.open[place >> 6], ~(1ull << (place & 63)));
+        }
+        __syncthreads();
+    }
+    for (int k = tid; k <= kSetsSlots; k += kSetsThreads) {
+        if (k < kSetsSlots) {
+            const uint32_t j = S.jobs.job[k];
+            if (j != kSetsNoJob && int(S.jobs.claim[k] >> 20) <= played) atomicOr(&held[j >> 5], 1u << (j & 31u));
+        }
+        sets_clear(S.jobs, k);
+    }
+    for (int u = tid; u < A.n_lb; u += kSetsThreads) A.block[u].open = S.open[u];
+    if (over || why == kSetsPause) return false;
+    if (tid == 0) {
+        A.out[kSoloDone] = kSoloEnded; A.out[kSoloRounds] = done + played; A.out[kSoloStable] = why == kSetsNoClaim || S.lost == 0;
+    }
+    return true;
+}
+
+// After a batch of `played` rounds: the jobs the gaps of a set are to have in common in the next one, and whether
+// to go on.
+__device__ __forceinline__ bool sets_go_on(int played, int &least, int &strain)
+{
+    if (played < 0) return false;
+    least = min(max(2 * played, kSetsLeastFirst), kSetsLeast);
+    strain = max(strain + (played <= kSetsShort ? 1 : -1), 0);
+    return strain < kSetsPatience;
+}
+
+// Too much work: the state of list block u as a launched round leaves it, but for the outcome already known.
+__device__ __forceinline__ void sets_hand_back(const SetsArgs &A, int u, int lane)
+{
+    const int slot = u * kWave + lane;
+    const unsigned long long on = A.block[u].open;
+    const int at = A.block[u].at;
+    const int4 st = A.state[slot];
+    const bool highest = on != 0 && lane == 63 - __clzll((long long)on);
+    if ((on >> lane) & 1ull) A.state[slot].x = max(st.x, highest ? at : at - 63);
+    else if ((st.w & 3) == 0) A.state[slot].w |= 2;
+    else if ((st.w & 3) == 1) A.claim[st.y] = claim_of(1, st.w >> 2);       // any stamp of a past round says held
+}
+
+// The rounds behind those that k_grant_solo has left calm, up to round cap.  held: two copies of the bitmap, alike.
+// out: whether the process has ended, the rounds done, whether they are stable.
+__global__ __launch_bounds__(kSetsThreads) void k_sets_one(SetsArgs A)
+{
+    __shared__ SetsShared<kSetsOneBlocks> S;
+    __shared__ uint32_t s_held[kHeldMaxWords];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (A.out[kSoloDone] != kSoloCalm) return;
+    sets_classes(A, S);
+    for (int i = tid; i < A.held_words; i += kSetsThreads) s_held[i] = A.held[i];
+    for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_open(A, u, lane);
+    __syncthreads();
+    if (A.build) sets_by_class(A.n_gaps, A.plan[kPlanClasses], A.class_begin, S.first, A.place_of, A.by_class, reinterpret_cast<int(*)[kMaxClasses]>(&S.found[0][0]));
+    int done = A.out[kSoloRounds], least = kSetsLeastFirst, strain = 0, played = 0;
+    for (;;) {
+        __syncthreads();
+        for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_form(A, u, lane, least, s_held, S.found[wave], S.found_from[wave]);
+        __syncthreads();
+        const bool ended = sets_batch(A, S, done, s_held, played);
+        done += max(played, 0);
+        if (ended) return;
+        if (!sets_go_on(played, least, strain)) break;
+    }
+    if (tid == 0) {
+        A.out[kSoloDone] = kSetsLeft; A.out[kSoloRounds] = done; A.out[kSoloStable] = 0;
+    }
+    __syncthreads();
+    for (int i = tid; i < A.held_words; i += kSetsThreads) A.held[i] = A.held[A.held_words + i] = s_held[i];
+    for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_hand_back(A, u, lane);
+}
+
+// The same in several launches: the start; then searches and batches in turn, as long as out says that it is
+// running; and what is left for launched rounds.
+constexpr int kSetsFormThreads = 256;
+
+__global__ __launch_bounds__(kSetsFormThreads) void k_sets_open(SetsArgs A)
+{
+    const int lane = threadIdx.x & (kWave - 1), u = blockIdx.x * (kSetsFormThreads / kWave) + (threadIdx.x >> 6);
+    if (u < A.n_lb) sets_open(A, u, lane);
+}
+
+__global__ __launch_bounds__(kSetsThreads) void k_sets_begin(SetsArgs A)
+{
+    __shared__ SetsShared<kSetsMaxBlocks> S;
+    sets_classes(A, S);
+    if (threadIdx.x < kMaxClasses) A.low[threadIdx.x] = 0;
+    if (threadIdx.x == 0) { A.out[kSoloDone] = kSetsRunning; A.out[kSetsState] = kSetsLeastFirst << 8; }
+    if (A.build)
+        sets_by_class(A.n_gaps, A.plan[kPlanClasses], A.class_begin, S.first, A.place_of, A.by_class, reinterpret_cast<int(*)[kMaxClasses]>(&S.found[0][0]));
+}
+
+__global__ __launch_bounds__(kSetsFormThreads) void k_sets_form(SetsArgs A)
+{
+    __shared__ uint4 s_held[kHeldMaxWords / 4];
+    __shared__ uint32_t s_job[kSetsFormThreads / kWave][kWave], s_from[kSetsFormThreads / kWave][kWave];
+    if (A.out[kSoloDone] != kSetsRunning) return;
+    const uint4 *held = reinterpret_cast<const uint4 *>(A.held);
+    for (int i = threadIdx.x; i < A.held_words / 4; i += kSetsFormThreads) s_held[i] = held[i];
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int u = blockIdx.x * (kSetsFormThreads / kWave) + wave;
+    if (u < A.n_lb) sets_form(A, u, lane, A.out[kSetsState] >> 8, reinterpret_cast<const uint32_t *>(s_held), s_job[wave], s_from[wave]);
+}
+
+__global__ __launch_bounds__(kSetsThreads) void k_sets_play(SetsArgs A)
+{
+    __shared__ SetsShared<kSetsMaxBlocks> S;
+    if (A.out[kSoloDone] != kSetsRunning) return;
+    const int done = A.out[kSoloRounds];
+    sets_classes(A, S);
+    if (threadIdx.x < kMaxClasses) S.low[threadIdx.x] = A.low[threadIdx.x];
+    int played = 0, least = 0, strain = A.out[kSetsState] & 255;
+    if (sets_batch(A, S, done, A.held, played)) return;
+    const bool go_on = sets_go_on(played, least, strain);
+    if (threadIdx.x < kMaxClasses) A.low[threadIdx.x] = S.low[threadIdx.x];
+    if (threadIdx.x == 0) {
+        A.out[kSoloRounds] = done + max(played, 0);
+        A.out[kSetsState] = least << 8 | strain;
+        if (!go_on) A.out[kSoloDone] = kSetsLeft;
+    }
+}
+
+__global__ __launch_bounds__(kSetsFormThreads) void k_sets_hand_back(SetsArgs A)
+{
+    const int lane = threadIdx.x & (kWave - 1), u = blockIdx.x * (kSetsFormThreads / kWave) + (threadIdx.x >> 6);
+    if (u < A.n_lb) sets_hand_back(A, u, lane);
+    uint32_t *to = A.held + A.held_words;
+    for (int i = blockIdx.x * kSetsFormThreads + threadIdx.x; i < A.held_words; i += gridDim.x * kSetsFormThreads) to[i] = A.held[i];
+}
+
+}  // namespace sja

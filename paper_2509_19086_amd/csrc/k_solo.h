@@ -52,7 +52,9 @@ constexpr int kSoloMostSteps = 48;      // steps after which it stops in the mid
 constexpr int kSoloStart = 3;           // effort per wave of the last launched round up to which it starts;
 constexpr int kSoloStartFew = 16;       // with few list blocks, whose start and whose rounds in pieces cost little
 enum { kSoloDone = 0, kSoloRounds = 1, kSoloStable = 2 };
-enum { kSoloHandedBack = 0, kSoloEnded = 1, kSoloPutOff = 2 };      // what out[kSoloDone] says
+// Rounds are calm if few pieces were served in the last kSoloCalmRounds of them (a power of two).
+constexpr int kSoloCalmRounds = 32, kSoloCalmPieces = 128;
+enum { kSoloHandedBack = 0, kSoloEnded = 1, kSoloPutOff = 2, kSoloCalm = 3 };      // what out[kSoloDone] says
 
 __device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long v, int l)
 {
@@ -62,8 +64,9 @@ __device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long
 
 // Rounds after + 1 .. at most cap, by blockDim.x / kWave waves (n_lb <= blockDim.x).  `after` rounds have
 // been launched; cnt_lost / cnt_cand tell of those from first_check on whether one of them was already the
-// last.  out: whether the process has ended, is to be taken up again by launched rounds, or has not been taken
-// over at all (the end of round `after` is then still open); the rounds done, whether they are stable.
+// last.  out: whether the process has ended, is to be taken up again by launched rounds, has not been taken
+// over at all (the end of round `after` is then still open), or has become calm by round calm_from or later; the
+// rounds done, whether they are stable.
 //
 // A wave has its SIMD to itself (or shares it with one or two others), so a round takes as long as its
 // instructions: what a thread tests every round (eight records' held bits) is prepared when the records
@@ -75,7 +78,7 @@ template <bool SMALL>
 __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     int4 *state, const int32_t *__restrict__ list_off, const Rec32 *__restrict__ rec, unsigned long long *claim, int after,
     int first_check, int cap, int n_lb, int held_words, uint32_t *held, const int32_t *__restrict__ cnt_lost,
-    const int32_t *__restrict__ cnt_cand, int32_t *effort, int32_t *out)
+    const int32_t *__restrict__ cnt_cand, int calm_from, int32_t *effort, int32_t *out)
 {
     __shared__ uint32_t s_held[2][kHeldMaxWords + 4];           // the word behind the last job's is all ones: nobody's job
     __shared__ SoloTables s_tabs;       // the claims of this round and of the one before or after it
@@ -85,6 +88,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     // by round stamp: somebody claims, a wave gives up, (round << 8 | most effort of a wave), open lanes found nothing more
     __shared__ int4 s_ctl[2];
     __shared__ int s_flag;
+    __shared__ int s_served[2];         // pieces served, by turns of kSoloCalmRounds rounds
     __shared__ int s_order[SMALL ? kSoloSmallBlocks * kWave : 1];      // per list block its open lanes, lowest gap first: gap << 6 | lane
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int threads = blockDim.x, waves = threads / kWave;
@@ -105,7 +109,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     }
     for (int i = tid; i < held_words; i += threads) s_held[0][i] = s_held[1][i] = held[size_t((after + 1) & 1) * held_words + i];
     for (int i = tid; i < kSoloTable; i += threads) s_tabs.word[0][i] = s_tabs.word[1][i] = 0;
-    if (tid < 2) { s_ctl[tid] = make_int4(0, 0, 0, 0); s_held[tid][held_words] = ~0u; }
+    if (tid < 2) { s_ctl[tid] = make_int4(0, 0, 0, 0); s_held[tid][held_words] = ~0u; s_served[tid] = 0; }
     if (tid == 0) s_flag = 0;
     __syncthreads();
 
@@ -240,6 +244,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     int strain = 0;             // effort beyond what is easy, summed up
     int done = after;           // rounds finished
     int ended = 0, stable = 0;
+    bool calm = false;
     uint32_t marked = nobody, marked_piece = nobody;    // the jobs this lane marked a round ago
     for (int round = after + 1;; ++round) {
         const int half = round & 1;
@@ -380,6 +385,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
                 set_mark(marked_piece);
             }
         }
+        if (n_pieces && lane == 0) atomicAdd(&s_served[(round / kSoloCalmRounds) & 1], n_pieces);
         if (n_pieces + step > kSoloEasy && lane == 0) {
             if (over) s_ctl[half].y = round;
             atomicMax(&s_ctl[half].z, (round << 8) | (n_pieces + step));
@@ -427,7 +433,12 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         }
         done = round;
         strain = max(strain + max((ctl.z >> 8) == round ? (ctl.z & 255) - kSoloEasy : 0, 0) - 1, 0);
-        if (round == cap || strain > kSoloPatience) {
+        // (the other turn's count is complete, and cleared half a turn later)
+        const int turn = round % kSoloCalmRounds;
+        int *const served = &s_served[((round / kSoloCalmRounds) & 1) ^ 1];
+        if (turn == kSoloCalmRounds / 2 && tid == 0) *served = 0;
+        if (turn == 0 && round >= calm_from) calm = *served <= kSoloCalmPieces;
+        if (round == cap || strain > kSoloPatience || calm) {
             // the block stops here.  A lane still open has lost this round; if there is none, the process has ended with it
             if (open) s_flag = 1;
             __syncthreads();
@@ -439,7 +450,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     }
     flush();
     if (tid == 0) {
-        out[kSoloDone] = ended ? kSoloEnded : kSoloHandedBack; out[kSoloRounds] = done; out[kSoloStable] = stable;
+        out[kSoloDone] = ended ? kSoloEnded : calm ? kSoloCalm : kSoloHandedBack; out[kSoloRounds] = done; out[kSoloStable] = stable;
         effort[0] = effort[1] = 0;
     }
     if (ended) return;

@@ -220,6 +220,7 @@ struct Rec64 {
     }
 };
 struct NoRec {};
+struct Rec32Placed {};          // Rec32, and the entries' places beside them
 
 // What the last pass over list entries writes instead of the keys themselves: the record of an entry
 // job : hi (7 bits) : lo (6 bits), whatever bits (the list block) lie above the job's 24.
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
                                                       const uint32_t *__restrict__ pay_src,
                                                       uint32_t *__restrict__ pay_dst, const int32_t *n_ptr,
                                                       int shift, unsigned digit_mask, const int32_t *__restrict__ hist,
-                                                      int n_tiles, void *rec)
+                                                      int n_tiles, void *rec, uint16_t *rec_from)
 {
     __shared__ unsigned long long s_key[kKeyTile];
     __shared__ uint32_t s_pay[PAY ? kKeyTile : 1];
@@ -327,7 +328,10 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
         const unsigned long long v = s_key[k];
         const unsigned d = unsigned(v >> shift) & digit_mask;
         const int64_t o = int64_t(s_goff[d]) + (k - s_start[d]);
-        if constexpr (!std::is_same<REC, NoRec>::value) {
+        if constexpr (std::is_same<REC, Rec32Placed>::value) {
+            static_cast<Rec32 *>(rec)[o] = Rec32::make(uint32_t(v >> 13) & 0x1ffffu, unsigned(v) & 63u, unsigned(v >> 6) & 127u);
+            rec_from[o] = uint16_t(v >> 30);
+        } else if constexpr (!std::is_same<REC, NoRec>::value) {
             static_cast<REC *>(rec)[o] = key_record<REC>(v);
         } else {
             dst[o] = v;

@@ -1,7 +1,7 @@
 // C ABI of the gap-job fit / slot-grant engine: argument validation, workspace
 // bookkeeping and kernel launches.  See include/sja.h for the contract.
 #include "sja_kernels.h"
-#include "k_solo.h"
+#include "k_sets.h"
 
 #include <mutex>
 #include <new>
@@ -196,7 +196,7 @@ int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t
                                       auto kern = few ? k_keys_scatter<true, true, NoRec> : k_keys_scatter<false, true, NoRec>;
                                       hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, dst,
                                                          pay[from ? 1 : 0], pay[from ? 0 : 1], n_dev, shift, mask, hist, n_tiles,
-                                                         static_cast<void *>(nullptr));
+                                                         static_cast<void *>(nullptr), static_cast<uint16_t *>(nullptr));
                                   });
         if (rc != SJA_OK) return rc;
     }
@@ -206,19 +206,20 @@ int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t
 // The list entries by list block (they come in rank order), the last pass writes their records.
 template <typename REC>
 int radix_sort_entries(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host, int block_bits,
-                       unsigned long long *const buf[2], void *rec)
+                       unsigned long long *const buf[2], void *rec, uint16_t *rec_from = nullptr)
 {
     bool flip = false;
     const int passes = (block_bits + 7) / 8, width = (block_bits + passes - 1) / passes;
+    constexpr int first_bit = std::is_same<REC, Rec32Placed>::value ? kEntryPlacedBlockShift : kEntryBlockShift;
     for (int p = 0; p < passes; ++p) {
-        const int rc = radix_pass(ctx, st, L, n_dev, n_host, kEntryBlockShift + p * width, width, flip, buf,
+        const int rc = radix_pass(ctx, st, L, n_dev, n_host, first_bit + p * width, width, flip, buf,
                                   [&](bool few, dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
                                       const int32_t *hist, int n_tiles) {
                                       auto kern = p == passes - 1 ? (few ? k_keys_scatter<true, false, REC> : k_keys_scatter<false, false, REC>)
                                                                   : (few ? k_keys_scatter<true, false, NoRec> : k_keys_scatter<false, false, NoRec>);
                                       hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, dst,
                                                          static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr),
-                                                         n_dev, shift, mask, hist, n_tiles, rec);
+                                                         n_dev, shift, mask, hist, n_tiles, rec, rec_from);
                                   });
         if (rc != SJA_OK) return rc;
     }
@@ -366,12 +367,12 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         per_chunk /= 2;
     const int64_t n_chunks = chunks_of(per_chunk), want = (n_chunks + waves_per_block - 1) / waves_per_block;
     const unsigned entry_grid = unsigned(want < most ? want : most);
-    auto launch_entries = [&](auto emit) {
+    auto launch_entries = [&](auto emit, int placed) {
         auto kern = small ? k_list_entries<decltype(emit)::value, kEntryWinSmall>
                           : in_lds ? k_list_entries<decltype(emit)::value, kEntryWinBig> : k_list_entries<decltype(emit)::value, 0>;
         hipLaunchKernelGGL(kern, dim3(entry_grid), dim3(kEntryThreads), 0, st, int(n_atoms), per_chunk, n_subs, G, pos_entries,
                            plan, class_begin, lb_begin, pos_block, pos_tab, gap_w, ws_ptr<int32_t>(ctx, L.gap_c), perm[flip ? 1 : 0], info, chunk_at,
-                           list_off, reinterpret_cast<unsigned long long *>(counters), ekey[0]);
+                           list_off, reinterpret_cast<unsigned long long *>(counters), ekey[0], placed);
         return hipGetLastError();
     };
     long long n_entries = 0;
@@ -379,7 +380,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         if (n_atoms > 0) {
             const int rc = rank_atoms(both);
             if (rc != SJA_OK) return rc;
-            SJA_HIP(launch_entries(std::false_type{}), "k_list_entries launch");
+            SJA_HIP(launch_entries(std::false_type{}, 0), "k_list_entries launch");
             SJA_HIP(enqueue_scan(st, chunk_at, n_chunks, tmp, nullptr), "entry scan launch");
         }
         int32_t h[kCountTies + 1] = {0};
@@ -395,12 +396,32 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     }
     if (n_entries > L.entry_cap || n_entries >= (1ll << 31)) return SJA_OK;
     SJA_HIP(enqueue_scan(st, list_off, int64_t(lb_bound) + 2, tmp, nullptr), "list offset scan launch");
-    void *rec = ws_ptr<void>(ctx, L.g_rec);
+    const int held_words = held_bitmap_words(J);
+    const bool use_held = held_words <= kHeldMaxWords;
     const bool wide_records = int64_t(J) > (int64_t(1) << kRec32JobBits);
+    // the block that runs rounds by itself: it needs the held bitmap, a thread per list block, and keys
+    // that never fall along a job's atoms (a minimum gain above the distance of two capacities of the
+    // hysteresis set can let a longer fit end in a shorter cut); and more than a few rounds to go, which cost no
+    // more launched than the block needs to start and report (20 us of a Medium batch, 200 at 630 list blocks)
+    bool rising = true;
+    for (int i = 1; i < ctx->hyst_used_n_caps; ++i)
+        rising = rising && int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] >= ctx->hyst_used_min_gain;
+    const bool solo_fits = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks;
+    const bool long_lists = n_entries >= int64_t(kFirstLong) * n_subs;
+    const int solo_few = kSoloFewRounds + n_subs / kSoloBlocksPerRound;
+    const int solo_first = n_subs <= kSoloFewBlocks ? kSoloFirstFew : kSoloFirstMany;
+    const bool solo = solo_fits && cap >= solo_first + solo_few;
+    const int solo_waves = (n_subs + kWave - 1) / kWave > kSoloMinWaves ? (n_subs + kWave - 1) / kWave : kSoloMinWaves;
+    // and the calm rounds after it, in batches: with a place per record (Medium tick 1775 -> 1290 us)
+    const bool sets = solo && n_subs <= kSetsMaxBlocks && J <= kPlacedJobs;
+    // (records of four bytes leave half of their space to the places; entry_cap is at least 192)
+    void *rec = ws_ptr<void>(ctx, L.g_rec);
+    uint16_t *rec_from = ws_ptr<uint16_t>(ctx, L.g_rec + align_up(size_t(L.entry_cap) * sizeof(Rec32)));
     if (n_entries > 0) {
-        SJA_HIP(launch_entries(std::true_type{}), "k_list_entries launch");
+        SJA_HIP(launch_entries(std::true_type{}, sets), "k_list_entries launch");
         const int block_bits = bits_for(n_subs > 1 ? n_subs : 2);
         const int rc = wide_records ? radix_sort_entries<Rec64>(ctx, st, L, counters, n_entries, block_bits, ekey, rec)
+                       : sets       ? radix_sort_entries<Rec32Placed>(ctx, st, L, counters, n_entries, block_bits, ekey, rec, rec_from)
                                     : radix_sort_entries<Rec32>(ctx, st, L, counters, n_entries, block_bits, ekey, rec);
         if (rc != SJA_OK) return rc;
     }
@@ -414,22 +435,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
 
     // one launch per round, in batches between looks at the flags
     // the first kHeldRounds rounds keep the held jobs as a bitmap too (two alternating copies), if it fits LDS
-    const int held_words = held_bitmap_words(J);
-    const bool use_held = held_words <= kHeldMaxWords;
     uint32_t *held = ws_ptr<uint32_t>(ctx, L.g_held);
-    // the block that runs rounds by itself: it needs the held bitmap, a thread per list block, and keys
-    // that never fall along a job's atoms (a minimum gain above the distance of two capacities of the
-    // hysteresis set can let a longer fit end in a shorter cut); and more than a few rounds to go, which cost no
-    // more launched than the block needs to start and report (20 us of a Medium batch, 200 at 630 list blocks)
-    bool rising = true;
-    for (int i = 1; i < ctx->hyst_used_n_caps; ++i)
-        rising = rising && int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] >= ctx->hyst_used_min_gain;
-    const bool solo_fits = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks;
-    const int solo_few = kSoloFewRounds + n_subs / kSoloBlocksPerRound;
-    const int solo_first = n_subs <= kSoloFewBlocks ? kSoloFirstFew : kSoloFirstMany;
-    const bool solo = solo_fits && cap >= solo_first + solo_few;
-    const int solo_waves = (n_subs + kWave - 1) / kWave > kSoloMinWaves ? (n_subs + kWave - 1) / kWave : kSoloMinWaves;
-    const bool long_lists = n_entries >= int64_t(kFirstLong) * n_subs;
     auto launch_round = [&](int64_t k, int propose) {
         const bool with_bitmap = use_held && (solo || k <= kHeldRounds);
         if (k == 1 && long_lists && propose) {
@@ -458,7 +464,8 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     int64_t launched = 0;        // kernels 1..launched have been enqueued
     int64_t next_check = 1;      // first round whose end is not yet decided
     int64_t open_left = cap;     // rounds that can still follow, as far as is known
-    bool finished = false;
+    bool finished = false, sets_built = false;
+    int64_t calm_wait = kSoloCalmRounds;
     constexpr int64_t kLaunchedRounds = 64;
     int64_t batch = solo ? solo_first : kLaunchedRounds;   // rounds enqueued between looks at the flags; grows, a finished batch costs little
     const int64_t most_rounds = solo ? 256 : 1024;  // (a look at whether the block can go on costs three or four rounds)
@@ -467,18 +474,81 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         if (!take_over && batch < kLaunchedRounds) batch = kLaunchedRounds;
         const int64_t rounds = batch < open_left ? batch : open_left;
         const int64_t upto = (launched + rounds < cap) ? launched + rounds : cap;
-        if (batch < most_rounds) batch *= 2;
+        if (batch < most_rounds) batch = batch ? 2 * batch : solo_first;
         for (int64_t k = launched + 1; k <= upto; ++k) SJA_HIP(launch_round(k, 1), "k_grant_round launch");
         if (take_over) {
+            int32_t h_out[4] = {0, 0, 0, 0};
+            auto look = [&]() -> int {
+                SJA_HIP(hipMemcpyAsync(h_out, counters + 8, sizeof(h_out), hipMemcpyDeviceToHost, st), "rounds readback");
+                SJA_HIP(hipStreamSynchronize(st), "round synchronise");
+                return SJA_OK;
+            };
             auto solo_kern = n_subs <= kSoloSmallBlocks ? k_grant_solo<true> : k_grant_solo<false>;
             hipLaunchKernelGGL(solo_kern, dim3(1), dim3(solo_waves * kWave), 0, st, state, list_off, static_cast<const Rec32 *>(rec),
                                claim, int(upto), int(next_check), int(cap), n_subs, held_words, held, cnt_lost, cnt_cand,
-                               counters + 14, counters + 8);
+                               sets && upto + calm_wait < INT32_MAX ? int(upto + calm_wait) : INT32_MAX, counters + 14, counters + 8);
             SJA_HIP(hipGetLastError(), "k_grant_solo launch");
-            int32_t h_out[3] = {0, 0, 0};
-            SJA_HIP(hipMemcpyAsync(h_out, counters + 8, sizeof(h_out), hipMemcpyDeviceToHost, st), "rounds readback");
-            SJA_HIP(hipStreamSynchronize(st), "round synchronise");
+            int rc = look();
+            if (rc != SJA_OK) return rc;
+            if (h_out[kSoloDone] == kSoloCalm) {
+                SetsArgs args{};
+                args.state = state;
+                args.list_off = list_off;
+                args.rec = static_cast<const Rec32 *>(rec);
+                args.rec_from = rec_from;
+                args.claim = claim;
+                args.held = held;
+                args.plan = plan;
+                args.class_begin = class_begin;
+                args.gap_cls = ws_ptr<int32_t>(ctx, L.gap_cls);
+                args.lb_begin = lb_begin;
+                args.lb_end = lb_end;
+                args.gap_order = gap_order;
+                args.place_of = pos_tab;           // the lists are built: the tables of positions are done with
+                args.by_class = ws_ptr<int2>(ctx, L.gap_tile_key);
+                // (the states' space behind those of the list blocks that there are)
+                args.list = reinterpret_cast<SetsList *>(state + size_t(n_subs) * kWave);
+                args.block = reinterpret_cast<SetsBlock *>(args.list + size_t(n_subs) * kSetsPieces);
+                args.low = reinterpret_cast<int32_t *>(args.block + n_subs);
+                static_assert((kListSplits * kMaxClasses + kMaxClasses - kSetsMaxBlocks) * kWave * sizeof(int4) >
+                              size_t(kSetsMaxBlocks) * kSetsBlockBytes + kMaxClasses * 4, "room for them");
+                args.out = counters + 8;
+                args.cap = int(cap);
+                args.n_gaps = G;
+                args.n_lb = n_subs;
+                args.held_words = held_words;
+                args.build = !sets_built;
+                if (n_subs <= kSetsOneBlocks) {
+                    hipLaunchKernelGGL(k_sets_one, dim3(1), dim3(kSetsThreads), 0, st, args);
+                    SJA_HIP(hipGetLastError(), "k_sets_one launch");
+                    rc = look();
+                } else {
+                    const dim3 blocks((n_subs + kSetsFormThreads / kWave - 1) / (kSetsFormThreads / kWave)), threads(kSetsFormThreads);
+                    hipLaunchKernelGGL(k_sets_open, blocks, threads, 0, st, args);
+                    hipLaunchKernelGGL(k_sets_begin, dim3(1), dim3(kSetsThreads), 0, st, args);
+                    // (a launch too many does nothing and takes 3 us)
+                    for (int pairs = 4; rc == SJA_OK; pairs = pairs < 32 ? 2 * pairs : 32) {
+                        for (int k = 0; k < pairs; ++k) {
+                            hipLaunchKernelGGL(k_sets_form, blocks, threads, 0, st, args);
+                            hipLaunchKernelGGL(k_sets_play, dim3(1), dim3(kSetsThreads), 0, st, args);
+                        }
+                        SJA_HIP(hipGetLastError(), "k_sets_play launch");
+                        rc = look();
+                        if (h_out[kSoloDone] != kSetsRunning) break;
+                    }
+                    if (rc == SJA_OK && h_out[kSoloDone] == kSetsLeft) {
+                        hipLaunchKernelGGL(k_sets_hand_back, blocks, threads, 0, st, args);
+                        SJA_HIP(hipGetLastError(), "k_sets_hand_back launch");
+                    }
+                }
+                if (rc != SJA_OK) return rc;
+            }
             launched = h_out[kSoloRounds];
+            if (h_out[kSoloDone] == kSetsLeft) {        // on with k_grant_solo, the longer the shorter it was calm
+                sets_built = true;
+                batch = 0;
+                calm_wait = launched - upto < 4 * calm_wait ? 2 * calm_wait : kSoloCalmRounds;
+            }
             next_check = h_out[kSoloDone] == kSoloPutOff ? launched : launched + 1;
             if (h_out[kSoloDone] == kSoloEnded) {
                 result[0] = h_out[kSoloRounds];
