@@ -837,6 +837,133 @@ __global__ __launch_bounds__(kRoundBlock) void k_grant_round(
     }
 }
 
+// One round per launch while rounds are much work, with the held-job bitmap: a thread block per list block, a
+// wave per gap.  In the first rounds of a batch the gaps of a list block stand thousands of records apart and
+// each of them has a few dozen to pass: a wave that walks for all of them (k_grant_round) sweeps everything
+// between in window after window, 10 to 40 us a round.  Here every gap still looking is a wave's, which reads 256
+// records a step from the gap's own place on (its waves take up to four gaps each, and ask for the first step
+// of all four before they look at one).  What the gaps found is merged by the first wave, as there.
+// Waves per list block: sixteen while two such thread blocks per compute unit hold all list blocks, else eight.
+constexpr int kWideWaves = 16, kWideFewWaves = 8, kWideManyBlocks = 512;
+constexpr int kWideChunk = 4 * kWave;    // records a wave reads at a time, four a lane
+// Large (8192 gaps x 32768 jobs) 36 -> 6.2 us a round, the first rounds of Medium 12 -> 7; where the gaps of a list
+// block stand together k_grant_round's one wave is quicker (Stress, 566 list blocks, from some hundred rounds on:
+// 5.5 against 8.7).
+constexpr int kWideBlocks = 1024;        // list blocks: beyond that the waves come in several turns
+constexpr int kWideRounds = 256;         // the rounds it is used for (all of them at Stress: 3 ms slower; none: 1 ms)
+
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void k_grant_wide(
+    int4 *state, const int32_t *__restrict__ list_off, const Rec32 *__restrict__ rec, unsigned long long *claim, int round, int held_words,
+    uint32_t *held, const int32_t *__restrict__ lb_begin, const int32_t *__restrict__ lb_end, const int32_t *__restrict__ gap_order,
+    int32_t *cnt_lost, int32_t *cnt_cand, int32_t *effort)
+{
+    __shared__ uint4 s_held4[kHeldMaxWords / 4];
+    __shared__ int s_found[kWave], s_job[kWave];
+    constexpr int kTurns = kWave / WAVES;
+    const uint32_t *s_held = reinterpret_cast<const uint32_t *>(s_held4);
+    const int u = blockIdx.x, lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int4 st = state[u * kWave + lane];
+    const int begin = list_off[u], end = list_off[u + 1], last4 = (end - 1) >> 2;
+    const uint4 *now = reinterpret_cast<const uint4 *>(held + size_t(round & 1) * held_words);
+    uint32_t *held_next = held + size_t((round + 1) & 1) * held_words;
+    for (int i = threadIdx.x; i < held_words / 4; i += WAVES * kWave) s_held4[i] = now[i];
+    if (round == 1) {
+        const int b0 = lb_begin[u];
+        st = make_int4(begin, -1, 0, lane < lb_end[u] - b0 ? (gap_order[b0 + lane] << 2) : 2);
+    }
+    const int g = st.w >> 2, flag = st.w & 3;
+    const bool waiting = flag == 0 && st.y >= 0;
+    const bool won = waiting && claim[max(st.y, 0)] == claim_of(round - 1, g), lost = waiting && !won;
+    const bool open = flag == 0 && !won, looking = open && st.x < end;
+    const unsigned long long look = __ballot(looking);
+    const int rank = __popcll(look & ((1ull << lane) - 1ull));
+    int at[kTurns], of[kTurns];
+    uint4 ahead[kTurns];
+#pragma unroll
+    for (int t = 0; t < kTurns; ++t) {
+        const unsigned long long mine = __ballot(looking && rank == t * WAVES + wave);
+        of[t] = mine ? __ffsll((long long)mine) - 1 : -1;
+        at[t] = __builtin_amdgcn_readlane(st.x, max(of[t], 0));
+        if (mine) ahead[t] = reinterpret_cast<const uint4 *>(rec)[min((at[t] >> 2) + lane, last4)];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kTurns; ++t) {
+        const int l = of[t];
+        if (l < 0) continue;
+        uint4 r4 = ahead[t];
+        int found = -1, job = 0;
+        for (int base = at[t] & ~3;;) {
+            const uint32_t r[4] = {r4.x, r4.y, r4.z, r4.w};
+            unsigned ok = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const Rec32 x{r[k]};
+                const int i = base + 4 * lane + k;
+                const bool covers = (i >= at[t]) & (i < end) & (uint32_t(l - x.lo()) < uint32_t(x.hi() - x.lo()));
+                ok |= unsigned(covers && !held_bit(s_held, x.job())) << k;
+            }
+            const unsigned long long some = __ballot(ok != 0);
+            if (some) {
+                const int s = __ffsll((long long)some) - 1, k = __ffs(__builtin_amdgcn_readlane(int(ok), s)) - 1;
+                const uint32_t v = k & 2 ? (k & 1 ? r4.w : r4.z) : (k & 1 ? r4.y : r4.x);
+                found = base + 4 * s + k;
+                job = int(Rec32{v}.of_lane(s).job());
+                break;
+            }
+            base += kWideChunk;
+            if (base >= end) break;
+            r4 = reinterpret_cast<const uint4 *>(rec)[min((base >> 2) + lane, last4)];
+        }
+        if (lane == 0) { s_found[l] = found; s_job[l] = job; }
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    const bool cand = looking && s_found[lane] >= 0;
+    const int job = cand ? s_job[lane] : -1;
+    if (won) {
+        atomicOr(&held_next[uint32_t(st.y) >> 5], 1u << (uint32_t(st.y) & 31u));
+        state[u * kWave + lane].w = st.w | 1;
+    } else if (cand) {
+        state[u * kWave + lane] = make_int4(s_found[lane] + 1, job, 0, g << 2);
+    } else if (open || round == 1) {
+        state[u * kWave + lane] = make_int4(end, -1, 0, (g << 2) | 2);
+    }
+    if (__ballot(lost) && lane == 0) cnt_lost[round - 1] = 1;
+    if (__ballot(cand) && lane == 0) cnt_cand[round] = 1;
+    // the claims: the gaps that name one job agree on the lowest of them; one that the job's word already beats is not made
+    const unsigned long long word_was = cand ? claim[job] : ~0ull;
+    auto send = [&](int low) {
+        const unsigned long long word = claim_of(round, low);
+        if (word_was >= word) return;
+        atomicMax(&claim[job], word);
+        atomicOr(&held_next[uint32_t(job) >> 5], 1u << (uint32_t(job) & 31u));
+    };
+    int pieces = -1;
+    unsigned long long todo = __ballot(cand);
+    for (int turn = 0; todo; ++turn) {
+        ++pieces;
+        if (turn == kClaimTurns) {
+            pieces += __popcll(todo) - 1;
+            if ((todo >> lane) & 1ull) send(g);
+            break;
+        }
+        const int leader = __ffsll((long long)todo) - 1;
+        const bool same = cand && job == __builtin_amdgcn_readlane(job, leader);
+        const int low = wave_min_dpp(same ? g : 0x7fffffff);
+        if (lane == leader) send(low);
+        todo &= ~__ballot(same);
+    }
+    const int nearest = wave_min_dpp(looking ? st.x : INT32_MAX), furthest = -wave_min_dpp(cand ? -s_found[lane] : 0);
+    if (effort && lane == 0) {
+        // (a wave of k_grant_round would have swept all records between the first and the last of them)
+        const int mine = max(pieces, 0) + kEffortWindow * max((furthest - nearest) / (kSweepHeld * kWave), 0);
+        if (mine > 0) atomicAdd(&effort[round & 1], mine);
+        if (u == 0) effort[(round + 1) & 1] = 0;
+    }
+}
+
 // Round 1 where the lists are long.  No job is held yet, so a lane's candidate is the first record that covers
 // it, but the lowest lanes' lie tens of thousands of records down (a Large list block: 25 thousand records,
 // 200 us for one wave in k_grant_round).  A thread block per list block: its waves take stretches of

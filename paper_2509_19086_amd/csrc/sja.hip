@@ -436,6 +436,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     // one launch per round, in batches between looks at the flags
     // the first kHeldRounds rounds keep the held jobs as a bitmap too (two alternating copies), if it fits LDS
     uint32_t *held = ws_ptr<uint32_t>(ctx, L.g_held);
+    const bool wide = !wide_records && n_subs <= kWideBlocks;
     auto launch_round = [&](int64_t k, int propose) {
         const bool with_bitmap = use_held && (solo || k <= kHeldRounds);
         if (k == 1 && long_lists && propose) {
@@ -447,6 +448,14 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
                 first(k_grant_first<Rec64>, static_cast<const Rec64 *>(rec));
             else
                 first(k_grant_first<Rec32>, static_cast<const Rec32 *>(rec));
+            return hipGetLastError();
+        }
+        if (wide && k <= kWideRounds && with_bitmap && propose) {
+            const bool few = n_subs > kWideManyBlocks;
+            hipLaunchKernelGGL(few ? k_grant_wide<kWideFewWaves> : k_grant_wide<kWideWaves>, dim3(n_subs),
+                               dim3((few ? kWideFewWaves : kWideWaves) * kWave), 0, st, state, list_off, static_cast<const Rec32 *>(rec), claim,
+                               int(k), held_words, held, lb_begin, lb_end, gap_order, cnt_lost, cnt_cand,
+                               solo ? counters + 14 : static_cast<int32_t *>(nullptr));
             return hipGetLastError();
         }
         auto go = [&](auto kern, auto *records) {
