@@ -1,0 +1,460 @@
+// Small batches, pair by pair.
+//
+// A tick of a few hundred gaps and jobs has next to no work in it: what it
+// costs are the launches of the ordered forms (nine for a fit, three for a
+// select, some thirty for the lists and the rounds of a resolve) and three looks
+// of the host at what came out.  Up to kPairsMost pairs nothing is ordered ahead:
+//   * k_fit_pairs, k_best_pairs: a thread per pair finds its atom by one search
+//     on both conditions;
+//   * k_select_pairs: a thread block per gap reads the gap's row of replies;
+//   * k_order_pairs, k_rounds_pairs: a thread block per gap puts the jobs that
+//     fit in the order of their keys, and one block plays all rounds, a thread per gap.
+// A whole tick is five launches and one look.  Gaps x jobs, 256 segments each, us a tick
+// (fairness), ordered forms and so: 8 x 16 300 / 57, 256 x 1024 547 / 117, 1024 x 512 578 / 182,
+// 256 x 4096 537 / 179, 1024 x 1024 with 784 rounds 1306 / 707, 1024 x 2048 with 221 rounds 796 / 415.
+#pragma once
+
+#include "k_fused.h"
+
+namespace sja {
+
+constexpr int kPairsGaps = 1024;            // a thread per gap in k_rounds_pairs
+constexpr int kPairsJobs = 4096;            // a gap's keys are put in order in LDS
+// Pairs up to which all of it is faster.  fit -> select by itself decides: 51 us at 1024 x 2048 against 54 in the
+// ordered form, 77 against 54 at 1024 x 4096 (a fit takes 20 against 67 and 38 against 69, a tick as above and 607
+// against 767).
+constexpr int64_t kPairsMost = 1 << 21;
+constexpr int kPairsQ = 4;                  // pairs a thread searches side by side: their loads overlap
+constexpr int kPairsThreads = 256;           // of a block of k_fit_pairs;
+constexpr int kPairsMostThreads = 1024;     // the others have as many as they have work for
+constexpr int kPairsSlots = 4;              // list entries are read four at a time (16 bits each)
+
+// Of pair q the atoms that fit, a prefix: durations and peaks ascend.  The first atom of pair q is dp[q], there are
+// n[q] of them.
+template <int Q>
+__device__ __forceinline__ void search_pairs(const int2 *const (&dp)[Q], const int (&n)[Q], const int (&w)[Q], const int (&c)[Q], int (&lo)[Q])
+{
+    int hi[Q], most = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) { lo[q] = 0; hi[q] = n[q]; most = max(most, n[q]); }
+    for (; most > 0; most >>= 1) {
+        int2 v[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lo[q] < hi[q]) v[q] = dp[q][(lo[q] + hi[q]) >> 1];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lo[q] < hi[q]) {
+                const int mid = (lo[q] + hi[q]) >> 1;
+                if (v[q].x <= w[q] && v[q].y <= c[q]) lo[q] = mid + 1; else hi[q] = mid;
+            }
+    }
+}
+
+// The gaps as they came, for the calls that follow.
+struct PairGaps {
+    int32_t *w, *c, *order;
+};
+__device__ __forceinline__ void keep_gap(const PairGaps &keep, int g, int w, int c)
+{
+    keep.w[g] = w;
+    keep.c[g] = c;
+    keep.order[g] = g;
+}
+
+// A block per 256 jobs and kPairsQ gaps.
+__global__ __launch_bounds__(kPairsThreads) void k_fit_pairs(int n_gaps, int n_jobs, const int32_t *__restrict__ W, const int32_t *__restrict__ C,
+                                                             const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
+                                                             const int2 *__restrict__ atom_db, const int32_t *__restrict__ n_atoms,
+                                                             PairGaps keep, int32_t *__restrict__ cut, uint32_t *__restrict__ bits)
+{
+    constexpr int Q = kPairsQ;
+    const int j = blockIdx.x * kPairsThreads + threadIdx.x, g0 = blockIdx.y * Q, words = (n_jobs + 31) / 32;
+    const int64_t base = j < n_jobs ? seg_off[j] : 0;
+    const int atoms = j < n_jobs ? n_atoms[j] : 0;
+    const int2 *dp[Q];
+    int n[Q], w[Q], c[Q], lo[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int g = min(g0 + q, n_gaps - 1);
+        dp[q] = atom_dp + base;
+        n[q] = g0 + q < n_gaps ? atoms : 0;
+        w[q] = W[g];
+        c[q] = C[g];
+    }
+    if (blockIdx.x == 0 && threadIdx.x < Q && g0 + int(threadIdx.x) < n_gaps)
+        keep_gap(keep, g0 + threadIdx.x, W[g0 + threadIdx.x], C[g0 + threadIdx.x]);
+    search_pairs<Q>(dp, n, w, c, lo);
+    int b[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) b[q] = lo[q] > 0 ? atom_db[base + lo[q] - 1].y : -1;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        if (g0 + q >= n_gaps) break;
+        if (j < n_jobs) cut[int64_t(g0 + q) * n_jobs + j] = b[q];
+        if (!bits) continue;
+        const unsigned long long on = __ballot(b[q] >= 0);
+        const int lane = threadIdx.x & (kWave - 1), word = (j - lane) / 32 + (lane >> 5);
+        if ((lane & 31) == 0 && word < words) bits[int64_t(g0 + q) * words + word] = lane ? uint32_t(on >> 32) : uint32_t(on);
+    }
+}
+
+// The best of a block's keys (hi 0: none), in every thread of its first wave.
+template <bool MIXED>
+__device__ __forceinline__ void best_of_block(unsigned long long &bh, unsigned long long &bl, int &bj, int &ba)
+{
+    constexpr int kMostWaves = kPairsMostThreads / kWave;
+    __shared__ unsigned long long s_hi[kMostWaves], s_lo[kMostWaves];
+    __shared__ int s_job[kMostWaves], s_atoms[kMostWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    auto wave_best = [&]() {
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const unsigned long long oh = (unsigned long long)__shfl_xor((long long)bh, d, kWave);
+            const unsigned long long ol = MIXED ? (unsigned long long)__shfl_xor((long long)bl, d, kWave) : 0ull;
+            const int oj = __shfl_xor(bj, d, kWave), oa = __shfl_xor(ba, d, kWave);
+            if (fused_better(oh, ol, oj, bh, bl, bj)) { bh = oh; bl = ol; bj = oj; ba = oa; }
+        }
+    };
+    wave_best();
+    if (lane == 0) { s_hi[wave] = bh; s_lo[wave] = bl; s_job[wave] = bj; s_atoms[wave] = ba; }
+    __syncthreads();
+    if (wave > 0) return;
+    const bool there = lane < int(blockDim.x) / kWave;
+    const int at = there ? lane : 0;
+    bh = there ? s_hi[at] : 0ull; bl = there ? s_lo[at] : 0ull; bj = there ? s_job[at] : INT32_MAX; ba = s_atoms[at];
+    wave_best();
+}
+
+// Key of a job's reply: (tier : F * multiplier) + 1, and F for the MIXED policy's ties.
+template <bool MIXED>
+__device__ __forceinline__ void pair_key(unsigned long long F, unsigned long long mult, unsigned long long tier, unsigned long long &hi, unsigned long long &lo)
+{
+    hi = ((tier << 62) | times_mult(F, mult)) + 1ull;
+    lo = MIXED ? F : 0ull;
+}
+
+// The best reply to a gap, a block per gap.
+template <bool MIXED>
+__global__ __launch_bounds__(kPairsMostThreads) void k_best_pairs(int n_jobs, PolicyDev pol, const int32_t *__restrict__ W, const int32_t *__restrict__ C,
+                                                              const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
+                                                              const int2 *__restrict__ atom_db, const long long *__restrict__ atom_area,
+                                                              const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
+                                                              const uint8_t *__restrict__ sla_class, const int32_t *__restrict__ job_held,
+                                                              const uint8_t *__restrict__ gap_active, PairGaps keep,
+                                                              int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut,
+                                                              int64_t *__restrict__ cand_score)
+{
+    constexpr int Q = kPairsQ;
+    const int g = blockIdx.x, tid = threadIdx.x;
+    const int gw = W[g], gc = C[g];
+    const bool on = !gap_active || gap_active[g];
+    if (tid == 0) keep_gap(keep, g, gw, gc);
+    unsigned long long bh = 0, bl = 0;
+    int bj = INT32_MAX, ba = 0;
+    for (int j0 = tid; on && j0 < n_jobs; j0 += Q * int(blockDim.x)) {
+        const int2 *dp[Q];
+        int n[Q], w[Q], c[Q], lo[Q];
+        int64_t base[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int j = j0 + q * int(blockDim.x);
+            const bool usable = j < n_jobs && !(job_held && job_held[j] >= 0);
+            base[q] = usable ? seg_off[j] : 0;
+            n[q] = usable ? n_atoms[j] : 0;
+            dp[q] = atom_dp + base[q];
+            w[q] = gw;
+            c[q] = gc;
+        }
+        search_pairs<Q>(dp, n, w, c, lo);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (lo[q] == 0) continue;
+            const int j = j0 + q * int(blockDim.x);
+            unsigned long long mult, tier, kh, kl;
+            job_policy(pol, wait, sla_class, j, mult, tier);
+            const int2 v = dp[q][lo[q] - 1];
+            pair_key<MIXED>(atom_area ? (unsigned long long)atom_area[base[q] + lo[q] - 1] : rect_of(v.x, v.y), mult, tier, kh, kl);
+            if (fused_better(kh, kl, j, bh, bl, bj)) { bh = kh; bl = kl; bj = j; ba = lo[q]; }
+        }
+    }
+    best_of_block<MIXED>(bh, bl, bj, ba);
+    if (tid == 0) {
+        cand_job[g] = bh ? bj : -1;
+        cand_cut[g] = bh ? atom_db[seg_off[bj] + ba - 1].y : -1;
+        cand_score[g] = bh ? int64_t((bh - 1ull) & ((1ull << 62) - 1ull)) : 0;
+    }
+}
+
+// The same from the replies that sja_fit left: the gap's row of the matrix.
+template <bool MIXED>
+__global__ __launch_bounds__(kPairsMostThreads) void k_select_pairs(int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off,
+                                                                const int32_t *__restrict__ pre_dur, const int32_t *__restrict__ pre_peak,
+                                                                const long long *__restrict__ pre_area, const int32_t *__restrict__ cut,
+                                                                const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
+                                                                const int32_t *__restrict__ job_held, const uint8_t *__restrict__ gap_active,
+                                                                int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut,
+                                                                int64_t *__restrict__ cand_score)
+{
+    const int g = blockIdx.x, tid = threadIdx.x;
+    const bool on = !gap_active || gap_active[g];
+    unsigned long long bh = 0, bl = 0;
+    int bj = INT32_MAX, bc = -1;
+#pragma unroll 4
+    for (int j = tid; on && j < n_jobs; j += int(blockDim.x)) {
+        const int b = cut[int64_t(g) * n_jobs + j];
+        if (b < 0 || (job_held && job_held[j] >= 0)) continue;
+        const int64_t at = seg_off[j] + b - 1;
+        unsigned long long mult, tier, kh, kl;
+        job_policy(pol, wait, sla_class, j, mult, tier);
+        pair_key<MIXED>(pre_area ? (unsigned long long)pre_area[at] : rect_of(pre_dur[at], pre_peak[at]), mult, tier, kh, kl);
+        if (fused_better(kh, kl, j, bh, bl, bj)) { bh = kh; bl = kl; bj = j; bc = b; }
+    }
+    best_of_block<MIXED>(bh, bl, bj, bc);
+    if (tid == 0) {
+        cand_job[g] = bh ? bj : -1;
+        cand_cut[g] = bh ? bc : -1;
+        cand_score[g] = bh ? int64_t((bh - 1ull) & ((1ull << 62) - 1ull)) : 0;
+    }
+}
+
+// Where entry k of gap g's list is: four entries side by side, those of neighbouring gaps next to each other.
+__host__ __device__ constexpr size_t pair_list_words(int n_gaps, int most) { return size_t((most + kPairsSlots - 1) / kPairsSlots) * n_gaps; }
+
+// The jobs that fit gap blockIdx.x in the order of their keys, as many as the rounds can ask for: a gap passes
+// only jobs that other gaps hold, so it needs no more of them than there are gaps (`most`).  The jobs that fit are
+// gathered in LDS and sorted there by a bitonic network; steps within the 128 entries that a wave's threads
+// exchange need no barrier.  If LDS has no room for all of them (ROOM entries, a power of two, at least
+// `most` + Q x threads if there are more jobs than Q x threads), those that are not among the best so far are dropped on the way.
+template <bool MIXED, int ROOM, int Q>
+__global__ __launch_bounds__(kPairsMostThreads) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, const int32_t *__restrict__ gap_w,
+                                                                   const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
+                                                                   const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area,
+                                                                   const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
+                                                                   const uint8_t *__restrict__ sla_class, int32_t *__restrict__ list_len,
+                                                                   unsigned long long *__restrict__ list)
+{
+    __shared__ unsigned long long s_hi[ROOM], s_lo[MIXED ? ROOM : 1];
+    __shared__ alignas(8) uint16_t s_job[ROOM];
+    __shared__ int s_n;
+    const int g = blockIdx.x, tid = threadIdx.x, threads = blockDim.x, lane = tid & (kWave - 1);
+    auto lo_at = [&](int i) -> unsigned long long & { return s_lo[MIXED ? i : 0]; };
+    // puts the first `fit` entries in order; returns up to where there are entries, a multiple of kPairsSlots
+    auto sort = [&](int fit) {
+        int n = kPairsSlots;
+        while (n < fit) n <<= 1;
+        for (int i = fit + tid; i < n; i += threads) {
+            s_hi[i] = 0;
+            if (MIXED) lo_at(i) = 0;
+            s_job[i] = uint16_t(n_jobs);            // nobody
+        }
+        __syncthreads();
+        for (int k = 2; k <= n; k <<= 1) {
+            for (int d = k >> 1; d > 0; d >>= 1) {
+                for (int t = tid; t < n / 2; t += threads) {
+                    const int a = 2 * t - (t & (d - 1)), b = a + d;
+                    const unsigned long long ha = s_hi[a], hb = s_hi[b];
+                    const unsigned long long la = MIXED ? lo_at(a) : 0ull, lb = MIXED ? lo_at(b) : 0ull;
+                    const uint16_t ja = s_job[a], jb = s_job[b];
+                    // the better one first, in every second stretch of k entries last
+                    if (fused_better(hb, lb, jb, ha, la, ja) == ((a & k) == 0)) {
+                        s_hi[a] = hb; s_hi[b] = ha;
+                        if (MIXED) { lo_at(a) = lb; lo_at(b) = la; }
+                        s_job[a] = jb; s_job[b] = ja;
+                    }
+                }
+                // what the next step reads was written by the same wave while it stays within 128 entries
+                const int next = d > 1 ? d >> 1 : k;
+                if (max(d, next) > kWave) __syncthreads(); else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+        }
+        __syncthreads();
+        return n;
+    };
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    const int gw = gap_w[g], gc = gap_c[g];
+    unsigned long long least_hi = 0, least_lo = 0;      // the last one of the best so far
+    int least_job = INT32_MAX;
+    for (int j0 = 0; j0 < n_jobs; j0 += Q * threads) {
+        const int2 *dp[Q];
+        int n[Q], w[Q], c[Q], lo[Q];
+        int64_t base[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int j = j0 + tid + q * threads;
+            base[q] = j < n_jobs ? seg_off[j] : 0;
+            n[q] = j < n_jobs ? n_atoms[j] : 0;
+            dp[q] = atom_dp + base[q];
+            w[q] = gw;
+            c[q] = gc;
+        }
+        search_pairs<Q>(dp, n, w, c, lo);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int j = j0 + tid + q * threads;
+            unsigned long long mult, tier, kh = 0, kl = 0;
+            if (lo[q] > 0) {
+                job_policy(pol, wait, sla_class, j, mult, tier);
+                const int2 v = dp[q][lo[q] - 1];
+                pair_key<MIXED>(atom_area ? (unsigned long long)atom_area[base[q] + lo[q] - 1] : rect_of(v.x, v.y), mult, tier, kh, kl);
+            }
+            const bool in = lo[q] > 0 && fused_better(kh, kl, j, least_hi, least_lo, least_job);
+            const unsigned long long fits = __ballot(in);
+            if (!fits) continue;
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_n, __popcll(fits));
+            at = __builtin_amdgcn_readfirstlane(at) + __popcll(fits & ((1ull << lane) - 1ull));
+            if (in) {
+                s_hi[at] = kh;
+                if (MIXED) lo_at(at) = kl;
+                s_job[at] = uint16_t(j);
+            }
+        }
+        if (j0 + Q * threads >= n_jobs) break;
+        __syncthreads();
+        const int fit = s_n;
+        __syncthreads();
+        if (fit + Q * threads > ROOM) {
+            sort(fit);
+            if (fit >= most) {
+                least_hi = s_hi[most - 1]; least_lo = MIXED ? lo_at(most - 1) : 0ull; least_job = s_job[most - 1];
+            }
+            if (tid == 0) s_n = min(fit, most);
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    const int fit = s_n, n = sort(fit);
+    if (tid == 0) list_len[g] = min(fit, most);
+    const int words = (min(n, most) + kPairsSlots - 1) / kPairsSlots;
+    for (int k = tid; k < words; k += threads)
+        list[size_t(k) * n_gaps + g] = *reinterpret_cast<const unsigned long long *>(s_job + kPairsSlots * k);
+}
+
+// All rounds by one block, a thread per gap.  A job's word is the smallest of its claims, round (22 bits) : gap
+// (10 bits), all ones before; a job is named in one round only, so its word also says whether it is held: if it is
+// smaller than any of the present round.  Behind a round's barrier one trip to LDS tells who won and which of the next
+// four jobs on the list are free in the next round: claims that others have made there already look free, too.
+// So a round is that trip, some 50 instructions and the barrier.
+// LDS: the lists are kept there, too; else a thread reads 16 entries ahead.
+// list holds `most` entries for each gap, rounded up.
+constexpr int kPairsListLds = 128 << 10;        // bytes for the lists
+
+template <bool LDS>
+__global__ __launch_bounds__(kPairsGaps) void k_rounds_pairs(
+    int n_gaps, int n_jobs, int most, int cap, PolicyDev pol, const int32_t *__restrict__ list_len, const unsigned long long *__restrict__ list,
+    const int32_t *__restrict__ gap_w, const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off, const int32_t *__restrict__ n_atoms,
+    const int2 *__restrict__ atom_dp, const int2 *__restrict__ atom_db, const long long *__restrict__ atom_area, const int32_t *__restrict__ wait,
+    const uint8_t *__restrict__ sla_class, int32_t *__restrict__ grant_job, int32_t *__restrict__ grant_cut, int64_t *__restrict__ grant_score,
+    int32_t *__restrict__ job_gap, int32_t *__restrict__ rounds_and_stable)
+{
+    __shared__ unsigned long long s_list[LDS ? kPairsListLds / 8 : 1];
+    __shared__ uint32_t s_word[kPairsJobs + 1];         // the one behind the last job's: nobody, never free
+    __shared__ int s_claims, s_lost;                    // the last round in which somebody claimed; the last one had losers
+    const int g = threadIdx.x, threads = blockDim.x, lane = g & (kWave - 1);
+    for (int i = g; i <= n_jobs; i += threads) s_word[i] = i < n_jobs ? ~0u : 0u;
+    if (g == 0) s_claims = s_lost = 0;
+    const int words = (most + kPairsSlots - 1) / kPairsSlots;
+    if (LDS)
+        for (int i = g; i < words * n_gaps; i += threads) s_list[LDS ? i : 0] = list[i];       // (what lies behind a list's end is not looked at)
+    int left = g < n_gaps ? (list_len[g] + kPairsSlots - 1) / kPairsSlots : 0;      // words of the list not yet read
+    constexpr int kAhead = LDS ? 1 : 4;
+    unsigned long long ahead[kAhead];           // what the list has next
+    uint32_t c[4], w[4];            // the next four jobs (byte offsets of their words), and their words
+    int at = 0, in_hand = 0;
+    auto ask = [&]() {
+        if (in_hand > 0) return;
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const size_t to = size_t(min(at + k, words - 1)) * n_gaps + g;
+            ahead[k] = LDS ? s_list[LDS ? to : 0] : list[to];
+        }
+        at += kAhead;
+        in_hand = kAhead;
+    };
+    auto take = [&]() {
+        const uint32_t a = uint32_t(ahead[0]), b = uint32_t(ahead[0] >> 32);
+        c[0] = (a & 0xffffu) * 4; c[1] = (a >> 16) * 4; c[2] = (b & 0xffffu) * 4; c[3] = (b >> 16) * 4;
+#pragma unroll
+        for (int k = 1; k < kAhead; ++k) ahead[k - 1] = ahead[k];
+        --in_hand;
+        --left;
+    };
+    auto word = [&](uint32_t off) -> uint32_t & { return *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(s_word) + off); };
+    const uint32_t nobody = uint32_t(n_jobs) * 4;
+    __syncthreads();
+    bool open = left > 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { c[k] = nobody; w[k] = 0; }
+    if (open) {
+        ask();
+        take();
+        ask();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = word(c[k]);
+    }
+    int won = -1, lost_in = 0, rounds = 0, stable = 0;
+    for (int round = 1;; ++round) {
+        const uint32_t now = uint32_t(round) << 10;
+        // (a job that was passed is held, and stays so)
+        while (open && max(max(w[0], w[1]), max(w[2], w[3])) < now) {
+            if (left == 0) { open = false; break; }
+            take();
+            ask();
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w[k] = word(c[k]);
+        }
+        uint32_t job = w[0] >= now ? c[0] : w[1] >= now ? c[1] : w[2] >= now ? c[2] : c[3];
+        job = open ? job : nobody;
+        // the job of a wave's lowest gap is claimed once for all of its gaps that want it
+        const unsigned long long claims = __ballot(open);
+        if (claims) {
+            const int first = __ffsll((long long)claims) - 1;
+            const bool same = job == uint32_t(__builtin_amdgcn_readlane(int(job), first));
+            if (open && (!same || lane == first)) atomicMin(&word(job), now | uint32_t(g));
+            if (lane == first) s_claims = round;
+        }
+        __syncthreads();
+        const uint32_t outcome = word(job);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = word(c[k]);
+        const int claimed = *static_cast<volatile int *>(&s_claims);
+        if (claimed < round || round == cap) {
+            // nobody is left that could claim anything, or it is to end: were there losers in the last round played?
+            const bool lost = claimed < round ? round > 1 && lost_in == round - 1 : open && outcome != (now | uint32_t(g));
+            if (claimed >= round && open && !lost) won = int(job >> 2);
+            if (lost) s_lost = 1;
+            __syncthreads();
+            rounds = claimed >= round || round == 1 || s_lost ? round : round - 1;
+            stable = claimed < round || !s_lost;
+            break;
+        }
+        if (open) {
+            if (outcome == (now | uint32_t(g))) { won = int(job >> 2); open = false; }
+            else lost_in = round;
+        }
+    }
+    for (int j = g; j < n_jobs; j += threads) job_gap[j] = s_word[j] == ~0u ? -1 : int(s_word[j] & (kPairsGaps - 1));
+    if (g == 0) { rounds_and_stable[0] = rounds; rounds_and_stable[1] = stable; }
+    if (g >= n_gaps) return;
+    grant_job[g] = won;
+    int b = -1;
+    long long score = 0;
+    if (won >= 0) {
+        const int64_t base = seg_off[won];
+        const int2 *dp[1] = {atom_dp + base};
+        const int n[1] = {n_atoms[won]}, w[1] = {gap_w[g]}, c[1] = {gap_c[g]};
+        int lo[1];
+        search_pairs<1>(dp, n, w, c, lo);
+        const int2 v = dp[0][lo[0] - 1];
+        unsigned long long mult, tier;
+        job_policy(pol, wait, sla_class, won, mult, tier);
+        b = atom_db[base + lo[0] - 1].y;
+        score = int64_t(times_mult(atom_area ? (unsigned long long)atom_area[base + lo[0] - 1] : rect_of(v.x, v.y), mult));
+    }
+    grant_cut[g] = b;
+    grant_score[g] = score;
+}
+
+}  // namespace sja

@@ -2,6 +2,7 @@
 // bookkeeping and kernel launches.  See include/sja.h for the contract.
 #include "sja_kernels.h"
 #include "k_sets.h"
+#include "k_pairs.h"
 
 #include <mutex>
 #include <new>
@@ -644,6 +645,69 @@ int enqueue_gap_plan(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_ga
     return SJA_OK;
 }
 
+// A batch served pair by pair.  The gaps' lists take the space of the list entries.
+int pair_list_most(int64_t G, int64_t J) { return int(G < J ? G : J); }
+
+bool pairs_batch(const sja_ctx *ctx, const Layout &L, int64_t G, int64_t J)
+{
+    return ctx->resolve_mode == SJA_RESOLVE_LISTS && J > 0 && G <= kPairsGaps && J <= kPairsJobs && G * J <= kPairsMost &&
+           pair_list_words(int(G), pair_list_most(G, J)) * 8 <= L.lb_begin - L.g_ekey0;
+}
+
+PairGaps pair_gaps(sja_ctx *ctx, const Layout &L)
+{
+    return {ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_c), ws_ptr<int32_t>(ctx, L.gap_order)};
+}
+
+// The plan that a small batch went without.
+int plan_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L)
+{
+    int32_t *W = ws_ptr<int32_t>(ctx, L.res_cand_job), *C = ws_ptr<int32_t>(ctx, L.res_cand_cut);
+    const size_t bytes = size_t(ctx->n_gaps) * 4;
+    SJA_HIP(hipMemcpyAsync(W, ws_ptr<int32_t>(ctx, L.gap_w), bytes, hipMemcpyDeviceToDevice, st), "gap copy");
+    SJA_HIP(hipMemcpyAsync(C, ws_ptr<int32_t>(ctx, L.gap_c), bytes, hipMemcpyDeviceToDevice, st), "gap copy");
+    const int rc = enqueue_gap_plan(ctx, st, L, ctx->n_gaps, W, C);
+    if (rc == SJA_OK) ctx->pairs = false;
+    return rc;
+}
+
+int pair_threads(int J) { return J <= kWave ? kWave : J <= 4 * 256 ? 256 : kPairsMostThreads; }
+
+int resolve_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params, const int32_t *wait, const uint8_t *sla_class,
+                  int32_t *grant_job, int32_t *grant_cut, int64_t *grant_score, int32_t *job_gap, int cap, int32_t *rounds_and_stable)
+{
+    const int G = ctx->n_gaps, J = ctx->n_jobs, most = pair_list_most(G, J);
+    const PolicyDev pol = to_dev(params);
+    const long long *area = atom_area_of(ctx, L);
+    const int32_t *gap_w = ws_ptr<int32_t>(ctx, L.gap_w), *gap_c = ws_ptr<int32_t>(ctx, L.gap_c), *n_atoms = ws_ptr<int32_t>(ctx, L.n_atoms);
+    const int2 *atom_dp = ws_ptr<int2>(ctx, L.atom_dp), *atom_db = ws_ptr<int2>(ctx, L.atom_db);
+    int32_t *len = ws_ptr<int32_t>(ctx, L.gap_rank);
+    unsigned long long *list = ws_ptr<unsigned long long>(ctx, L.g_ekey0);
+    auto order = [&](auto mixed) {
+        constexpr bool M = decltype(mixed)::value;
+        // a thread per two entries, if it is not too many
+        auto launch = [&](auto kern, int threads) {
+            hipLaunchKernelGGL(kern, dim3(G), dim3(threads), 0, st, G, J, most, pol, gap_w, gap_c, ctx->seg_off, atom_dp, area, n_atoms, wait,
+                               sla_class, len, list);
+        };
+        if (J <= 128) launch(k_order_pairs<M, 128, 2>, 64);
+        else if (J <= 512) launch(k_order_pairs<M, 512, 2>, 256);
+        else if (J <= 1024) launch(k_order_pairs<M, 1024, 2>, 512);
+        else if (J <= 2048) launch(k_order_pairs<M, 2048, 2>, 1024);
+        else launch(k_order_pairs<M, 4096, 2>, 1024);
+    };
+    if (params->policy == SJA_POLICY_MIXED) order(std::true_type{});
+    else order(std::false_type{});
+    SJA_HIP(hipGetLastError(), "k_order_pairs launch");
+    auto kern = pair_list_words(G, most) * 8 <= kPairsListLds ? k_rounds_pairs<true> : k_rounds_pairs<false>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3((G + kWave - 1) / kWave * kWave), 0, st, G, J, most, cap, pol, len, list, gap_w, gap_c,
+                       ctx->seg_off, n_atoms, atom_dp, atom_db, area, wait, sla_class, grant_job, grant_cut, grant_score, job_gap,
+                       rounds_and_stable);
+    SJA_HIP(hipGetLastError(), "k_rounds_pairs launch");
+    SJA_HIP(hipStreamSynchronize(st), "final synchronise");
+    return SJA_OK;
+}
+
 JobLimits job_limits(const sja_limits &l, const int32_t *power, const int32_t *deadline)
 {
     JobLimits out;
@@ -654,6 +718,34 @@ JobLimits job_limits(const sja_limits &l, const int32_t *power, const int32_t *d
     out.power = power;
     out.deadline = deadline;
     return out;
+}
+
+// The start and the end of the pair evaluation, for sja_last_fit_kernel_ms.
+int mark_kernel(sja_ctx *ctx, hipStream_t st, bool end)
+{
+    if (!ctx->ev_start) {
+        SJA_HIP(hipEventCreate(&ctx->ev_start), "hipEventCreate");
+        SJA_HIP(hipEventCreate(&ctx->ev_stop), "hipEventCreate");
+    }
+    SJA_HIP(hipEventRecord(end ? ctx->ev_stop : ctx->ev_start, st), "hipEventRecord");
+    ctx->timed = end;
+    return SJA_OK;
+}
+
+// fit -> select of a small batch.
+int launch_best_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const int32_t *W, const int32_t *C,
+                      const sja_params *params, const int32_t *wait, const uint8_t *sla_class, const int32_t *job_held,
+                      const uint8_t *gap_active, int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score)
+{
+    const int J = ctx->n_jobs;
+    auto kern = params->policy == SJA_POLICY_MIXED ? k_best_pairs<true> : k_best_pairs<false>;
+    int rc = ctx->timing ? mark_kernel(ctx, st, false) : SJA_OK;
+    if (rc != SJA_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3(n_gaps), dim3(pair_threads(J)), 0, st, J, to_dev(params), W, C, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
+                       ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class, job_held,
+                       gap_active, pair_gaps(ctx, L), cand_job, cand_cut, cand_score);
+    SJA_HIP(hipGetLastError(), "k_best_pairs launch");
+    return ctx->timing ? mark_kernel(ctx, st, true) : SJA_OK;
 }
 
 // The fused fit -> select pass over the planned batch of gaps (the plan of enqueue_gap_plan is in
@@ -689,13 +781,8 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
                                        : k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, false, true>)
                               : (mixed ? k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, true, false>
                                        : k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, false, false>);
-        if (timed) {
-            if (!ctx->ev_start) {
-                SJA_HIP(hipEventCreate(&ctx->ev_start), "hipEventCreate");
-                SJA_HIP(hipEventCreate(&ctx->ev_stop), "hipEventCreate");
-            }
-            SJA_HIP(hipEventRecord(ctx->ev_start, st), "hipEventRecord");
-        }
+        int rc = timed ? mark_kernel(ctx, st, false) : SJA_OK;
+        if (rc != SJA_OK) return rc;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, to_dev(params),
                            ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
                            ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin),
@@ -706,10 +793,7 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
                            ws_ptr<int32_t>(ctx, L.gap_run_end), wait, sla_class, job_held, gap_active,
                            ws_ptr<SelPartial>(ctx, L.sel_part));
         SJA_HIP(hipGetLastError(), "k_fit_select launch");
-        if (timed) {
-            SJA_HIP(hipEventRecord(ctx->ev_stop, st), "hipEventRecord");
-            ctx->timed = true;
-        }
+        if (timed && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
     }
     hipLaunchKernelGGL(k_fused_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_db), cand_job,
@@ -1004,25 +1088,30 @@ int sja_fit(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W, const 
     DeviceGuard guard(ctx->device);
     SJA_HIP(guard.err, "hipSetDevice");
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const bool pairs = pairs_batch(ctx, L, n_gaps, J);
     if (n_gaps > 0) {
         const int words = (J + 31) / 32;
         const int chunk_bound = int(fit_chunk_bound(n_gaps, J));
         const dim3 b256(256);
         int32_t *gw = ws_ptr<int32_t>(ctx, L.gap_w), *gcap = ws_ptr<int32_t>(ctx, L.gap_c);
         int32_t *plan = ws_ptr<int32_t>(ctx, L.plan);
-        int rc = enqueue_gap_plan(ctx, st, L, n_gaps, W, C);
-        if (rc != SJA_OK) return rc;
-        if (J > 0) {
+        int rc = SJA_OK;
+        if (pairs) {
+            if (ctx->timing && (rc = mark_kernel(ctx, st, false)) != SJA_OK) return rc;
+            hipLaunchKernelGGL(k_fit_pairs, dim3((J + kPairsThreads - 1) / kPairsThreads, (n_gaps + kPairsQ - 1) / kPairsQ), dim3(kPairsThreads), 0, st,
+                               n_gaps, J, W, C, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), ws_ptr<int2>(ctx, L.atom_db),
+                               ws_ptr<int32_t>(ctx, L.n_atoms), pair_gaps(ctx, L), cut, interest_bits);
+            SJA_HIP(hipGetLastError(), "k_fit_pairs launch");
+            if (ctx->timing && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
+        } else {
+            rc = enqueue_gap_plan(ctx, st, L, n_gaps, W, C);
+            if (rc != SJA_OK) return rc;
+        }
+        if (J > 0 && !pairs) {
             const int job_tiles = (J + kFitBlock - 1) / kFitBlock;
             const int tiles8 = (job_tiles + 7) / 8 * 8;
             const unsigned grid = unsigned(tiles8) * unsigned(chunk_bound);
-            if (ctx->timing) {
-                if (!ctx->ev_start) {
-                    SJA_HIP(hipEventCreate(&ctx->ev_start), "hipEventCreate");
-                    SJA_HIP(hipEventCreate(&ctx->ev_stop), "hipEventCreate");
-                }
-                SJA_HIP(hipEventRecord(ctx->ev_start, st), "hipEventRecord");
-            }
+            if (ctx->timing && (rc = mark_kernel(ctx, st, false)) != SJA_OK) return rc;
             hipLaunchKernelGGL((k_fit_main<kFitBlock, kFitWindow, kFitPeriod>), dim3(grid), dim3(kFitBlock), 0, st,
                                J, chunk_bound, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
                                ws_ptr<int2>(ctx, L.atom_db), ws_ptr<int32_t>(ctx, L.n_atoms), plan,
@@ -1032,10 +1121,7 @@ int sja_fit(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W, const 
                                ws_ptr<int32_t>(ctx, L.ncap_tab), gw, gcap, ws_ptr<int64_t>(ctx, L.gap_row),
                                ws_ptr<int32_t>(ctx, L.gap_run_end), cut);
             SJA_HIP(hipGetLastError(), "k_fit_main launch");
-            if (ctx->timing) {
-                SJA_HIP(hipEventRecord(ctx->ev_stop, st), "hipEventRecord");
-                ctx->timed = true;
-            }
+            if (ctx->timing && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
             if (interest_bits) {
                 uint32_t *table = ws_ptr<uint32_t>(ctx, L.bits_table);
                 int32_t *class_dmax = ws_ptr<int32_t>(ctx, L.class_dmax);
@@ -1065,6 +1151,7 @@ int sja_fit(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W, const 
     ctx->cut = cut;
     ctx->fitted = true;
     ctx->planned = true;
+    ctx->pairs = pairs;
     return SJA_OK;
 }
 
@@ -1081,6 +1168,10 @@ int sja_store_reference(sja_ctx *ctx, void *stream, int32_t *cut)
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int job_tiles = (J + kFitBlock - 1) / kFitBlock;
     if (G > 0 && job_tiles > 0) {
+        if (ctx->pairs) {
+            const int rc = plan_pairs(ctx, st, L);
+            if (rc != SJA_OK) return rc;
+        }
         const int chunk_bound = int(fit_chunk_bound(G, J));
         const int tiles8 = (job_tiles + 7) / 8 * 8;
         hipLaunchKernelGGL(k_store_reference<kFitBlock>, dim3(unsigned(tiles8) * unsigned(chunk_bound)), dim3(kFitBlock), 0, st,
@@ -1114,7 +1205,11 @@ int sja_fit_select(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W,
     DeviceGuard guard(ctx->device);
     SJA_HIP(guard.err, "hipSetDevice");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (n_gaps > 0) {
+    const bool pairs = pairs_batch(ctx, L, n_gaps, J);
+    if (n_gaps > 0 && pairs) {
+        rc = launch_best_pairs(ctx, st, L, n_gaps, W, C, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut, cand_score);
+        if (rc != SJA_OK) return rc;
+    } else if (n_gaps > 0) {
         rc = enqueue_gap_plan(ctx, st, L, n_gaps, W, C);
         if (rc != SJA_OK) return rc;
         rc = launch_fused(ctx, st, L, n_gaps, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut,
@@ -1124,6 +1219,7 @@ int sja_fit_select(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W,
     ctx->n_gaps = n_gaps;
     ctx->cut = nullptr;
     ctx->planned = true;
+    ctx->pairs = pairs;
     return SJA_OK;
 }
 
@@ -1140,8 +1236,16 @@ int sja_select(sja_ctx *ctx, void *stream, const sja_params *params, const int32
     if (!ctx->ws || ctx->ws_bytes < L.total) return fail(ctx, SJA_ERR_WORKSPACE, "workspace too small");
     DeviceGuard guard(ctx->device);
     SJA_HIP(guard.err, "hipSetDevice");
-    return launch_select(ctx, static_cast<hipStream_t>(stream), params, wait, sla_class, job_held,
-                         gap_active, cand_job, cand_cut, cand_score);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (ctx->pairs && ctx->n_gaps > 0) {
+        auto kern = params->policy == SJA_POLICY_MIXED ? k_select_pairs<true> : k_select_pairs<false>;
+        hipLaunchKernelGGL(kern, dim3(ctx->n_gaps), dim3(pair_threads(ctx->n_jobs)), 0, st, ctx->n_jobs, to_dev(params), ctx->seg_off, ctx->pre_dur,
+                           ctx->pre_peak, pre_area_of(ctx, L), ctx->cut, wait, sla_class, job_held, gap_active, cand_job, cand_cut,
+                           cand_score);
+        SJA_HIP(hipGetLastError(), "k_select_pairs launch");
+        return SJA_OK;
+    }
+    return launch_select(ctx, st, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut, cand_score);
 }
 
 int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int32_t *wait,
@@ -1162,6 +1266,14 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
     DeviceGuard guard(ctx->device);
     SJA_HIP(guard.err, "hipSetDevice");
     hipStream_t st = static_cast<hipStream_t>(stream);
+
+    // every round that does not end the process grants at least one job, so it
+    // ends by itself within min(G, J) + 1 rounds: a larger cap changes nothing
+    const int64_t natural = int64_t(G < J ? G : J) + 1;
+    const int64_t cap = (params->max_rounds > 0 && params->max_rounds < natural) ? params->max_rounds : natural;
+    if (ctx->pairs && G > 0 && ctx->resolve_mode == SJA_RESOLVE_LISTS)
+        return resolve_pairs(ctx, st, L, params, wait, sla_class, grant_job, grant_cut, grant_score, job_gap, int(cap), rounds_used_and_stable);
+    if (ctx->pairs && G > 0 && ctx->resolve_mode != SJA_RESOLVE_MATRIX && (rc = plan_pairs(ctx, st, L)) != SJA_OK) return rc;
 
     int32_t *cand_job = ws_ptr<int32_t>(ctx, L.res_cand_job);
     int32_t *cand_cut = ws_ptr<int32_t>(ctx, L.res_cand_cut);
@@ -1189,10 +1301,6 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
                            grant_cut, grant_score, job_gap, active, claim, clear);
         SJA_HIP(hipGetLastError(), "k_resolve_init launch");
     }
-    // every round that does not end the process grants at least one job, so it
-    // ends by itself within min(G, J) + 1 rounds: a larger cap changes nothing
-    const int64_t natural = int64_t(G < J ? G : J) + 1;
-    const int64_t cap = (params->max_rounds > 0 && params->max_rounds < natural) ? params->max_rounds : natural;
     int32_t result[2] = {0, 0};
     bool done = false, many_capacities = false;
     if (G > 0 && J > 0 && ctx->resolve_mode != SJA_RESOLVE_MATRIX) {
@@ -1211,7 +1319,7 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
     // and 4; 272 rounds of 700 x 2501: 12.0 ms one by one, 8.6 so).
     constexpr int kMostRounds = 8;
     constexpr int64_t kShortPass = int64_t(1) << 24;        // pairs; 40 us
-    const bool searched = many_capacities && !ctx->fitted;
+    const bool searched = (many_capacities || ctx->pairs) && !ctx->fitted;
     auto batch_from = [&](int64_t r) -> int64_t {
         const int64_t n = searched ? r + 1 : int64_t(G) * J <= kShortPass ? r / 8 : 1;
         return n < 1 ? 1 : n < kMostRounds ? n : kMostRounds;

@@ -240,6 +240,7 @@ struct sja_ctx {
     // state left by sja_fit (planned and fitted) or sja_fit_select (planned only: no cut matrix)
     bool planned;
     bool fitted;
+    bool pairs;          // a small batch: its gaps in the caller's order, nothing else is planned
     int32_t n_gaps;
     const int32_t *cut;
 };
