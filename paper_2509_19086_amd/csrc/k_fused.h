@@ -44,9 +44,10 @@ __device__ __forceinline__ unsigned long long fused_readlane_u64(unsigned long l
 // compiler takes by itself: the stepping loop is bound by latency (1.5 against 2.1 ms).
 // AREA: the key's F is the atom's area under the envelope (a second window of
 // 64-bit values beside the (duration, peak) one) instead of duration x peak.
+// untabled_only: k_range_select serves the batch if its classes have tables.
 template <int BLOCK, int CAP, int PERIOD, bool MIXED, bool AREA>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fit_select(
-    int n_jobs, int n_gaps, int chunk_bound, PolicyDev pol, const int64_t *__restrict__ seg_off,
+    int n_jobs, int n_gaps, int chunk_bound, int untabled_only, PolicyDev pol, const int64_t *__restrict__ seg_off,
     const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area,
     const int32_t *__restrict__ n_atoms,
     const int32_t *__restrict__ plan, const int32_t *__restrict__ chunk_begin,
@@ -77,6 +78,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
     const int chunk = k % chunk_bound;
     if (job_tile * BLOCK >= n_jobs || chunk >= plan[kPlanChunks]) return;
     const bool tabled = plan[kPlanTabled] != 0;
+    if (tabled && untabled_only) return;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const int j_raw = job_tile * BLOCK + tid;
@@ -452,6 +454,244 @@ __global__ __launch_bounds__(256) void k_fused_reduce(int n_gaps, int n_job_tile
     int g, bj, ba;
     unsigned long long bh;
     if (!reduce_tiles(n_gaps, n_job_tiles, part, g, bh, bj, ba)) return;
+    cand_job[g] = bh ? bj : -1;
+    cand_cut[g] = bh ? atom_db[seg_off[bj] + ba - 1].y : -1;
+    cand_score[g] = bh ? int64_t((bh - 1ull) & ((1ull << 62) - 1ull)) : 0;
+}
+
+// The same without a step per position.  Along the sorted positions of a class a job's key never falls (the
+// host sees to it where the hysteresis rule could undo that), so the best key at a position is the largest one
+// that any job has reached by then: every atom is an event at the first position whose window reaches its
+// duration, and the answer a running maximum over the positions.  A block takes a chunk of positions and
+// `batches` x 256 jobs.  Most jobs end the chunk below what the best one began it with: a thread per job looks at its
+// last atom there and at its first one; of the others sixteen lanes read the atoms side by side, find their
+// positions by a table in LDS and raise the largest key there.  Then those jobs are looked through again for the keys that
+// are exactly the largest, the lowest of them counts (under MIXED the one with the largest F: a third time, if a
+// position has several).  Work per atom of few jobs instead of per pair: what is left are the tables of the plan and the
+// trips for the jobs' ends.  32768 gaps x 65536 jobs 1607 -> 293 us (with every atom looked at 856), a call 1768 -> 489;
+// 2048 x 8192 80 -> 21 us, 1777 x 6151 with the area score 102 -> 59.
+constexpr int kRangeThreads = 256, kRangeLanes = 16, kRangeGroups = kRangeThreads / kRangeLanes;
+constexpr int kRangeBatches = 8;            // batches of kRangeThreads jobs per block, at most,
+constexpr int kRangeBlocks = 2048;          // as long as there are so many blocks
+constexpr int kRangeTable = 512;
+constexpr int kRangeTogether = 4;           // jobs whose atoms a group asks for together
+
+template <bool MIXED, bool AREA>
+__global__ __launch_bounds__(kRangeThreads) void k_range_select(
+    int n_jobs, int n_gaps, int chunk_bound, int batches, PolicyDev pol, const int64_t *__restrict__ seg_off,
+    const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area, const int32_t *__restrict__ plan,
+    const int32_t *__restrict__ chunk_begin, const int32_t *__restrict__ chunk_end, const int32_t *__restrict__ chunk_class,
+    const int32_t *__restrict__ start_tab, const int32_t *__restrict__ ncap_tab, const int32_t *__restrict__ gap_w,
+    const int32_t *__restrict__ gap_order, const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
+    const int32_t *__restrict__ job_held, const uint8_t *__restrict__ gap_active, SelPartial *__restrict__ part)
+{
+    __shared__ unsigned long long s_best[kFitMaxChunk], s_second[MIXED ? kFitMaxChunk : 1];
+    __shared__ int s_who[kFitMaxChunk], s_w[kFitMaxChunk];
+    __shared__ uint16_t s_tab[kRangeTable + 1];
+    __shared__ long long s_base[kRangeThreads];
+    __shared__ unsigned long long s_mult[kRangeThreads];
+    __shared__ int s_from[kRangeThreads], s_to[kRangeThreads], s_id[kRangeThreads];
+    __shared__ uint8_t s_tier[kRangeThreads];
+    __shared__ uint16_t s_near[kRangeBatches * kRangeThreads];      // jobs of the tile that came near the best
+    __shared__ int s_count, s_n_near, s_several;
+    const int k = blockIdx.x >> 3, job_tile = (k / chunk_bound) * 8 + (blockIdx.x & 7), chunk = k % chunk_bound;
+    const int tile_jobs = batches * kRangeThreads, job0 = job_tile * tile_jobs;
+    if (!plan[kPlanTabled] || job0 >= n_jobs || chunk >= plan[kPlanChunks]) return;
+    const int tid = threadIdx.x, sub = tid & (kRangeLanes - 1), group = tid / kRangeLanes;
+    const int begin = chunk_begin[chunk], n = chunk_end[chunk] - begin, cls = chunk_class[chunk];
+    const bool last_of_class = chunk + 1 >= plan[kPlanChunks] || chunk_class[chunk + 1] != cls;
+    const int32_t *from_row = start_tab + int64_t(chunk) * n_jobs;
+    const int32_t *to_row = last_of_class ? ncap_tab + int64_t(cls) * n_jobs : from_row + n_jobs;
+    for (int i = tid; i < n; i += kRangeThreads) {
+        s_w[i] = gap_w[begin + i];
+        s_best[i] = 0;
+        if (MIXED) s_second[MIXED ? i : 0] = 0;
+        s_who[i] = INT32_MAX;
+    }
+    if (tid == 0) s_count = s_n_near = s_several = 0;
+    __syncthreads();
+    const int w_first = s_w[0], w_last = s_w[n - 1];
+    int shift = 0;
+    while (((uint32_t(w_last) - uint32_t(w_first)) >> shift) >= uint32_t(kRangeTable - 1)) ++shift;
+    // entry t: the first position whose window reaches w_first + (t << shift)
+    for (int t = tid; t <= kRangeTable; t += kRangeThreads) {
+        const long long d = (long long)w_first + ((long long)t << shift);
+        int lo = 0, hi = n;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (s_w[mid] < d) lo = mid + 1; else hi = mid;
+        }
+        s_tab[t] = uint16_t(lo);
+    }
+    auto position = [&](int d) {            // of a duration up to w_last
+        if (d <= w_first) return 0;
+        const uint32_t t = (uint32_t(d) - uint32_t(w_first)) >> shift;
+        int lo = s_tab[t], hi = s_tab[t + 1];
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (s_w[mid] < d) lo = mid + 1; else hi = mid;
+        }
+        return lo;
+    };
+    auto key_of = [](unsigned long long F, unsigned long long mult, unsigned long long tier) { return ((tier << 62) | times_mult(F, mult)) + 1ull; };
+    auto area = [&](int64_t at) { return AREA ? (unsigned long long)atom_area[at] : 0ull; };
+    auto size_of = [](const int2 &v, unsigned long long area_of) { return AREA ? area_of : rect_of(v.x, v.y); };
+    // Calls on(duration, key, F, job) for the atoms that the jobs near the best have in the chunk: of the tile's jobs, or of
+    // those that were near it before.
+    auto walk = [&](bool again, auto on) {
+        const int n_jobs_here = again ? s_n_near : min(tile_jobs, n_jobs - job0);
+        for (int b = 0; b < n_jobs_here; b += kRangeThreads) {
+            int job = -1;
+            if (b + tid < n_jobs_here) job = job0 + (again ? int(s_near[b + tid]) : b + tid);
+            if (!again && job >= 0 && job_held && job_held[job] >= 0) job = -1;
+            int from = 0, to = 0;
+            int64_t base = 0;
+            unsigned long long mult = 1, tier = 0, last = 0, first = 0;
+            if (job >= 0) {
+                from = max(from_row[job] - 1, 0);
+                to = to_row[job];
+                base = seg_off[job];
+                job_policy(pol, wait, sla_class, job, mult, tier);
+            }
+            if (from < to) {
+                const int2 v = atom_dp[base + to - 1], u = atom_dp[base + from];
+                const unsigned long long last_area = area(base + to - 1), first_area = area(base + from);
+                last = key_of(size_of(v, last_area), mult, tier);
+                if (!again && u.x <= w_first) first = key_of(size_of(u, first_area), mult, tier);
+            }
+            if (!again) {
+#pragma unroll
+                for (int d = 1; d < kWave; d <<= 1) {
+                    const unsigned long long o = (unsigned long long)__shfl_xor((long long)first, d, kWave);
+                    first = o > first ? o : first;
+                }
+                if ((tid & (kWave - 1)) == 0 && first) atomicMax(&s_best[0], first);
+                __syncthreads();
+            }
+            const bool near = from < to && last >= s_best[0];
+            if (near) {
+                const int to_slot = atomicAdd(&s_count, 1);
+                s_base[to_slot] = base; s_mult[to_slot] = mult; s_tier[to_slot] = uint8_t(tier);
+                s_from[to_slot] = from; s_to[to_slot] = to; s_id[to_slot] = job;
+                if (!again) s_near[atomicAdd(&s_n_near, 1)] = uint16_t(job - job0);
+            }
+            __syncthreads();
+            const int count = s_count;
+            for (int i0 = group; i0 < count; i0 += kRangeTogether * kRangeGroups) {
+                int2 v[kRangeTogether];
+                unsigned long long f[kRangeTogether];
+                int a[kRangeTogether], end[kRangeTogether];
+#pragma unroll
+                for (int q = 0; q < kRangeTogether; ++q) {
+                    const int i = i0 + q * kRangeGroups;
+                    a[q] = i < count ? s_from[i] + sub : 0;
+                    end[q] = i < count ? s_to[i] : 0;
+                    if (a[q] < end[q]) { v[q] = atom_dp[s_base[i] + a[q]]; f[q] = area(s_base[i] + a[q]); }
+                }
+#pragma unroll
+                for (int q = 0; q < kRangeTogether; ++q) {
+                    const int i = min(i0 + q * kRangeGroups, count - 1);
+                    while (a[q] < end[q] && v[q].x <= w_last) {
+                        const int64_t at = s_base[i] + a[q];
+                        const unsigned long long F = size_of(v[q], f[q]);
+                        on(v[q].x, key_of(F, s_mult[i], s_tier[i]), F, s_id[i]);
+                        a[q] += kRangeLanes;
+                        if (a[q] < end[q]) { v[q] = atom_dp[at + kRangeLanes]; f[q] = area(at + kRangeLanes); }
+                    }
+                }
+            }
+            __syncthreads();
+            if (tid == 0) s_count = 0;
+            __syncthreads();
+        }
+    };
+    // the running best over the positions: keys, then F, then the lowest job
+    auto running = [&]() {
+        constexpr int PER = kFitMaxChunk / kRangeThreads;
+        for (int d = 1; d < n; d <<= 1) {
+            unsigned long long hi[PER], lo[PER];
+            int job[PER];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int i = tid + q * kRangeThreads;
+                if (i >= n) continue;
+                hi[q] = s_best[i]; lo[q] = MIXED ? s_second[MIXED ? i : 0] : 0ull; job[q] = s_who[i];
+                if (i < d) continue;
+                const unsigned long long oh = s_best[i - d], ol = MIXED ? s_second[MIXED ? i - d : 0] : 0ull;
+                const int oj = s_who[i - d];
+                if (fused_better(oh, ol, oj, hi[q], lo[q], job[q])) { hi[q] = oh; lo[q] = ol; job[q] = oj; }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int i = tid + q * kRangeThreads;
+                if (i >= n) continue;
+                s_best[i] = hi[q];
+                if (MIXED) s_second[MIXED ? i : 0] = lo[q];
+                s_who[i] = job[q];
+            }
+        }
+        __syncthreads();
+    };
+    __syncthreads();
+    walk(false, [&](int d, unsigned long long key, unsigned long long, int) {
+        if (key >= *static_cast<volatile unsigned long long *>(&s_best[0])) atomicMax(&s_best[position(d)], key);      // else below the best everywhere
+    });
+    running();
+    walk(true, [&](int d, unsigned long long key, unsigned long long F, int job) {
+        if (key < s_best[0]) return;
+        const int p = position(d);
+        if (key != s_best[p]) return;
+        if (MIXED) atomicMax(&s_second[MIXED ? p : 0], F);
+        const int other = atomicMin(&s_who[p], job);
+        if (MIXED && other != INT32_MAX && other != job) s_several = 1;
+    });
+    const bool several = MIXED && s_several;
+    running();
+    if (several) {
+        for (int i = tid; i < n; i += kRangeThreads) s_who[i] = INT32_MAX;
+        __syncthreads();
+        walk(true, [&](int d, unsigned long long key, unsigned long long F, int job) {
+            if (key < s_best[0]) return;
+            const int p = position(d);
+            if (key == s_best[p] && F == s_second[MIXED ? p : 0]) atomicMin(&s_who[p], job);
+        });
+        running();
+    }
+    for (int i = tid; i < n; i += kRangeThreads) {
+        const int g = gap_order[begin + i];
+        const unsigned long long best = !gap_active || gap_active[g] ? s_best[i] : 0ull;
+        SelPartial out;
+        out.hi = best; out.lo = MIXED ? s_second[MIXED ? i : 0] : 0ull; out.job = best ? s_who[i] : -1; out.cut = begin + i; out.pad = 0;
+        part[int64_t(job_tile) * n_gaps + g] = out;
+    }
+}
+
+// Final arg-max over the job tiles of either form: where there were steps, the winner's atom count becomes its
+// boundary, else its atom is searched.
+__global__ __launch_bounds__(256) void k_range_reduce(int n_gaps, int step_tiles, int range_tiles, const SelPartial *__restrict__ part,
+                                                      const int32_t *__restrict__ plan, const int32_t *__restrict__ gap_w,
+                                                      const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
+                                                      const int2 *__restrict__ atom_dp, const int2 *__restrict__ atom_db,
+                                                      const int32_t *__restrict__ n_atoms, int32_t *__restrict__ cand_job,
+                                                      int32_t *__restrict__ cand_cut, int64_t *__restrict__ cand_score)
+{
+    const bool ranges = plan[kPlanTabled] != 0;
+    int g, bj, ba;
+    unsigned long long bh;
+    if (!reduce_tiles(n_gaps, ranges ? range_tiles : step_tiles, part, g, bh, bj, ba)) return;
+    if (bh && ranges) {
+        const int w = gap_w[ba], c = gap_c[ba];         // (the partial has the gap's position)
+        const int2 *dp = atom_dp + seg_off[bj];
+        int lo = 0, hi = n_atoms[bj];
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            const int2 v = dp[mid];
+            if (v.x <= w && v.y <= c) lo = mid + 1; else hi = mid;
+        }
+        ba = lo;
+    }
     cand_job[g] = bh ? bj : -1;
     cand_cut[g] = bh ? atom_db[seg_off[bj] + ba - 1].y : -1;
     cand_score[g] = bh ? int64_t((bh - 1ull) & ((1ull << 62) - 1ull)) : 0;

@@ -91,6 +91,15 @@ const long long *pre_area_of(const sja_ctx *ctx, const Layout &L)
     return ctx->score_used == SJA_SCORE_AREA ? reinterpret_cast<const long long *>(ctx->ws + L.pre_area) : nullptr;
 }
 
+// Whether the keys never fall along a job's atoms: under the hysteresis rule a longer fit can end in a shorter cut if
+// its minimum gain is above the distance of two capacities.
+bool keys_rise(const sja_ctx *ctx)
+{
+    for (int i = 1; i < ctx->hyst_used_n_caps; ++i)
+        if (int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] < ctx->hyst_used_min_gain) return false;
+    return true;
+}
+
 int check_params(sja_ctx *ctx, const sja_params *p, const int32_t *wait, const uint8_t *sla_class)
 {
     if (!p) return fail(ctx, SJA_ERR_NULL, "params");
@@ -404,10 +413,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     // that never fall along a job's atoms (a minimum gain above the distance of two capacities of the
     // hysteresis set can let a longer fit end in a shorter cut); and more than a few rounds to go, which cost no
     // more launched than the block needs to start and report (20 us of a Medium batch, 200 at 630 list blocks)
-    bool rising = true;
-    for (int i = 1; i < ctx->hyst_used_n_caps; ++i)
-        rising = rising && int64_t(ctx->hyst_used_cap[i]) - ctx->hyst_used_cap[i - 1] >= ctx->hyst_used_min_gain;
-    const bool solo_fits = use_held && !wide_records && rising && n_subs <= kSoloMaxBlocks;
+    const bool solo_fits = use_held && !wide_records && keys_rise(ctx) && n_subs <= kSoloMaxBlocks;
     const bool long_lists = n_entries >= int64_t(kFirstLong) * n_subs;
     const int solo_few = kSoloFewRounds + n_subs / kSoloBlocksPerRound;
     const int solo_first = n_subs <= kSoloFewBlocks ? kSoloFirstFew : kSoloFirstMany;
@@ -757,6 +763,7 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
 {
     const int J = ctx->n_jobs;
     const int job_tiles = (J + kFusedBlock - 1) / kFusedBlock;
+    int range_tiles = 0;
     if (job_tiles > 0 && searched) {
         const bool mixed = params->policy == SJA_POLICY_MIXED;
         const long long *atom_area = atom_area_of(ctx, L);
@@ -783,7 +790,23 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
                                        : k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, false, false>);
         int rc = timed ? mark_kernel(ctx, st, false) : SJA_OK;
         if (rc != SJA_OK) return rc;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, to_dev(params),
+        const bool ranges = keys_rise(ctx);
+        if (ranges) {
+            const int64_t jobs_once = (J + kRangeThreads - 1) / kRangeThreads, chunks = (n_gaps + fit_chunk_len(n_gaps, J) - 1) / fit_chunk_len(n_gaps, J);
+            int batches = 1;
+            while (batches < kRangeBatches && jobs_once * chunks >= 2 * batches * int64_t(kRangeBlocks)) batches *= 2;
+            range_tiles = int((jobs_once + batches - 1) / batches);
+            auto range_kern = atom_area ? (mixed ? k_range_select<true, true> : k_range_select<false, true>)
+                                        : (mixed ? k_range_select<true, false> : k_range_select<false, false>);
+            hipLaunchKernelGGL(range_kern, dim3(unsigned((range_tiles + 7) / 8 * 8) * unsigned(chunk_bound)), dim3(kRangeThreads), 0, st, J, n_gaps,
+                               chunk_bound, batches, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area,
+                               ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin), ws_ptr<int32_t>(ctx, L.chunk_end),
+                               ws_ptr<int32_t>(ctx, L.chunk_class), ws_ptr<int32_t>(ctx, L.start_tab), ws_ptr<int32_t>(ctx, L.ncap_tab),
+                               ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active,
+                               ws_ptr<SelPartial>(ctx, L.sel_part));
+            SJA_HIP(hipGetLastError(), "k_range_select launch");
+        }
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, int(ranges), to_dev(params),
                            ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
                            ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin),
                            ws_ptr<int32_t>(ctx, L.chunk_end), ws_ptr<int32_t>(ctx, L.chunk_class),
@@ -794,6 +817,14 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
                            ws_ptr<SelPartial>(ctx, L.sel_part));
         SJA_HIP(hipGetLastError(), "k_fit_select launch");
         if (timed && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
+    }
+    if (range_tiles > 0) {
+        hipLaunchKernelGGL(k_range_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles, range_tiles,
+                           ws_ptr<SelPartial>(ctx, L.sel_part), ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.gap_w),
+                           ws_ptr<int32_t>(ctx, L.gap_c), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), ws_ptr<int2>(ctx, L.atom_db),
+                           ws_ptr<int32_t>(ctx, L.n_atoms), cand_job, cand_cut, cand_score);
+        SJA_HIP(hipGetLastError(), "k_range_reduce launch");
+        return SJA_OK;
     }
     hipLaunchKernelGGL(k_fused_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_db), cand_job,
