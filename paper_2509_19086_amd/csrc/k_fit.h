@@ -39,13 +39,16 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
 }
 
 // Rank of every gap in the order (C, W, index), in two steps: tiles of
-// kGapTile gaps are sorted in LDS (runs merged by binary search, the tile's gaps
-// padded to a power of two only: 12 merges of a full tile where a bitonic network
-// had 78 exchanges with a barrier each, 46 us whatever the gaps), then every gap
+// kGapTile gaps are sorted in LDS (runs merged by binary search, an element per
+// thread, the tile padded to a power of two only), then every gap
 // adds up, over all tiles, how many pairs of the tile precede its own (a binary
-// search in the tile, staged in LDS; its position, inside its own tile).
-constexpr int kGapSortThreads = 1024;
-constexpr int kGapRankBlock = 256;
+// search in the tile, staged in LDS; its position, inside its own tile).  Both are
+// chains of LDS reads: tiles of 1024 have 55 of them in a row where tiles of
+// 4096, four elements a thread, had 90 (28 -> 12 us at 2048 gaps, 47 -> 11 from 4096 on); the four times as
+// many tiles are shared by kGapRankGroups groups of threads per entry (32768 gaps: 28 -> 19 us).
+constexpr int kGapSortThreads = kGapTile;
+constexpr int kGapRankBlock = 256, kGapRankGroups = 4;
+static_assert(kGapTile % kGapRankBlock == 0 && kGapRoom % kGapTile == 0, "tiles");
 
 __device__ __forceinline__ bool gap_pair_less(unsigned long long ka, int ia, unsigned long long kb, int ib)
 {
@@ -58,67 +61,46 @@ __global__ __launch_bounds__(kGapSortThreads) void k_gap_tile_sort(int n_gaps, c
                                                                    int32_t *__restrict__ tile_idx, int32_t *plan,
                                                                    int32_t *class_dmax)
 {
-    constexpr int PER = kGapTile / kGapSortThreads;
     __shared__ unsigned long long s_key[2][kGapTile];
     __shared__ uint16_t s_idx[2][kGapTile];
+    const int i = threadIdx.x;
     if (blockIdx.x == 0) {     // counters that later kernels of the sequence add to
-        if (threadIdx.x == 0) plan[kPlanMarks] = 0;
-        if (threadIdx.x < kMaxClasses) class_dmax[threadIdx.x] = INT32_MIN;
+        if (i == 0) plan[kPlanMarks] = 0;
+        if (i < kMaxClasses) class_dmax[i] = INT32_MIN;
     }
     const int base = blockIdx.x * kGapTile, count = min(kGapTile, n_gaps - base);
     int m = 1;                  // the power of two that is sorted
     while (m < count) m <<= 1;
-    for (int i = threadIdx.x; i < m; i += kGapSortThreads) {
-        s_key[0][i] = i < count ? gap_key(W[base + i], C[base + i]) : ~0ull;      // padding stays behind every gap: the merges are stable
-        s_idx[0][i] = uint16_t(i);
-    }
-    __syncthreads();
+    unsigned long long key = i < count ? gap_key(W[base + i], C[base + i]) : ~0ull;      // padding stays behind every gap: the merges are stable
+    int idx = i, at = i;
     int cur = 0;
     for (int len = 1; len < m; len <<= 1, cur ^= 1) {
         // every element's place in the merged run: its own place plus the elements of the neighbouring run before it
-        unsigned long long key[PER];
-        int lo[PER], hi[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int i = threadIdx.x + q * kGapSortThreads;
-            key[q] = i < m ? s_key[cur][i] : 0ull;
-            lo[q] = 0;
-            hi[q] = i < m ? len : 0;
-        }
-        for (int step = len; step > 0; step >>= 1) {
-#pragma unroll
-            for (int q = 0; q < PER; ++q) {
-                const int i = threadIdx.x + q * kGapSortThreads;
-                if (lo[q] < hi[q]) {
-                    const int mid = (lo[q] + hi[q]) >> 1;
-                    const unsigned long long k = s_key[cur][((i ^ len) & ~(len - 1)) + mid];
-                    const bool before = (i & len) ? k <= key[q] : k < key[q];
-                    if (before) lo[q] = mid + 1; else hi[q] = mid;
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int i = threadIdx.x + q * kGapSortThreads;
-            if (i < m) {
-                const int to = (i & ~(2 * len - 1)) + (i & (len - 1)) + lo[q];
-                s_key[cur ^ 1][to] = key[q];
-                s_idx[cur ^ 1][to] = s_idx[cur][i];
-            }
-        }
+        if (at < m) { s_key[cur][at] = key; s_idx[cur][at] = uint16_t(idx); }
         __syncthreads();
+        if (i < m) {
+            key = s_key[cur][i];
+            idx = s_idx[cur][i];
+            const unsigned long long *other = &s_key[cur][(i ^ len) & ~(len - 1)];
+            int lo = 0;
+            // (the run has a power of two of elements: the place among them bit by bit)
+            auto before = [&](unsigned long long k) { return (i & len) ? k <= key : k < key; };
+            for (int step = len; step > 0; step >>= 1)
+                if (lo + step <= len && before(other[lo + step - 1])) lo += step;
+            at = (i & ~(2 * len - 1)) + (i & (len - 1)) + lo;
+        }
     }
-    for (int i = threadIdx.x; i < kGapTile; i += kGapSortThreads) {
-        const int from = i < m ? s_idx[cur][i] : count;
-        tile_key[base + i] = i < m ? s_key[cur][i] : ~0ull;
-        tile_idx[base + i] = from < count ? base + from : INT32_MAX;
-    }
+    if (at < m && m > 1) { s_key[cur][at] = key; s_idx[cur][at] = uint16_t(idx); }
+    __syncthreads();
+    if (m > 1 && i < m) { key = s_key[cur][i]; idx = s_idx[cur][i]; }
+    tile_key[base + i] = i < m ? key : ~0ull;
+    tile_idx[base + i] = i < m && idx < count ? base + idx : INT32_MAX;
 }
 
-// One thread per entry of the sorted tiles.  rank[g] = number of gaps that precede g; the
-// gap's window, capacity, index and the element offset of its cut row go to that position of
+// kGapRankGroups threads per entry of the sorted tiles, each with its share of the tiles.  rank[g] = number of gaps that
+// precede g; the gap's window, capacity, index and the element offset of its cut row go to that position of
 // the sorted copies.
-__global__ __launch_bounds__(kGapRankBlock) void k_gap_rank(int n_gaps, int n_jobs, int n_tiles,
+__global__ __launch_bounds__(kGapRankBlock * kGapRankGroups) void k_gap_rank(int n_gaps, int n_jobs, int n_tiles,
                                                             const unsigned long long *__restrict__ tile_key,
                                                             const int32_t *__restrict__ tile_idx,
                                                             const int32_t *__restrict__ W,
@@ -127,35 +109,47 @@ __global__ __launch_bounds__(kGapRankBlock) void k_gap_rank(int n_gaps, int n_jo
                                                             int32_t *__restrict__ ws, int32_t *__restrict__ cs,
                                                             int64_t *__restrict__ row)
 {
-    __shared__ unsigned long long s_key[kGapTile];
-    __shared__ int s_idx[kGapTile];
-    const int e = blockIdx.x * kGapRankBlock + threadIdx.x;       // entry of the sorted tiles
-    const int own = e / kGapTile;
+    __shared__ unsigned long long s_key[kGapRankGroups][kGapTile];
+    __shared__ int s_idx[kGapRankGroups][kGapTile];
+    __shared__ int s_before[kGapRankGroups][kGapRankBlock];
+    const int tid = threadIdx.x % kGapRankBlock, group = threadIdx.x / kGapRankBlock;
+    const int e = blockIdx.x * kGapRankBlock + tid;                // entry of the sorted tiles
+    const int own = e / kGapTile;                                  // (the same over the block)
     const unsigned long long key = tile_key[e];
     const int idx = tile_idx[e];
-    int r = e - own * kGapTile;                                    // pairs of its own tile before it
-    for (int t = 0; t < n_tiles; ++t) {
-        if (t == own) continue;                                    // uniform over the block: kGapTile % kGapRankBlock == 0
+    int r = 0;
+    for (int t0 = 0; t0 < n_tiles; t0 += kGapRankGroups) {
+        const int t = t0 + group;
+        const bool there = t < n_tiles && t != own;                // uniform over the group
         __syncthreads();
-        for (int i = threadIdx.x; i < kGapTile; i += kGapRankBlock) {
-            s_key[i] = tile_key[t * kGapTile + i];
-            s_idx[i] = tile_idx[t * kGapTile + i];
+        if (there) {
+#pragma unroll
+            for (int i = tid; i < kGapTile; i += kGapRankBlock) {
+                s_key[group][i] = tile_key[t * kGapTile + i];
+                s_idx[group][i] = tile_idx[t * kGapTile + i];
+            }
         }
         __syncthreads();
-        int lo = 0, hi = kGapTile;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (gap_pair_less(s_key[mid], s_idx[mid], key, idx)) lo = mid + 1; else hi = mid;
+        if (there) {
+            int lo = 0, hi = kGapTile;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (gap_pair_less(s_key[group][mid], s_idx[group][mid], key, idx)) lo = mid + 1; else hi = mid;
+            }
+            r += lo;
         }
-        r += lo;
     }
-    if (idx < n_gaps) {
-        rank[idx] = r;
-        order[r] = idx;
-        ws[r] = W[idx];
-        cs[r] = C[idx];
-        row[r] = int64_t(idx) * n_jobs;
-    }
+    s_before[group][tid] = r;
+    __syncthreads();
+    if (group > 0 || idx >= n_gaps) return;
+    r = e - own * kGapTile;                                        // pairs of its own tile before it
+#pragma unroll
+    for (int v = 0; v < kGapRankGroups; ++v) r += s_before[v][tid];
+    rank[idx] = r;
+    order[r] = idx;
+    ws[r] = W[idx];
+    cs[r] = C[idx];
+    row[r] = int64_t(idx) * n_jobs;
 }
 
 // Capacity classes = runs of equal C in the sorted order.  k_gap_marks appends the

@@ -623,7 +623,7 @@ int enqueue_gap_plan(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_ga
     hipLaunchKernelGGL(k_gap_tile_sort, dim3(gap_tiles), dim3(kGapSortThreads), 0, st, n_gaps, W, C, tile_key, tile_idx,
                        plan, ws_ptr<int32_t>(ctx, L.class_dmax));
     SJA_HIP(hipGetLastError(), "k_gap_tile_sort launch");
-    hipLaunchKernelGGL(k_gap_rank, dim3(gap_tiles * (kGapTile / kGapRankBlock)), dim3(kGapRankBlock), 0, st, n_gaps, J,
+    hipLaunchKernelGGL(k_gap_rank, dim3(gap_tiles * (kGapTile / kGapRankBlock)), dim3(kGapRankBlock * kGapRankGroups), 0, st, n_gaps, J,
                        gap_tiles, tile_key, tile_idx, W, C, rank, ws_ptr<int32_t>(ctx, L.gap_order), gw, gcap,
                        ws_ptr<int64_t>(ctx, L.gap_row));
     SJA_HIP(hipGetLastError(), "k_gap_rank launch");

@@ -21,7 +21,8 @@ constexpr int kFitPeriod = 32;        // steps between window top-ups (multiple 
 constexpr int kMaxClasses = 64;       // distinct capacities served by the table-driven path
 constexpr int kSelBlock = 256;        // threads per select block, one job per thread
 constexpr int kSelGapChunk = 64;      // sorted gap positions walked by one select block
-constexpr int kGapTile = 4096;        // gaps sorted together in LDS when the gaps are ordered
+constexpr int kGapTile = 1024;        // gaps sorted together in LDS when the gaps are ordered
+constexpr int kGapRoom = 4096;        // the sorted tiles have room for a multiple of so many gaps (other tables move in later)
 constexpr int kListSplits = 40;       // most pieces one capacity class's small windows are split into
 
 // One partial arg-max per (job tile, gap): 32 bytes.
@@ -43,7 +44,7 @@ struct Layout {
     size_t first_dp;                       // [J] int2: a job's first atom (duration, peak), INT32_MAX twice if none
     size_t atom_area, pre_area;            // area score only: int64 area under the envelope per atom / per segment
     size_t gap_rank, gap_order;            // [G] int32
-    size_t gap_tile_key, gap_tile_idx;     // [ceil(G / kGapTile) * kGapTile] uint64 / int32: gaps sorted tile by tile
+    size_t gap_tile_key, gap_tile_idx;     // [ceil(G / kGapRoom) * kGapRoom] uint64 / int32: gaps sorted tile by tile
     size_t gap_w, gap_c, gap_run_end;      // [G+16] int32, in sorted order
     size_t gap_cls;                        // [G+16] int32: capacity class of a sorted position
     size_t bits_table;                     // [kMaxClasses * ceil(J/32)] uint32: per class and job word, the jobs whose first atom fits the capacity
@@ -131,9 +132,9 @@ inline Layout make_layout(int64_t G, int64_t J, int64_t S)
     L.pre_area = take(size_t(S + 8) * 8);
     L.gap_rank = take(size_t(G) * 4);
     L.gap_order = take(size_t(G) * 4);
-    const size_t gap_tiles = size_t((G + kGapTile - 1) / kGapTile);
-    L.gap_tile_key = take(gap_tiles * kGapTile * 8);
-    L.gap_tile_idx = take(gap_tiles * kGapTile * 4);
+    const size_t gap_room = size_t((G + kGapRoom - 1) / kGapRoom) * kGapRoom;
+    L.gap_tile_key = take(gap_room * 8);
+    L.gap_tile_idx = take(gap_room * 4);
     L.gap_w = take(size_t(G + 16) * 4);
     L.gap_c = take(size_t(G + 16) * 4);
     L.gap_run_end = take(size_t(G + 16) * 4);
