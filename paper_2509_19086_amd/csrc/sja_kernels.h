@@ -193,14 +193,15 @@ __device__ __forceinline__ void hysteresis_remap(const Hysteresis &h, int lane, 
 }
 
 // After prepare_job / prepare_job_wide of the same wave: make the wave's own atom
-// stores visible to its other lanes, then apply the rule.
+// stores visible to its other lanes (they share its compute unit's cache; a fence for the whole
+// GPU writes a level-2 cache back, wave after wave: 219 us against 26 for 6151 jobs), then apply the rule.
 __device__ __forceinline__ void hysteresis_after_prepare(const Hysteresis &h, int j, int lane, int64_t base,
                                                          const int2 *atom_dp, int2 *atom_db,
                                                          const int32_t *n_atoms, long long *atom_f,
                                                          bool f_is_area)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     const int count = n_atoms[j];
     hysteresis_remap(h, lane, base, count, atom_dp, atom_db, atom_f, f_is_area);
 }
