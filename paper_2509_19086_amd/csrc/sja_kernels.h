@@ -321,9 +321,17 @@ __device__ __forceinline__ void prepare_job(
 // consecutive segments per lane: 256 segments per step, 16-byte loads and stores,
 // a lane-local scan of its four values plus one wave scan of the lane totals.  With
 // one segment per lane a step is a memory trip for 64 segments, and the trips,
-// not the bytes, bound the kernel.
-struct __attribute__((packed, aligned(4))) Int4U {      // a 16-byte group of ints at any 4-byte boundary
-    int v[4];
+// not the bytes, bound the kernel.  The tables go past the caches' usual order (65536 jobs, 67 million
+// segments, half of them left: 250 -> 231 us, 3.7 TB/s; the profiles' loads too: 244, these alone 271).
+typedef int Int4U __attribute__((ext_vector_type(4), aligned(4)));       // a 16-byte group of ints at any 4-byte boundary
+
+constexpr int kWidePer = 4;
+// A step's atoms are put next to each other in LDS, a row per wave, and leave from there a lane each: straight from the
+// lanes that found them they took as many cache lines as all other stores together (where the tables do not wait for
+// memory 213 -> 190 us).
+struct WideAtoms {
+    int2 dp[kWidePer * kWave];
+    int b[kWidePer * kWave];
 };
 
 __device__ __forceinline__ void prepare_job_wide(
@@ -331,42 +339,45 @@ __device__ __forceinline__ void prepare_job_wide(
     const int32_t *__restrict__ mem, const uint8_t *__restrict__ safe, int32_t *__restrict__ pre_dur,
     int32_t *__restrict__ pre_peak, int32_t *__restrict__ prev_safe,
     int2 *__restrict__ atom_dp, int2 *__restrict__ atom_db, int32_t *__restrict__ n_atoms,
-    int2 *__restrict__ first_dp)
+    int2 *__restrict__ first_dp, WideAtoms &s_atoms)
 {
-    constexpr int PER = 4, STEP = PER * kWave;
+    constexpr int PER = kWidePer, STEP = PER * kWave;
     int carry_sum = 0, carry_peak = INT32_MIN, carry_last = -1, count = 0;
     int first_d = INT32_MAX, first_p = INT32_MAX;
     int nd[PER], nm[PER];
     uint32_t nf = 0;
     auto fetch = [&](int k0) {
         const int k = k0 + PER * lane;
-        if (k + PER <= L) {
+        if (k >= p && k + PER <= L) {
             const Int4U d4 = *reinterpret_cast<const Int4U *>(dur + base + k);
             const Int4U m4 = *reinterpret_cast<const Int4U *>(mem + base + k);
             uint32_t f4;
             __builtin_memcpy(&f4, safe + base + k, 4);
 #pragma unroll
-            for (int i = 0; i < PER; ++i) { nd[i] = d4.v[i]; nm[i] = m4.v[i]; }
+            for (int i = 0; i < PER; ++i) { nd[i] = d4[i]; nm[i] = m4[i]; }
             nf = f4;
         } else {
             nf = 0;
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
-                const bool in = k + i < L;
+                const bool in = k + i >= p && k + i < L;
                 nd[i] = in ? dur[base + k + i] : 0;
                 nm[i] = in ? mem[base + k + i] : INT32_MIN;
                 nf |= (in && safe[base + k + i] != 0 ? 1u : 0u) << (8 * i);
             }
         }
     };
-    fetch(p);
-    for (int k0 = p; k0 < L; k0 += STEP) {
+    // from a multiple of four segments on, before p if need be: groups of 16 bytes that lie across two cache lines take
+    // longer (32768 jobs of 1024 segments: 96 -> 84 us)
+    const int begin = p - int((base + p) & (PER - 1));
+    if (p < L) fetch(begin);
+    for (int k0 = begin; k0 < L && p < L; k0 += STEP) {
         const int k = k0 + PER * lane;
         int s[PER], m[PER], l[PER];
         bool flag[PER];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const bool valid = k + i < L;
+            const bool valid = k + i >= p && k + i < L;
             flag[i] = valid && (((nf >> (8 * i)) & 0xffu) != 0 || k + i + 1 == L);
             s[i] = valid ? nd[i] : 0;
             m[i] = valid ? nm[i] : INT32_MIN;
@@ -396,21 +407,21 @@ __device__ __forceinline__ void prepare_job_wide(
             l[i] = max(l[i], el);
             nflag += flag[i] ? 1 : 0;
         }
-        if (k + PER <= L) {
+        if (k >= p && k + PER <= L) {
             Int4U o;
 #pragma unroll
-            for (int i = 0; i < PER; ++i) o.v[i] = s[i];
-            *reinterpret_cast<Int4U *>(pre_dur + base + k) = o;
+            for (int i = 0; i < PER; ++i) o[i] = s[i];
+            __builtin_nontemporal_store(o, reinterpret_cast<Int4U *>(pre_dur + base + k));
 #pragma unroll
-            for (int i = 0; i < PER; ++i) o.v[i] = m[i];
-            *reinterpret_cast<Int4U *>(pre_peak + base + k) = o;
+            for (int i = 0; i < PER; ++i) o[i] = m[i];
+            __builtin_nontemporal_store(o, reinterpret_cast<Int4U *>(pre_peak + base + k));
 #pragma unroll
-            for (int i = 0; i < PER; ++i) o.v[i] = l[i];
-            *reinterpret_cast<Int4U *>(prev_safe + base + k) = o;
+            for (int i = 0; i < PER; ++i) o[i] = l[i];
+            __builtin_nontemporal_store(o, reinterpret_cast<Int4U *>(prev_safe + base + k));
         } else {
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
-                if (k + i < L) {
+                if (k + i >= p && k + i < L) {
                     pre_dur[base + k + i] = s[i];
                     pre_peak[base + k + i] = m[i];
                     prev_safe[base + k + i] = l[i];
@@ -420,7 +431,7 @@ __device__ __forceinline__ void prepare_job_wide(
         // atoms: the flagged boundaries, compacted in order
         const int incl = wave_scan_add(nflag);
         const int total = lane_value(incl, kWave - 1);
-        int idx = count + incl - nflag;
+        int idx = incl - nflag;
         if (count == 0 && total > 0) {
             // the first atom of the job: the lowest lane with a flag, its first flagged value
             const unsigned long long has = __ballot(nflag > 0);
@@ -436,11 +447,18 @@ __device__ __forceinline__ void prepare_job_wide(
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             if (flag[i]) {
-                atom_dp[base + idx] = make_int2(s[i], m[i]);
-                atom_db[base + idx] = make_int2(s[i], k + i + 1);
+                s_atoms.dp[idx] = make_int2(s[i], m[i]);
+                s_atoms.b[idx] = k + i + 1;
                 ++idx;
             }
         }
+        asm volatile("" ::: "memory");          // (the wave's lanes write before one of them reads)
+        for (int i = lane; i < total; i += kWave) {
+            const int2 v = s_atoms.dp[i];
+            atom_dp[base + count + i] = v;
+            atom_db[base + count + i] = make_int2(v.x, s_atoms.b[i]);
+        }
+        asm volatile("" ::: "memory");
         count += total;
         carry_sum += tot_s;
         carry_peak = max(carry_peak, tot_m);
@@ -461,6 +479,7 @@ __global__ __launch_bounds__(256) void k_prepare(
     int2 *__restrict__ atom_dp, int2 *__restrict__ atom_db, int32_t *__restrict__ n_atoms,
     int2 *__restrict__ first_dp)
 {
+    __shared__ WideAtoms s_atoms[256 / kWave];
     const int lane = lane_id();
     const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
     if (j >= n_jobs) return;
@@ -469,7 +488,8 @@ __global__ __launch_bounds__(256) void k_prepare(
     int p = progress[j];
     p = p < 0 ? 0 : (p > L ? L : p);
     if (!LIMITED && !pre_area)
-        prepare_job_wide(j, lane, base, L, p, dur, mem, safe, pre_dur, pre_peak, prev_safe, atom_dp, atom_db, n_atoms, first_dp);
+        prepare_job_wide(j, lane, base, L, p, dur, mem, safe, pre_dur, pre_peak, prev_safe, atom_dp, atom_db, n_atoms, first_dp,
+                         s_atoms[threadIdx.x / kWave]);
     else
         prepare_job<LIMITED>(lim, pre_area, pre_area ? atom_area : nullptr, j, lane, base, L, p, dur, mem, safe, pre_dur, pre_peak, prev_safe, atom_dp,
                              atom_db, n_atoms, first_dp);
@@ -594,6 +614,7 @@ __global__ __launch_bounds__(256) void k_advance_jobs(
     int32_t *__restrict__ n_atoms, int2 *__restrict__ first_dp, unsigned long long *__restrict__ metrics)
 {
     __shared__ int s_done[256 / kWave];
+    __shared__ WideAtoms s_atoms[256 / kWave];
     const int lane = lane_id();
     const int wave = threadIdx.x / kWave;
     const int j = blockIdx.x * (blockDim.x / kWave) + wave;
@@ -608,7 +629,7 @@ __global__ __launch_bounds__(256) void k_advance_jobs(
             p = cut;
             if (!LIMITED && !pre_area)
                 prepare_job_wide(j, lane, base, L, p, dur, mem, safe, pre_dur, pre_peak, prev_safe, atom_dp, atom_db, n_atoms,
-                                 first_dp);
+                                 first_dp, s_atoms[wave]);
             else
                 prepare_job<LIMITED>(lim, pre_area, pre_area ? atom_area : nullptr, j, lane, base, L, p, dur, mem, safe, pre_dur, pre_peak, prev_safe,
                                      atom_dp, atom_db, n_atoms, first_dp);
