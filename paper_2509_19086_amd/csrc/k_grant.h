@@ -96,13 +96,24 @@ __global__ void k_reach(int n_jobs, const int32_t *__restrict__ plan, const int3
     reach[j] = r;
 }
 
+// The leading 32 bits of a key as they matter: tier, exponent and the leading bits of the score, which grow with
+// the key.  Scores spread over tens of octaves, so a byte of this orders more than a byte of the key.
+__device__ __forceinline__ uint32_t key_digest(const PolicyDev &pol, unsigned long long tier, unsigned long long score)
+{
+    const int tier_bits = pol.policy == SJA_POLICY_MIXED ? 2 : pol.policy == SJA_POLICY_SLA ? 1 : 0, rest = 26 - tier_bits;
+    const int e = score ? 63 - __clzll((long long)score) : 0;
+    const unsigned long long mantissa = e ? score << (64 - e) : 0ull;
+    return (tier_bits ? uint32_t(tier) << (32 - tier_bits) : 0u) | (uint32_t(e) << rest) | uint32_t(mantissa >> (64 - rest));
+}
+
 // One wave per job: inverted policy keys of its reachable atoms (ascending sort
-// of the inverted key = descending key) and the identity permutation.
+// of the inverted key = descending key) and the identity permutation, and both as one word: inverted digest : atom.
 __global__ __launch_bounds__(256) void k_atom_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ abase, const int32_t *__restrict__ wait,
     const uint8_t *__restrict__ sla_class, unsigned long long *__restrict__ key_hi,
-    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm, int4 *__restrict__ info, unsigned long long *bits)
+    unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm, int4 *__restrict__ info, unsigned long long *__restrict__ digest,
+    unsigned long long *bits)
 {
     __shared__ unsigned long long s_bits[2][256 / kWave];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -120,6 +131,7 @@ __global__ __launch_bounds__(256) void k_atom_keys(
                                                    : (unsigned long long)v.x * (unsigned long long)v.y;
             const unsigned long long k = (tier << 62) | (F * mult);
             key_hi[a0 + a] = ~k;
+            digest[a0 + a] = (static_cast<unsigned long long>(~key_digest(pol, tier, F * mult)) << 32) | uint32_t(a0 + a);
             any_hi |= k;
             if (mixed) {
                 key_lo[a0 + a] = ~F;

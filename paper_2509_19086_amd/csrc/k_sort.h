@@ -457,6 +457,76 @@ __global__ __launch_bounds__(256) void k_fix_ties(const int32_t *n_ptr, const un
     }
 }
 
+// Items in the order of their digests (the upper bits of `items`, from `shift` on; their ids in the lower 32): puts
+// those of equal digests in the order of their keys, then second keys (MIXED), then as they stand, and writes
+// the ids.  The first one's thread serves a run, all of its keys asked for together if they are at most kRunNear;
+// a run of more than kTieRun that is out of order sets *flag.
+constexpr int kRunNear = 8;
+
+template <bool MIXED>
+__global__ __launch_bounds__(256) void k_fix_runs(const int32_t *n_ptr, const unsigned long long *__restrict__ items, int shift,
+                                                  const unsigned long long *__restrict__ keys, const unsigned long long *__restrict__ second,
+                                                  uint32_t *perm, int32_t *flag)
+{
+    const int64_t n = *n_ptr, i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const unsigned long long digest = items[i] >> shift;
+    const uint32_t id = uint32_t(items[i]);
+    auto same = [&](int64_t k) { return items[k] >> shift == digest; };
+    auto less = [&](unsigned long long ka, unsigned long long sa, unsigned long long kb, unsigned long long sb) { return ka < kb || (MIXED && ka == kb && sa < sb); };
+    auto before = [&](uint32_t a, uint32_t b) { return less(keys[a], MIXED ? second[a] : 0ull, keys[b], MIXED ? second[b] : 0ull); };
+    if (i > 0 && same(i - 1)) {
+        if (i > kTieRun && same(i - kTieRun - 1)) {             // beyond the part that the first one's thread looks at
+            perm[i] = id;
+            if (before(id, uint32_t(items[i - 1]))) *flag = 1;
+        }
+        return;
+    }
+    if (i + 1 >= n || !same(i + 1)) { perm[i] = id; return; }
+    uint32_t ids[kRunNear];
+    int run = 1;
+#pragma unroll
+    for (int k = 0; k < kRunNear; ++k) {
+        const unsigned long long v = items[i + k < n ? i + k : n - 1];
+        ids[k] = uint32_t(v);
+        if (run == k && i + k < n && v >> shift == digest) ++run;
+    }
+    if (run < kRunNear || i + run >= n || !same(i + run)) {
+        unsigned long long key[kRunNear], sec[kRunNear];
+#pragma unroll
+        for (int k = 0; k < kRunNear; ++k) {
+            key[k] = k < run ? keys[ids[k]] : ~0ull;
+            sec[k] = MIXED && k < run ? second[ids[k]] : ~0ull;
+        }
+#pragma unroll
+        for (int k = 0; k < kRunNear; ++k) {
+            int rank = 0;
+#pragma unroll
+            for (int l = 0; l < kRunNear; ++l) {
+                if (l < k) rank += l < run && !less(key[k], sec[k], key[l], sec[l]);
+                if (l > k) rank += l < run && less(key[l], sec[l], key[k], sec[k]);
+            }
+            if (k < run) perm[i + rank] = ids[k];
+        }
+        return;
+    }
+    int64_t e = i;
+    bool ordered = true;
+    for (; e < n && e - i <= kTieRun && same(e); ++e) {
+        const uint32_t a = uint32_t(items[e]);
+        perm[e] = a;
+        if (e > i) ordered = ordered && !before(a, uint32_t(items[e - 1]));
+    }
+    if (ordered) return;
+    if (e - i > kTieRun) { *flag = 1; return; }
+    for (int64_t k = i + 1; k < e; ++k) {
+        const uint32_t a = perm[k];
+        int64_t at = k;
+        for (; at > i && before(a, perm[at - 1]); --at) perm[at] = perm[at - 1];
+        perm[at] = a;
+    }
+}
+
 // out[i] = keys[idx[i]]: the keys of a permutation, laid out in its order.
 __global__ void k_gather_keys(const int32_t *n_ptr, const unsigned long long *__restrict__ keys,
                               const uint32_t *__restrict__ idx, unsigned long long *__restrict__ out)
