@@ -143,11 +143,8 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
     const int job_tiles = (J + kSelBlock - 1) / kSelBlock;
     unsigned long long *seg_key = ws_ptr<unsigned long long>(ctx, L.g_key_hi);
     if (job_tiles > 0 && !keys_ready) {
-        const long long *pre_area = pre_area_of(ctx, L);
-        auto kern = pre_area ? k_select_keys<true> : k_select_keys<false>;
-        hipLaunchKernelGGL(kern, dim3((J + 3) / 4), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ctx->pre_dur,
-                           ctx->pre_peak, pre_area, ws_ptr<int32_t>(ctx, L.n_atoms), ws_ptr<int2>(ctx, L.atom_db),
-                           ctx->hyst_used_n_caps > 0, wait, sla_class, seg_key);
+        hipLaunchKernelGGL(k_select_keys, dim3((J + 3) / 4), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
+                           ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class, seg_key);
         SJA_HIP(hipGetLastError(), "k_select_keys launch");
     }
     if (job_tiles > 0) {

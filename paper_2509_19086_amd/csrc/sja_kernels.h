@@ -729,36 +729,27 @@ __global__ __launch_bounds__(256) void k_validate(
 // partial per (job tile, gap); k_select_reduce finishes the arg-max.
 // Key order: hi desc, lo desc, job asc.
 // --------------------------------------------------------------------------
-// The key of every prefix of every job, ((tier << 62) | F * multiplier) + 1, once
+// The key of every cut of every job, ((tier << 62) | F * multiplier) + 1, at the cut's prefix, once
 // per call: the stepping kernel below then fetches a finished key where a job's
 // cut changes instead of (duration, peak) and three 64-bit multiplies per lane.
-// One wave per job; the kernel moves 16 bytes per segment and runs at the rate
-// of a copy (a wave running along four neighbouring jobs as one stretch, so that
-// the shortest jobs fill it, was no faster).  Only prefixes a cut can point at are
-// visited, from a job's first atom to its last: about half of them where jobs are
-// half done (Stress 250 -> 130 us).
-template <bool AREA>
+// One wave per job, lanes along its atoms (from the running tables, for every prefix a cut can lie
+// between, it moved 16 bytes per segment: 8192 gaps x 32768 jobs 74 -> 35 us).
 __global__ __launch_bounds__(256) void k_select_keys(
-    int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int32_t *__restrict__ pre_dur,
-    const int32_t *__restrict__ pre_peak, const long long *__restrict__ pre_area, const int32_t *__restrict__ n_atoms,
-    const int2 *__restrict__ atom_db, bool remapped,
-    const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
-    unsigned long long *__restrict__ seg_key)
+    int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp, const int2 *__restrict__ atom_db,
+    const long long *__restrict__ atom_area, const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
+    const uint8_t *__restrict__ sla_class, unsigned long long *__restrict__ seg_key)
 {
     const int lane = lane_id();
     const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
     if (j >= n_jobs) return;
     const int64_t base = seg_off[j];
     const int n = n_atoms[j];
-    if (n <= 0) return;
-    // boundaries ascend along the atoms; under the hysteresis rule an atom may have an earlier one's boundary,
-    // but the first keeps its own
-    const int first = atom_db[base].y, last = remapped ? int(seg_off[j + 1] - base) : atom_db[base + n - 1].y;
     unsigned long long mult, tier;
     job_policy(pol, wait, sla_class, j, mult, tier);
-    for (int k = first - 1 + lane; k < last; k += kWave) {
-        const unsigned long long F = AREA ? (unsigned long long)pre_area[base + k] : rect_of(pre_dur[base + k], pre_peak[base + k]);
-        seg_key[base + k] = ((tier << 62) | times_mult(F, mult)) + 1ull;
+    for (int a = lane; a < n; a += kWave) {
+        const int2 v = atom_dp[base + a];
+        const unsigned long long F = atom_area ? (unsigned long long)atom_area[base + a] : rect_of(v.x, v.y);
+        seg_key[base + atom_db[base + a].y - 1] = ((tier << 62) | times_mult(F, mult)) + 1ull;
     }
 }
 
