@@ -341,8 +341,9 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         }
         // by the leading bits only, the rest where those are equal, if that takes fewer passes: three in place of six at
         // 2048 gaps x 8192 jobs (tick 1175 -> 1134 us), in place of eight under MIXED (three ticks 4655 -> 4245)
+        // (the hysteresis rule gives many atoms of a job the same cut: long runs of equal keys, and others among them)
         const int passes = n_atoms <= kDigestFew ? 3 : 4;
-        if (!both && __builtin_popcount(bytes_of(bits_hi)) > passes) {
+        if (!both && ctx->hyst_used_n_caps == 0 && __builtin_popcount(bytes_of(bits_hi)) > passes) {
             for (int p = 0; p < passes; ++p) {
                 const int rc = radix_pass(ctx, st, L, counters + 2, n_atoms, 64 - 8 * (passes - p), 8, flip, ekey,
                                           [&](bool few, dim3 tiles, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
