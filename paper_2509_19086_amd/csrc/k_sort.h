@@ -79,39 +79,40 @@ __global__ __launch_bounds__(256) void k_scan_add(int32_t *data, int64_t n, cons
         if (base + i < n) data[base + i] += add;
 }
 
-// The same by one thread block, for scans whose three launches cost more than the work: a thread takes
-// 32 consecutive items a turn.
-constexpr int kScanOneItems = 32, kScanOneMost = 2 * 1024 * kScanOneItems;
+// The same by one thread block, for scans whose three launches cost more than the work: a wave takes up to
+// kScanOneRows rows of 64 items a turn, all of them asked for together (32 consecutive items a thread, every
+// load of it 64 lines for a wave: 19 us for 32768 items, so 8; a tick with three of them 1443 -> 1404).
+constexpr int kScanOneRows = 32, kScanOneMost = 2 * 1024 * kScanOneRows;
 
 __global__ __launch_bounds__(1024) void k_scan_one(int32_t *data, int n, int32_t *total)
 {
     __shared__ int s_sum[1024 / kWave];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     int carry = 0;
-    for (int b0 = 0; b0 < n; b0 += 1024 * kScanOneItems) {
-        const int left = (n - b0 + 1023) / 1024;                       // items per thread of this turn
-        const int each = min(kScanOneItems, (left + 3) / 4 * 4);
-        const int base = b0 + int(threadIdx.x) * each;
-        int v[kScanOneItems];
+    for (int b0 = 0; b0 < n; b0 += 1024 * kScanOneRows) {
+        const int rows = min(kScanOneRows, (n - b0 + 1023) / 1024);
+        const int base = b0 + wave * rows * kWave + lane;
+        int v[kScanOneRows];
+#pragma unroll
+        for (int i = 0; i < kScanOneRows; ++i) v[i] = i < rows && base + i * kWave < n ? data[base + i * kWave] : 0;
         int sum = 0;
 #pragma unroll
-        for (int i = 0; i < kScanOneItems; ++i) {
-            v[i] = i < each && base + i < n ? data[base + i] : 0;
-            sum += v[i];
+        for (int i = 0; i < kScanOneRows; ++i) {
+            if (i >= rows) continue;
+            const int upto = wave_scan_add(v[i]);
+            v[i] = sum + upto - v[i];
+            sum += __builtin_amdgcn_readlane(upto, kWave - 1);
         }
-        const int upto = wave_scan_add(sum);
-        if (lane == kWave - 1) s_sum[wave] = upto;
+        if (lane == 0) s_sum[wave] = sum;
         __syncthreads();
-        int run = carry + upto - sum;
+        int run = carry;
         for (int w = 0; w < 1024 / kWave; ++w) {
             if (w < wave) run += s_sum[w];
             carry += s_sum[w];
         }
 #pragma unroll
-        for (int i = 0; i < kScanOneItems; ++i) {
-            if (i < each && base + i < n) data[base + i] = run;
-            run += v[i];
-        }
+        for (int i = 0; i < kScanOneRows; ++i)
+            if (i < rows && base + i * kWave < n) data[base + i * kWave] = run + v[i];
         __syncthreads();
     }
     if (threadIdx.x == 0 && total) *total = carry;
