@@ -86,3 +86,24 @@ def test_too_many_capacities(engine, oracle):
     wl = make_workload("medium", 9, n_gaps=2500, n_jobs=1200)
     wl.C = np.linspace(3000, 90000, 65).astype(np.int32)[np.arange(2500) % 65]
     fused_check(engine, oracle, wl, policies=[0, 3], resolve=False)
+
+
+@pytest.mark.parametrize("max_rounds", [1, 6])
+def test_scanning_rounds_without_a_matrix(engine, oracle, max_rounds):
+    import paper_2509_19086_amd as P
+    wl = make_workload("medium", 4, n_gaps=1100, n_jobs=2100)
+    t = P.DeviceTick(engine, wl, want_cut=False)
+    t.prepare()
+    par, opar = (m.Params.make(3, wl.wait_scale, wl.sla_weight, wl.class0_override, max_rounds) for m in (P, oracle))
+    t.fit_select(par)
+    pd, pp, _ = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
+    cut, _ = oracle.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W, wl.C, False)
+    want = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
+    try:
+        engine.sja_set_resolve_mode(1)
+        t.resolve(par)
+    finally:
+        engine.sja_set_resolve_mode(0)
+    for x, y in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap), want[:4]):
+        np.testing.assert_array_equal(x.cpu().numpy(), y)
+    assert t.rounds.cpu().tolist() == [want[4], want[5]]
