@@ -8,9 +8,11 @@
 // advances a merge pointer through its job's atoms (staged in an LDS window
 // that is topped up once per period).  Instead of storing the cut, a lane that
 // passes an atom recomputes its key F * weight from the atom's (duration,
-// peak).  Along the sorted positions of a class a job's key never decreases,
-// so the wave's arg-max is a running one: only a key that changed and reaches
-// the wave's best can move it.  After every period the waves of a block
+// peak).  Along the sorted positions of a class a job's key decreases only
+// where the hysteresis rule lets a longer fit end in a shorter cut, so the
+// wave's arg-max is a running one: a key that changed and reaches the wave's
+// best can move it, and a best that falls itself, after which all lanes are
+// compared again.  After every period the waves of a block
 // combine their bests per position and the block leaves one partial per (job
 // tile, gap); k_fused_reduce finishes the arg-max and turns the winning atom
 // into its boundary.
@@ -44,10 +46,11 @@ __device__ __forceinline__ unsigned long long fused_readlane_u64(unsigned long l
 // compiler takes by itself: the stepping loop is bound by latency (1.5 against 2.1 ms).
 // AREA: the key's F is the atom's area under the envelope (a second window of
 // 64-bit values beside the (duration, peak) one) instead of duration x peak.
-// untabled_only: k_range_select serves the batch if its classes have tables.
+// keys_fall: a job's key may fall along the positions (the host's keys_rise); else k_range_select serves the batch
+// if its classes have tables.
 template <int BLOCK, int CAP, int PERIOD, bool MIXED, bool AREA>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fit_select(
-    int n_jobs, int n_gaps, int chunk_bound, int untabled_only, PolicyDev pol, const int64_t *__restrict__ seg_off,
+    int n_jobs, int n_gaps, int chunk_bound, int keys_fall, PolicyDev pol, const int64_t *__restrict__ seg_off,
     const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area,
     const int32_t *__restrict__ n_atoms,
     const int32_t *__restrict__ plan, const int32_t *__restrict__ chunk_begin,
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
     const int chunk = k % chunk_bound;
     if (job_tile * BLOCK >= n_jobs || chunk >= plan[kPlanChunks]) return;
     const bool tabled = plan[kPlanTabled] != 0;
-    if (tabled && untabled_only) return;
+    if (tabled && !keys_fall) return;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const int j_raw = job_tile * BLOCK + tid;
@@ -249,7 +252,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
             } while (__any(adv));
             q_now = q;
             if (changed) key_of(ld, lp);         // once per step, for the last atom passed
-            challenge(changed && key_hi >= best_hi);
+            bool in = changed && key_hi >= best_hi;
+            // the best lane's key fell: any lane may lead now
+            if (keys_fall && __ballot(changed && lane == best_lane && fused_better(best_hi, best_lo, 0, key_hi, key_lo, 0))) {
+                best_hi = best_lo = 0;
+                best_lane = kWave;
+                in = a > 0;
+            }
+            challenge(in);
         }
     };
 

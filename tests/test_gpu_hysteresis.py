@@ -211,3 +211,56 @@ def test_chain_of_ticks_under_hysteresis(engine, oracle):
         assert moved > 100 and shortened > 1000
     finally:
         engine.sja_set_hysteresis(None)
+
+
+@pytest.mark.parametrize("capacities", ["three", "eighty"])
+@pytest.mark.parametrize("area", [False, True])
+def test_best_reply_while_the_best_jobs_key_falls(engine, oracle, capacities, area):
+    """Beyond the sizes that are served pair by pair, with a gain above the distance of two capacities: a job of three
+    atoms with peaks below 10, 12 and 14 gets the first, the second and again the first one's cut as windows grow, so
+    the best job of a run of gaps drops behind others whose keys have not changed."""
+    import torch
+    import paper_2509_19086_amd as P
+    rng = np.random.default_rng(7)
+    wl = make_workload("tiny", 0, n_gaps=1100, n_jobs=700)
+    J, G = 700, 1100
+    wl.seg_off = (3 * np.arange(J + 1)).astype(np.int64)
+    # 24 long jobs, each a quarter longer than the one before, among short ones that keep below the first capacity
+    dur, mem = rng.integers(1, 5, size=(J, 3)), rng.integers(5, 11, size=(J, 3))
+    long = rng.choice(J, size=24, replace=False)
+    dur[long] = np.floor(20 * 1.25 ** np.arange(24)[:, None] * [0.5, 0.4, 0.05])
+    mem[long] = np.stack([rng.integers(9, 11, size=24), rng.integers(11, 13, size=24), rng.integers(13, 15, size=24)], 1)
+    wl.dur, wl.mem = dur.reshape(-1).astype(np.int32), mem.reshape(-1).astype(np.int32)
+    wl.safe, wl.progress = np.ones(3 * J, dtype=np.uint8), np.zeros(J, dtype=np.int32)
+    wl.W = np.floor(5 * 1000.0 ** rng.random(G)).astype(np.int32)
+    wl.C = rng.choice([10, 12, 14, 14, 14] if capacities == "three" else np.arange(10, 90), size=G).astype(np.int32)
+    cap_set, min_gain = [10, 12, 14], 4
+    cut, _ = oracle.fit_hysteresis(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W, wl.C, cap_set, min_gain, None, None, None, False)
+    pd, pp, _ = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
+    pa = oracle.area(wl.seg_off, wl.dur, wl.mem, wl.progress) if area else None
+    widest = np.nonzero(wl.C == wl.C.max())[0]
+    rows = cut[widest[np.argsort(wl.W[widest], kind="stable")]][:, long]
+    assert capacities == "eighty" or (np.diff(rows, axis=0) < 0).any(axis=0).sum() > 20       # the long jobs' cuts fall
+    engine.sja_set_hysteresis(cap_set, min_gain)
+    engine.sja_set_score(1 if area else 0)
+    try:
+        t = P.DeviceTick(engine, wl, want_cut=False)
+        t.prepare()
+        for policy in (0, 1, 2, 3):
+            par, opar = (m.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, 0) for m in (P, oracle))
+            t.fit_select(par)
+            want = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, pre_area=pa)
+            for x, y in zip((t.cand_job, t.cand_cut, t.cand_score), want):
+                np.testing.assert_array_equal(x.cpu().numpy(), y, err_msg=f"policy {policy}")
+            want = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, pre_area=pa)
+            for mode in (0, 1):
+                engine.sja_set_resolve_mode(mode)
+                t.resolve(par)
+                for x, y in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap), want[:4]):
+                    np.testing.assert_array_equal(x.cpu().numpy(), y, err_msg=f"policy {policy} mode {mode}")
+                assert t.rounds.cpu().tolist() == [want[4], want[5]]
+                engine.sja_set_resolve_mode(0)
+    finally:
+        engine.sja_set_resolve_mode(0)
+        engine.sja_set_hysteresis(None)
+        engine.sja_set_score(0)
