@@ -1,5 +1,34 @@
-"""Small random-profile builders shared by the CPU tests (inputs only)."""
+"""Small random-profile builders shared by the CPU tests (inputs only), and the forms in which a batch is served."""
+import contextlib
+import os
+import re
+
 import numpy as np
+
+ORDERED = 2         # SJA_RESOLVE_LISTS_LOOKUP, in force at the fit, keeps small batches with the ordered forms
+
+
+def by_pairs(n_gaps, n_jobs):
+    """Whether a batch fitted in mode 0 is served pair by pair (pairs_batch in sja.hip; its limits are read from k_pairs.h)."""
+    with open(os.path.join(os.path.dirname(__file__), "..", "paper_2509_19086_amd", "csrc", "k_pairs.h")) as f:
+        text = f.read()
+    gaps, jobs, most = (eval(re.search(rf"constexpr int(?:64_t)? {k} = ([0-9 <]+);", text).group(1))
+                        for k in ("kPairsGaps", "kPairsJobs", "kPairsMost"))
+    return n_jobs > 0 and n_gaps <= gaps and n_jobs <= jobs and n_gaps * n_jobs <= most
+
+
+def forms(wl):
+    """The modes in which a test fits a batch: as it comes, and so that the forms of larger batches serve it too."""
+    return (0, ORDERED) if by_pairs(len(wl.W), len(wl.seg_off) - 1) else (0,)
+
+
+@contextlib.contextmanager
+def in_mode(engine, mode):
+    engine.sja_set_resolve_mode(mode)
+    try:
+        yield
+    finally:
+        engine.sja_set_resolve_mode(0)
 
 
 def random_jobs(rng, n_jobs, l_lo, l_hi, *, d_hi=9, m_hi=9, safe_p=0.4, allow_done=True):

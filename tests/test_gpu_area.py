@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from gen import make_gaps, make_workload
+from helpers import forms, in_mode
 
 pytestmark = pytest.mark.gpu
 
@@ -34,30 +35,30 @@ def area_tick_check(engine, oracle, wl, policies, fused):
         for policy in policies:
             par = P.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
             opar = oracle.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
-            if fused:
-                t.fit_select(par)
-            else:
-                t.fit(); t.select(par)
-            torch.cuda.synchronize()
             cj, cc, cs = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, pre_area=pa)
             rj, _, rs = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
             differs = differs or bool((cj != rj).any() or (cs != rs).any())
-            np.testing.assert_array_equal(t.cand_job.cpu().numpy(), cj, err_msg=f"policy {policy}")
-            np.testing.assert_array_equal(t.cand_cut.cpu().numpy(), cc, err_msg=f"policy {policy}")
-            np.testing.assert_array_equal(t.cand_score.cpu().numpy(), cs, err_msg=f"policy {policy}")
             want = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, pre_area=pa)
-            for mode in ((0,) if fused else (0, 1)):
-                try:
-                    engine.sja_set_resolve_mode(mode)
+            for form in forms(wl):
+                for out in (t.cand_job, t.cand_cut, t.cand_score):
+                    out.fill_(-5)
+                with in_mode(engine, form):
+                    if fused:
+                        t.fit_select(par)
+                    else:
+                        t.fit(); t.select(par)
+                torch.cuda.synchronize()
+                for got, x in zip((t.cand_job, t.cand_cut, t.cand_score), (cj, cc, cs)):
+                    np.testing.assert_array_equal(got.cpu().numpy(), x, err_msg=f"form {form} policy {policy}")
+                for mode in ((form,) if fused else (form, 1)):
                     for out in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap):
                         out.fill_(-5)
-                    t.resolve(par)
-                finally:
-                    engine.sja_set_resolve_mode(0)
-                got = (t.grant_job, t.grant_cut, t.grant_score, t.job_gap)
-                for x, y in zip(got, want[:4]):
-                    np.testing.assert_array_equal(x.cpu().numpy(), y, err_msg=f"policy {policy} mode {mode}")
-                assert t.rounds.cpu().tolist() == [want[4], want[5]]
+                    with in_mode(engine, mode):
+                        t.resolve(par)
+                    got = (t.grant_job, t.grant_cut, t.grant_score, t.job_gap)
+                    for x, y in zip(got, want[:4]):
+                        np.testing.assert_array_equal(x.cpu().numpy(), y, err_msg=f"form {form} policy {policy} mode {mode}")
+                    assert t.rounds.cpu().tolist() == [want[4], want[5]]
         return differs
     finally:
         engine.sja_set_score(RECTANGLE)
@@ -77,7 +78,7 @@ def test_area_score_ragged(engine, oracle, fused):
     area_tick_check(engine, oracle, make_workload("medium", 5, n_gaps=1, n_jobs=1), [2], fused)
 
 
-def test_area_score_chain_of_ticks_and_back(engine, oracle):
+def test_area_score_chain_of_ticks_and_back(engine, oracle, form):
     import torch
     import paper_2509_19086_amd as P
     wl = make_workload("small", 8)
@@ -121,7 +122,7 @@ def test_area_score_chain_of_ticks_and_back(engine, oracle):
         engine.sja_set_score(2)
 
 
-def test_area_score_under_admission_limits(engine, oracle):
+def test_area_score_under_admission_limits(engine, oracle, form):
     """Both options at once: atoms filtered by the limits carry their areas along."""
     import torch
     import paper_2509_19086_amd as P

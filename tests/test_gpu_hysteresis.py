@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from gen import make_channels, make_gaps, make_workload
+from helpers import forms, in_mode
 
 pytestmark = pytest.mark.gpu
 
@@ -63,35 +64,35 @@ def hysteresis_tick_check(engine, oracle, wl, which, policies, fused, limits=Fal
         for policy in policies:
             par = P.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
             opar = oracle.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
-            if fused:
-                t.fit_select(par)
-            else:
-                t.fit(); t.select(par)
-            torch.cuda.synchronize()
-            # the caller-visible running tables do not depend on the rule
-            np.testing.assert_array_equal(t.pre_dur.cpu().numpy().astype(np.int64), pd)
-            np.testing.assert_array_equal(t.pre_peak.cpu().numpy().astype(np.int64), pp)
-            np.testing.assert_array_equal(t.prev_safe.cpu().numpy(), ps)
-            if not fused:
-                np.testing.assert_array_equal(t.cut.cpu().numpy(), cut)
-                np.testing.assert_array_equal(t.bits.cpu().numpy().view(np.uint32), bits)
-            cj, cc, cs = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, pre_area=pa)
-            np.testing.assert_array_equal(t.cand_job.cpu().numpy(), cj, err_msg=f"policy {policy}")
-            np.testing.assert_array_equal(t.cand_cut.cpu().numpy(), cc, err_msg=f"policy {policy}")
-            np.testing.assert_array_equal(t.cand_score.cpu().numpy(), cs, err_msg=f"policy {policy}")
+            best = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, pre_area=pa)
             want = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, pre_area=pa)
-            for mode in ((0,) if fused else (0, 1)):
-                try:
-                    engine.sja_set_resolve_mode(mode)
+            for form in forms(wl):
+                for out in (t.cand_job, t.cand_cut, t.cand_score) + (() if fused else (t.cut, t.bits)):
+                    out.fill_(-5)
+                with in_mode(engine, form):
+                    if fused:
+                        t.fit_select(par)
+                    else:
+                        t.fit(); t.select(par)
+                torch.cuda.synchronize()
+                # the caller-visible running tables do not depend on the rule
+                np.testing.assert_array_equal(t.pre_dur.cpu().numpy().astype(np.int64), pd)
+                np.testing.assert_array_equal(t.pre_peak.cpu().numpy().astype(np.int64), pp)
+                np.testing.assert_array_equal(t.prev_safe.cpu().numpy(), ps)
+                if not fused:
+                    np.testing.assert_array_equal(t.cut.cpu().numpy(), cut)
+                    np.testing.assert_array_equal(t.bits.cpu().numpy().view(np.uint32), bits)
+                for got, x in zip((t.cand_job, t.cand_cut, t.cand_score), best):
+                    np.testing.assert_array_equal(got.cpu().numpy(), x, err_msg=f"form {form} policy {policy}")
+                for mode in ((form,) if fused else (form, 1)):
                     for out in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap):
                         out.fill_(-5)
-                    t.resolve(par)
-                finally:
-                    engine.sja_set_resolve_mode(0)
-                got = (t.grant_job, t.grant_cut, t.grant_score, t.job_gap)
-                for x, y in zip(got, want[:4]):
-                    np.testing.assert_array_equal(x.cpu().numpy(), y, err_msg=f"policy {policy} mode {mode}")
-                assert t.rounds.cpu().tolist() == [want[4], want[5]]
+                    with in_mode(engine, mode):
+                        t.resolve(par)
+                    got = (t.grant_job, t.grant_cut, t.grant_score, t.job_gap)
+                    for x, y in zip(got, want[:4]):
+                        np.testing.assert_array_equal(x.cpu().numpy(), y, err_msg=f"form {form} policy {policy} mode {mode}")
+                    assert t.rounds.cpu().tolist() == [want[4], want[5]]
         return float((cut != plain).mean())
     finally:
         engine.sja_set_hysteresis(None)
@@ -167,7 +168,7 @@ def test_rule_takes_effect_at_prepare_and_clears_again(engine, oracle):
         engine.sja_set_hysteresis(None)
 
 
-def test_chain_of_ticks_under_hysteresis(engine, oracle):
+def test_chain_of_ticks_under_hysteresis(engine, oracle, form):
     """sja_advance rebuilds the moved jobs under the rule their prepare used, and leaves the
     others' tables as they are."""
     import torch

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from gen import make_channels, make_gaps, make_workload
+from helpers import forms, in_mode
 
 pytestmark = pytest.mark.gpu
 
@@ -54,30 +55,29 @@ def limited_tick_check(engine, oracle, wl, which, policy=None, fused=False):
         pd, pp, ps = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
         cut, bits = oracle.fit_limited(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W, wl.C, olim,
                                        power if use_pow else None, deadline if use_dl else None, True)
-        if fused:
-            t.fit_select(par)
-        else:
-            t.fit()
-            t.select(par)
-        torch.cuda.synchronize()
-        # the caller-visible running tables do not depend on the limits
-        np.testing.assert_array_equal(t.pre_dur.cpu().numpy().astype(np.int64), pd)
-        np.testing.assert_array_equal(t.pre_peak.cpu().numpy().astype(np.int64), pp)
-        np.testing.assert_array_equal(t.prev_safe.cpu().numpy(), ps)
-        if not fused:
-            np.testing.assert_array_equal(t.cut.cpu().numpy(), cut)
-            np.testing.assert_array_equal(t.bits.cpu().numpy().view(np.uint32), bits)
-        cj, cc, cs = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
-        np.testing.assert_array_equal(t.cand_job.cpu().numpy(), cj)
-        np.testing.assert_array_equal(t.cand_cut.cpu().numpy(), cc)
-        np.testing.assert_array_equal(t.cand_score.cpu().numpy(), cs)
-        gj, gc, gs, jg, rounds, stable = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
-        t.resolve(par)
-        np.testing.assert_array_equal(t.grant_job.cpu().numpy(), gj)
-        np.testing.assert_array_equal(t.grant_cut.cpu().numpy(), gc)
-        np.testing.assert_array_equal(t.grant_score.cpu().numpy(), gs)
-        np.testing.assert_array_equal(t.job_gap.cpu().numpy(), jg)
-        assert t.rounds.cpu().tolist() == [rounds, stable]
+        best = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
+        grants = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
+        for form in forms(wl):
+            for out in (t.cand_job, t.cand_cut, t.cand_score, t.grant_job, t.grant_cut, t.grant_score, t.job_gap):
+                out.fill_(-5)
+            with in_mode(engine, form):
+                if fused:
+                    t.fit_select(par)
+                else:
+                    t.fit()
+                    t.select(par)
+                t.resolve(par)
+            torch.cuda.synchronize()
+            # the caller-visible running tables do not depend on the limits
+            np.testing.assert_array_equal(t.pre_dur.cpu().numpy().astype(np.int64), pd)
+            np.testing.assert_array_equal(t.pre_peak.cpu().numpy().astype(np.int64), pp)
+            np.testing.assert_array_equal(t.prev_safe.cpu().numpy(), ps)
+            if not fused:
+                np.testing.assert_array_equal(t.cut.cpu().numpy(), cut)
+                np.testing.assert_array_equal(t.bits.cpu().numpy().view(np.uint32), bits)
+            for got, want in zip((t.cand_job, t.cand_cut, t.cand_score, t.grant_job, t.grant_cut, t.grant_score, t.job_gap), best + grants[:4]):
+                np.testing.assert_array_equal(got.cpu().numpy(), want, err_msg=f"form {form}")
+            assert t.rounds.cpu().tolist() == list(grants[4:])
         return (cut >= 0).mean()
     finally:
         engine.sja_set_limits(None)
@@ -132,7 +132,7 @@ def test_limits_differ_from_the_plain_fit_and_clear_again(engine, oracle):
         engine.sja_set_limits(P.Limits.make(tau_max=-2))
 
 
-def test_chain_of_ticks_under_limits(engine, oracle):
+def test_chain_of_ticks_under_limits(engine, oracle, form):
     """sja_advance rebuilds the moved jobs under the limits their prepare used."""
     import torch
     import paper_2509_19086_amd as P

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from gen import make_workload
+from helpers import ORDERED, forms, in_mode
 
 pytestmark = pytest.mark.gpu
 
@@ -32,48 +33,50 @@ def _oracle_params(O, wl, policy=None, max_rounds=None):
 def full_tick_check(engine, oracle, wl, policies=None, check_resolve=True, resolve_modes=(0, 1)):
     """prepare, fit, select (each policy), resolve: every output equals the oracle's.
     Resolve runs once per mode (candidate lists / matrix-scanning rounds): each
-    must reproduce the oracle's rounds exactly."""
+    must reproduce the oracle's rounds exactly.  A batch small enough to be served
+    pair by pair is fitted once more so that it takes the forms of larger ones."""
     import torch
     import paper_2509_19086_amd as P
     t = P.DeviceTick(engine, wl)
-    t.prepare()
-    t.fit()
-    torch.cuda.synchronize()
-
     pd, pp, ps = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
-    np.testing.assert_array_equal(t.pre_dur.cpu().numpy().astype(np.int64), pd)
-    np.testing.assert_array_equal(t.pre_peak.cpu().numpy().astype(np.int64), pp)
-    np.testing.assert_array_equal(t.prev_safe.cpu().numpy(), ps)
-
     cut, bits = oracle.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W, wl.C)
-    np.testing.assert_array_equal(t.cut.cpu().numpy(), cut)
-    np.testing.assert_array_equal(t.bits.cpu().numpy().view(np.uint32), bits)
-
-    for policy in (policies if policies is not None else [wl.policy]):
-        par = P.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
-        t.select(par)
+    wants = {}
+    for form in forms(wl):
+        for out in (t.pre_dur, t.pre_peak, t.prev_safe, t.cut, t.bits):
+            out.fill_(-7)
+        with in_mode(engine, form):
+            t.prepare()
+            t.fit()
         torch.cuda.synchronize()
-        cj, cc, cs = oracle.select(cut, wl.seg_off, pd, pp, _oracle_params(oracle, wl, policy),
-                                   wl.wait, wl.sla_class)
-        np.testing.assert_array_equal(t.cand_job.cpu().numpy(), cj)
-        np.testing.assert_array_equal(t.cand_cut.cpu().numpy(), cc)
-        np.testing.assert_array_equal(t.cand_score.cpu().numpy(), cs)
-        if check_resolve:
-            gj, gc, gs, jg, rounds, stable = oracle.resolve(
-                cut, wl.seg_off, pd, pp, _oracle_params(oracle, wl, policy), wl.wait, wl.sla_class)
-            try:
-                for mode in resolve_modes:
-                    engine.sja_set_resolve_mode(mode)
-                    for out in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds):
-                        out.fill_(-5)
+        np.testing.assert_array_equal(t.pre_dur.cpu().numpy().astype(np.int64), pd)
+        np.testing.assert_array_equal(t.pre_peak.cpu().numpy().astype(np.int64), pp)
+        np.testing.assert_array_equal(t.prev_safe.cpu().numpy(), ps)
+        np.testing.assert_array_equal(t.cut.cpu().numpy(), cut)
+        np.testing.assert_array_equal(t.bits.cpu().numpy().view(np.uint32), bits)
+
+        for policy in (policies if policies is not None else [wl.policy]):
+            par = P.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
+            opar = _oracle_params(oracle, wl, policy)
+            for out in (t.cand_job, t.cand_cut, t.cand_score):
+                out.fill_(-5)
+            t.select(par)
+            torch.cuda.synchronize()
+            if policy not in wants:
+                wants[policy] = (oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class),
+                                 oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class) if check_resolve else None)
+            best, grants = wants[policy]
+            for got, want in zip((t.cand_job, t.cand_cut, t.cand_score), best):
+                np.testing.assert_array_equal(got.cpu().numpy(), want, err_msg=f"form {form} policy {policy}")
+            if not check_resolve:
+                continue
+            for mode in resolve_modes:
+                for out in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds):
+                    out.fill_(-5)
+                with in_mode(engine, mode):
                     t.resolve(par)
-                    np.testing.assert_array_equal(t.grant_job.cpu().numpy(), gj, err_msg=f"mode {mode}")
-                    np.testing.assert_array_equal(t.grant_cut.cpu().numpy(), gc, err_msg=f"mode {mode}")
-                    np.testing.assert_array_equal(t.grant_score.cpu().numpy(), gs, err_msg=f"mode {mode}")
-                    np.testing.assert_array_equal(t.job_gap.cpu().numpy(), jg, err_msg=f"mode {mode}")
-                    assert t.rounds.cpu().tolist() == [rounds, stable], f"mode {mode}"
-            finally:
-                engine.sja_set_resolve_mode(0)
+                for got, want in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap), grants):
+                    np.testing.assert_array_equal(got.cpu().numpy(), want, err_msg=f"form {form} policy {policy} mode {mode}")
+                assert t.rounds.cpu().tolist() == list(grants[4:]), f"form {form} policy {policy} mode {mode}"
     return t
 
 
@@ -138,7 +141,7 @@ def test_long_chain_of_rounds(engine, oracle, cap):
         assert t.rounds.cpu().tolist()[0] > 448
 
 
-def test_select_with_held_jobs_and_inactive_gaps(engine, oracle):
+def test_select_with_held_jobs_and_inactive_gaps(engine, oracle, form):
     import torch
     import paper_2509_19086_amd as P
     wl = make_workload("small", 5)
@@ -213,7 +216,7 @@ def test_repeatable(engine):
 
 def fused_check(engine, oracle, wl, policies, held=None, act=None, resolve=True):
     """sja_fit_select reports what sja_select reports after sja_fit (the oracle's), and
-    sja_resolve works on top of it without any cut matrix."""
+    sja_resolve works on top of it without any cut matrix; small batches in both forms."""
     import torch
     import paper_2509_19086_amd as P
     t = P.DeviceTick(engine, wl, want_cut=False)
@@ -225,22 +228,22 @@ def fused_check(engine, oracle, wl, policies, held=None, act=None, resolve=True)
     for policy in policies:
         par = P.Params.make(policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
         opar = _oracle_params(oracle, wl, policy)
-        for out in (t.cand_job, t.cand_cut, t.cand_score):
-            out.fill_(-5)
-        t.fit_select(par, h, a)
-        torch.cuda.synchronize()
-        cj, cc, cs = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, held, act)
-        np.testing.assert_array_equal(t.cand_job.cpu().numpy(), cj, err_msg=f"policy {policy}")
-        np.testing.assert_array_equal(t.cand_cut.cpu().numpy(), cc, err_msg=f"policy {policy}")
-        np.testing.assert_array_equal(t.cand_score.cpu().numpy(), cs, err_msg=f"policy {policy}")
-        if resolve and held is None and act is None:
-            t.resolve(par)
-            gj, gc, gs, jg, rounds, stable = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
-            np.testing.assert_array_equal(t.grant_job.cpu().numpy(), gj)
-            np.testing.assert_array_equal(t.grant_cut.cpu().numpy(), gc)
-            np.testing.assert_array_equal(t.grant_score.cpu().numpy(), gs)
-            np.testing.assert_array_equal(t.job_gap.cpu().numpy(), jg)
-            assert t.rounds.cpu().tolist() == [rounds, stable]
+        best = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, held, act)
+        resolve = resolve and held is None and act is None
+        grants = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class) if resolve else None
+        for form in forms(wl):
+            for out in (t.cand_job, t.cand_cut, t.cand_score, t.grant_job, t.grant_cut, t.grant_score, t.job_gap):
+                out.fill_(-5)
+            with in_mode(engine, form):
+                t.fit_select(par, h, a)
+                torch.cuda.synchronize()
+                for got, want in zip((t.cand_job, t.cand_cut, t.cand_score), best):
+                    np.testing.assert_array_equal(got.cpu().numpy(), want, err_msg=f"form {form} policy {policy}")
+                if resolve:
+                    t.resolve(par)
+                    for got, want in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap), grants):
+                        np.testing.assert_array_equal(got.cpu().numpy(), want, err_msg=f"form {form} policy {policy}")
+                    assert t.rounds.cpu().tolist() == list(grants[4:])
     return t
 
 
@@ -275,7 +278,7 @@ def test_fused_many_capacity_classes(engine, oracle, n_classes):
     fused_check(engine, oracle, wl, policies=[3, 0], resolve=True)
 
 
-def test_fused_then_select_is_refused_and_scanning_rounds_work(engine, oracle):
+def test_fused_then_select_is_refused_and_scanning_rounds_work(engine, oracle, form):
     """After sja_fit_select there is no matrix: sja_select is refused, while the scanning rounds
     re-evaluate the pairs and give the oracle's grants."""
     import torch
@@ -334,7 +337,8 @@ def test_more_jobs_than_the_held_bitmap_holds(engine, oracle):
 def test_resolve_after_the_fused_call_with_too_many_capacities(engine, oracle, policy):
     """After sja_fit_select there is no cut matrix, and with more than 64 distinct capacities the
     candidate lists cannot run either: the rounds then re-evaluate the pairs of the still-active
-    gaps each round.  Same grants as the oracle's, in both resolve modes, also under a round cap."""
+    gaps each round.  Same grants as the oracle's, in all resolve modes (pair by pair, and the
+    ordered forms of larger batches), also under a round cap."""
     import paper_2509_19086_amd as P
     wl = make_workload("medium", 13, n_gaps=300, n_jobs=200)
     wl.C = np.ascontiguousarray((9000 + 7 * np.arange(wl.n_gaps)).astype(np.int32))     # 300 distinct capacities
@@ -348,7 +352,7 @@ def test_resolve_after_the_fused_call_with_too_many_capacities(engine, oracle, p
         want = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
         assert want[4] > 3 or cap == 3
         try:
-            for mode in (0, 1):
+            for mode in (0, 1, ORDERED):
                 engine.sja_set_resolve_mode(mode)
                 t.fit_select(par)
                 for o in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds):
@@ -406,11 +410,10 @@ def test_matrix_rounds_in_batches(engine, oracle, cap):
     assert want[4][0] == (cap or 90)
     par = _params(P, wl)
     par.policy = 0
-    t.fit_select(par)
-    engine.sja_set_resolve_mode(1)
-    try:
-        t.resolve(par)
-    finally:
-        engine.sja_set_resolve_mode(0)
-    for a, b in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds), want):
-        np.testing.assert_array_equal(a.cpu().numpy(), b)
+    for form in forms(wl):
+        with in_mode(engine, form):
+            t.fit_select(par)
+        with in_mode(engine, 1):
+            t.resolve(par)
+        for a, b in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds), want):
+            np.testing.assert_array_equal(a.cpu().numpy(), b)

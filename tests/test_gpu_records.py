@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from gen import make_workload
+from helpers import forms, in_mode
 from test_gpu_parity import full_tick_check
 
 pytestmark = pytest.mark.gpu
@@ -101,16 +102,18 @@ def test_rounds_that_search(engine, oracle, caps, n_gaps, n_jobs, max_rounds):
     for policy in (0, 1, 3):
         par = P.Params.make(policy, max_rounds=max_rounds)
         opar = O.Params.make(policy, max_rounds=max_rounds)
-        t.fit_select(par)
-        t.resolve(par)
         gj, gc, gs, jg, rounds, stable = O.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
-        for got, want in ((t.grant_job, gj), (t.grant_cut, gc), (t.grant_score, gs), (t.job_gap, jg)):
-            np.testing.assert_array_equal(got.cpu().numpy(), want)
-        assert t.rounds.cpu().tolist() == [rounds, stable]
+        for form in forms(wl):
+            with in_mode(engine, form):
+                t.fit_select(par)
+                t.resolve(par)
+            for got, want in ((t.grant_job, gj), (t.grant_cut, gc), (t.grant_score, gs), (t.job_gap, jg)):
+                np.testing.assert_array_equal(got.cpu().numpy(), want)
+            assert t.rounds.cpu().tolist() == [rounds, stable]
 
 
 @pytest.mark.parametrize("n_gaps", [1, 15, 16, 17, 63, 65])
-def test_select_with_gaps_switched_off(engine, oracle, n_gaps):
+def test_select_with_gaps_switched_off(engine, oracle, n_gaps, form):
     # the masked pass and the reduction at the edges of a chunk of positions and of a block's gaps
     import torch
     import paper_2509_19086_amd as P

@@ -1,6 +1,7 @@
 """Calm conflict rounds, played in batches (k_sets.h): one and several list blocks and classes, up to one,
 two and four sets per lane, one launch and launches in turn, caps in the middle of a batch, jobs or gaps that
-run out, equal keys, cuts that only some windows get, against the oracle."""
+run out, equal keys, cuts that only some windows get, against the oracle.  Most batches here are small enough to be
+served pair by pair: full_tick_check fits those a second time, in the mode that leaves them to these kernels."""
 import numpy as np
 import pytest
 

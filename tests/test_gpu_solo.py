@@ -1,6 +1,7 @@
 """Conflict rounds run by one thread block: what its rule takes and what it leaves to the launched
 rounds, round caps on both sides of the hand-over, equal keys, lists that run dry, and keys that fall
-along a job's atoms, against the oracle."""
+along a job's atoms, against the oracle (small batches in the mode that leaves them to these kernels
+too, see full_tick_check)."""
 import numpy as np
 import pytest
 
@@ -53,15 +54,16 @@ def test_hysteresis_keys_that_fall(engine, oracle, caps, gain):
     try:
         t = P.DeviceTick(engine, wl)
         t.prepare()
-        t.fit()
         want = None
-        for mode in (1, 0):                 # the matrix-scanning rounds are checked against the oracle elsewhere
+        for fitted, mode in ((0, 1), (0, 0), (2, 0)):       # the matrix-scanning rounds are checked against the oracle elsewhere
+            engine.sja_set_resolve_mode(fitted)
+            t.fit()
             engine.sja_set_resolve_mode(mode)
             t.resolve(P.Params.make(3))
             got = [x.cpu().numpy().copy() for x in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds)]
             want = want or got
-        for a, b in zip(got, want):
-            np.testing.assert_array_equal(a, b)
+            for a, b in zip(got, want):
+                np.testing.assert_array_equal(a, b)
     finally:
         engine.sja_set_resolve_mode(0)
         engine.sja_set_hysteresis([], 1)

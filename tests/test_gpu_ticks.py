@@ -91,12 +91,12 @@ def run_ticks(engine, oracle, name, seed, n_ticks, policy, fused, wait_step, n_g
 
 @pytest.mark.parametrize("policy", [0, 1, 2, 3])
 @pytest.mark.parametrize("fused", [False, True])
-def test_tiny_chain_of_ticks(engine, oracle, policy, fused):
+def test_tiny_chain_of_ticks(engine, oracle, policy, fused, form):
     run_ticks(engine, oracle, "tiny", 1, 6, policy, fused, wait_step=250)
 
 
 @pytest.mark.parametrize("fused", [False, True])
-def test_small_chain_of_ticks(engine, oracle, fused):
+def test_small_chain_of_ticks(engine, oracle, fused, form):
     run_ticks(engine, oracle, "small", 2, 5, 3, fused, wait_step=1000)
 
 
@@ -104,12 +104,12 @@ def test_medium_chain_of_ticks(engine, oracle):
     run_ticks(engine, oracle, "medium", 0, 3, 3, True, wait_step=1000)
 
 
-def test_ragged_chain_without_wait(engine, oracle):
+def test_ragged_chain_without_wait(engine, oracle, form):
     """Odd sizes; no waiting-time array; jobs longer than one 64-segment stride are rebuilt mid-profile."""
     run_ticks(engine, oracle, "stress", 7, 4, 0, True, wait_step=1, n_gaps=333, n_jobs=1111, with_wait=False)
 
 
-def test_ticks_until_every_job_is_done(engine, oracle):
+def test_ticks_until_every_job_is_done(engine, oracle, form):
     """More gap capacity than work: the chain ends with every progress point at its job's end."""
     import torch
     import paper_2509_19086_amd as P
@@ -222,7 +222,7 @@ def test_advance_and_cover_with_no_gaps(engine, oracle):
     assert w2[2] == wl.wait[2] and (np.delete(w2, 2) == np.delete(wl.wait, 2) + 11).all()
 
 
-def test_whole_chain_on_a_side_stream(engine, oracle):
+def test_whole_chain_on_a_side_stream(engine, oracle, form):
     """Every call takes the caller's stream: two ticks enqueued on a non-default stream (default
     priority), the device only synchronised where sja_resolve does it itself and at the end."""
     import torch

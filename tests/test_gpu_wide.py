@@ -1,6 +1,6 @@
 """Launched rounds with a wave per gap (k_grant_wide): few and many list blocks (sixteen and eight waves each, and
 more than it takes), list blocks of one lane and of 64, records that many lanes pass, bounded rounds, against the
-oracle."""
+oracle (small batches in the mode that leaves them to these kernels too, see full_tick_check)."""
 import numpy as np
 import pytest
 
