@@ -106,19 +106,42 @@ __device__ __forceinline__ uint32_t key_digest(const PolicyDev &pol, unsigned lo
     return (tier_bits ? uint32_t(tier) << (32 - tier_bits) : 0u) | (uint32_t(e) << rest) | uint32_t(mantissa >> (64 - rest));
 }
 
+// Whether digests tell atoms apart depends on the keys: many jobs of one profile, their waits a thousandth apart, have
+// hundreds of atoms of different keys behind each 24 bits.  kAlikeLeast to twice as many atoms, by a hash of their ids,
+// are compared with the last one before them in a slot of `seen` (zeros at the start): alike counts those whose keys
+// differ and whose leading 24 bits (lower half) or 32 bits (upper half) do not.
+constexpr int kAlikeSlots = 4096, kAlikeLeast = 2048;
+__host__ __device__ inline int alike_shift(uint32_t n_atoms)          // one atom in 2^shift is looked at
+{
+    int s = 0;
+    while ((n_atoms >> s) >= 2u * kAlikeLeast) ++s;
+    return s;
+}
+__device__ __forceinline__ void note_alike(const PolicyDev &pol, unsigned long long key, uint32_t digest, unsigned long long *seen, int32_t *alike)
+{
+    const unsigned long long was = atomicExch(&seen[((digest >> 8) * 2654435761u) >> 20], key + 1);
+    if (was == 0 || was == key + 1) return;
+    const uint32_t other = key_digest(pol, (was - 1) >> 62, (was - 1) & ((1ull << 62) - 1));
+    if (other >> 8 == digest >> 8) atomicAdd(alike, other == digest ? 0x10001 : 1);
+}
+static_assert(kAlikeSlots == 1 << 12 && 2 * kAlikeLeast < 1 << 15, "slots by 12 bits of the product; the counts fit");
+
 // One wave per job: inverted policy keys of its reachable atoms (ascending sort
 // of the inverted key = descending key) and the identity permutation, and both as one word: inverted digest : atom.
+// seen may be null.
 __global__ __launch_bounds__(256) void k_atom_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ abase, const int32_t *__restrict__ wait,
     const uint8_t *__restrict__ sla_class, unsigned long long *__restrict__ key_hi,
     unsigned long long *__restrict__ key_lo, uint32_t *__restrict__ perm, int4 *__restrict__ info, unsigned long long *__restrict__ digest,
-    unsigned long long *bits)
+    unsigned long long *bits, unsigned long long *seen, int32_t *alike)
 {
     __shared__ unsigned long long s_bits[2][256 / kWave];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const bool mixed = pol.policy == SJA_POLICY_MIXED;
     unsigned long long any_hi = 0, any_lo = 0;
+    const uint32_t total = seen ? uint32_t(abase[n_jobs]) : 0u;
+    const uint32_t sampled = total > uint32_t(kKeyTile) ? uint32_t((1ull << 32) >> alike_shift(total)) : 0u;      // (a hash below it)
     for (int j = blockIdx.x * (256 / kWave) + wave; j < n_jobs; j += gridDim.x * (256 / kWave)) {
         const int a0 = abase[j], n = abase[j + 1] - a0;
         const int64_t base = seg_off[j];
@@ -131,7 +154,9 @@ __global__ __launch_bounds__(256) void k_atom_keys(
                                                    : (unsigned long long)v.x * (unsigned long long)v.y;
             const unsigned long long k = (tier << 62) | (F * mult);
             key_hi[a0 + a] = ~k;
-            digest[a0 + a] = (static_cast<unsigned long long>(~key_digest(pol, tier, F * mult)) << 32) | uint32_t(a0 + a);
+            const uint32_t lead = key_digest(pol, tier, F * mult);
+            digest[a0 + a] = (static_cast<unsigned long long>(~lead) << 32) | uint32_t(a0 + a);
+            if (uint32_t(a0 + a) * 2654435761u < sampled) note_alike(pol, k, lead, seen, alike);
             any_hi |= k;
             if (mixed) {
                 key_lo[a0 + a] = ~F;

@@ -461,8 +461,10 @@ __global__ __launch_bounds__(256) void k_fix_ties(const int32_t *n_ptr, const un
 // Items in the order of their digests (the upper bits of `items`, from `shift` on; their ids in the lower 32): puts
 // those of equal digests in the order of their keys, then second keys (MIXED), then as they stand, and writes
 // the ids.  The first one's thread serves a run, all of its keys asked for together if they are at most kRunNear;
-// a run of more than kTieRun that is out of order sets *flag.
+// a run of more than kTieRun that is out of order sets *flag: kRunsByKey if keys are, kRunsBySecond if second keys of
+// equal ones are.
 constexpr int kRunNear = 8;
+enum { kRunsByKey = 1, kRunsBySecond = 2 };
 
 template <bool MIXED>
 __global__ __launch_bounds__(256) void k_fix_runs(const int32_t *n_ptr, const unsigned long long *__restrict__ items, int shift,
@@ -479,7 +481,8 @@ __global__ __launch_bounds__(256) void k_fix_runs(const int32_t *n_ptr, const un
     if (i > 0 && same(i - 1)) {
         if (i > kTieRun && same(i - kTieRun - 1)) {             // beyond the part that the first one's thread looks at
             perm[i] = id;
-            if (before(id, uint32_t(items[i - 1]))) *flag = 1;
+            const uint32_t a = uint32_t(items[i - 1]);
+            if (before(id, a)) atomicOr(flag, keys[id] < keys[a] ? kRunsByKey : kRunsBySecond);
         }
         return;
     }
@@ -512,14 +515,14 @@ __global__ __launch_bounds__(256) void k_fix_runs(const int32_t *n_ptr, const un
         return;
     }
     int64_t e = i;
-    bool ordered = true;
+    int found = 0;
     for (; e < n && e - i <= kTieRun && same(e); ++e) {
-        const uint32_t a = uint32_t(items[e]);
+        const uint32_t a = uint32_t(items[e]), b = uint32_t(items[e > i ? e - 1 : e]);
         perm[e] = a;
-        if (e > i) ordered = ordered && !before(a, uint32_t(items[e - 1]));
+        if (before(a, b)) found |= keys[a] < keys[b] ? kRunsByKey : kRunsBySecond;
     }
-    if (ordered) return;
-    if (e - i > kTieRun) { *flag = 1; return; }
+    if (!found) return;
+    if (e - i > kTieRun) { atomicOr(flag, found); return; }
     for (int64_t k = i + 1; k < e; ++k) {
         const uint32_t a = perm[k];
         int64_t at = k;

@@ -4,6 +4,8 @@
 #include "k_sets.h"
 #include "k_pairs.h"
 
+#include <math.h>
+
 #include <mutex>
 #include <new>
 #include <vector>
@@ -259,7 +261,9 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     int32_t *tmp = ws_ptr<int32_t>(ctx, L.g_scan_tmp);
     int32_t *counters = ws_ptr<int32_t>(ctx, L.res_counters);      // [0..1] entries (64 bit), [2] atoms, [4..7] key bits
     constexpr int kCountTies = 13;
-    constexpr int64_t kDigestFew = 1 << 20;         // atoms that 24 bits of their keys' digests tell apart well enough
+    constexpr int64_t kDigestFew = 1 << 20;         // atoms that 24 bits of their keys' digests tell apart well enough,
+    constexpr int kDigestAlike = 8;                 // unless an atom shares them with so many others: a run of more than
+                                                    // kTieRun would be likely, and the sort begun for nothing
     int32_t *list_off = ws_ptr<int32_t>(ctx, L.g_list_off);
     const int2 *atom_dp = ws_ptr<int2>(ctx, L.atom_dp);
     const int2 *atom_db = ws_ptr<int2>(ctx, L.atom_db);
@@ -295,13 +299,14 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     SJA_HIP(hipGetLastError(), "k_reach launch");
     SJA_HIP(enqueue_scan(st, abase, int64_t(J) + 1, tmp, counters + 2), "atom scan launch");
     // policy keys of the atoms and the bytes in which they differ
-    auto launch_keys = [&]() {
+    auto launch_keys = [&](bool first) {
         hipLaunchKernelGGL(k_atom_keys, dim3(J < 4 * 4096 ? (J + 3) / 4 : 4096), dim3(256), 0, st, J, pol, ctx->seg_off, atom_dp,
                            atom_area_of(ctx, L), abase, wait, sla_class, key_hi, key_lo, perm[0], info, ekey[0],
-                           reinterpret_cast<unsigned long long *>(counters + 4));
+                           reinterpret_cast<unsigned long long *>(counters + 4), 
+                           first && ctx->hyst_used_n_caps == 0 ? ekey[1] : nullptr, counters + 3);
         return hipGetLastError();
     };
-    SJA_HIP(launch_keys(), "k_atom_keys launch");
+    SJA_HIP(launch_keys(true), "k_atom_keys launch");
     char host_both[512] = {0};      // the plan, and the counters behind it
     const size_t apart = L.res_counters - L.plan;
     static_assert(sizeof(host_both) >= 256 + 64, "plan and counters");
@@ -322,15 +327,29 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     //    the primary key and their ties put in order; `both`: by the secondary key first
     const bool mixed = params->policy == SJA_POLICY_MIXED;
     bool flip = false;      // where the atom ids are: perm[flip]
+    // 24 or 32 bits, or no digest (the hysteresis rule gives many atoms of a job the same cut: long runs of equal keys, and
+    // others among them).  8192 jobs of one profile, 2048 gaps: with 24 bits whatever the keys 770 us a resolve with waits
+    // between 10^6 and 10^6 + 1000 and 930 under MIXED, by all bytes 600 and 620, so 530 and 525
+    auto alike = [&](int found) {
+        // of those looked at, every one but the first of each run was found: a share of 1 - (1 - exp(-x)) / x in runs that
+        // leave x of their atoms on average
+        const int shift = alike_shift(uint32_t(n_atoms));
+        const double x = double(kDigestAlike) / double(1 << shift);
+        return found > kDigestAlike && found > double(n_atoms >> shift) * (1.0 + expm1(-x) / x);
+    };
+    int digest_passes = n_atoms <= kDigestFew && !alike(host_counters[3] & 0xffff) ? 3 : 4;
+    unsigned long long bits_hi = 0, bits_lo = 0;
+    memcpy(&bits_hi, host_counters + 4, 8);
+    memcpy(&bits_lo, host_counters + 6, 8);
+    auto bytes_of = [](unsigned long long v) {
+        unsigned m = 0;
+        for (int b = 0; b < 8; ++b) if ((v >> (8 * b)) & 0xffull) m |= 1u << b;
+        return m;
+    };
+    if (ctx->hyst_used_n_caps > 0 || (digest_passes == 4 && alike(host_counters[3] >> 16)) ||
+        __builtin_popcount(bytes_of(bits_hi)) <= digest_passes)
+        digest_passes = 0;
     auto rank_atoms = [&](bool both) -> int {
-        unsigned long long bits_hi = 0, bits_lo = 0;
-        memcpy(&bits_hi, host_counters + 4, 8);
-        memcpy(&bits_lo, host_counters + 6, 8);
-        auto bytes_of = [](unsigned long long v) {
-            unsigned m = 0;
-            for (int b = 0; b < 8; ++b) if ((v >> (8 * b)) & 0xffull) m |= 1u << b;
-            return m;
-        };
         const dim3 grid(unsigned((n_atoms + 255) / 256)), block(256);
         flip = false;
         if (n_atoms <= kKeyTile) {
@@ -341,9 +360,8 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         }
         // by the leading bits only, the rest where those are equal, if that takes fewer passes: three in place of six at
         // 2048 gaps x 8192 jobs (tick 1175 -> 1134 us), in place of eight under MIXED (three ticks 4655 -> 4245)
-        // (the hysteresis rule gives many atoms of a job the same cut: long runs of equal keys, and others among them)
-        const int passes = n_atoms <= kDigestFew ? 3 : 4;
-        if (!both && ctx->hyst_used_n_caps == 0 && __builtin_popcount(bytes_of(bits_hi)) > passes) {
+        const int passes = digest_passes;
+        if (!both && passes) {
             for (int p = 0; p < passes; ++p) {
                 const int rc = radix_pass(ctx, st, L, counters + 2, n_atoms, 64 - 8 * (passes - p), 8, flip, ekey,
                                           [&](bool few, dim3 tiles, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
@@ -405,7 +423,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         return hipGetLastError();
     };
     long long n_entries = 0;
-    for (bool both = false;; both = true) {
+    for (bool both = false;;) {
         if (n_atoms > 0) {
             const int rc = rank_atoms(both);
             if (rc != SJA_OK) return rc;
@@ -417,11 +435,13 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         SJA_HIP(hipStreamSynchronize(st), "entry count synchronise");
         memcpy(&n_entries, h, sizeof(n_entries));
         if (!h[kCountTies]) break;
-        // a long run of equal primary keys out of order: once more, by both keys
+        // a long run out of order: once more, by all of the primary key if that was not done and the run lacks it, else by both
+        both = !digest_passes || !(h[kCountTies] & kRunsByKey);
+        digest_passes = 0;
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, st, counters, int64_t(2), 0);
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, st, counters + kCountTies, int64_t(1), 0);
         hipLaunchKernelGGL(k_fill_i32, dim3((lb_bound + 2 + 255) / 256), dim3(256), 0, st, list_off, int64_t(lb_bound + 2), 0);
-        SJA_HIP(launch_keys(), "k_atom_keys launch");
+        SJA_HIP(launch_keys(false), "k_atom_keys launch");
     }
     if (n_entries > L.entry_cap || n_entries >= (1ll << 31)) return SJA_OK;
     SJA_HIP(enqueue_scan(st, list_off, int64_t(lb_bound) + 2, tmp, nullptr), "list offset scan launch");
@@ -1342,6 +1362,7 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
         };
         also(L.res_counters, 16);
         also(L.g_list_off, list_block_bound(G, J) + 2);
+        also(L.g_ekey1, 2 * (L.entry_cap < kAlikeSlots ? L.entry_cap : kAlikeSlots));      // (used if there are more atoms than that)
         also(L.g_cnt_lost, (G < J ? G : J) + 4);
         also(L.g_cnt_cand, (G < J ? G : J) + 4);
         if (held_bitmap_words(J) <= kHeldMaxWords) also(L.g_held, 2 * held_bitmap_words(J));
