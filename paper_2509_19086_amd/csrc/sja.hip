@@ -145,8 +145,10 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
     const int job_tiles = (J + kSelBlock - 1) / kSelBlock;
     unsigned long long *seg_key = ws_ptr<unsigned long long>(ctx, L.g_key_hi);
     if (job_tiles > 0 && !keys_ready) {
-        hipLaunchKernelGGL(k_select_keys, dim3((J + 3) / 4), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
-                           ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class, seg_key);
+        const int per_wave = keys_jobs_per_wave(J, ctx->n_segments);
+        hipLaunchKernelGGL(k_select_keys, dim3((J + 4 * per_wave - 1) / (4 * per_wave)), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
+                           ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class,
+                           ctx->pre_dur, ctx->pre_peak, pre_area_of(ctx, L), keys_dense(ctx->n_segments, ctx->hyst_used_n_caps > 0), per_wave, seg_key);
         SJA_HIP(hipGetLastError(), "k_select_keys launch");
     }
     if (job_tiles > 0) {

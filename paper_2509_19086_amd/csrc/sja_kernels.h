@@ -72,6 +72,10 @@ __device__ __forceinline__ int lane_value(int v, int src)
 {
     return __builtin_amdgcn_readlane(v, src);
 }
+__device__ __forceinline__ unsigned long long lane_value64(unsigned long long v, int l)
+{
+    return (static_cast<unsigned long long>(uint32_t(lane_value(int(uint32_t(v >> 32)), l))) << 32) | uint32_t(lane_value(int(uint32_t(v)), l));
+}
 __device__ __forceinline__ long long lane_value(long long v, int src)
 {
     const unsigned int lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t((unsigned long long)v)), src));
@@ -733,23 +737,62 @@ __global__ __launch_bounds__(256) void k_validate(
 // per call: the stepping kernel below then fetches a finished key where a job's
 // cut changes instead of (duration, peak) and three 64-bit multiplies per lane.
 // One wave per job, lanes along its atoms (from the running tables, for every prefix a cut can lie
-// between, it moved 16 bytes per segment: 8192 gaps x 32768 jobs 74 -> 35 us).
+// between, it moved 16 bytes per segment: 8192 gaps x 32768 jobs 74 -> 35 us), but along those prefixes where many of
+// them are atoms: an atom takes 24 bytes, and 8 of them are a scattered store, which costs the more the less of the
+// table of keys the last-level cache (256 MB) holds.  dense: atoms per 64 prefixes from which on.  A select of 512 gaps x
+// 32768 jobs along prefixes / along atoms, us: 256 segments a job, every boundary safe 79 / 95, half of them 75 / 79,
+// 0.35 72.3 / 72.0, 0.25 69 / 66; 1024 segments, 0.3 226 / 242, 0.25 221 / 228, 0.2 215 / 210, half of each job done 0.3
+// 136 / 124; 2048 segments, 0.25 333 / 410, 0.15 319 / 339, 0.1 307 / 273, half done 0.25 219 / 230, 0.15 206 / 176; under
+// the hysteresis rule, where many atoms share a cut, 512 segments, every boundary safe 89 / 94, 0.8 90 / 79.
+inline int keys_dense(int64_t n_segments, bool remapped)
+{
+    return remapped ? 61 : n_segments <= int64_t(1) << 24 ? 24 : n_segments <= int64_t(1) << 25 ? 18 : 11;
+}
+// Jobs per wave, one after the other: where they are short and enough of them, so that what is asked about a job before its
+// first atom is asked for several together (one, two, four and eight a wave, a select as above: 64 segments 43.2, 41.2, 39.9 and
+// 41.0 us, 256 segments 65.3, 64.8, 64.8 and 65.3, 1024 segments 230, 236, 239 and 249).
+inline int keys_jobs_per_wave(int64_t n_jobs, int64_t n_segments)
+{
+    return n_jobs < 16384 || n_segments > 512 * n_jobs ? 1 : n_segments > 256 * n_jobs ? 2 : 4;
+}
 __global__ __launch_bounds__(256) void k_select_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp, const int2 *__restrict__ atom_db,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
-    const uint8_t *__restrict__ sla_class, unsigned long long *__restrict__ seg_key)
+    const uint8_t *__restrict__ sla_class, const int32_t *__restrict__ pre_dur, const int32_t *__restrict__ pre_peak,
+    const long long *__restrict__ pre_area, int dense, int per_wave, unsigned long long *__restrict__ seg_key)
 {
-    const int lane = lane_id();
-    const int j = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-    if (j >= n_jobs) return;
-    const int64_t base = seg_off[j];
-    const int n = n_atoms[j];
-    unsigned long long mult, tier;
-    job_policy(pol, wait, sla_class, j, mult, tier);
-    for (int a = lane; a < n; a += kWave) {
-        const int2 v = atom_dp[base + a];
-        const unsigned long long F = atom_area ? (unsigned long long)atom_area[base + a] : rect_of(v.x, v.y);
-        seg_key[base + atom_db[base + a].y - 1] = ((tier << 62) | times_mult(F, mult)) + 1ull;
+    const int lane = lane_id(), j0 = (blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave)) * per_wave;
+    // what says which form a job takes, a lane each (no cut lies beyond a job's end; the first atom reports its own
+    // boundary under the hysteresis rule, too)
+    const int mine = min(j0 + lane, n_jobs - 1);
+    const bool there = lane < per_wave && j0 + lane < n_jobs;
+    const int64_t base_of = seg_off[mine];
+    const int n_of = there ? n_atoms[mine] : 0, last_of = int(seg_off[mine + 1] - base_of);
+    unsigned long long mult_of, tier_of;
+    job_policy(pol, wait, sla_class, mine, mult_of, tier_of);
+    const int first_of = n_of > 0 ? atom_db[base_of].y : 0;
+    for (int q = 0; q < per_wave; ++q) {
+        const int n = lane_value(n_of, q), first = lane_value(first_of, q), last = lane_value(last_of, q);
+        if (n == 0) continue;
+        const int64_t base = int64_t(lane_value64(base_of, q));
+        const unsigned long long mult = lane_value64(mult_of, q), tier = lane_value64(tier_of, q);
+        auto key = [&](unsigned long long F) { return ((tier << 62) | times_mult(F, mult)) + 1ull; };
+        if (int64_t(n) * 64 >= int64_t(last - first + 1) * dense) {
+            for (int k = first - 1 + lane; k < last; k += kWave)
+                seg_key[base + k] = key(pre_area ? (unsigned long long)pre_area[base + k] : rect_of(pre_dur[base + k], pre_peak[base + k]));
+            continue;
+        }
+        for (int a = lane; a < n; a += kWave) {
+            const int boundary = atom_db[base + a].y;
+            unsigned long long F;
+            if (atom_area) {
+                F = (unsigned long long)atom_area[base + a];
+            } else {
+                const int2 v = atom_dp[base + a];
+                F = rect_of(v.x, v.y);
+            }
+            seg_key[base + boundary - 1] = key(F);
+        }
     }
 }
 

@@ -190,3 +190,44 @@ def test_entries_of_large_batches(engine, oracle, name, n_gaps, n_jobs, classes,
         wl.W = np.floor(10 * 10.0 ** (4 * rng.random(n_gaps))).astype(np.int32)
     wl.max_rounds = 6
     full_tick_check(engine, oracle, wl, policies=[0, 3], resolve_modes=(0,))
+
+
+@pytest.mark.parametrize("n_jobs,longest", [(16383, 40), (16385, 40), (16386, 600), (20001, 1100)])
+def test_select_from_many_jobs(engine, oracle, n_jobs, longest):
+    # one, four, two and one job to a wave, some without anything left, the last wave without its full number
+    wl = make_workload("tiny", 5, n_gaps=40, n_jobs=8)
+    rng = np.random.default_rng(n_jobs)
+    lens = rng.integers(1, longest + 1, size=n_jobs)
+    lens[::3] = longest
+    wl.n_jobs = n_jobs
+    wl.seg_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    S = int(wl.seg_off[-1])
+    wl.dur, wl.mem = rng.integers(1, 30, size=S).astype(np.int32), rng.integers(256, 9000, size=S).astype(np.int32)
+    wl.safe = (rng.random(S) < np.repeat(rng.choice([0.05, 0.3, 1.0], size=n_jobs), lens)).astype(np.uint8)
+    wl.progress = np.where(rng.random(n_jobs) < 0.1, lens, (rng.random(n_jobs) * lens)).astype(np.int32)
+    wl.wait, wl.sla_class = rng.integers(0, 100, size=n_jobs).astype(np.int32), rng.integers(0, 3, size=n_jobs).astype(np.uint8)
+    full_tick_check(engine, oracle, wl, policies=[1, 3], check_resolve=False)
+
+
+@pytest.mark.parametrize("how", ["plain", "area", "hysteresis", "limits"])
+def test_select_from_jobs_of_few_and_of_many_cuts(engine, oracle, how):
+    # the keys go along a job's atoms or along all its prefixes by how many of those are atoms: shares on both sides of the
+    # line, and jobs with every boundary safe or only the end
+    from test_gpu_area import area_tick_check
+    from test_gpu_hysteresis import hysteresis_tick_check
+    from test_gpu_limits import limited_tick_check
+    wl = make_workload("medium", 17, n_gaps=1100, n_jobs=700)
+    rng = np.random.default_rng(3)
+    lens = np.diff(wl.seg_off)
+    share = rng.choice([0.0, 0.1, 0.3, 0.36, 0.375, 0.39, 0.6, 0.9, 0.953, 0.98, 1.0], size=700)
+    wl.safe = (rng.random(int(wl.seg_off[-1])) < np.repeat(share, lens)).astype(np.uint8)
+    wl.progress = np.where(rng.random(700) < 0.3, lens - rng.integers(0, 3, size=700), wl.progress).astype(np.int32)
+    if how == "plain":
+        full_tick_check(engine, oracle, wl, policies=[0, 3], resolve_modes=(1,))
+    elif how == "area":
+        area_tick_check(engine, oracle, wl, [1, 3], False)
+    elif how == "limits":
+        limited_tick_check(engine, oracle, wl, "all", policy=3)
+    else:
+        hysteresis_tick_check(engine, oracle, wl, "gap_capacities", [2, 3], False)
+        hysteresis_tick_check(engine, oracle, wl, "gap_capacities_big_gain", [0], False)
