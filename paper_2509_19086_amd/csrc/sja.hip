@@ -247,10 +247,11 @@ int bits_for(int64_t n)
 // List-driven conflict rounds.  Returns SJA_OK with *done = true when it
 // produced the grants, *done = false when the batch is outside what the lists
 // serve (more than kMaxClasses capacities, or more list entries than the
-// workspace holds) and the caller must take the matrix-scanning rounds.
+// workspace holds) and the caller must take the matrix-scanning rounds; *tabled and *many_capacities say what
+// it has seen of the plan by then.
 int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params,
                        const int32_t *wait, const uint8_t *sla_class, int32_t *grant_job, int32_t *grant_cut,
-                       int64_t *grant_score, int32_t *job_gap, int64_t cap, int32_t *rounds_and_stable, bool *done, bool *many_capacities)
+                       int64_t *grant_score, int32_t *job_gap, int64_t cap, int32_t *rounds_and_stable, bool *done, bool *tabled, bool *many_capacities)
 {
     *done = false;
     int32_t result[2] = {0, 0};
@@ -320,7 +321,8 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     const int64_t n_atoms = host_counters[2];
     const int n_subs = host_plan[kPlanListBlocks];          // list blocks from here on
     // runs of one capacity so short that the stepping form would begin anew every few positions
-    *many_capacities = !host_plan[kPlanTabled] && int64_t(host_plan[kPlanMarks]) * kShortRun > G;
+    *tabled = host_plan[kPlanTabled] != 0;
+    *many_capacities = !*tabled && int64_t(host_plan[kPlanMarks]) * kShortRun > G;
     if (!host_plan[kPlanTabled] || n_subs > lb_bound || n_atoms > L.atom_cap) return SJA_OK;
 
     // 2. rank the atoms by policy key (descending key, ascending job id): stable passes over
@@ -797,10 +799,13 @@ int launch_best_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_g
 
 // The fused fit -> select pass over the planned batch of gaps (the plan of enqueue_gap_plan is in
 // the workspace): candidates per gap among the jobs that job_held does not mark, for the gaps that
-// gap_active does not switch off.  No cut matrix is read or written.
+// gap_active does not switch off.  No cut matrix is read or written.  A batch has class tables or not, and one of two
+// forms serves it, k_range_select or k_fit_select; which one, only the device knows, so both are launched and one
+// returns at once, unless the caller has seen the plan (2500 gaps of 65 capacities x 1200 jobs: 6 us of a round of 290).
+enum class Tabled { Unknown, No, Yes };
 int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params,
                  const int32_t *wait, const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active,
-                 int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool timed, bool searched = false)
+                 int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool timed, bool searched = false, Tabled tabled = Tabled::Unknown)
 {
     const int J = ctx->n_jobs;
     const int job_tiles = (J + kFusedBlock - 1) / kFusedBlock;
@@ -831,8 +836,8 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
                                        : k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, false, false>);
         int rc = timed ? mark_kernel(ctx, st, false) : SJA_OK;
         if (rc != SJA_OK) return rc;
-        const bool ranges = keys_rise(ctx);
-        if (ranges) {
+        const bool rise = keys_rise(ctx);
+        if (rise && tabled != Tabled::No) {
             const int64_t jobs_once = (J + kRangeThreads - 1) / kRangeThreads, chunks = (n_gaps + fit_chunk_len(n_gaps, J) - 1) / fit_chunk_len(n_gaps, J);
             int batches = 1;
             while (batches < kRangeBatches && jobs_once * chunks >= 2 * batches * int64_t(kRangeBlocks)) batches *= 2;
@@ -847,16 +852,18 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
                                ws_ptr<SelPartial>(ctx, L.sel_part));
             SJA_HIP(hipGetLastError(), "k_range_select launch");
         }
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, int(!ranges), to_dev(params),
-                           ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
-                           ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin),
-                           ws_ptr<int32_t>(ctx, L.chunk_end), ws_ptr<int32_t>(ctx, L.chunk_class),
-                           ws_ptr<int32_t>(ctx, L.chunk_sub), ws_ptr<int32_t>(ctx, L.start_tab),
-                           ws_ptr<int32_t>(ctx, L.ncap_tab), ws_ptr<int32_t>(ctx, L.gap_w),
-                           ws_ptr<int32_t>(ctx, L.gap_c), ws_ptr<int32_t>(ctx, L.gap_order),
-                           ws_ptr<int32_t>(ctx, L.gap_run_end), wait, sla_class, job_held, gap_active,
-                           ws_ptr<SelPartial>(ctx, L.sel_part));
-        SJA_HIP(hipGetLastError(), "k_fit_select launch");
+        if (!rise || tabled != Tabled::Yes) {
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, int(!rise), to_dev(params),
+                               ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
+                               ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin),
+                               ws_ptr<int32_t>(ctx, L.chunk_end), ws_ptr<int32_t>(ctx, L.chunk_class),
+                               ws_ptr<int32_t>(ctx, L.chunk_sub), ws_ptr<int32_t>(ctx, L.start_tab),
+                               ws_ptr<int32_t>(ctx, L.ncap_tab), ws_ptr<int32_t>(ctx, L.gap_w),
+                               ws_ptr<int32_t>(ctx, L.gap_c), ws_ptr<int32_t>(ctx, L.gap_order),
+                               ws_ptr<int32_t>(ctx, L.gap_run_end), wait, sla_class, job_held, gap_active,
+                               ws_ptr<SelPartial>(ctx, L.sel_part));
+            SJA_HIP(hipGetLastError(), "k_fit_select launch");
+        }
         if (timed && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
     }
     if (range_tiles > 0) {
@@ -1375,11 +1382,13 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
         SJA_HIP(hipGetLastError(), "k_resolve_init launch");
     }
     int32_t result[2] = {0, 0};
-    bool done = false, many_capacities = false;
+    bool done = false, many_capacities = false, has_tables = false;
+    Tabled tabled = Tabled::Unknown;
     if (G > 0 && J > 0 && ctx->resolve_mode != SJA_RESOLVE_MATRIX) {
         rc = resolve_with_lists(ctx, st, L, params, wait, sla_class, grant_job, grant_cut, grant_score, job_gap, cap,
-                                rounds_used_and_stable, &done, &many_capacities);
+                                rounds_used_and_stable, &done, &has_tables, &many_capacities);
         if (rc != SJA_OK) return rc;
+        tabled = has_tables ? Tabled::Yes : Tabled::No;
     }
     if (done) {
         SJA_HIP(hipStreamSynchronize(st), "final synchronise");
@@ -1409,7 +1418,7 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
                                    /*keys_ready=*/r + k > 1);
             else
                 rc = launch_fused(ctx, st, L, G, params, wait, sla_class, job_gap, active, cand_job, cand_cut, cand_score,
-                                  false, searched);
+                                  false, searched, tabled);
             if (rc != SJA_OK) return rc;
             const dim3 grid((G + 255) / 256), block(256);
             hipLaunchKernelGGL(k_claim, grid, block, 0, st, G, int(r) + k, active, cand_job, claim, counters + 2 * k);
