@@ -34,7 +34,7 @@ namespace sja {
 // With places: list block (18 bits) : place of the atom's first position (16) : job (17) : hi : lo; a place is
 // the list block and lane of a position (up to kPlacedBlocks list blocks and kPlacedJobs jobs).
 constexpr int kEntryJobShift = 13, kEntryBlockShift = 37, kEntryPlaceShift = 30, kEntryPlacedBlockShift = 46;
-constexpr int kPlacedBlocks = 1024, kPlacedJobs = 1 << (kEntryPlaceShift - kEntryJobShift);
+constexpr int kPlacedBlocks = 1 << (kEntryPlacedBlockShift - kEntryPlaceShift - 6), kPlacedJobs = 1 << (kEntryPlaceShift - kEntryJobShift);
 static_assert(SJA_MAX_JOBS <= 1 << (kEntryBlockShift - kEntryJobShift), "job ids fit an entry");
 
 struct PolicyDev {

@@ -224,8 +224,7 @@ __host__ __device__ constexpr size_t pair_list_words(int n_gaps, int most) { ret
 // The jobs that fit gap blockIdx.x in the order of their keys, as many as the rounds can ask for: a gap passes
 // only jobs that other gaps hold, so it needs no more of them than there are gaps (`most`).  The jobs that fit are
 // gathered in LDS and sorted there by a bitonic network; steps within the 128 entries that a wave's threads
-// exchange need no barrier.  If LDS has no room for all of them (ROOM entries, a power of two, at least
-// `most` + Q x threads if there are more jobs than Q x threads), those that are not among the best so far are dropped on the way.
+// exchange need no barrier.  ROOM: a power of two, at least the number of jobs.
 template <bool MIXED, int ROOM, int Q>
 __global__ __launch_bounds__(kPairsMostThreads) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, const int32_t *__restrict__ gap_w,
                                                                    const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
@@ -274,8 +273,6 @@ __global__ __launch_bounds__(kPairsMostThreads) void k_order_pairs(int n_gaps, i
     if (tid == 0) s_n = 0;
     __syncthreads();
     const int gw = gap_w[g], gc = gap_c[g];
-    unsigned long long least_hi = 0, least_lo = 0;      // the last one of the best so far
-    int least_job = INT32_MAX;
     for (int j0 = 0; j0 < n_jobs; j0 += Q * threads) {
         const int2 *dp[Q];
         int n[Q], w[Q], c[Q], lo[Q];
@@ -299,7 +296,7 @@ __global__ __launch_bounds__(kPairsMostThreads) void k_order_pairs(int n_gaps, i
                 const int2 v = dp[q][lo[q] - 1];
                 pair_key<MIXED>(atom_area ? (unsigned long long)atom_area[base[q] + lo[q] - 1] : rect_of(v.x, v.y), mult, tier, kh, kl);
             }
-            const bool in = lo[q] > 0 && fused_better(kh, kl, j, least_hi, least_lo, least_job);
+            const bool in = lo[q] > 0;
             const unsigned long long fits = __ballot(in);
             if (!fits) continue;
             int at = 0;
@@ -310,18 +307,6 @@ __global__ __launch_bounds__(kPairsMostThreads) void k_order_pairs(int n_gaps, i
                 if (MIXED) lo_at(at) = kl;
                 s_job[at] = uint16_t(j);
             }
-        }
-        if (j0 + Q * threads >= n_jobs) break;
-        __syncthreads();
-        const int fit = s_n;
-        __syncthreads();
-        if (fit + Q * threads > ROOM) {
-            sort(fit);
-            if (fit >= most) {
-                least_hi = s_hi[most - 1]; least_lo = MIXED ? lo_at(most - 1) : 0ull; least_job = s_job[most - 1];
-            }
-            if (tid == 0) s_n = min(fit, most);
-            __syncthreads();
         }
     }
     __syncthreads();

@@ -39,6 +39,7 @@ namespace sja {
 
 constexpr int kSetsWaves = 16, kSetsThreads = kSetsWaves * kWave;
 constexpr int kSetsMaxBlocks = 768;     // list blocks
+static_assert(kSetsMaxBlocks <= kPlacedBlocks, "a place is a list block and a lane");
 constexpr int kSetsOneBlocks = 128;     // and up to which one thread block does it all
 constexpr int kSetsPieces = 6;          // pieces of a list block, at most
 constexpr int kSetsMost = 256;          // sets, at most

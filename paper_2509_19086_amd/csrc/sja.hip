@@ -734,6 +734,7 @@ int resolve_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_param
     unsigned long long *list = ws_ptr<unsigned long long>(ctx, L.g_ekey0);
     auto order = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
+        static_assert(kPairsJobs <= 4096, "the largest has room for every job");
         // a thread per two entries, if it is not too many
         auto launch = [&](auto kern, int threads) {
             hipLaunchKernelGGL(kern, dim3(G), dim3(threads), 0, st, G, J, most, pol, gap_w, gap_c, ctx->seg_off, atom_dp, area, n_atoms, wait,
