@@ -298,12 +298,13 @@ int sja_select(sja_ctx *ctx, void *stream, const sja_params *params, const int32
  * job_held, gap_active, cand_*), with the same meaning, layout and results:
  * cand_job / cand_cut / cand_score equal what sja_select would report after
  * sja_fit on the same inputs.  No cut matrix and no interest rows exist
- * afterwards: sja_select needs a sja_fit of its own; sja_resolve works (its
- * candidate lists need no matrix, and where they cannot run - more than 64
- * distinct capacities, the lists are built per capacity class - its scanning
- * rounds evaluate the pairs again each round instead of reading a matrix).
+ * afterwards: sja_select needs a sja_fit of its own; sja_resolve works (small
+ * batches and candidate lists need no matrix, and where lists cannot run - beyond
+ * a small batch with more than 64 distinct capacities, they are built per
+ * capacity class - its scanning rounds evaluate the pairs again each round
+ * instead of reading a matrix).
  * Only enqueues work.
- * With sja_enable_timing the events bracket this call's stepping kernel.
+ * With sja_enable_timing the events bracket this call's pair evaluation.
  */
 int sja_fit_select(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W, const int32_t *C,
                    const sja_params *params, const int32_t *wait, const uint8_t *sla_class,
@@ -423,26 +424,37 @@ int sja_last_fit_kernel_ms(sja_ctx *ctx, float *ms_host);
  * sja_fit_select - but computes nothing: cut[g][j] = j afterwards.  Its
  * duration is what the memory system allows for that address pattern, the
  * ceiling the pair-evaluation kernel is measured against.  Needs the plan of
- * the last sja_fit / sja_fit_select (SJA_ERR_STATE otherwise); if `cut` is the
+ * the last sja_fit / sja_fit_select (SJA_ERR_STATE otherwise; a small batch, see
+ * sja_set_resolve_mode, is planned by this call); if `cut` is the
  * matrix that sja_fit wrote, that matrix is gone and sja_select / matrix rounds
  * need a new sja_fit.  Only enqueues work.
  */
 int sja_store_reference(sja_ctx *ctx, void *stream, int32_t *cut);
 
 /*
- * How sja_resolve runs the rounds of Sec. 3.5's grant phase.  Both modes give
+ * How sja_resolve runs the rounds of Sec. 3.5's grant phase.  All modes give
  * the same grants, rounds_used and stable flag; they differ in speed only.
- *   SJA_RESOLVE_LISTS   per-gap candidate lists in preference order, one cheap
- *                       launch per round (the default).  Falls back to the
- *                       other mode by itself with more than 64 distinct
- *                       capacities or when the lists would not fit the workspace.
+ * A batch of up to 1024 gaps, 4096 jobs and 2^21 pairs is small: fitted with
+ * SJA_RESOLVE_LISTS in force, its pairs are evaluated one by one, whatever the
+ * capacities, and its gaps are neither ordered nor planned.  The mode in force
+ * at sja_fit / sja_fit_select decides that; sja_resolve honours a mode set later
+ * (SJA_RESOLVE_MATRIX scans the unordered gaps, SJA_RESOLVE_LISTS_LOOKUP makes
+ * the plan first).
+ *   SJA_RESOLVE_LISTS   the default.  Small batches: the jobs that fit, in
+ *                       preference order per gap, and all rounds in one thread
+ *                       block.  Else candidate lists in preference order, shared
+ *                       by neighbouring gaps; rounds are launched one by one, or
+ *                       played by one thread block, one by one or in batches, as
+ *                       their work suggests.  Falls back to the scanning rounds by
+ *                       itself with more than 64 distinct capacities or when the
+ *                       lists would not fit the workspace.
  *   SJA_RESOLVE_MATRIX  every round re-scans the gaps that are still
  *                       ungranted: the rows of the cut matrix after sja_fit,
  *                       the pairs themselves (evaluated again, nothing stored)
  *                       after sja_fit_select.
- *   SJA_RESOLVE_LISTS_LOOKUP  the same as SJA_RESOLVE_LISTS (once a form that
- *                       looked the job of a list record up; every list entry
- *                       now carries its job).
+ *   SJA_RESOLVE_LISTS_LOOKUP  SJA_RESOLVE_LISTS with the forms of larger batches
+ *                       for small ones, too (once a form that looked the job of a
+ *                       list record up; every list entry now carries its job).
  * SJA_ERR_SIZE for any other value.
  */
 typedef enum {

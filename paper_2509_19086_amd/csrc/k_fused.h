@@ -478,7 +478,7 @@ __global__ __launch_bounds__(256) void k_fused_reduce(int n_gaps, int n_job_tile
 // positions by a table in LDS and raise the largest key there.  Then those jobs are looked through again for the keys that
 // are exactly the largest, the lowest of them counts (under MIXED the one with the largest F: a third time, if a
 // position has several).  Work per atom of few jobs instead of per pair: what is left are the tables of the plan and the
-// trips for the jobs' ends.  32768 gaps x 65536 jobs 1607 -> 293 us (with every atom looked at 856), a call 1768 -> 489;
+// trips for the jobs' ends.  32768 gaps x 65536 jobs 1607 -> 293 us (with every atom looked at 856), a call 1768 -> 434;
 // 2048 x 8192 80 -> 21 us, 1777 x 6151 with the area score 102 -> 59.
 constexpr int kRangeThreads = 256, kRangeLanes = 16, kRangeGroups = kRangeThreads / kRangeLanes;
 constexpr int kRangeBatches = 8;            // batches of kRangeThreads jobs per block, at most,

@@ -887,7 +887,10 @@ constexpr int kWideChunk = 4 * kWave;    // records a wave reads at a time, four
 // block stand together k_grant_round's one wave is quicker (Stress, 566 list blocks, from some hundred rounds on:
 // 5.5 against 8.7).
 constexpr int kWideBlocks = 1024;        // list blocks: beyond that the waves come in several turns
-constexpr int kWideRounds = 256;         // the rounds it is used for (all of them at Stress: 3 ms slower; none: 1 ms)
+// Gaps stand the further apart the earlier the round.  A resolve with the first 64, 128, 256 and 512 rounds so: Stress 41.0,
+// 41.0, 40.7 and 41.9 ms (MIXED), 4096 gaps x 16384 jobs 4.75, 4.25, 4.25 and 4.26, 8192 x 8192 9.38, 8.45, 8.41 and 8.54
+// (FAIRNESS); Medium and 8192 x 32768 within 3 %.
+constexpr int kWideRounds = 256;
 
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void k_grant_wide(

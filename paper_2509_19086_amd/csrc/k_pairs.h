@@ -22,7 +22,8 @@ constexpr int kPairsGaps = 1024;            // a thread per gap in k_rounds_pair
 constexpr int kPairsJobs = 4096;            // a gap's keys are put in order in LDS
 // Pairs up to which all of it is faster.  fit -> select by itself decides: 51 us at 1024 x 2048 against 54 in the
 // ordered form, 77 against 54 at 1024 x 4096 (a fit takes 20 against 67 and 38 against 69, a tick as above and 607
-// against 767).
+// against 767).  Where all gaps are alike the ordered form has next to nothing to do: 512 equal gaps x 4096 jobs 41 us
+// against 65 so, but the rounds that follow, a grant each, 1005 against 385.
 constexpr int64_t kPairsMost = 1 << 21;
 constexpr int kPairsQ = 4;                  // pairs a thread searches side by side: their loads overlap
 constexpr int kPairsThreads = 256;           // of a block of k_fit_pairs;

@@ -116,7 +116,8 @@ def test_many_capacity_classes(engine, oracle, n_classes):
 
 
 def test_the_lookup_mode_is_an_alias(engine, oracle):
-    """SJA_RESOLVE_LISTS_LOOKUP, once a form of the lists of its own, is taken and gives the same grants."""
+    """SJA_RESOLVE_LISTS_LOOKUP, once a form of the lists of its own, is taken and gives the same grants (of a batch
+    fitted pair by pair, too, which it plans first)."""
     full_tick_check(engine, oracle, make_workload("small", 6), policies=[3], resolve_modes=(2,))
 
 
