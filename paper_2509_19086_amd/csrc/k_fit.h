@@ -290,16 +290,21 @@ __global__ __launch_bounds__(256) void k_gap_plan(int n_gaps, int gc, int sb, in
 //                   duration <= the class's largest window)
 // A block takes kStartsJobs consecutive jobs: their atoms go to LDS once
 // (coalesced), then every lane keeps one of the jobs (lane % kStartsJobs) and
-// the lanes run along the classes and along the rows, each lane with a binary
-// search of its own: both counts are "how many atoms have a running duration
-// (peak) of at most x", and both sequences ascend.  A wave's store is then four
-// rows of sixteen consecutive jobs, 64 bytes each (a wave per job, lanes along
-// the rows, wrote every value into a cache line of its own: 0.6 ms for 565 rows
-// of the Stress workload against 0.14).
+// the lanes run along the classes and along the rows, each lane with binary
+// searches of its own: both counts are "how many atoms have a running duration
+// (peak) of at most x", and both sequences ascend.  A wave's store is then eight
+// rows of eight consecutive jobs, 32 bytes each; neighbouring blocks share an XCD,
+// so that its L2 puts the pieces of a line together.  With that, four rows a lane
+// searched side by side, and the jobs' atoms one behind the other in LDS (18 KB
+// where places of 512 atoms a job took 45, three blocks a compute unit) the table of
+// 72 rows x 65536 jobs takes 76 us where it took 106.
 // --------------------------------------------------------------------------
-constexpr int kStartsAtoms = 512;           // atoms of a job kept in LDS (more: the rest is read from memory)
 constexpr int kStartsJobs = 8;              // consecutive jobs of a block
-constexpr int kStartsRows = 1024;           // rows whose window and class are kept in LDS
+constexpr int kStartsAtoms = 2048;          // atoms of theirs that are kept in LDS (the rest is read from memory)
+constexpr int kStartsRows = 512;            // rows whose window and class are kept in LDS
+constexpr int kStartsQ = 4;                 // rows a lane searches side by side
+
+__host__ __device__ inline int starts_tiles(int n_jobs) { return (n_jobs + kStartsJobs - 1) / kStartsJobs; }
 
 __global__ __launch_bounds__(256) void k_fit_starts(
     int n_jobs, const int32_t *__restrict__ plan, const int32_t *__restrict__ class_begin,
@@ -309,75 +314,100 @@ __global__ __launch_bounds__(256) void k_fit_starts(
     int32_t *__restrict__ start_tab, int32_t *__restrict__ ncap_tab)
 {
     constexpr int GROUPS = 256 / kStartsJobs;                  // rows (or classes) a block takes per step
-    __shared__ int2 s_at[kStartsJobs][kStartsAtoms + 1];       // padded: equal places of different jobs in different banks
-    __shared__ int s_n[kStartsJobs];
+    constexpr int Q = kStartsQ;
+    __shared__ int s_dur[kStartsAtoms], s_peak[kStartsAtoms];  // the jobs' atoms, one job behind the other
     __shared__ int s_roww[kStartsRows];
-    __shared__ int s_rowc[kStartsRows];
+    __shared__ uint8_t s_rowc[kStartsRows];
     __shared__ int s_cap[kMaxClasses], s_wmax[kMaxClasses];
     __shared__ int s_ncap[kMaxClasses][kStartsJobs];
     if (!plan[kPlanTabled]) return;
     const int n_classes = plan[kPlanClasses], n_rows = plan[kPlanChunks];
     const int tid = threadIdx.x;
+    const int n_tiles = starts_tiles(n_jobs), tile = int(blockIdx.x & 7) * ((n_tiles + 7) / 8) + int(blockIdx.x >> 3);
+    if (int(blockIdx.x >> 3) >= (n_tiles + 7) / 8 || tile >= n_tiles) return;
     for (int q = tid; q < min(n_rows, kStartsRows); q += 256) {
         s_roww[q] = gap_w[row_begin[q]];
-        s_rowc[q] = row_class[q];
+        s_rowc[q] = uint8_t(row_class[q]);
     }
     if (tid < n_classes) {
         s_cap[tid] = gap_c[class_begin[tid]];
         s_wmax[tid] = gap_w[class_begin[tid + 1] - 1];
     }
-    const int j0 = blockIdx.x * kStartsJobs;
-    {
-        // staging: GROUPS threads per job
-        const int jl = tid / GROUPS, sub = tid % GROUPS, j = j0 + jl;
-        int n = 0;
-        if (j < n_jobs) {
-            n = n_atoms[j];
-            // eight loads in flight per thread: one trip per 8 * GROUPS atoms, not one per GROUPS
-            const int2 *src = atom_dp + seg_off[j];
-            const int lim = min(n, kStartsAtoms);
-            for (int a0 = sub; a0 < lim; a0 += 8 * GROUPS) {
-                int2 v[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) v[t] = src[min(a0 + t * GROUPS, lim - 1)];
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    if (a0 + t * GROUPS < lim) s_at[jl][a0 + t * GROUPS] = v[t];
-            }
-        }
-        if (sub == 0) s_n[jl] = n;
-    }
-    __syncthreads();
+    const int j0 = tile * kStartsJobs;
     const int jl = tid % kStartsJobs, group = tid / kStartsJobs, j = j0 + jl;
     const bool live = j < n_jobs;
-    const int n = s_n[jl];
-    const int2 *dp = atom_dp + (live ? seg_off[j] : 0);
-    auto atom = [&](int a) { return a < kStartsAtoms ? s_at[jl][a] : dp[a]; };
-    auto count_dur = [&](int w) {               // atoms with running duration <= w
-        int lo = 0, hi = n;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (atom(mid).x <= w) lo = mid + 1; else hi = mid;
+    // every eight lanes: their jobs' atoms, and where each job's begin
+    const int n = live ? n_atoms[j] : 0;
+    const int64_t base = live ? seg_off[j] : 0;
+    int off = n;
+#pragma unroll
+    for (int d = 1; d < kStartsJobs; d <<= 1) {
+        const int o = __shfl_up(off, d, kStartsJobs);
+        if (jl >= d) off += o;
+    }
+    off = min(off - n, kStartsAtoms);
+    const int kept = min(n, kStartsAtoms - off);
+    {
+        // staging: GROUPS threads per job, eight loads in flight per thread
+        const int from_lane = (tid & (kWave - 1) & ~(kStartsJobs - 1)) + tid / GROUPS, sub = tid % GROUPS;
+        const int to = __shfl(off, from_lane, kWave), lim = __shfl(kept, from_lane, kWave);
+        const int2 *src = atom_dp + __shfl((long long)base, from_lane, kWave);
+        for (int a0 = sub; a0 < lim; a0 += 8 * GROUPS) {
+            int2 v[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] = src[min(a0 + t * GROUPS, lim - 1)];
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (a0 + t * GROUPS < lim) { s_dur[to + a0 + t * GROUPS] = v[t].x; s_peak[to + a0 + t * GROUPS] = v[t].y; }
         }
-        return lo;
-    };
-    for (int c = group; c < n_classes; c += GROUPS) {
-        const int cap = s_cap[c];
-        int lo = 0, hi = n;                     // atoms with running peak <= cap
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (atom(mid).y <= cap) lo = mid + 1; else hi = mid;
-        }
-        const int reach = min(lo, count_dur(s_wmax[c]));
-        s_ncap[c][jl] = reach;
-        if (live) ncap_tab[int64_t(c) * n_jobs + j] = reach;
     }
     __syncthreads();
-    for (int q = group; q < n_rows; q += GROUPS) {
-        const int w = q < kStartsRows ? s_roww[q] : gap_w[row_begin[q]];
-        const int c = q < kStartsRows ? s_rowc[q] : row_class[q];
-        const int v = min(count_dur(w), s_ncap[c][jl]);
-        if (live) start_tab[int64_t(q) * n_jobs + j] = v;
+    const int2 *dp = atom_dp + base;
+    auto dur_of = [&](int a) { return a < kept ? s_dur[off + a] : dp[a].x; };
+    auto peak_of = [&](int a) { return a < kept ? s_peak[off + a] : dp[a].y; };
+    for (int c = group; c < n_classes; c += GROUPS) {
+        const int cap = s_cap[c], w = s_wmax[c];
+        int lo = 0, hi = n;                     // atoms with running peak <= cap,
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (peak_of(mid) <= cap) lo = mid + 1; else hi = mid;
+        }
+        hi = lo;                                // of these the ones with running duration <= w
+        lo = 0;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (dur_of(mid) <= w) lo = mid + 1; else hi = mid;
+        }
+        s_ncap[c][jl] = lo;
+        if (live) ncap_tab[int64_t(c) * n_jobs + j] = lo;
+    }
+    __syncthreads();
+    for (int q0 = group; q0 < n_rows; q0 += Q * GROUPS) {
+        int w[Q], lo[Q], hi[Q];
+        int most = 0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int q = min(q0 + i * GROUPS, n_rows - 1);
+            w[i] = q < kStartsRows ? s_roww[q] : gap_w[row_begin[q]];
+            lo[i] = 0;
+            hi[i] = s_ncap[q < kStartsRows ? int(s_rowc[q]) : row_class[q]][jl];
+            most = max(most, hi[i]);
+        }
+        for (; most > 0; most >>= 1) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                const int mid = (lo[i] + hi[i]) >> 1;
+                if (lo[i] < hi[i]) {
+                    if (dur_of(mid) <= w[i]) lo[i] = mid + 1; else hi[i] = mid;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int q = q0 + i * GROUPS;
+            if (q >= n_rows) break;
+            if (live) start_tab[int64_t(q) * n_jobs + j] = lo[i];
+        }
     }
 }
 

@@ -683,8 +683,7 @@ int enqueue_gap_plan(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_ga
                            ws_ptr<int32_t>(ctx, L.sub_end), ws_ptr<int32_t>(ctx, L.gap_cls),
                            ws_ptr<int32_t>(ctx, L.gap_run_end));
         SJA_HIP(hipGetLastError(), "k_gap_plan launch");
-        const int jobs_per_block = kStartsJobs;
-        hipLaunchKernelGGL(k_fit_starts, dim3((J + jobs_per_block - 1) / jobs_per_block), b256, 0, st, J, plan,
+        hipLaunchKernelGGL(k_fit_starts, dim3((starts_tiles(J) + 7) / 8 * 8), b256, 0, st, J, plan,
                            ws_ptr<int32_t>(ctx, L.class_begin), ws_ptr<int32_t>(ctx, L.chunk_begin),
                            ws_ptr<int32_t>(ctx, L.chunk_class), gw, gcap, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
                            ws_ptr<int32_t>(ctx, L.n_atoms), ws_ptr<int32_t>(ctx, L.start_tab),
