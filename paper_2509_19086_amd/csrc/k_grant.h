@@ -26,6 +26,7 @@
 //      (k_grant_solo).
 #pragma once
 
+#include "k_policy.h"
 #include "k_sort.h"
 
 namespace sja {
@@ -37,73 +38,19 @@ constexpr int kEntryJobShift = 13, kEntryBlockShift = 37, kEntryPlaceShift = 30,
 constexpr int kPlacedBlocks = 1 << (kEntryPlacedBlockShift - kEntryPlaceShift - 6), kPlacedJobs = 1 << (kEntryPlaceShift - kEntryJobShift);
 static_assert(SJA_MAX_JOBS <= 1 << (kEntryBlockShift - kEntryJobShift), "job ids fit an entry");
 
-struct PolicyDev {
-    int policy;
-    int wait_scale;
-    int w0, w1, w2;
-    int class0_override;
-};
-
-// Per-job multiplier and tier of the policy key: key = (tier, F * mult [, F]).
-__device__ __forceinline__ void job_policy(const PolicyDev &pol, const int32_t *wait,
-                                           const uint8_t *sla_class, int j,
-                                           unsigned long long &mult, unsigned long long &tier)
-{
-    const int cls = sla_class ? sla_class[j] : 0;
-    const long long wt = wait ? wait[j] : 0;
-    mult = 1;
-    tier = 0;
-    switch (pol.policy) {
-    case SJA_POLICY_FAIRNESS: mult = (unsigned long long)(pol.wait_scale + wt); break;
-    case SJA_POLICY_SLA:
-        mult = (unsigned long long)(cls == 0 ? pol.w0 : (cls == 1 ? pol.w1 : pol.w2));
-        tier = (pol.class0_override && cls == 0) ? 1 : 0;
-        break;
-    case SJA_POLICY_MIXED:
-        mult = (unsigned long long)(pol.wait_scale + wt);
-        tier = (unsigned long long)(2 - cls);
-        break;
-    default: break;
-    }
-}
-
-// F = duration x peak and F x multiplier with as few of the (slow) 32-bit integer
-// multiplies as the value ranges allow: durations, peaks and multipliers are
-// non-negative and fit 32 bits, and a score stays below 2^62.
-__device__ __forceinline__ unsigned long long rect_of(int dur, int peak)
-{
-    return static_cast<unsigned long long>(uint32_t(dur)) * uint32_t(peak);
-}
-
-__device__ __forceinline__ unsigned long long times_mult(unsigned long long F, unsigned long long mult)
-{
-    const uint32_t m = uint32_t(mult);            // wait_scale + wait, or an SLA weight: below 2^32
-    return static_cast<unsigned long long>(uint32_t(F)) * m +
-           (static_cast<unsigned long long>(uint32_t(F >> 32) * m) << 32);
-}
-
-// reach[j] = atoms of job j that some capacity class can reach; reach[n_jobs] = 0.
-__global__ void k_reach(int n_jobs, const int32_t *__restrict__ plan, const int32_t *__restrict__ ncap_tab,
+// reach[j] = atoms of job j that some capacity class can reach; reach[n_jobs] = 0.  all_classes: ncap_tab already has
+// that in its first row.
+__global__ void k_reach(int n_jobs, const int32_t *__restrict__ plan, const int32_t *__restrict__ ncap_tab, int all_classes,
                         int32_t *__restrict__ reach)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j > n_jobs) return;
     int r = 0;
     if (j < n_jobs && plan[kPlanTabled]) {
-        const int n_classes = plan[kPlanClasses];
+        const int n_classes = all_classes ? 1 : plan[kPlanClasses];
         for (int c = 0; c < n_classes; ++c) r = max(r, ncap_tab[int64_t(c) * n_jobs + j]);
     }
     reach[j] = r;
-}
-
-// The leading 32 bits of a key as they matter: tier, exponent and the leading bits of the score, which grow with
-// the key.  Scores spread over tens of octaves, so a byte of this orders more than a byte of the key.
-__device__ __forceinline__ uint32_t key_digest(const PolicyDev &pol, unsigned long long tier, unsigned long long score)
-{
-    const int tier_bits = pol.policy == SJA_POLICY_MIXED ? 2 : pol.policy == SJA_POLICY_SLA ? 1 : 0, rest = 26 - tier_bits;
-    const int e = score ? 63 - __clzll((long long)score) : 0;
-    const unsigned long long mantissa = e ? score << (64 - e) : 0ull;
-    return (tier_bits ? uint32_t(tier) << (32 - tier_bits) : 0u) | (uint32_t(e) << rest) | uint32_t(mantissa >> (64 - rest));
 }
 
 // Whether digests tell atoms apart depends on the keys: many jobs of one profile, their waits a thousandth apart, have

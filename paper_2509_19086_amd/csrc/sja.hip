@@ -130,25 +130,28 @@ PolicyDev to_dev(const sja_params *p)
     return d;
 }
 
-// Enqueues the select kernels; outputs may be user or workspace arrays.  The
+// Blocks of a launch that returns at once if the plan, which only the device knows, rules its form out: many empty
+// ones take longer (131072 of k_select_pass 25 us).  As many as the chip holds at once.
+constexpr unsigned kSparseGrid = 2048;
+constexpr int64_t kSelectByAtoms = int64_t(1) << 24, kFloorLeast = int64_t(11) << 15;
+
+// Enqueues the pass over the cut matrix, which leaves partial bests per job tile.  The
 // per-prefix keys live in the space the list building of sja_resolve uses for
 // its atom keys (the two never run at the same time); `keys_ready` says that an
 // earlier call with the same policy inputs left them there and nothing has
-// written that space since.
-int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const int32_t *wait,
-                  const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active,
-                  int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool keys_ready = false)
+// written that space since.  With unless_tabled (the plan) the kernels do nothing where that has class tables.
+int launch_matrix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params, const int32_t *wait,
+                       const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active, const int32_t *unless_tabled,
+                       bool keys_ready)
 {
-    const Layout L = make_layout(ctx->n_gaps, ctx->n_jobs, ctx->n_segments);
-    const int G = ctx->n_gaps, J = ctx->n_jobs;
-    if (G == 0) return SJA_OK;
-    const int job_tiles = (J + kSelBlock - 1) / kSelBlock;
+    const int G = ctx->n_gaps, J = ctx->n_jobs, job_tiles = (J + kSelBlock - 1) / kSelBlock;
     unsigned long long *seg_key = ws_ptr<unsigned long long>(ctx, L.g_key_hi);
     if (job_tiles > 0 && !keys_ready) {
         const int per_wave = keys_jobs_per_wave(J, ctx->n_segments);
-        hipLaunchKernelGGL(k_select_keys, dim3((J + 4 * per_wave - 1) / (4 * per_wave)), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
+        const unsigned key_blocks = unsigned((J + 4 * per_wave - 1) / (4 * per_wave));
+        hipLaunchKernelGGL(k_select_keys, dim3(unless_tabled && key_blocks > kSparseGrid ? kSparseGrid : key_blocks), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
                            ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class,
-                           ctx->pre_dur, ctx->pre_peak, pre_area_of(ctx, L), keys_dense(ctx->n_segments, ctx->hyst_used_n_caps > 0), per_wave, seg_key);
+                           ctx->pre_dur, ctx->pre_peak, pre_area_of(ctx, L), keys_dense(ctx->n_segments, ctx->hyst_used_n_caps > 0), per_wave, unless_tabled, seg_key);
         SJA_HIP(hipGetLastError(), "k_select_keys launch");
     }
     if (job_tiles > 0) {
@@ -157,12 +160,25 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
         const unsigned grid = unsigned(tiles8) * unsigned(n_chunks);
         const bool mixed = params->policy == SJA_POLICY_MIXED;
         auto kern = mixed ? k_select_pass<true> : k_select_pass<false>;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kSelBlock), 0, st, J, G, n_chunks,
+        hipLaunchKernelGGL(kern, dim3(unless_tabled && grid > kSparseGrid ? kSparseGrid : grid), dim3(kSelBlock), 0, st, J, G, n_chunks, grid,
                            to_dev(params), ctx->seg_off, seg_key, ctx->cut,
-                           ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active,
+                           ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active, unless_tabled,
                            ws_ptr<SelPartial>(ctx, L.sel_part));
         SJA_HIP(hipGetLastError(), "k_select_pass launch");
     }
+    return SJA_OK;
+}
+
+// The select from the cut matrix; outputs may be user or workspace arrays.
+int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const int32_t *wait,
+                  const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active,
+                  int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool keys_ready = false)
+{
+    const Layout L = make_layout(ctx->n_gaps, ctx->n_jobs, ctx->n_segments);
+    const int G = ctx->n_gaps, job_tiles = (ctx->n_jobs + kSelBlock - 1) / kSelBlock;
+    if (G == 0) return SJA_OK;
+    const int rc = launch_matrix_pass(ctx, st, L, params, wait, sla_class, job_held, gap_active, nullptr, keys_ready);
+    if (rc != SJA_OK) return rc;
     hipLaunchKernelGGL(k_select_reduce, dim3((G + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, G, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), cand_job, cand_cut, cand_score);
     SJA_HIP(hipGetLastError(), "k_select_reduce launch");
@@ -298,7 +314,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
                            sub_begin, sub_end, gap_w, lb_off, lb_begin, lb_end, pos_block, pos_tab);
     }
     SJA_HIP(hipGetLastError(), "list block launch");
-    hipLaunchKernelGGL(k_reach, dim3((J + 1 + 255) / 256), dim3(256), 0, st, J, plan, ncap_tab, abase);
+    hipLaunchKernelGGL(k_reach, dim3((J + 1 + 255) / 256), dim3(256), 0, st, J, plan, ncap_tab, int(ctx->reach_only), abase);
     SJA_HIP(hipGetLastError(), "k_reach launch");
     SJA_HIP(enqueue_scan(st, abase, int64_t(J) + 1, tmp, counters + 2), "atom scan launch");
     // policy keys of the atoms and the bytes in which they differ
@@ -647,8 +663,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     return SJA_OK;
 }
 
-// Gap ordering, capacity classes, chunk / sub-block plan and the start tables
-// for a batch of gaps: everything the stepping kernels need before they run.
+// Gap ordering, capacity classes and chunk / sub-block plan of a batch of gaps.
 int enqueue_gap_plan(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const int32_t *W, const int32_t *C)
 {
     const int J = ctx->n_jobs;
@@ -683,13 +698,21 @@ int enqueue_gap_plan(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_ga
                            ws_ptr<int32_t>(ctx, L.sub_end), ws_ptr<int32_t>(ctx, L.gap_cls),
                            ws_ptr<int32_t>(ctx, L.gap_run_end));
         SJA_HIP(hipGetLastError(), "k_gap_plan launch");
-        hipLaunchKernelGGL(k_fit_starts, dim3((starts_tiles(J) + 7) / 8 * 8), b256, 0, st, J, plan,
-                           ws_ptr<int32_t>(ctx, L.class_begin), ws_ptr<int32_t>(ctx, L.chunk_begin),
-                           ws_ptr<int32_t>(ctx, L.chunk_class), gw, gcap, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
-                           ws_ptr<int32_t>(ctx, L.n_atoms), ws_ptr<int32_t>(ctx, L.start_tab),
-                           ws_ptr<int32_t>(ctx, L.ncap_tab));
-        SJA_HIP(hipGetLastError(), "k_fit_starts launch");
     }
+    return SJA_OK;
+}
+
+// The start tables: what the stepping kernels still need.
+int enqueue_starts(sja_ctx *ctx, hipStream_t st, const Layout &L)
+{
+    const int J = ctx->n_jobs;
+    if (J == 0) return SJA_OK;
+    hipLaunchKernelGGL(k_fit_starts, dim3((starts_tiles(J) + 7) / 8 * 8), dim3(256), 0, st, J, ws_ptr<int32_t>(ctx, L.plan),
+                       ws_ptr<int32_t>(ctx, L.class_begin), ws_ptr<int32_t>(ctx, L.chunk_begin), ws_ptr<int32_t>(ctx, L.chunk_class),
+                       ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_c), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
+                       ws_ptr<int32_t>(ctx, L.n_atoms), ws_ptr<int32_t>(ctx, L.start_tab), ws_ptr<int32_t>(ctx, L.ncap_tab));
+    SJA_HIP(hipGetLastError(), "k_fit_starts launch");
+    ctx->reach_only = false;
     return SJA_OK;
 }
 
@@ -714,7 +737,8 @@ int plan_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L)
     const size_t bytes = size_t(ctx->n_gaps) * 4;
     SJA_HIP(hipMemcpyAsync(W, ws_ptr<int32_t>(ctx, L.gap_w), bytes, hipMemcpyDeviceToDevice, st), "gap copy");
     SJA_HIP(hipMemcpyAsync(C, ws_ptr<int32_t>(ctx, L.gap_c), bytes, hipMemcpyDeviceToDevice, st), "gap copy");
-    const int rc = enqueue_gap_plan(ctx, st, L, ctx->n_gaps, W, C);
+    int rc = enqueue_gap_plan(ctx, st, L, ctx->n_gaps, W, C);
+    if (rc == SJA_OK) rc = enqueue_starts(ctx, st, L);
     if (rc == SJA_OK) ctx->pairs = false;
     return rc;
 }
@@ -797,19 +821,148 @@ int launch_best_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_g
     return ctx->timing ? mark_kernel(ctx, st, true) : SJA_OK;
 }
 
+// The best job per gap by atoms (k_floor.h).  The intermediate results take the space of the list entries, of the
+// records and of the partials.
+FloorArgs floor_args(sja_ctx *ctx, const Layout &L, int32_t n_gaps, const sja_params *params, const int32_t *wait, const uint8_t *sla_class,
+                     const int32_t *job_held)
+{
+    FloorArgs args{};
+    const int64_t room = L.entry_cap * 2 / (kFloorFirstBlocks + 3);
+    args.pol = to_dev(params);
+    args.n_jobs = ctx->n_jobs;
+    args.n_gaps = n_gaps;
+    args.room = int(room < kFloorBuckets ? room : kFloorBuckets);
+    args.seg_off = ctx->seg_off;
+    args.atom_dp = ws_ptr<int2>(ctx, L.atom_dp);
+    args.atom_area = atom_area_of(ctx, L);
+    args.n_atoms = ws_ptr<int32_t>(ctx, L.n_atoms);
+    args.plan = ws_ptr<int32_t>(ctx, L.plan);
+    args.class_begin = ws_ptr<int32_t>(ctx, L.class_begin);
+    args.gap_w = ws_ptr<int32_t>(ctx, L.gap_w);
+    args.gap_c = ws_ptr<int32_t>(ctx, L.gap_c);
+    args.wait = wait;
+    args.sla_class = sla_class;
+    args.job_held = job_held;
+    args.near = ws_ptr<ulonglong2>(ctx, L.g_ekey0);            // (an entry per segment: entry_cap has two of half its size)
+    args.near_job = ws_ptr<ulonglong2>(ctx, L.g_rec);
+    args.floors = ws_ptr<uint32_t>(ctx, L.g_ekey1);
+    args.floor = args.floors + int64_t(kFloorFirstBlocks) * args.room;
+    args.running = args.floor + args.room;
+    args.bucket_pos = reinterpret_cast<int32_t *>(args.running + args.room);
+    args.n_near = ws_ptr<int32_t>(ctx, L.g_list_off);
+    static_assert(kMaxClasses * kListSplits > kFloorBlocks, "room for n_near");
+    args.best = ws_ptr<unsigned long long>(ctx, L.sel_part);
+    args.second = args.best + n_gaps;
+    args.who = reinterpret_cast<int32_t *>(args.second + n_gaps);
+    static_assert(sizeof(SelPartial) >= 20, "a partial per gap has room for them");
+    return args;
+}
+
+// With `reach` the atoms that any class can reach are noted for the lists of sja_resolve, too.
+int launch_floor(sja_ctx *ctx, hipStream_t st, const Layout &L, FloorArgs args, bool reach)
+{
+    const int J = ctx->n_jobs, blocks = floor_blocks_of(J, kFloorBlocks);
+    const int floor_step = floor_step_of(J), floor_blocks = floor_blocks_of((J + floor_step - 1) / floor_step, kFloorFirstBlocks);
+    if (reach) args.reach = ws_ptr<int32_t>(ctx, L.ncap_tab);
+    const bool area = args.atom_area != nullptr;
+    hipLaunchKernelGGL(area ? k_floor_first<true> : k_floor_first<false>, dim3(floor_blocks), dim3(kFloorThreads), 0, st, args, floor_step);
+    SJA_HIP(hipGetLastError(), "k_floor_first launch");
+    hipLaunchKernelGGL(k_floor_merge, dim3((args.room + kFloorMergeEntries - 1) / kFloorMergeEntries), dim3(kFloorMergeThreads), 0, st, args, floor_blocks);
+    SJA_HIP(hipGetLastError(), "k_floor_merge launch");
+    hipLaunchKernelGGL(area ? k_floor_filter<true> : k_floor_filter<false>, dim3(blocks), dim3(kFloorThreads), 0, st, args);
+    SJA_HIP(hipGetLastError(), "k_floor_filter launch");
+    if (args.pol.policy == SJA_POLICY_MIXED) {
+        hipLaunchKernelGGL(k_floor_ties<true>, dim3(blocks), dim3(kTiesThreads), 0, st, args, 0);
+        hipLaunchKernelGGL(k_floor_ties<true>, dim3(blocks), dim3(kTiesThreads), 0, st, args, 1);
+    } else {
+        hipLaunchKernelGGL(k_floor_ties<false>, dim3(blocks), dim3(kTiesThreads), 0, st, args, 0);
+    }
+    SJA_HIP(hipGetLastError(), "k_floor_ties launch");
+    if (reach) ctx->reach_only = true;
+    return SJA_OK;
+}
+
+// The running maximum; where the plan has no class tables the best over the partials of the other form's job_tiles.
+int launch_floor_reduce(sja_ctx *ctx, hipStream_t st, const Layout &L, const FloorArgs &args, int job_tiles, bool from_matrix, const uint8_t *gap_active,
+                        int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score)
+{
+    auto kern = args.pol.policy == SJA_POLICY_MIXED ? k_floor_reduce<true> : k_floor_reduce<false>;
+    static_assert(kReduceGaps <= kFloorTile, "a grid for either form");
+    hipLaunchKernelGGL(kern, dim3((args.n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, args, floor_tile(args.n_gaps), job_tiles, int(from_matrix),
+                       ws_ptr<SelPartial>(ctx, L.sel_part), ws_ptr<int32_t>(ctx, L.gap_cls), ws_ptr<int32_t>(ctx, L.gap_order), gap_active,
+                       ws_ptr<int2>(ctx, L.atom_db), cand_job, cand_cut, cand_score);
+    SJA_HIP(hipGetLastError(), "k_floor_reduce launch");
+    return SJA_OK;
+}
+
+// Whether a select goes by the atoms or along the matrix, which takes 1.05 us per million pairs besides the keys of all cuts.
+// Matrix and atoms, us: 2048 gaps x 8192 jobs 50 and 27, 8192 x 32768 320 and 61, 886 x 13356 37 and 43, 96 x 10128 21 and
+// 22; where a table of F (area, hysteresis) makes three gathers of two and fewer atoms differ 6701 x 2866 38 and 48,
+// 10727 x 19926 230 and 68.
+bool select_by_atoms(int64_t n_gaps, int64_t n_jobs, bool table_of_F) { return n_gaps * n_jobs >= (table_of_F ? 2 * kSelectByAtoms : kSelectByAtoms); }
+
+// Which form looks for the best job per gap where the plan has class tables and the keys rise.  k_range_select looks at the
+// ends of every job in every chunk of positions, two gathers each; the k_floor_ kernels at all atoms once or twice, and
+// take 40 us of launches and short kernels, but no start tables after sja_fit_select.  k_range_select and they, us (from
+// the heavy to the light profiles), fit -> select of 20000 gaps x 8192 jobs (327000 jobs and chunks) 194 to 82 and 170 to
+// 84, a select 154 to 45 and 102 to 54; 3000 x 65536 (393000) 175 to 112 and 170 to 76, a select 120 to 64 and 140 to 55;
+// 8192 x 32768 (524000) 293 to 104 and 149 to 81; 32768 x 65536 (4.2 million) 704 to 202 and 163 to 102.
+bool by_floor(int64_t n_gaps, int64_t n_jobs)
+{
+    const int64_t len = fit_chunk_len(n_gaps, n_jobs);
+    return (n_gaps + len - 1) / len * n_jobs > kFloorLeast;
+}
+
+// k_range_select, along the start tables: partials of as many tiles of jobs as returned.
+int launch_ranges(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params, const int32_t *wait,
+                  const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active, int *tiles)
+{
+    const int J = ctx->n_jobs, chunk_bound = int(fit_chunk_bound(n_gaps, J));
+    const bool mixed = params->policy == SJA_POLICY_MIXED;
+    const long long *atom_area = atom_area_of(ctx, L);
+    const int64_t jobs_once = (J + kRangeThreads - 1) / kRangeThreads, chunks = (n_gaps + fit_chunk_len(n_gaps, J) - 1) / fit_chunk_len(n_gaps, J);
+    int batches = 1;
+    while (batches < kRangeBatches && jobs_once * chunks >= 2 * batches * int64_t(kRangeBlocks)) batches *= 2;
+    *tiles = int((jobs_once + batches - 1) / batches);
+    auto kern = atom_area ? (mixed ? k_range_select<true, true> : k_range_select<false, true>)
+                          : (mixed ? k_range_select<true, false> : k_range_select<false, false>);
+    hipLaunchKernelGGL(kern, dim3(unsigned((*tiles + 7) / 8 * 8) * unsigned(chunk_bound)), dim3(kRangeThreads), 0, st, J, n_gaps,
+                       chunk_bound, batches, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area,
+                       ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin), ws_ptr<int32_t>(ctx, L.chunk_end),
+                       ws_ptr<int32_t>(ctx, L.chunk_class), ws_ptr<int32_t>(ctx, L.start_tab), ws_ptr<int32_t>(ctx, L.ncap_tab),
+                       ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active,
+                       ws_ptr<SelPartial>(ctx, L.sel_part));
+    SJA_HIP(hipGetLastError(), "k_range_select launch");
+    return SJA_OK;
+}
+
+int launch_range_reduce(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, int job_tiles, int range_tiles, bool from_matrix,
+                        int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score)
+{
+    hipLaunchKernelGGL(k_range_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles, range_tiles, int(from_matrix),
+                       ws_ptr<SelPartial>(ctx, L.sel_part), ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.gap_w),
+                       ws_ptr<int32_t>(ctx, L.gap_c), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), ws_ptr<int2>(ctx, L.atom_db),
+                       ws_ptr<int32_t>(ctx, L.n_atoms), cand_job, cand_cut, cand_score);
+    SJA_HIP(hipGetLastError(), "k_range_reduce launch");
+    return SJA_OK;
+}
+
 // The fused fit -> select pass over the planned batch of gaps (the plan of enqueue_gap_plan is in
 // the workspace): candidates per gap among the jobs that job_held does not mark, for the gaps that
-// gap_active does not switch off.  No cut matrix is read or written.  A batch has class tables or not, and one of two
-// forms serves it, k_range_select or k_fit_select; which one, only the device knows, so both are launched and one
+// gap_active does not switch off.  No cut matrix is read or written.  A batch has class tables or not, and either
+// k_range_select or the k_floor_ kernels serve it, or k_fit_select; which, only the device knows, so both are launched and one
 // returns at once, unless the caller has seen the plan (2500 gaps of 65 capacities x 1200 jobs: 6 us of a round of 290).
+// starts: the start tables are still to be made, where they are needed.
 enum class Tabled { Unknown, No, Yes };
 int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params,
                  const int32_t *wait, const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active,
-                 int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool timed, bool searched = false, Tabled tabled = Tabled::Unknown)
+                 int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score, bool timed, bool starts, bool searched = false, Tabled tabled = Tabled::Unknown)
 {
     const int J = ctx->n_jobs;
     const int job_tiles = (J + kFusedBlock - 1) / kFusedBlock;
+    bool by_atoms = false;
     int range_tiles = 0;
+    FloorArgs args{};
     if (job_tiles > 0 && searched) {
         const bool mixed = params->policy == SJA_POLICY_MIXED;
         const long long *atom_area = atom_area_of(ctx, L);
@@ -837,23 +990,21 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
         int rc = timed ? mark_kernel(ctx, st, false) : SJA_OK;
         if (rc != SJA_OK) return rc;
         const bool rise = keys_rise(ctx);
+        const bool floor = rise && by_floor(n_gaps, J);
+        if (starts && !floor && (rc = enqueue_starts(ctx, st, L)) != SJA_OK) return rc;
         if (rise && tabled != Tabled::No) {
-            const int64_t jobs_once = (J + kRangeThreads - 1) / kRangeThreads, chunks = (n_gaps + fit_chunk_len(n_gaps, J) - 1) / fit_chunk_len(n_gaps, J);
-            int batches = 1;
-            while (batches < kRangeBatches && jobs_once * chunks >= 2 * batches * int64_t(kRangeBlocks)) batches *= 2;
-            range_tiles = int((jobs_once + batches - 1) / batches);
-            auto range_kern = atom_area ? (mixed ? k_range_select<true, true> : k_range_select<false, true>)
-                                        : (mixed ? k_range_select<true, false> : k_range_select<false, false>);
-            hipLaunchKernelGGL(range_kern, dim3(unsigned((range_tiles + 7) / 8 * 8) * unsigned(chunk_bound)), dim3(kRangeThreads), 0, st, J, n_gaps,
-                               chunk_bound, batches, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area,
-                               ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin), ws_ptr<int32_t>(ctx, L.chunk_end),
-                               ws_ptr<int32_t>(ctx, L.chunk_class), ws_ptr<int32_t>(ctx, L.start_tab), ws_ptr<int32_t>(ctx, L.ncap_tab),
-                               ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active,
-                               ws_ptr<SelPartial>(ctx, L.sel_part));
-            SJA_HIP(hipGetLastError(), "k_range_select launch");
+            by_atoms = true;
+            if (floor) {
+                args = floor_args(ctx, L, n_gaps, params, wait, sla_class, job_held);
+                rc = launch_floor(ctx, st, L, args, starts);
+            } else {
+                rc = launch_ranges(ctx, st, L, n_gaps, params, wait, sla_class, job_held, gap_active, &range_tiles);
+            }
+            if (rc != SJA_OK) return rc;
         }
         if (!rise || tabled != Tabled::Yes) {
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, int(!rise), to_dev(params),
+            const bool sparse = rise && tabled == Tabled::Unknown && grid > kSparseGrid;
+            hipLaunchKernelGGL(kern, dim3(sparse ? kSparseGrid : grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, grid, int(!rise), to_dev(params),
                                ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
                                ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin),
                                ws_ptr<int32_t>(ctx, L.chunk_end), ws_ptr<int32_t>(ctx, L.chunk_class),
@@ -866,14 +1017,8 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
         }
         if (timed && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
     }
-    if (range_tiles > 0) {
-        hipLaunchKernelGGL(k_range_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles, range_tiles,
-                           ws_ptr<SelPartial>(ctx, L.sel_part), ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.gap_w),
-                           ws_ptr<int32_t>(ctx, L.gap_c), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), ws_ptr<int2>(ctx, L.atom_db),
-                           ws_ptr<int32_t>(ctx, L.n_atoms), cand_job, cand_cut, cand_score);
-        SJA_HIP(hipGetLastError(), "k_range_reduce launch");
-        return SJA_OK;
-    }
+    if (by_atoms && range_tiles == 0) return launch_floor_reduce(ctx, st, L, args, job_tiles, false, gap_active, cand_job, cand_cut, cand_score);
+    if (by_atoms) return launch_range_reduce(ctx, st, L, n_gaps, job_tiles, range_tiles, false, cand_job, cand_cut, cand_score);
     hipLaunchKernelGGL(k_fused_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_db), cand_job,
                        cand_cut, cand_score);
@@ -1184,6 +1329,7 @@ int sja_fit(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W, const 
             if (ctx->timing && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
         } else {
             rc = enqueue_gap_plan(ctx, st, L, n_gaps, W, C);
+            if (rc == SJA_OK) rc = enqueue_starts(ctx, st, L);
             if (rc != SJA_OK) return rc;
         }
         if (J > 0 && !pairs) {
@@ -1292,7 +1438,7 @@ int sja_fit_select(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W,
         rc = enqueue_gap_plan(ctx, st, L, n_gaps, W, C);
         if (rc != SJA_OK) return rc;
         rc = launch_fused(ctx, st, L, n_gaps, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut,
-                          cand_score, ctx->timing);
+                          cand_score, ctx->timing, true);
         if (rc != SJA_OK) return rc;
     }
     ctx->n_gaps = n_gaps;
@@ -1324,7 +1470,23 @@ int sja_select(sja_ctx *ctx, void *stream, const sja_params *params, const int32
         SJA_HIP(hipGetLastError(), "k_select_pairs launch");
         return SJA_OK;
     }
-    return launch_select(ctx, st, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut, cand_score);
+    const int G = ctx->n_gaps, J = ctx->n_jobs, job_tiles = (J + kSelBlock - 1) / kSelBlock;
+    if (!keys_rise(ctx) || !select_by_atoms(G, J, atom_area_of(ctx, L) != nullptr))
+        return launch_select(ctx, st, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut, cand_score);
+    // along the plan of the fit, without reading the matrix; along the matrix if the plan has no class tables
+    const bool floor = by_floor(G, J);
+    FloorArgs args{};
+    int range_tiles = 0;
+    if (floor) {
+        args = floor_args(ctx, L, G, params, wait, sla_class, job_held);
+        rc = launch_floor(ctx, st, L, args, false);
+    } else {
+        rc = launch_ranges(ctx, st, L, G, params, wait, sla_class, job_held, gap_active, &range_tiles);
+    }
+    if (rc == SJA_OK) rc = launch_matrix_pass(ctx, st, L, params, wait, sla_class, job_held, gap_active, ws_ptr<int32_t>(ctx, L.plan), false);
+    if (rc != SJA_OK) return rc;
+    return floor ? launch_floor_reduce(ctx, st, L, args, job_tiles, true, gap_active, cand_job, cand_cut, cand_score)
+                 : launch_range_reduce(ctx, st, L, G, job_tiles, range_tiles, true, cand_job, cand_cut, cand_score);
 }
 
 int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int32_t *wait,
@@ -1418,7 +1580,7 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
                                    /*keys_ready=*/r + k > 1);
             else
                 rc = launch_fused(ctx, st, L, G, params, wait, sla_class, job_gap, active, cand_job, cand_cut, cand_score,
-                                  false, searched, tabled);
+                                  false, false, searched, tabled);
             if (rc != SJA_OK) return rc;
             const dim3 grid((G + 255) / 256), block(256);
             hipLaunchKernelGGL(k_claim, grid, block, 0, st, G, int(r) + k, active, cand_job, claim, counters + 2 * k);

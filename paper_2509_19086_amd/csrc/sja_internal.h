@@ -242,6 +242,7 @@ struct sja_ctx {
     bool planned;
     bool fitted;
     bool pairs;          // a small batch: its gaps in the caller's order, nothing else is planned
+    bool reach_only;     // ncap_tab has the atoms that any class reaches, in its first row, and start_tab nothing
     int32_t n_gaps;
     const int32_t *cut;
 };
