@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256) void k_gap_plan(int n_gaps, int gc, int sb, in
 // so that its L2 puts the pieces of a line together.  With that, four rows a lane
 // searched side by side, and the jobs' atoms one behind the other in LDS (18 KB
 // where places of 512 atoms a job took 45, three blocks a compute unit) the table of
-// 72 rows x 65536 jobs takes 76 us where it took 106.
+// 72 rows x 65536 jobs takes 63 us where it took 106.
 // --------------------------------------------------------------------------
 constexpr int kStartsJobs = 8;              // consecutive jobs of a block
 constexpr int kStartsAtoms = 2048;          // atoms of theirs that are kept in LDS (the rest is read from memory)
@@ -361,54 +361,59 @@ __global__ __launch_bounds__(256) void k_fit_starts(
                 if (a0 + t * GROUPS < lim) { s_dur[to + a0 + t * GROUPS] = v[t].x; s_peak[to + a0 + t * GROUPS] = v[t].y; }
         }
     }
-    __syncthreads();
+    // whether the jobs' atoms are all in LDS (an atom from either place would be fetched by its flat address)
+    const bool whole = __syncthreads_and(kept == n);
     const int2 *dp = atom_dp + base;
-    auto dur_of = [&](int a) { return a < kept ? s_dur[off + a] : dp[a].x; };
-    auto peak_of = [&](int a) { return a < kept ? s_peak[off + a] : dp[a].y; };
-    for (int c = group; c < n_classes; c += GROUPS) {
-        const int cap = s_cap[c], w = s_wmax[c];
-        int lo = 0, hi = n;                     // atoms with running peak <= cap,
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (peak_of(mid) <= cap) lo = mid + 1; else hi = mid;
+    auto fill = [&](auto dur_of, auto peak_of) {
+        for (int c = group; c < n_classes; c += GROUPS) {
+            const int cap = s_cap[c], w = s_wmax[c];
+            int lo = 0, hi = n;                     // atoms with running peak <= cap,
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (peak_of(mid) <= cap) lo = mid + 1; else hi = mid;
+            }
+            hi = lo;                                // of these the ones with running duration <= w
+            lo = 0;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (dur_of(mid) <= w) lo = mid + 1; else hi = mid;
+            }
+            s_ncap[c][jl] = lo;
+            if (live) ncap_tab[int64_t(c) * n_jobs + j] = lo;
         }
-        hi = lo;                                // of these the ones with running duration <= w
-        lo = 0;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (dur_of(mid) <= w) lo = mid + 1; else hi = mid;
-        }
-        s_ncap[c][jl] = lo;
-        if (live) ncap_tab[int64_t(c) * n_jobs + j] = lo;
-    }
-    __syncthreads();
-    for (int q0 = group; q0 < n_rows; q0 += Q * GROUPS) {
-        int w[Q], lo[Q], hi[Q];
-        int most = 0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const int q = min(q0 + i * GROUPS, n_rows - 1);
-            w[i] = q < kStartsRows ? s_roww[q] : gap_w[row_begin[q]];
-            lo[i] = 0;
-            hi[i] = s_ncap[q < kStartsRows ? int(s_rowc[q]) : row_class[q]][jl];
-            most = max(most, hi[i]);
-        }
-        for (; most > 0; most >>= 1) {
+        __syncthreads();
+        for (int q0 = group; q0 < n_rows; q0 += Q * GROUPS) {
+            int w[Q], lo[Q], hi[Q];
+            int most = 0;
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
-                const int mid = (lo[i] + hi[i]) >> 1;
-                if (lo[i] < hi[i]) {
-                    if (dur_of(mid) <= w[i]) lo[i] = mid + 1; else hi[i] = mid;
+                const int q = min(q0 + i * GROUPS, n_rows - 1);
+                w[i] = q < kStartsRows ? int(s_roww[q]) : gap_w[row_begin[q]];
+                lo[i] = 0;
+                hi[i] = s_ncap[q < kStartsRows ? int(s_rowc[q]) : row_class[q]][jl];
+                most = max(most, hi[i]);
+            }
+            for (; most > 0; most >>= 1) {
+                int d[Q];
+#pragma unroll
+                for (int i = 0; i < Q; ++i) d[i] = dur_of(min((lo[i] + hi[i]) >> 1, n - 1));
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    const int mid = (lo[i] + hi[i]) >> 1;
+                    const bool in = d[i] <= w[i], open = lo[i] < hi[i];
+                    lo[i] = open & in ? mid + 1 : lo[i];
+                    hi[i] = open & !in ? mid : hi[i];
                 }
             }
-        }
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const int q = q0 + i * GROUPS;
-            if (q >= n_rows) break;
-            if (live) start_tab[int64_t(q) * n_jobs + j] = lo[i];
+            for (int i = 0; i < Q; ++i) {
+                const int q = q0 + i * GROUPS;
+                if (q < n_rows && live) start_tab[int64_t(q) * n_jobs + j] = lo[i];
+            }
         }
-    }
+    };
+    if (whole) fill([&](int a) { return s_dur[off + a]; }, [&](int a) { return s_peak[off + a]; });
+    else fill([&](int a) { return dp[a].x; }, [&](int a) { return dp[a].y; });
 }
 
 // --------------------------------------------------------------------------

@@ -9,7 +9,7 @@
 //   * k_select_pairs: a thread block per gap reads the gap's row of replies;
 //   * k_order_pairs, k_rounds_pairs: a thread block per gap puts the jobs that
 //     fit in the order of their keys, and one block plays all rounds, a thread per gap.
-// A whole tick is five launches and one look.  Gaps x jobs, 256 segments each, us a tick
+// A whole tick is five launches and one look (six after sja_fit_select with many pairs).  Gaps x jobs, 256 segments each, us a tick
 // (fairness), ordered forms and so: 8 x 16 300 / 57, 256 x 1024 547 / 117, 1024 x 512 578 / 182,
 // 256 x 4096 537 / 179, 1024 x 1024 with 784 rounds 1306 / 707, 1024 x 2048 with 221 rounds 796 / 415.
 #pragma once
@@ -50,6 +50,20 @@ __device__ __forceinline__ void search_pairs(const int2 *const (&dp)[Q], const i
                 if (v[q].x <= w[q] && v[q].y <= c[q]) lo[q] = mid + 1; else hi[q] = mid;
             }
     }
+}
+
+// The same where the atoms of some pairs are known already: n is 0 for them.
+template <int Q>
+__device__ __forceinline__ void pair_atoms_or_search(const int2 *const (&dp)[Q], const int (&n)[Q], const int (&w)[Q], const int (&c)[Q], int (&at)[Q])
+{
+    int any = 0, lo[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) any |= n[q];
+    if (any == 0) return;
+    search_pairs<Q>(dp, n, w, c, lo);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (n[q] > 0) at[q] = lo[q];
 }
 
 // The gaps as they came, for the calls that follow.
@@ -135,14 +149,80 @@ __device__ __forceinline__ void pair_key(unsigned long long F, unsigned long lon
     lo = MIXED ? F : 0ull;
 }
 
+// Where the replies of a gap come from: the matrix of sja_fit; the atoms that k_pair_atoms has left; or neither, each is
+// searched.
+struct PairReplies {
+    const int32_t *cut, *pre_dur, *pre_peak;        // [gap][job], and the running tables
+    const long long *pre_area;
+    const uint16_t *atoms;                          // [gap][job]: atoms that fit (kManyAtoms: so many or more)
+};
+constexpr int kManyAtoms = 0xffff;
+
+// The atoms of every pair, job by job: a block keeps 64 jobs' atoms in LDS and goes through a share of the gaps, four at a
+// time a wave, a lane per job.  (From memory each step of a search is a trip to the caches: the best replies of 700 gaps x
+// 2501 jobs took 48 us, so 15 and 22.)
+constexpr int kAtomsThreads = 256, kAtomsJobs = kWave, kAtomsRoom = 4096, kAtomsQ = 4;
+constexpr int kAtomsGaps = 32;              // gaps of a share
+__global__ __launch_bounds__(kAtomsThreads) void k_pair_atoms(int n_gaps, int n_jobs, const int32_t *__restrict__ gap_w, const int32_t *__restrict__ gap_c,
+                                                              const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
+                                                              const int32_t *__restrict__ n_atoms, uint16_t *__restrict__ atoms)
+{
+    constexpr int WAVES = kAtomsThreads / kWave, Q = kAtomsQ;
+    __shared__ int2 s_atom[kAtomsRoom];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int j = blockIdx.x * kAtomsJobs + lane;
+    const int n = j < n_jobs ? n_atoms[j] : 0;
+    const int64_t base = j < n_jobs ? seg_off[j] : 0;
+    const int off = min(wave_scan_add(n) - n, kAtomsRoom), kept = min(n, kAtomsRoom - off);
+    for (int l = wave; l < kWave; l += WAVES) {
+        const int to = lane_value(off, l), m = lane_value(kept, l);
+        const int2 *src = atom_dp + int64_t(lane_value64((unsigned long long)base, l));
+        for (int a = lane; a < m; a += kWave) s_atom[to + a] = src[a];
+    }
+    __syncthreads();
+    const int2 *dp = atom_dp + base;
+    const bool whole = __all(kept == n);        // (the same in every wave)
+    const int g1 = min((int(blockIdx.y) + 1) * kAtomsGaps, n_gaps);
+    for (int g0 = int(blockIdx.y) * kAtomsGaps + wave * Q; g0 < g1; g0 += WAVES * Q) {
+        int w[Q], c[Q], lo[Q], hi[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int g = min(g0 + q, g1 - 1);
+            w[q] = gap_w[g];
+            c[q] = gap_c[g];
+            lo[q] = 0;
+            hi[q] = n;
+        }
+        auto search = [&](auto atom) {
+            for (int most = n; most > 0; most >>= 1) {
+                int2 v[Q];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) v[q] = atom(min((lo[q] + hi[q]) >> 1, n - 1));
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int mid = (lo[q] + hi[q]) >> 1;
+                    const bool in = (v[q].x <= w[q]) & (v[q].y <= c[q]), open = lo[q] < hi[q];
+                    lo[q] = open & in ? mid + 1 : lo[q];
+                    hi[q] = open & !in ? mid : hi[q];
+                }
+            }
+        };
+        if (whole) search([&](int a) { return s_atom[off + a]; });
+        else search([&](int a) { return dp[a]; });
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (g0 + q < g1 && j < n_jobs) atoms[int64_t(g0 + q) * n_jobs + j] = uint16_t(min(lo[q], kManyAtoms));
+    }
+}
+
 // The best reply to a gap, a block per gap.
-template <bool MIXED>
+template <bool MIXED, bool ATOMS>
 __global__ __launch_bounds__(kPairsMostThreads) void k_best_pairs(int n_jobs, PolicyDev pol, const int32_t *__restrict__ W, const int32_t *__restrict__ C,
                                                               const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp,
                                                               const int2 *__restrict__ atom_db, const long long *__restrict__ atom_area,
                                                               const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
                                                               const uint8_t *__restrict__ sla_class, const int32_t *__restrict__ job_held,
-                                                              const uint8_t *__restrict__ gap_active, PairGaps keep,
+                                                              const uint8_t *__restrict__ gap_active, PairGaps keep, const uint16_t *__restrict__ atoms,
                                                               int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut,
                                                               int64_t *__restrict__ cand_score)
 {
@@ -162,12 +242,14 @@ __global__ __launch_bounds__(kPairsMostThreads) void k_best_pairs(int n_jobs, Po
             const int j = j0 + q * int(blockDim.x);
             const bool usable = j < n_jobs && !(job_held && job_held[j] >= 0);
             base[q] = usable ? seg_off[j] : 0;
-            n[q] = usable ? n_atoms[j] : 0;
+            if (ATOMS) lo[q] = usable ? int(atoms[int64_t(g) * n_jobs + j]) : 0;
+            n[q] = usable && (!ATOMS || lo[q] == kManyAtoms) ? n_atoms[j] : 0;
             dp[q] = atom_dp + base[q];
             w[q] = gw;
             c[q] = gc;
         }
-        search_pairs<Q>(dp, n, w, c, lo);
+        if (ATOMS) pair_atoms_or_search<Q>(dp, n, w, c, lo);
+        else search_pairs<Q>(dp, n, w, c, lo);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             if (lo[q] == 0) continue;
@@ -222,46 +304,105 @@ __global__ __launch_bounds__(kPairsMostThreads) void k_select_pairs(int n_jobs, 
 // Where entry k of gap g's list is: four entries side by side, those of neighbouring gaps next to each other.
 __host__ __device__ constexpr size_t pair_list_words(int n_gaps, int most) { return size_t((most + kPairsSlots - 1) / kPairsSlots) * n_gaps; }
 
-// The jobs that fit gap blockIdx.x in the order of their keys, as many as the rounds can ask for: a gap passes
-// only jobs that other gaps hold, so it needs no more of them than there are gaps (`most`).  The jobs that fit are
-// gathered in LDS and sorted there by a bitonic network; steps within the 128 entries that a wave's threads
-// exchange need no barrier.  ROOM: a power of two, at least the number of jobs.
-template <bool MIXED, int ROOM, int Q>
-__global__ __launch_bounds__(kPairsMostThreads) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, const int32_t *__restrict__ gap_w,
-                                                                   const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
-                                                                   const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area,
-                                                                   const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
-                                                                   const uint8_t *__restrict__ sla_class, int32_t *__restrict__ list_len,
-                                                                   unsigned long long *__restrict__ list)
+// A key as 52 bits that order nearly as it does: tier, exponent and 44 bits of the score.
+__device__ __forceinline__ unsigned long long pair_digest(unsigned long long hi)
 {
-    __shared__ unsigned long long s_hi[ROOM], s_lo[MIXED ? ROOM : 1];
-    __shared__ alignas(8) uint16_t s_job[ROOM];
-    __shared__ int s_n;
-    const int g = blockIdx.x, tid = threadIdx.x, threads = blockDim.x, lane = tid & (kWave - 1);
-    auto lo_at = [&](int i) -> unsigned long long & { return s_lo[MIXED ? i : 0]; };
-    // puts the first `fit` entries in order; returns up to where there are entries, a multiple of kPairsSlots
-    auto sort = [&](int fit) {
-        int n = kPairsSlots;
-        while (n < fit) n <<= 1;
-        for (int i = fit + tid; i < n; i += threads) {
-            s_hi[i] = 0;
-            if (MIXED) lo_at(i) = 0;
-            s_job[i] = uint16_t(n_jobs);            // nobody
+    const unsigned long long key = hi - 1ull, score = key & ((1ull << 62) - 1ull);
+    const int e = score ? 63 - __clzll((long long)score) : 0;
+    const unsigned long long mantissa = e ? score << (64 - e) : 0ull;
+    return (key >> 62) << 50 | (unsigned long long)e << 44 | mantissa >> 20;
+}
+
+// The jobs that fit gap blockIdx.x in the order of their keys, as many as the rounds can ask for: a gap passes
+// only jobs that other gaps hold, so it needs no more of them than there are gaps (`most`).  A job is one word, its key's
+// digest and its number.  Where fewer jobs are needed than fit, a histogram of the digests' leading bits says down to
+// which of them to go; what is left is sorted in LDS by a bitonic network (steps within the 128 entries that a wave's
+// threads exchange need no barrier).  Neighbours of the same digest are compared by their keys, and if one pair is out of
+// order the gap's jobs are sorted anew, by all of the key.  ROOM: a power of two, at least the number of jobs.
+// 700 gaps x 2501 jobs, 700 of them each, MIXED: 60 us and 15 for k_pair_atoms, where all jobs searched and sorted by keys
+// of 128 bits took 243; 256 x 1024 from the matrix, all words sorted, 16 us where that took 26.
+constexpr int kOrderBins = 4096, kOrderBinShift = 40;
+constexpr int kOrderBinsLeast = 1024;       // room from which on a histogram pays
+static_assert(kPairsJobs <= 4096, "12 bits for a job");
+template <bool MIXED, int ROOM, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, PairReplies from, const int32_t *__restrict__ gap_w,
+                                                         const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
+                                                         const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area,
+                                                         const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
+                                                         const uint8_t *__restrict__ sla_class, int32_t *__restrict__ list_len,
+                                                         unsigned long long *__restrict__ list)
+{
+    constexpr int Q = (ROOM + THREADS - 1) / THREADS, WAVES = THREADS / kWave;
+    // the words, before them the histogram; or the keys of all jobs
+    constexpr bool BINS = ROOM >= kOrderBinsLeast;
+    constexpr int bytes = BINS && kOrderBins * 4 > ROOM * (MIXED ? 18 : 10) ? kOrderBins * 4 : ROOM * (MIXED ? 18 : 10);
+    __shared__ alignas(8) unsigned char s_room[bytes];
+    __shared__ int s_n, s_kept, s_all, s_bin, s_upto, s_bad, s_wave[WAVES];
+    unsigned long long *const s_item = reinterpret_cast<unsigned long long *>(s_room);
+    int *const s_hist = reinterpret_cast<int *>(s_room);
+    unsigned long long *const s_hi = s_item, *const s_lo = s_item + (MIXED ? ROOM : 0);
+    uint16_t *const s_job = reinterpret_cast<uint16_t *>(s_lo + ROOM);
+    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int gw = gap_w[g], gc = gap_c[g];
+    // the keys of N jobs; hi 0: it does not fit
+    auto keys = [&](auto many, const int *job, unsigned long long *hi, unsigned long long *lo) {
+        constexpr int N = decltype(many)::value;
+        unsigned long long F[N];
+        bool fits[N];
+        if (from.cut) {
+            int b[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) b[q] = job[q] < n_jobs ? from.cut[int64_t(g) * n_jobs + job[q]] : -1;
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                fits[q] = b[q] > 0;
+                const int64_t at = fits[q] ? seg_off[job[q]] + b[q] - 1 : 0;
+                F[q] = !fits[q] ? 0ull : from.pre_area ? (unsigned long long)from.pre_area[at] : rect_of(from.pre_dur[at], from.pre_peak[at]);
+            }
+        } else {
+            const int2 *dp[N];
+            int n[N], w[N], c[N], at[N];
+            int64_t base[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                base[q] = job[q] < n_jobs ? seg_off[job[q]] : 0;
+                dp[q] = atom_dp + base[q];
+                at[q] = from.atoms && job[q] < n_jobs ? int(from.atoms[int64_t(g) * n_jobs + job[q]]) : 0;
+                n[q] = job[q] < n_jobs && (!from.atoms || at[q] == kManyAtoms) ? n_atoms[job[q]] : 0;
+                w[q] = gw;
+                c[q] = gc;
+            }
+            pair_atoms_or_search<N>(dp, n, w, c, at);
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                fits[q] = at[q] > 0;
+                F[q] = 0;
+                if (!fits[q]) continue;
+                if (atom_area) {
+                    F[q] = (unsigned long long)atom_area[base[q] + at[q] - 1];
+                } else {
+                    const int2 v = dp[q][at[q] - 1];
+                    F[q] = rect_of(v.x, v.y);
+                }
+            }
         }
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            hi[q] = lo[q] = 0;
+            if (!fits[q]) continue;
+            unsigned long long mult, tier;
+            job_policy(pol, wait, sla_class, job[q], mult, tier);
+            pair_key<MIXED>(F[q], mult, tier, hi[q], lo[q]);
+        }
+    };
+    // a bitonic network over n entries, a power of two: swap(a, b) if entry b is to come before a
+    auto network = [&](int n, auto exchange) {
         __syncthreads();
         for (int k = 2; k <= n; k <<= 1) {
             for (int d = k >> 1; d > 0; d >>= 1) {
-                for (int t = tid; t < n / 2; t += threads) {
-                    const int a = 2 * t - (t & (d - 1)), b = a + d;
-                    const unsigned long long ha = s_hi[a], hb = s_hi[b];
-                    const unsigned long long la = MIXED ? lo_at(a) : 0ull, lb = MIXED ? lo_at(b) : 0ull;
-                    const uint16_t ja = s_job[a], jb = s_job[b];
-                    // the better one first, in every second stretch of k entries last
-                    if (fused_better(hb, lb, jb, ha, la, ja) == ((a & k) == 0)) {
-                        s_hi[a] = hb; s_hi[b] = ha;
-                        if (MIXED) { lo_at(a) = lb; lo_at(b) = la; }
-                        s_job[a] = jb; s_job[b] = ja;
-                    }
+                for (int t = tid; t < n / 2; t += THREADS) {
+                    const int a = 2 * t - (t & (d - 1));
+                    exchange(a, a + d, (a & k) == 0);
                 }
                 // what the next step reads was written by the same wave while it stays within 128 entries
                 const int next = d > 1 ? d >> 1 : k;
@@ -269,52 +410,132 @@ __global__ __launch_bounds__(kPairsMostThreads) void k_order_pairs(int n_gaps, i
             }
         }
         __syncthreads();
-        return n;
     };
-    if (tid == 0) s_n = 0;
+    const bool cut_off = BINS && most + most / 8 < n_jobs;
+    if (tid == 0) { s_n = s_kept = s_all = s_bad = 0; s_bin = kOrderBins; }
+    if (cut_off)
+        for (int i = tid; i < kOrderBins; i += THREADS) s_hist[i] = 0;
     __syncthreads();
-    const int gw = gap_w[g], gc = gap_c[g];
-    for (int j0 = 0; j0 < n_jobs; j0 += Q * threads) {
-        const int2 *dp[Q];
-        int n[Q], w[Q], c[Q], lo[Q];
-        int64_t base[Q];
+    unsigned long long item[Q];
+    unsigned fits = 0;                  // which of them are
+    int fit = 0;                        // of this wave's jobs
+    {
+        int job[Q];
+        unsigned long long hi[Q], lo[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) job[q] = tid + q * THREADS;
+        keys(std::integral_constant<int, Q>{}, job, hi, lo);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const int j = j0 + tid + q * threads;
-            base[q] = j < n_jobs ? seg_off[j] : 0;
-            n[q] = j < n_jobs ? n_atoms[j] : 0;
-            dp[q] = atom_dp + base[q];
-            w[q] = gw;
-            c[q] = gc;
-        }
-        search_pairs<Q>(dp, n, w, c, lo);
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int j = j0 + tid + q * threads;
-            unsigned long long mult, tier, kh = 0, kl = 0;
-            if (lo[q] > 0) {
-                job_policy(pol, wait, sla_class, j, mult, tier);
-                const int2 v = dp[q][lo[q] - 1];
-                pair_key<MIXED>(atom_area ? (unsigned long long)atom_area[base[q] + lo[q] - 1] : rect_of(v.x, v.y), mult, tier, kh, kl);
-            }
-            const bool in = lo[q] > 0;
-            const unsigned long long fits = __ballot(in);
-            if (!fits) continue;
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&s_n, __popcll(fits));
-            at = __builtin_amdgcn_readfirstlane(at) + __popcll(fits & ((1ull << lane) - 1ull));
-            if (in) {
-                s_hi[at] = kh;
-                if (MIXED) lo_at(at) = kl;
-                s_job[at] = uint16_t(j);
-            }
+            item[q] = hi[q] ? (~pair_digest(hi[q]) << 12) | uint32_t(job[q]) : ~0ull;
+            fits |= unsigned(hi[q] != 0) << q;
+            fit += __popcll(__ballot(hi[q] != 0));
+            if (cut_off && hi[q]) atomicAdd(&s_hist[item[q] >> (kOrderBinShift + 12)], 1);
         }
     }
+    if (lane == 0) atomicAdd(&s_n, fit);
     __syncthreads();
-    const int fit = s_n, n = sort(fit);
-    if (tid == 0) list_len[g] = min(fit, most);
-    const int words = (min(n, most) + kPairsSlots - 1) / kPairsSlots;
-    for (int k = tid; k < words; k += threads)
+    const int n_fit = s_n;
+    int n = n_fit;                      // entries to be put in order
+    if (BINS && cut_off && n_fit > most) {
+        // the first bin by whose end there are enough
+        constexpr int each = kOrderBins / THREADS;
+        int mine = 0;
+#pragma unroll 4
+        for (int i = 0; i < each; ++i) mine += s_hist[tid * each + i];
+        const int upto = wave_scan_add(mine);
+        if (lane == kWave - 1) s_wave[wave] = upto;
+        __syncthreads();
+        int before = upto - mine;
+        for (int w = 0; w < wave; ++w) before += s_wave[w];
+        if (before < most && before + mine >= most) {
+            int b = tid * each, sum = before;
+            while ((sum += s_hist[b]) < most) ++b;
+            s_bin = b;
+            s_upto = sum;
+        }
+        __syncthreads();
+        n = s_upto;
+    }
+    const int last_bin = s_bin;
+    __syncthreads();                    // (the words take the histogram's place)
+    int room = kPairsSlots;
+    while (room < n) room <<= 1;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const bool in = (fits >> q & 1u) && int(item[q] >> (kOrderBinShift + 12)) <= last_bin;
+        const unsigned long long some = __ballot(in);
+        if (!some) continue;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s_kept, __popcll(some));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(some & ((1ull << lane) - 1ull));
+        if (in) s_item[at] = item[q];
+    }
+    for (int i = n + tid; i < room; i += THREADS) s_item[i] = ~0ull;
+    network(room, [&](int a, int b, bool up) {
+        const unsigned long long x = s_item[a], y = s_item[b];
+        if ((y < x) == up) { s_item[a] = y; s_item[b] = x; }
+    });
+    const int len = min(n_fit, most);
+    // neighbours of one digest: the jobs are in order, the keys may not be
+    for (int i = tid; i + 1 < n; i += THREADS) {
+        if (s_item[i] >> 12 != s_item[i + 1] >> 12) continue;
+        const int job[2] = {int(s_item[i] & 0xfffu), int(s_item[i + 1] & 0xfffu)};
+        unsigned long long hi[2], lo[2];
+        keys(std::integral_constant<int, 2>{}, job, hi, lo);
+        if (hi[1] > hi[0] || (hi[1] == hi[0] && lo[1] > lo[0])) s_bad = 1;
+    }
+    __syncthreads();
+    const int words = (min(room, most) + kPairsSlots - 1) / kPairsSlots;
+    if (tid == 0) list_len[g] = len;
+    if (!s_bad) {
+        for (int k = tid; k < words; k += THREADS) {
+            unsigned long long out = 0;
+#pragma unroll
+            for (int q = 0; q < kPairsSlots; ++q) {
+                const int i = kPairsSlots * k + q;
+                out |= (unsigned long long)(i < n ? uint32_t(s_item[i]) & 0xfffu : uint32_t(n_jobs)) << (16 * q);
+            }
+            list[size_t(k) * n_gaps + g] = out;
+        }
+        return;
+    }
+    // all jobs that fit, by all of their keys
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const bool in = fits >> q & 1u;
+        const unsigned long long some = __ballot(in);
+        if (!some) continue;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s_all, __popcll(some));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(some & ((1ull << lane) - 1ull));
+        if (!in) continue;
+        const int job[1] = {int(item[q] & 0xfffu)};
+        unsigned long long hi[1], lo[1];
+        keys(std::integral_constant<int, 1>{}, job, hi, lo);
+        s_hi[at] = hi[0];
+        if (MIXED) s_lo[at] = lo[0];
+        s_job[at] = uint16_t(job[0]);
+    }
+    room = kPairsSlots;
+    while (room < n_fit) room <<= 1;
+    for (int i = n_fit + tid; i < room; i += THREADS) {
+        s_hi[i] = 0;
+        if (MIXED) s_lo[i] = 0;
+        s_job[i] = uint16_t(n_jobs);            // nobody
+    }
+    network(room, [&](int a, int b, bool up) {
+        const unsigned long long ha = s_hi[a], hb = s_hi[b];
+        const unsigned long long la = MIXED ? s_lo[a] : 0ull, lb = MIXED ? s_lo[b] : 0ull;
+        const uint16_t ja = s_job[a], jb = s_job[b];
+        if (fused_better(hb, lb, jb, ha, la, ja) == up) {
+            s_hi[a] = hb; s_hi[b] = ha;
+            if (MIXED) { s_lo[a] = lb; s_lo[b] = la; }
+            s_job[a] = jb; s_job[b] = ja;
+        }
+    });
+    for (int k = tid; k < (min(room, most) + kPairsSlots - 1) / kPairsSlots; k += THREADS)
         list[size_t(k) * n_gaps + g] = *reinterpret_cast<const unsigned long long *>(s_job + kPairsSlots * k);
 }
 

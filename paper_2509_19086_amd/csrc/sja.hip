@@ -719,6 +719,8 @@ int enqueue_starts(sja_ctx *ctx, hipStream_t st, const Layout &L)
 // A batch served pair by pair.  The gaps' lists take the space of the list entries.
 int pair_list_most(int64_t G, int64_t J) { return int(G < J ? G : J); }
 
+constexpr int64_t kPairAtomsLeast = int64_t(1) << 19;        // pairs (256 gaps x 1024 jobs are searched in 9 us)
+
 bool pairs_batch(const sja_ctx *ctx, const Layout &L, int64_t G, int64_t J)
 {
     return ctx->resolve_mode == SJA_RESOLVE_LISTS && J > 0 && G <= kPairsGaps && J <= kPairsJobs && G * J <= kPairsMost &&
@@ -743,6 +745,19 @@ int plan_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L)
     return rc;
 }
 
+// The atoms of every pair job by job, behind the gaps' lists, where there are enough pairs to pay for the launch and room
+// for them; else null: each pair is searched where it is needed.
+uint16_t *pair_atoms(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const int32_t *W, const int32_t *C)
+{
+    const int J = ctx->n_jobs;
+    const size_t at = align_up(L.g_ekey0 + pair_list_words(n_gaps, pair_list_most(n_gaps, J)) * 8);
+    if (int64_t(n_gaps) * J < kPairAtomsLeast || at + size_t(n_gaps) * J * 2 > L.lb_begin) return nullptr;
+    uint16_t *atoms = ws_ptr<uint16_t>(ctx, at);
+    hipLaunchKernelGGL(k_pair_atoms, dim3((J + kAtomsJobs - 1) / kAtomsJobs, (n_gaps + kAtomsGaps - 1) / kAtomsGaps), dim3(kAtomsThreads), 0, st, n_gaps, J,
+                       W, C, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), ws_ptr<int32_t>(ctx, L.n_atoms), atoms);
+    return atoms;
+}
+
 int pair_threads(int J) { return J <= kWave ? kWave : J <= 4 * 256 ? 256 : kPairsMostThreads; }
 
 int resolve_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params, const int32_t *wait, const uint8_t *sla_class,
@@ -755,19 +770,28 @@ int resolve_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_param
     const int2 *atom_dp = ws_ptr<int2>(ctx, L.atom_dp), *atom_db = ws_ptr<int2>(ctx, L.atom_db);
     int32_t *len = ws_ptr<int32_t>(ctx, L.gap_rank);
     unsigned long long *list = ws_ptr<unsigned long long>(ctx, L.g_ekey0);
+    PairReplies from{};
+    if (ctx->fitted) {
+        from.cut = ctx->cut;
+        from.pre_dur = ctx->pre_dur;
+        from.pre_peak = ctx->pre_peak;
+        from.pre_area = pre_area_of(ctx, L);
+    } else {
+        from.atoms = pair_atoms(ctx, st, L, G, gap_w, gap_c);
+        SJA_HIP(hipGetLastError(), "k_pair_atoms launch");
+    }
     auto order = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
         static_assert(kPairsJobs <= 4096, "the largest has room for every job");
-        // a thread per two entries, if it is not too many
         auto launch = [&](auto kern, int threads) {
-            hipLaunchKernelGGL(kern, dim3(G), dim3(threads), 0, st, G, J, most, pol, gap_w, gap_c, ctx->seg_off, atom_dp, area, n_atoms, wait,
+            hipLaunchKernelGGL(kern, dim3(G), dim3(threads), 0, st, G, J, most, pol, from, gap_w, gap_c, ctx->seg_off, atom_dp, area, n_atoms, wait,
                                sla_class, len, list);
         };
-        if (J <= 128) launch(k_order_pairs<M, 128, 2>, 64);
-        else if (J <= 512) launch(k_order_pairs<M, 512, 2>, 256);
-        else if (J <= 1024) launch(k_order_pairs<M, 1024, 2>, 512);
-        else if (J <= 2048) launch(k_order_pairs<M, 2048, 2>, 1024);
-        else launch(k_order_pairs<M, 4096, 2>, 1024);
+        if (J <= 128) launch(k_order_pairs<M, 128, 64>, 64);
+        else if (J <= 512) launch(k_order_pairs<M, 512, 256>, 256);
+        else if (J <= 1024) launch(k_order_pairs<M, 1024, 512>, 512);
+        else if (J <= 2048) launch(k_order_pairs<M, 2048, 1024>, 1024);
+        else launch(k_order_pairs<M, 4096, 1024>, 1024);
     };
     if (params->policy == SJA_POLICY_MIXED) order(std::true_type{});
     else order(std::false_type{});
@@ -811,12 +835,15 @@ int launch_best_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_g
                       const uint8_t *gap_active, int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score)
 {
     const int J = ctx->n_jobs;
-    auto kern = params->policy == SJA_POLICY_MIXED ? k_best_pairs<true> : k_best_pairs<false>;
+    const bool mixed = params->policy == SJA_POLICY_MIXED;
     int rc = ctx->timing ? mark_kernel(ctx, st, false) : SJA_OK;
     if (rc != SJA_OK) return rc;
+    const uint16_t *atoms = pair_atoms(ctx, st, L, n_gaps, W, C);
+    SJA_HIP(hipGetLastError(), "k_pair_atoms launch");
+    auto kern = atoms ? (mixed ? k_best_pairs<true, true> : k_best_pairs<false, true>) : (mixed ? k_best_pairs<true, false> : k_best_pairs<false, false>);
     hipLaunchKernelGGL(kern, dim3(n_gaps), dim3(pair_threads(J)), 0, st, J, to_dev(params), W, C, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
                        ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class, job_held,
-                       gap_active, pair_gaps(ctx, L), cand_job, cand_cut, cand_score);
+                       gap_active, pair_gaps(ctx, L), atoms, cand_job, cand_cut, cand_score);
     SJA_HIP(hipGetLastError(), "k_best_pairs launch");
     return ctx->timing ? mark_kernel(ctx, st, true) : SJA_OK;
 }
