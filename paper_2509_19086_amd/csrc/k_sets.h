@@ -10,15 +10,27 @@
 //     are a piece, the rest form further ones (sets_form);
 //   * neighbouring pieces of a capacity class whose gaps want the same jobs for
 //     some rounds to come are joined to a set, a range of the class's sorted
-//     positions (sets_join);
-//   * one wave plays round after round on what lies in LDS, a lane for one to
+//     positions (sets_join), and a set's jobs and lowest gaps are brought to LDS
+//     (sets_fill);
+//   * one wave plays round after round on what lies there, a lane for one to
 //     four sets: the first of the set's jobs that no round has named yet, a claim
-//     for the set's lowest open gap, the outcome (sets_play).  A round is two
-//     trips to LDS and needs no barrier: 0.35 us.
+//     for the set's lowest open gap, the outcome (sets_play).  A round is one
+//     trip to LDS and 55 instructions and needs no barrier: 0.21 us.
 // A batch ends when some set has used up its jobs or the lowest gaps it has at
-// hand: some 30 to 60 rounds.  Up to kSetsOneBlocks list blocks one launch does
-// all of it (k_sets_one); beyond that the lists are searched by many thread
-// blocks and the rounds played by one, in turn (k_sets_form, k_sets_play).
+// hand: up to 252 rounds of a few sets, some 20 to 60 where there are many.  Up
+// to kSetsOneBlocks list blocks one launch does all of it (k_sets_one); beyond
+// that the lists are searched by many thread blocks, which also list the pieces'
+// jobs, and the rounds played by one, in turn (k_sets_form, k_sets_play).
+//
+// Between two batches lie 17 us at 66 list blocks and 4 sets (searching 7, jobs
+// and gaps 7, joining 2, writing down 1) and 35 to 45 with 40 sets, as much as 80
+// to 150 rounds: hence as many jobs at hand as a lane's registers and LDS allow.
+// 2048 gaps x 8192 jobs, 542 rounds: 10 batches of 54 in 345 us when a set had 63
+// jobs at hand and a round took 0.40 us, now three batches in 160.
+//
+// Working the rounds of a batch out together (all waves, pass after pass over the
+// claims until they stay) was slower: neighbouring sets want nearly the same jobs,
+// so that a pass puts right only one to two rounds more.
 //
 // What the sets rely on: along the positions of a class a job's key never falls
 // (F grows with the cut; the host sees to it where the hysteresis rule could
@@ -40,18 +52,24 @@ namespace sja {
 constexpr int kSetsWaves = 16, kSetsThreads = kSetsWaves * kWave;
 constexpr int kSetsMaxBlocks = 768;     // list blocks
 static_assert(kSetsMaxBlocks <= kPlacedBlocks, "a place is a list block and a lane");
-constexpr int kSetsOneBlocks = 128;     // and up to which one thread block does it all
+// and up to which one thread block does it all: 66 of them 910 us a tick of 2048 gaps x 8192 jobs in one launch, 1030 in
+// turn; 118 as fast in either (two launches cost 10 us a batch, searching the lists by one block 8 to 30)
+constexpr int kSetsOneBlocks = 80;
 constexpr int kSetsPieces = 6;          // pieces of a list block, at most
 constexpr int kSetsMost = 256;          // sets, at most
-constexpr int kSetsK = 63;              // jobs at hand per set, at most (a lane each)
-constexpr int kSetsRoom = 70;           // 16-bit words for them: twice an odd number (banks); the last four used ones are nobody's job
-constexpr int kSetsHeads = 6144;        // lowest gaps at hand of all sets: as many each as there is room for,
-constexpr int kSetsMostHeads = 63;      // up to so many
+constexpr int kSetsMostJobs = 252;      // jobs at hand of a set, at most,
+constexpr int kSetsMostRounds = kSetsMostJobs + 1;      // and rounds of a batch: each passes a job of every set
+constexpr int kSetsSeq = kSetsMost * 70;        // 16-bit words for the jobs at hand of all sets; a set's last four are nobody's job
+constexpr int kSetsHeads = 6144;        // lowest gaps at hand of all sets
 constexpr int kSetsGapsAhead = 8;       // chunks of 64 gaps a wave looks at together,
 constexpr int kSetsFewGaps = 8, kSetsGapsFar = 512;     // and how far for more than a few gaps
+constexpr int kSetsListed = 2 * kWave;  // jobs that are listed for a piece, at most,
+constexpr int kSetsLeastListed = 16;    // and at least
 constexpr int kSetsChunk = 4 * kWave;   // records a wave reads at a time, four a lane
 constexpr int kSetsMostSteps = 64;      // chunks a wave reads for one piece before it gives up
-constexpr int kSetsLeastFirst = 16, kSetsLeast = 32;      // jobs that the gaps of a set have in common, at least: at first, and at most
+// jobs that the gaps of a set have in common, at least: at first, and at most (k_sets_one, and with more list blocks,
+// where more in common makes more sets: 32768 gaps x 65536 jobs 43.0 / 42.0 / 41.4 / 42.3 / 43.0 ms for 16 / 24 / 32 / 48 / 64)
+constexpr int kSetsLeastFirst = 16, kSetsLeast = 64, kSetsLeastMany = 32;
 constexpr int kSetsShort = 8, kSetsPatience = 3;       // batches of so few rounds are short ones; more of those than others by so many end it
 constexpr int kSetsState = 3;           // out[]: k_grant_solo's words, and this one between launches: least << 8 | strain
 enum { kSetsRunning = 4, kSetsLeft = 5 };       // out[kSoloDone]: between launches; on with k_grant_solo
@@ -59,19 +77,21 @@ enum { kSetsPause = 0, kSetsNoClaim = 1, kSetsAtCap = 2 };          // why the r
 
 // The jobs at hand: slots of a hash table, so that a set needs two bytes for a job and a claim has a word of its
 // own, which also says whether the job is held.  A job is named in one round only: its word is the smallest of
-// that round's claims, round of the batch (12 bits) : gap (20 bits), all ones before.  The slot behind the last
-// one is nobody's job: never free.
+// that round's claims, round of the batch (12 bits) : gap (20 bits), all ones before.  Behind the last
+// slot there are two claims more: nobody's job, never free, and one that always is and stays so.
 constexpr int kSetsSlots = 4096;
 constexpr uint32_t kSetsNoJob = ~0u;
 constexpr int kSetsTries = 16;
 struct SetsJobs {
     uint32_t job[kSetsSlots];
-    uint32_t claim[kSetsSlots + 1];
+    uint32_t claim[kSetsSlots + 2];
 };
+constexpr uint32_t kSetsNobody = 4 * kSetsSlots, kSetsIdle = kSetsNobody + 4;       // byte offsets of the last two claims
+constexpr uint32_t kSetsServed = 1u << 20, kSetsMoreGaps = kSetsServed + 1;            // behind a set's lowest gaps: it has no others, or has some
 __device__ __forceinline__ void sets_clear(SetsJobs &t, int i)
 {
     if (i < kSetsSlots) t.job[i] = kSetsNoJob;
-    t.claim[i] = i < kSetsSlots ? ~0u : 0u;
+    t.claim[i] = i == kSetsSlots ? 0u : i == kSetsSlots + 1 ? ~1u : ~0u;
 }
 // The job's slot, -1 if there is none within reach: the set has fewer jobs at hand then.
 __device__ __forceinline__ int sets_slot(SetsJobs &t, uint32_t job)
@@ -138,19 +158,16 @@ __device__ __forceinline__ void sets_by_class(int n_gaps, int n_classes, const i
 struct SetsPiece {
     uint16_t top, bottom;           // places of its highest and lowest lane
     uint16_t from_most;             // the highest place from which on one of the first jobs' atoms is the answer
-    uint8_t jobs, last;             // jobs; no more behind them.  No jobs at all: none is left for these lanes
+    uint16_t jobs;                  // none is left for these lanes; else how many are listed, with kSetsAll if those are all
+    int at;                         // where the first free job of its highest lane is
 };
+constexpr uint16_t kSetsAll = 0x8000;
 struct SetsBlock {
     unsigned long long open;
     int at, pieces;                 // pieces: -1 if the block has more of them, -2 if the next job lies further on
     SetsPiece piece[kSetsPieces];
 };
-struct SetsList {                   // the jobs of a piece
-    uint32_t job[kWave];
-    uint16_t from[kWave];
-};
-static_assert(sizeof(SetsBlock) == 64 && sizeof(SetsList) == 384, "layout");
-constexpr int kSetsBlockBytes = int(sizeof(SetsBlock)) + kSetsPieces * int(sizeof(SetsList));      // what a list block needs in all
+static_assert(sizeof(SetsBlock) == 88, "layout");
 
 struct SetsArgs {
     int4 *state;
@@ -163,7 +180,9 @@ struct SetsArgs {
     int32_t *place_of;              // [gaps]
     int2 *by_class;                 // [gaps]
     SetsBlock *block;               // [list blocks]
-    SetsList *list;                 // [list blocks][kSetsPieces]
+    uint32_t *list;                 // [list blocks][kSetsPieces][list_jobs] jobs of the pieces, and behind all of them
+    uint16_t *list_from;            // the places from which on they are the answer (not for k_sets_one)
+    int list_jobs;
     int32_t *low;                   // per class where its lowest open gap lies among its gaps (between launches)
     int32_t *out;
     int cap, n_gaps, n_lb, held_words;
@@ -184,68 +203,110 @@ __device__ __forceinline__ void sets_open(const SetsArgs &A, int u, int lane)
     }
 }
 
+// A list's records from i0 on that cover lane `top` and whose job is free, kSetsChunk at a time.
+struct SetsSearch {
+    const uint4 *rec4;
+    const ushort4 *from4;
+    const uint32_t *held;
+    int i0, end, top, base;
+    uint4 r0, r1;
+    ushort4 f0, f1;
+
+    __device__ __forceinline__ void ask(int i, int lane, uint4 &r, ushort4 &f) const
+    {
+        const int k = min((i >> 2) + lane, (end - 1) >> 2);
+        r = rec4[k];
+        f = from4[k];
+    }
+    __device__ __forceinline__ void start(const SetsArgs &A, const uint32_t *is_held, int at, int list_end, int for_lane, int lane)
+    {
+        rec4 = reinterpret_cast<const uint4 *>(A.rec);
+        from4 = reinterpret_cast<const ushort4 *>(A.rec_from);
+        held = is_held;
+        i0 = at;
+        end = list_end;
+        top = for_lane;
+        base = at & ~3;
+        if (i0 < end) {
+            ask(base, lane, r0, f0);
+            ask(base + kSetsChunk, lane, r1, f1);
+        }
+    }
+    __device__ __forceinline__ bool over() const { return i0 >= end || base >= end; }
+    // Which of the lane's four records (r0, f0) are such ones.
+    __device__ __forceinline__ unsigned look(int lane) const
+    {
+        const uint32_t r[4] = {r0.x, r0.y, r0.z, r0.w};
+        unsigned ok = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const Rec32 x{r[k]};
+            const int i = base + 4 * lane + k;
+            const bool covers = (i >= i0) & (i < end) & (uint32_t(top - x.lo()) < uint32_t(x.hi() - x.lo()));
+            ok |= unsigned(covers && !held_bit(held, x.job())) << k;
+        }
+        return ok;
+    }
+    __device__ __forceinline__ void next(int lane)
+    {
+        r0 = r1;
+        f0 = f1;
+        base += kSetsChunk;
+        ask(base + kSetsChunk, lane, r1, f1);
+    }
+};
+
 // The pieces of list block u.  A lane's records lie behind a higher lane's, but for 63 of equal keys.
-__device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, int least, const uint32_t *s_held, uint32_t *s_job, uint32_t *s_from)
+// LISTS: with the jobs of each, twice as many as its lanes are to have in common.
+template <bool LISTS>
+__device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, int least, const uint32_t *s_held)
 {
     SetsBlock &B = A.block[u];
     unsigned long long rest = B.open;
     if (!rest) return;
     int at = B.at, n_pieces = 0;
-    const int end = A.list_off[u + 1], last4 = (end - 1) >> 2;
-    auto ask = [&](int i, uint4 &r, ushort4 &f) {
-        const int k = min((i >> 2) + lane, last4);
-        r = reinterpret_cast<const uint4 *>(A.rec)[k];
-        f = reinterpret_cast<const ushort4 *>(A.rec_from)[k];
-    };
+    const int end = A.list_off[u + 1];
     int first_at = at;
     for (bool first = true; rest; first = false) {
     again:
         const int top = 63 - __clzll((long long)rest);
-        int bottom = __ffsll((long long)rest) - 1;
-        int i0 = at;
-        if (!first) i0 = max(at - 63, __builtin_amdgcn_readfirstlane(A.state[u * kWave + top].x));
-        int n = 0, hit = -1, base = i0 & ~3, steps = 0;
-        if (i0 < end) {
-            uint4 r0, r1;
-            ushort4 f0, f1;
-            ask(base, r0, f0);
-            ask(base + kSetsChunk, r1, f1);
+        const int bottom = __ffsll((long long)rest) - 1;
+        SetsSearch find;
+        find.start(A, s_held, first ? at : max(at - 63, __builtin_amdgcn_readfirstlane(A.state[u * kWave + top].x)), end, top, lane);
+        const int room = LISTS ? A.list_jobs : 0, want = LISTS ? min(2 * least, room) : least;
+        const size_t list = LISTS && n_pieces < kSetsPieces ? size_t(u * kSetsPieces + n_pieces) * room : 0;
+        int n = 0, hit = -1, steps = 0, most = 0;       // most: of the first `least` jobs
+        if (!find.over()) {
             for (;;) {
-                const uint32_t r[4] = {r0.x, r0.y, r0.z, r0.w};
-                const uint16_t f[4] = {f0.x, f0.y, f0.z, f0.w};
-                unsigned ok = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const Rec32 x{r[k]};
-                    const int i = base + 4 * lane + k;
-                    const bool covers = (i >= i0) & (i < end) & (uint32_t(top - x.lo()) < uint32_t(x.hi() - x.lo()));
-                    ok |= unsigned(covers && !held_bit(s_held, x.job())) << k;
-                }
+                const unsigned ok = find.look(lane);
                 const unsigned long long some = __ballot(ok != 0);
                 if (some) {
                     const int mine = __popc(ok), upto = wave_scan_add(mine);
+                    const uint32_t r[4] = {find.r0.x, find.r0.y, find.r0.z, find.r0.w};
+                    const uint16_t f[4] = {find.f0.x, find.f0.y, find.f0.z, find.f0.w};
                     int rank = n + upto - mine;
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         if (!(ok >> k & 1u)) continue;
-                        if (rank < kSetsK) { s_job[rank] = Rec32{r[k]}.job(); s_from[rank] = f[k]; }
+                        if (rank < least) most = max(most, int(f[k]));
+                        if (LISTS && rank < room && n_pieces < kSetsPieces) {
+                            A.list[list + rank] = Rec32{r[k]}.job();
+                            A.list_from[list + rank] = f[k];
+                        }
                         ++rank;
                     }
                     if (n == 0) {
                         const int t = __ffsll((long long)some) - 1;
-                        hit = base + 4 * t + __ffs(__builtin_amdgcn_readlane(int(ok), t)) - 1;
+                        hit = find.base + 4 * t + __ffs(__builtin_amdgcn_readlane(int(ok), t)) - 1;
                     }
                     n += __builtin_amdgcn_readlane(upto, kWave - 1);
                 }
-                base += kSetsChunk;
-                if (n >= kSetsK || base >= end || ++steps > kSetsMostSteps) break;
-                r0 = r1; f0 = f1;
-                ask(base + kSetsChunk, r1, f1);
+                if (n >= want || find.base + kSetsChunk >= end || ++steps > kSetsMostSteps) break;
+                find.next(lane);
             }
         }
-        const bool last = (i0 >= end || base >= end) && n <= kSetsK;        // nothing behind these
-        if (n == 0 && !last) {              // from there on the next time
-            if (lane == 0) { if (first) B.at = base; else A.state[u * kWave + top].x = base; }
+        if (n == 0 && find.i0 < end && find.base + kSetsChunk < end) {              // from there on the next time
+            if (lane == 0) { if (first) B.at = find.base + kSetsChunk; else A.state[u * kWave + top].x = find.base + kSetsChunk; }
             n_pieces = -2;
             break;
         }
@@ -259,36 +320,21 @@ __device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, in
             first = true;
             goto again;
         }
-        SetsList &L = A.list[u * kSetsPieces + n_pieces];
         SetsPiece &P = B.piece[n_pieces++];
-        if (n == 0) {               // no job is left for the highest lane, and so for none below it
-            if (lane == 0) { P.top = uint16_t(u * kWave + top); P.bottom = uint16_t(u * kWave + bottom); P.from_most = 0; P.jobs = P.last = 0; }
-            break;
-        }
-        n = min(n, kSetsK);
-        asm volatile("" ::: "memory");
-        const uint32_t job = s_job[lane];
-        const int from = lane < n ? int(s_from[lane]) : 0;
-        // the lanes that share the jobs, or at least the first of them
-        unsigned long long set = rest;
-        unsigned long long beyond = __ballot(from > u * kWave + bottom);
-        const int most = -wave_min_dpp(lane < least ? -from : 0);
-        if (beyond && __ffsll((long long)beyond) - 1 < least) {
-            set = rest & (~0ull << (most & 63));
-            bottom = __ffsll((long long)set) - 1;
-            beyond = __ballot(from > u * kWave + bottom);
-        }
-        const int jobs = beyond ? __ffsll((long long)beyond) - 1 : n;
-        L.job[lane] = job;
-        L.from[lane] = uint16_t(from);
+        // the lanes that share the first jobs
+        const int most_of_all = -wave_min_dpp(-most);
+        const bool parted = n > 0 && most_of_all > u * kWave + bottom;
+        const unsigned long long set = parted ? rest & (~0ull << (most_of_all & 63)) : rest;
         if (lane == 0) {
             P.top = uint16_t(u * kWave + top);
-            P.bottom = uint16_t(u * kWave + bottom);
-            P.from_most = uint16_t(most);
-            P.jobs = uint8_t(jobs);
-            P.last = uint8_t(last && jobs == n);
-            if (first) B.at = hit; else A.state[u * kWave + top].x = hit;
+            P.bottom = uint16_t(u * kWave + __ffsll((long long)set) - 1);
+            P.from_most = uint16_t(most_of_all);
+            P.jobs = uint16_t(LISTS ? min(n, room) | (n <= room && find.base + kSetsChunk >= end ? kSetsAll : 0) : n);
+            if (n == 0) P.jobs = 0;
+            P.at = hit;
+            if (n > 0) { if (first) B.at = hit; else A.state[u * kWave + top].x = hit; }
         }
+        if (n == 0) break;          // no job is left for the highest lane, and so for none below it
         if (first) first_at = hit;
         at = hit;
         rest &= ~set;
@@ -299,19 +345,18 @@ __device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, in
 template <int BLOCKS>
 struct SetsShared {
     SetsJobs jobs;                                      // the jobs at hand and their claims
-    uint16_t seq[kSetsMost * kSetsRoom];                // per set its jobs' slots in there; then those it was granted
-    uint32_t head[kSetsHeads];                          // its lowest open gaps, [H][sets]
-    uint16_t place[kSetsHeads];                         // and their places
+    alignas(16) uint16_t seq[kSetsSeq];                 // per set its jobs' slots in there
+    alignas(8) uint16_t idle[kSetsMostRounds + 11];     // nobody's jobs that are always free, for those that have left
+    uint32_t head[kSetsHeads + kSetsMost];              // its lowest open gaps
     unsigned long long open[BLOCKS];            // open lanes of the list blocks
     uint16_t piece[BLOCKS * kSetsPieces], ends[BLOCKS * kSetsPieces], from_most[BLOCKS * kSetsPieces];  // the pieces: number, highest lane << 8 | lowest lane
-    uint8_t piece_jobs[BLOCKS * kSetsPieces];
+    uint8_t none[BLOCKS * kSetsPieces];                 // no job is left for its lanes
     int8_t pieces[BLOCKS];
     uint16_t lo[kSetsMost], hi[kSetsMost], source[kSetsMost], cls[kSetsMost];    // first and last place of a set, the piece whose jobs it has, its class
-    uint32_t set[kSetsMost];                            // jobs at hand : gaps at hand : no more jobs : no more gaps
-    int won[kSetsMost];
+    uint32_t set[kSetsMost];                            // jobs at hand, bit 16: no more jobs
     int first[kMaxClasses + 1], gaps_at[kMaxClasses + 1];       // first list block of a class, its first position,
     int low[kMaxClasses];                               // and where its lowest open gap lies among its gaps
-    uint32_t found[kSetsWaves][kWave], found_from[kSetsWaves][kWave];
+    uint32_t found[kSetsWaves][kWave];
     int n, over, closed, lost, end, why;
 };
 
@@ -365,7 +410,7 @@ __device__ __forceinline__ void sets_join(const SetsArgs &A, SetsShared<BLOCKS> 
             break;
         }
         int lo = u_first * kWave;
-        if (S.piece_jobs[piece] == 0) {         // no job is left for these lanes
+        if (S.none[piece]) {                    // no job is left for these lanes
             k1 = k + 1;
             next_top = k1 < n ? top_of(k1) : 0;
             if (lane == 0) {
@@ -398,21 +443,50 @@ __device__ __forceinline__ void sets_join(const SetsArgs &A, SetsShared<BLOCKS> 
     }
 }
 
-// The jobs and the lowest gaps of a set.
-template <int BLOCKS>
-__device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> &S, int id, int lane, int wave, int width, int H)
+// How the space is shared out among the sets of a batch: per set `room` words for up to `most` jobs (twice an odd
+// number: banks), and up to `heads` lowest gaps, of which the r-th of set i is at i + r * width.
+struct SetsShape { int room, most, width, heads; };
+__device__ __forceinline__ SetsShape sets_shape(int n_sets)
+{
+    if (n_sets <= 16) return {262, kSetsMostJobs, 16, 253};
+    if (n_sets <= 32) return {262, kSetsMostJobs, 32, 191};
+    if (n_sets <= kWave) return {262, kSetsMostJobs, 64, 95};
+    if (n_sets <= 2 * kWave) return {138, 126, 128, 47};
+    return {70, 58, kSetsMost, 23};
+}
+static_assert(kWave * 262 <= kSetsSeq && 2 * kWave * 138 <= kSetsSeq && kSetsMost * 70 <= kSetsSeq, "jobs at hand");
+// (behind the last gap a word that says whether there are more, and one that is read and not looked at)
+static_assert((253 + 2) * 16 <= kSetsHeads + kSetsMost && (191 + 2) * 32 <= kSetsHeads + kSetsMost && (95 + 2) * 64 <= kSetsHeads + kSetsMost &&
+              (47 + 2) * 128 <= kSetsHeads + kSetsMost && (23 + 2) * kSetsMost <= kSetsHeads + kSetsMost, "gaps at hand");
+
+// The jobs (up to `most`) and the lowest gaps of a set.  LISTS: its piece's jobs are listed.
+template <bool LISTS, int BLOCKS>
+__device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> &S, int id, int lane, int wave, const SetsShape &shape, int most, const uint32_t *held)
 {
     const int lo = __builtin_amdgcn_readfirstlane(int(S.lo[id])), hi = __builtin_amdgcn_readfirstlane(int(S.hi[id]));
     const int piece = __builtin_amdgcn_readfirstlane(int(S.source[id])), c = __builtin_amdgcn_readfirstlane(int(S.cls[id]));
-    const uint32_t job = A.list[piece].job[lane];
-    const int from = A.list[piece].from[lane];
-    const int n = S.piece_jobs[piece] & 127;
-    const bool last = S.piece_jobs[piece] >> 7;
+    const int u = piece / kSetsPieces, H = shape.heads;
+    const SetsPiece P = A.block[u].piece[piece % kSetsPieces];
     const int begin = S.gaps_at[c], count = S.gaps_at[c + 1] - begin;
     const int low = S.low[c];
     int2 ahead[kSetsGapsAhead];
 #pragma unroll
     for (int k = 0; k < kSetsGapsAhead; ++k) ahead[k] = A.by_class[begin + min(low + k * kWave + lane, count - 1)];
+    SetsSearch find;
+    constexpr int kLane = kSetsListed / kWave;
+    uint32_t listed[kLane];
+    int listed_from[kLane];
+    const int room = A.list_jobs;
+    if (LISTS) {
+#pragma unroll
+        for (int m = 0; m < kLane; ++m) {
+            const size_t at = size_t(piece) * room + min(m * kWave + lane, room - 1);
+            listed[m] = A.list[at];
+            listed_from[m] = A.list_from[at];
+        }
+    } else {
+        find.start(A, held, __builtin_amdgcn_readfirstlane(P.at), A.list_off[u + 1], __builtin_amdgcn_readfirstlane(int(P.top & 63)), lane);
+    }
     // its lowest place, and how many are open (a few, or more than a wave)
     int bottom = hi, n_open = 0;
     for (int v0 = hi >> 6; v0 >= lo >> 6; v0 -= kWave) {
@@ -423,14 +497,56 @@ __device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> 
             n_open += __builtin_amdgcn_readlane(wave_scan_add(__popcll(m)), kWave - 1);
         }
     }
-    const unsigned long long beyond = __ballot(lane < n && from > bottom);
-    int jobs = beyond ? __ffsll((long long)beyond) - 1 : n;
-    const int slot = lane < jobs ? sets_slot(S.jobs, job) : -1;
-    const unsigned long long none = __ballot(lane < jobs && slot < 0);
-    if (none) jobs = __ffsll((long long)none) - 1;
+    // its jobs, up to the first one whose atom is not the answer of all its gaps
+    int n = 0, limit = most;
+    if (LISTS) {
+        n = min(__builtin_amdgcn_readfirstlane(int(P.jobs & ~kSetsAll)), limit + 1);
+#pragma unroll
+        for (int m = 0; m < kLane; ++m) {
+            const int k = m * kWave + lane;
+            const unsigned long long beyond = __ballot(k < n && listed_from[m] > bottom);
+            if (beyond) limit = min(limit, m * kWave + __ffsll((long long)beyond) - 1);
+            const bool in = k < min(n, limit);
+            const int slot = in ? sets_slot(S.jobs, listed[m]) : -1;
+            if (slot >= 0) S.seq[id * shape.room + k] = uint16_t(4 * slot);
+            const unsigned long long none = __ballot(in && slot < 0);
+            if (none) limit = min(limit, m * kWave + __ffsll((long long)none) - 1);
+        }
+    }
+    for (int steps = 0; !LISTS;) {
+        const unsigned ok = find.look(lane);
+        if (__ballot(ok != 0)) {
+            constexpr int none = 0x7fffffff;
+            const int mine = __popc(ok), upto = wave_scan_add(mine);
+            const uint32_t r[4] = {find.r0.x, find.r0.y, find.r0.z, find.r0.w};
+            const uint16_t f[4] = {find.f0.x, find.f0.y, find.f0.z, find.f0.w};
+            int rank = n + upto - mine, cut = none;
+#pragma unroll
+            for (int k = 3; k >= 0; --k)
+                if ((ok >> k & 1u) && int(f[k]) > bottom) cut = rank + __popc(ok & ((1u << k) - 1u));
+            limit = min(limit, wave_min_dpp(cut));
+            cut = none;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (!(ok >> k & 1u)) continue;
+                if (rank < limit) {
+                    const int slot = sets_slot(S.jobs, Rec32{r[k]}.job());
+                    if (slot < 0) cut = min(cut, rank);
+                    else S.seq[id * shape.room + rank] = uint16_t(4 * slot);
+                }
+                ++rank;
+            }
+            if (__ballot(cut != none)) limit = min(limit, wave_min_dpp(cut));
+            n += __builtin_amdgcn_readlane(upto, kWave - 1);
+        }
+        if (n >= limit || find.base + kSetsChunk >= find.end || ++steps > kSetsMostSteps) break;
+        find.next(lane);
+    }
+    const bool last = n <= limit && (LISTS ? (P.jobs & kSetsAll) != 0 : find.base + kSetsChunk >= find.end);        // nothing behind these
+    const int jobs = min(n, limit);
     if (jobs == 0 && lane == 0) S.over = 1;
-    if (lane < jobs + 4) S.seq[id * kSetsRoom + lane] = uint16_t(4 * (lane < jobs ? slot : kSetsSlots));
-    if (lane < jobs + 4 - kWave) S.seq[id * kSetsRoom + kWave + lane] = uint16_t(4 * kSetsSlots);
+    asm volatile("" ::: "memory");
+    if (lane < 4) S.seq[id * shape.room + jobs + lane] = uint16_t(4 * kSetsSlots);
     // its lowest gaps: few open ones are put in order, of many the class's are looked through
     int gaps = 0;
     bool all_gaps;
@@ -450,7 +566,7 @@ __device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> 
         const int g = A.state[place].w >> 2;
         int rank = 0;
         for (int l = 0; l < gaps; ++l) rank += __builtin_amdgcn_readlane(g, l) < g;
-        if (lane < gaps && rank < H) { S.head[rank * width + id] = uint32_t(g); S.place[rank * width + id] = uint16_t(place); }
+        if (lane < gaps && rank < H) S.head[id + rank * shape.width] = uint32_t(g);
         all_gaps = gaps <= H;
     } else {
         int g0 = low;
@@ -463,7 +579,7 @@ __device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> 
                 const bool in = on && x.x >= lo && x.x <= hi;
                 const unsigned long long b = __ballot(in);
                 const int rank = gaps + __popcll(b & ((1ull << lane) - 1ull));
-                if (in && rank < H) { S.head[rank * width + id] = uint32_t(x.y); S.place[rank * width + id] = uint16_t(x.x); }
+                if (in && rank < H) S.head[id + rank * shape.width] = uint32_t(x.y);
                 gaps += __popcll(b);
                 if (g0 == low) {                        // the class's lowest open gap only moves up
                     const unsigned long long o = __ballot(on);
@@ -477,115 +593,134 @@ __device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> 
         }
         all_gaps = g0 >= count && gaps <= H;
     }
-    if (lane == 0) S.set[id] = uint32_t(jobs) | uint32_t(min(gaps, H)) << 8 | uint32_t(last && jobs == n) << 16 | uint32_t(all_gaps) << 17;
+    if (lane == 0) {
+        S.head[id + min(gaps, H) * shape.width] = all_gaps ? kSetsServed : kSetsMoreGaps;
+        S.set[id] = uint32_t(jobs) | uint32_t(last) << 16;
+    }
 }
 
-// The rounds of a batch by one wave, N sets per lane.  Leaves why they stopped, at which round of the batch, and
-// what the sets were granted.
+// The rounds of a batch by one wave, N sets per lane.  Leaves why they stopped and at which round of the batch; who was
+// granted what is read off the claims.
+// A lane issues an instruction every five cycles or so, and so a round takes as long as its instructions and one trip to
+// LDS.  What is seldom (a set without a job or a gap at hand) is looked for in one go and sorted out aside, the round
+// then begun anew; the next jobs are shifted in from eight that are there, instead of being fetched once it is known
+// how many were passed; a lane without a set goes on with words that change nothing.  0.40 -> 0.21 us a round of up
+// to 64 sets.
 template <int N, int BLOCKS>
-__device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n_sets, int width, int H, int before, int cap)
+__device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n_sets, const SetsShape &shape, int before, int cap)
 {
-    constexpr uint32_t nobody = 4 * kSetsSlots;
     auto claim_at = [&](uint32_t off) -> uint32_t & { return *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(S.jobs.claim) + off); };
     uint2 c[N];                     // the slots of the next four jobs (byte offsets of their claims)
-    uint32_t head[N], next[N];      // the lowest open gap, and the next one
-    int p[N], len[N], heads[N], won[N];         // jobs passed, jobs and gaps at hand, gaps granted
-    int active[N], no_jobs[N], no_gaps[N];      // it has gaps and jobs; nothing behind those at hand
+    uint32_t head[N];               // the lowest open gap
+    const uint32_t *next[N];        // where the one after it is
+    const uint16_t *at[N];          // where the slots are
     uint32_t cand[N], word[N];      // the claim of the round before
-    auto window = [&](int i) { __builtin_memcpy(&c[i], &S.seq[(lane + i * kWave) * kSetsRoom + p[i]], 8); };
+    uint32_t out[N];                // all ones: no gaps or no jobs are left
+    auto four = [](const uint16_t *from) { uint2 x; __builtin_memcpy(&x, from, 8); return x; };
+    auto leave = [&](int i) {
+        at[i] = S.idle;
+        c[i] = four(at[i]);
+        head[i] = 0;
+        out[i] = ~0u;
+    };
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int id = lane + i * kWave;
-        const uint32_t info = id < n_sets ? S.set[id] : 0u;
-        len[i] = int(info & 255u);
-        heads[i] = int(info >> 8 & 255u);
-        no_jobs[i] = int(info >> 16 & 1u);
-        no_gaps[i] = int(info >> 17 & 1u);
-        p[i] = 0;
-        won[i] = 0;
-        active[i] = int(id < n_sets);
+        at[i] = &S.seq[min(id, n_sets - 1) * shape.room];
+        next[i] = &S.head[id + shape.width];
         head[i] = S.head[id];
-        next[i] = S.head[width + id];
-        cand[i] = nobody;
+        c[i] = four(at[i]);
+        out[i] = 0;
+        cand[i] = kSetsNobody;
         word[i] = ~0u;
-        window(i);
+        if (id >= n_sets) leave(i);
     }
-    int why = kSetsPause, q = 1;
-    for (;; ++q) {
+    int why = kSetsPause;
+    const int last = min(cap - before, kSetsMostRounds);
+    int q = 1;
+    for (;;) {
         const uint32_t now = uint32_t(q) << 20;
-        uint32_t w[N][4], outcome[N];
+        uint32_t w[N][4], outcome[N], after[N];
+        uint2 more[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             w[i][0] = claim_at(c[i].x & 0xffffu); w[i][1] = claim_at(c[i].x >> 16);
             w[i][2] = claim_at(c[i].y & 0xffffu); w[i][3] = claim_at(c[i].y >> 16);
             outcome[i] = claim_at(cand[i]);
+            more[i] = four(at[i] + 4);
+            after[i] = *next[i];
         }
 #pragma unroll
         for (int i = 0; i < N; ++i)     // all of them are on their way before the first is waited for
-            asm volatile("" : "+v"(w[i][0]), "+v"(w[i][1]), "+v"(w[i][2]), "+v"(w[i][3]), "+v"(outcome[i]));
+            asm volatile("" : "+v"(w[i][0]), "+v"(w[i][1]), "+v"(w[i][2]), "+v"(w[i][3]), "+v"(outcome[i]), "+v"(more[i].x), "+v"(more[i].y), "+v"(after[i]));
+        bool rare = q > last;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            if (outcome[i] == word[i]) {      // (the job it was granted goes where the set's first ones have been read)
-                S.seq[(lane + i * kWave) * kSetsRoom + won[i]] = uint16_t(cand[i]);
-                ++won[i];
-                head[i] = next[i];
-                next[i] = S.head[min(won[i] + 1, H - 1) * width + lane + i * kWave];
-                if (no_gaps[i] & int(won[i] == heads[i])) active[i] = 0;
+            const bool won = outcome[i] == word[i];
+            head[i] = won ? after[i] : head[i];
+            next[i] += won ? shape.width : 0;
+            rare |= (max(max(w[i][0], w[i][1]), max(w[i][2], w[i][3])) < now) | (head[i] >= kSetsServed);
+        }
+        if (__builtin_expect(__ballot(rare) != 0, 0)) {
+            bool none[N], go_on = false, lost = false;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if (head[i] == kSetsServed) leave(i);
+                lost |= out[i] == 0;
+                cand[i] = kSetsNobody;          // its outcome is known
+                word[i] = ~0u;
+                none[i] = out[i] == 0 && max(max(w[i][0], w[i][1]), max(w[i][2], w[i][3])) < now;
             }
-        }
-        if (before + q > cap) {
-#pragma unroll
-            for (int i = 0; i < N; ++i)
-                if (active[i]) S.lost = 1;
-            why = kSetsAtCap;
-            break;
-        }
-        int passed[N], cannot = 0, dry = 0, some = 0;
-        uint32_t job[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            for (;;) {          // none of the four is free, and there are more: seldom
-                const bool more = active[i] != 0 && max(max(w[i][0], w[i][1]), max(w[i][2], w[i][3])) < now && p[i] + 4 < len[i];
-                if (__builtin_expect(__ballot(more) == 0, 1)) break;
-                if (more) { p[i] += 4; window(i); }
-                w[i][0] = claim_at(c[i].x & 0xffffu); w[i][1] = claim_at(c[i].x >> 16);
-                w[i][2] = claim_at(c[i].y & 0xffffu); w[i][3] = claim_at(c[i].y >> 16);
+            if (q > last) {
+                if (lost) S.lost = 1;
+                why = kSetsAtCap;
+                break;
             }
-            // the first free one
-            job[i] = w[i][2] >= now ? c[i].y & 0xffffu : c[i].y >> 16;
-            int f = w[i][2] >= now ? 3 : w[i][3] >= now ? 4 : 0;
-            job[i] = w[i][1] >= now ? c[i].x >> 16 : job[i];
-            f = w[i][1] >= now ? 2 : f;
-            job[i] = w[i][0] >= now ? c[i].x & 0xffffu : job[i];
-            f = w[i][0] >= now ? 1 : f;
-            f = active[i] ? f : 0;
-            dry |= active[i] & int(f == 0) & no_jobs[i];
-            cannot |= active[i] & ((int(f == 0) & ~no_jobs[i]) | (int(f != 0) & int(won[i] >= heads[i])));
-            some |= f;
-            passed[i] = f;
-        }
-        if (__builtin_expect(__ballot(cannot) != 0, 0)) break;         // round q cannot be played
-        if (__builtin_expect(__ballot(dry) != 0, 0)) {
+            bool cannot = false, dry = false, some = false;
 #pragma unroll
-            for (int i = 0; i < N; ++i)
-                if (passed[i] == 0) active[i] = 0;
-            S.closed = q;
+            for (int i = 0; i < N; ++i) {
+                const int id = min(lane + i * kWave, n_sets - 1);
+                const uint32_t info = S.set[id];
+                if (none[i] && at[i] + 4 < &S.seq[id * shape.room + int(info & 255u)]) {       // there are more
+                    at[i] += 4;
+                    c[i] = four(at[i]);
+                    none[i] = false;
+                    go_on = true;
+                }
+                cannot |= none[i] ? !(info >> 16) : head[i] == kSetsMoreGaps;
+                dry |= none[i];
+            }
+            if (__ballot(go_on)) continue;
+            if (__ballot(cannot)) break;         // round q cannot be played
+            if (__ballot(dry)) S.closed = q;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if (none[i]) leave(i);
+                some |= out[i] == 0;
+            }
+            if (!__ballot(some)) { why = kSetsNoClaim; break; }       // nobody claims anything in round q
+            continue;
         }
-        if (__builtin_expect(__ballot(some) == 0, 0)) { why = kSetsNoClaim; break; }       // nobody claims anything in round q
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            cand[i] = passed[i] ? job[i] : nobody;
-            word[i] = passed[i] ? now | head[i] : ~0u;
-            p[i] += passed[i];
-            // (without a claim: the word behind the last slot, which stays what it is)
+            // the first free one, and what is shifted in
+            const bool f0 = w[i][0] >= now, f1 = w[i][1] >= now, f2 = w[i][2] >= now;
+            const uint32_t s01 = f0 ? c[i].x & 0xffffu : c[i].x >> 16, s23 = f2 ? c[i].y & 0xffffu : c[i].y >> 16;
+            const bool none_of_two = !(f0 | f1);
+            cand[i] = none_of_two ? s23 : s01;
+            word[i] = now | head[i] | out[i];
             atomicMin(&claim_at(cand[i]), word[i]);
-            window(i);
+            at[i] += none_of_two ? (f2 ? 3 : 4) : (f0 ? 1 : 2);
+            const bool all = none_of_two & !f2;
+            const uint32_t shift = f0 | (none_of_two & f2) ? 16u : 0u;
+            const uint32_t d0 = all ? more[i].x : f0 ? c[i].x : c[i].y, d1 = all ? more[i].y : f0 ? c[i].y : more[i].x;
+            const uint32_t d2 = f0 ? more[i].x : more[i].y;
+            c[i].x = __builtin_amdgcn_alignbit(d1, d0, shift);
+            c[i].y = __builtin_amdgcn_alignbit(d2, d1, shift);
         }
+        ++q;
         asm volatile("" ::: "memory");
     }
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        if (lane + i * kWave < n_sets) S.won[lane + i * kWave] = won[i];
     if (lane == 0) { S.end = q; S.why = why; }
 }
 
@@ -603,8 +738,8 @@ __device__ __forceinline__ void sets_classes(const SetsArgs &A, SetsShared<BLOCK
         const int c = A.gap_cls[A.lb_begin[tid]];
         if (tid == 0 || A.gap_cls[A.lb_begin[tid - 1]] != c) S.first[c] = tid;
     }
-    for (int i = tid; i <= kSetsSlots; i += kSetsThreads) sets_clear(S.jobs, i);
-    if (tid < 4 * kSetsMost) S.seq[(tid >> 2) * kSetsRoom + (tid & 3)] = uint16_t(4 * kSetsSlots);      // (sets that there are not)
+    for (int i = tid; i < kSetsSlots + 2; i += kSetsThreads) sets_clear(S.jobs, i);
+    if (tid < kSetsMostRounds + 11) S.idle[tid] = uint16_t(kSetsIdle);
     if (tid < kMaxClasses) S.low[tid] = 0;
     __syncthreads();
 }
@@ -612,8 +747,8 @@ __device__ __forceinline__ void sets_classes(const SetsArgs &A, SetsShared<BLOCK
 // A batch: the pieces are joined, its rounds played, and the grants written down.  held: the bitmap that sets_form
 // reads.  Returns whether the process has ended (out says how), and how many rounds were played; -1: too much
 // work, none was.
-template <int BLOCKS>
-__device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS> &S, int done, uint32_t *held, int &played)
+template <bool LISTS, int BLOCKS>
+__device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS> &S, int done, int least, uint32_t *held, int &played)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_classes = A.plan[kPlanClasses];
@@ -626,7 +761,7 @@ __device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS>
         S.pieces[u] = int8_t(max(n, 0));
         if (n < 0) atomicOr(&S.over, -n);
     }
-    for (int k = tid; k < A.n_lb * kSetsPieces; k += kSetsThreads) S.piece_jobs[k] = uint8_t(A.block[k / kSetsPieces].piece[k % kSetsPieces].jobs | A.block[k / kSetsPieces].piece[k % kSetsPieces].last << 7);
+    for (int k = tid; k < A.n_lb * kSetsPieces; k += kSetsThreads) S.none[k] = uint8_t(A.block[k / kSetsPieces].piece[k % kSetsPieces].jobs == 0);
     __syncthreads();
     played = S.over & 1 ? -1 : 0;
     if (S.over) return false;
@@ -635,36 +770,35 @@ __device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS>
     __syncthreads();
     const int n_sets = S.n;
     if (n_sets > kSetsMost) return false;
-    const int width = n_sets <= kWave ? kWave : n_sets <= 2 * kWave ? 2 * kWave : kSetsMost, H = min(kSetsMostHeads, kSetsHeads / width);
-    for (int id = wave; id < n_sets; id += kSetsWaves) sets_fill(A, S, id, lane, wave, width, H);
+    const SetsShape shape = sets_shape(n_sets);
+    // where there are many sets the batch ends by one of them that has hardly more jobs than they are to have in common
+    const int most = n_sets <= kSetsWaves ? shape.most : min(shape.most, 3 * least / 2);
+    for (int id = wave; id < n_sets; id += kSetsWaves) sets_fill<LISTS>(A, S, id, lane, wave, shape, most, held);
     __syncthreads();
     const bool over = S.over != 0;
     if (!over && wave == 0) {
-        if (width == kWave) sets_play<1>(S, lane, n_sets, width, H, done, A.cap);
-        else if (width == 2 * kWave) sets_play<2>(S, lane, n_sets, width, H, done, A.cap);
-        else sets_play<4>(S, lane, n_sets, width, H, done, A.cap);
+        if (n_sets == 0) {              // nobody claims anything
+            if (lane == 0) { S.end = 1; S.why = done < A.cap ? kSetsNoClaim : kSetsAtCap; }
+        } else if (n_sets <= kWave) sets_play<1>(S, lane, n_sets, shape, done, A.cap);
+        else if (n_sets <= 2 * kWave) sets_play<2>(S, lane, n_sets, shape, done, A.cap);
+        else sets_play<4>(S, lane, n_sets, shape, done, A.cap);
     }
     __syncthreads();
     // the rounds played: not one that could not be; one without any claim if it found out that a set has no job left
     const int why = S.why;
     played = over ? -1 : why == kSetsNoClaim && S.closed == S.end ? S.end : S.end - 1;
-    if (!over) {
-        for (int id = wave; id < n_sets; id += kSetsWaves) {        // the grants of a set, a lane each
-            if (lane >= S.won[id]) continue;
-            const int place = S.place[lane * width + id];
-            A.state[place].y = int(S.jobs.job[S.seq[id * kSetsRoom + lane] >> 2]);
-            A.state[place].w = int(S.head[lane * width + id]) << 2 | 1;
+    for (int k = tid; k < kSetsSlots + 2; k += kSetsThreads) {
+        const uint32_t j = k < kSetsSlots ? S.jobs.job[k] : kSetsNoJob, claim = S.jobs.claim[k];
+        if (j != kSetsNoJob && int(claim >> 20) <= played) {        // named, and granted to the gap of the smallest claim
+            const int gap = int(claim & 0xfffffu), place = A.place_of[gap];
+            atomicOr(&held[j >> 5], 1u << (j & 31u));
+            A.state[place].y = int(j);
+            A.state[place].w = gap << 2 | 1;
             atomicAnd(&S.open[place >> 6], ~(1ull << (place & 63)));
-        }
-        __syncthreads();
-    }
-    for (int k = tid; k <= kSetsSlots; k += kSetsThreads) {
-        if (k < kSetsSlots) {
-            const uint32_t j = S.jobs.job[k];
-            if (j != kSetsNoJob && int(S.jobs.claim[k] >> 20) <= played) atomicOr(&held[j >> 5], 1u << (j & 31u));
         }
         sets_clear(S.jobs, k);
     }
+    __syncthreads();
     for (int u = tid; u < A.n_lb; u += kSetsThreads) A.block[u].open = S.open[u];
     if (over || why == kSetsPause) return false;
     if (tid == 0) {
@@ -675,10 +809,10 @@ __device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS>
 
 // After a batch of `played` rounds: the jobs the gaps of a set are to have in common in the next one, and whether
 // to go on.
-__device__ __forceinline__ bool sets_go_on(int played, int &least, int &strain)
+__device__ __forceinline__ bool sets_go_on(int played, int most, int &least, int &strain)
 {
     if (played < 0) return false;
-    least = min(max(2 * played, kSetsLeastFirst), kSetsLeast);
+    least = min(max(2 * played, kSetsLeastFirst), most);
     strain = max(strain + (played <= kSetsShort ? 1 : -1), 0);
     return strain < kSetsPatience;
 }
@@ -712,12 +846,12 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_one(SetsArgs A)
     int done = A.out[kSoloRounds], least = kSetsLeastFirst, strain = 0, played = 0;
     for (;;) {
         __syncthreads();
-        for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_form(A, u, lane, least, s_held, S.found[wave], S.found_from[wave]);
+        for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_form<false>(A, u, lane, least, s_held);
         __syncthreads();
-        const bool ended = sets_batch(A, S, done, s_held, played);
+        const bool ended = sets_batch<false>(A, S, done, least, s_held, played);
         done += max(played, 0);
         if (ended) return;
-        if (!sets_go_on(played, least, strain)) break;
+        if (!sets_go_on(played, kSetsLeast, least, strain)) break;
     }
     if (tid == 0) {
         A.out[kSoloDone] = kSetsLeft; A.out[kSoloRounds] = done; A.out[kSoloStable] = 0;
@@ -750,14 +884,13 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_begin(SetsArgs A)
 __global__ __launch_bounds__(kSetsFormThreads) void k_sets_form(SetsArgs A)
 {
     __shared__ uint4 s_held[kHeldMaxWords / 4];
-    __shared__ uint32_t s_job[kSetsFormThreads / kWave][kWave], s_from[kSetsFormThreads / kWave][kWave];
     if (A.out[kSoloDone] != kSetsRunning) return;
     const uint4 *held = reinterpret_cast<const uint4 *>(A.held);
     for (int i = threadIdx.x; i < A.held_words / 4; i += kSetsFormThreads) s_held[i] = held[i];
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int u = blockIdx.x * (kSetsFormThreads / kWave) + wave;
-    if (u < A.n_lb) sets_form(A, u, lane, A.out[kSetsState] >> 8, reinterpret_cast<const uint32_t *>(s_held), s_job[wave], s_from[wave]);
+    if (u < A.n_lb) sets_form<true>(A, u, lane, A.out[kSetsState] >> 8, reinterpret_cast<const uint32_t *>(s_held));
 }
 
 __global__ __launch_bounds__(kSetsThreads) void k_sets_play(SetsArgs A)
@@ -767,9 +900,9 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_play(SetsArgs A)
     const int done = A.out[kSoloRounds];
     sets_classes(A, S);
     if (threadIdx.x < kMaxClasses) S.low[threadIdx.x] = A.low[threadIdx.x];
-    int played = 0, least = 0, strain = A.out[kSetsState] & 255;
-    if (sets_batch(A, S, done, A.held, played)) return;
-    const bool go_on = sets_go_on(played, least, strain);
+    int played = 0, least = A.out[kSetsState] >> 8, strain = A.out[kSetsState] & 255;
+    if (sets_batch<true>(A, S, done, least, A.held, played)) return;
+    const bool go_on = sets_go_on(played, kSetsLeastMany, least, strain);
     if (threadIdx.x < kMaxClasses) A.low[threadIdx.x] = S.low[threadIdx.x];
     if (threadIdx.x == 0) {
         A.out[kSoloRounds] = done + max(played, 0);

@@ -479,7 +479,9 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     const bool solo = solo_fits && cap >= solo_first + solo_few;
     const int solo_waves = (n_subs + kWave - 1) / kWave > kSoloMinWaves ? (n_subs + kWave - 1) / kWave : kSoloMinWaves;
     // and the calm rounds after it, in batches: with a place per record (Medium tick 1775 -> 1290 us)
-    const bool sets = solo && n_subs <= kSetsMaxBlocks && J <= kPlacedJobs;
+    const int64_t list_room = L.entry_cap * 8 / (int64_t(n_subs > 0 ? n_subs : 1) * kSetsPieces * 6);
+    const int list_jobs = int(list_room < kSetsListed ? list_room / 2 * 2 : kSetsListed);
+    const bool sets = solo && n_subs <= kSetsMaxBlocks && J <= kPlacedJobs && (n_subs <= kSetsOneBlocks || list_jobs >= kSetsLeastListed);
     // (records of four bytes leave half of their space to the places; entry_cap is at least 192)
     void *rec = ws_ptr<void>(ctx, L.g_rec);
     uint16_t *rec_from = ws_ptr<uint16_t>(ctx, L.g_rec + align_up(size_t(L.entry_cap) * sizeof(Rec32)));
@@ -582,11 +584,14 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
                 args.place_of = pos_tab;           // the lists are built: the tables of positions are done with
                 args.by_class = ws_ptr<int2>(ctx, L.gap_tile_key);
                 // (the states' space behind those of the list blocks that there are)
-                args.list = reinterpret_cast<SetsList *>(state + size_t(n_subs) * kWave);
-                args.block = reinterpret_cast<SetsBlock *>(args.list + size_t(n_subs) * kSetsPieces);
+                args.block = reinterpret_cast<SetsBlock *>(state + size_t(n_subs) * kWave);
                 args.low = reinterpret_cast<int32_t *>(args.block + n_subs);
+                // (the records are sorted: the buffers of the entries are free)
+                args.list_jobs = list_jobs;
+                args.list = reinterpret_cast<uint32_t *>(ekey[0]);
+                args.list_from = reinterpret_cast<uint16_t *>(args.list + size_t(n_subs) * kSetsPieces * list_jobs);
                 static_assert((kListSplits * kMaxClasses + kMaxClasses - kSetsMaxBlocks) * kWave * sizeof(int4) >
-                              size_t(kSetsMaxBlocks) * kSetsBlockBytes + kMaxClasses * 4, "room for them");
+                              size_t(kSetsMaxBlocks) * sizeof(SetsBlock) + kMaxClasses * 4, "room for them");
                 args.out = counters + 8;
                 args.cap = int(cap);
                 args.n_gaps = G;

@@ -55,6 +55,15 @@ def test_calm_rounds(engine, oracle, caps, groups, gaps_each, jobs, mixed):
     full_tick_check(engine, oracle, _calm(caps, groups, gaps_each, jobs, mixed), policies=[0, 3], resolve_modes=(0,))
 
 
+@pytest.mark.parametrize("caps,groups,gaps_each,jobs", [
+    (1, 1, 600, 1500), (2, 1, 300, 400),                        # batches as long as a set's jobs and gaps at hand allow
+    (16, 1, 40, 1200), (17, 1, 40, 1200), (32, 1, 20, 1200), (33, 1, 20, 1200), (64, 1, 10, 1200), (33, 2, 8, 900),
+    (40, 2, 6, 900), (41, 2, 6, 900),                           # one launch, and launches in turn
+    (43, 3, 2, 100), (43, 3, 2, 40)])                           # fewer jobs listed for a piece than elsewhere, or no room for any
+def test_jobs_at_hand(engine, oracle, caps, groups, gaps_each, jobs):
+    full_tick_check(engine, oracle, _calm(caps, groups, gaps_each, jobs, 0.05, seed=3), policies=[0, 3], resolve_modes=(0,))
+
+
 @pytest.mark.parametrize("max_rounds", [41, 56, 57, 80, 119, 120, 121])
 @pytest.mark.parametrize("caps,groups,gaps_each", [(1, 1, 120), (43, 3, 2)])
 def test_caps_within_a_batch(engine, oracle, caps, groups, gaps_each, max_rounds):
