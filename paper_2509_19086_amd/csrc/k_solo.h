@@ -52,8 +52,11 @@ constexpr int kSoloMostSteps = 48;      // steps after which it stops in the mid
 constexpr int kSoloStart = 3;           // effort per wave of the last launched round up to which it starts;
 constexpr int kSoloStartFew = 16;       // with few list blocks, whose start and whose rounds in pieces cost little
 enum { kSoloDone = 0, kSoloRounds = 1, kSoloStable = 2 };
-// Rounds are calm if few pieces were served in the last kSoloCalmRounds of them (a power of two).
-constexpr int kSoloCalmRounds = 32, kSoloCalmPieces = 128;
+// Rounds are calm if few pieces were served in the last ones of them (two to the power of the shift).  Where one launch
+// plays them from there on (k_sets_one) it is worth to begin early, and to begin in vain: 2048 gaps x 8192 jobs 905 us a tick
+// by the first line, 810 by the second; 118 list blocks, with launches in turn, 5.48 ms by the first, 6.1 with 512 pieces.
+constexpr int kSoloCalmShift = 5, kSoloCalmPieces = 128;
+constexpr int kSoloCalmShiftFew = 3, kSoloCalmPiecesFew = 8;
 enum { kSoloHandedBack = 0, kSoloEnded = 1, kSoloPutOff = 2, kSoloCalm = 3 };      // what out[kSoloDone] says
 
 __device__ __forceinline__ unsigned long long solo_readlane64(unsigned long long v, int l)
@@ -78,7 +81,7 @@ template <bool SMALL>
 __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     int4 *state, const int32_t *__restrict__ list_off, const Rec32 *__restrict__ rec, unsigned long long *claim, int after,
     int first_check, int cap, int n_lb, int held_words, uint32_t *held, const int32_t *__restrict__ cnt_lost,
-    const int32_t *__restrict__ cnt_cand, int calm_from, int32_t *effort, int32_t *out)
+    const int32_t *__restrict__ cnt_cand, int calm_from, int calm_shift, int calm_pieces, int32_t *effort, int32_t *out)
 {
     __shared__ uint32_t s_held[2][kHeldMaxWords + 4];           // the word behind the last job's is all ones: nobody's job
     __shared__ SoloTables s_tabs;       // the claims of this round and of the one before or after it
@@ -88,7 +91,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
     // by round stamp: somebody claims, a wave gives up, (round << 8 | most effort of a wave), open lanes found nothing more
     __shared__ int4 s_ctl[2];
     __shared__ int s_flag;
-    __shared__ int s_served[2];         // pieces served, by turns of kSoloCalmRounds rounds
+    __shared__ int s_served[2];         // pieces served, by turns of as many rounds as have to be calm
     __shared__ int s_order[SMALL ? kSoloSmallBlocks * kWave : 1];      // per list block its open lanes, lowest gap first: gap << 6 | lane
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int threads = blockDim.x, waves = threads / kWave;
@@ -385,7 +388,7 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
                 set_mark(marked_piece);
             }
         }
-        if (n_pieces && lane == 0) atomicAdd(&s_served[(round / kSoloCalmRounds) & 1], n_pieces);
+        if (n_pieces && lane == 0) atomicAdd(&s_served[(round >> calm_shift) & 1], n_pieces);
         if (n_pieces + step > kSoloEasy && lane == 0) {
             if (over) s_ctl[half].y = round;
             atomicMax(&s_ctl[half].z, (round << 8) | (n_pieces + step));
@@ -434,10 +437,10 @@ __global__ __launch_bounds__(kSoloMaxWaves * kWave) void k_grant_solo(
         done = round;
         strain = max(strain + max((ctl.z >> 8) == round ? (ctl.z & 255) - kSoloEasy : 0, 0) - 1, 0);
         // (the other turn's count is complete, and cleared half a turn later)
-        const int turn = round % kSoloCalmRounds;
-        int *const served = &s_served[((round / kSoloCalmRounds) & 1) ^ 1];
-        if (turn == kSoloCalmRounds / 2 && tid == 0) *served = 0;
-        if (turn == 0 && round >= calm_from) calm = *served <= kSoloCalmPieces;
+        const int turn = round & ((1 << calm_shift) - 1);
+        int *const served = &s_served[((round >> calm_shift) & 1) ^ 1];
+        if (turn == 1 << (calm_shift - 1) && tid == 0) *served = 0;
+        if (turn == 0 && round >= calm_from) calm = *served <= calm_pieces;
         if (round == cap || strain > kSoloPatience || calm) {
             // the block stops here.  A lane still open has lost this round; if there is none, the process has ended with it
             if (open) s_flag = 1;

@@ -542,7 +542,10 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     int64_t next_check = 1;      // first round whose end is not yet decided
     int64_t open_left = cap;     // rounds that can still follow, as far as is known
     bool finished = false, sets_built = false;
-    int64_t calm_wait = kSoloCalmRounds;
+    const bool few_blocks = n_subs <= kSetsOneBlocks;
+    const int calm_shift = few_blocks ? kSoloCalmShiftFew : kSoloCalmShift, calm_pieces = few_blocks ? kSoloCalmPiecesFew : kSoloCalmPieces;
+    const int64_t calm_rounds = int64_t(1) << calm_shift;
+    int64_t calm_wait = calm_rounds;
     constexpr int64_t kLaunchedRounds = 64;
     int64_t batch = solo ? solo_first : kLaunchedRounds;   // rounds enqueued between looks at the flags; grows, a finished batch costs little
     const int64_t most_rounds = solo ? 256 : 1024;  // (a look at whether the block can go on costs three or four rounds)
@@ -563,63 +566,63 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             auto solo_kern = n_subs <= kSoloSmallBlocks ? k_grant_solo<true> : k_grant_solo<false>;
             hipLaunchKernelGGL(solo_kern, dim3(1), dim3(solo_waves * kWave), 0, st, state, list_off, static_cast<const Rec32 *>(rec),
                                claim, int(upto), int(next_check), int(cap), n_subs, held_words, held, cnt_lost, cnt_cand,
-                               sets && upto + calm_wait < INT32_MAX ? int(upto + calm_wait) : INT32_MAX, counters + 14, counters + 8);
+                               sets && upto + calm_wait < INT32_MAX ? int(upto + calm_wait) : INT32_MAX, calm_shift, calm_pieces, counters + 14, counters + 8);
             SJA_HIP(hipGetLastError(), "k_grant_solo launch");
+            SetsArgs args{};
+            args.state = state;
+            args.list_off = list_off;
+            args.rec = static_cast<const Rec32 *>(rec);
+            args.rec_from = rec_from;
+            args.claim = claim;
+            args.held = held;
+            args.plan = plan;
+            args.class_begin = class_begin;
+            args.gap_cls = ws_ptr<int32_t>(ctx, L.gap_cls);
+            args.lb_begin = lb_begin;
+            args.lb_end = lb_end;
+            args.gap_order = gap_order;
+            args.place_of = pos_tab;           // the lists are built: the tables of positions are done with
+            args.by_class = ws_ptr<int2>(ctx, L.gap_tile_key);
+            // (the states' space behind those of the list blocks that there are)
+            args.block = reinterpret_cast<SetsBlock *>(state + size_t(n_subs) * kWave);
+            args.low = reinterpret_cast<int32_t *>(args.block + n_subs);
+            // (the records are sorted: the buffers of the entries are free)
+            args.list_jobs = list_jobs;
+            args.list = reinterpret_cast<uint32_t *>(ekey[0]);
+            args.list_from = reinterpret_cast<uint16_t *>(args.list + size_t(n_subs) * kSetsPieces * list_jobs);
+            static_assert((kListSplits * kMaxClasses + kMaxClasses - kSetsMaxBlocks) * kWave * sizeof(int4) >
+                          size_t(kSetsMaxBlocks) * sizeof(SetsBlock) + kMaxClasses * 4, "room for them");
+            args.out = counters + 8;
+            args.cap = int(cap);
+            args.n_gaps = G;
+            args.n_lb = n_subs;
+            args.held_words = held_words;
+            args.build = !sets_built;
+            // one launch that returns at once if the block has not left the rounds calm: 5 us, a look 20
+            const bool sets_follow = sets && few_blocks;
+            if (sets_follow) {
+                hipLaunchKernelGGL(k_sets_one, dim3(1), dim3(kSetsThreads), 0, st, args);
+                SJA_HIP(hipGetLastError(), "k_sets_one launch");
+            }
             int rc = look();
             if (rc != SJA_OK) return rc;
-            if (h_out[kSoloDone] == kSoloCalm) {
-                SetsArgs args{};
-                args.state = state;
-                args.list_off = list_off;
-                args.rec = static_cast<const Rec32 *>(rec);
-                args.rec_from = rec_from;
-                args.claim = claim;
-                args.held = held;
-                args.plan = plan;
-                args.class_begin = class_begin;
-                args.gap_cls = ws_ptr<int32_t>(ctx, L.gap_cls);
-                args.lb_begin = lb_begin;
-                args.lb_end = lb_end;
-                args.gap_order = gap_order;
-                args.place_of = pos_tab;           // the lists are built: the tables of positions are done with
-                args.by_class = ws_ptr<int2>(ctx, L.gap_tile_key);
-                // (the states' space behind those of the list blocks that there are)
-                args.block = reinterpret_cast<SetsBlock *>(state + size_t(n_subs) * kWave);
-                args.low = reinterpret_cast<int32_t *>(args.block + n_subs);
-                // (the records are sorted: the buffers of the entries are free)
-                args.list_jobs = list_jobs;
-                args.list = reinterpret_cast<uint32_t *>(ekey[0]);
-                args.list_from = reinterpret_cast<uint16_t *>(args.list + size_t(n_subs) * kSetsPieces * list_jobs);
-                static_assert((kListSplits * kMaxClasses + kMaxClasses - kSetsMaxBlocks) * kWave * sizeof(int4) >
-                              size_t(kSetsMaxBlocks) * sizeof(SetsBlock) + kMaxClasses * 4, "room for them");
-                args.out = counters + 8;
-                args.cap = int(cap);
-                args.n_gaps = G;
-                args.n_lb = n_subs;
-                args.held_words = held_words;
-                args.build = !sets_built;
-                if (n_subs <= kSetsOneBlocks) {
-                    hipLaunchKernelGGL(k_sets_one, dim3(1), dim3(kSetsThreads), 0, st, args);
-                    SJA_HIP(hipGetLastError(), "k_sets_one launch");
+            if (!sets_follow && h_out[kSoloDone] == kSoloCalm) {
+                const dim3 blocks((n_subs + kSetsFormThreads / kWave - 1) / (kSetsFormThreads / kWave)), threads(kSetsFormThreads);
+                hipLaunchKernelGGL(k_sets_open, blocks, threads, 0, st, args);
+                hipLaunchKernelGGL(k_sets_begin, dim3(1), dim3(kSetsThreads), 0, st, args);
+                // (a launch too many does nothing and takes 3 us)
+                for (int pairs = 4; rc == SJA_OK; pairs = pairs < 32 ? 2 * pairs : 32) {
+                    for (int k = 0; k < pairs; ++k) {
+                        hipLaunchKernelGGL(k_sets_form, blocks, threads, 0, st, args);
+                        hipLaunchKernelGGL(k_sets_play, dim3(1), dim3(kSetsThreads), 0, st, args);
+                    }
+                    SJA_HIP(hipGetLastError(), "k_sets_play launch");
                     rc = look();
-                } else {
-                    const dim3 blocks((n_subs + kSetsFormThreads / kWave - 1) / (kSetsFormThreads / kWave)), threads(kSetsFormThreads);
-                    hipLaunchKernelGGL(k_sets_open, blocks, threads, 0, st, args);
-                    hipLaunchKernelGGL(k_sets_begin, dim3(1), dim3(kSetsThreads), 0, st, args);
-                    // (a launch too many does nothing and takes 3 us)
-                    for (int pairs = 4; rc == SJA_OK; pairs = pairs < 32 ? 2 * pairs : 32) {
-                        for (int k = 0; k < pairs; ++k) {
-                            hipLaunchKernelGGL(k_sets_form, blocks, threads, 0, st, args);
-                            hipLaunchKernelGGL(k_sets_play, dim3(1), dim3(kSetsThreads), 0, st, args);
-                        }
-                        SJA_HIP(hipGetLastError(), "k_sets_play launch");
-                        rc = look();
-                        if (h_out[kSoloDone] != kSetsRunning) break;
-                    }
-                    if (rc == SJA_OK && h_out[kSoloDone] == kSetsLeft) {
-                        hipLaunchKernelGGL(k_sets_hand_back, blocks, threads, 0, st, args);
-                        SJA_HIP(hipGetLastError(), "k_sets_hand_back launch");
-                    }
+                    if (h_out[kSoloDone] != kSetsRunning) break;
+                }
+                if (rc == SJA_OK && h_out[kSoloDone] == kSetsLeft) {
+                    hipLaunchKernelGGL(k_sets_hand_back, blocks, threads, 0, st, args);
+                    SJA_HIP(hipGetLastError(), "k_sets_hand_back launch");
                 }
                 if (rc != SJA_OK) return rc;
             }
@@ -627,7 +630,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             if (h_out[kSoloDone] == kSetsLeft) {        // on with k_grant_solo, the longer the shorter it was calm
                 sets_built = true;
                 batch = 0;
-                calm_wait = launched - upto < 4 * calm_wait ? 2 * calm_wait : kSoloCalmRounds;
+                calm_wait = launched - upto < 4 * calm_wait ? 2 * calm_wait : calm_rounds;
             }
             next_check = h_out[kSoloDone] == kSoloPutOff ? launched : launched + 1;
             if (h_out[kSoloDone] == kSoloEnded) {
