@@ -137,16 +137,23 @@ inline hipError_t enqueue_scan(hipStream_t st, int32_t *data, int64_t n, int32_t
 // --------------------------------------------------------------------------
 // Stable radix pass over bare 64-bit keys (the grant-list entries), tiles of
 // kKeyTile items.  A tile is ranked per wave (each wave owns a contiguous
-// quarter, walked in order so the pass stays stable), put in digit order in
+// part, walked in order so the pass stays stable), put in digit order in
 // LDS and written out from there, so that items of one digit leave as one
 // contiguous run.  hist is digit-major ([256][n_tiles]) so that one exclusive
-// scan over it yields every (digit, tile) output offset; with few tiles
-// (FEW) it is tile-major and every tile of the scatter adds its column up
-// itself, which saves the scan's launches.  n lives in device memory (it is
-// produced by earlier kernels).
+// scan over it yields every (digit, tile) output offset; up to kKeyFewTiles tiles
+// (FEW) it is tile-major, with the sums of every kKeyGroup tiles beside it, and every
+// tile of the scatter adds its column up itself, which saves the scan's
+// launches.  n lives in device memory (it is produced by earlier kernels).
+//
+// A pass of some hundred thousand items is a chain of waits (a tile's columns, its
+// keys, a ballot chain and two trips to LDS for every 64 of a wave's items), so
+// a tile has sixteen waves, of four times 64 items each, and four threads a column:
+// 124 tiles 17 us a scatter with four waves and a thread that reads all rows of hist,
+// 9.8 so, the counts 6.8 and 4.0; 387 tiles with payloads 16 and three launches less.
 // --------------------------------------------------------------------------
 constexpr int kKeyTile = 4096;
-constexpr int kKeyPerWave = kKeyTile / 4;
+constexpr int kKeyThreads = 1024, kKeyWaves = kKeyThreads / kWave;
+constexpr int kKeyPerWave = kKeyTile / kKeyWaves;
 constexpr int kKeyChunks = kKeyPerWave / kWave;
 
 // Lanes of the wave (among `valid`) holding the same 8-bit digit as this lane.
@@ -161,22 +168,24 @@ __device__ __forceinline__ unsigned long long digit_peers(unsigned d, bool valid
     return peers;
 }
 
-constexpr int kKeyFewTiles = 256;        // (at 256 tiles the sums take 2 us more in the scatter, the scan takes 10)
+constexpr int kKeyGroup = 16;
+constexpr int kKeyFewTiles = 1024;       // (the scan takes three launches, 12 us and more; a column's sums of so many tiles 20 rows a thread)
+constexpr int kKeyGroupSums = kKeyFewTiles / kKeyGroup * 256;
 
 template <bool FEW>
-__global__ __launch_bounds__(256) void k_keys_hist(const unsigned long long *__restrict__ keys,
-                                                   const int32_t *n_ptr, int shift, unsigned digit_mask, int32_t *hist,
-                                                   int n_tiles)
+__global__ __launch_bounds__(kKeyThreads) void k_keys_hist(const unsigned long long *__restrict__ keys,
+                                                           const int32_t *n_ptr, int shift, unsigned digit_mask, int32_t *hist,
+                                                           int n_tiles, int32_t *group_sums)
 {
     __shared__ int s_h[256];
     const int64_t n = *n_ptr;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    s_h[tid] = 0;
+    if (tid < 256) s_h[tid] = 0;
     __syncthreads();
     const int64_t base = int64_t(blockIdx.x) * kKeyTile;
-#pragma unroll 4
-    for (int r = 0; r < kKeyTile / 256; ++r) {
-        const int64_t i = base + r * 256 + tid;
+#pragma unroll
+    for (int r = 0; r < kKeyTile / kKeyThreads; ++r) {
+        const int64_t i = base + r * kKeyThreads + tid;
         const bool valid = i < n;
         const unsigned d = valid ? unsigned(keys[i] >> shift) & digit_mask : 0u;
         // counting needs no order: a wave whose keys all carry one digit (the block digits, and
@@ -193,7 +202,10 @@ __global__ __launch_bounds__(256) void k_keys_hist(const unsigned long long *__r
         }
     }
     __syncthreads();
-    hist[FEW ? int64_t(blockIdx.x) * 256 + tid : int64_t(tid) * n_tiles + blockIdx.x] = s_h[tid];
+    if (tid >= 256) return;
+    const int h = s_h[tid];
+    hist[FEW ? int64_t(blockIdx.x) * 256 + tid : int64_t(tid) * n_tiles + blockIdx.x] = h;
+    if (FEW && h) atomicAdd(&group_sums[int(blockIdx.x) / kKeyGroup * 256 + tid], h);
 }
 
 // A list record: a job and the lane range [lo, hi) of its list block that one of the job's atoms
@@ -234,45 +246,26 @@ __device__ __forceinline__ REC key_record(unsigned long long v)
 // PAY: every key carries a 32-bit payload that moves with it.  REC other than NoRec: the sorted keys
 // are not written at all, their records are (the pass that finishes the order of the list entries).
 template <bool FEW, bool PAY, typename REC = NoRec>
-__global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *__restrict__ src,
-                                                      unsigned long long *__restrict__ dst,
-                                                      const uint32_t *__restrict__ pay_src,
-                                                      uint32_t *__restrict__ pay_dst, const int32_t *n_ptr,
-                                                      int shift, unsigned digit_mask, const int32_t *__restrict__ hist,
-                                                      int n_tiles, void *rec, uint16_t *rec_from)
+__global__ __launch_bounds__(kKeyThreads) void k_keys_scatter(const unsigned long long *__restrict__ src,
+                                                              unsigned long long *__restrict__ dst,
+                                                              const uint32_t *__restrict__ pay_src,
+                                                              uint32_t *__restrict__ pay_dst, const int32_t *n_ptr,
+                                                              int shift, unsigned digit_mask, const int32_t *__restrict__ hist,
+                                                              int n_tiles, const int32_t *__restrict__ group_sums, int32_t *next_sums,
+                                                              void *rec, uint16_t *rec_from)
 {
     __shared__ unsigned long long s_key[kKeyTile];
     __shared__ uint32_t s_pay[PAY ? kKeyTile : 1];
-    __shared__ int s_cnt[4][256];       // per wave and digit: running count, later the offset inside the digit
+    __shared__ int s_cnt[kKeyWaves][256];       // per wave and digit: running count, later the offset inside the digit
     __shared__ int s_start[256];        // first tile-local slot of a digit
     __shared__ int s_goff[256];         // where the tile's items of a digit go
     __shared__ int s_wsum[4];
     const int64_t n = *n_ptr;
     const int64_t base = int64_t(blockIdx.x) * kKeyTile;
-    if (base >= n) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) s_cnt[w][tid] = 0;
-    if (FEW) {
-        // digit tid: its items in all tiles and in those before this one
-        int all = 0, before = 0;
-#pragma unroll 16
-        for (int t = 0; t < n_tiles; ++t) {
-            const int h = hist[int64_t(t) * 256 + tid];
-            all += h;
-            before += t < int(blockIdx.x) ? h : 0;
-        }
-        const int upto = wave_scan_add(all);
-        if (lane == kWave - 1) s_wsum[wave] = upto;
-        __syncthreads();
-        int off = upto - all + before;
-        for (int w = 0; w < wave; ++w) off += s_wsum[w];
-        s_goff[tid] = off;
-    } else {
-        s_goff[tid] = hist[int64_t(tid) * n_tiles + blockIdx.x];
-    }
-    __syncthreads();
-
+    if (FEW)        // the sums of the next pass start at zero
+        for (int i = int(blockIdx.x) * kKeyThreads + tid; i < kKeyGroupSums; i += int(gridDim.x) * kKeyThreads) next_sums[i] = 0;
+    if (base >= n) return;
     unsigned long long key[kKeyChunks];
     uint32_t pay[PAY ? kKeyChunks : 1];
     int pos[kKeyChunks];
@@ -282,6 +275,44 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
         key[c] = wbase + c * kWave < n ? src[wbase + c * kWave] : ~0ull;
         if (PAY) pay[c] = wbase + c * kWave < n ? pay_src[wbase + c * kWave] : 0u;
     }
+#pragma unroll
+    for (int i = 0; i < kKeyWaves * 256; i += kKeyThreads) s_cnt[0][i + tid] = 0;
+    if (FEW) {
+        // digit d: its items in all tiles and in those before this one, a share of them by each of four threads
+        constexpr int kShares = kKeyThreads / 256;
+        int (*const s_part)[256] = reinterpret_cast<int (*)[256]>(s_key);
+        const int d = tid & 255, share = tid >> 8, own = int(blockIdx.x) / kKeyGroup, groups = (n_tiles + kKeyGroup - 1) / kKeyGroup;
+        int all = 0, before = 0;
+#pragma unroll 8
+        for (int g = share; g < groups; g += kShares) {
+            const int h = group_sums[g * 256 + d];
+            all += h;
+            before += g < own ? h : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kKeyGroup; k += kShares) {
+            const int t = own * kKeyGroup + k + share;
+            if (t < int(blockIdx.x)) before += hist[t * 256 + d];
+        }
+        s_part[share][d] = all;
+        s_part[kShares + share][d] = before;
+        __syncthreads();
+        if (tid < 256) {
+            all = before = 0;
+#pragma unroll
+            for (int k = 0; k < kShares; ++k) { all += s_part[k][d]; before += s_part[kShares + k][d]; }
+            const int upto = wave_scan_add(all);
+            if (lane == kWave - 1) s_wsum[wave] = upto;
+            s_goff[d] = upto - all + before;
+        }
+        __syncthreads();
+        if (tid < 256)
+            for (int w = 0; w < wave; ++w) s_goff[d] += s_wsum[w];
+    } else if (tid < 256) {
+        s_goff[tid] = hist[int64_t(tid) * n_tiles + blockIdx.x];
+    }
+    __syncthreads();
+
     volatile int *cnt = &s_cnt[wave][0];
 #pragma unroll
     for (int c = 0; c < kKeyChunks; ++c) {
@@ -297,21 +328,22 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
     }
     __syncthreads();
 
-    {   // digit tid: offsets of the four waves inside the digit, then the digits' starts
-        const int c0 = s_cnt[0][tid], c1 = s_cnt[1][tid], c2 = s_cnt[2][tid], c3 = s_cnt[3][tid];
-        s_cnt[0][tid] = 0; s_cnt[1][tid] = c0; s_cnt[2][tid] = c0 + c1; s_cnt[3][tid] = c0 + c1 + c2;
-        const int total = c0 + c1 + c2 + c3;
-        int incl = total;
+    // digit tid: offsets of the waves inside the digit, then the digits' starts
+    int total = 0, upto = 0;
+    if (tid < 256) {
+        int h[kKeyWaves];
 #pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int t = __shfl_up(incl, d, kWave);
-            if (lane >= d) incl += t;
-        }
-        if (lane == kWave - 1) s_wsum[wave] = incl;
-        __syncthreads();
-        int off = 0;
+        for (int w = 0; w < kKeyWaves; ++w) h[w] = s_cnt[w][tid];
+#pragma unroll
+        for (int w = 0; w < kKeyWaves; ++w) { s_cnt[w][tid] = total; total += h[w]; }
+        upto = wave_scan_add(total);
+        if (lane == kWave - 1) s_wsum[wave] = upto;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        int off = upto - total;
         for (int w = 0; w < wave; ++w) off += s_wsum[w];
-        s_start[tid] = off + incl - total;
+        s_start[tid] = off;
     }
     __syncthreads();
 #pragma unroll
@@ -325,7 +357,7 @@ __global__ __launch_bounds__(256) void k_keys_scatter(const unsigned long long *
     }
     __syncthreads();
     const int count = int(n - base < kKeyTile ? n - base : kKeyTile);
-    for (int k = tid; k < count; k += 256) {
+    for (int k = tid; k < count; k += kKeyThreads) {
         const unsigned long long v = s_key[k];
         const unsigned d = unsigned(v >> shift) & digit_mask;
         const int64_t o = int64_t(s_goff[d]) + (k - s_start[d]);

@@ -190,20 +190,24 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
 // buffer; `launch` enqueues the scatter kernel of the kind the caller wants.
 template <typename Launch>
 int radix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host, int shift, int width,
-               bool &flip, unsigned long long *const buf[2], Launch &&launch)
+               int &turn, bool &flip, unsigned long long *const buf[2], Launch &&launch)
 {
     const int n_tiles = int((n_host + kKeyTile - 1) / kKeyTile);
     int32_t *hist = ws_ptr<int32_t>(ctx, L.g_hist);
     const unsigned long long *src = buf[flip ? 1 : 0];
     const unsigned digit_mask = (1u << width) - 1u;
     const bool few = n_tiles <= kKeyFewTiles;
-    hipLaunchKernelGGL(few ? k_keys_hist<true> : k_keys_hist<false>, dim3(n_tiles), dim3(256), 0, st, src, n_dev, shift, digit_mask,
-                       hist, n_tiles);
+    // the groups' sums of a pass and of the next one, by turns; the state of the rounds is not in use yet
+    static_assert(size_t(kMaxClasses) * kListSplits * kWave * 16 >= 2 * size_t(kKeyGroupSums) * 4, "room for them");
+    int32_t *sums = ws_ptr<int32_t>(ctx, L.g_state), *next_sums = sums + kKeyGroupSums;
+    if (few && (turn++ & 1)) std::swap(sums, next_sums);
+    hipLaunchKernelGGL(few ? k_keys_hist<true> : k_keys_hist<false>, dim3(n_tiles), dim3(kKeyThreads), 0, st, src, n_dev, shift, digit_mask,
+                       hist, n_tiles, sums);
     SJA_HIP(hipGetLastError(), "k_keys_hist launch");
     if (!few)
         SJA_HIP(enqueue_scan(st, hist, (int64_t(1) << width) * n_tiles, ws_ptr<int32_t>(ctx, L.g_scan_tmp), nullptr),
                 "radix scan launch");
-    launch(few, dim3(n_tiles), src, buf[flip ? 0 : 1], shift, digit_mask, hist, n_tiles);
+    launch(few, dim3(n_tiles), src, buf[flip ? 0 : 1], shift, digit_mask, hist, n_tiles, sums, next_sums);
     SJA_HIP(hipGetLastError(), "k_keys_scatter launch");
     flip = !flip;
     return SJA_OK;
@@ -212,17 +216,17 @@ int radix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_d
 // Stable radix passes over 64-bit keys with a 32-bit payload each, lowest byte first; only the bytes named
 // in byte_mask are sorted on (a byte that is the same in every key needs no pass).
 int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host,
-                    unsigned byte_mask, bool &flip, unsigned long long *const buf[2], uint32_t *const pay[2])
+                    unsigned byte_mask, int &turn, bool &flip, unsigned long long *const buf[2], uint32_t *const pay[2])
 {
     for (int b = 0; b < 8 && n_host > 0; ++b) {
         if (!((byte_mask >> b) & 1u)) continue;
         const bool from = flip;
-        const int rc = radix_pass(ctx, st, L, n_dev, n_host, 8 * b, 8, flip, buf,
+        const int rc = radix_pass(ctx, st, L, n_dev, n_host, 8 * b, 8, turn, flip, buf,
                                   [&](bool few, dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
-                                      const int32_t *hist, int n_tiles) {
+                                      const int32_t *hist, int n_tiles, const int32_t *sums, int32_t *next_sums) {
                                       auto kern = few ? k_keys_scatter<true, true, NoRec> : k_keys_scatter<false, true, NoRec>;
-                                      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, dst,
-                                                         pay[from ? 1 : 0], pay[from ? 0 : 1], n_dev, shift, mask, hist, n_tiles,
+                                      hipLaunchKernelGGL(kern, grid, dim3(kKeyThreads), 0, st, src, dst,
+                                                         pay[from ? 1 : 0], pay[from ? 0 : 1], n_dev, shift, mask, hist, n_tiles, sums, next_sums,
                                                          static_cast<void *>(nullptr), static_cast<uint16_t *>(nullptr));
                                   });
         if (rc != SJA_OK) return rc;
@@ -232,21 +236,21 @@ int radix_sort_keys(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t
 
 // The list entries by list block (they come in rank order), the last pass writes their records.
 template <typename REC>
-int radix_sort_entries(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host, int block_bits,
+int radix_sort_entries(sja_ctx *ctx, hipStream_t st, const Layout &L, const int32_t *n_dev, int64_t n_host, int block_bits, int &turn,
                        unsigned long long *const buf[2], void *rec, uint16_t *rec_from = nullptr)
 {
     bool flip = false;
     const int passes = (block_bits + 7) / 8, width = (block_bits + passes - 1) / passes;
     constexpr int first_bit = std::is_same<REC, Rec32Placed>::value ? kEntryPlacedBlockShift : kEntryBlockShift;
     for (int p = 0; p < passes; ++p) {
-        const int rc = radix_pass(ctx, st, L, n_dev, n_host, first_bit + p * width, width, flip, buf,
+        const int rc = radix_pass(ctx, st, L, n_dev, n_host, first_bit + p * width, width, turn, flip, buf,
                                   [&](bool few, dim3 grid, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
-                                      const int32_t *hist, int n_tiles) {
+                                      const int32_t *hist, int n_tiles, const int32_t *sums, int32_t *next_sums) {
                                       auto kern = p == passes - 1 ? (few ? k_keys_scatter<true, false, REC> : k_keys_scatter<false, false, REC>)
                                                                   : (few ? k_keys_scatter<true, false, NoRec> : k_keys_scatter<false, false, NoRec>);
-                                      hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, dst,
+                                      hipLaunchKernelGGL(kern, grid, dim3(kKeyThreads), 0, st, src, dst,
                                                          static_cast<const uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr),
-                                                         n_dev, shift, mask, hist, n_tiles, rec, rec_from);
+                                                         n_dev, shift, mask, hist, n_tiles, sums, next_sums, rec, rec_from);
                                   });
         if (rc != SJA_OK) return rc;
     }
@@ -347,6 +351,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     //    the primary key and their ties put in order; `both`: by the secondary key first
     const bool mixed = params->policy == SJA_POLICY_MIXED;
     bool flip = false;      // where the atom ids are: perm[flip]
+    int turn = 0;           // of the sorts' passes
     // 24 or 32 bits, or no digest (the hysteresis rule gives many atoms of a job the same cut: long runs of equal keys, and
     // others among them).  8192 jobs of one profile, 2048 gaps: with 24 bits whatever the keys 770 us a resolve with waits
     // between 10^6 and 10^6 + 1000 and 930 under MIXED, by all bytes 600 and 620, so 530 and 525
@@ -383,12 +388,12 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         const int passes = digest_passes;
         if (!both && passes) {
             for (int p = 0; p < passes; ++p) {
-                const int rc = radix_pass(ctx, st, L, counters + 2, n_atoms, 64 - 8 * (passes - p), 8, flip, ekey,
+                const int rc = radix_pass(ctx, st, L, counters + 2, n_atoms, 64 - 8 * (passes - p), 8, turn, flip, ekey,
                                           [&](bool few, dim3 tiles, const unsigned long long *src, unsigned long long *dst, int shift, unsigned mask,
-                                              const int32_t *hist, int n_tiles) {
+                                              const int32_t *hist, int n_tiles, const int32_t *sums, int32_t *next_sums) {
                                               hipLaunchKernelGGL((few ? k_keys_scatter<true, false, NoRec> : k_keys_scatter<false, false, NoRec>), tiles,
-                                                                 dim3(256), 0, st, src, dst, static_cast<const uint32_t *>(nullptr),
-                                                                 static_cast<uint32_t *>(nullptr), counters + 2, shift, mask, hist, n_tiles,
+                                                                 dim3(kKeyThreads), 0, st, src, dst, static_cast<const uint32_t *>(nullptr),
+                                                                 static_cast<uint32_t *>(nullptr), counters + 2, shift, mask, hist, n_tiles, sums, next_sums,
                                                                  static_cast<void *>(nullptr), static_cast<uint16_t *>(nullptr));
                                           });
                 if (rc != SJA_OK) return rc;
@@ -400,7 +405,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         }
         if (!both) {
             unsigned long long *kb[2] = {key_hi, ekey[0]};
-            const int rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), flip, kb, perm);
+            const int rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), turn, flip, kb, perm);
             if (rc != SJA_OK || !mixed) return rc;
             hipLaunchKernelGGL(k_fix_ties, grid, block, 0, st, counters + 2, kb[flip ? 1 : 0], key_lo, perm[flip ? 1 : 0],
                                counters + kCountTies);
@@ -408,14 +413,14 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             return SJA_OK;
         }
         unsigned long long *kb[2] = {key_lo, ekey[0]};
-        const int rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_lo), flip, kb, perm);
+        const int rc = radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_lo), turn, flip, kb, perm);
         if (rc != SJA_OK) return rc;
         // the primary keys in the order reached so far
         unsigned long long *kh[2] = {ekey[1], ekey[0]};
         if (flip) { kh[0] = ekey[0]; kh[1] = ekey[1]; }      // buffer index must follow the id buffers
         hipLaunchKernelGGL(k_gather_keys, grid, block, 0, st, counters + 2, key_hi, perm[flip ? 1 : 0], kh[flip ? 1 : 0]);
         SJA_HIP(hipGetLastError(), "k_gather_keys launch");
-        return radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), flip, kh, perm);
+        return radix_sort_keys(ctx, st, L, counters + 2, n_atoms, bytes_of(bits_hi), turn, flip, kh, perm);
     };
 
     // 3. list entries in rank order: counted, then written, then sorted by list block
@@ -488,9 +493,9 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     if (n_entries > 0) {
         SJA_HIP(launch_entries(std::true_type{}, sets), "k_list_entries launch");
         const int block_bits = bits_for(n_subs > 1 ? n_subs : 2);
-        const int rc = wide_records ? radix_sort_entries<Rec64>(ctx, st, L, counters, n_entries, block_bits, ekey, rec)
-                       : sets       ? radix_sort_entries<Rec32Placed>(ctx, st, L, counters, n_entries, block_bits, ekey, rec, rec_from)
-                                    : radix_sort_entries<Rec32>(ctx, st, L, counters, n_entries, block_bits, ekey, rec);
+        const int rc = wide_records ? radix_sort_entries<Rec64>(ctx, st, L, counters, n_entries, block_bits, turn, ekey, rec)
+                       : sets       ? radix_sort_entries<Rec32Placed>(ctx, st, L, counters, n_entries, block_bits, turn, ekey, rec, rec_from)
+                                    : radix_sort_entries<Rec32>(ctx, st, L, counters, n_entries, block_bits, turn, ekey, rec);
         if (rc != SJA_OK) return rc;
     }
 
@@ -1571,6 +1576,7 @@ int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int3
         also(L.g_ekey1, 2 * (L.entry_cap < kAlikeSlots ? L.entry_cap : kAlikeSlots));      // (used if there are more atoms than that)
         also(L.g_cnt_lost, (G < J ? G : J) + 4);
         also(L.g_cnt_cand, (G < J ? G : J) + 4);
+        also(L.g_state, 2 * kKeyGroupSums);        // (radix_pass)
         if (held_bitmap_words(J) <= kHeldMaxWords) also(L.g_held, 2 * held_bitmap_words(J));
     }
     if (n_init > 0) {

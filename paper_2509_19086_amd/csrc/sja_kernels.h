@@ -977,7 +977,7 @@ __global__ __launch_bounds__(256) void k_select_reduce(int n_gaps, int n_job_til
 // --------------------------------------------------------------------------
 // Arrays that start at zero, cleared along with the outputs (a launch each was a sixth of a small resolve).
 struct ClearList {
-    static constexpr int kMost = 6;
+    static constexpr int kMost = 7;
     int32_t *p[kMost];
     int n[kMost];
 };
