@@ -1406,8 +1406,9 @@ int sja_fit(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W, const 
                 const int64_t row_tiles = (n_gaps + kBitsRows - 1) / kBitsRows;
                 hipLaunchKernelGGL(k_fit_bits, dim3(unsigned(col_tiles * row_tiles)), b256, 0, st, bits, J, plan, gw, gcap);
                 SJA_HIP(hipGetLastError(), "k_fit_bits launch");
-                hipLaunchKernelGGL(k_fit_bits_low, dim3((words + 255) / 256, (n_gaps + kLowRows - 1) / kLowRows), b256, 0, st,
-                                   bits, J, plan, gw);
+                const int low_tiles = int((words + 255) / 256), low_rows = fit_low_rows(low_tiles, n_gaps);
+                hipLaunchKernelGGL(k_fit_bits_low, dim3(low_tiles, (n_gaps + low_rows - 1) / low_rows), b256, 0, st,
+                                   bits, J, low_rows, plan, gw);
                 SJA_HIP(hipGetLastError(), "k_fit_bits launch");
             }
         }

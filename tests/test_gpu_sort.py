@@ -1,5 +1,6 @@
 """The passes that put atoms and list entries in order (k_sort.h): one tile, the edges of a tile and of a group of
-tiles, more tiles than are summed up in the scatter, keys with and without a payload, against the scanning rounds."""
+tiles, more tiles than are summed up in the scatter, keys with and without a payload, against the scanning rounds; and
+the interest rows of short windows (k_fit_bits_low) at the edges of their tiles, against the oracle."""
 import numpy as np
 import pytest
 
@@ -58,3 +59,16 @@ def test_order_by_tiles(engine, jobs, each, gaps, policy):
     _, got = _replies(engine, _staircase(jobs, each, gaps), policy, 12)
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+# words of 32 jobs: a block takes 256 of them, and 8, 16 or 32 rows
+@pytest.mark.parametrize("gaps,jobs", [(1025, 4097), (1033, 8192), (1100, 8193), (4096, 8161), (16400, 8225), (2100, 33000)])
+def test_rows_of_short_windows(engine, oracle, gaps, jobs):
+    wl = _staircase(jobs, 6, gaps, seed=2)
+    wl.W[: gaps // 2] = np.random.default_rng(5).integers(1, 30, size=gaps // 2)         # below many a job's first cut
+    import paper_2509_19086_amd as P
+    t = P.DeviceTick(engine, wl)
+    t.prepare(); t.fit()
+    rows = np.unique(np.concatenate([np.arange(0, gaps, max(1, gaps // 200)), [gaps - 1]]))
+    _, bits = oracle.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W[rows], wl.C[rows])
+    np.testing.assert_array_equal(t.bits.cpu().numpy().view(np.uint32)[rows], bits)
