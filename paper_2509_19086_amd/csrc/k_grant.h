@@ -1021,9 +1021,14 @@ __global__ __launch_bounds__(kFirstThreads) void k_grant_first(
 // Gap positions that are neither granted nor out of candidates.  Every round that
 // does not end the process grants at least one of them, so this bounds the rounds
 // that can still follow; the host sizes its next batch of launches with it.
-__global__ __launch_bounds__(1024) void k_count_open(int lb_cap, const int32_t *__restrict__ plan,
-                                                     const int4 *__restrict__ state, int32_t *out)
+// out: how many, then the counters of n rounds, lost and cand.
+__global__ __launch_bounds__(1024) void k_count_open(int lb_cap, const int32_t *__restrict__ plan, const int4 *__restrict__ state,
+                                                     const int32_t *__restrict__ lost, const int32_t *__restrict__ cand, int n_rounds, int32_t *out)
 {
+    for (int i = threadIdx.x; i < n_rounds; i += 1024) {
+        out[1 + i] = lost[i];
+        out[1 + n_rounds + i] = cand[i];
+    }
     __shared__ int s_sum[1024 / kWave];
     const int n = min(plan[kPlanListBlocks], lb_cap) * kWave;
     int c = 0;

@@ -542,7 +542,7 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             go(with_bitmap ? k_grant_round<true, Rec32> : k_grant_round<false, Rec32>, static_cast<const Rec32 *>(rec));
         return hipGetLastError();
     };
-    std::vector<int32_t> h_lost, h_cand;
+    std::vector<int32_t> h_told;
     int64_t launched = 0;        // kernels 1..launched have been enqueued
     int64_t next_check = 1;      // first round whose end is not yet decided
     int64_t open_left = cap;     // rounds that can still follow, as far as is known
@@ -647,22 +647,22 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         }
         if (upto == cap) SJA_HIP(launch_round(cap + 1, 0), "k_grant_round launch");
         launched = upto;
-        hipLaunchKernelGGL(k_count_open, dim3(1), dim3(1024), 0, st, lb_bound, plan, state, counters + 12);
-        SJA_HIP(hipGetLastError(), "k_count_open launch");
         const int64_t known = (upto == cap) ? cap + 1 : upto;        // kernels that have run
-        h_lost.resize(size_t(known + 1));
-        h_cand.resize(size_t(known + 1));
-        SJA_HIP(hipMemcpyAsync(h_lost.data(), cnt_lost, size_t(known + 1) * 4, hipMemcpyDeviceToHost, st), "round counters");
-        SJA_HIP(hipMemcpyAsync(h_cand.data(), cnt_cand, size_t(known + 1) * 4, hipMemcpyDeviceToHost, st), "round counters");
-        int32_t h_open = 0;
-        SJA_HIP(hipMemcpyAsync(&h_open, counters + 12, 4, hipMemcpyDeviceToHost, st), "open count");
+        // what the host looks at lies side by side (the entries' buffer is free), a copy of its own took 10 us each
+        const int64_t since = next_check, told = known + 1 - since;
+        int32_t *told_at = reinterpret_cast<int32_t *>(ekey[0]);
+        hipLaunchKernelGGL(k_count_open, dim3(1), dim3(1024), 0, st, lb_bound, plan, state, cnt_lost + since, cnt_cand + since, int(told), told_at);
+        SJA_HIP(hipGetLastError(), "k_count_open launch");
+        h_told.resize(size_t(1 + 2 * told));
+        SJA_HIP(hipMemcpyAsync(h_told.data(), told_at, h_told.size() * 4, hipMemcpyDeviceToHost, st), "round counters");
         SJA_HIP(hipStreamSynchronize(st), "round synchronise");
+        const int32_t *h_lost = h_told.data() + 1, *h_cand = h_lost + told;
         // every further round grants at least one open position: no point in enqueueing more than that
-        open_left = int64_t(h_open) + 1;
-        for (int64_t r = next_check; r <= upto; ++r) {
-            if (h_cand[size_t(r)] == 0) { result[0] = int32_t(r); result[1] = 1; finished = true; break; }
+        open_left = int64_t(h_told[0]) + 1;
+        for (int64_t r = since; r <= upto; ++r) {
+            if (h_cand[r - since] == 0) { result[0] = int32_t(r); result[1] = 1; finished = true; break; }
             if (r + 1 > known) { next_check = r; break; }              // losers of r not counted yet
-            if (h_lost[size_t(r)] == 0) { result[0] = int32_t(r); result[1] = 1; finished = true; break; }
+            if (h_lost[r - since] == 0) { result[0] = int32_t(r); result[1] = 1; finished = true; break; }
             if (r == cap) { result[0] = int32_t(cap); result[1] = 0; finished = true; break; }
             next_check = r + 1;
         }
