@@ -63,3 +63,23 @@ def test_equal_digests(engine, oracle, gaps, jobs):
     wl.wait[:] = 7          # and all keys of a tier the same
     wl.mem[:] = 2**20
     check(engine, oracle, wl, (1, 3))
+
+
+# one list for all gaps, so that every round passes an entry of each: one, two and more times the 64 that are brought to LDS
+# together, up to all of it, lists that fit LDS and lists that do not
+@pytest.mark.parametrize("gaps,jobs", [(1, 5), (63, 64), (65, 65), (72, 300), (128, 127), (136, 700), (256, 1024), (257, 1024), (333, 90), (1000, 70), (1024, 64)])
+@pytest.mark.parametrize("max_rounds", [0, 60])
+def test_rounds_along_one_list(engine, oracle, gaps, jobs, max_rounds):
+    wl = make_workload("tiny", 3, n_gaps=gaps, n_jobs=jobs)
+    rng = np.random.default_rng(gaps)
+    wl.seg_off = np.arange(jobs + 1, dtype=np.int64)
+    wl.dur = np.ones(jobs, dtype=np.int32)
+    wl.mem = rng.integers(1000, 2000, size=jobs).astype(np.int32)
+    wl.safe = np.ones(jobs, dtype=np.uint8)
+    wl.progress = np.zeros(jobs, dtype=np.int32)
+    wl.wait = rng.integers(0, 1000, size=jobs).astype(np.int32)
+    wl.sla_class = rng.integers(0, 3, size=jobs).astype(np.uint8)
+    wl.W[:] = 5
+    wl.C = rng.choice(np.array([2000, 1990], np.int32), size=gaps)
+    wl.max_rounds = max_rounds
+    check(engine, oracle, wl, (1, 3))
