@@ -183,7 +183,8 @@ struct SetsArgs {
     uint32_t *list;                 // [list blocks][kSetsPieces][list_jobs] jobs of the pieces, and behind all of them
     uint16_t *list_from;            // the places from which on they are the answer (not for k_sets_one)
     int list_jobs;
-    int32_t *low;                   // per class where its lowest open gap lies among its gaps (between launches)
+    // between launches: per class where its lowest open gap lies among its gaps; its first list block and first position
+    int32_t *low, *classes;
     int32_t *out;
     int cap, n_gaps, n_lb, held_words;
     int build;                      // place_of and by_class are to be made
@@ -263,9 +264,12 @@ __device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, in
 {
     SetsBlock &B = A.block[u];
     unsigned long long rest = B.open;
+    int at = B.at, end = A.list_off[u + 1], n_pieces = 0;
+    asm volatile("" : "+v"(rest), "+v"(at), "+v"(end));        // one trip to memory for all of them
+    rest = sets_readlane64(rest, 0);
+    at = __builtin_amdgcn_readfirstlane(at);
+    end = __builtin_amdgcn_readfirstlane(end);
     if (!rest) return;
-    int at = B.at, n_pieces = 0;
-    const int end = A.list_off[u + 1];
     int first_at = at;
     for (bool first = true; rest; first = false) {
     again:
@@ -724,7 +728,14 @@ __device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n
     if (lane == 0) { S.end = q; S.why = why; }
 }
 
-// The classes, once per launch.
+template <int BLOCKS>
+__device__ __forceinline__ void sets_empty(SetsShared<BLOCKS> &S)
+{
+    for (int i = threadIdx.x; i < kSetsSlots + 2; i += kSetsThreads) sets_clear(S.jobs, i);
+    if (threadIdx.x < kSetsMostRounds + 11) S.idle[threadIdx.x] = uint16_t(kSetsIdle);
+}
+
+// The classes.
 template <int BLOCKS>
 __device__ __forceinline__ void sets_classes(const SetsArgs &A, SetsShared<BLOCKS> &S)
 {
@@ -738,8 +749,7 @@ __device__ __forceinline__ void sets_classes(const SetsArgs &A, SetsShared<BLOCK
         const int c = A.gap_cls[A.lb_begin[tid]];
         if (tid == 0 || A.gap_cls[A.lb_begin[tid - 1]] != c) S.first[c] = tid;
     }
-    for (int i = tid; i < kSetsSlots + 2; i += kSetsThreads) sets_clear(S.jobs, i);
-    if (tid < kSetsMostRounds + 11) S.idle[tid] = uint16_t(kSetsIdle);
+    sets_empty(S);
     if (tid < kMaxClasses) S.low[tid] = 0;
     __syncthreads();
 }
@@ -875,6 +885,10 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_begin(SetsArgs A)
 {
     __shared__ SetsShared<kSetsMaxBlocks> S;
     sets_classes(A, S);
+    if (threadIdx.x <= kMaxClasses) {
+        A.classes[threadIdx.x] = S.first[threadIdx.x];
+        A.classes[kMaxClasses + 1 + threadIdx.x] = S.gaps_at[threadIdx.x];
+    }
     if (threadIdx.x < kMaxClasses) A.low[threadIdx.x] = 0;
     if (threadIdx.x == 0) { A.out[kSoloDone] = kSetsRunning; A.out[kSetsState] = kSetsLeastFirst << 8; }
     if (A.build)
@@ -884,23 +898,32 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_begin(SetsArgs A)
 __global__ __launch_bounds__(kSetsFormThreads) void k_sets_form(SetsArgs A)
 {
     __shared__ uint4 s_held[kHeldMaxWords / 4];
-    if (A.out[kSoloDone] != kSetsRunning) return;
+    int running = A.out[kSoloDone], least = A.out[kSetsState] >> 8;
     const uint4 *held = reinterpret_cast<const uint4 *>(A.held);
     for (int i = threadIdx.x; i < A.held_words / 4; i += kSetsFormThreads) s_held[i] = held[i];
+    asm volatile("" : "+v"(running), "+v"(least));
     __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(running) != kSetsRunning) return;
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int u = blockIdx.x * (kSetsFormThreads / kWave) + wave;
-    if (u < A.n_lb) sets_form<true>(A, u, lane, A.out[kSetsState] >> 8, reinterpret_cast<const uint32_t *>(s_held));
+    if (u < A.n_lb) sets_form<true>(A, u, lane, __builtin_amdgcn_readfirstlane(least), reinterpret_cast<const uint32_t *>(s_held));
 }
 
 __global__ __launch_bounds__(kSetsThreads) void k_sets_play(SetsArgs A)
 {
     __shared__ SetsShared<kSetsMaxBlocks> S;
-    if (A.out[kSoloDone] != kSetsRunning) return;
-    const int done = A.out[kSoloRounds];
-    sets_classes(A, S);
-    if (threadIdx.x < kMaxClasses) S.low[threadIdx.x] = A.low[threadIdx.x];
-    int played = 0, least = A.out[kSetsState] >> 8, strain = A.out[kSetsState] & 255;
+    // one trip to memory for all that is known from the launch before
+    const int tid = threadIdx.x, c = min(tid, kMaxClasses);
+    int running = A.out[kSoloDone], done = A.out[kSoloRounds], state = A.out[kSetsState];
+    int first = A.classes[c], gaps_at = A.classes[kMaxClasses + 1 + c], low = A.low[min(c, kMaxClasses - 1)];
+    asm volatile("" : "+v"(running), "+v"(done), "+v"(state), "+v"(first), "+v"(gaps_at), "+v"(low));
+    if (__builtin_amdgcn_readfirstlane(running) != kSetsRunning) return;
+    done = __builtin_amdgcn_readfirstlane(done);
+    if (tid <= kMaxClasses) { S.first[tid] = first; S.gaps_at[tid] = gaps_at; }
+    if (tid < kMaxClasses) S.low[tid] = low;
+    sets_empty(S);
+    __syncthreads();
+    int played = 0, least = __builtin_amdgcn_readfirstlane(state) >> 8, strain = __builtin_amdgcn_readfirstlane(state) & 255;
     if (sets_batch<true>(A, S, done, least, A.held, played)) return;
     const bool go_on = sets_go_on(played, kSetsLeastMany, least, strain);
     if (threadIdx.x < kMaxClasses) A.low[threadIdx.x] = S.low[threadIdx.x];

@@ -591,12 +591,13 @@ int resolve_with_lists(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
             // (the states' space behind those of the list blocks that there are)
             args.block = reinterpret_cast<SetsBlock *>(state + size_t(n_subs) * kWave);
             args.low = reinterpret_cast<int32_t *>(args.block + n_subs);
+            args.classes = args.low + kMaxClasses;
             // (the records are sorted: the buffers of the entries are free)
             args.list_jobs = list_jobs;
             args.list = reinterpret_cast<uint32_t *>(ekey[0]);
             args.list_from = reinterpret_cast<uint16_t *>(args.list + size_t(n_subs) * kSetsPieces * list_jobs);
             static_assert((kListSplits * kMaxClasses + kMaxClasses - kSetsMaxBlocks) * kWave * sizeof(int4) >
-                          size_t(kSetsMaxBlocks) * sizeof(SetsBlock) + kMaxClasses * 4, "room for them");
+                          size_t(kSetsMaxBlocks) * sizeof(SetsBlock) + (3 * kMaxClasses + 2) * 4, "room for them");
             args.out = counters + 8;
             args.cap = int(cap);
             args.n_gaps = G;
