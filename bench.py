@@ -31,13 +31,13 @@ def algorithmic_fit_bytes(wl, n_atoms_total):
 def secondary_rates(wl, n_atoms_total, call_ms, rounds):
     """Algorithmic bytes and rates of the other calls (whole calls, HIP events): prepare moves 9 B in
     and 12 B out per segment after the progress point plus 16 B per atom and 20 B per job; select
-    reads the 4-byte cut of every pair and writes 16 B per gap; the rounds of resolve are bound by
-    latency, so they are reported per round."""
+    reads the 8 B of every atom (below 2^24 pairs the 4-byte cut of every pair) and writes 16 B per gap;
+    the rounds of resolve are bound by latency, so they are reported per round."""
     import numpy as np
     G, J = wl.n_gaps, wl.n_jobs
     remaining = int((np.diff(wl.seg_off) - wl.progress).clip(min=0).sum())
     out = {}
-    for name, nbytes in (("prepare", 21 * remaining + 16 * n_atoms_total + 20 * J), ("select", 4 * G * J + 16 * G)):
+    for name, nbytes in (("prepare", 21 * remaining + 16 * n_atoms_total + 20 * J), ("select", (8 * n_atoms_total if G * J >= 1 << 24 else 4 * G * J) + 16 * G)):
         gbs = nbytes / (call_ms[name] * 1e-3) / 1e9
         out[name] = {"algorithmic_bytes": nbytes, "achieved_GBs": gbs, "frac": gbs / HBM_PEAK_GBS,
                      "evals_per_s": G * J / (call_ms[name] * 1e-3)}
