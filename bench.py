@@ -52,9 +52,9 @@ def secondary_rates(wl, n_atoms_total, call_ms, rounds):
 # sources are hashed, and a different hash means the counters are stale.
 FIT_TRAFFIC = {
     "workload": ("stress", 0),
-    "sources_sha256": "c39734715f137a80993a3471c0a9b79fe46bf46006a5592eefbe7e60e04683be",
-    "fetch_kib": 51540.5, "fetch_scale": 2.0,
-    "write_kib": 8391954.4, "write_scale": 1.0,
+    "sources_sha256": "b18cf3d33ca5c7f2a533dfb635df86daab7adb5eb26cf07376b463890e97b159",
+    "fetch_kib": 51539.7, "fetch_scale": 2.0,
+    "write_kib": 8392309.6, "write_scale": 1.0,
 }
 
 
