@@ -133,7 +133,7 @@ PolicyDev to_dev(const sja_params *p)
 // Blocks of a launch that returns at once if the plan, which only the device knows, rules its form out: many empty
 // ones take longer (131072 of k_select_pass 25 us).  As many as the chip holds at once.
 constexpr unsigned kSparseGrid = 2048;
-constexpr int64_t kSelectByAtoms = int64_t(1) << 24, kFloorLeast = int64_t(11) << 15;
+constexpr int64_t kSelectByAtoms = int64_t(1) << 24, kFloorLeast = int64_t(1) << 27, kFloorLeastOfJobs = 6 << 10;
 
 // Enqueues the pass over the cut matrix, which leaves partial bests per job tile.  The
 // per-prefix keys live in the space the list building of sja_resolve uses for
@@ -948,11 +948,9 @@ bool select_by_atoms(int64_t n_gaps, int64_t n_jobs, bool table_of_F) { return n
 // the heavy to the light profiles), fit -> select of 20000 gaps x 8192 jobs (327000 jobs and chunks) 194 to 82 and 170 to
 // 84, a select 154 to 45 and 102 to 54; 3000 x 65536 (393000) 175 to 112 and 170 to 76, a select 120 to 64 and 140 to 55;
 // 8192 x 32768 (524000) 293 to 104 and 149 to 81; 32768 x 65536 (4.2 million) 704 to 202 and 163 to 102.
-bool by_floor(int64_t n_gaps, int64_t n_jobs)
-{
-    const int64_t len = fit_chunk_len(n_gaps, n_jobs);
-    return (n_gaps + len - 1) / len * n_jobs > kFloorLeast;
-}
+// The line lies at pairs, and at the jobs: few of them have shorter chunks and stay in the caches.  24888 x 1936 78 to 111,
+// 32000 x 3500 98 to 110, 32000 x 5000 147 to 120 and 86 to 93; 20000 x 7000 172 to 110 and 83 to 84, 8192 x 17000 203 to 104.
+bool by_floor(int64_t n_gaps, int64_t n_jobs) { return n_gaps * n_jobs > kFloorLeast && n_jobs >= kFloorLeastOfJobs; }
 
 // k_range_select, along the start tables: partials of as many tiles of jobs as returned.
 int launch_ranges(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params, const int32_t *wait,

@@ -72,3 +72,27 @@ def test_masks(engine, oracle, held_share, on_share):
     rng = np.random.default_rng(4)
     held = np.where(rng.random(wl.n_jobs) < held_share, 0, -1).astype(np.int32)
     check(engine, oracle, wl, (1, 3), held, (rng.random(wl.n_gaps) < on_share).astype(np.uint8))
+
+
+# batches large enough for the floor under the keys (k_floor.h), on either side of its line, some gaps of each against the
+# oracle: a gap's best reply does not depend on the other gaps
+@pytest.mark.parametrize("name,gaps,jobs,caps", [("stress", 2100, 65600, 0), ("large", 22000, 6144, 0), ("large", 22000, 6143, 0),
+                                                 ("medium", 8300, 16400, 1), ("medium", 8300, 16400, 64), ("medium", 8300, 16400, 65)])
+def test_large(engine, oracle, name, gaps, jobs, caps):
+    import paper_2509_19086_amd as P
+    wl = make_workload(name, 7, n_gaps=gaps, n_jobs=jobs)
+    if caps:
+        wl.C = np.linspace(2000, 90000, caps).astype(np.int32)[np.arange(gaps) % caps]
+    t = P.DeviceTick(engine, wl)
+    t.prepare()
+    rows = np.unique(np.linspace(0, gaps - 1, 67).astype(np.int64))
+    pd, pp, _ = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
+    cut, _ = oracle.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W[rows], wl.C[rows], False)
+    for policy in (0, 3):
+        args = (policy, wl.wait_scale, wl.sla_weight, wl.class0_override, wl.max_rounds)
+        want = oracle.select(cut, wl.seg_off, pd, pp, oracle.Params.make(*args), wl.wait, wl.sla_class)
+        par = P.Params.make(*args)
+        for call in (lambda: t.fit_select(par), lambda: (t.fit(), t.select(par))):
+            call()
+            for got, x in zip((t.cand_job, t.cand_cut, t.cand_score), want):
+                np.testing.assert_array_equal(got.cpu().numpy()[rows], x)
