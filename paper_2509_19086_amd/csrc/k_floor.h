@@ -96,7 +96,8 @@ struct FloorArgs {
     int32_t *reach;                             // [n_jobs] atoms that some class can reach, may be null
 };
 
-constexpr int kPeakBits = 3, kPeakBuckets = 256;        // (the last one that there can be is 239)
+constexpr int kPeakBits = 3, kPeakBuckets = 256, kPeakLast = ((31 - kPeakBits) << kPeakBits) + (1 << kPeakBits) - 1;
+static_assert(kPeakLast < kPeakBuckets, "the bucket of 2^31 - 1");
 struct FloorClasses {
     int cap[kMaxClasses + 1], longest[kMaxClasses + 1];     // capacity; the largest window of this class and those of larger capacities
     uint8_t below[kPeakBuckets];                            // classes whose capacity is below a bucket of peaks
@@ -121,7 +122,7 @@ __device__ __forceinline__ FloorBuckets floor_classes(const FloorArgs &A, FloorC
     __syncthreads();
     if (tid < kPeakBuckets) {            // (blocks have as many threads)
         int c = 0;
-        const int peak = tid <= ((31 - kPeakBits) << kPeakBits) ? bucket_begin(tid, kPeakBits) : INT32_MAX;
+        const int peak = tid <= kPeakLast ? bucket_begin(tid, kPeakBits) : INT32_MAX;
         while (c < n_classes && S.cap[c] < peak) ++c;
         S.below[tid] = uint8_t(c);
     }
