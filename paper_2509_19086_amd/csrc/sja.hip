@@ -130,16 +130,16 @@ PolicyDev to_dev(const sja_params *p)
     return d;
 }
 
-// Blocks of a launch that returns at once if the plan, which only the device knows, rules its form out: many empty
-// ones take longer (131072 of k_select_pass 25 us).  As many as the chip holds at once.
-constexpr unsigned kSparseGrid = 2048;
 constexpr int64_t kSelectByAtoms = int64_t(1) << 24, kFloorLeast = int64_t(1) << 27, kFloorLeastOfJobs = 6 << 10;
 
 // Enqueues the pass over the cut matrix, which leaves partial bests per job tile.  The
 // per-prefix keys live in the space the list building of sja_resolve uses for
 // its atom keys (the two never run at the same time); `keys_ready` says that an
 // earlier call with the same policy inputs left them there and nothing has
-// written that space since.  With unless_tabled (the plan) the kernels do nothing where that has class tables.
+// written that space since.  With unless_tabled (the plan) the kernels do nothing where that has class tables, and take 3 us
+// for every 16384 blocks of that; fewer blocks with several tiles each made the batches that they do serve slower (8192 gaps
+// of 65 capacities x 32768 jobs 528 us a select with a block to a tile, 590 with 2048 blocks and 536 with 16384; the loop
+// takes registers).
 int launch_matrix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params, const int32_t *wait,
                        const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active, const int32_t *unless_tabled,
                        bool keys_ready)
@@ -149,7 +149,7 @@ int launch_matrix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
     if (job_tiles > 0 && !keys_ready) {
         const int per_wave = keys_jobs_per_wave(J, ctx->n_segments);
         const unsigned key_blocks = unsigned((J + 4 * per_wave - 1) / (4 * per_wave));
-        hipLaunchKernelGGL(k_select_keys, dim3(unless_tabled && key_blocks > kSparseGrid ? kSparseGrid : key_blocks), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
+        hipLaunchKernelGGL(k_select_keys, dim3(key_blocks), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
                            ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class,
                            ctx->pre_dur, ctx->pre_peak, pre_area_of(ctx, L), keys_dense(ctx->n_segments, ctx->hyst_used_n_caps > 0), per_wave, unless_tabled, seg_key);
         SJA_HIP(hipGetLastError(), "k_select_keys launch");
@@ -160,7 +160,7 @@ int launch_matrix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         const unsigned grid = unsigned(tiles8) * unsigned(n_chunks);
         const bool mixed = params->policy == SJA_POLICY_MIXED;
         auto kern = mixed ? k_select_pass<true> : k_select_pass<false>;
-        hipLaunchKernelGGL(kern, dim3(unless_tabled && grid > kSparseGrid ? kSparseGrid : grid), dim3(kSelBlock), 0, st, J, G, n_chunks, grid,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kSelBlock), 0, st, J, G, n_chunks,
                            to_dev(params), ctx->seg_off, seg_key, ctx->cut,
                            ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active, unless_tabled,
                            ws_ptr<SelPartial>(ctx, L.sel_part));
@@ -991,6 +991,8 @@ int launch_range_reduce(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n
 // gap_active does not switch off.  No cut matrix is read or written.  A batch has class tables or not, and either
 // k_range_select or the k_floor_ kernels serve it, or k_fit_select; which, only the device knows, so both are launched and one
 // returns at once, unless the caller has seen the plan (2500 gaps of 65 capacities x 1200 jobs: 6 us of a round of 290).
+// k_fit_select has a block to a tile all the same: 32768 that return at once take 7 us, but 2048 blocks with a fixed share of
+// the tiles each took 672 us where this takes 492 (32000 gaps of 65 capacities x 4500 jobs).
 // starts: the start tables are still to be made, where they are needed.
 enum class Tabled { Unknown, No, Yes };
 int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params,
@@ -1042,8 +1044,7 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
             if (rc != SJA_OK) return rc;
         }
         if (!rise || tabled != Tabled::Yes) {
-            const bool sparse = rise && tabled == Tabled::Unknown && grid > kSparseGrid;
-            hipLaunchKernelGGL(kern, dim3(sparse ? kSparseGrid : grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, grid, int(!rise), to_dev(params),
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedBlock), 0, st, J, n_gaps, chunk_bound, int(!rise), to_dev(params),
                                ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area, ws_ptr<int32_t>(ctx, L.n_atoms),
                                ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin),
                                ws_ptr<int32_t>(ctx, L.chunk_end), ws_ptr<int32_t>(ctx, L.chunk_class),

@@ -764,39 +764,37 @@ __global__ __launch_bounds__(256) void k_select_keys(
     unsigned long long *__restrict__ seg_key)
 {
     if (unless_tabled && unless_tabled[kPlanTabled]) return;
-    const int lane = lane_id(), waves = blockDim.x / kWave;
-    for (int j0 = (blockIdx.x * waves + threadIdx.x / kWave) * per_wave; j0 < n_jobs; j0 += gridDim.x * waves * per_wave) {
-        // what says which form a job takes, a lane each (no cut lies beyond a job's end; the first atom reports its own
-        // boundary under the hysteresis rule, too)
-        const int mine = min(j0 + lane, n_jobs - 1);
-        const bool there = lane < per_wave && j0 + lane < n_jobs;
-        const int64_t base_of = seg_off[mine];
-        const int n_of = there ? n_atoms[mine] : 0, last_of = int(seg_off[mine + 1] - base_of);
-        unsigned long long mult_of, tier_of;
-        job_policy(pol, wait, sla_class, mine, mult_of, tier_of);
-        const int first_of = n_of > 0 ? atom_db[base_of].y : 0;
-        for (int q = 0; q < per_wave; ++q) {
-            const int n = lane_value(n_of, q), first = lane_value(first_of, q), last = lane_value(last_of, q);
-            if (n == 0) continue;
-            const int64_t base = int64_t(lane_value64(base_of, q));
-            const unsigned long long mult = lane_value64(mult_of, q), tier = lane_value64(tier_of, q);
-            auto key = [&](unsigned long long F) { return ((tier << 62) | times_mult(F, mult)) + 1ull; };
-            if (int64_t(n) * 64 >= int64_t(last - first + 1) * dense) {
-                for (int k = first - 1 + lane; k < last; k += kWave)
-                    seg_key[base + k] = key(pre_area ? (unsigned long long)pre_area[base + k] : rect_of(pre_dur[base + k], pre_peak[base + k]));
-                continue;
+    const int lane = lane_id(), j0 = (blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave)) * per_wave;
+    // what says which form a job takes, a lane each (no cut lies beyond a job's end; the first atom reports its own
+    // boundary under the hysteresis rule, too)
+    const int mine = min(j0 + lane, n_jobs - 1);
+    const bool there = lane < per_wave && j0 + lane < n_jobs;
+    const int64_t base_of = seg_off[mine];
+    const int n_of = there ? n_atoms[mine] : 0, last_of = int(seg_off[mine + 1] - base_of);
+    unsigned long long mult_of, tier_of;
+    job_policy(pol, wait, sla_class, mine, mult_of, tier_of);
+    const int first_of = n_of > 0 ? atom_db[base_of].y : 0;
+    for (int q = 0; q < per_wave; ++q) {
+        const int n = lane_value(n_of, q), first = lane_value(first_of, q), last = lane_value(last_of, q);
+        if (n == 0) continue;
+        const int64_t base = int64_t(lane_value64(base_of, q));
+        const unsigned long long mult = lane_value64(mult_of, q), tier = lane_value64(tier_of, q);
+        auto key = [&](unsigned long long F) { return ((tier << 62) | times_mult(F, mult)) + 1ull; };
+        if (int64_t(n) * 64 >= int64_t(last - first + 1) * dense) {
+            for (int k = first - 1 + lane; k < last; k += kWave)
+                seg_key[base + k] = key(pre_area ? (unsigned long long)pre_area[base + k] : rect_of(pre_dur[base + k], pre_peak[base + k]));
+            continue;
+        }
+        for (int a = lane; a < n; a += kWave) {
+            const int boundary = atom_db[base + a].y;
+            unsigned long long F;
+            if (atom_area) {
+                F = (unsigned long long)atom_area[base + a];
+            } else {
+                const int2 v = atom_dp[base + a];
+                F = rect_of(v.x, v.y);
             }
-            for (int a = lane; a < n; a += kWave) {
-                const int boundary = atom_db[base + a].y;
-                unsigned long long F;
-                if (atom_area) {
-                    F = (unsigned long long)atom_area[base + a];
-                } else {
-                    const int2 v = atom_dp[base + a];
-                    F = rect_of(v.x, v.y);
-                }
-                seg_key[base + boundary - 1] = key(F);
-            }
+            seg_key[base + boundary - 1] = key(F);
         }
     }
 }
@@ -806,7 +804,7 @@ constexpr int kSelBatch = 8;
 
 template <bool MIXED>
 __global__ __launch_bounds__(kSelBlock) void k_select_pass(
-    int n_jobs, int n_gaps, int n_chunks, unsigned n_tiles, PolicyDev pol, const int64_t *__restrict__ seg_off,
+    int n_jobs, int n_gaps, int n_chunks, PolicyDev pol, const int64_t *__restrict__ seg_off,
     const unsigned long long *__restrict__ seg_key, const int32_t *__restrict__ cut, const int32_t *__restrict__ gap_order,
     const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
     const int32_t *__restrict__ job_held, const uint8_t *__restrict__ gap_active, const int32_t *__restrict__ unless_tabled,
@@ -820,140 +818,136 @@ __global__ __launch_bounds__(kSelBlock) void k_select_pass(
     __shared__ int s_job[WAVES][kSelGapChunk];
 
     if (unless_tabled && unless_tabled[kPlanTabled]) return;
-    // (a block takes one tile after the other where the launch is smaller than their number)
-    for (unsigned tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int xcd = tile & 7;
-        const int k = tile >> 3;
-        const int job_tile = (k / n_chunks) * 8 + xcd;
-        const int chunk = k % n_chunks;
-        if (job_tile * kSelBlock >= n_jobs) continue;
-        const int j = job_tile * kSelBlock + threadIdx.x;
-        const int wave = threadIdx.x / kWave;
-        const int lane = lane_id();
-        const int wave_job0 = job_tile * kSelBlock + wave * kWave;
+    const int xcd = blockIdx.x & 7;
+    const int k = blockIdx.x >> 3;
+    const int job_tile = (k / n_chunks) * 8 + xcd;
+    const int chunk = k % n_chunks;
+    if (job_tile * kSelBlock >= n_jobs) return;
+    const int j = job_tile * kSelBlock + threadIdx.x;
+    const int wave = threadIdx.x / kWave;
+    const int lane = lane_id();
+    const int wave_job0 = job_tile * kSelBlock + wave * kWave;
 
-        bool usable = j < n_jobs;
-        int64_t base = 0;
-        unsigned long long mult = 1, tier = 0;
-        if (usable) {
-            if (job_held && job_held[j] >= 0) usable = false;
-            base = seg_off[j];
-            if (MIXED) job_policy(pol, wait, sla_class, j, mult, tier);    // the multiplier, for ties only
-        }
-        s_mult[wave][lane] = mult;
+    bool usable = j < n_jobs;
+    int64_t base = 0;
+    unsigned long long mult = 1, tier = 0;
+    if (usable) {
+        if (job_held && job_held[j] >= 0) usable = false;
+        base = seg_off[j];
+        if (MIXED) job_policy(pol, wait, sla_class, j, mult, tier);    // the multiplier, for ties only
+    }
+    s_mult[wave][lane] = mult;
 
-        const int s_begin = chunk * kSelGapChunk;
-        const int s_end = min(n_gaps, s_begin + kSelGapChunk);
-        int last_cut = -1;
-        unsigned long long hi = 0;
-        // secondary score of a key (MIXED: F = score / multiplier), only needed to break ties
-        auto second = [&](unsigned long long key, int src) -> unsigned long long {
-            return MIXED ? ((key - 1ull) & ((1ull << 62) - 1ull)) / s_mult[wave][src] : 0ull;
-        };
-        // the chunk's gaps, a lane each, and which of them are on: a flag fetched on the way to each cut (a byte per
-        // step, waited for behind all cuts in flight) made a masked pass 490 us instead of 285 (8192 x 32768)
-        static_assert(kSelGapChunk == kWave, "a lane per position");
-        const int my_gap = s_begin + lane < s_end ? gap_order[s_begin + lane] : 0;
-        const unsigned long long on = __ballot(s_begin + lane < s_end && (!gap_active || gap_active[my_gap]));
-        // the cuts of one batch of steps (cut rows are read coalesced)
-        auto load_cuts = [&](int s0, int (&out)[kSelBatch]) {
+    const int s_begin = chunk * kSelGapChunk;
+    const int s_end = min(n_gaps, s_begin + kSelGapChunk);
+    int last_cut = -1;
+    unsigned long long hi = 0;
+    // secondary score of a key (MIXED: F = score / multiplier), only needed to break ties
+    auto second = [&](unsigned long long key, int src) -> unsigned long long {
+        return MIXED ? ((key - 1ull) & ((1ull << 62) - 1ull)) / s_mult[wave][src] : 0ull;
+    };
+    // the chunk's gaps, a lane each, and which of them are on: a flag fetched on the way to each cut (a byte per
+    // step, waited for behind all cuts in flight) made a masked pass 490 us instead of 285 (8192 x 32768)
+    static_assert(kSelGapChunk == kWave, "a lane per position");
+    const int my_gap = s_begin + lane < s_end ? gap_order[s_begin + lane] : 0;
+    const unsigned long long on = __ballot(s_begin + lane < s_end && (!gap_active || gap_active[my_gap]));
+    // the cuts of one batch of steps (cut rows are read coalesced)
+    auto load_cuts = [&](int s0, int (&out)[kSelBatch]) {
 #pragma unroll
-            for (int t = 0; t < kSelBatch; ++t) {
-                out[t] = -1;
-                const int at = s0 - s_begin + t;
-                if (((on >> at) & 1ull) && usable) out[t] = cut[int64_t(lane_value(my_gap, at)) * n_jobs + j];
-            }
-        };
-        int cv_next[kSelBatch];
-        load_cuts(s_begin, cv_next);
-        for (int s0 = s_begin; s0 < s_end; s0 += kSelBatch) {
-            const int n_step = min(kSelBatch, s_end - s0);
-            // phase 1: every lane's key for each step of the batch
-            int cv[kSelBatch];
-#pragma unroll
-            for (int t = 0; t < kSelBatch; ++t) cv[t] = cv_next[t];
-            // a job's cut rarely changes from one sorted position to the next: only the changes
-            // gather the prefix's key, all of a batch's gathers in flight together
-            unsigned long long kv[kSelBatch];
-            bool fresh[kSelBatch];
-            int prev = last_cut;
-#pragma unroll
-            for (int t = 0; t < kSelBatch; ++t) {
-                const int c = cv[t];
-                fresh[t] = c >= 0 && c != prev;
-                if (fresh[t]) kv[t] = seg_key[base + c - 1];
-                prev = c >= 0 ? c : prev;
-            }
-            last_cut = prev;
-            // the next batch's cuts travel together with this batch's gathers
-            if (s0 + kSelBatch < s_end) load_cuts(s0 + kSelBatch, cv_next);
-#pragma unroll
-            for (int t = 0; t < kSelBatch; ++t) {
-                if (fresh[t]) hi = kv[t];
-                s_key[wave][t][lane] = cv[t] >= 0 ? hi : 0ull;
-            }
-            // the keys just written are read by other lanes of this wave: order the two
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // phase 2: lane l reduces step (l % 16) over lanes [16 * (l / 16), +16), then the four
-            // quarter results of a step are combined across lanes l, l+16, l+32, l+48
-            const int t = lane & (kSelBatch - 1), q = lane / kSelBatch;
-            unsigned long long bh = 0;
-            int bsrc = kWave;
-#pragma unroll
-            for (int i = 0; i < kSelBatch; ++i) {
-                const int src = q * kSelBatch + i;
-                const unsigned long long oh = s_key[wave][t][src];
-                bool better = oh > bh;
-                if (MIXED && oh == bh && oh != 0) better = second(oh, src) > second(bh, bsrc);
-                if (better) { bh = oh; bsrc = src; }     // equal keys keep the lower lane = lower job id
-            }
-#pragma unroll
-            for (int d = kSelBatch; d < kWave; d <<= 1) {
-                const unsigned long long oh = __shfl_xor(bh, d, kWave);
-                const int osrc = __shfl_xor(bsrc, d, kWave);
-                bool better = oh > bh || (oh == bh && osrc < bsrc);
-                if (MIXED && oh == bh && oh != 0) {
-                    const unsigned long long fo = second(oh, osrc), fb = second(bh, bsrc);
-                    better = fo > fb || (fo == fb && osrc < bsrc);
-                }
-                if (better) { bh = oh; bsrc = osrc; }
-            }
-            // the winner's secondary score is a 64-bit division: it is left to the end, where it is
-            // needed once per position (and per tie between waves), not once per wave and batch
-            if (lane < n_step) {
-                const int slot = s0 - s_begin + lane;
-                s_hi[wave][slot] = bh; s_job[wave][slot] = bh ? wave_job0 + bsrc : INT32_MAX;
-            }
+        for (int t = 0; t < kSelBatch; ++t) {
+            out[t] = -1;
+            const int at = s0 - s_begin + t;
+            if (((on >> at) & 1ull) && usable) out[t] = cut[int64_t(lane_value(my_gap, at)) * n_jobs + j];
         }
-        __syncthreads();
-        // secondary score of wave w's winner (its multiplier sits in that wave's row of s_mult)
-        auto second_of = [&](unsigned long long key, int w, int job) -> unsigned long long {
-            return MIXED ? ((key - 1ull) & ((1ull << 62) - 1ull)) / s_mult[w][job - (job_tile * kSelBlock + w * kWave)] : 0ull;
-        };
-        for (int slot = threadIdx.x; slot < s_end - s_begin; slot += kSelBlock) {
-            unsigned long long bh = s_hi[0][slot];
-            int bj = bh ? s_job[0][slot] : INT32_MAX, bw = 0;
+    };
+    int cv_next[kSelBatch];
+    load_cuts(s_begin, cv_next);
+    for (int s0 = s_begin; s0 < s_end; s0 += kSelBatch) {
+        const int n_step = min(kSelBatch, s_end - s0);
+        // phase 1: every lane's key for each step of the batch
+        int cv[kSelBatch];
 #pragma unroll
-            for (int w = 1; w < WAVES; ++w) {
-                const unsigned long long oh = s_hi[w][slot];
-                const int oj = oh ? s_job[w][slot] : INT32_MAX;
-                bool better = oh > bh;
-                // equal keys: the larger secondary score, then the lower job, which is the earlier wave's
-                if (MIXED && oh == bh && oh != 0) better = second_of(oh, w, oj) > second_of(bh, bw, bj);
-                if (better) { bh = oh; bj = oj; bw = w; }
-            }
-            const unsigned long long bl = (MIXED && bh) ? second_of(bh, bw, bj) : 0ull;
-            const int g = gap_order[s_begin + slot];
-            // the winner's cut, fetched here for all of the block's positions at once (inside the
-            // stepping loop it would be one more memory trip per batch)
-            const int bc = bh ? cut[int64_t(g) * n_jobs + bj] : -1;
-            SelPartial out;
-            out.hi = bh; out.lo = bl; out.job = bh ? bj : -1; out.cut = bh ? bc : -1; out.pad = 0;
-            part[int64_t(job_tile) * n_gaps + g] = out;
+        for (int t = 0; t < kSelBatch; ++t) cv[t] = cv_next[t];
+        // a job's cut rarely changes from one sorted position to the next: only the changes
+        // gather the prefix's key, all of a batch's gathers in flight together
+        unsigned long long kv[kSelBatch];
+        bool fresh[kSelBatch];
+        int prev = last_cut;
+#pragma unroll
+        for (int t = 0; t < kSelBatch; ++t) {
+            const int c = cv[t];
+            fresh[t] = c >= 0 && c != prev;
+            if (fresh[t]) kv[t] = seg_key[base + c - 1];
+            prev = c >= 0 ? c : prev;
         }
-        __syncthreads();
+        last_cut = prev;
+        // the next batch's cuts travel together with this batch's gathers
+        if (s0 + kSelBatch < s_end) load_cuts(s0 + kSelBatch, cv_next);
+#pragma unroll
+        for (int t = 0; t < kSelBatch; ++t) {
+            if (fresh[t]) hi = kv[t];
+            s_key[wave][t][lane] = cv[t] >= 0 ? hi : 0ull;
+        }
+        // the keys just written are read by other lanes of this wave: order the two
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // phase 2: lane l reduces step (l % 16) over lanes [16 * (l / 16), +16), then the four
+        // quarter results of a step are combined across lanes l, l+16, l+32, l+48
+        const int t = lane & (kSelBatch - 1), q = lane / kSelBatch;
+        unsigned long long bh = 0;
+        int bsrc = kWave;
+#pragma unroll
+        for (int i = 0; i < kSelBatch; ++i) {
+            const int src = q * kSelBatch + i;
+            const unsigned long long oh = s_key[wave][t][src];
+            bool better = oh > bh;
+            if (MIXED && oh == bh && oh != 0) better = second(oh, src) > second(bh, bsrc);
+            if (better) { bh = oh; bsrc = src; }     // equal keys keep the lower lane = lower job id
+        }
+#pragma unroll
+        for (int d = kSelBatch; d < kWave; d <<= 1) {
+            const unsigned long long oh = __shfl_xor(bh, d, kWave);
+            const int osrc = __shfl_xor(bsrc, d, kWave);
+            bool better = oh > bh || (oh == bh && osrc < bsrc);
+            if (MIXED && oh == bh && oh != 0) {
+                const unsigned long long fo = second(oh, osrc), fb = second(bh, bsrc);
+                better = fo > fb || (fo == fb && osrc < bsrc);
+            }
+            if (better) { bh = oh; bsrc = osrc; }
+        }
+        // the winner's secondary score is a 64-bit division: it is left to the end, where it is
+        // needed once per position (and per tie between waves), not once per wave and batch
+        if (lane < n_step) {
+            const int slot = s0 - s_begin + lane;
+            s_hi[wave][slot] = bh; s_job[wave][slot] = bh ? wave_job0 + bsrc : INT32_MAX;
+        }
+    }
+    __syncthreads();
+    // secondary score of wave w's winner (its multiplier sits in that wave's row of s_mult)
+    auto second_of = [&](unsigned long long key, int w, int job) -> unsigned long long {
+        return MIXED ? ((key - 1ull) & ((1ull << 62) - 1ull)) / s_mult[w][job - (job_tile * kSelBlock + w * kWave)] : 0ull;
+    };
+    for (int slot = threadIdx.x; slot < s_end - s_begin; slot += kSelBlock) {
+        unsigned long long bh = s_hi[0][slot];
+        int bj = bh ? s_job[0][slot] : INT32_MAX, bw = 0;
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            const unsigned long long oh = s_hi[w][slot];
+            const int oj = oh ? s_job[w][slot] : INT32_MAX;
+            bool better = oh > bh;
+            // equal keys: the larger secondary score, then the lower job, which is the earlier wave's
+            if (MIXED && oh == bh && oh != 0) better = second_of(oh, w, oj) > second_of(bh, bw, bj);
+            if (better) { bh = oh; bj = oj; bw = w; }
+        }
+        const unsigned long long bl = (MIXED && bh) ? second_of(bh, bw, bj) : 0ull;
+        const int g = gap_order[s_begin + slot];
+        // the winner's cut, fetched here for all of the block's positions at once (inside the
+        // stepping loop it would be one more memory trip per batch)
+        const int bc = bh ? cut[int64_t(g) * n_jobs + bj] : -1;
+        SelPartial out;
+        out.hi = bh; out.lo = bl; out.job = bh ? bj : -1; out.cut = bh ? bc : -1; out.pad = 0;
+        part[int64_t(job_tile) * n_gaps + g] = out;
     }
 }
 
