@@ -29,6 +29,7 @@ constexpr int kFloorStep = 4;               // which looks at every second or fo
                                             // give a floor, a quarter of them leaves three times as many atoms (12 of 4 thousand)
 constexpr int kFloorBuckets = 8192;         // of all classes together
 constexpr int kFloorAhead = 4;              // atoms a lane asks for together
+constexpr int kFloorThinFrom = 1024;        // atoms that a block keeps from which on it looks for equal ones among them
 constexpr int kFloorMergeThreads = 256, kFloorMergeEntries = 32;
 
 inline int floor_blocks_of(int n_jobs, int most)
@@ -231,7 +232,9 @@ struct FloorAtoms {
                 on(j, Atom{now.v[q], x.base + a, x.tier, x.mult, a == 0}, area, c[q], floor_digest(uint32_t(x.tier), F * float(x.mult)));
             }
             // (behind atoms that nothing reaches there are no others)
-            if (more && ((__ballot(any) >> first_lane) & ((1ull << kFloorLanes) - 1)) != 0) {
+            const unsigned long long met = __ballot(any);
+            const uint32_t half = first_lane & 32 ? uint32_t(met >> 32) : uint32_t(met);
+            if (more && (half >> (first_lane & 31) & ((1u << kFloorLanes) - 1u)) != 0) {
                 a0 += TRIP;
                 now = behind;
                 continue;
@@ -311,37 +314,154 @@ __global__ __launch_bounds__(kFloorMergeThreads) void k_floor_merge(FloorArgs A,
     A.floor[i] = top;
 }
 
-// Calls on(position, key, place) for the first position that each atom of list b reaches in every class that admits
-// it, unless it is below the running maximum there already.
+// Calls on(position, key, place, largest key there so far) for the first position that each of n atoms from `first` on reaches
+// in every class that admits it, unless it is below the running maximum there already.  Several atoms side by side: each
+// is a chain of trips to memory.
+constexpr int kEventsQ = 4;
 template <typename On>
 __device__ __forceinline__ void floor_events(const FloorArgs &A, const FloorClasses &S, const FloorBuckets &B, const uint32_t *running, int64_t first,
                                              int n, int threads, On on)
 {
+    constexpr int Q = kEventsQ;
     const int n_classes = A.plan[kPlanClasses];
     int lanes = 1;                              // to an atom: one to a class
     while (lanes < n_classes) lanes <<= 1;
     const int c = threadIdx.x & (lanes - 1), step = threads / lanes;
     if (c >= n_classes) return;
     const int cap = S.cap[c], begin = A.class_begin[c], end = A.class_begin[c + 1];
-    for (int i = threadIdx.x / lanes; i < n; i += step) {
-        const ulonglong2 x = A.near[first + i];
-        const int d = int(x.y >> 32);
-        if (int(uint32_t(x.y)) > cap) continue;
-        int lo = begin, hi = end;
-        if (B.per_class) {
-            const int k = bucket_of(d, B.bits);
-            if (k >= B.per_class - 1) continue;         // (longer than every window)
-            const unsigned long long score = (x.x - 1ull) & ((1ull << 62) - 1ull);
-            if (floor_digest(uint32_t((x.x - 1ull) >> 62), float(score)) + kDigestSlack < running[c * B.per_class + k]) continue;
-            lo = A.bucket_pos[c * B.per_class + k];
-            hi = A.bucket_pos[c * B.per_class + k + 1];
+    for (int i = threadIdx.x / lanes; i < n; i += Q * step) {
+        ulonglong2 x[Q];
+        int lo[Q], hi[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) x[q] = A.near[first + min(i + q * step, n - 1)];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int d = int(x[q].y >> 32);
+            bool in = i + q * step < n && int(uint32_t(x[q].y)) <= cap;
+            lo[q] = begin;
+            hi[q] = end;
+            if (B.per_class) {
+                const int k = bucket_of(d, B.bits), at = c * B.per_class + min(k, B.per_class - 2);
+                const unsigned long long score = (x[q].x - 1ull) & ((1ull << 62) - 1ull);
+                // (longer than every window; below the running maximum)
+                in = in && k < B.per_class - 1 && floor_digest(uint32_t((x[q].x - 1ull) >> 62), float(score)) + kDigestSlack >= running[at];
+                if (in) {
+                    lo[q] = A.bucket_pos[at];
+                    hi[q] = A.bucket_pos[at + 1];
+                }
+            }
+            if (!in) lo[q] = hi[q] = end;
         }
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (A.gap_w[mid] < d) lo = mid + 1; else hi = mid;
+        for (bool more = true; more;) {
+            int w[Q];
+            more = false;
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (lo[q] < hi[q]) w[q] = A.gap_w[(lo[q] + hi[q]) >> 1];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (lo[q] >= hi[q]) continue;
+                const int mid = (lo[q] + hi[q]) >> 1;
+                if (w[q] < int(x[q].y >> 32)) lo[q] = mid + 1; else hi[q] = mid;
+                more |= lo[q] < hi[q];
+            }
         }
-        if (lo < end) on(lo, x.x, first + i);
+        unsigned long long best[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lo[q] < end) best[q] = __hip_atomic_load(&A.best[lo[q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lo[q] < end) on(lo[q], x[q].x, first + i + q * step, best[q]);
     }
+}
+
+// Jobs of one profile and equal preferences have nothing but equal keys, and every atom that leads is there once for each of
+// them.  Of a block's atoms of one duration and peak only the one that a position can want is kept: the largest key, of equal
+// ones the largest F, of these the lowest job.  In place; returns how many are left.
+template <bool AREA>
+struct FloorSlots {
+    static constexpr int N = AREA ? 1024 : 2048, TRIES = 4;         // (with the table of floors, half of a compute unit's LDS)
+    unsigned long long at[N], key[N], second[AREA ? N : 1];         // duration and peak, 0: free
+    int job[N];
+    int n;
+
+    __device__ __forceinline__ static int slot_of(unsigned long long x, int k)
+    {
+        return int(((uint32_t(x) * 2654435761u ^ uint32_t(x >> 32)) * 2246822519u >> 16) + k) & (N - 1);
+    }
+    __device__ __forceinline__ int find(unsigned long long x) const         // -1: all of its slots are others'
+    {
+        for (int k = 0; k < TRIES; ++k)
+            if (at[slot_of(x, k)] == x) return slot_of(x, k);
+        return -1;
+    }
+};
+template <bool AREA>
+__device__ __forceinline__ int floor_thin(const FloorArgs &A, FloorSlots<AREA> &T, int64_t first, int n)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const bool by_second = AREA && A.pol.policy == SJA_POLICY_MIXED;        // (else F follows from the key, or does not matter)
+    for (int i = tid; i < FloorSlots<AREA>::N; i += kFloorThreads) {
+        T.at[i] = T.key[i] = 0;
+        if (AREA) T.second[AREA ? i : 0] = 0;
+        T.job[i] = INT32_MAX;
+    }
+    if (tid == 0) T.n = 0;
+    __syncthreads();
+#pragma unroll 1
+    for (int i = tid; i < n; i += kFloorThreads) {
+        const ulonglong2 x = A.near[first + i];
+        for (int k = 0; k < FloorSlots<AREA>::TRIES; ++k) {
+            const int to = T.slot_of(x.y, k);
+            unsigned long long was = *static_cast<volatile unsigned long long *>(&T.at[to]);
+            if (was == 0) was = atomicCAS(&T.at[to], 0ull, x.y);
+            if (was != 0 && was != x.y) continue;
+            if (x.x > *static_cast<volatile unsigned long long *>(&T.key[to])) atomicMax(&T.key[to], x.x);
+            break;
+        }
+    }
+    __syncthreads();
+    if (by_second) {
+    #pragma unroll 1
+    for (int i = tid; i < n; i += kFloorThreads) {
+            const ulonglong2 x = A.near[first + i];
+            const int to = T.find(x.y);
+            if (to >= 0 && x.x == T.key[to]) atomicMax(&T.second[AREA ? to : 0], A.near_job[first + i].x);
+        }
+        __syncthreads();
+    }
+    auto leads = [&](int to, const ulonglong2 &x, const ulonglong2 &y) { return x.x == T.key[to] && (!by_second || y.x == T.second[AREA ? to : 0]); };
+#pragma unroll 1
+    for (int i = tid; i < n; i += kFloorThreads) {
+        const ulonglong2 x = A.near[first + i], y = A.near_job[first + i];
+        const int to = T.find(x.y), job = int(y.y);
+        if (to >= 0 && leads(to, x, y) && job < *static_cast<volatile int *>(&T.job[to])) atomicMin(&T.job[to], job);
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 < n; i0 += kFloorThreads) {
+        const int i = i0 + tid;
+        ulonglong2 x{}, y{};
+        bool stays = false;
+        if (i < n) {
+            x = A.near[first + i];
+            y = A.near_job[first + i];
+            const int to = T.find(x.y);
+            stays = to < 0 || (leads(to, x, y) && int(y.y) == T.job[to]);
+        }
+        __syncthreads();            // (these have been read: what is left takes no more places than there were)
+        const unsigned long long some = __ballot(stays);
+        if (!some) continue;
+        int to = 0;
+        if (lane == 0) to = atomicAdd(&T.n, __popcll(some));
+        to = __builtin_amdgcn_readfirstlane(to) + __popcll(some & ((1ull << lane) - 1ull));
+        if (stays) {
+            A.near[first + to] = x;
+            A.near_job[first + to] = y;
+        }
+    }
+    __syncthreads();
+    return T.n;
 }
 
 template <bool AREA>
@@ -349,6 +469,7 @@ __global__ __launch_bounds__(kFloorThreads) __attribute__((amdgpu_waves_per_eu(A
 {
     __shared__ uint32_t s_table[kFloorBuckets];
     __shared__ FloorClasses S;
+    __shared__ FloorSlots<AREA> s_slots;
     __shared__ int s_n;
     if (!A.plan[kPlanTabled]) return;
     FloorAtoms<AREA> atoms;
@@ -398,9 +519,11 @@ __global__ __launch_bounds__(kFloorThreads) __attribute__((amdgpu_waves_per_eu(A
                    if ((tid & (kFloorLanes - 1)) == 0) A.reach[j] = reached;
                });
     __syncthreads();
-    if (tid == 0) A.n_near[blockIdx.x] = s_n;
-    floor_events(A, S, B, s_table, first, s_n, kFloorThreads, [&](int p, unsigned long long key, int64_t) {
-        if (key > __hip_atomic_load(&A.best[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&A.best[p], key);
+    int n = s_n;
+    if (n > kFloorThinFrom) n = floor_thin<AREA>(A, s_slots, first, n);
+    if (tid == 0) A.n_near[blockIdx.x] = n;
+    floor_events(A, S, B, s_table, first, n, kFloorThreads, [&](int p, unsigned long long key, int64_t, unsigned long long best) {
+        if (key > best) atomicMax(&A.best[p], key);
     });
 }
 
@@ -422,19 +545,21 @@ __global__ __launch_bounds__(kTiesThreads) void k_floor_ties(FloorArgs A, int ag
     const int each = (A.n_jobs + int(gridDim.x) - 1) / int(gridDim.x), j0 = int(blockIdx.x) * each;
     const int64_t first = j0 < A.n_jobs ? A.seg_off[j0] : 0;
     const FloorBuckets B = floor_classes(A, S);
-    floor_events(A, S, B, A.running, first, n, kTiesThreads, [&](int p, unsigned long long key, int64_t place) {
-        if (key != A.best[p]) return;
+    // (atomics on one word are served one after the other: most need none)
+    auto now = [](auto &x) { return __hip_atomic_load(&x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    floor_events(A, S, B, A.running, first, n, kTiesThreads, [&](int p, unsigned long long key, int64_t place, unsigned long long best) {
+        if (key != best) return;
         const ulonglong2 y = A.near_job[place];
         const int job = int(y.y);
         if (again) {
-            if (y.x == A.second[p]) atomicMin(&A.who[p], job);
+            if (y.x == A.second[p] && job < now(A.who[p])) atomicMin(&A.who[p], job);
             return;
         }
         if (MIXED) {
-            atomicMax(&A.second[p], y.x);
+            if (y.x > now(A.second[p])) atomicMax(&A.second[p], y.x);
             // (of a job only the first atom of a key is here: two jobs)
-            if (atomicExch(&A.who[p], job | kTiesMark) != INT32_MAX) *several = 1;
-        } else if (job < __hip_atomic_load(&A.who[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            if ((now(A.who[p]) != INT32_MAX || atomicExch(&A.who[p], job | kTiesMark) != INT32_MAX) && !now(*several)) atomicMax(several, 1);
+        } else if (job < now(A.who[p])) {
             atomicMin(&A.who[p], job);
         }
     });

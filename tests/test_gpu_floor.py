@@ -1,0 +1,119 @@
+"""The best job per gap by the floor under the keys (k_floor.h) at sizes that it serves, sja_fit_select and sja_select alike:
+equal keys within a block of jobs and across them, of one duration and peak and of several, more of them than a block
+has slots for, equal scores of different F, held jobs, gaps that are off, windows far apart, under every policy and score,
+some gaps of each batch against the oracle (a gap's best reply does not depend on the other gaps)."""
+import numpy as np
+import pytest
+
+from gen import make_workload
+
+pytestmark = pytest.mark.gpu
+GAPS, JOBS = 33000, 16400       # more than 2^29 pairs, blocks of 64 jobs
+
+
+@pytest.fixture(scope="module")
+def engine():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2509_19086_amd as P
+    eng = P.Engine(0)
+    yield eng
+    eng.sja_set_score(0)
+
+
+def check(engine, oracle, wl, policies, held=None, act=None, area=False, matrix=True, rows=61):
+    import torch
+    import paper_2509_19086_amd as P
+    engine.sja_set_score(int(area))
+    t = P.DeviceTick(engine, wl, want_bits=False, want_cut=matrix)
+    t.prepare()
+    rows = np.unique(np.concatenate([[int(np.argmin(wl.W)), int(np.argmax(wl.W))], np.linspace(0, len(wl.W) - 1, rows)])).astype(np.int64)
+    pd, pp, _ = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
+    pa = oracle.area(wl.seg_off, wl.dur, wl.mem, wl.progress) if area else None
+    cut, _ = oracle.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W[rows], wl.C[rows], False)
+    dev = lambda x: None if x is None else torch.from_numpy(x).cuda()
+    d_held, d_act = dev(held), dev(act)
+    pars = [(m.Params.make(p, wl.wait_scale, wl.sla_weight, wl.class0_override, 0) for m in (P, oracle)) for p in policies]
+    pars = [tuple(x) for x in pars]
+    wants = [oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class, held, None if act is None else act[rows], pre_area=pa) for _, opar in pars]
+    for from_matrix in (False, True) if matrix else (False,):
+        if from_matrix:
+            t.fit()
+        for (par, _), want in zip(pars, wants):
+            (t.select if from_matrix else t.fit_select)(par, d_held, d_act)
+            for got, x in zip((t.cand_job, t.cand_cut, t.cand_score), want):
+                np.testing.assert_array_equal(got.cpu().numpy()[rows], x)
+
+
+def of_profiles(wl, many, length):
+    """The first `many` jobs' profiles by turns, from their start, for jobs of one class and wait."""
+    turn = np.arange(wl.n_jobs) % many
+    for name in ("dur", "mem", "safe"):
+        setattr(wl, name, getattr(wl, name).reshape(wl.n_jobs, length)[turn].reshape(-1))
+    wl.progress[:] = 0
+    wl.wait[:] = 77
+    wl.sla_class[:] = 1
+
+
+@pytest.mark.parametrize("area", [False, True])
+@pytest.mark.parametrize("many", [1, 40])           # (40 profiles have more durations and peaks than a block's slots)
+def test_jobs_of_the_same_profiles(engine, oracle, many, area):
+    wl = make_workload("small", 5, n_gaps=GAPS, n_jobs=JOBS)
+    of_profiles(wl, many, 256)
+    wl.wait[:64] = 76           # not of one key throughout: the others' are larger
+    wl.sla_class[JOBS // 2:] = 2
+    check(engine, oracle, wl, (0, 1, 2, 3), area=area)
+
+
+@pytest.mark.parametrize("kind", ["weights", "memory", "twins"])
+def test_equal_keys(engine, oracle, kind):
+    # weight 0: every reply of a tier has the same key; no memory: every F is 0; twins: equal scores, under MIXED of different F
+    wl = make_workload("tiny", 6, n_gaps=GAPS, n_jobs=JOBS)
+    if kind == "weights":
+        wl.sla_weight, wl.class0_override = (0, 0, 0), 0
+    elif kind == "memory":
+        wl.mem[:] = 0
+    else:
+        half = JOBS // 2 * 64
+        wl.dur[half:], wl.safe[half:], wl.mem[half:] = wl.dur[:half], wl.safe[:half], 2 * wl.mem[:half]
+        wl.progress[JOBS // 2:] = wl.progress[:JOBS // 2]
+        wl.C[:] = int(wl.mem.max()) + 1
+        wl.sla_class[:] = 1
+        wl.wait[:JOBS // 2], wl.wait[JOBS // 2:] = wl.wait_scale + 14, 7        # half the weight for twice the memory
+    check(engine, oracle, wl, (0, 2, 3))
+
+
+def test_one_duration_and_peak_of_different_areas(engine, oracle):
+    # a short peak of 100, then 1 or 3 for long: 200 or 400 of area per unit, weights of 2000 and 1000, so that all keys of a
+    # length are equal, and under MIXED the lowest job of the larger F is wanted; blocks of more than 1024 jobs
+    jobs, gaps = 600_000, 1000
+    rng = np.random.default_rng(8)
+    wl = make_workload("tiny", 8, n_gaps=gaps, n_jobs=8)
+    unit, large = rng.integers(1, 4, size=jobs), rng.random(jobs) < 0.5
+    wl.n_jobs, wl.seg_off = jobs, np.arange(0, 2 * jobs + 1, 2, dtype=np.int64)
+    wl.dur = np.stack([unit, 100 * unit], 1).reshape(-1).astype(np.int32)
+    wl.mem = np.stack([np.full(jobs, 100), np.where(large, 3, 1)], 1).reshape(-1).astype(np.int32)
+    wl.safe = np.tile(np.array([0, 1], dtype=np.uint8), jobs)
+    wl.progress = np.zeros(jobs, dtype=np.int32)
+    wl.wait = np.where(large, 0, 1000).astype(np.int32)
+    wl.sla_class = np.ones(jobs, dtype=np.uint8)
+    wl.W = rng.integers(50, 400, size=gaps).astype(np.int32)
+    wl.C = np.array([99, 100, 500], dtype=np.int32)[rng.integers(0, 3, size=gaps)]
+    check(engine, oracle, wl, (0, 1, 3), area=True, matrix=False)
+
+
+@pytest.mark.parametrize("area", [False, True])
+@pytest.mark.parametrize("windows", ["far", "negative", "huge"])
+def test_masks_and_windows(engine, oracle, windows, area):
+    wl = make_workload("tiny", 7, n_gaps=GAPS, n_jobs=JOBS)
+    rng = np.random.default_rng(9)
+    if windows == "far":
+        wl.W = ((2.0 ** (31 * rng.random(GAPS))).astype(np.int64) - 1).astype(np.int32)
+    elif windows == "negative":
+        wl.W[:GAPS // 2] = rng.integers(-2**31, 0, size=GAPS // 2)
+        wl.C[::7] = -5
+    else:
+        wl.W[:] = 2**31 - 1
+        wl.W[::3] = -2**31
+    held = np.where(rng.random(JOBS) < 0.4, 3, -1).astype(np.int32)
+    check(engine, oracle, wl, (0, 1, 2, 3), held, (rng.random(GAPS) < 0.7).astype(np.uint8), area=area)
