@@ -12,8 +12,8 @@
 //     their position of every class that admits them;
 //   * k_floor_ties: who has that key, under MIXED with the largest F; k_floor_reduce: the running maximum.
 // What is left is reading all atoms once and those of every fourth job twice, bound by some fifty instructions for an
-// atom (filter, 32768 gaps x 65536 jobs of 130 atoms: 50 us; with keys of 64 bits throughout, 83), and 40 us of short
-// kernels.  At that size fit -> select takes 159 us where k_range_select takes 435, at 8192 x 32768 a select 61 us where
+// atom (filter, 32768 gaps x 65536 jobs of 130 atoms: 56 us; with keys of 64 bits throughout, 83), and 40 us of short
+// kernels.  At that size fit -> select takes 175 us where k_range_select takes 398, at 8192 x 32768 a select 66 us where
 // reading the matrix takes 320.  sja.hip says where the line lies (by_floor).
 #pragma once
 
@@ -45,9 +45,6 @@ inline int floor_step_of(int n_jobs)
 }
 
 // Buckets of durations: exact below 2^(bits + 1), then 2^bits to an octave.
-struct FloorBuckets {
-    int bits, per_class;        // per_class: 0 if there is no room for any
-};
 __device__ __forceinline__ int bucket_of(int d, int bits)
 {
     const int e = max(31 - __clz(d) - bits, 0);
@@ -63,14 +60,25 @@ __device__ __forceinline__ int bucket_begin(int b, int bits)
     const int e = max((b >> bits) - 1, 0);
     return (b - (e << bits)) << e;
 }
-// As fine as there is room for, for durations up to `longest`.
-__device__ __forceinline__ FloorBuckets floor_buckets(int n_classes, int longest, int room)
+struct FloorBuckets {
+    int bits, per_class;        // per_class: 0 if there is no room for any
+    int base, low;
+
+    __device__ __forceinline__ int of(int d) const { return bucket_of(max(d, low), bits) - base; }
+    __device__ __forceinline__ int behind(int d) const { return d <= low ? 0 : bucket_behind(d, bits) - base; }     // the first that begins at or behind it
+    __device__ __forceinline__ int begin(int k) const { return k == 0 ? low : bucket_begin(k + base, bits); }
+};
+// The buckets of a batch: from its smallest window on, which stands for all durations below, up to its longest one; as fine
+// as there is room for.
+__device__ __forceinline__ FloorBuckets floor_buckets(int n_classes, int low, int longest, int room)
 {
+    low = max(low, 1);
+    longest = max(longest, low);
     for (int bits = 12; bits >= 0; --bits) {
-        const int n = bucket_of(max(longest, 0), bits) + 2;
-        if (int64_t(n) * n_classes <= room) return {bits, n};
+        const int base = bucket_of(low, bits), n = bucket_of(longest, bits) - base + 2;
+        if (int64_t(n) * n_classes <= room) return {bits, n, base, low};
     }
-    return {0, 0};
+    return {0, 0, 0, 1};
 }
 
 // What the kernels share: the tables of the plan, and where the intermediate results are.
@@ -101,6 +109,8 @@ constexpr int kPeakBits = 3, kPeakBuckets = 256, kPeakLast = ((31 - kPeakBits) <
 static_assert(kPeakLast < kPeakBuckets, "the bucket of 2^31 - 1");
 struct FloorClasses {
     int cap[kMaxClasses + 1], longest[kMaxClasses + 1];     // capacity; the largest window of this class and those of larger capacities
+    int begin[kMaxClasses + 1];                             // the first position
+    int low;                                                // the smallest window
     uint8_t below[kPeakBuckets];                            // classes whose capacity is below a bucket of peaks
 };
 
@@ -110,15 +120,18 @@ __device__ __forceinline__ FloorBuckets floor_classes(const FloorArgs &A, FloorC
     if (tid < kWave) {
         const int begin = A.class_begin[tid], end = A.class_begin[tid + 1];         // (asked for together with the plan)
         const bool there = tid < n_classes;
-        int w = there ? A.gap_w[end - 1] : INT32_MIN;
+        int w = there ? A.gap_w[end - 1] : INT32_MIN, low = there ? A.gap_w[begin] : INT32_MAX;
         S.cap[tid] = there ? A.gap_c[begin] : INT32_MAX;
+        S.begin[tid] = begin;
+        if (tid == kWave - 1) S.begin[kMaxClasses] = end;
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
             const int o = __shfl_down(w, d, kWave);
             if (tid + d < kWave) w = max(w, o);
+            low = min(low, __shfl_xor(low, d, kWave));
         }
         S.longest[tid] = w;
-        if (tid == 0) { S.cap[kMaxClasses] = INT32_MAX; S.longest[kMaxClasses] = INT32_MIN; }
+        if (tid == 0) { S.cap[kMaxClasses] = INT32_MAX; S.longest[kMaxClasses] = INT32_MIN; S.low = low; }
     }
     __syncthreads();
     if (tid < kPeakBuckets) {            // (blocks have as many threads)
@@ -128,7 +141,7 @@ __device__ __forceinline__ FloorBuckets floor_classes(const FloorArgs &A, FloorC
         S.below[tid] = uint8_t(c);
     }
     __syncthreads();
-    return floor_buckets(n_classes, S.longest[0], A.room);
+    return floor_buckets(n_classes, __builtin_amdgcn_readfirstlane(S.low), __builtin_amdgcn_readfirstlane(S.longest[0]), A.room);
 }
 
 // A stand-in for a key that grows with it, but for kDigestSlack: tier, and the score rounded to 24 bits (five roundings
@@ -271,7 +284,7 @@ __global__ __launch_bounds__(kFloorThreads) __attribute__((amdgpu_waves_per_eu(A
     if (B.per_class > 0)
         atoms.walk(A, S,
                    [&](int, const typename FloorAtoms<AREA>::Atom &x, unsigned long long, int c, uint32_t digest) {
-                       uint32_t &at = s_table[c * B.per_class + bucket_behind(x.v.x, B.bits)];
+                       uint32_t &at = s_table[c * B.per_class + B.behind(x.v.x)];
                        if (digest > *static_cast<volatile uint32_t *>(&at)) atomicMax(&at, digest);
                    },
                    [](int, int) {});
@@ -299,7 +312,7 @@ __global__ __launch_bounds__(kFloorMergeThreads) void k_floor_merge(FloorArgs A,
     __syncthreads();
     if (!there) return;
     if (group == 1) {
-        const int c = i / B.per_class, k = i - c * B.per_class, w = bucket_begin(k, B.bits);
+        const int c = i / B.per_class, k = i - c * B.per_class, w = B.begin(k);
         int lo = A.class_begin[c], hi = A.class_begin[c + 1];
         if (k == B.per_class - 1) lo = hi;          // (begins behind every window, be it beyond 31 bits)
         while (lo < hi) {
@@ -315,64 +328,73 @@ __global__ __launch_bounds__(kFloorMergeThreads) void k_floor_merge(FloorArgs A,
 }
 
 // Calls on(position, key, place, largest key there so far) for the first position that each of n atoms from `first` on reaches
-// in every class that admits it, unless it is below the running maximum there already.  Several atoms side by side: each
-// is a chain of trips to memory.
-constexpr int kEventsQ = 4;
-template <typename On>
+// in every class that admits it, unless it is below the running maximum there already; as that does not fall along the
+// classes, an atom is done with at the first one where it is.  Several atoms side by side: each is a chain of trips to memory.
+// Where many atoms are near the best that is what counts, and how fine the buckets are (fit -> select of 32768 gaps of 64
+// capacities x 65536 jobs of 128 segments, EFFICIENCY: 1190 us with a lane for each of 64 classes and buckets from duration
+// 1 on, 746 so; of one profile 489 and 318).
+constexpr int kEventsLanes = 16;
+template <int Q, typename On>
 __device__ __forceinline__ void floor_events(const FloorArgs &A, const FloorClasses &S, const FloorBuckets &B, const uint32_t *running, int64_t first,
                                              int n, int threads, On on)
 {
-    constexpr int Q = kEventsQ;
     const int n_classes = A.plan[kPlanClasses];
-    int lanes = 1;                              // to an atom: one to a class
-    while (lanes < n_classes) lanes <<= 1;
-    const int c = threadIdx.x & (lanes - 1), step = threads / lanes;
-    if (c >= n_classes) return;
-    const int cap = S.cap[c], begin = A.class_begin[c], end = A.class_begin[c + 1];
+    int lanes = 1;                              // to an atom: one to a class,
+    while (lanes < n_classes && lanes < kEventsLanes) lanes <<= 1;      // of many classes they take the next ones after these
+    const int c0 = threadIdx.x & (lanes - 1), step = threads / lanes;
     for (int i = threadIdx.x / lanes; i < n; i += Q * step) {
         ulonglong2 x[Q];
-        int lo[Q], hi[Q];
+        int k[Q];
+        uint32_t digest[Q];
+        unsigned live = 0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) x[q] = A.near[first + min(i + q * step, n - 1)];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const int d = int(x[q].y >> 32);
-            bool in = i + q * step < n && int(uint32_t(x[q].y)) <= cap;
-            lo[q] = begin;
-            hi[q] = end;
-            if (B.per_class) {
-                const int k = bucket_of(d, B.bits), at = c * B.per_class + min(k, B.per_class - 2);
-                const unsigned long long score = (x[q].x - 1ull) & ((1ull << 62) - 1ull);
-                // (longer than every window; below the running maximum)
-                in = in && k < B.per_class - 1 && floor_digest(uint32_t((x[q].x - 1ull) >> 62), float(score)) + kDigestSlack >= running[at];
-                if (in) {
-                    lo[q] = A.bucket_pos[at];
-                    hi[q] = A.bucket_pos[at + 1];
-                }
-            }
-            if (!in) lo[q] = hi[q] = end;
+            const unsigned long long score = (x[q].x - 1ull) & ((1ull << 62) - 1ull);
+            digest[q] = floor_digest(uint32_t((x[q].x - 1ull) >> 62), float(score)) + kDigestSlack;
+            k[q] = B.of(int(x[q].y >> 32));
+            live |= unsigned(i + q * step < n && (B.per_class == 0 || k[q] < B.per_class - 1)) << q;        // (not longer than every window)
         }
-        for (bool more = true; more;) {
-            int w[Q];
-            more = false;
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (lo[q] < hi[q]) w[q] = A.gap_w[(lo[q] + hi[q]) >> 1];
+#pragma unroll 1
+        for (int c = c0; c < n_classes && live; c += lanes) {
+            const int cap = S.cap[c], begin = S.begin[c], end = S.begin[c + 1];
+            int lo[Q], hi[Q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-                if (lo[q] >= hi[q]) continue;
-                const int mid = (lo[q] + hi[q]) >> 1;
-                if (w[q] < int(x[q].y >> 32)) lo[q] = mid + 1; else hi[q] = mid;
-                more |= lo[q] < hi[q];
+                lo[q] = hi[q] = end;
+                if (!(live >> q & 1u) || int(uint32_t(x[q].y)) > cap) continue;
+                if (B.per_class == 0) {
+                    lo[q] = begin;
+                } else if (digest[q] < running[c * B.per_class + k[q]]) {
+                    live &= ~(1u << q);
+                } else {
+                    lo[q] = A.bucket_pos[c * B.per_class + k[q]];
+                    hi[q] = A.bucket_pos[c * B.per_class + k[q] + 1];
+                }
             }
+            for (bool more = true; more;) {
+                int w[Q];
+                more = false;
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if (lo[q] < hi[q]) w[q] = A.gap_w[(lo[q] + hi[q]) >> 1];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    if (lo[q] >= hi[q]) continue;
+                    const int mid = (lo[q] + hi[q]) >> 1;
+                    if (w[q] < int(x[q].y >> 32)) lo[q] = mid + 1; else hi[q] = mid;
+                    more |= lo[q] < hi[q];
+                }
+            }
+            unsigned long long best[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (lo[q] < end) best[q] = __hip_atomic_load(&A.best[lo[q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (lo[q] < end) on(lo[q], x[q].x, first + i + q * step, best[q]);
         }
-        unsigned long long best[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (lo[q] < end) best[q] = __hip_atomic_load(&A.best[lo[q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (lo[q] < end) on(lo[q], x[q].x, first + i + q * step, best[q]);
     }
 }
 
@@ -502,7 +524,7 @@ __global__ __launch_bounds__(kFloorThreads) __attribute__((amdgpu_waves_per_eu(A
     const int64_t first = j0 < A.n_jobs ? A.seg_off[j0] : 0;
     atoms.walk(A, S,
                [&](int j, const typename FloorAtoms<AREA>::Atom &x, unsigned long long area, int c, uint32_t digest) {
-                   if (B.per_class && digest + kDigestSlack < s_table[c * B.per_class + bucket_of(x.v.x, B.bits)]) return;
+                   if (B.per_class && digest + kDigestSlack < s_table[c * B.per_class + B.of(x.v.x)]) return;
                    const unsigned long long F = AREA ? area : rect_of(x.v.x, x.v.y), score = times_mult(F, x.mult);
                    if (!x.first) {              // a key that the atom before it had already says nothing new
                        const int2 u = A.atom_dp[x.at - 1];
@@ -522,7 +544,7 @@ __global__ __launch_bounds__(kFloorThreads) __attribute__((amdgpu_waves_per_eu(A
     int n = s_n;
     if (n > kFloorThinFrom) n = floor_thin<AREA>(A, s_slots, first, n);
     if (tid == 0) A.n_near[blockIdx.x] = n;
-    floor_events(A, S, B, s_table, first, n, kFloorThreads, [&](int p, unsigned long long key, int64_t, unsigned long long best) {
+    floor_events<4>(A, S, B, s_table, first, n, kFloorThreads, [&](int p, unsigned long long key, int64_t, unsigned long long best) {
         if (key > best) atomicMax(&A.best[p], key);
     });
 }
@@ -547,7 +569,7 @@ __global__ __launch_bounds__(kTiesThreads) void k_floor_ties(FloorArgs A, int ag
     const FloorBuckets B = floor_classes(A, S);
     // (atomics on one word are served one after the other: most need none)
     auto now = [](auto &x) { return __hip_atomic_load(&x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    floor_events(A, S, B, A.running, first, n, kTiesThreads, [&](int p, unsigned long long key, int64_t place, unsigned long long best) {
+    floor_events<2>(A, S, B, A.running, first, n, kTiesThreads, [&](int p, unsigned long long key, int64_t place, unsigned long long best) {
         if (key != best) return;
         const ulonglong2 y = A.near_job[place];
         const int job = int(y.y);

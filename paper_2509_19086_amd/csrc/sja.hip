@@ -130,7 +130,7 @@ PolicyDev to_dev(const sja_params *p)
     return d;
 }
 
-constexpr int64_t kSelectByAtoms = int64_t(1) << 24, kFloorLeast = int64_t(1) << 27, kFloorLeastOfJobs = 6 << 10;
+constexpr int64_t kSelectByAtoms = int64_t(1) << 24;
 
 // Enqueues the pass over the cut matrix, which leaves partial bests per job tile.  The
 // per-prefix keys live in the space the list building of sja_resolve uses for
@@ -943,14 +943,22 @@ int launch_floor_reduce(sja_ctx *ctx, hipStream_t st, const Layout &L, const Flo
 bool select_by_atoms(int64_t n_gaps, int64_t n_jobs, bool table_of_F) { return n_gaps * n_jobs >= (table_of_F ? 2 * kSelectByAtoms : kSelectByAtoms); }
 
 // Which form looks for the best job per gap where the plan has class tables and the keys rise.  k_range_select looks at the
-// ends of every job in every chunk of positions, two gathers each; the k_floor_ kernels at all atoms once or twice, and
-// take 40 us of launches and short kernels, but no start tables after sja_fit_select.  k_range_select and they, us (from
-// the heavy to the light profiles), fit -> select of 20000 gaps x 8192 jobs (327000 jobs and chunks) 194 to 82 and 170 to
-// 84, a select 154 to 45 and 102 to 54; 3000 x 65536 (393000) 175 to 112 and 170 to 76, a select 120 to 64 and 140 to 55;
-// 8192 x 32768 (524000) 293 to 104 and 149 to 81; 32768 x 65536 (4.2 million) 704 to 202 and 163 to 102.
-// The line lies at pairs, and at the jobs: few of them have shorter chunks and stay in the caches.  24888 x 1936 78 to 111,
-// 32000 x 3500 98 to 110, 32000 x 5000 147 to 120 and 86 to 93; 20000 x 7000 172 to 110 and 83 to 84, 8192 x 17000 203 to 104.
-bool by_floor(int64_t n_gaps, int64_t n_jobs) { return n_gaps * n_jobs > kFloorLeast && n_jobs >= kFloorLeastOfJobs; }
+// ends of every job in every chunk of positions, two gathers each; the k_floor_ kernels at all atoms once or twice and at
+// those near the best again, and take 40 us of launches and short kernels, but no start tables after sja_fit_select.
+// Near the best are many atoms where many jobs have equal keys, or where many capacities leave few buckets to each.
+// k_range_select and they, us, fit -> select by EFFICIENCY of random jobs / of 16 profiles and equal waits / of 64 capacities:
+// 30000 gaps x 8000 jobs 129 and 157 / 137 and 181 / 270 and 950, 8192 x 32768 183 and 172 / 187 and 252 / 534 and 980,
+// 24000 x 32768 184 and 130 / 181 and 231 / 369 and 444, 32768 x 32768 220 and 135 / 223 and 238 / 449 and 502, 16384 x 65536
+// 302 and 151 / 314 and 180 / 585 and 662, 32768 x 65536 345 and 158 / 352 and 192 / 797 and 746, the last of 512 segments
+// a job instead of 128 364 and 249 / 374 and 335 / 1628 and 2348; by MIXED 227 and 130 / 475 and 218 / 450 and 201 at that size.
+// (Of few jobs the chunks' rows stay in the caches: 150000 x 7000 416 and 324, 32000 x 3500 98 and 110.)
+// A select does not need the matrix then, which takes 1.05 us per million pairs: from fewer pairs on.
+constexpr int64_t kFloorFitLeast = int64_t(1) << 30, kFloorSelectLeast = int64_t(1) << 27;
+constexpr int kFloorLeastOfJobs = 6 << 10;
+bool by_floor(int64_t n_gaps, int64_t n_jobs, bool fitted)
+{
+    return n_gaps * n_jobs >= (fitted ? kFloorSelectLeast : kFloorFitLeast) && n_jobs >= kFloorLeastOfJobs;
+}
 
 // k_range_select, along the start tables: partials of as many tiles of jobs as returned.
 int launch_ranges(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params, const int32_t *wait,
@@ -1031,7 +1039,7 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
         int rc = timed ? mark_kernel(ctx, st, false) : SJA_OK;
         if (rc != SJA_OK) return rc;
         const bool rise = keys_rise(ctx);
-        const bool floor = rise && by_floor(n_gaps, J);
+        const bool floor = rise && by_floor(n_gaps, J, false);
         if (starts && !floor && (rc = enqueue_starts(ctx, st, L)) != SJA_OK) return rc;
         if (rise && tabled != Tabled::No) {
             by_atoms = true;
@@ -1515,7 +1523,7 @@ int sja_select(sja_ctx *ctx, void *stream, const sja_params *params, const int32
     if (!keys_rise(ctx) || !select_by_atoms(G, J, atom_area_of(ctx, L) != nullptr))
         return launch_select(ctx, st, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut, cand_score);
     // along the plan of the fit, without reading the matrix; along the matrix if the plan has no class tables
-    const bool floor = by_floor(G, J);
+    const bool floor = by_floor(G, J, true);
     FloorArgs args{};
     int range_tiles = 0;
     if (floor) {

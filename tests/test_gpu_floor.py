@@ -8,7 +8,7 @@ import pytest
 from gen import make_workload
 
 pytestmark = pytest.mark.gpu
-GAPS, JOBS = 33000, 16400       # more than 2^29 pairs, blocks of 64 jobs
+GAPS, JOBS = 66000, 16400       # more than 2^30 pairs, blocks of 64 jobs
 
 
 @pytest.fixture(scope="module")
@@ -86,7 +86,7 @@ def test_equal_keys(engine, oracle, kind):
 def test_one_duration_and_peak_of_different_areas(engine, oracle):
     # a short peak of 100, then 1 or 3 for long: 200 or 400 of area per unit, weights of 2000 and 1000, so that all keys of a
     # length are equal, and under MIXED the lowest job of the larger F is wanted; blocks of more than 1024 jobs
-    jobs, gaps = 600_000, 1000
+    jobs, gaps = 600_000, 1800
     rng = np.random.default_rng(8)
     wl = make_workload("tiny", 8, n_gaps=gaps, n_jobs=8)
     unit, large = rng.integers(1, 4, size=jobs), rng.random(jobs) < 0.5
@@ -100,6 +100,14 @@ def test_one_duration_and_peak_of_different_areas(engine, oracle):
     wl.W = rng.integers(50, 400, size=gaps).astype(np.int32)
     wl.C = np.array([99, 100, 500], dtype=np.int32)[rng.integers(0, 3, size=gaps)]
     check(engine, oracle, wl, (0, 1, 3), area=True, matrix=False)
+
+
+@pytest.mark.parametrize("caps", [1, 16, 17, 64, 65])        # (16 classes of an atom side by side; 65 capacities have no class tables)
+def test_capacities(engine, oracle, caps):
+    wl = make_workload("tiny", 3, n_gaps=GAPS, n_jobs=JOBS)
+    wl.C = np.linspace(2000, 40960, caps).astype(np.int32)[np.random.default_rng(5).integers(0, caps, size=GAPS)]
+    wl.W[:50] = 1 + np.arange(50)
+    check(engine, oracle, wl, (0, 3))
 
 
 @pytest.mark.parametrize("area", [False, True])
