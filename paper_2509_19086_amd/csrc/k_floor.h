@@ -85,6 +85,7 @@ __device__ __forceinline__ FloorBuckets floor_buckets(int n_classes, int low, in
 struct FloorArgs {
     PolicyDev pol;
     int n_jobs, n_gaps, room;                   // room: buckets that there is space for
+    int most_classes;                           // of the batches that are served
     const int64_t *seg_off;
     const int2 *atom_dp;
     const long long *atom_area;                 // F of an atom, null: duration x peak
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(kFloorThreads) __attribute__((amdgpu_waves_per_eu(A
 {
     __shared__ uint32_t s_table[kFloorBuckets];
     __shared__ FloorClasses S;
-    if (!A.plan[kPlanTabled]) return;
+    if (!serves(A.plan, A.most_classes)) return;
     FloorAtoms<AREA> atoms;
     atoms.begin(A, step);
     const FloorBuckets B = floor_classes(A, S);
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(kFloorMergeThreads) void k_floor_merge(FloorArgs A,
     __shared__ uint32_t s_top[GROUPS][kFloorMergeEntries];
     __shared__ FloorClasses S;
     static_assert(kFloorMergeThreads >= kPeakBuckets && kFloorThreads >= kPeakBuckets, "a thread per bucket of peaks");
-    if (!A.plan[kPlanTabled]) return;
+    if (!serves(A.plan, A.most_classes)) return;
     const FloorBuckets B = floor_classes(A, S);
     const int at = threadIdx.x % kFloorMergeEntries, group = threadIdx.x / kFloorMergeEntries, i = blockIdx.x * kFloorMergeEntries + at;
     const bool there = i < B.per_class * A.plan[kPlanClasses];
@@ -493,7 +494,7 @@ __global__ __launch_bounds__(kFloorThreads) __attribute__((amdgpu_waves_per_eu(A
     __shared__ FloorClasses S;
     __shared__ FloorSlots<AREA> s_slots;
     __shared__ int s_n;
-    if (!A.plan[kPlanTabled]) return;
+    if (!serves(A.plan, A.most_classes)) return;
     FloorAtoms<AREA> atoms;
     atoms.begin(A, 1);
     const FloorBuckets B = floor_classes(A, S);
@@ -559,7 +560,7 @@ template <bool MIXED>
 __global__ __launch_bounds__(kTiesThreads) void k_floor_ties(FloorArgs A, int again)
 {
     __shared__ FloorClasses S;
-    if (!A.plan[kPlanTabled]) return;
+    if (!serves(A.plan, A.most_classes)) return;
     int32_t *several = A.n_near + kFloorBlocks;
     if (again && !*several) return;
     const int n = A.n_near[blockIdx.x];
@@ -588,7 +589,7 @@ __global__ __launch_bounds__(kTiesThreads) void k_floor_ties(FloorArgs A, int ag
 }
 
 // The running maximum over the positions of a class, by blocks of `tile` positions that first look at those before them;
-// and the winner's atom.  Without class tables the best over the job tiles of the form that served the batch: the winner's
+// and the winner's atom.  Where another form has served the batch the best over its job tiles: the winner's
 // atom count becomes its boundary (from_matrix: the partial has the boundary itself).
 constexpr int kFloorTile = 256;
 inline int floor_tile(int n_gaps) { return kFloorTile * ((n_gaps + 65535) / 65536); }
@@ -599,7 +600,7 @@ __global__ __launch_bounds__(256) void k_floor_reduce(FloorArgs A, int tile, int
                                                       const uint8_t *__restrict__ gap_active, const int2 *__restrict__ atom_db,
                                                       int32_t *__restrict__ cand_job, int32_t *__restrict__ cand_cut, int64_t *__restrict__ cand_score)
 {
-    if (!A.plan[kPlanTabled]) {
+    if (!serves(A.plan, A.most_classes)) {
         int g, bj, ba;
         unsigned long long bh;
         if (!reduce_tiles(A.n_gaps, step_tiles, part, g, bh, bj, ba)) return;

@@ -489,7 +489,7 @@ constexpr int kRangeTogether = 4;           // jobs whose atoms a group asks for
 
 template <bool MIXED, bool AREA>
 __global__ __launch_bounds__(kRangeThreads) void k_range_select(
-    int n_jobs, int n_gaps, int chunk_bound, int batches, PolicyDev pol, const int64_t *__restrict__ seg_off,
+    int n_jobs, int n_gaps, int chunk_bound, int batches, int most_classes, PolicyDev pol, const int64_t *__restrict__ seg_off,
     const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area, const int32_t *__restrict__ plan,
     const int32_t *__restrict__ chunk_begin, const int32_t *__restrict__ chunk_end, const int32_t *__restrict__ chunk_class,
     const int32_t *__restrict__ start_tab, const int32_t *__restrict__ ncap_tab, const int32_t *__restrict__ gap_w,
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kRangeThreads) void k_range_select(
     __shared__ int s_count, s_n_near, s_several;
     const int k = blockIdx.x >> 3, job_tile = (k / chunk_bound) * 8 + (blockIdx.x & 7), chunk = k % chunk_bound;
     const int tile_jobs = batches * kRangeThreads, job0 = job_tile * tile_jobs;
-    if (!plan[kPlanTabled] || job0 >= n_jobs || chunk >= plan[kPlanChunks]) return;
+    if (!serves(plan, most_classes) || job0 >= n_jobs || chunk >= plan[kPlanChunks]) return;
     const int tid = threadIdx.x, sub = tid & (kRangeLanes - 1), group = tid / kRangeLanes;
     const int begin = chunk_begin[chunk], n = chunk_end[chunk] - begin, cls = chunk_class[chunk];
     const bool last_of_class = chunk + 1 >= plan[kPlanChunks] || chunk_class[chunk + 1] != cls;
@@ -681,14 +681,14 @@ __global__ __launch_bounds__(kRangeThreads) void k_range_select(
 
 // Final arg-max over the job tiles of either form: where there were steps, the winner's atom count becomes its
 // boundary (from_matrix: the partial has the boundary itself), else its atom is searched.
-__global__ __launch_bounds__(256) void k_range_reduce(int n_gaps, int step_tiles, int range_tiles, int from_matrix, const SelPartial *__restrict__ part,
+__global__ __launch_bounds__(256) void k_range_reduce(int n_gaps, int step_tiles, int range_tiles, int most_classes, int from_matrix, const SelPartial *__restrict__ part,
                                                       const int32_t *__restrict__ plan, const int32_t *__restrict__ gap_w,
                                                       const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
                                                       const int2 *__restrict__ atom_dp, const int2 *__restrict__ atom_db,
                                                       const int32_t *__restrict__ n_atoms, int32_t *__restrict__ cand_job,
                                                       int32_t *__restrict__ cand_cut, int64_t *__restrict__ cand_score)
 {
-    const bool ranges = plan[kPlanTabled] != 0;
+    const bool ranges = serves(plan, most_classes);
     int g, bj, ba;
     unsigned long long bh;
     if (!reduce_tiles(n_gaps, ranges ? range_tiles : step_tiles, part, g, bh, bj, ba)) return;

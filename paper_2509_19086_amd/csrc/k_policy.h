@@ -1,9 +1,13 @@
-// The policy key of a pair (Sec. 3.5 phase 3): what the kernels that compare jobs share.
+// The policy key of a pair (Sec. 3.5 phase 3), and which batches a form serves: what the kernels that compare jobs share.
 #pragma once
 
 #include "sja_internal.h"
 
 namespace sja {
+
+// The batches that a form serves: those whose plan, which only the device knows, has class tables and at most so many classes.
+constexpr int kAnyClasses = kMaxClasses, kNoClasses = -1;
+__device__ __forceinline__ bool serves(const int32_t *plan, int most_classes) { return plan[kPlanTabled] && plan[kPlanClasses] <= most_classes; }
 
 struct PolicyDev {
     int policy;

@@ -130,28 +130,27 @@ PolicyDev to_dev(const sja_params *p)
     return d;
 }
 
-constexpr int64_t kSelectByAtoms = int64_t(1) << 24;
-
 // Enqueues the pass over the cut matrix, which leaves partial bests per job tile.  The
 // per-prefix keys live in the space the list building of sja_resolve uses for
 // its atom keys (the two never run at the same time); `keys_ready` says that an
 // earlier call with the same policy inputs left them there and nothing has
-// written that space since.  With unless_tabled (the plan) the kernels do nothing where that has class tables, and take 3 us
-// for every 16384 blocks of that; fewer blocks with several tiles each made the batches that they do serve slower (8192 gaps
+// written that space since.  The kernels do nothing for batches that another form serves, and take 3 us for every 16384
+// blocks of that; fewer blocks with several tiles each made the batches that they do serve slower (8192 gaps
 // of 65 capacities x 32768 jobs 528 us a select with a block to a tile, 590 with 2048 blocks and 536 with 16384; the loop
 // takes registers).
 int launch_matrix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_params *params, const int32_t *wait,
-                       const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active, const int32_t *unless_tabled,
+                       const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active, int unless_classes,
                        bool keys_ready)
 {
     const int G = ctx->n_gaps, J = ctx->n_jobs, job_tiles = (J + kSelBlock - 1) / kSelBlock;
+    const int32_t *plan = unless_classes == kNoClasses ? nullptr : ws_ptr<int32_t>(ctx, L.plan);
     unsigned long long *seg_key = ws_ptr<unsigned long long>(ctx, L.g_key_hi);
     if (job_tiles > 0 && !keys_ready) {
         const int per_wave = keys_jobs_per_wave(J, ctx->n_segments);
         const unsigned key_blocks = unsigned((J + 4 * per_wave - 1) / (4 * per_wave));
         hipLaunchKernelGGL(k_select_keys, dim3(key_blocks), dim3(256), 0, st, J, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp),
                            ws_ptr<int2>(ctx, L.atom_db), atom_area_of(ctx, L), ws_ptr<int32_t>(ctx, L.n_atoms), wait, sla_class,
-                           ctx->pre_dur, ctx->pre_peak, pre_area_of(ctx, L), keys_dense(ctx->n_segments, ctx->hyst_used_n_caps > 0), per_wave, unless_tabled, seg_key);
+                           ctx->pre_dur, ctx->pre_peak, pre_area_of(ctx, L), keys_dense(ctx->n_segments, ctx->hyst_used_n_caps > 0), per_wave, unless_classes, plan, seg_key);
         SJA_HIP(hipGetLastError(), "k_select_keys launch");
     }
     if (job_tiles > 0) {
@@ -162,7 +161,7 @@ int launch_matrix_pass(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_
         auto kern = mixed ? k_select_pass<true> : k_select_pass<false>;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(kSelBlock), 0, st, J, G, n_chunks,
                            to_dev(params), ctx->seg_off, seg_key, ctx->cut,
-                           ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active, unless_tabled,
+                           ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active, unless_classes, plan,
                            ws_ptr<SelPartial>(ctx, L.sel_part));
         SJA_HIP(hipGetLastError(), "k_select_pass launch");
     }
@@ -177,7 +176,7 @@ int launch_select(sja_ctx *ctx, hipStream_t st, const sja_params *params, const 
     const Layout L = make_layout(ctx->n_gaps, ctx->n_jobs, ctx->n_segments);
     const int G = ctx->n_gaps, job_tiles = (ctx->n_jobs + kSelBlock - 1) / kSelBlock;
     if (G == 0) return SJA_OK;
-    const int rc = launch_matrix_pass(ctx, st, L, params, wait, sla_class, job_held, gap_active, nullptr, keys_ready);
+    const int rc = launch_matrix_pass(ctx, st, L, params, wait, sla_class, job_held, gap_active, kNoClasses, keys_ready);
     if (rc != SJA_OK) return rc;
     hipLaunchKernelGGL(k_select_reduce, dim3((G + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, G, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), cand_job, cand_cut, cand_score);
@@ -864,7 +863,7 @@ int launch_best_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_g
 
 // The best job per gap by atoms (k_floor.h).  The intermediate results take the space of the list entries, of the
 // records and of the partials.
-FloorArgs floor_args(sja_ctx *ctx, const Layout &L, int32_t n_gaps, const sja_params *params, const int32_t *wait, const uint8_t *sla_class,
+FloorArgs floor_args(sja_ctx *ctx, const Layout &L, int32_t n_gaps, int most_classes, const sja_params *params, const int32_t *wait, const uint8_t *sla_class,
                      const int32_t *job_held)
 {
     FloorArgs args{};
@@ -872,6 +871,7 @@ FloorArgs floor_args(sja_ctx *ctx, const Layout &L, int32_t n_gaps, const sja_pa
     args.pol = to_dev(params);
     args.n_jobs = ctx->n_jobs;
     args.n_gaps = n_gaps;
+    args.most_classes = most_classes;
     args.room = int(room < kFloorBuckets ? room : kFloorBuckets);
     args.seg_off = ctx->seg_off;
     args.atom_dp = ws_ptr<int2>(ctx, L.atom_dp);
@@ -936,12 +936,6 @@ int launch_floor_reduce(sja_ctx *ctx, hipStream_t st, const Layout &L, const Flo
     return SJA_OK;
 }
 
-// Whether a select goes by the atoms or along the matrix, which takes 1.05 us per million pairs besides the keys of all cuts.
-// Matrix and atoms, us: 2048 gaps x 8192 jobs 50 and 27, 8192 x 32768 320 and 61, 886 x 13356 37 and 43, 96 x 10128 21 and
-// 22; where a table of F (area, hysteresis) makes three gathers of two and fewer atoms differ 6701 x 2866 38 and 48,
-// 10727 x 19926 230 and 68.
-bool select_by_atoms(int64_t n_gaps, int64_t n_jobs, bool table_of_F) { return n_gaps * n_jobs >= (table_of_F ? 2 * kSelectByAtoms : kSelectByAtoms); }
-
 // Which form looks for the best job per gap where the plan has class tables and the keys rise.  k_range_select looks at the
 // ends of every job in every chunk of positions, two gathers each; the k_floor_ kernels at all atoms once or twice and at
 // those near the best again, and take 40 us of launches and short kernels, but no start tables after sja_fit_select.
@@ -952,29 +946,51 @@ bool select_by_atoms(int64_t n_gaps, int64_t n_jobs, bool table_of_F) { return n
 // 302 and 151 / 314 and 180 / 585 and 662, 32768 x 65536 345 and 158 / 352 and 192 / 797 and 746, the last of 512 segments
 // a job instead of 128 364 and 249 / 374 and 335 / 1628 and 2348; by MIXED 227 and 130 / 475 and 218 / 450 and 201 at that size.
 // (Of few jobs the chunks' rows stay in the caches: 150000 x 7000 416 and 324, 32000 x 3500 98 and 110.)
-// A select does not need the matrix then, which takes 1.05 us per million pairs: from fewer pairs on.
-constexpr int64_t kFloorFitLeast = int64_t(1) << 30, kFloorSelectLeast = int64_t(1) << 27;
+constexpr int64_t kFloorLeast = int64_t(1) << 30;
 constexpr int kFloorLeastOfJobs = 6 << 10;
-bool by_floor(int64_t n_gaps, int64_t n_jobs, bool fitted)
+bool by_floor(int64_t n_gaps, int64_t n_jobs) { return n_gaps * n_jobs >= kFloorLeast && n_jobs >= kFloorLeastOfJobs; }
+
+// A select goes along the matrix, which takes 1.05 us per million pairs besides the keys of all cuts whatever the jobs are
+// like, or without it.  Matrix / k_range_select, us, random jobs and jobs of 16 profiles with equal waits, 4 to 8 capacities:
+// 2048 gaps x 8192 jobs 63 / 67 and 89 / 156, 886 x 20000 57 / 80 and 87 / 102, 8192 x 8192 103 / 70 and 178 / 174, 20000 x 4000
+// 111 / 60 and 202 / 104, 4096 x 36000 204 / 115 and 346 / 155.  The more capacities, the fewer gaps to a chunk: 300 x 450000 of
+// 8 / 16 / 24 capacities 293 / 183, 312 / 326 and 303 / 381, 700 x 200000 of 16 / 24 243 / 223 and 248 / 273, 2100 x 65600 of 24 / 64
+// 209 / 161 and 285 / 415, 4096 x 36000 of 24 / 64 301 / 227 and 300 / 505, 30000 x 8000 of 64 367 / 231.
+// Matrix / k_range_select / k_floor_: 5000 x 27000 of 16 profiles 185 / 99 / 304, 9000 x 16400 219 / 155 / 249, of random jobs and 24
+// capacities 234 / 156 / 296; 8192 x 32768 of 8 capacities 340 / 105 / 80 to 349 / 141 / 287, of 24 471 / 282 / 530; 16384 x 32768 of
+// 24 593 / 259 / 226, of 64 1022 / 538 / 376.
+constexpr int64_t kSelectByAtoms = int64_t(1) << 27, kSelectFloor = int64_t(1) << 28, kSelectFloorAnyClasses = int64_t(1) << 29;
+constexpr int kSelectFloorGaps = 8 << 10, kSelectFloorClasses = 16;
+struct SelectForm {
+    bool by_atoms, floor;
+    int most_classes;           // of the batches that go without the matrix
+};
+SelectForm select_form(int64_t n_gaps, int64_t n_jobs)
 {
-    return n_gaps * n_jobs >= (fitted ? kFloorSelectLeast : kFloorFitLeast) && n_jobs >= kFloorLeastOfJobs;
+    const int64_t pairs = n_gaps * n_jobs;
+    if (n_jobs >= kFloorLeastOfJobs && pairs >= kSelectFloorAnyClasses) return {true, true, kAnyClasses};
+    if (n_jobs >= kFloorLeastOfJobs && pairs >= kSelectFloor && n_gaps >= kSelectFloorGaps) return {true, true, kSelectFloorClasses};
+    int classes = kMaxClasses;
+    while (3 * int64_t(classes) * classes > n_gaps) --classes;
+    return {pairs >= kSelectByAtoms, false, classes};
 }
 
 // k_range_select, along the start tables: partials of as many tiles of jobs as returned.
-int launch_ranges(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, const sja_params *params, const int32_t *wait,
+int launch_ranges(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, int most_classes, const sja_params *params, const int32_t *wait,
                   const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active, int *tiles)
 {
-    const int J = ctx->n_jobs, chunk_bound = int(fit_chunk_bound(n_gaps, J));
+    const int J = ctx->n_jobs;
     const bool mixed = params->policy == SJA_POLICY_MIXED;
     const long long *atom_area = atom_area_of(ctx, L);
     const int64_t jobs_once = (J + kRangeThreads - 1) / kRangeThreads, chunks = (n_gaps + fit_chunk_len(n_gaps, J) - 1) / fit_chunk_len(n_gaps, J);
+    const int chunk_bound = int(chunks) + most_classes;         // (of a batch that is served; 16000 blocks that return at once take 27 us)
     int batches = 1;
     while (batches < kRangeBatches && jobs_once * chunks >= 2 * batches * int64_t(kRangeBlocks)) batches *= 2;
     *tiles = int((jobs_once + batches - 1) / batches);
     auto kern = atom_area ? (mixed ? k_range_select<true, true> : k_range_select<false, true>)
                           : (mixed ? k_range_select<true, false> : k_range_select<false, false>);
     hipLaunchKernelGGL(kern, dim3(unsigned((*tiles + 7) / 8 * 8) * unsigned(chunk_bound)), dim3(kRangeThreads), 0, st, J, n_gaps,
-                       chunk_bound, batches, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area,
+                       chunk_bound, batches, most_classes, to_dev(params), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), atom_area,
                        ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.chunk_begin), ws_ptr<int32_t>(ctx, L.chunk_end),
                        ws_ptr<int32_t>(ctx, L.chunk_class), ws_ptr<int32_t>(ctx, L.start_tab), ws_ptr<int32_t>(ctx, L.ncap_tab),
                        ws_ptr<int32_t>(ctx, L.gap_w), ws_ptr<int32_t>(ctx, L.gap_order), wait, sla_class, job_held, gap_active,
@@ -983,10 +999,10 @@ int launch_ranges(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps,
     return SJA_OK;
 }
 
-int launch_range_reduce(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, int job_tiles, int range_tiles, bool from_matrix,
+int launch_range_reduce(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, int job_tiles, int range_tiles, int most_classes, bool from_matrix,
                         int32_t *cand_job, int32_t *cand_cut, int64_t *cand_score)
 {
-    hipLaunchKernelGGL(k_range_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles, range_tiles, int(from_matrix),
+    hipLaunchKernelGGL(k_range_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles, range_tiles, most_classes, int(from_matrix),
                        ws_ptr<SelPartial>(ctx, L.sel_part), ws_ptr<int32_t>(ctx, L.plan), ws_ptr<int32_t>(ctx, L.gap_w),
                        ws_ptr<int32_t>(ctx, L.gap_c), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), ws_ptr<int2>(ctx, L.atom_db),
                        ws_ptr<int32_t>(ctx, L.n_atoms), cand_job, cand_cut, cand_score);
@@ -1039,15 +1055,15 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
         int rc = timed ? mark_kernel(ctx, st, false) : SJA_OK;
         if (rc != SJA_OK) return rc;
         const bool rise = keys_rise(ctx);
-        const bool floor = rise && by_floor(n_gaps, J, false);
+        const bool floor = rise && by_floor(n_gaps, J);
         if (starts && !floor && (rc = enqueue_starts(ctx, st, L)) != SJA_OK) return rc;
         if (rise && tabled != Tabled::No) {
             by_atoms = true;
             if (floor) {
-                args = floor_args(ctx, L, n_gaps, params, wait, sla_class, job_held);
+                args = floor_args(ctx, L, n_gaps, kAnyClasses, params, wait, sla_class, job_held);
                 rc = launch_floor(ctx, st, L, args, starts);
             } else {
-                rc = launch_ranges(ctx, st, L, n_gaps, params, wait, sla_class, job_held, gap_active, &range_tiles);
+                rc = launch_ranges(ctx, st, L, n_gaps, kAnyClasses, params, wait, sla_class, job_held, gap_active, &range_tiles);
             }
             if (rc != SJA_OK) return rc;
         }
@@ -1066,7 +1082,7 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
         if (timed && (rc = mark_kernel(ctx, st, true)) != SJA_OK) return rc;
     }
     if (by_atoms && range_tiles == 0) return launch_floor_reduce(ctx, st, L, args, job_tiles, false, gap_active, cand_job, cand_cut, cand_score);
-    if (by_atoms) return launch_range_reduce(ctx, st, L, n_gaps, job_tiles, range_tiles, false, cand_job, cand_cut, cand_score);
+    if (by_atoms) return launch_range_reduce(ctx, st, L, n_gaps, job_tiles, range_tiles, kAnyClasses, false, cand_job, cand_cut, cand_score);
     hipLaunchKernelGGL(k_fused_reduce, dim3((n_gaps + kReduceGaps - 1) / kReduceGaps), dim3(256), 0, st, n_gaps, job_tiles,
                        ws_ptr<SelPartial>(ctx, L.sel_part), ctx->seg_off, ws_ptr<int2>(ctx, L.atom_db), cand_job,
                        cand_cut, cand_score);
@@ -1520,22 +1536,22 @@ int sja_select(sja_ctx *ctx, void *stream, const sja_params *params, const int32
         return SJA_OK;
     }
     const int G = ctx->n_gaps, J = ctx->n_jobs, job_tiles = (J + kSelBlock - 1) / kSelBlock;
-    if (!keys_rise(ctx) || !select_by_atoms(G, J, atom_area_of(ctx, L) != nullptr))
+    const SelectForm form = select_form(G, J);
+    if (!keys_rise(ctx) || !form.by_atoms)
         return launch_select(ctx, st, params, wait, sla_class, job_held, gap_active, cand_job, cand_cut, cand_score);
-    // along the plan of the fit, without reading the matrix; along the matrix if the plan has no class tables
-    const bool floor = by_floor(G, J, true);
+    // along the plan of the fit, without reading the matrix; along the matrix if the plan has no class tables or too many classes
     FloorArgs args{};
     int range_tiles = 0;
-    if (floor) {
-        args = floor_args(ctx, L, G, params, wait, sla_class, job_held);
+    if (form.floor) {
+        args = floor_args(ctx, L, G, form.most_classes, params, wait, sla_class, job_held);
         rc = launch_floor(ctx, st, L, args, false);
     } else {
-        rc = launch_ranges(ctx, st, L, G, params, wait, sla_class, job_held, gap_active, &range_tiles);
+        rc = launch_ranges(ctx, st, L, G, form.most_classes, params, wait, sla_class, job_held, gap_active, &range_tiles);
     }
-    if (rc == SJA_OK) rc = launch_matrix_pass(ctx, st, L, params, wait, sla_class, job_held, gap_active, ws_ptr<int32_t>(ctx, L.plan), false);
+    if (rc == SJA_OK) rc = launch_matrix_pass(ctx, st, L, params, wait, sla_class, job_held, gap_active, form.most_classes, false);
     if (rc != SJA_OK) return rc;
-    return floor ? launch_floor_reduce(ctx, st, L, args, job_tiles, true, gap_active, cand_job, cand_cut, cand_score)
-                 : launch_range_reduce(ctx, st, L, G, job_tiles, range_tiles, true, cand_job, cand_cut, cand_score);
+    return form.floor ? launch_floor_reduce(ctx, st, L, args, job_tiles, true, gap_active, cand_job, cand_cut, cand_score)
+                      : launch_range_reduce(ctx, st, L, G, job_tiles, range_tiles, form.most_classes, true, cand_job, cand_cut, cand_score);
 }
 
 int sja_resolve(sja_ctx *ctx, void *stream, const sja_params *params, const int32_t *wait,

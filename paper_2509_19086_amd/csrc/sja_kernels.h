@@ -760,10 +760,10 @@ __global__ __launch_bounds__(256) void k_select_keys(
     int n_jobs, PolicyDev pol, const int64_t *__restrict__ seg_off, const int2 *__restrict__ atom_dp, const int2 *__restrict__ atom_db,
     const long long *__restrict__ atom_area, const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
     const uint8_t *__restrict__ sla_class, const int32_t *__restrict__ pre_dur, const int32_t *__restrict__ pre_peak,
-    const long long *__restrict__ pre_area, int dense, int per_wave, const int32_t *__restrict__ unless_tabled,
+    const long long *__restrict__ pre_area, int dense, int per_wave, int unless_classes, const int32_t *__restrict__ plan,
     unsigned long long *__restrict__ seg_key)
 {
-    if (unless_tabled && unless_tabled[kPlanTabled]) return;
+    if (plan && serves(plan, unless_classes)) return;
     const int lane = lane_id(), j0 = (blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave)) * per_wave;
     // what says which form a job takes, a lane each (no cut lies beyond a job's end; the first atom reports its own
     // boundary under the hysteresis rule, too)
@@ -807,7 +807,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_pass(
     int n_jobs, int n_gaps, int n_chunks, PolicyDev pol, const int64_t *__restrict__ seg_off,
     const unsigned long long *__restrict__ seg_key, const int32_t *__restrict__ cut, const int32_t *__restrict__ gap_order,
     const int32_t *__restrict__ wait, const uint8_t *__restrict__ sla_class,
-    const int32_t *__restrict__ job_held, const uint8_t *__restrict__ gap_active, const int32_t *__restrict__ unless_tabled,
+    const int32_t *__restrict__ job_held, const uint8_t *__restrict__ gap_active, int unless_classes, const int32_t *__restrict__ plan,
     SelPartial *__restrict__ part)
 {
     constexpr int WAVES = kSelBlock / kWave;
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_pass(
     __shared__ unsigned long long s_hi[WAVES][kSelGapChunk];
     __shared__ int s_job[WAVES][kSelGapChunk];
 
-    if (unless_tabled && unless_tabled[kPlanTabled]) return;
+    if (plan && serves(plan, unless_classes)) return;
     const int xcd = blockIdx.x & 7;
     const int k = blockIdx.x >> 3;
     const int job_tile = (k / n_chunks) * 8 + xcd;

@@ -125,3 +125,42 @@ def test_masks_and_windows(engine, oracle, windows, area):
         wl.W[::3] = -2**31
     held = np.where(rng.random(JOBS) < 0.4, 3, -1).astype(np.int32)
     check(engine, oracle, wl, (0, 1, 2, 3), held, (rng.random(GAPS) < 0.7).astype(np.uint8), area=area)
+
+
+# the lines of a select: classes that k_range_select serves (3 * classes^2 up to the gaps) and one more, then the matrix; the floor
+# for 16 classes and, from twice as many pairs on, for all; more than 64 capacities have no class tables
+@pytest.mark.parametrize("gaps,jobs,caps", [(3000, 45000, 31), (3000, 45000, 32), (5000, 26844, 8), (8192, 32768, 16), (8192, 32768, 17),
+                                            (16384, 32768, 64), (16384, 32768, 65)])
+def test_lines_of_a_select(engine, oracle, gaps, jobs, caps):
+    wl = make_workload("tiny", 4, n_gaps=gaps, n_jobs=jobs)
+    wl.C = np.linspace(2000, 40960, caps).astype(np.int32)[np.arange(gaps) % caps]
+    check(engine, oracle, wl, (0, 2, 3))
+
+
+# memory counted in small units: running peaks up to 2^31 - 1, capacities on both sides of 2^30, 9 * 2^27 and 15 * 2^27, whose
+# bucket of peaks is the last one; and the grants of eight rounds after either call, whose lists take the atoms that a gap
+# can reach from either's tables
+@pytest.mark.parametrize("caps", [(2**30 - 1, 2**30, 9 * 2**27 - 1, 9 * 2**27, 1500000000, 15 * 2**27), (9 * 2**27 + 5, 2**31 - 1)])
+def test_large_peaks(engine, oracle, caps):
+    import paper_2509_19086_amd as P
+    wl = make_workload("tiny", 11, n_gaps=GAPS, n_jobs=JOBS)
+    rng = np.random.default_rng(12)
+    wl.mem = np.minimum(2.0 ** (27 + 4 * rng.random(wl.n_segments)), 2**31 - 1).astype(np.int32)
+    edges = np.array([x + d for x in (2**30, 9 * 2**27, 15 * 2**27) for d in (-1, 0, 1)] + [2**31 - 1], dtype=np.int32)
+    some = rng.integers(0, wl.n_segments, size=wl.n_segments // 20)
+    wl.mem[some] = edges[rng.integers(0, len(edges), size=len(some))]
+    wl.C = np.array(caps, dtype=np.int32)[rng.integers(0, len(caps), size=GAPS)]
+    wl.wait = (wl.wait % 1000).astype(np.int32)         # a score stays below 2^62
+    check(engine, oracle, wl, (0, 3))
+    engine.sja_set_score(0)
+    t = P.DeviceTick(engine, wl, want_bits=False)
+    par = P.Params.make(3, wl.wait_scale, wl.sla_weight, wl.class0_override, 8)
+    t.prepare()
+    grants = []
+    for call in (lambda: t.fit_select(par), t.fit):
+        call()
+        t.resolve(par)
+        grants.append([x.cpu().numpy() for x in (t.grant_job, t.grant_cut, t.grant_score, t.job_gap, t.rounds)])
+    assert (grants[0][0] >= 0).sum() > 1000
+    for x, y in zip(*grants):
+        np.testing.assert_array_equal(x, y)

@@ -1,6 +1,6 @@
-"""sja_select by atoms (k_floor.h, k_range_select) along the plan of the fit: batches on both sides of its lines, at the
-edges of its blocks of jobs and of its classes, with equal keys and masks, each select after a resolve of the one before,
-against the oracle; one class more than there are tables for goes along the matrix."""
+"""sja_select: along the matrix up to 2^27 pairs, at the edges of blocks of jobs and of classes, with equal keys and masks,
+each select after a resolve of the one before, against the oracle; larger batches along the chunks of the plan of the fit
+(k_range_select), fit -> select likewise (tests/test_gpu_floor.py has the form of the largest)."""
 import numpy as np
 import pytest
 
@@ -74,8 +74,8 @@ def test_masks(engine, oracle, held_share, on_share):
     check(engine, oracle, wl, (1, 3), held, (rng.random(wl.n_gaps) < on_share).astype(np.uint8))
 
 
-# batches large enough for the floor under the keys (k_floor.h), on either side of its line, some gaps of each against the
-# oracle: a gap's best reply does not depend on the other gaps
+# about 2^27 pairs, from which on a select goes along the chunks, some gaps of each against the oracle: a gap's best reply does
+# not depend on the other gaps
 @pytest.mark.parametrize("name,gaps,jobs,caps", [("stress", 2100, 65600, 0), ("large", 22000, 6144, 0), ("large", 22000, 6143, 0),
                                                  ("medium", 8300, 16400, 1), ("medium", 8300, 16400, 64), ("medium", 8300, 16400, 65)])
 def test_large(engine, oracle, name, gaps, jobs, caps):
@@ -96,34 +96,3 @@ def test_large(engine, oracle, name, gaps, jobs, caps):
             call()
             for got, x in zip((t.cand_job, t.cand_cut, t.cand_score), want):
                 np.testing.assert_array_equal(got.cpu().numpy()[rows], x)
-
-
-# memory counted in small units: running peaks up to 2^31 - 1, capacities on both sides of 2^30, 9 * 2^27 and 15 * 2^27, whose
-# bucket of peaks is the last one.  Every gap's candidate and the grants of eight rounds on top of them.
-@pytest.mark.parametrize("caps", [(2**30 - 1, 2**30, 9 * 2**27 - 1, 9 * 2**27, 1500000000, 15 * 2**27), (9 * 2**27 + 5, 2**31 - 1)])
-def test_large_peaks(engine, oracle, caps):
-    import paper_2509_19086_amd as P
-    wl = make_workload("tiny", 11, n_gaps=22000, n_jobs=6144)
-    rng = np.random.default_rng(12)
-    wl.mem = np.minimum(2.0 ** (27 + 4 * rng.random(wl.n_segments)), 2**31 - 1).astype(np.int32)
-    edges = np.array([x + d for x in (2**30, 9 * 2**27, 15 * 2**27) for d in (-1, 0, 1)] + [2**31 - 1], dtype=np.int32)
-    some = rng.integers(0, wl.n_segments, size=wl.n_segments // 20)
-    wl.mem[some] = edges[rng.integers(0, len(edges), size=len(some))]
-    wl.C = np.array(caps, dtype=np.int32)[rng.integers(0, len(caps), size=wl.n_gaps)]
-    wl.wait = (wl.wait % 1000).astype(np.int32)         # a score stays below 2^62
-    t = P.DeviceTick(engine, wl, want_cut=False)
-    t.prepare()
-    pd, pp, _ = oracle.prepare(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress)
-    cut, _ = oracle.fit(wl.seg_off, wl.dur, wl.mem, wl.safe, wl.progress, wl.W, wl.C, False)
-    for policy in (0, 3):
-        args = (policy, wl.wait_scale, wl.sla_weight, wl.class0_override, 8)
-        par, opar = P.Params.make(*args), oracle.Params.make(*args)
-        t.fit_select(par)
-        want = oracle.select(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
-        for got, x in zip((t.cand_job, t.cand_cut, t.cand_score), want):
-            np.testing.assert_array_equal(got.cpu().numpy(), x)
-        t.resolve(par)
-        want = oracle.resolve(cut, wl.seg_off, pd, pp, opar, wl.wait, wl.sla_class)
-        for got, x in zip((t.grant_job, t.grant_cut, t.grant_score, t.job_gap), want[:4]):
-            np.testing.assert_array_equal(got.cpu().numpy(), x)
-        assert t.rounds.cpu().tolist() == [want[4], want[5]]
