@@ -450,7 +450,7 @@ __device__ __forceinline__ void sets_join(const SetsArgs &A, SetsShared<BLOCKS> 
 // How the space is shared out among the sets of a batch: per set `room` words for up to `most` jobs (twice an odd
 // number: banks), and up to `heads` lowest gaps, of which the r-th of set i is at i + r * width.
 struct SetsShape { int room, most, width, heads; };
-__device__ __forceinline__ SetsShape sets_shape(int n_sets)
+constexpr SetsShape sets_shape(int n_sets)
 {
     if (n_sets <= 16) return {262, kSetsMostJobs, 16, 253};
     if (n_sets <= 32) return {262, kSetsMostJobs, 32, 191};
@@ -458,6 +458,9 @@ __device__ __forceinline__ SetsShape sets_shape(int n_sets)
     if (n_sets <= 2 * kWave) return {138, 126, 128, 47};
     return {70, 58, kSetsMost, 23};
 }
+// (every round passes a job of each set: a batch ends by its jobs before it ends by its bound, and a round fits a claim's word)
+static_assert(sets_shape(1).most < kSetsMostRounds && sets_shape(17).most < kSetsMostRounds && sets_shape(33).most < kSetsMostRounds &&
+              sets_shape(kWave + 1).most < kSetsMostRounds && sets_shape(kSetsMost).most < kSetsMostRounds && kSetsMostRounds + 1 < 1 << 12, "rounds of a batch");
 static_assert(kWave * 262 <= kSetsSeq && 2 * kWave * 138 <= kSetsSeq && kSetsMost * 70 <= kSetsSeq, "jobs at hand");
 // (behind the last gap a word that says whether there are more, and one that is read and not looked at)
 static_assert((253 + 2) * 16 <= kSetsHeads + kSetsMost && (191 + 2) * 32 <= kSetsHeads + kSetsMost && (95 + 2) * 64 <= kSetsHeads + kSetsMost &&
@@ -676,9 +679,11 @@ __device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n
                 none[i] = out[i] == 0 && max(max(w[i][0], w[i][1]), max(w[i][2], w[i][3])) < now;
             }
             if (q > last) {
-                if (lost) S.lost = 1;
-                why = kSetsAtCap;
-                break;
+                if (q > cap - before) {
+                    if (lost) S.lost = 1;
+                    why = kSetsAtCap;
+                }
+                break;          // (at the batch's own bound it is a pause like any other)
             }
             bool cannot = false, dry = false, some = false;
 #pragma unroll
