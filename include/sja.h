@@ -409,9 +409,12 @@ int sja_validate(sja_ctx *ctx, void *stream, int32_t n_jobs, int64_t n_segments,
 /*
  * Measurement aid for benchmarks (callers that report the pair-evaluation
  * kernel's own duration rather than the whole call's).  With timing enabled,
- * sja_fit brackets its pair-evaluation kernel with HIP events on `stream`;
- * sja_last_fit_kernel_ms waits for that kernel and stores its duration in
- * *ms_host (host pointer).  SJA_ERR_STATE if no timed sja_fit has run.
+ * sja_fit brackets its pair-evaluation kernel with HIP events on `stream`, and
+ * sja_fit_select the kernels that look for the best replies: behind the order of
+ * the gaps, the plan and the tables of where chunks start, up to the last
+ * arg-max over what these kernels left (small batches: that included).
+ * sja_last_fit_kernel_ms waits for them and stores their duration in
+ * *ms_host (host pointer).  SJA_ERR_STATE if no timed call has run.
  */
 int sja_enable_timing(sja_ctx *ctx, int on);
 int sja_last_fit_kernel_ms(sja_ctx *ctx, float *ms_host);

@@ -1052,11 +1052,11 @@ int launch_fused(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_gaps, 
                                        : k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, false, true>)
                               : (mixed ? k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, true, false>
                                        : k_fit_select<kFusedBlock, kFusedWindow, kFusedPeriod, false, false>);
-        int rc = timed ? mark_kernel(ctx, st, false) : SJA_OK;
-        if (rc != SJA_OK) return rc;
         const bool rise = keys_rise(ctx);
         const bool floor = rise && by_floor(n_gaps, J);
-        if (starts && !floor && (rc = enqueue_starts(ctx, st, L)) != SJA_OK) return rc;
+        int rc = starts && !floor ? enqueue_starts(ctx, st, L) : SJA_OK;
+        if (rc == SJA_OK && timed) rc = mark_kernel(ctx, st, false);        // (from here on pairs are evaluated)
+        if (rc != SJA_OK) return rc;
         if (rise && tabled != Tabled::No) {
             by_atoms = true;
             if (floor) {
