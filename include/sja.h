@@ -285,6 +285,10 @@ int sja_fit(sja_ctx *ctx, void *stream, int32_t n_gaps, const int32_t *W, const 
  *   cand_job[g]   winning job id, or -1 if no candidate
  *   cand_cut[g]   its cut (-1 if none)
  *   cand_score[g] its score term (0 if none)
+ * What counts are the replies that sja_fit computed: large batches are served
+ * without reading `cut`, so that a reply struck out of the matrix by the caller
+ * is left out for some sizes and not for others.  To leave out jobs or gaps, use
+ * job_held and gap_active.
  */
 int sja_select(sja_ctx *ctx, void *stream, const sja_params *params, const int32_t *wait,
                const uint8_t *sla_class, const int32_t *job_held, const uint8_t *gap_active,
