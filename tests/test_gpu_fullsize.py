@@ -13,6 +13,45 @@ from gen import make_workload
 pytestmark = [pytest.mark.gpu, pytest.mark.slow]
 
 
+def best_by_matrix(t, wl, prefix_F):
+    """Every gap's best reply, by an arg-max in plain torch over the cut matrix that sja_fit left: (job, cut, score).
+    prefix_F [n_segments] int64 (numpy): F of a job's subjob up to each of its segments."""
+    import torch
+    dev = t.cut.device
+    up = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev)
+    F_of, first = up(prefix_F.astype(np.int64)), t.seg_off[:-1] - 1
+    wait, cls = up(wl.wait.astype(np.int64)), up(wl.sla_class.astype(np.int64))
+    one, none = torch.ones_like(wait), torch.zeros_like(wait)
+    mult = {0: one, 1: wl.wait_scale + wait, 2: up(np.asarray(wl.sla_weight, dtype=np.int64))[cls], 3: wl.wait_scale + wait}[wl.policy]
+    tier = {0: none, 1: none, 2: ((cls == 0) & bool(wl.class0_override)).to(torch.int64), 3: 2 - cls}[wl.policy]
+    jobs = torch.arange(t.J, dtype=torch.int64, device=dev)
+    out = [torch.empty(t.G, dtype=x, device=dev) for x in (torch.int32, torch.int32, torch.int64)]
+    step = max(1, (1 << 24) // t.J)
+    for g in range(0, t.G, step):
+        cut = t.cut[g:g + step]
+        fits = cut > 0
+        F = F_of[first + cut.clamp(min=1)]
+        score = F * mult
+        for of in (tier.expand_as(F), score) + ((F,) if wl.policy == 3 else ()):        # a key's parts, then the lowest job
+            most = torch.where(fits, of, -1).amax(1, keepdim=True)
+            fits = fits & (of == most)
+        job = torch.where(fits, jobs, t.J).amin(1)
+        some = job < t.J
+        at = job.clamp(max=t.J - 1)[:, None]
+        out[0][g:g + step] = torch.where(some, job, -1).to(torch.int32)
+        out[1][g:g + step] = torch.where(some, cut.gather(1, at)[:, 0], -1)
+        out[2][g:g + step] = torch.where(some, score.gather(1, at)[:, 0], 0)
+    return out
+
+
+def same_candidates(t, best):
+    import torch
+    torch.cuda.synchronize()
+    for a, b in zip(best, (t.cand_job, t.cand_cut, t.cand_score)):
+        assert torch.equal(a, b)
+        b.fill_(-5)
+
+
 def _check_full_size(oracle, name, n_pairs, n_rows, max_rounds, until_stable=False):
     import torch
     import paper_2509_19086_amd as P
@@ -93,15 +132,11 @@ def _check_full_size(oracle, name, n_pairs, n_rows, max_rounds, until_stable=Fal
                 assert (rj == -1).all()
         return gj, gc, gs, jg, rounds, stable
 
-    # the fused call reports the same candidates as sja_select after sja_fit, for every gap
-    sel = (t.cand_job.clone(), t.cand_cut.clone(), t.cand_score.clone())
-    for out in (t.cand_job, t.cand_cut, t.cand_score):
-        out.fill_(-5)
+    # the candidates of sja_select after sja_fit and of the fused call, for every gap
+    best = best_by_matrix(t, wl, pd * pp)
+    same_candidates(t, best)
     t.fit_select(par)
-    torch.cuda.synchronize()
-    for a, b in zip(sel, (t.cand_job, t.cand_cut, t.cand_score)):
-        assert torch.equal(a, b)
-    np.testing.assert_array_equal(t.cand_job[rows_t].cpu().numpy(), cj)
+    same_candidates(t, best)
     t.fit()                                   # the cut matrix again, for the matrix-scanning rounds below
     torch.cuda.synchronize()
 
@@ -237,11 +272,10 @@ def test_stress_limits_full_size(oracle):
     np.testing.assert_array_equal(t.cand_job[rows_t].cpu().numpy(), cj)
     np.testing.assert_array_equal(t.cand_score[rows_t].cpu().numpy(), cs)
 
-    sel = (t.cand_job.clone(), t.cand_cut.clone(), t.cand_score.clone())
+    best = best_by_matrix(t, wl, pd * pp)
+    same_candidates(t, best)
     t.fit_select(par)
-    torch.cuda.synchronize()
-    for a, b in zip(sel, (t.cand_job, t.cand_cut, t.cand_score)):
-        assert torch.equal(a, b)
+    same_candidates(t, best)
 
     t.resolve(par)
     gj = t.grant_job.cpu().numpy(); gc = t.grant_cut.cpu().numpy(); jg = t.job_gap.cpu().numpy()
@@ -330,7 +364,8 @@ def test_beyond_stress_64bit_indexing(oracle):
     np.testing.assert_array_equal(t.cand_cut[rows_t].cpu().numpy(), cc)
     np.testing.assert_array_equal(t.cand_score[rows_t].cpu().numpy(), cs)
 
-    sel = (t.cand_job.clone(), t.cand_cut.clone(), t.cand_score.clone())
+    best = best_by_matrix(t, wl, pd * pp)
+    same_candidates(t, best)
     outs = []
     try:
         for mode in (0, 1):
@@ -348,9 +383,7 @@ def test_beyond_stress_64bit_indexing(oracle):
                                   wl.progress, wl.W, wl.C)
     np.testing.assert_array_equal(gc[granted], ocut)
     t.fit_select(par)
-    torch.cuda.synchronize()
-    for a, b in zip(sel, (t.cand_job, t.cand_cut, t.cand_score)):
-        assert torch.equal(a, b)
+    same_candidates(t, best)
 
 
 def test_stress_area_score_full_size(oracle):
@@ -380,7 +413,8 @@ def test_stress_area_score_full_size(oracle):
     np.testing.assert_array_equal(t.cand_job[rows_t].cpu().numpy(), cj)
     np.testing.assert_array_equal(t.cand_cut[rows_t].cpu().numpy(), cc)
     np.testing.assert_array_equal(t.cand_score[rows_t].cpu().numpy(), cs)
-    sel = (t.cand_job.clone(), t.cand_cut.clone(), t.cand_score.clone())
+    best = best_by_matrix(t, wl, pa)
+    same_candidates(t, best)
     t.resolve(par)
     gj = t.grant_job.cpu().numpy(); gc = t.grant_cut.cpu().numpy(); gs = t.grant_score.cpu().numpy()
     granted = np.nonzero(gj >= 0)[0]
@@ -392,9 +426,7 @@ def test_stress_area_score_full_size(oracle):
     np.testing.assert_array_equal(gs[granted], F * (wl.wait_scale + wl.wait[gj[granted]].astype(np.int64)))
     assert gj[0] == cj[0] and gs[0] == cs[0]
     t.fit_select(par)
-    torch.cuda.synchronize()
-    for a, b in zip(sel, (t.cand_job, t.cand_cut, t.cand_score)):
-        assert torch.equal(a, b)
+    same_candidates(t, best)
 
 
 def test_stress_hysteresis_full_size(oracle):
@@ -438,11 +470,10 @@ def test_stress_hysteresis_full_size(oracle):
     np.testing.assert_array_equal(t.cand_cut[rows_t].cpu().numpy(), cc)
     np.testing.assert_array_equal(t.cand_score[rows_t].cpu().numpy(), cs)
 
-    sel = (t.cand_job.clone(), t.cand_cut.clone(), t.cand_score.clone())
+    best = best_by_matrix(t, wl, pd * pp)
+    same_candidates(t, best)
     t.fit_select(par)
-    torch.cuda.synchronize()
-    for a, b in zip(sel, (t.cand_job, t.cand_cut, t.cand_score)):
-        assert torch.equal(a, b)
+    same_candidates(t, best)
 
     t.resolve(par)
     gj = t.grant_job.cpu().numpy(); gc = t.grant_cut.cpu().numpy(); gs = t.grant_score.cpu().numpy()
