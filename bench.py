@@ -31,16 +31,20 @@ def algorithmic_fit_bytes(wl, n_atoms_total):
 def secondary_rates(wl, n_atoms_total, call_ms, rounds):
     """Algorithmic bytes and rates of the other calls (whole calls, HIP events): prepare moves 9 B in
     and 12 B out per segment after the progress point plus 16 B per atom and 20 B per job; select
-    reads the 8 B of every atom (below 2^24 pairs the 4-byte cut of every pair) and writes 16 B per gap;
-    the rounds of resolve are bound by latency, so they are reported per round."""
+    reads the 4-byte cut of every pair below 2^27 pairs and the 8 B of every atom where the floor under the keys
+    serves it, and writes 16 B per gap (between the two it looks at the ends of jobs and at few atoms: no byte
+    rate); the rounds of resolve are bound by latency, so they are reported per round."""
     import numpy as np
     G, J = wl.n_gaps, wl.n_jobs
     remaining = int((np.diff(wl.seg_off) - wl.progress).clip(min=0).sum())
     out = {}
-    for name, nbytes in (("prepare", 21 * remaining + 16 * n_atoms_total + 20 * J), ("select", (8 * n_atoms_total if G * J >= 1 << 24 else 4 * G * J) + 16 * G)):
-        gbs = nbytes / (call_ms[name] * 1e-3) / 1e9
-        out[name] = {"algorithmic_bytes": nbytes, "achieved_GBs": gbs, "frac": gbs / HBM_PEAK_GBS,
-                     "evals_per_s": G * J / (call_ms[name] * 1e-3)}
+    floor = J >= 6144 and (G * J >= 1 << 29 or (G * J >= 1 << 28 and G >= 8192))
+    select_bytes = 8 * n_atoms_total + 16 * G if floor else 4 * G * J + 16 * G if G * J < 1 << 27 else None
+    for name, nbytes in (("prepare", 21 * remaining + 16 * n_atoms_total + 20 * J), ("select", select_bytes)):
+        out[name] = {"evals_per_s": G * J / (call_ms[name] * 1e-3)}
+        if nbytes is not None:
+            gbs = nbytes / (call_ms[name] * 1e-3) / 1e9
+            out[name].update(algorithmic_bytes=nbytes, achieved_GBs=gbs, frac=gbs / HBM_PEAK_GBS)
     out["resolve"] = {"us_per_round": 1e3 * call_ms["resolve"] / max(rounds, 1), "rounds": rounds,
                       "evals_per_s": G * J / (call_ms["resolve"] * 1e-3)}
     return out
