@@ -312,6 +312,12 @@ __device__ __forceinline__ unsigned long long pair_digest(unsigned long long hi)
     const unsigned long long mantissa = e ? score << (64 - e) : 0ull;
     return (key >> 62) << 50 | (unsigned long long)e << 44 | mantissa >> 20;
 }
+// Whether two keys of this digest are the same: a score from 2 up to 2^45 - 1 is in it whole.
+__device__ __forceinline__ bool pair_digest_is_key(unsigned long long digest)
+{
+    const uint32_t e = uint32_t(digest >> 44) & 63u;
+    return e - 1u < 44u;
+}
 
 // The jobs that fit gap blockIdx.x in the order of their keys, as many as the rounds can ask for: a gap passes
 // only jobs that other gaps hold, so it needs no more of them than there are gaps (`most`).  A job is one word, its key's
@@ -480,6 +486,7 @@ __global__ __launch_bounds__(THREADS) void k_order_pairs(int n_gaps, int n_jobs,
     // neighbours of one digest: the jobs are in order, the keys may not be
     for (int i = tid; i + 1 < n; i += THREADS) {
         if (s_item[i] >> 12 != s_item[i + 1] >> 12) continue;
+        if (!MIXED && pair_digest_is_key(~(s_item[i] >> 12))) continue;
         const int job[2] = {int(s_item[i] & 0xfffu), int(s_item[i + 1] & 0xfffu)};
         unsigned long long hi[2], lo[2];
         keys(std::integral_constant<int, 2>{}, job, hi, lo);

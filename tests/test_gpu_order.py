@@ -65,6 +65,31 @@ def test_equal_digests(engine, oracle, gaps, jobs):
     check(engine, oracle, wl, (1, 3))
 
 
+# scores that differ by less than the bits behind a digest's would tell, just inside and just outside of what it holds whole:
+# 0 to 2 (which share a leading digit, or have none), and 2^44 + 2^24 + 0, 3 and 4, half of that, twice that
+@pytest.mark.parametrize("gaps,jobs", [(150, 4000), (20, 100)])
+@pytest.mark.parametrize("e", [0, 1, 43, 44, 45])
+def test_scores_at_the_digests_edges(engine, oracle, gaps, jobs, e):
+    wl = make_workload("tiny", 1, n_gaps=gaps, n_jobs=jobs)
+    rng = np.random.default_rng(e)
+    wl.seg_off = np.arange(jobs + 1, dtype=np.int64)
+    wl.dur = np.ones(jobs, dtype=np.int32)
+    wl.safe = np.ones(jobs, dtype=np.uint8)
+    wl.progress = np.zeros(jobs, dtype=np.int32)
+    if e < 2:
+        wl.mem = rng.integers(0, 2 + 2 * e, size=jobs).astype(np.int32)
+        mult = np.where(rng.random(jobs) < 0.5, 1, 2)
+    else:
+        at = rng.integers(0, 3, size=jobs)
+        wl.mem = (2**22 + at).astype(np.int32)
+        mult = 2**(e - 22) + ((4 - at) << (e - 44) if e > 44 else (4 - at) >> (44 - e))
+    wl.wait_scale, wl.wait = 1, (mult - 1).astype(np.int32)
+    wl.sla_class = rng.integers(0, 3, size=jobs).astype(np.uint8)
+    wl.W[:] = 5
+    wl.C[:] = 2**22 + np.arange(gaps) % 3
+    check(engine, oracle, wl, (0, 1, 3))
+
+
 # one list for all gaps, so that every round passes an entry of each: one, two and more times the 64 that are brought to LDS
 # together, up to all of it, lists that fit LDS and lists that do not
 @pytest.mark.parametrize("gaps,jobs", [(1, 5), (63, 64), (65, 65), (72, 300), (128, 127), (136, 700), (256, 1024), (257, 1024), (333, 90), (1000, 70), (1024, 64)])
