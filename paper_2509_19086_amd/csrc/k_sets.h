@@ -70,8 +70,10 @@ constexpr int kSetsMostSteps = 64;      // chunks a wave reads for one piece bef
 // jobs that the gaps of a set have in common, at least: at first, and at most (k_sets_one, and with more list blocks,
 // where more in common makes more sets: 32768 gaps x 65536 jobs 43.0 / 42.0 / 41.4 / 42.3 / 43.0 ms for 16 / 24 / 32 / 48 / 64)
 constexpr int kSetsLeastFirst = 16, kSetsLeast = 64, kSetsLeastMany = 32;
-constexpr int kSetsShort = 8, kSetsPatience = 3;       // batches of so few rounds are short ones; more of those than others by so many end it
-constexpr int kSetsState = 3;           // out[]: k_grant_solo's words, and this one between launches: least << 8 | strain
+// batches of so few rounds are short ones (a batch takes as long as so many by k_grant_solo, or in turn as so many launched
+// ones); more of those than others by so many end it
+constexpr int kSetsShort = 8, kSetsShortMany = 5, kSetsPatience = 3;
+constexpr int kSetsState = 3;           // out[]: k_grant_solo's words, and this one between launches: jobs << 16 | least << 8 | strain
 enum { kSetsRunning = 4, kSetsLeft = 5 };       // out[kSoloDone]: between launches; on with k_grant_solo
 enum { kSetsPause = 0, kSetsNoClaim = 1, kSetsAtCap = 2 };          // why the rounds of a batch stopped
 
@@ -258,9 +260,9 @@ struct SetsSearch {
 };
 
 // The pieces of list block u.  A lane's records lie behind a higher lane's, but for 63 of equal keys.
-// LISTS: with the jobs of each, twice as many as its lanes are to have in common.
+// LISTS: with the jobs of each, twice as many as its lanes are to have in common, or `jobs` if those are more.
 template <bool LISTS>
-__device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, int least, const uint32_t *s_held)
+__device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, int least, int jobs, const uint32_t *s_held)
 {
     SetsBlock &B = A.block[u];
     unsigned long long rest = B.open;
@@ -277,7 +279,7 @@ __device__ __forceinline__ void sets_form(const SetsArgs &A, int u, int lane, in
         const int bottom = __ffsll((long long)rest) - 1;
         SetsSearch find;
         find.start(A, s_held, first ? at : max(at - 63, __builtin_amdgcn_readfirstlane(A.state[u * kWave + top].x)), end, top, lane);
-        const int room = LISTS ? A.list_jobs : 0, want = LISTS ? min(2 * least, room) : least;
+        const int room = LISTS ? A.list_jobs : 0, want = LISTS ? min(max(2 * least, jobs), room) : least;
         const size_t list = LISTS && n_pieces < kSetsPieces ? size_t(u * kSetsPieces + n_pieces) * room : 0;
         int n = 0, hit = -1, steps = 0, most = 0;       // most: of the first `least` jobs
         if (!find.over()) {
@@ -358,6 +360,7 @@ struct SetsShared {
     int8_t pieces[BLOCKS];
     uint16_t lo[kSetsMost], hi[kSetsMost], source[kSetsMost], cls[kSetsMost];    // first and last place of a set, the piece whose jobs it has, its class
     uint32_t set[kSetsMost];                            // jobs at hand, bit 16: no more jobs
+    int most, through;                                  // jobs that a set has at hand at most; one that had so many has passed them all
     int first[kMaxClasses + 1], gaps_at[kMaxClasses + 1];       // first list block of a class, its first position,
     int low[kMaxClasses];                               // and where its lowest open gap lies among its gaps
     uint32_t found[kSetsWaves][kWave];
@@ -613,7 +616,7 @@ __device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> 
 // then begun anew; the next jobs are shifted in from eight that are there, instead of being fetched once it is known
 // how many were passed; a lane without a set goes on with words that change nothing.  0.40 -> 0.21 us a round of up
 // to 64 sets.
-template <int N, int BLOCKS>
+template <bool LISTS, int N, int BLOCKS>
 __device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n_sets, const SetsShape &shape, int before, int cap)
 {
     auto claim_at = [&](uint32_t off) -> uint32_t & { return *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(S.jobs.claim) + off); };
@@ -685,7 +688,7 @@ __device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n
                 }
                 break;          // (at the batch's own bound it is a pause like any other)
             }
-            bool cannot = false, dry = false, some = false;
+            bool cannot = false, dry = false, some = false, through = false;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const int id = min(lane + i * kWave, n_sets - 1);
@@ -698,9 +701,13 @@ __device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n
                 }
                 cannot |= none[i] ? !(info >> 16) : head[i] == kSetsMoreGaps;
                 dry |= none[i];
+                if (LISTS) through |= none[i] && !(info >> 16) && int(info & 255u) >= S.most;
             }
             if (__ballot(go_on)) continue;
-            if (__ballot(cannot)) break;         // round q cannot be played
+            if (__ballot(cannot)) {              // round q cannot be played
+                if (LISTS && __ballot(through)) S.through = 1;
+                break;
+            }
             if (__ballot(dry)) S.closed = q;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -760,14 +767,15 @@ __device__ __forceinline__ void sets_classes(const SetsArgs &A, SetsShared<BLOCK
 }
 
 // A batch: the pieces are joined, its rounds played, and the grants written down.  held: the bitmap that sets_form
-// reads.  Returns whether the process has ended (out says how), and how many rounds were played; -1: too much
-// work, none was.
+// reads.  Returns whether the process has ended (out says how), how many rounds were played (-1: too much
+// work, none was) and by how many sets.  LISTS: jobs is how many a set is to have at hand at least, and becomes that of
+// the next batch.
 template <bool LISTS, int BLOCKS>
-__device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS> &S, int done, int least, uint32_t *held, int &played)
+__device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS> &S, int done, int least, uint32_t *held, int &played, int &sets, int &jobs)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_classes = A.plan[kPlanClasses];
-    if (tid == 0) S.n = S.over = S.closed = S.lost = 0;
+    if (tid == 0) S.n = S.over = S.closed = S.lost = S.through = 0;
     __syncthreads();
     for (int u = tid; u < A.n_lb; u += kSetsThreads) {
         const unsigned long long open = A.block[u].open;
@@ -783,24 +791,29 @@ __device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS>
     played = -1;
     for (int c = wave; c < n_classes; c += kSetsWaves) sets_join(A, S, c, lane);
     __syncthreads();
-    const int n_sets = S.n;
+    const int n_sets = sets = S.n;
     if (n_sets > kSetsMost) return false;
     const SetsShape shape = sets_shape(n_sets);
-    // where there are many sets the batch ends by one of them that has hardly more jobs than they are to have in common
-    const int most = n_sets <= kSetsWaves ? shape.most : min(shape.most, 3 * least / 2);
+    // Where there are many sets the batch ends by one of them that has hardly more jobs than they are to have in common.
+    // Not where the sets take each other's jobs: a round passes as many as there are sets then, the batch ends by
+    // the jobs at hand after a few, and the next one would have no more of them.  So twice as many if that was its end: 2379
+    // gaps of 40 capacities x 3077 jobs 2430 -> 1700 us a resolve, 3446 of 64 x 3420 2570 -> 1890; 32768 x 65536 the same.
+    const int most = n_sets <= kSetsWaves ? shape.most : min(shape.most, LISTS ? max(3 * least / 2, jobs) : 3 * least / 2);
+    if (LISTS && tid == 0) S.most = min(most, min(max(2 * least, jobs), A.list_jobs));
     for (int id = wave; id < n_sets; id += kSetsWaves) sets_fill<LISTS>(A, S, id, lane, wave, shape, most, held);
     __syncthreads();
     const bool over = S.over != 0;
     if (!over && wave == 0) {
         if (n_sets == 0) {              // nobody claims anything
             if (lane == 0) { S.end = 1; S.why = done < A.cap ? kSetsNoClaim : kSetsAtCap; }
-        } else if (n_sets <= kWave) sets_play<1>(S, lane, n_sets, shape, done, A.cap);
-        else if (n_sets <= 2 * kWave) sets_play<2>(S, lane, n_sets, shape, done, A.cap);
-        else sets_play<4>(S, lane, n_sets, shape, done, A.cap);
+        } else if (n_sets <= kWave) sets_play<LISTS, 1>(S, lane, n_sets, shape, done, A.cap);
+        else if (n_sets <= 2 * kWave) sets_play<LISTS, 2>(S, lane, n_sets, shape, done, A.cap);
+        else sets_play<LISTS, 4>(S, lane, n_sets, shape, done, A.cap);
     }
     __syncthreads();
     // the rounds played: not one that could not be; one without any claim if it found out that a set has no job left
     const int why = S.why;
+    if (LISTS) jobs = S.through ? min(2 * S.most, kSetsListed) : 3 * jobs / 4;
     played = over ? -1 : why == kSetsNoClaim && S.closed == S.end ? S.end : S.end - 1;
     for (int k = tid; k < kSetsSlots + 2; k += kSetsThreads) {
         const uint32_t j = k < kSetsSlots ? S.jobs.job[k] : kSetsNoJob, claim = S.jobs.claim[k];
@@ -822,13 +835,13 @@ __device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS>
     return true;
 }
 
-// After a batch of `played` rounds: the jobs the gaps of a set are to have in common in the next one, and whether
-// to go on.
-__device__ __forceinline__ bool sets_go_on(int played, int most, int &least, int &strain)
+// After a batch of `played` rounds, a short one if they are up to `few`: the jobs the gaps of a set are to have in common in
+// the next one, and whether to go on.
+__device__ __forceinline__ bool sets_go_on(int played, int most, int few, int &least, int &strain)
 {
     if (played < 0) return false;
     least = min(max(2 * played, kSetsLeastFirst), most);
-    strain = max(strain + (played <= kSetsShort ? 1 : -1), 0);
+    strain = max(strain + (played <= few ? 1 : -1), 0);
     return strain < kSetsPatience;
 }
 
@@ -858,15 +871,20 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_one(SetsArgs A)
     for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_open(A, u, lane);
     __syncthreads();
     if (A.build) sets_by_class(A.n_gaps, A.plan[kPlanClasses], A.class_begin, S.first, A.place_of, A.by_class, reinterpret_cast<int(*)[kMaxClasses]>(&S.found[0][0]));
-    int done = A.out[kSoloRounds], least = kSetsLeastFirst, strain = 0, played = 0;
+    const int begun = A.out[kSoloRounds];
+    int done = begun, least = kSetsLeastFirst, strain = 0, played = 0, sets = 0, jobs = 0;
     for (;;) {
         __syncthreads();
-        for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_form<false>(A, u, lane, least, s_held);
+        for (int u = wave; u < A.n_lb; u += kSetsWaves) sets_form<false>(A, u, lane, least, 0, s_held);
         __syncthreads();
-        const bool ended = sets_batch<false>(A, S, done, least, s_held, played);
+        const bool ended = sets_batch<false>(A, S, done, least, s_held, played, sets, jobs);
+        const bool first = done == begun;
         done += max(played, 0);
         if (ended) return;
-        if (!sets_go_on(played, kSetsLeast, least, strain)) break;
+        // Begun in vain: many sets, whose batches take long, and which have no jobs for themselves (2328 gaps x 1074 jobs, 37
+        // sets, four rounds a batch: 590 us a resolve with two more of them, 525 so, 480 with no batch at all)
+        if (first && 6 * played < sets) break;
+        if (!sets_go_on(played, kSetsLeast, kSetsShort, least, strain)) break;
     }
     if (tid == 0) {
         A.out[kSoloDone] = kSetsLeft; A.out[kSoloRounds] = done; A.out[kSoloStable] = 0;
@@ -903,15 +921,16 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_begin(SetsArgs A)
 __global__ __launch_bounds__(kSetsFormThreads) void k_sets_form(SetsArgs A)
 {
     __shared__ uint4 s_held[kHeldMaxWords / 4];
-    int running = A.out[kSoloDone], least = A.out[kSetsState] >> 8;
+    int running = A.out[kSoloDone], state = A.out[kSetsState];
     const uint4 *held = reinterpret_cast<const uint4 *>(A.held);
     for (int i = threadIdx.x; i < A.held_words / 4; i += kSetsFormThreads) s_held[i] = held[i];
-    asm volatile("" : "+v"(running), "+v"(least));
+    asm volatile("" : "+v"(running), "+v"(state));
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(running) != kSetsRunning) return;
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int u = blockIdx.x * (kSetsFormThreads / kWave) + wave;
-    if (u < A.n_lb) sets_form<true>(A, u, lane, __builtin_amdgcn_readfirstlane(least), reinterpret_cast<const uint32_t *>(s_held));
+    state = __builtin_amdgcn_readfirstlane(state);
+    if (u < A.n_lb) sets_form<true>(A, u, lane, state >> 8 & 255, state >> 16, reinterpret_cast<const uint32_t *>(s_held));
 }
 
 __global__ __launch_bounds__(kSetsThreads) void k_sets_play(SetsArgs A)
@@ -928,13 +947,14 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets_play(SetsArgs A)
     if (tid < kMaxClasses) S.low[tid] = low;
     sets_empty(S);
     __syncthreads();
-    int played = 0, least = __builtin_amdgcn_readfirstlane(state) >> 8, strain = __builtin_amdgcn_readfirstlane(state) & 255;
-    if (sets_batch<true>(A, S, done, least, A.held, played)) return;
-    const bool go_on = sets_go_on(played, kSetsLeastMany, least, strain);
+    state = __builtin_amdgcn_readfirstlane(state);
+    int played = 0, sets = 0, jobs = state >> 16, least = state >> 8 & 255, strain = state & 255;
+    if (sets_batch<true>(A, S, done, least, A.held, played, sets, jobs)) return;
+    const bool go_on = sets_go_on(played, kSetsLeastMany, kSetsShortMany, least, strain);
     if (threadIdx.x < kMaxClasses) A.low[threadIdx.x] = S.low[threadIdx.x];
     if (threadIdx.x == 0) {
         A.out[kSoloRounds] = done + max(played, 0);
-        A.out[kSetsState] = least << 8 | strain;
+        A.out[kSetsState] = jobs << 16 | least << 8 | strain;
         if (!go_on) A.out[kSoloDone] = kSetsLeft;
     }
 }

@@ -64,6 +64,13 @@ def test_jobs_at_hand(engine, oracle, caps, groups, gaps_each, jobs):
     full_tick_check(engine, oracle, _calm(caps, groups, gaps_each, jobs, 0.05, seed=3), policies=[0, 3], resolve_modes=(0,))
 
 
+# launches in turn whose sets pass many jobs a round, by which they come to have more at hand; one launch begun in vain
+@pytest.mark.parametrize("caps,groups,gaps_each,jobs", [(43, 3, 6, 2500), (60, 2, 5, 2000), (20, 2, 20, 1500)])
+@pytest.mark.parametrize("mixed", [0.0, 0.5, 1.0])
+def test_sets_that_take_each_others_jobs(engine, oracle, caps, groups, gaps_each, jobs, mixed):
+    full_tick_check(engine, oracle, _calm(caps, groups, gaps_each, jobs, mixed, seed=5), policies=[0, 3], resolve_modes=(0,))
+
+
 @pytest.mark.parametrize("max_rounds", [41, 56, 57, 80, 119, 120, 121])
 @pytest.mark.parametrize("caps,groups,gaps_each", [(1, 1, 120), (43, 3, 2)])
 def test_caps_within_a_batch(engine, oracle, caps, groups, gaps_each, max_rounds):
