@@ -327,11 +327,13 @@ __device__ __forceinline__ bool pair_digest_is_key(unsigned long long digest)
 // order the gap's jobs are sorted anew, by all of the key.  ROOM: a power of two, at least the number of jobs.
 // 700 gaps x 2501 jobs, 700 of them each, MIXED: 60 us and 15 for k_pair_atoms, where all jobs searched and sorted by keys
 // of 128 bits took 243; 256 x 1024 from the matrix, all words sorted, 16 us where that took 26.
+// Two blocks of 1024 threads to a compute unit (that is, up to 78 scalar registers): with one, 283 blocks took two turns, 283 gaps
+// x 1542 jobs 29 us where this takes 22, a resolve of eight rounds of 1005 x 1174 111 and 89.
 constexpr int kOrderBins = 4096, kOrderBinShift = 40;
 constexpr int kOrderBinsLeast = 1024;       // room from which on a histogram pays
 static_assert(kPairsJobs <= 4096, "12 bits for a job");
 template <bool MIXED, int ROOM, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, PairReplies from, const int32_t *__restrict__ gap_w,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, PairReplies from, const int32_t *__restrict__ gap_w,
                                                          const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
                                                          const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area,
                                                          const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
