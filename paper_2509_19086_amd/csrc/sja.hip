@@ -732,7 +732,12 @@ int enqueue_starts(sja_ctx *ctx, hipStream_t st, const Layout &L)
 // A batch served pair by pair.  The gaps' lists take the space of the list entries.
 int pair_list_most(int64_t G, int64_t J) { return int(G < J ? G : J); }
 
-constexpr int64_t kPairAtomsLeast = int64_t(1) << 19;        // pairs (256 gaps x 1024 jobs are searched in 9 us)
+// Pairs, and gaps x segments, from which on the atoms are found job by job: a launch more, and shorter searches, which pays the
+// more the longer the profiles are.  A fit -> select and the resolve behind it, searched and so, us, means over batches of
+// 2^19 to 2^19.5 pairs: 22 segments a job 28.4 / 31.1 and 112 / 114, 50 29.4 / 30.9 and 218 / 219, 120 34.2 / 32.1 and
+// 140 / 138; of 2^20 to 2^21 pairs 22 segments 39.2 / 37.1 and 205 / 202, 120 51.2 / 39.1 and 203 / 189; of 2^18 pairs
+// 50 23.7 / 28.3 and 79 / 84, 300 27.2 / 30.1 and 75 / 78.
+constexpr int64_t kPairAtomsLeast = int64_t(1) << 19, kPairAtomsSegments = int64_t(1) << 25;
 
 bool pairs_batch(const sja_ctx *ctx, const Layout &L, int64_t G, int64_t J)
 {
@@ -764,7 +769,7 @@ uint16_t *pair_atoms(sja_ctx *ctx, hipStream_t st, const Layout &L, int32_t n_ga
 {
     const int J = ctx->n_jobs;
     const size_t at = align_up(L.g_ekey0 + pair_list_words(n_gaps, pair_list_most(n_gaps, J)) * 8);
-    if (int64_t(n_gaps) * J < kPairAtomsLeast || at + size_t(n_gaps) * J * 2 > L.lb_begin) return nullptr;
+    if (int64_t(n_gaps) * J < kPairAtomsLeast || int64_t(n_gaps) * ctx->n_segments < kPairAtomsSegments || at + size_t(n_gaps) * J * 2 > L.lb_begin) return nullptr;
     uint16_t *atoms = ws_ptr<uint16_t>(ctx, at);
     hipLaunchKernelGGL(k_pair_atoms, dim3((J + kAtomsJobs - 1) / kAtomsJobs, (n_gaps + kAtomsGaps - 1) / kAtomsGaps), dim3(kAtomsThreads), 0, st, n_gaps, J,
                        W, C, ctx->seg_off, ws_ptr<int2>(ctx, L.atom_dp), ws_ptr<int32_t>(ctx, L.n_atoms), atoms);
