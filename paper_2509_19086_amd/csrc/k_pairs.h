@@ -333,7 +333,7 @@ constexpr int kOrderBins = 4096, kOrderBinShift = 40;
 constexpr int kOrderBinsLeast = 1024;       // room from which on a histogram pays
 static_assert(kPairsJobs <= 4096, "12 bits for a job");
 template <bool MIXED, int ROOM, int THREADS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, PairReplies from, const int32_t *__restrict__ gap_w,
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 1024 ? 8 : 1, 8))) void k_order_pairs(int n_gaps, int n_jobs, int most, PolicyDev pol, PairReplies from, const int32_t *__restrict__ gap_w,
                                                          const int32_t *__restrict__ gap_c, const int64_t *__restrict__ seg_off,
                                                          const int2 *__restrict__ atom_dp, const long long *__restrict__ atom_area,
                                                          const int32_t *__restrict__ n_atoms, const int32_t *__restrict__ wait,
