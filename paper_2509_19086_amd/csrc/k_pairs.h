@@ -7,7 +7,7 @@
 //   * k_fit_pairs, k_best_pairs: a thread per pair finds its atom by one search
 //     on both conditions;
 //   * k_select_pairs: a thread block per gap reads the gap's row of replies;
-//   * k_order_pairs, k_rounds_lds (k_rounds_pairs): a thread block per gap puts the jobs that
+//   * k_order_pairs, k_rounds_pairs: a thread block per gap puts the jobs that
 //     fit in the order of their keys, and one block plays all rounds, a thread per gap.
 // A whole tick is five launches and one look (six after sja_fit_select with many pairs).  Gaps x jobs, 256 segments each, us a tick
 // (fairness), ordered forms and so: 8 x 16 300 / 57, 256 x 1024 547 / 91, 1024 x 512 578 / 182,
@@ -554,7 +554,6 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS
 // four jobs on the list are free in the next round: claims that others have made there already look free, too.
 // So a round is that trip, some 50 instructions and the barrier.
 // list holds `most` entries for each gap, rounded up.
-constexpr int kPairsLds = (160 << 10) - 64;     // bytes for the jobs' words and the lists, up to which these are kept in LDS
 
 // Where the rounds leave what they found, and what a grant's cut is found by.
 struct RoundsOut {
@@ -596,147 +595,10 @@ __device__ __forceinline__ void rounds_out(int n_gaps, int n_jobs, int g, int th
     out.grant_score[g] = score;
 }
 
-// A gap's row of its list in LDS, in words of 32 bits: `most` entries, four that are nobody's and four that are read and
-// not looked at; an odd number, for the banks.
-__host__ __device__ constexpr int pair_row_words(int most) { return (most + 8 + 1) / 2 | 1; }
-
-// The rounds where all lists fit LDS.  Such a round is as long as its instructions, a trip to LDS and the barrier, so
-// the next four jobs are shifted in from eight that are there: with four in hand until all are held, some lane of a
-// wave had to fetch the next ones and then their words in nearly every round, two trips more.  Of the lists the first
-// 64 entries are brought to LDS, the next 64, which are on their way, when a gap of the wave gets there: all 128 KB of
-// 256 gaps x 1024 jobs took one compute unit 18 us, and 48 rounds looked at no more than 128 of 256 entries (a trip to
-// memory when they are wanted is 5 us).  47 -> 37 us in all.
-__global__ __launch_bounds__(kPairsGaps) void k_rounds_lds(int n_gaps, int n_jobs, int most, int cap, const int32_t *__restrict__ list_len,
-                                                           const unsigned long long *__restrict__ list, RoundsOut out)
-{
-    __shared__ uint32_t s_word[kPairsLds / 4];          // per job; behind the last one's nobody's, never free, and one that always is; then the lists
-    __shared__ uint16_t s_idle[8];
-    __shared__ int s_claims, s_lost;                    // the last round in which somebody claimed; the last one had losers
-    uint32_t *const s_list = s_word + n_jobs + 2;
-    const int g = threadIdx.x, threads = blockDim.x, lane = g & (kWave - 1);
-    const int room = pair_row_words(most), words = (most + kPairsSlots - 1) / kPairsSlots;
-    const uint32_t nobody = uint32_t(n_jobs) * 4, idle = nobody + 4;
-    for (int i = g; i < n_jobs; i += threads) s_word[i] = ~0u;
-    if (g < 8) s_idle[g] = uint16_t(idle);
-    if (g == 0) { s_word[n_jobs] = 0u; s_word[n_jobs + 1] = ~1u; s_claims = s_lost = 0; }
-    const int len = g < n_gaps ? min(list_len[g], most) : 0;
-    uint16_t *const row = reinterpret_cast<uint16_t *>(&s_list[(g < n_gaps ? g : 0) * room]);
-    // the next entries of all rows of a wave, as byte offsets of the jobs' words (what lies behind a list's end is not looked at)
-    constexpr int kAhead = 16;          // words of the list
-    int loaded = 0;
-    const uint16_t *limit = nullptr;    // the eight next jobs are there up to this place
-    unsigned long long x[kAhead];       // the words behind those that are there, asked for ahead
-    auto ask = [&]() {
-#pragma unroll
-        for (int k = 0; k < kAhead; ++k) x[k] = list[size_t(min(loaded + k, words - 1)) * n_gaps + min(g, n_gaps - 1)];
-    };
-    auto load = [&]() {
-        uint32_t *const to = reinterpret_cast<uint32_t *>(row);
-        if (g < n_gaps) {
-#pragma unroll
-            for (int k = 0; k < kAhead; ++k) {
-                if (loaded + k >= words) break;
-                to[2 * (loaded + k)] = uint32_t(x[k] << 2);
-                to[2 * (loaded + k) + 1] = uint32_t((x[k] << 2) >> 32);
-            }
-        }
-        loaded += kAhead;
-        asm volatile("" ::: "memory");
-        if (g < n_gaps && len <= 4 * loaded)        // (nobody's behind the list, once all of it is there)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) row[len + k] = uint16_t(nobody);
-        asm volatile("" ::: "memory");
-        limit = loaded >= words ? row + 4 * words + 8 : row + 4 * loaded - 8;
-        if (loaded < words) ask();
-    };
-    ask();
-    load();
-    __syncthreads();
-    auto word = [&](uint32_t off) -> uint32_t & { return *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(s_word) + off); };
-    auto four = [](const uint16_t *from) { uint2 x; __builtin_memcpy(&x, from, 8); return x; };
-    const uint16_t *at = row;           // the next jobs
-    uint2 c = four(at), more;
-    uint32_t out_of_it = 0;             // all ones: the gap has its job, or none is left
-    uint32_t w[4];
-    auto fetch = [&]() {
-        w[0] = word(c.x & 0xffffu); w[1] = word(c.x >> 16); w[2] = word(c.y & 0xffffu); w[3] = word(c.y >> 16);
-        more = four(at + 4);
-    };
-    auto leave = [&]() {                // from now on it goes on with words that change nothing
-        out_of_it = ~0u;
-        at = limit = s_idle;
-        c = more = make_uint2(idle | idle << 16, idle | idle << 16);
-        w[0] = w[1] = w[2] = w[3] = ~1u;
-    };
-    fetch();
-    if (len == 0) leave();
-    int won = -1, lost_in = 0, rounds = 0, stable = 0;
-    for (int round = 1;; ++round) {
-        const uint32_t now = uint32_t(round) << 10;
-        // (a job that was passed is held, and stays so)
-        for (;;) {
-            const bool none = max(max(w[0], w[1]), max(w[2], w[3])) < now, behind = at > limit;
-            if (__builtin_expect(__ballot(none | behind) == 0, 1)) break;
-            if (__ballot(behind)) {
-                load();
-                if (out_of_it) limit = at;
-                else more = four(at + 4);
-            } else if (none) {
-                if (at + 4 >= row + len) {
-                    leave();
-                } else {
-                    at += 4;
-                    c = four(at);
-                    fetch();
-                }
-            }
-        }
-        // the first free one, and what is shifted in
-        const bool f0 = w[0] >= now, f1 = w[1] >= now, f2 = w[2] >= now, none_of_two = !(f0 | f1);
-        const uint32_t s01 = f0 ? c.x & 0xffffu : c.x >> 16, s23 = f2 ? c.y & 0xffffu : c.y >> 16;
-        const uint32_t job = none_of_two ? s23 : s01, mine = now | uint32_t(g) | out_of_it;
-        // the job of a wave's lowest gap is claimed once for all of its gaps that want it
-        const unsigned long long claims = __ballot(out_of_it == 0);
-        if (claims) {
-            const int first = __ffsll((long long)claims) - 1;
-            const uint32_t its = uint32_t(__builtin_amdgcn_readlane(int(job), first));
-            if ((out_of_it == 0) & ((job != its) | (lane == first))) atomicMin(&word(job), mine);
-            if (lane == first) s_claims = round;
-        }
-        const uint32_t step = none_of_two ? (f2 ? 3 : 4) : (f0 ? 1 : 2);
-        at += step & ~out_of_it;
-        const bool all = none_of_two & !f2;
-        const uint32_t shift = f0 | (none_of_two & f2) ? 16u : 0u;
-        const uint32_t d0 = all ? more.x : f0 ? c.x : c.y, d1 = all ? more.y : f0 ? c.y : more.x, d2 = f0 ? more.x : more.y;
-        c.x = __builtin_amdgcn_alignbit(d1, d0, shift);
-        c.y = __builtin_amdgcn_alignbit(d2, d1, shift);
-        __syncthreads();
-        uint32_t outcome = word(job);
-        fetch();
-        int claimed = s_claims;
-        asm volatile("" : "+v"(outcome), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(more.x), "+v"(more.y), "+v"(claimed));
-        claimed = __builtin_amdgcn_readfirstlane(claimed);
-        if (__builtin_expect((claimed < round) | (round == cap), 0)) {
-            // nobody is left that could claim anything, or it is to end: were there losers in the last round played?
-            const bool open = out_of_it == 0;
-            const bool lost = claimed < round ? round > 1 && lost_in == round - 1 : open && outcome != mine;
-            if (claimed >= round && open && !lost) won = int(job >> 2);
-            if (lost) s_lost = 1;
-            __syncthreads();
-            rounds = claimed >= round || round == 1 || s_lost ? round : round - 1;
-            stable = claimed < round || !s_lost;
-            break;
-        }
-        if (outcome == mine) {
-            won = int(job >> 2);
-            leave();
-        }
-        lost_in = out_of_it == 0 ? round : lost_in;
-    }
-    rounds_out(n_gaps, n_jobs, g, threads, won, rounds, stable, s_word, out);
-}
-
-// The rounds of larger lists, from global memory: a thread reads 16 entries ahead.
+// A thread reads 16 entries of its list ahead, from memory.  With the lists in LDS (64 entries at a time, the next four jobs
+// shifted in from eight) a round was no shorter: 330 resolves of up to 1024 gaps took 1.6 % longer on average, 0.86 to 1.06
+// times as long this way, the most where all gaps pass the same jobs (263 gaps x 657 jobs of one capacity, 81 rounds:
+// 83 us so and 71) or fill more than four waves; 256 x 1024 the same.
 __global__ __launch_bounds__(kPairsGaps) void k_rounds_pairs(int n_gaps, int n_jobs, int most, int cap, const int32_t *__restrict__ list_len,
                                                              const unsigned long long *__restrict__ list, RoundsOut out)
 {

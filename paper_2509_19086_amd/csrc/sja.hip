@@ -816,8 +816,7 @@ int resolve_pairs(sja_ctx *ctx, hipStream_t st, const Layout &L, const sja_param
     SJA_HIP(hipGetLastError(), "k_order_pairs launch");
     const RoundsOut out{pol, gap_w, gap_c, ctx->seg_off, n_atoms, atom_dp, atom_db, area, wait, sla_class, grant_job, grant_cut, grant_score, job_gap,
                         rounds_and_stable};
-    auto kern = J + 2 + int64_t(G) * pair_row_words(most) <= kPairsLds / 4 ? k_rounds_lds : k_rounds_pairs;
-    hipLaunchKernelGGL(kern, dim3(1), dim3((G + kWave - 1) / kWave * kWave), 0, st, G, J, most, cap, len, list, out);
+    hipLaunchKernelGGL(k_rounds_pairs, dim3(1), dim3((G + kWave - 1) / kWave * kWave), 0, st, G, J, most, cap, len, list, out);
     SJA_HIP(hipGetLastError(), "k_rounds_pairs launch");
     SJA_HIP(hipStreamSynchronize(st), "final synchronise");
     return SJA_OK;

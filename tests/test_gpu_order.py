@@ -90,8 +90,8 @@ def test_scores_at_the_digests_edges(engine, oracle, gaps, jobs, e):
     check(engine, oracle, wl, (0, 1, 3))
 
 
-# one list for all gaps, so that every round passes an entry of each: one, two and more times the 64 that are brought to LDS
-# together, up to all of it, lists that fit LDS and lists that do not
+# one list for all gaps, so that every round passes an entry of each: less than the 16 that are read ahead, one, two and many
+# times 16 and 64 of them
 @pytest.mark.parametrize("gaps,jobs", [(1, 5), (63, 64), (65, 65), (72, 300), (128, 127), (136, 700), (256, 1024), (257, 1024), (333, 90), (1000, 70), (1024, 64)])
 @pytest.mark.parametrize("max_rounds", [0, 60])
 def test_rounds_along_one_list(engine, oracle, gaps, jobs, max_rounds):

@@ -1,5 +1,5 @@
 """Small batches, served pair by pair (k_pairs.h): the smallest and the largest of its range and sizes just beyond,
-edges of waves, bit words and sort lengths, lists in LDS and not, bounded rounds, equal keys, masks, and the ordered
+edges of waves, bit words and sort lengths, bounded rounds, equal keys, masks, and the ordered
 forms on the same batches (mode 2 plans them after all), against the oracle."""
 import numpy as np
 import pytest
