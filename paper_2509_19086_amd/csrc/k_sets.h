@@ -52,8 +52,10 @@ namespace sja {
 constexpr int kSetsWaves = 16, kSetsThreads = kSetsWaves * kWave;
 constexpr int kSetsMaxBlocks = 768;     // list blocks
 static_assert(kSetsMaxBlocks <= kPlacedBlocks, "a place is a list block and a lane");
-// and up to which one thread block does it all: 66 of them 910 us a tick of 2048 gaps x 8192 jobs in one launch, 1030 in
-// turn; 118 as fast in either (two launches cost 10 us a batch, searching the lists by one block 8 to 30)
+// and up to which one thread block does it all, and begins early (k_solo.h).  With the line at 40 and at 60, resolves of 41
+// to 80 list blocks took 1.0 to 1.47 times as long, 1.2 on average (107 of random sizes, profiles, capacities), those
+// of up to 40 the same.  With 104 and 128, those of 81 to 128 took 0.74 to 1.32 times as long, 0.88 on average (126 of
+// them): the longer ones are those of many sets.
 constexpr int kSetsOneBlocks = 80;
 constexpr int kSetsPieces = 6;          // pieces of a list block, at most
 constexpr int kSetsMost = 256;          // sets, at most

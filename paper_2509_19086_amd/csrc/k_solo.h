@@ -53,8 +53,9 @@ constexpr int kSoloStart = 3;           // effort per wave of the last launched 
 constexpr int kSoloStartFew = 16;       // with few list blocks, whose start and whose rounds in pieces cost little
 enum { kSoloDone = 0, kSoloRounds = 1, kSoloStable = 2 };
 // Rounds are calm if few pieces were served in the last ones of them (two to the power of the shift).  Where one launch
-// plays them from there on (k_sets_one) it is worth to begin early, and to begin in vain: 2048 gaps x 8192 jobs 905 us a tick
-// by the first line, 810 by the second; 118 list blocks, with launches in turn, 5.48 ms by the first, 6.1 with 512 pieces.
+// plays them from there on (k_sets_one) it is worth to begin early, and to end after one batch if that was in vain: 2048 gaps x
+// 8192 jobs 905 us a tick by the first line, 810 by the second; 118 list blocks, with launches in turn, 5.48 ms by the
+// first, 6.1 with 512 pieces, and 5.26 and 5.71 by the two lines since the sets have more jobs at hand.
 constexpr int kSoloCalmShift = 5, kSoloCalmPieces = 128;
 constexpr int kSoloCalmShiftFew = 3, kSoloCalmPiecesFew = 8;
 enum { kSoloHandedBack = 0, kSoloEnded = 1, kSoloPutOff = 2, kSoloCalm = 3 };      // what out[kSoloDone] says
