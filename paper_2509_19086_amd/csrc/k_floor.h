@@ -13,7 +13,7 @@
 //   * k_floor_ties: who has that key, under MIXED with the largest F; k_floor_reduce: the running maximum.
 // What is left is reading all atoms once and those of every fourth job twice, bound by some fifty instructions for an
 // atom (filter, 32768 gaps x 65536 jobs of 130 atoms: 56 us; with keys of 64 bits throughout, 83), and 40 us of short
-// kernels.  At that size fit -> select takes 170 us where k_range_select takes 398, at 8192 x 32768 a select 66 us where
+// kernels.  At that size fit -> select takes 175 us where k_range_select takes 398, at 8192 x 32768 a select 66 us where
 // reading the matrix takes 320.  sja.hip says where the line lies (by_floor).
 #pragma once
 
@@ -74,14 +74,11 @@ __device__ __forceinline__ FloorBuckets floor_buckets(int n_classes, int low, in
 {
     low = max(low, 1);
     longest = max(longest, low);
-    // (a lane for each: one after the other they took a microsecond of every one of these kernels)
-    constexpr int kMostBits = 12;
-    const int lane = threadIdx.x & (kWave - 1), mine = max(kMostBits - lane, 0);
-    const int n_mine = bucket_of(longest, mine) - bucket_of(low, mine) + 2;
-    const unsigned long long fits = __ballot(lane <= kMostBits && int64_t(n_mine) * n_classes <= room);
-    if (!fits) return {0, 0, 0, 1};
-    const int first = __ffsll((long long)fits) - 1, bits = kMostBits - first;
-    return {bits, __builtin_amdgcn_readlane(n_mine, first), bucket_of(low, bits), low};
+    for (int bits = 12; bits >= 0; --bits) {
+        const int base = bucket_of(low, bits), n = bucket_of(longest, bits) - base + 2;
+        if (int64_t(n) * n_classes <= room) return {bits, n, base, low};
+    }
+    return {0, 0, 0, 1};
 }
 
 // What the kernels share: the tables of the plan, and where the intermediate results are.
