@@ -362,6 +362,7 @@ struct SetsShared {
     int8_t pieces[BLOCKS];
     uint16_t lo[kSetsMost], hi[kSetsMost], source[kSetsMost], cls[kSetsMost];    // first and last place of a set, the piece whose jobs it has, its class
     uint32_t set[kSetsMost];                            // jobs at hand, bit 16: no more jobs
+    uint8_t dry[kSetsMost];                             // the round of the batch in which it found no job left, 0: none
     int most, through;                                  // jobs that a set has at hand at most; one that had so many has passed them all
     int first[kMaxClasses + 1], gaps_at[kMaxClasses + 1];       // first list block of a class, its first position,
     int low[kMaxClasses];                               // and where its lowest open gap lies among its gaps
@@ -463,9 +464,9 @@ constexpr SetsShape sets_shape(int n_sets)
     if (n_sets <= 2 * kWave) return {138, 126, 128, 47};
     return {70, 58, kSetsMost, 23};
 }
-// (every round passes a job of each set: a batch ends by its jobs before it ends by its bound, and a round fits a claim's word)
+// (every round passes a job of each set: a batch ends by its jobs before it ends by its bound, and a round fits a claim's word and a byte)
 static_assert(sets_shape(1).most < kSetsMostRounds && sets_shape(17).most < kSetsMostRounds && sets_shape(33).most < kSetsMostRounds &&
-              sets_shape(kWave + 1).most < kSetsMostRounds && sets_shape(kSetsMost).most < kSetsMostRounds && kSetsMostRounds + 1 < 1 << 12, "rounds of a batch");
+              sets_shape(kWave + 1).most < kSetsMostRounds && sets_shape(kSetsMost).most < kSetsMostRounds && kSetsMostRounds + 1 < 1 << 8, "rounds of a batch");
 static_assert(kWave * 262 <= kSetsSeq && 2 * kWave * 138 <= kSetsSeq && kSetsMost * 70 <= kSetsSeq, "jobs at hand");
 // (behind the last gap a word that says whether there are more, and one that is read and not looked at)
 static_assert((253 + 2) * 16 <= kSetsHeads + kSetsMost && (191 + 2) * 32 <= kSetsHeads + kSetsMost && (95 + 2) * 64 <= kSetsHeads + kSetsMost &&
@@ -608,6 +609,7 @@ __device__ __forceinline__ void sets_fill(const SetsArgs &A, SetsShared<BLOCKS> 
     if (lane == 0) {
         S.head[id + min(gaps, H) * shape.width] = all_gaps ? kSetsServed : kSetsMoreGaps;
         S.set[id] = uint32_t(jobs) | uint32_t(last) << 16;
+        S.dry[id] = 0;
     }
 }
 
@@ -713,7 +715,10 @@ __device__ __forceinline__ void sets_play(SetsShared<BLOCKS> &S, int lane, int n
             if (__ballot(dry)) S.closed = q;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                if (none[i]) leave(i);
+                if (none[i]) {
+                    S.dry[lane + i * kWave] = uint8_t(q);
+                    leave(i);
+                }
                 some |= out[i] == 0;
             }
             if (!__ballot(some)) { why = kSetsNoClaim; break; }       // nobody claims anything in round q
@@ -827,6 +832,18 @@ __device__ __forceinline__ bool sets_batch(const SetsArgs &A, SetsShared<BLOCKS>
             atomicAnd(&S.open[place >> 6], ~(1ull << (place & 63)));
         }
         sets_clear(S.jobs, k);
+    }
+    // the gaps of a set that found no job left in one of these rounds are done with: found again by the next batch they
+    // would count for a round of that
+    for (int id = wave; id < n_sets && !over; id += kSetsWaves) {
+        const int dry = S.dry[id], lo = S.lo[id], hi = S.hi[id];
+        if (dry == 0 || dry > played) continue;
+        for (int u = (lo >> 6) + lane; u <= hi >> 6; u += kWave) {
+            unsigned long long gone = ~0ull;
+            if (u == lo >> 6) gone &= ~0ull << (lo & 63);
+            if (u == hi >> 6) gone &= ~0ull >> (63 - (hi & 63));
+            atomicAnd(&S.open[u], ~gone);
+        }
     }
     __syncthreads();
     for (int u = tid; u < A.n_lb; u += kSetsThreads) A.block[u].open = S.open[u];

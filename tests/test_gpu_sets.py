@@ -71,6 +71,31 @@ def test_sets_that_take_each_others_jobs(engine, oracle, caps, groups, gaps_each
     full_tick_check(engine, oracle, _calm(caps, groups, gaps_each, jobs, mixed, seed=5), policies=[0, 3], resolve_modes=(0,))
 
 
+def _runs_dry(long_gaps, short_gaps, long_jobs, short_jobs):
+    """Gaps with long windows, and behind them gaps with short ones; jobs for either.  The short jobs run out in the middle of
+    a batch of rounds; then the last long gap is served, at which the batch pauses (the class's further gaps are far away)."""
+    rng = np.random.default_rng(long_gaps)
+    wl = make_workload("tiny", 0, n_gaps=8, n_jobs=8)
+    wl.n_gaps, wl.n_jobs = long_gaps + short_gaps, long_jobs + short_jobs
+    wl.W = np.repeat([100000, 100], [long_gaps, short_gaps]).astype(np.int32)
+    wl.C = np.full(wl.n_gaps, 40960, dtype=np.int32)
+    wl.dur = rng.permutation(np.concatenate([50000 + rng.permutation(long_jobs), 10 + rng.permutation(short_jobs) % 90])).astype(np.int32)
+    wl.mem = rng.integers(20000, 20100, size=wl.n_jobs).astype(np.int32)
+    wl.seg_off = np.arange(wl.n_jobs + 1, dtype=np.int64)
+    wl.safe, wl.progress = np.ones(wl.n_jobs, dtype=np.uint8), np.zeros(wl.n_jobs, dtype=np.int32)
+    wl.wait = rng.integers(0, 50, size=wl.n_jobs).astype(np.int32)
+    wl.sla_class = np.zeros(wl.n_jobs, dtype=np.uint8)
+    wl.max_rounds = 0
+    return wl
+
+
+# a set that found no job left in one batch does not count for a round of the next; one launch, and launches in turn
+@pytest.mark.parametrize("long_gaps,short_gaps,long_jobs,short_jobs", [(160, 1300, 300, 90), (200, 1500, 260, 70), (150, 2000, 149, 80),
+                                                                       (200, 7000, 400, 110), (250, 6500, 260, 90)])
+def test_jobs_run_out_for_some(engine, oracle, long_gaps, short_gaps, long_jobs, short_jobs):
+    full_tick_check(engine, oracle, _runs_dry(long_gaps, short_gaps, long_jobs, short_jobs), policies=[0, 1], resolve_modes=(0,))
+
+
 @pytest.mark.parametrize("max_rounds", [41, 56, 57, 80, 119, 120, 121])
 @pytest.mark.parametrize("caps,groups,gaps_each", [(1, 1, 120), (43, 3, 2)])
 def test_caps_within_a_batch(engine, oracle, caps, groups, gaps_each, max_rounds):
