@@ -13,7 +13,7 @@
 //   * k_floor_ties: who has that key, under MIXED with the largest F; k_floor_reduce: the running maximum.
 // What is left is reading all atoms once and those of every fourth job twice, bound by some fifty instructions for an
 // atom (filter, 32768 gaps x 65536 jobs of 130 atoms: 56 us; with keys of 64 bits throughout, 83), and 40 us of short
-// kernels.  At that size fit -> select takes 175 us where k_range_select takes 398, at 8192 x 32768 a select 66 us where
+// kernels.  At that size fit -> select takes 171 us where k_range_select takes 398, at 8192 x 32768 a select 66 us where
 // reading the matrix takes 320.  sja.hip says where the line lies (by_floor).
 #pragma once
 
